@@ -29,7 +29,7 @@ bool desc_ok(const rmm_layer_desc_t *d) {
            dims_ok(d->k, d->d_in) && dims_ok(d->k, d->d_out) && dims_ok(d->n, d->k);
 }
 
-// The plain kernels put the row tile index in gridDim.y.
+// (kept from when the plain kernels put the row tile index in gridDim.y: the documented refusal stays)
 bool grid_ok(int64_t rows) { return (rows + 63) / 64 <= 65535; }
 
 bool use_mfma(const rmm_layer_desc_t *d) {
@@ -132,14 +132,18 @@ int sketch_impl(int64_t n, int64_t d, int64_t k, int kind, SketchState st, const
         return from_hip(launch_sketch_bf16((const bf16_t *)A, (bf16_t *)out, n, d, k, kind, st, ws, stream,
                                            timed ? ev.begin : nullptr, timed ? ev.end : nullptr, d_other));
     StageScope scope(ev, product_stage, stream);  // the plain path is one kernel
-    const float alpha = 1.0f / sqrtf((float)k);
-    return from_hip(launch_sketch_plain<T, T>((const T *)A, (T *)out, n, d, k, kind, st, alpha, stream));
+    return from_hip(launch_forward_plain<T>((const T *)A, nullptr, nullptr, nullptr, (T *)out, n, d, d, k, kind, st, stream));
 }
 
 template <typename T>
 int forward_impl(const rmm_layer_desc_t *d, SketchState st, const void *X, const void *W, const void *bias, void *Y,
                  void *X_proj, void *ws, hipStream_t stream, const StageEvents &ev) {
     const bool mfma = use_mfma(d);
+    if (!mfma && X_proj != nullptr && !separate_stage(ev.stage)) {  // both products in one launch
+        StageScope scope(ev, RMM_STAGE_FWD_PAIR, stream);
+        return from_hip(launch_forward_plain<T>((const T *)X, (const T *)W, (const T *)bias, (T *)Y, (T *)X_proj, d->n,
+                                                d->d_in, d->d_out, d->k, d->kind, st, stream));
+    }
     if (X_proj != nullptr && sliced_sketch(d) && !separate_stage(ev.stage) &&
         forward_pair_available(d->n, d->d_in, d->d_out, d->k)) {
         const bool timed = ev.stage == RMM_STAGE_FWD_PAIR;
@@ -154,13 +158,13 @@ int forward_impl(const rmm_layer_desc_t *d, SketchState st, const void *X, const
                                                       (bf16_t *)X_proj, d->n, d->d_in, d->d_out, d->k, st, stream,
                                                       timed ? ev.begin : nullptr, timed ? ev.end : nullptr));
     }
-    {   // Y = X W^T (+ bias): A = X (n x d_in), B(kk, c) = W[c][kk].
+    {   // Y = X W^T (+ bias)
         StageScope scope(ev, RMM_STAGE_FWD_Y, stream);
         hipError_t e =
             mfma ? launch_linear_nt_bf16((const bf16_t *)X, (const bf16_t *)W, (const bf16_t *)bias, (bf16_t *)Y,
                                          d->n, d->d_in, d->d_out, stream)
-                 : launch_gemm_plain<T, T>((const T *)X, d->d_in, 1, (const T *)W, 1, d->d_in, (T *)Y, d->d_out,
-                                           (const T *)bias, d->n, d->d_out, d->d_in, 1.0f, stream);
+                 : launch_forward_plain<T>((const T *)X, (const T *)W, (const T *)bias, (T *)Y, nullptr, d->n, d->d_in,
+                                           d->d_out, d->k, d->kind, st, stream);
         if (e != hipSuccess) return RMM_ERR_LAUNCH;
     }
     if (X_proj == nullptr) return RMM_OK;  // no backward pass will follow: nothing to keep
@@ -184,11 +188,18 @@ int backward_impl(const rmm_layer_desc_t *d, SketchState st, const void *dY, con
                                            d->d_out, d->k, st, stream, timed ? ev.begin : nullptr, timed ? ev.end : nullptr);
         if (e != hipSuccess) return RMM_ERR_LAUNCH;
     }
-    const bool paired = paired_sors || (sliced_sketch(d) && dX != nullptr && !separate_stage(ev.stage) &&
+    const bool paired_plain = !mfma && !separate_stage(ev.stage);
+    if (paired_plain) {  // dX, G and db in one launch
+        StageScope scope(ev, RMM_STAGE_BWD_PAIR, stream);
+        e = launch_backward_plain<T>((const T *)dY, (const T *)W, (T *)dX, G, ev.stage == RMM_STAGE_BWD_DBIAS ? nullptr : (T *)dbias,
+                                     d->n, d->d_in, d->d_out, d->k, d->kind, st, accumulate, stream);
+        if (e != hipSuccess) return RMM_ERR_LAUNCH;
+    }
+    const bool paired = paired_plain || paired_sors || (sliced_sketch(d) && dX != nullptr && !separate_stage(ev.stage) &&
                                         backward_pair_available(d->n, d->d_in, d->d_out, d->k));
     const bool own_db_stage = ev.stage == RMM_STAGE_BWD_DW || ev.stage == RMM_STAGE_BWD_DBIAS;
-    bool db_done = false;
-    if (paired && !paired_sors) {
+    bool db_done = paired_plain && ev.stage != RMM_STAGE_BWD_DBIAS;
+    if (paired && !paired_sors && !paired_plain) {
         const bool timed = ev.stage == RMM_STAGE_BWD_PAIR;
         db_done = dbias != nullptr && !own_db_stage && backward_pair_takes_colsum(d->n, d->d_in, d->d_out, d->k);
         e = launch_backward_pair_bf16((const bf16_t *)dY, (const bf16_t *)W, (bf16_t *)dX, (bf16_t *)G, d->n, d->d_in,
@@ -201,8 +212,8 @@ int backward_impl(const rmm_layer_desc_t *d, SketchState st, const void *dY, con
         StageScope scope(ev, RMM_STAGE_BWD_DX, stream);
         e = mfma ? launch_linear_nn_bf16((const bf16_t *)dY, (const bf16_t *)W, (bf16_t *)dX, d->n, d->d_in, d->d_out,
                                          stream)
-                 : launch_gemm_plain<T, T>((const T *)dY, d->d_out, 1, (const T *)W, d->d_in, 1, (T *)dX, d->d_in,
-                                           (const T *)nullptr, d->n, d->d_in, d->d_out, 1.0f, stream);
+                 : launch_backward_plain<T>((const T *)dY, (const T *)W, (T *)dX, nullptr, nullptr, d->n, d->d_in,
+                                            d->d_out, d->k, d->kind, st, false, stream);
         if (e != hipSuccess) return RMM_ERR_LAUNCH;
     }
     if (!paired) {
@@ -221,8 +232,7 @@ int backward_impl(const rmm_layer_desc_t *d, SketchState st, const void *dY, con
         StageScope scope(ev, RMM_STAGE_BWD_DW, stream);
         e = mfma ? launch_dw_bf16((const bf16_t *)G, (const bf16_t *)X_proj, (bf16_t *)dW, d->k, d->d_in, d->d_out,
                                   stream, accumulate)
-                 : launch_gemm_plain<T, T>(G, 1, d->d_out, (const T *)X_proj, d->d_in, 1, (T *)dW, d->d_in,
-                                           (const T *)nullptr, d->d_out, d->d_in, d->k, 1.0f, stream, accumulate);
+                 : launch_tn_plain<T, T>(G, (const T *)X_proj, (T *)dW, d->d_out, d->d_in, d->k, stream, accumulate);
         if (e != hipSuccess) return RMM_ERR_LAUNCH;
     }
     if (dbias != nullptr && !db_done) {
@@ -266,7 +276,8 @@ size_t rmm_workspace_bytes(const rmm_layer_desc_t *desc, int op) {
 }
 
 int rmm_uses_paired_launch(const rmm_layer_desc_t *desc, int op) {
-    if (!desc_ok(desc) || !use_mfma(desc)) return 0;
+    if (!desc_ok(desc) || (op != RMM_OP_FORWARD && op != RMM_OP_BACKWARD)) return 0;
+    if (!use_mfma(desc)) return 1;
     if (desc->kind == RMM_SKETCH_SORS) {
         if (op == RMM_OP_FORWARD) return sors_pair_available(desc->n, desc->d_in, desc->d_out, desc->k) ? 1 : 0;
         if (op == RMM_OP_BACKWARD) return sors_pair_available(desc->n, desc->d_out, desc->d_in, desc->k) ? 1 : 0;
@@ -406,18 +417,14 @@ int rmm_variance_stats(const rmm_layer_desc_t *desc, const void *X, const void *
             e = launch_xty_sumsq_bf16((const bf16_t *)X, (const bf16_t *)dY, xty, desc->n, desc->d_in, desc->d_out, s);
         } else {
             float *P = (float *)((char *)ws + var_partial_bytes(desc));  // P(i, j) = sum_t X[t][i] dY[t][j]
-            e = launch_gemm_plain<bf16_t, float>((const bf16_t *)X, 1, desc->d_in, (const bf16_t *)dY, desc->d_out, 1, P,
-                                                 desc->d_out, (const bf16_t *)nullptr, desc->d_in, desc->d_out,
-                                                 desc->n, 1.0f, s);
+            e = launch_tn_plain<bf16_t, float>((const bf16_t *)X, (const bf16_t *)dY, P, desc->d_in, desc->d_out, desc->n, s);
             if (e == hipSuccess) e = launch_sumsq(P, desc->d_in * desc->d_out, xty, s);
         }
     } else {
         e = launch_row_norms<float>((const float *)X, (const float *)dY, desc->n, desc->d_in, desc->d_out, rows, s);
         if (e != hipSuccess) return RMM_ERR_LAUNCH;
         float *P = (float *)((char *)ws + var_partial_bytes(desc));
-        e = launch_gemm_plain<float, float>((const float *)X, 1, desc->d_in, (const float *)dY, desc->d_out, 1, P,
-                                            desc->d_out, (const float *)nullptr, desc->d_in, desc->d_out, desc->n,
-                                            1.0f, s);
+        e = launch_tn_plain<float, float>((const float *)X, (const float *)dY, P, desc->d_in, desc->d_out, desc->n, s);
         if (e == hipSuccess) e = launch_sumsq(P, desc->d_in * desc->d_out, xty, s);
     }
     if (e != hipSuccess) return RMM_ERR_LAUNCH;

@@ -20,7 +20,7 @@ struct ColsumArgs {
     void *out;      // d
     int64_t n, d;
     int accumulate;
-    int lpr;        // 16-byte pieces of a row per work-group: 4 or 1 (colsum_lpr)
+    int lpr;        // 16-byte pieces of a row per work-group: 4 or 1 (colsum_lpr); 0: element by element
 };
 
 // 16-byte pieces per row and work-group: four where that still gives 96 work-groups, else one
@@ -33,6 +33,7 @@ inline int64_t colsum_blocks(int64_t d, int64_t elem_bytes) {
 inline bool colsum_wide_ok(const void *A, int64_t d, int64_t elem_bytes) {  // 16-byte loads apply
     return (d * elem_bytes) % 16 == 0 && (reinterpret_cast<uintptr_t>(A) & 15u) == 0;
 }
+inline int64_t colsum_narrow_blocks(int64_t d) { return (d + 15) / 16; }
 constexpr int kColsumLdsFloats = 256 * 9;  // 256 row groups x (8 columns + 1), the larger of the two forms
 
 // `lds` holds kColsumLdsFloats floats; block `blk` of `blocks`.
@@ -85,6 +86,45 @@ __device__ __forceinline__ void colsum_body(const ColsumArgs &g, float *lds, int
         if (g.accumulate) s += load_f32<T>(out + col);
         store_f32<T>(out + col, s);
     }
+}
+
+// The same for widths that rule out 16-byte loads: 16 columns per work-group, 16 row
+// lanes per column with eight loads in flight each (latency bounds a thread's chain of loads: 64
+// columns and 4 row lanes without the unrolling took 75 us at 3000 x 1001).
+template <typename T>
+__device__ __forceinline__ void colsum_narrow_body(const ColsumArgs &g, float *lds, int64_t blk) {
+    constexpr int U = 8;
+    const T *A = reinterpret_cast<const T *>(g.A);
+    T *out = reinterpret_cast<T *>(g.out);
+    const int cl = threadIdx.x & 15, rl = threadIdx.x >> 4;
+    const int64_t c = blk * 16 + cl;
+    float s = 0.0f;
+    if (rl < 16 && c < g.d) {
+        for (int64_t r = rl; r < g.n; r += 16 * U) {
+            float v[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) v[u] = r + 16 * u < g.n ? load_f32<T>(A + (r + 16 * u) * g.d + c) : 0.0f;
+#pragma unroll
+            for (int u = 0; u < U; ++u) s += v[u];
+        }
+    }
+    if (rl < 16) lds[rl * 17 + cl] = s;
+    __syncthreads();
+    if (rl == 0 && c < g.d) {
+        float t = 0.0f;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) t += lds[r * 17 + cl];
+        if (g.accumulate) t += load_f32<T>(out + c);
+        store_f32<T>(out + c, t);
+    }
+}
+
+template <typename T>
+__device__ __forceinline__ void colsum_any_body(const ColsumArgs &g, float *lds, int64_t blk, int64_t blocks) {
+    if (g.lpr == 0)
+        colsum_narrow_body<T>(g, lds, blk);
+    else
+        colsum_body<T>(g, lds, blk, blocks);
 }
 
 }  // namespace rmm

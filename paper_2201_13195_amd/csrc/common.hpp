@@ -37,17 +37,20 @@ __device__ __forceinline__ void store_f32<bf16_t>(bf16_t *p, float v) { *p = f32
 // Host launchers (each returns the hipError_t of its launches).
 // ---------------------------------------------------------------------------
 
-// Plain LDS-tiled fp32-FMA kernels: the fp32 data path, and a slow bf16 one.
-//   C[m x n] = alpha * A * B (+ bias[n] per row) (+ the old C if `accumulate`), A(m,kk) at
-//   A[m*sam + kk*sak], B(kk,n) at B[kk*sbk + n*sbn], C row-major with leading dimension ldc.
+// fp32-matrix kernels (plain.hip): the fp32 data path, and the bf16 shapes the bf16 MFMA path does
+// not take.  One launch per call:
+//   Y = X W^T (+ bias) and X_proj = S^T X; either output may be null
+template <typename T>
+hipError_t launch_forward_plain(const T *X, const T *W, const T *bias, T *Y, T *X_proj, int64_t n, int64_t d_in,
+                                int64_t d_out, int64_t k, int kind, SketchState st, hipStream_t stream);
+//   dX = dY W, G = S^T dY and dbias = dY^T 1 (+ the old dbias); any output may be null
+template <typename T>
+hipError_t launch_backward_plain(const T *dY, const T *W, T *dX, T *G, T *dbias, int64_t n, int64_t d_in, int64_t d_out,
+                                 int64_t k, int kind, SketchState st, bool accumulate_dbias, hipStream_t stream);
+//   C[m x n] = A^T B (+ the old C if `accumulate`), A[kk x m], B[kk x n]
 template <typename Tin, typename Tout>
-hipError_t launch_gemm_plain(const Tin *A, int64_t sam, int64_t sak, const Tin *B, int64_t sbk, int64_t sbn,
-                             Tout *C, int64_t ldc, const Tin *bias, int64_t m, int64_t n, int64_t kk, float alpha,
-                             hipStream_t stream, bool accumulate = false);
-//   out[k x d] = alpha * P^T A with P the unscaled sketch (n x k) of `st`.
-template <typename Tin, typename Tout>
-hipError_t launch_sketch_plain(const Tin *A, Tout *out, int64_t n, int64_t d, int64_t k, int kind, SketchState st,
-                               float alpha, hipStream_t stream);
+hipError_t launch_tn_plain(const Tin *A, const Tin *B, Tout *C, int64_t m, int64_t n, int64_t kk, hipStream_t stream,
+                           bool accumulate = false);
 //   out[d] = column sums of A[n x d] (+ the old out if `accumulate`).
 template <typename T>
 hipError_t launch_colsum(const T *A, T *out, int64_t n, int64_t d, hipStream_t stream, bool accumulate = false);

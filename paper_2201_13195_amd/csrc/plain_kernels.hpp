@@ -1,0 +1,465 @@
+// Tiled products for the fp32 data path of the layer, and for the bf16 shapes that the bf16 kernels
+// (mfma_kernels.hpp) do not take:
+//
+//   C[M x N] = alpha * A B (+ bias) (+ old C),   A in memory either way round or P^T generated on
+//   chip, B in memory either way round, accumulation in fp32.
+//
+// An fp32 number is the exact sum of three bf16 numbers (24 significant bits = 3 x 8: round to
+// nearest, subtract, round, subtract; the last rest fits), so an fp32 product runs on the bf16 matrix
+// pipes: the operand tiles are split on their way into LDS (three planes) and a 32x32x16 block is the
+// sum of eight bf16 MFMAs, every pair of planes but the last with the last, whose share is below 2^-32
+// of a product.  Each plane product is exact in fp32, so what rounds is the fp32 accumulation, as with
+// an fp32 multiply-add.  Operands that are bf16 already, and the +-1 entries of the Rademacher and
+// SORS sketches, are one plane.
+//
+// Why not v_mfma_f32_32x32x2_f32: it runs on the vector units' fp32 multipliers (measured on this
+// chip: 72 cycles plus 4 for every vector instruction beside it), 576 cycles for the block that takes
+// 8 x 32 here, and address arithmetic, splitting and the sketch generator would add to that instead of
+// running beside it.
+#pragma once
+#include <type_traits>
+
+#include "colsum.hpp"
+#include "mfma_frag.hpp"
+
+namespace rmm {
+
+enum { PA_K = 0, PA_M = 1, PA_GAUSS = 2, PA_SIGN = 3 };  // A[m][kk] / A[kk][m] / P^T(m, kk) generated: Gaussian / +-1 entries
+enum { PB_K = 0, PB_N = 1 };                             // B[n][kk] / B[kk][n]
+
+struct PlainArgs {
+    const void *A;
+    int64_t lda;
+    const void *B;
+    int64_t ldb;
+    void *C;
+    int64_t ldc;
+    const void *bias;
+    int64_t M, N, K;
+    float alpha;
+    int accumulate;
+    int kind;  // sketch operand only
+    SketchState st;
+};
+
+namespace {
+
+// BM x BN outputs, BK contraction elements per LDS tile, WM x WN waves over the tile, WK waves that
+// take a share of each tile's contraction; always eight waves, two per SIMD, so that one wave's
+// splitting, LDS traffic and generator work run beside the other's MFMAs.
+constexpr int kPlainThreads = 512;
+template <int BM_, int BN_, int BK_, int WM_, int WN_, int WK_>
+struct PlainShape {
+    static constexpr int BM = BM_, BN = BN_, BK = BK_, WM = WM_, WN = WN_, WK = WK_;
+    static_assert(64 * WM * WN * WK == kPlainThreads, "eight waves");
+};
+typedef PlainShape<128, 128, 32, 2, 4, 1> PlainBig;    // most flops per byte
+typedef PlainShape<64, 64, 64, 2, 2, 2> PlainMid;      // four times as many tiles
+typedef PlainShape<32, 32, 128, 1, 1, 8> PlainTiny;    // few tiles: short chains, each wave an eighth of the contraction
+typedef PlainShape<32, 128, 64, 1, 4, 2> PlainSketch;  // sketch products: an entry is generated once per 128 columns
+
+// How operands are loaded: 4 = 16-byte buffer loads (fp32, every row on 16 bytes); 3 = the same for rows
+// that start anywhere (fp32 or bf16); both with 32-bit offsets inside a tile (rows below 2^22 elements).
+// 0 = element loads from 64-bit addresses, for longer rows.
+template <typename T>
+constexpr int plain_planes() { return sizeof(T) == 4 ? 3 : 1; }
+
+template <typename T, typename S, int AMODE, int BMODE>
+struct PlainTile {
+    static constexpr bool A_KROWS = AMODE != PA_M, B_KROWS = BMODE == PB_K;  // LDS tile [row][contraction] or [contraction][row]
+    static constexpr int PA = AMODE == PA_GAUSS ? 3 : AMODE == PA_SIGN ? 1 : plain_planes<T>(), PB = plain_planes<T>();
+    // (rows of 64 or 192 bytes modulo 256 keep the transposing reads off each other's banks)
+    static constexpr int SA = A_KROWS ? S::BK : S::BM % 64 == 0 ? S::BM + TPAD : S::BM;
+    static constexpr int SB = B_KROWS ? S::BK : S::BN % 64 == 0 ? S::BN + TPAD : S::BN;
+    static constexpr int A_PLANE = (A_KROWS ? S::BM : S::BK) * SA, B_PLANE = (B_KROWS ? S::BN : S::BK) * SB;
+    static constexpr int STAGE = PA * A_PLANE + PB * B_PLANE;  // bf16 elements
+    static constexpr int RED_BYTES = S::WK > 1 ? 8 * 16 * 64 * 4 : 0;  // cross-wave sum
+    static constexpr int LDS_BYTES = 2 * STAGE * 2 > RED_BYTES ? 2 * STAGE * 2 : RED_BYTES;
+};
+
+// Eight fp32 values as PLANES bf16 vectors whose sum they are.
+template <int PLANES>
+__device__ __forceinline__ void split_eight(const float (&x)[8], bf16x8_t (&out)[PLANES]) {
+    float r[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) r[u] = x[u];
+#pragma unroll
+    for (int p = 0; p < PLANES; ++p) {
+        union {
+            bf16x8_t v;
+            bf16x2_t h[4];
+            uint32_t w[4];
+        } o;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            o.h[q] = __builtin_convertvector((f32x2_t){r[2 * q], r[2 * q + 1]}, bf16x2_t);  // nearest even
+            if (p + 1 < PLANES) {
+                r[2 * q] -= __uint_as_float(o.w[q] << 16);
+                r[2 * q + 1] -= __uint_as_float(o.w[q] & 0xFFFF0000u);
+            }
+        }
+        out[p] = o.v;
+    }
+}
+
+// One operand tile (ROWS rows or columns of the product x BK contraction elements) on its way from
+// memory to LDS, in chunks of eight elements that are neighbours in memory.  KROWS: the chunk runs
+// along the contraction.  Elements beyond the contraction become zeros; rows beyond the operand hold
+// anything: they only reach outputs that are not stored.
+//
+// Modes 4 and 3: the buffer descriptor starts at the tile and moves along the contraction with scalar
+// arithmetic; it ends with the dword that holds the last valid element, and every dword beyond it reads
+// as zero, so an edge costs at most a compare and a select per load.  Mode 3 loads whole dwords too: a
+// bf16 row that starts in the middle of one is shifted into place (a fifth dword and a funnel shift per
+// chunk), and what a chunk holds beyond the end of its row is cleared in store().
+template <typename T, int ROWS, int BK, bool KROWS, int MODE, int STRIDE, int PLANE>
+struct PlainLoader {
+    static constexpr int CHUNKS = ROWS * BK / 8 / kPlainThreads, PLANES = plain_planes<T>(), ES = (int)sizeof(T);
+    static constexpr int WORDS = MODE == 0 ? 8 : ES == 4 ? 8 : 5;  // registers of a chunk in flight
+    static_assert(ROWS * BK % (8 * kPlainThreads) == 0, "whole chunks per thread");
+    static_assert(MODE != 4 || ES == 4, "bf16 rows on 16 bytes are the other kernels' business");
+    struct Regs {
+        uint32_t v[CHUNKS][WORDS];
+    };
+    int kk[CHUNKS], at[CHUNKS];
+    uint32_t off[CHUNKS];
+    const T *p[MODE == 0 ? CHUNKS : 1];
+    const T *base;
+    int64_t ld, rows_left;
+    int clamp[MODE == 0 ? CHUNKS : 1];
+
+    __device__ __forceinline__ void init(const T *operand, int64_t ld_, int64_t row0, int64_t rows, int tid) {
+        ld = ld_, rows_left = rows - row0;
+        base = operand + (MODE == 0 ? 0 : row0 * (KROWS ? ld : 1));
+        uint32_t skew = 0;
+        if constexpr (ES == 2 && MODE != 0) {  // descriptors start on a dword
+            skew = (uint32_t)(reinterpret_cast<uintptr_t>(base) & 2u);
+            base -= skew / 2;
+            rows_left += KROWS ? 0 : skew / 2;  // (columns counted from the new base)
+        }
+#pragma unroll
+        for (int q = 0; q < CHUNKS; ++q) {
+            const int c = tid + kPlainThreads * q;
+            const int r = KROWS ? c / (BK / 8) : c % (ROWS / 8) * 8, k = KROWS ? c % (BK / 8) * 8 : c / (ROWS / 8);
+            kk[q] = k;
+            at[q] = KROWS ? r * STRIDE + kchunk_pos<BK>(r, k / 8) * 8 : k * STRIDE + r;
+            if constexpr (MODE == 0) {
+                p[q] = operand + (KROWS ? min(row0 + r, rows - 1) * ld + k : k * ld + min(row0 + r, rows - 1));
+                clamp[q] = KROWS ? 7 : (int)max((int64_t)0, min((int64_t)7, rows - 1 - row0 - r));  // last element of the chunk that exists
+            } else {
+                off[q] = row0 + r < rows ? (uint32_t)((KROWS ? r * ld + k : k * ld + r) * ES) + skew : 0x80000000u;
+            }
+        }
+    }
+    // Requests the next tile; `left` = contraction elements that remain (may be <= 0).
+    __device__ __forceinline__ void load(Regs &g, int64_t left) {
+        if constexpr (MODE == 0) {
+#pragma unroll
+            for (int q = 0; q < CHUNKS; ++q) {
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    const bool ok = kk[q] + (KROWS ? u : 0) < left;
+                    const T *a = ok ? p[q] + min(u, clamp[q]) : base;  // an address that exists
+                    g.v[q][u] = ES == 4 ? *reinterpret_cast<const uint32_t *>(a) : *reinterpret_cast<const uint16_t *>(a);
+                }
+                p[q] += KROWS ? BK : BK * ld;
+            }
+        } else {
+            const int l = (int)(left < 0 ? 0 : left < BK ? left : BK);
+            const int64_t elems = KROWS ? (min(rows_left, (int64_t)ROWS) - 1) * ld + l : (l > 0 ? (l - 1) * ld + rows_left : 0);
+            const int64_t bytes = (elems * ES + (ES == 2 && KROWS ? 2 : 0) + 3) & ~(int64_t)3;  // (+2: a skewed base)
+            const __amdgpu_buffer_rsrc_t rsrc =
+                __builtin_amdgcn_make_buffer_rsrc(const_cast<T *>(base), (short)0,
+                                                  __builtin_amdgcn_readfirstlane((int)min(bytes, (int64_t)0x7FFFFFFC)), 0x00020000);
+#pragma unroll
+            for (int q = 0; q < CHUNKS; ++q) {
+#pragma unroll
+                for (int h = 0; h < ES / 2; ++h) {
+                    const bool ok = !KROWS || kk[q] + 4 * h < l;
+                    const u32x4_t w = __builtin_amdgcn_raw_buffer_load_b128(rsrc, ok ? (off[q] & ~3u) + 16 * h : 0x80000000u, 0, 0);
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) g.v[q][4 * h + u] = w[u];
+                }
+                if constexpr (ES == 2)
+                    g.v[q][4] = __builtin_amdgcn_raw_buffer_load_b32(rsrc, !KROWS || kk[q] < l ? (off[q] & ~3u) + 16 : 0x80000000u, 0, 0);
+            }
+            base += KROWS ? BK : BK * ld;
+        }
+    }
+    __device__ __forceinline__ void store(const Regs &g, bf16_t *tile, int64_t left) const {
+#pragma unroll
+        for (int q = 0; q < CHUNKS; ++q) {
+            // (a select at the load would make every request wait for its data)
+            const int valid = (int)max((int64_t)0, min((int64_t)8, KROWS ? left - kk[q] : (kk[q] < left ? (int64_t)8 : (int64_t)0)));
+            if constexpr (ES == 2) {
+                uint32_t w[4];
+                if constexpr (MODE == 0) {
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) w[u] = g.v[q][2 * u] | g.v[q][2 * u + 1] << 16;
+                } else {
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) w[u] = __builtin_amdgcn_alignbit(g.v[q][u + 1], g.v[q][u], (off[q] & 2u) * 8);
+                }
+                if constexpr (KROWS || MODE == 0) {
+#pragma unroll
+                    for (int u = 0; u < 4; ++u)
+                        w[u] = 2 * u + 1 < valid ? w[u] : 2 * u < valid ? w[u] & 0xFFFFu : 0u;
+                } else {  // (the descriptor's last dword may hold the first element behind the last row)
+                    w[0] = valid != 0 ? w[0] : 0u;
+                }
+                *reinterpret_cast<u32x4_t *>(tile + at[q]) = (u32x4_t){w[0], w[1], w[2], w[3]};
+            } else {
+                float x[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    x[u] = __uint_as_float(g.v[q][u]);
+                    if constexpr (MODE == 0 || (MODE == 3 && KROWS)) x[u] = u < valid ? x[u] : 0.0f;
+                }
+                bf16x8_t o[PLANES];
+                split_eight<PLANES>(x, o);
+#pragma unroll
+                for (int s = 0; s < PLANES; ++s) *reinterpret_cast<bf16x8_t *>(tile + s * PLANE + at[q]) = o[s];
+            }
+        }
+    }
+};
+
+// Eight unscaled Gaussian entries P[t0 .. t0+7][j], t0 a multiple of 8.
+__device__ __forceinline__ void gauss_eight_precise(const SketchState &st, uint32_t t0, uint32_t j, float (&v)[8]) {
+    const Words4 r = philox4x32_10(t0 >> 3, j, st.off0, st.off1, st.key0, st.key1);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) gauss_pair_precise(r.w[q], v[2 * q], v[2 * q + 1]);
+}
+
+// The same for the kinds whose entries are +1 and -1 (1 = Rademacher, 2 = SORS), as bf16.
+__device__ __forceinline__ bf16x8_t sign_eight(int kind, const SketchState &st, uint32_t t0, uint32_t j) {
+    const uint32_t t = t0 & 127u;
+    const Words4 s = philox4x32_10(t0 >> 7, kind == 1 ? j : kSorsSignColumn, st.off0, st.off1, st.key0, st.key1);
+    const uint32_t word = (t >> 5) == 0 ? s.w[0] : (t >> 5) == 1 ? s.w[1] : (t >> 5) == 2 ? s.w[2] : s.w[3];
+    uint32_t bits = word >> (t & 31u);
+    if (kind == 2) {
+        const Words4 w = philox4x32_10(j >> 2, kSorsRowColumn, st.off0, st.off1, st.key0, st.key1);
+        const uint32_t row = ((j & 3u) == 0 ? w.w[0] : (j & 3u) == 1 ? w.w[1] : (j & 3u) == 2 ? w.w[2] : w.w[3]) & st.row_mask;
+#pragma unroll
+        for (int u = 0; u < 8; ++u) bits ^= ((uint32_t)__popc(row & (t0 + u)) & 1u) << u;
+    }
+    union {
+        bf16x8_t v;
+        uint32_t d[4];
+    } out;
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+        out.d[q] = 0x3F803F80u | (((bits >> (2 * q)) & 1u) << 15) | (((bits >> (2 * q + 1)) & 1u) << 31);
+    return out.v;
+}
+
+// Output tile number `block` of `blocks`.
+template <typename T, typename Tout, typename S, int AMODE, int BMODE, int MODE>
+__device__ __forceinline__ void plain_tile(const PlainArgs &g, bf16_t *lds, int64_t block, int64_t blocks) {
+    typedef PlainTile<T, S, AMODE, BMODE> L;
+    constexpr int BM = S::BM, BN = S::BN, BK = S::BK, PA = L::PA, PB = L::PB;
+    constexpr int TM = BM / S::WM / 32, TN = BN / S::WN / 32;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int kg = wave / (S::WM * S::WN), wm = wave % (S::WM * S::WN) / S::WN, wn = wave % S::WN;
+    // Work-groups are dealt round-robin to the 8 XCDs: give each a contiguous run of positions, walked
+    // in bands of 8 tile rows, so that work-groups that run together on one XCD share operands in its L2.
+    const int64_t tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN;
+    int64_t tile;
+    {
+        const int64_t per = blocks / 8, rem = blocks % 8, x = block % 8, r = block / 8;
+        tile = x * per + (x < rem ? x : rem) + r;
+    }
+    const int64_t band = tile / (8 * tiles_n), in_band = tile % (8 * tiles_n);
+    const int64_t band_rows = min((int64_t)8, tiles_m - band * 8);
+    const int64_t m0 = (band * 8 + in_band % band_rows) * BM, n0 = (in_band / band_rows) * BN;
+
+    f32x16_t acc[TM][TN];
+#pragma unroll
+    for (int a = 0; a < TM; ++a)
+#pragma unroll
+        for (int b = 0; b < TN; ++b)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[a][b][v] = 0.0f;
+
+    constexpr bool GEN = AMODE == PA_GAUSS || AMODE == PA_SIGN;
+    typedef PlainLoader<T, BN, BK, BMODE == PB_K, MODE, L::SB, L::B_PLANE> LoadB;
+    typedef std::conditional_t<GEN, LoadB, PlainLoader<T, GEN ? BN : BM, BK, AMODE == PA_K, MODE, L::SA, L::A_PLANE>> LoadA;
+    [[maybe_unused]] LoadA la;  // (not used by a generated operand)
+    LoadB lb;
+    typename LoadA::Regs va[2];
+    typename LoadB::Regs vb[2];
+    if constexpr (!GEN) la.init(reinterpret_cast<const T *>(g.A), g.lda, m0, g.M, tid);
+    lb.init(reinterpret_cast<const T *>(g.B), g.ldb, n0, g.N, tid);
+
+    int64_t asked = 0;  // contraction elements requested so far
+    auto issue = [&](int set) {
+        if constexpr (!GEN) la.load(va[set], g.K - asked);
+        lb.load(vb[set], g.K - asked);
+        asked += BK;
+    };
+    // Writes tile t (in register set `set`) into LDS stage `set`.  A generated tile is made here: one
+    // chunk of eight tokens of a sketch column per thread, the waves taking turns where the tile has
+    // fewer chunks than the work-group threads, so that some generate while the others multiply.
+    // Entries beyond the operand meet zeros of B or are not stored.
+    auto put = [&](int set, int64_t t) {
+        bf16_t *As = lds + set * L::STAGE, *Bs = As + PA * L::A_PLANE;
+        if constexpr (GEN) {
+            constexpr int CALLS = BM * BK / 8, TURNS = kPlainThreads / CALLS;
+            static_assert(CALLS % 64 == 0 && TURNS * CALLS == kPlainThreads, "whole waves take turns");
+            if (TURNS == 1 || tid / CALLS == (int)(t % TURNS)) {
+                const int c = tid % CALLS, j = c / (BK / 8), kc = c % (BK / 8);
+                const uint32_t tok = (uint32_t)(t * BK + kc * 8), col = (uint32_t)(m0 + j);
+                bf16_t *to = As + j * L::SA + kchunk_pos<BK>(j, kc) * 8;
+                if constexpr (AMODE == PA_GAUSS) {
+                    float e[8];
+                    gauss_eight_precise(g.st, tok, col, e);
+                    bf16x8_t o[PA];
+                    split_eight<PA>(e, o);
+#pragma unroll
+                    for (int s = 0; s < PA; ++s) *reinterpret_cast<bf16x8_t *>(to + s * L::A_PLANE) = o[s];
+                } else {
+                    *reinterpret_cast<bf16x8_t *>(to) = sign_eight(g.kind, g.st, tok, col);
+                }
+            }
+        } else {
+            la.store(va[set], As, g.K - t * BK);
+        }
+        lb.store(vb[set], Bs, g.K - t * BK);
+    };
+    constexpr int STEPS = BK / 16 / S::WK;  // 16-deep contraction steps per tile and wave
+    struct Frags {
+        bf16x8_t a[PA][TM], b[PB][TN];
+    };
+    auto fetch = [&](Frags &f, int set, int step) {
+        const bf16_t *As = lds + set * L::STAGE, *Bs = As + PA * L::A_PLANE;
+        const int k0 = (kg * STEPS + step) * 16;
+#pragma unroll
+        for (int s = 0; s < PA; ++s)
+#pragma unroll
+            for (int u = 0; u < TM; ++u) {
+                const int r0 = wm * (BM / S::WM) + u * 32;
+                f.a[s][u] = L::A_KROWS ? frag_kcontig<BK>(As + s * L::A_PLANE, r0, k0, lane)
+                                       : frag_transposed(As + s * L::A_PLANE, L::SA, r0, k0, lane);
+            }
+#pragma unroll
+        for (int s = 0; s < PB; ++s)
+#pragma unroll
+            for (int u = 0; u < TN; ++u) {
+                const int c0 = wn * (BN / S::WN) + u * 32;
+                f.b[s][u] = L::B_KROWS ? frag_kcontig<BK>(Bs + s * L::B_PLANE, c0, k0, lane)
+                                       : frag_transposed(Bs + s * L::B_PLANE, L::SB, c0, k0, lane);
+            }
+    };
+    auto multiply = [&](const Frags &f) {  // smallest products first
+#pragma unroll
+        for (int order = PA + PB - 2; order >= 0; --order)
+#pragma unroll
+            for (int s = 0; s < PA; ++s) {
+                const int r = order - s;
+                if (r < 0 || r >= PB || s + r > 3) continue;
+#pragma unroll
+                for (int u = 0; u < TM; ++u)
+#pragma unroll
+                    for (int w = 0; w < TN; ++w)
+                        acc[u][w] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.a[s][u], f.b[r][w], acc[u][w], 0, 0, 0);
+            }
+    };
+
+    // Two LDS stages, two register sets: while tile t is multiplied, t+1 goes from registers to LDS and
+    // t+3 is requested.  Tiles past the end are zeros.
+    const int64_t num = (g.K + BK - 1) / BK;
+    issue(0);
+    issue(1);
+    put(0, 0);
+    issue(0);
+    __syncthreads();
+    for (int64_t t = 0; t < num; t += 2) {
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            Frags f[2];
+            fetch(f[0], s, 0);
+#pragma unroll
+            for (int step = 0; step < STEPS; ++step) {
+                if (step + 1 < STEPS) fetch(f[(step + 1) & 1], s, step + 1);
+                multiply(f[step & 1]);
+                if (step == 0) {
+                    put(s ^ 1, t + s + 1);
+                    issue(s ^ 1);
+                }
+            }
+            __syncthreads();
+        }
+    }
+
+    // Register v of lane l is C(8*(v/4) + 4*(l/32) + v%4, l % 32) of a 32x32 tile: a store instruction
+    // writes two rows of 32 consecutive elements, whatever the alignment of the rows.
+    Tout *C = reinterpret_cast<Tout *>(g.C);
+    const T *bias = reinterpret_cast<const T *>(g.bias);
+    const int half = lane >> 5;
+    auto put_out = [&](int64_t r, int64_t c, float x, float bv) {
+        if (r >= g.M || c >= g.N) return;
+        x = g.alpha * x;
+        if (g.bias != nullptr) x += bv;
+        if (g.accumulate) x += load_f32<Tout>(C + r * g.ldc + c);
+        store_f32<Tout>(C + r * g.ldc + c, x);
+    };
+    if constexpr (S::WK > 1) {
+        // The waves that shared a 32x32 tile's contraction each finish 16 / WK of its registers.
+        static_assert(TM == 1 && TN == 1, "one 32x32 tile per wave");
+        constexpr int OWN = 16 / S::WK, WAVES = S::WM * S::WN;
+        float *red = reinterpret_cast<float *>(lds);
+#pragma unroll
+        for (int v = 0; v < 16; ++v) red[(wave * 16 + v) * 64 + lane] = acc[0][0][v];
+        __syncthreads();
+        const int64_t c = n0 + wn * 32 + (lane & 31);
+        const float bv = bias != nullptr && c < g.N ? load_f32<T>(bias + c) : 0.0f;
+#pragma unroll
+        for (int u = 0; u < OWN; ++u) {
+            const int v = kg * OWN + u;
+            float x = 0.0f;
+#pragma unroll
+            for (int p = 0; p < S::WK; ++p) x += red[((p * WAVES + wave % WAVES) * 16 + v) * 64 + lane];
+            put_out(m0 + wm * 32 + 8 * (v / 4) + 4 * half + v % 4, c, x, bv);
+        }
+    } else {
+#pragma unroll
+        for (int w = 0; w < TN; ++w) {
+            const int64_t c = n0 + wn * (BN / S::WN) + w * 32 + (lane & 31);
+            const float bv = bias != nullptr && c < g.N ? load_f32<T>(bias + c) : 0.0f;
+#pragma unroll
+            for (int u = 0; u < TM; ++u)
+#pragma unroll
+                for (int v = 0; v < 16; ++v)
+                    put_out(m0 + wm * (BM / S::WM) + u * 32 + 8 * (v / 4) + 4 * half + v % 4, c, acc[u][w][v], bv);
+        }
+    }
+}
+
+// One launch for what a pass computes from one activation: `sketch_blocks` tiles of the sketch
+// product (first: they are the long ones), `colsum_blocks` column blocks of the bias gradient and
+// the tiles of the plain product.  Any of the three may be absent.
+template <typename T, typename S, typename SS, int SKETCH, int BMODE, int MODE>
+__global__ void __launch_bounds__(kPlainThreads) plain_pass_kernel(PlainArgs ga, PlainArgs gs, ColsumArgs gc, int plain_blocks,
+                                                                   int sketch_blocks, int colsum_blocks) {
+    constexpr int BA = PlainTile<T, S, PA_K, BMODE>::LDS_BYTES, BS = PlainTile<T, SS, SKETCH, PB_N>::LDS_BYTES;
+    constexpr int BYTES = (BA > BS ? BA : BS) > kColsumLdsFloats * 4 ? (BA > BS ? BA : BS) : kColsumLdsFloats * 4;
+    __shared__ __attribute__((aligned(16))) unsigned char lds[BYTES];
+    const int b = (int)blockIdx.x;
+    if (b < sketch_blocks)
+        plain_tile<T, T, SS, SKETCH, PB_N, MODE>(gs, reinterpret_cast<bf16_t *>(lds), b, sketch_blocks);
+    else if (b < sketch_blocks + colsum_blocks)
+        colsum_any_body<T>(gc, reinterpret_cast<float *>(lds), b - sketch_blocks, colsum_blocks);
+    else
+        plain_tile<T, T, S, PA_K, BMODE, MODE>(ga, reinterpret_cast<bf16_t *>(lds), b - sketch_blocks - colsum_blocks, plain_blocks);
+}
+
+// A^T B products (dW = G^T X_proj; X^T dY of the variance monitors).
+template <typename T, typename Tout, typename S, int MODE>
+__global__ void __launch_bounds__(kPlainThreads) plain_tn_kernel(PlainArgs g) {
+    __shared__ __attribute__((aligned(16))) unsigned char lds[PlainTile<T, S, PA_M, PB_N>::LDS_BYTES];
+    plain_tile<T, Tout, S, PA_M, PB_N, MODE>(g, reinterpret_cast<bf16_t *>(lds), blockIdx.x, gridDim.x);
+}
+
+}  // namespace
+
+}  // namespace rmm

@@ -1,0 +1,56 @@
+// Launcher of plain_pass_kernel, shared by the translation units that hold its instantiations
+// (plain_pass_*.hip; separate files only to keep the build parallel).
+#pragma once
+#include "plain_kernels.hpp"
+
+namespace rmm {
+
+// Which tile shapes a launch uses.
+enum { PLAIN_BIG = 0, PLAIN_MID = 1, PLAIN_TINY = 2 };
+struct PlainLaunch {
+    PlainArgs ga, gs;
+    ColsumArgs gc;
+    int plain_blocks, sketch_blocks, colsum_blocks;
+    int cfg;            // tile shape of the plain product
+    bool sketch_small;  // the 32 x 32 tile for the sketch product (always with PLAIN_TINY, never with PLAIN_BIG)
+};
+
+// One for each element type and way of loading it (plain_kernels.hpp: MODE 4, 3, 0).
+hipError_t launch_plain_pass_f32x4(const PlainLaunch &p, bool b_rows_k, hipStream_t stream);
+hipError_t launch_plain_pass_f32(const PlainLaunch &p, bool b_rows_k, hipStream_t stream);
+hipError_t launch_plain_pass_bf16(const PlainLaunch &p, bool b_rows_k, hipStream_t stream);
+hipError_t launch_plain_pass_far_f32(const PlainLaunch &p, bool b_rows_k, hipStream_t stream);   // PLAIN_TINY only
+hipError_t launch_plain_pass_far_bf16(const PlainLaunch &p, bool b_rows_k, hipStream_t stream);  // PLAIN_TINY only
+
+template <typename T, int MODE, int BMODE, int SKETCH>
+hipError_t launch_plain_pass_kind(const PlainLaunch &p, hipStream_t stream) {
+    const unsigned grid = (unsigned)(p.plain_blocks + p.sketch_blocks + p.colsum_blocks);
+#define RMM_PLAIN_PASS(S, SS)                                                                                        \
+    plain_pass_kernel<T, S, SS, SKETCH, BMODE, MODE>                                                                 \
+        <<<grid, kPlainThreads, 0, stream>>>(p.ga, p.gs, p.gc, p.plain_blocks, p.sketch_blocks, p.colsum_blocks)
+    if constexpr (MODE == 0) {
+        RMM_PLAIN_PASS(PlainTiny, PlainTiny);
+    } else {
+        if (p.cfg == PLAIN_TINY)
+            RMM_PLAIN_PASS(PlainTiny, PlainTiny);
+        else if (p.cfg == PLAIN_BIG)
+            RMM_PLAIN_PASS(PlainBig, PlainSketch);
+        else if (p.sketch_small)
+            RMM_PLAIN_PASS(PlainMid, PlainTiny);
+        else
+            RMM_PLAIN_PASS(PlainMid, PlainSketch);
+    }
+#undef RMM_PLAIN_PASS
+    return hipGetLastError();
+}
+
+template <typename T, int MODE>
+hipError_t launch_plain_pass_impl(const PlainLaunch &p, bool b_rows_k, hipStream_t stream) {
+    if (p.gs.kind == 0)
+        return b_rows_k ? launch_plain_pass_kind<T, MODE, PB_N, PA_GAUSS>(p, stream)
+                        : launch_plain_pass_kind<T, MODE, PB_K, PA_GAUSS>(p, stream);
+    return b_rows_k ? launch_plain_pass_kind<T, MODE, PB_N, PA_SIGN>(p, stream)
+                    : launch_plain_pass_kind<T, MODE, PB_K, PA_SIGN>(p, stream);
+}
+
+}  // namespace rmm

@@ -1,0 +1,66 @@
+"""GPU: the fp32 kernels (fp32 operands split into three bf16 planes on their way to the matrix pipes) and
+the bf16 shapes they serve, at the edges of their tiles and load modes, against the fp64 oracle; and how
+exact the split products are."""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+import paper_2201_13195_amd as rmm
+from paper_2201_13195_amd import synth
+from test_gpu_parity import check_layer
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+
+SHAPES = [
+    # (n, d_in, d_out, k): 32x32, 64x64 and 128x128 tiles of the plain products, both sketch tiles
+    (33, 36, 31, 5), (500, 129, 127, 40),          # 32 x 32 tiles; contractions around one and two LDS tiles
+    (1030, 1028, 1004, 70),                         # 64 x 64 tiles of Y and dX, rows on 16 bytes
+    (2049, 516, 1030, 290),                         # the same with rows that start on 8 bytes
+    (2050, 2044, 2052, 100),                        # 128 x 128 tiles (a last round of one)
+    (4096, 260, 1027, 33),                          # odd rows on one side only
+]
+
+
+@pytest.mark.parametrize("kind", [rmm.GAUSSIAN, rmm.RADEMACHER, rmm.SORS])
+@pytest.mark.parametrize("shape", SHAPES)
+def test_fp32_tiles_and_load_modes(shape, kind):
+    n, d_in, d_out, k = shape
+    X, W, dY = synth.layer_inputs(n, d_in, d_out, "f32", (n, d_in + 1, d_out + 2), w_std=1.0 / math.sqrt(d_in))
+    bias = synth.to_torch(synth.normal((d_out,), 15), "f32")
+    check_layer(X, W, dY, k, kind, 0x5EED0031, 5, "f32", bias=bias, label="f32 %s kind=%d" % (shape, kind))
+
+
+@pytest.mark.parametrize("kind", [rmm.GAUSSIAN, rmm.RADEMACHER, rmm.SORS])
+@pytest.mark.parametrize("shape", [(33, 35, 31, 5), (1030, 1028, 1004, 70), (2049, 515, 1030, 290), (3000, 768, 1001, 300),
+                                   (4096, 261, 1032, 33)])
+def test_bf16_widths_that_are_no_multiple_of_8(shape, kind):
+    n, d_in, d_out, k = shape
+    X, W, dY = synth.layer_inputs(n, d_in, d_out, "bf16", (n, d_in + 1, d_out + 2), w_std=1.0 / math.sqrt(d_in))
+    bias = synth.to_torch(synth.normal((d_out,), 16), "bf16")
+    check_layer(X, W, dY, k, kind, 0x5EED0032, 6, "bf16", bias=bias, label="bf16 %s kind=%d" % (shape, kind))
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_rows_beyond_the_descriptor_range(dtype):
+    """Rows of 2^22 elements and more are loaded from 64-bit addresses."""
+    n, d_in, d_out, k = 3, (1 << 22) + 5, 5, 2
+    X, W, dY = synth.layer_inputs(n, d_in, d_out, dtype, (1, 2, 3), w_std=1.0 / math.sqrt(d_in))
+    X[:, 3000:-3000] = 0      # (a sum of 2^22 fp32 terms is not exact to 1e-5 in any order)
+    check_layer(X, W, dY, k, rmm.GAUSSIAN, 7, 8, dtype, label="long rows %s" % dtype)
+
+
+@pytest.mark.parametrize("n,d_in,d_out", [(256, 1, 256), (512, 8, 512), (1024, 768, 1024)])
+def test_fp32_products_are_as_exact_as_fp32_multiply_adds(n, d_in, d_out):
+    """Contractions of one, a few and many terms, entries spread over 40 binades: the error against fp64
+    is bounded by the roundings of an fp32 accumulation, relative to the sum of the terms' magnitudes."""
+    g = np.random.default_rng(5)
+    X = (g.standard_normal((n, d_in)) * np.exp2(g.integers(-20, 20, (n, d_in)))).astype(np.float32)
+    W = (g.standard_normal((d_out, d_in)) * np.exp2(g.integers(-20, 20, (d_out, d_in)))).astype(np.float32)
+    Y, _ = rmm.rmm_forward(torch.from_numpy(X).to(DEV), torch.from_numpy(W).to(DEV), None, 1, 0, 1, 2, need_xproj=False)
+    X64, W64 = X.astype(np.float64), W.astype(np.float64)
+    err = np.abs(synth.to_f64(Y) - X64 @ W64.T) / (np.abs(X64) @ np.abs(W64).T)
+    print("K=%d: largest error / sum of magnitudes = %.2f * 2^-24" % (d_in, err.max() * 2.0 ** 24), flush=True)
+    assert err.max() <= 2.0 ** -24 * (2.0 + math.sqrt(d_in))
