@@ -1,6 +1,11 @@
-"""ctypes binding of librmm.so: same names as the C entry points, argument
-marshalling only.  There is no fallback: if the library is not built, or a tensor
-is not on the GPU, the call raises."""
+"""Binding of librmm.so: same names as the C entry points, argument marshalling only.
+There is no fallback: if the library is not built, or a tensor is not on the GPU, the
+call raises.
+
+The tensor functions go through the native module _rmm_host (csrc/torch_host.cpp), which
+checks, allocates and calls without Python or ctypes work per argument; arguments that it
+does not take (and calls with event pairs) go through the ctypes functions here, whose
+checks say what is wrong with them."""
 import ctypes
 import os
 
@@ -14,6 +19,7 @@ _DTYPES = {torch.float32: 0, torch.bfloat16: 1}
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB = None
+_HOST = None
 
 
 class RmmError(RuntimeError):
@@ -84,6 +90,28 @@ def load_library():
     return L
 
 
+def host():
+    """The native host module, built together with librmm.so (which it links)."""
+    global _HOST
+    if _HOST is None:
+        load_library()
+        if not os.path.exists(os.path.join(_HERE, "_rmm_host.so")):
+            raise RuntimeError("_rmm_host.so is not built: run `python -m paper_2201_13195_amd.build`")
+        from . import _rmm_host
+        _HOST = _rmm_host
+    return _HOST
+
+
+def _native(name, *args):
+    """The native module's answer, or None if it does not take these arguments."""
+    r = getattr(_HOST or host(), name)(*args)
+    if r is NotImplemented:
+        return None
+    if type(r) is int:
+        raise RmmError(r, "rmm_" + ("forward" if name in ("linear", "infer") else name))
+    return r
+
+
 def rmm_version():
     return load_library().rmm_version()
 
@@ -147,6 +175,10 @@ def _workspace(ws, need, device):
 def rmm_sketch(A, k, kind, seed, offset, out=None, ws=None, events=None):
     """A (n x d) -> S^T A (k x d).  Returns `out`.  `events` = (begin, end), torch.cuda.Event
     objects recorded once before, are re-recorded around the product kernel alone."""
+    if events is None:
+        r = _native("sketch", A, k, kind, seed, offset, out, ws)
+        if r is not None:
+            return r
     n, d = A.shape
     if out is None:
         out = torch.empty((k, d), dtype=A.dtype, device=A.device)
@@ -181,6 +213,9 @@ VARIANCE_FIELDS = ("x_fro2", "y_fro2", "rows", "xty_fro2", "d2_sgd", "d2_rmm", "
 
 def rmm_variance_stats(X, dY, k, kind, out=None, ws=None):
     """Variance monitors of Section 2.3.  Returns a device tensor of 8 doubles (VARIANCE_FIELDS)."""
+    r = _native("variance_stats", X, dY, k, kind, out, ws)
+    if r is not None:
+        return r
     n, d_in = X.shape
     d_out = dY.shape[1]
     if out is None:
@@ -212,6 +247,10 @@ def _event_args(profile):
 def rmm_forward(X, W, bias, k, kind, seed, offset, Y=None, X_proj=None, ws=None, profile=None, need_xproj=True):
     """Algorithm 1 forward.  Returns (Y, X_proj); with need_xproj=False (no backward pass will
     follow) the sketch is skipped and X_proj is None."""
+    if profile is None:
+        r = _native("forward", X, W, bias, k, kind, seed, offset, Y, X_proj, ws, need_xproj)
+        if r is not None:
+            return r
     n, d_in = X.shape
     d_out = W.shape[0]
     if Y is None:
@@ -235,6 +274,10 @@ def rmm_backward(dY, W, X_proj, kind, seed, offset, need_dX=True, need_dbias=Fal
                  ws=None, profile=None, accumulate=False):
     """Algorithm 1 backward with the forward call's state.  Returns (dX, dW, dbias).  With
     `accumulate` the given dW (and dbias) are added to instead of overwritten."""
+    if profile is None:
+        r = _native("backward", dY, W, X_proj, kind, seed, offset, need_dX, need_dbias, dX, dW, dbias, ws, accumulate)
+        if r is not None:
+            return r
     if accumulate and (dW is None or (need_dbias and dbias is None) or profile is not None):
         raise ValueError("accumulate needs existing dW / dbias tensors and no profile")
     n, d_out = dY.shape

@@ -1,20 +1,24 @@
-"""Builds librmm.so (HIP, gfx950 only) in-tree with hipcc.
+"""Builds librmm.so (HIP, gfx950 only) in-tree with hipcc, and the package's host module.
 
     python -m paper_2201_13195_amd.build
 
 Every .hip file under csrc/ is compiled to an object and the objects are linked
-into paper_2201_13195_amd/librmm.so.  Nothing is cached between calls.
+into paper_2201_13195_amd/librmm.so; csrc/torch_host.cpp (no device code) becomes
+paper_2201_13195_amd/_rmm_host.so next to it.  Nothing is cached between calls.
 """
+import importlib.util
 import os
 import shutil
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ_DIR = os.path.join(HERE, "_build")
 LIB_PATH = os.path.join(HERE, "librmm.so")
+HOST_PATH = os.path.join(HERE, "_rmm_host.so")
 
 # Packed-fp32 instructions are switched off on purpose (device flag, hipcc only).
 HIPCC_FLAGS = [
@@ -44,19 +48,48 @@ def _compile(src):
     return obj
 
 
+def _torch_dir():
+    return os.path.dirname(importlib.util.find_spec("torch").origin)
+
+
+def _compile_host():
+    """csrc/torch_host.cpp -> object, against the headers of the installed torch."""
+    obj, inc = os.path.join(OBJ_DIR, "torch_host.o"), os.path.join(_torch_dir(), "include")
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-fvisibility=hidden", "-w", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+           "-I" + inc, "-I" + os.path.join(inc, "torch", "csrc", "api", "include"), "-I/opt/rocm/include",
+           "-I" + sysconfig.get_paths()["include"], "-c", os.path.join(CSRC, "torch_host.cpp"), "-o", obj]
+    p = subprocess.run(cmd, capture_output=True, text=True)
+    if p.returncode != 0:
+        raise RuntimeError("g++ failed on torch_host.cpp:\n%s\n%s" % (p.stdout, p.stderr))
+    return obj
+
+
+def _link_host(obj):
+    lib, tmp = os.path.join(_torch_dir(), "lib"), HOST_PATH + ".tmp"
+    cmd = ["g++", "-shared", obj, "-o", tmp, "-L" + lib, "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_hip", "-ltorch_python",
+           "-L" + HERE, "-lrmm", "-Wl,-rpath,$ORIGIN"]
+    p = subprocess.run(cmd, capture_output=True, text=True)
+    if p.returncode != 0:
+        raise RuntimeError("link failed:\n%s\n%s" % (p.stdout, p.stderr))
+    os.replace(tmp, HOST_PATH)
+
+
 def build(verbose=False):
     os.makedirs(OBJ_DIR, exist_ok=True)
     srcs = sources()
-    with ThreadPoolExecutor(max_workers=min(8, len(srcs))) as ex:
+    with ThreadPoolExecutor(max_workers=8) as ex:
+        host = ex.submit(_compile_host)
         objs = list(ex.map(_compile, srcs))
+        host = host.result()
     tmp = LIB_PATH + ".tmp"
     cmd = [_hipcc(), "-shared", "-fPIC", "--offload-arch=gfx950", "-fno-gpu-rdc", *objs, "-o", tmp]
     p = subprocess.run(cmd, capture_output=True, text=True)
     if p.returncode != 0:
         raise RuntimeError("link failed:\n%s\n%s" % (p.stdout, p.stderr))
     os.replace(tmp, LIB_PATH)
+    _link_host(host)
     if verbose:
-        print("built", LIB_PATH)
+        print("built", LIB_PATH, HOST_PATH)
     return LIB_PATH
 
 

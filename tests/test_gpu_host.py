@@ -1,0 +1,84 @@
+"""GPU: the native host module and the ctypes functions behind it are the same entry points: same bits,
+same autograd behaviour, same errors."""
+import pytest
+import torch
+
+import paper_2201_13195_amd as rmm
+from paper_2201_13195_amd import binding
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+
+
+def both(monkeypatch, call):
+    """call() through the native module, then through the ctypes functions."""
+    native = call()
+    with monkeypatch.context() as m:
+        m.setattr(binding, "_native", lambda *args: None)
+        return native, call()
+
+
+def same(a, b):
+    assert len(a) == len(b)
+    for x, y in zip(a, b):
+        assert (x is None and y is None) or torch.equal(x, y)
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("n,d_in,d_out,k", [(1, 8, 8, 1), (200, 72, 40, 33)])
+def test_same_bits(monkeypatch, n, d_in, d_out, k, dtype):
+    g = torch.Generator(device=DEV).manual_seed(1)
+    X, W, b, dY = (torch.randn(s, generator=g, device=DEV).to(dtype) for s in ((n, d_in), (d_out, d_in), (d_out,), (n, d_out)))
+    seed, offset = -5, (1 << 70) + 3          # taken modulo 2^64
+    same(*both(monkeypatch, lambda: rmm.rmm_forward(X, W, b, k, rmm.GAUSSIAN, seed, offset)))
+    same(*both(monkeypatch, lambda: rmm.rmm_forward(X, W, None, k, rmm.SORS, seed, offset, need_xproj=False)))
+    Xp = rmm.rmm_sketch(X, k, rmm.GAUSSIAN, seed, offset)
+    for kw in (dict(need_dbias=True), dict(need_dX=False)):
+        same(*both(monkeypatch, lambda: rmm.rmm_backward(dY, W, Xp, rmm.GAUSSIAN, seed, offset, **kw)))
+    same(*both(monkeypatch, lambda: [rmm.rmm_sketch(X, k, rmm.RADEMACHER, seed, offset)]))
+    same(*both(monkeypatch, lambda: [rmm.rmm_variance_stats(X, dY, k, rmm.RADEMACHER)]))
+
+
+@pytest.mark.parametrize("bias", [True, False])
+def test_same_autograd(monkeypatch, bias):
+    """3-D and non-contiguous inputs, a retained graph, an input without gradient."""
+    lin = rmm.RMMLinear(64, 24, bias=bias, k=20, seed=3, layer_id=1)
+    X = torch.randn(2, 64, 30, device=DEV, dtype=torch.bfloat16).transpose(1, 2)
+    dY = torch.randn(2, 30, 24, device=DEV, dtype=torch.bfloat16)
+
+    def step():
+        lin.calls, lin.weight.grad, x = 0, None, X.detach().requires_grad_(True)
+        Y = lin(x)
+        assert Y.grad_fn.name() == "RMMLinearFunctionBackward"
+        Y.backward(dY, retain_graph=True)
+        once = (Y.detach(), x.grad.clone(), lin.weight.grad.clone())
+        Y.backward(dY)
+        with pytest.raises(RuntimeError):
+            Y.backward(dY)
+        Y2 = lin(X)                            # no gradient for the input
+        Y2.backward(dY)
+        assert lin.calls == 2 and lin.last_state == (3, (1 << 32) | 1)
+        return once + (x.grad, lin.weight.grad)
+    same(*both(monkeypatch, step))
+    with torch.no_grad():
+        same(*both(monkeypatch, lambda: [lin(X)]))
+
+
+def test_same_errors(monkeypatch):
+    X, W = torch.zeros(16, 8, device=DEV), torch.zeros(4, 8, device=DEV)
+    for call, error in ((lambda: rmm.rmm_forward(X, W.T, None, 3, 0, 1, 2), ValueError),
+                        (lambda: rmm.rmm_forward(X, W.double(), None, 3, 0, 1, 2), TypeError),
+                        (lambda: rmm.rmm_forward(X, W, None, 3, 9, 1, 2), rmm.RmmError),
+                        (lambda: rmm.rmm_backward(X, torch.zeros(8, 5, device=DEV), torch.zeros(3, 5, device=DEV), 0, 1, 2,
+                                                  ws=torch.empty(16, dtype=torch.uint8, device=DEV)), rmm.RmmError),
+                        (lambda: rmm.rmm_sketch(X.cpu(), 3, 0, 1, 2), ValueError),
+                        (lambda: rmm.rmm_variance_stats(X, X, 3, rmm.SORS), rmm.RmmError)):
+        raised = []
+        for native in (True, False):
+            with monkeypatch.context() as m:
+                if not native:
+                    m.setattr(binding, "_native", lambda *args: None)
+                with pytest.raises(error) as e:
+                    call()
+            raised.append(str(e.value))
+        assert raised[0] == raised[1]
