@@ -60,10 +60,11 @@ hipError_t launch_colsum(const T *A, T *out, int64_t n, int64_t d, hipStream_t s
 // launch_sketch_bf16 records the optional event pair around its product kernel
 // alone (the sum over token slices, when there is one, comes after `ev_end`).
 bool mfma_shape_ok(int64_t n, int64_t d_in, int64_t d_out, int64_t k);
+// (`as_pair`: with the tiles of the pass's paired launch, for passes that launch their products one by one)
 hipError_t launch_linear_nt_bf16(const bf16_t *X, const bf16_t *W, const bf16_t *bias, bf16_t *Y, int64_t n,
-                                 int64_t d_in, int64_t d_out, hipStream_t stream);
+                                 int64_t d_in, int64_t d_out, bool as_pair, hipStream_t stream);
 hipError_t launch_linear_nn_bf16(const bf16_t *dY, const bf16_t *W, bf16_t *dX, int64_t n, int64_t d_in,
-                                 int64_t d_out, hipStream_t stream);
+                                 int64_t d_out, bool as_pair, hipStream_t stream);
 hipError_t launch_dw_bf16(const bf16_t *G, const bf16_t *X_proj, bf16_t *dW, int64_t k, int64_t d_in, int64_t d_out,
                           hipStream_t stream, bool accumulate = false);
 // dW together with db = column sums of dY (n x d_out, 16-byte aligned, d_out a multiple of 8) in
@@ -82,13 +83,13 @@ hipError_t launch_sketch_bf16(const bf16_t *A, bf16_t *out, int64_t n, int64_t d
 // One launch for the two products of a pass that do not depend on each other: Y = X W^T (+ bias)
 // with the sketch product of X (forward), dX = dY W with the sketch product of dY (backward; G is
 // k x d_out), followed by the sum over the sketch's token slices.  Results are bit-identical to
-// the separate launches above (same kernels, same slices).  Only where *_pair_available() says so;
+// the separate launches above (same kernels, same slices).  Only where pass_pair_available() says so
+// (d_sk = the width of the sketched operand: d_in forward, d_out backward);
 // the optional event pair brackets the paired kernel alone.
-bool forward_pair_available(int64_t n, int64_t d_in, int64_t d_out, int64_t k);
+bool pass_pair_available(int64_t n, int64_t d_sk, int64_t k);
 hipError_t launch_forward_pair_bf16(const bf16_t *X, const bf16_t *W, const bf16_t *bias, bf16_t *Y, bf16_t *X_proj,
                                     int64_t n, int64_t d_in, int64_t d_out, int64_t k, int kind, SketchState st, void *ws,
                                     hipStream_t stream, hipEvent_t ev_begin = nullptr, hipEvent_t ev_end = nullptr);
-bool backward_pair_available(int64_t n, int64_t d_in, int64_t d_out, int64_t k);
 // With `dbias` the launch also takes the column sums of dY (the bias gradient), on the compute units
 // its last round leaves idle; backward_pair_takes_colsum() says where that beats the launch of dW.
 hipError_t launch_backward_pair_bf16(const bf16_t *dY, const bf16_t *W, bf16_t *dX, bf16_t *G, int64_t n, int64_t d_in,

@@ -20,7 +20,7 @@ template <typename S, int AMODE, int BMODE, int OUT>
 hipError_t launch(const GemmArgs &g, int splits, hipStream_t stream) {
     const int64_t tiles = ((g.M + S::BM - 1) / S::BM) * ((g.N + S::BN - 1) / S::BN);
     const dim3 grid((unsigned)tiles, 1, (unsigned)splits);
-    if constexpr (AMODE >= A_GAUSS || std::is_same<S, ShapeLarge>::value) {
+    if constexpr (AMODE >= A_GAUSS_LDS || std::is_same<S, ShapeLarge>::value) {
         gemm_mfma_kernel<S, AMODE, BMODE, OUT, 3><<<grid, S::THREADS, 0, stream>>>(g);
     } else {
         if (plain_depth(g.K < g.k_chunk ? g.K : g.k_chunk, S::BK) == 4)
@@ -37,7 +37,9 @@ int64_t tiles_of(int64_t m, int64_t n, int64_t bm, int64_t bn) { return ((m + bm
 //   256 x 256 (8 waves, one work-group per compute unit) once there are at least 160 such tiles:
 //     half the operand traffic per flop of the 128 x 128 tile, which needs more bytes per clock
 //     from L2 than it delivers at full MFMA rate;
-//   64 x 64 when there are fewer than 65 tiles of 128 x 128 (a quarter of the compute units);
+//   64 x 64, or 32 x 32 while those give at most one work-group per compute unit, with the contraction
+//     split over eight waves (few_tile) when there are fewer than 65 tiles of 128 x 128 (a quarter of
+//     the compute units);
 //   128 x 128 x 64 with two wave groups splitting the contraction when there are at most 256
 //     tiles and the contraction is 768 or longer (a compute unit then still holds 8 waves; at 768
 //     it runs like the 4-wave tile on its own, and its 512 threads allow the paired launch);
@@ -45,9 +47,22 @@ int64_t tiles_of(int64_t m, int64_t n, int64_t bm, int64_t bn) { return ((m + bm
 int gemm_cfg(int64_t m, int64_t n, int64_t kk) {
     if (tiles_of(m, n, ShapeLarge::BM, ShapeLarge::BN) >= 160) return GEMM_LARGE;
     const int64_t t128 = tiles_of(m, n, 128, 128);
-    if (t128 < 65) return GEMM_TINY;
+    if (t128 < 65) return GEMM_FEW;
     if (t128 <= 256 && kk >= 768) return GEMM_SPLIT;
     return GEMM_MID;
+}
+
+// Edge of the tile of few_tile: 32 while that gives at most two work-groups per compute unit.
+int few_edge(int64_t m, int64_t n) { return tiles_of(m, n, 32, 32) <= 512 ? 32 : 64; }
+
+template <int E, int AMODE, int BMODE>
+hipError_t launch_few(const GemmArgs &g, hipStream_t stream) {
+    const unsigned grid = (unsigned)tiles_of(g.M, g.N, E, E);
+    if (g.K <= kFewSingle)
+        few_tile_kernel<E, AMODE, BMODE, true><<<grid, kFewThreads, 0, stream>>>(g);
+    else
+        few_tile_kernel<E, AMODE, BMODE, false><<<grid, kFewThreads, 0, stream>>>(g);
+    return hipGetLastError();
 }
 
 template <int AMODE, int BMODE, int OUT>
@@ -55,7 +70,8 @@ hipError_t launch_gemm(int cfg, const GemmArgs &g, hipStream_t stream) {
     if (cfg == GEMM_LARGE) return launch<ShapeLarge, AMODE, BMODE, OUT>(g, 1, stream);
     if (cfg == GEMM_SPLIT) return launch<ShapeSplit, AMODE, BMODE, OUT>(g, 1, stream);
     if constexpr (OUT == OUT_BF16)
-        if (cfg == GEMM_TINY) return launch<ShapeTiny, AMODE, BMODE, OUT>(g, 1, stream);
+        if (cfg == GEMM_FEW)
+            return few_edge(g.M, g.N) == 32 ? launch_few<32, AMODE, BMODE>(g, stream) : launch_few<64, AMODE, BMODE>(g, stream);
     return launch<ShapeMid, AMODE, BMODE, OUT>(g, 1, stream);
 }
 
@@ -73,13 +89,14 @@ GemmArgs args_nn(const bf16_t *dY, const bf16_t *W, bf16_t *dX, int64_t n, int64
     return g;
 }
 
-// Which kernel serves a sketch product with k > 64 and how its token dimension is cut.
-//   d >= 1024:               the work-group generates the 128 x 32 sketch tile into LDS and all
-//                            eight waves read it, 512 columns per tile (an entry is generated once
-//                            per 512 columns); 64-row tiles for k <= 512 (k = 410 pads to 448 rows
-//                            instead of 512);
-//   d a multiple of 384:     the same with 384-column tiles (d = 768);
-//   other d below 1024:      128 x 256 tiles whose sketch fragments are generated in registers.
+// Which kernel serves a sketch product with k > 64 and how its token dimension is cut.  The work-group
+// generates the sketch tile into LDS and all eight waves read it.
+//   Rows: 64-row tiles for k <= 512 (k = 410 pads to 448 rows instead of 512), and up to k = 1024 while
+//     the contraction is short (at most 8192 tokens: (3001 x 1304, k = 600) 27.5 -> 23.1 us); longer ones
+//     want 128 rows (B tiles are staged half as often: (16384 x 1024, k = 1638) 84 against 100 us).
+//   Columns: of 512, 384 and 256 the one whose padded width costs least (an entry is generated once per
+//     tile column; measured weights), but 256 where even one slice per 128 tokens leaves less than one
+//     work-group per compute unit ((1500 x 3000, k = 150) 18.7 -> 17.0 us).
 // Tokens are cut into `splits` slices of `k_chunk` tokens (a multiple of 128) so that about
 // `target_wgs` work-groups exist (256 = one per compute unit; measured: more or fewer are slower
 // when the product runs alone); with more than one slice the kernel writes fp32 partial results
@@ -91,12 +108,14 @@ struct SketchPlan {
 
 SketchPlan plan_sketch(int64_t n, int64_t d, int64_t k, int target_wgs = 256) {
     SketchPlan p;
-    const bool rows64 = k <= 512;
-    p.cfg = d >= 1024 ? (rows64 ? SK_WIDE64 : SK_WIDE) : d % 384 == 0 ? (rows64 ? SK_MID64 : SK_MID) : SK_NARROW;
-    const int64_t bm = (p.cfg == SK_WIDE64 || p.cfg == SK_MID64) ? 64 : 128;
-    const int64_t bn = p.cfg == SK_NARROW ? 256 : (p.cfg == SK_MID64 || p.cfg == SK_MID) ? 384 : 512;
-    p.tiles = tiles_of(k, d, bm, bn);
     const int64_t blocks = (n + 127) / 128;
+    const bool rows64 = k <= 512 || (k <= 1024 && n <= 8192);
+    const int64_t bm = rows64 ? 64 : 128;
+    const int64_t w512 = (d + 511) / 512 * 512 * 100, w384 = (d + 383) / 384 * 384 * 103, w256 = (d + 255) / 256 * 256 * 112;
+    int64_t bn = w512 <= w384 && w512 <= w256 ? 512 : w384 <= w256 ? 384 : 256;
+    if (tiles_of(k, d, bm, bn) * blocks < 256) bn = 256;
+    p.cfg = bn == 512 ? (rows64 ? SK_WIDE64 : SK_WIDE) : bn == 384 ? (rows64 ? SK_MID64 : SK_MID) : (rows64 ? SK_NARROW64 : SK_NARROW);
+    p.tiles = tiles_of(k, d, bm, bn);
     int64_t s = target_wgs / p.tiles;
     if (s > blocks) s = blocks;
     if (s > 64) s = 64;
@@ -134,9 +153,12 @@ hipError_t launch_sketch_cfg(int cfg, int kind, const GemmArgs &g, int splits, h
         case SK_MID:
             return kind == 0 ? launch<ShapeSkMid, A_GAUSS_LDS, B_NCONTIG, OUT>(g, splits, stream)
                              : launch<ShapeSkMid, A_RADEM_LDS, B_NCONTIG, OUT>(g, splits, stream);
+        case SK_NARROW64:
+            return kind == 0 ? launch<ShapeSkNarrow64, A_GAUSS_LDS, B_NCONTIG, OUT>(g, splits, stream)
+                             : launch<ShapeSkNarrow64, A_RADEM_LDS, B_NCONTIG, OUT>(g, splits, stream);
         default:
-            return kind == 0 ? launch<ShapeSkNarrow, A_GAUSS, B_NCONTIG, OUT>(g, splits, stream)
-                             : launch<ShapeSkNarrow, A_RADEM, B_NCONTIG, OUT>(g, splits, stream);
+            return kind == 0 ? launch<ShapeSkNarrow, A_GAUSS_LDS, B_NCONTIG, OUT>(g, splits, stream)
+                             : launch<ShapeSkNarrow, A_RADEM_LDS, B_NCONTIG, OUT>(g, splits, stream);
     }
 }
 
@@ -195,18 +217,23 @@ struct EventPair {
     ~EventPair() { done(); }
 };
 
-// The paired launch exists for a plain product on 256 x 256 tiles, or on the 128 x 128 x 64 split
-// tiles at prefetch depth 4 (both run with 512 threads, like the sketch kernels), next to a sketch
-// product with an LDS-generated tile and at least two token slices.
-// An unsliced sketch product (more than 128 tiles) joins too when it leaves at least 32 compute
-// units idle: the plain product's tiles run there while its one long round lasts.  The paired
-// kernel always writes fp32 partial results, so the single slice goes through the summing kernel
-// like several would (same bits as the direct bf16 output: one rounding of the same fp32 value).
-bool pair_ok(int cfg_a, int depth_a, const SketchPlan &p) {
-    if (p.cfg == SK_NARROW) return false;
-    if (p.splits < 2 && !(p.tiles > 128 && p.tiles <= 224)) return false;
-    return cfg_a == GEMM_LARGE || (cfg_a == GEMM_SPLIT && depth_a == 4);
+// The plain product of a pass that is launched together with the pass's sketch product: 256 x 256
+// tiles where it fills the chip with them, else the 128 x 128 x 64 split tiles, whatever it would use
+// alone (both run with 512 threads, like the sketch kernels).
+PairPlain pair_plain(int64_t m, int64_t n, int64_t kk) {
+    PairPlain p;
+    p.large = tiles_of(m, n, ShapeLarge::BM, ShapeLarge::BN) >= 160;
+    p.depth = p.large ? 3 : plain_depth(kk, ShapeSplit::BK);
+    p.tiles = (int)(p.large ? tiles_of(m, n, ShapeLarge::BM, ShapeLarge::BN) : tiles_of(m, n, ShapeSplit::BM, ShapeSplit::BN));
+    return p;
 }
+
+// Whether a sketch product joins its pass's plain product: always with two or more token slices; an
+// unsliced one when it leaves at least 32 compute units idle (the plain tiles run there while its one
+// long round lasts).  The paired kernel always writes fp32 partial results, so a single slice goes
+// through the summing kernel like several would (same bits as the direct bf16 output: one rounding of
+// the same fp32 value).
+bool pair_ok(const SketchPlan &p) { return p.splits >= 2 || (p.tiles > 128 && p.tiles <= 224); }
 
 // Work-groups the sketch product of a pass should aim at when it is launched together with the
 // pass's plain product (`blocks_a` tiles, flops_a flop): if the plain product leaves compute units
@@ -223,12 +250,8 @@ int paired_sketch_target(int64_t blocks_a, double flops_a, double flops_sk) {
 SketchPlan plan_pass_sketch(int64_t n, int64_t d_sk, int64_t d_other, int64_t k) {
     // the plain product has an n x d_other output and contracts over d_sk
     const SketchPlan alone = plan_sketch(n, d_sk, k);
-    const int cfg_a = gemm_cfg(n, d_other, d_sk);
-    const int depth_a = cfg_a == GEMM_SPLIT ? plain_depth(d_sk, ShapeSplit::BK) : 3;
-    if (!pair_ok(cfg_a, depth_a, alone)) return alone;
-    const int64_t blocks_a = cfg_a == GEMM_LARGE ? tiles_of(n, d_other, ShapeLarge::BM, ShapeLarge::BN)
-                                                 : tiles_of(n, d_other, ShapeSplit::BM, ShapeSplit::BN);
-    const int target = paired_sketch_target(blocks_a, 2.0 * n * d_sk * d_other, 2.0 * n * k * d_sk);
+    if (!pair_ok(alone)) return alone;
+    const int target = paired_sketch_target(pair_plain(n, d_other, d_sk).tiles, 2.0 * n * d_sk * d_other, 2.0 * n * k * d_sk);
     SketchPlan paired = plan_sketch(n, d_sk, k, target);
     if (target == 256) {
         // Short slices (at most 1024 tokens) pack better into the time the plain product's work-groups
@@ -236,7 +259,7 @@ SketchPlan plan_pass_sketch(int64_t n, int64_t d_sk, int64_t d_other, int64_t k)
         const SketchPlan finer = plan_sketch(n, d_sk, k, 320);
         if (finer.splits > paired.splits && finer.k_chunk <= 1024) paired = finer;
     }
-    return paired.splits >= 2 || pair_ok(cfg_a, depth_a, paired) ? paired : alone;
+    return pair_ok(paired) ? paired : alone;
 }
 
 }  // namespace
@@ -250,16 +273,22 @@ bool mfma_shape_ok(int64_t n, int64_t d_in, int64_t d_out, int64_t k) {
     return d_in % 8 == 0 && d_out % 8 == 0 && d_in < lim && d_out < lim;
 }
 
+// `as_pair`: with the tiles the product has in its pass's paired launch, so that a pass whose products
+// are launched one by one (to be timed) gives the same bits.
+template <int BMODE>
+static hipError_t launch_plain_of_pass(const GemmArgs &g, bool as_pair, hipStream_t stream) {
+    if (!as_pair) return launch_gemm<A_KCONTIG, BMODE, OUT_BF16>(gemm_cfg(g.M, g.N, g.K), g, stream);
+    return launch_gemm<A_KCONTIG, BMODE, OUT_BF16>(pair_plain(g.M, g.N, g.K).large ? GEMM_LARGE : GEMM_SPLIT, g, stream);
+}
+
 hipError_t launch_linear_nt_bf16(const bf16_t *X, const bf16_t *W, const bf16_t *bias, bf16_t *Y, int64_t n,
-                                 int64_t d_in, int64_t d_out, hipStream_t stream) {
-    const GemmArgs g = args_nt(X, W, bias, Y, n, d_in, d_out);
-    return launch_gemm<A_KCONTIG, B_KCONTIG, OUT_BF16>(gemm_cfg(g.M, g.N, g.K), g, stream);
+                                 int64_t d_in, int64_t d_out, bool as_pair, hipStream_t stream) {
+    return launch_plain_of_pass<B_KCONTIG>(args_nt(X, W, bias, Y, n, d_in, d_out), as_pair, stream);
 }
 
 hipError_t launch_linear_nn_bf16(const bf16_t *dY, const bf16_t *W, bf16_t *dX, int64_t n, int64_t d_in,
-                                 int64_t d_out, hipStream_t stream) {
-    const GemmArgs g = args_nn(dY, W, dX, n, d_in, d_out);
-    return launch_gemm<A_KCONTIG, B_NCONTIG, OUT_BF16>(gemm_cfg(g.M, g.N, g.K), g, stream);
+                                 int64_t d_out, bool as_pair, hipStream_t stream) {
+    return launch_plain_of_pass<B_NCONTIG>(args_nn(dY, W, dX, n, d_in, d_out), as_pair, stream);
 }
 
 hipError_t launch_dw_bf16(const bf16_t *G, const bf16_t *X_proj, bf16_t *dW, int64_t k, int64_t d_in, int64_t d_out,
@@ -282,6 +311,17 @@ static hipError_t launch_dw_colsum(const GemmArgs &g, const ColsumArgs &c, hipSt
     return hipGetLastError();
 }
 
+template <int E>
+static hipError_t launch_few_dw_colsum(const GemmArgs &g, const ColsumArgs &c, hipStream_t stream) {
+    const int blocks_a = (int)tiles_of(g.M, g.N, E, E);
+    const unsigned grid = (unsigned)(blocks_a + colsum_blocks(c.d, 2));
+    if (g.K <= kFewSingle)
+        few_dw_colsum_kernel<E, true><<<grid, kFewThreads, 0, stream>>>(g, c, blocks_a);
+    else
+        few_dw_colsum_kernel<E, false><<<grid, kFewThreads, 0, stream>>>(g, c, blocks_a);
+    return hipGetLastError();
+}
+
 hipError_t launch_dw_colsum_bf16(const bf16_t *G, const bf16_t *X_proj, bf16_t *dW, int64_t k, int64_t d_in, int64_t d_out,
                                  const bf16_t *dY, bf16_t *dbias, int64_t n, hipStream_t stream, bool accumulate) {
     GemmArgs g{};
@@ -295,17 +335,17 @@ hipError_t launch_dw_colsum_bf16(const bf16_t *G, const bf16_t *X_proj, bf16_t *
             return e != hipSuccess ? e : launch_colsum<bf16_t>(dY, dbias, n, d_out, stream, accumulate);
         }
         case GEMM_SPLIT: return launch_dw_colsum<ShapeSplit>(g, c, stream);
-        case GEMM_TINY: return launch_dw_colsum<ShapeTiny>(g, c, stream);
+        case GEMM_FEW: return few_edge(g.M, g.N) == 32 ? launch_few_dw_colsum<32>(g, c, stream) : launch_few_dw_colsum<64>(g, c, stream);
         default: return launch_dw_colsum<ShapeMid>(g, c, stream);
     }
 }
 
 // |X^T dY|_F^2 per tile for the variance monitors: the dW-type product (both operands stored
 // [token][feature]) with the squared-norm epilogue; the tile menu of the other products without
-// its 64 x 64 entry.
+// its entry for few tiles.
 static int xty_cfg(int64_t m, int64_t n, int64_t kk) {
     const int cfg = gemm_cfg(m, n, kk);
-    return cfg == GEMM_TINY ? (kk >= 1536 ? GEMM_SPLIT : GEMM_MID) : cfg;
+    return cfg == GEMM_FEW ? (kk >= 1536 ? GEMM_SPLIT : GEMM_MID) : cfg;
 }
 
 int xty_sumsq_tiles(int64_t n, int64_t d_in, int64_t d_out) {
@@ -329,9 +369,7 @@ size_t sketch_workspace_bf16(int64_t n, int64_t d, int64_t k, int64_t d_other) {
     }
     if (d_other > 0) {  // inside a pass: a paired launch writes partial results even for a single slice
         const SketchPlan p = plan_pass_sketch(n, d, d_other, k);
-        const int cfg_a = gemm_cfg(n, d_other, d);
-        const bool paired = pair_ok(cfg_a, cfg_a == GEMM_SPLIT ? plain_depth(d, ShapeSplit::BK) : 3, p);
-        return p.splits > 1 || paired ? (size_t)p.splits * (size_t)k * (size_t)d * sizeof(float) : 0;
+        return p.splits > 1 || pair_ok(p) ? (size_t)p.splits * (size_t)k * (size_t)d * sizeof(float) : 0;
     }
     const int s = plan_sketch(n, d, k).splits;
     return s > 1 ? (size_t)s * (size_t)k * (size_t)d * sizeof(float) : 0;
@@ -366,11 +404,7 @@ hipError_t launch_sketch_bf16(const bf16_t *A, bf16_t *out, int64_t n, int64_t d
     return launch_reduce(ws, out, k, d, p.splits, stream);
 }
 
-bool forward_pair_available(int64_t n, int64_t d_in, int64_t d_out, int64_t k) {
-    if (k <= kSmallK) return false;
-    const int cfg = gemm_cfg(n, d_out, d_in);  // (the paired plan keeps >= 2 slices)
-    return pair_ok(cfg, cfg == GEMM_SPLIT ? plain_depth(d_in, ShapeSplit::BK) : 3, plan_sketch(n, d_in, k));
-}
+bool pass_pair_available(int64_t n, int64_t d_sk, int64_t k) { return k > kSmallK && pair_ok(plan_sketch(n, d_sk, k)); }
 
 hipError_t launch_forward_pair_bf16(const bf16_t *X, const bf16_t *W, const bf16_t *bias, bf16_t *Y, bf16_t *X_proj,
                                     int64_t n, int64_t d_in, int64_t d_out, int64_t k, int kind, SketchState st, void *ws,
@@ -379,39 +413,29 @@ hipError_t launch_forward_pair_bf16(const bf16_t *X, const bf16_t *W, const bf16
     const SketchPlan p = plan_pass_sketch(n, d_in, d_out, k);
     const GemmArgs gb = args_sketch(X, n, d_in, k, st, p, X_proj, ws, true);
     EventPair pev(ev_begin, ev_end, stream);
-    hipError_t e;
-    if (gemm_cfg(ga.M, ga.N, ga.K) == GEMM_LARGE)
-        e = launch_pair_nt(p.cfg, kind, ga, gb, (int)tiles_of(ga.M, ga.N, ShapeLarge::BM, ShapeLarge::BN), (int)p.tiles,
-                           p.splits, stream);
-    else
-        e = launch_pair_nt_split(p.cfg, kind, ga, gb, (int)tiles_of(ga.M, ga.N, ShapeSplit::BM, ShapeSplit::BN), (int)p.tiles,
-                                 p.splits, stream);
+    const hipError_t e = launch_pair_nt(pair_plain(ga.M, ga.N, ga.K), p.cfg, kind, ga, gb, (int)p.tiles, p.splits, stream);
     pev.done();
     if (e != hipSuccess) return e;
     return launch_reduce(ws, X_proj, k, d_in, p.splits, stream);
 }
 
-bool backward_pair_available(int64_t n, int64_t d_in, int64_t d_out, int64_t k) {
-    if (k <= kSmallK) return false;
-    const int cfg = gemm_cfg(n, d_in, d_out);
-    return pair_ok(cfg, cfg == GEMM_SPLIT ? plain_depth(d_out, ShapeSplit::BK) : 3, plan_sketch(n, d_out, k));
-}
-
 // Where the bias gradient goes in a backward pass that has the paired launch: into the launch of
-// dW when that leaves at least 64 compute units idle (dW is short and mostly latency); otherwise
-// into the paired launch when its last round leaves at least 16 idle (the sketch work-groups of
-// that round run for long, and dY is being read there anyway); otherwise into the launch of dW.
+// dW when that leaves at least 64 compute units idle (dW is short and mostly latency; where it runs on
+// few_tile, whose work-groups want a compute unit each, when the column blocks fit beside them);
+// otherwise into the paired launch when its last round leaves at least 16 idle (the sketch work-groups
+// of that round run for long, and dY is being read there anyway) or dW has no room; otherwise into
+// the launch of dW.
 bool backward_pair_takes_colsum(int64_t n, int64_t d_in, int64_t d_out, int64_t k) {
-    if (!backward_pair_available(n, d_in, d_out, k)) return false;
+    if (!pass_pair_available(n, d_out, k)) return false;
     const int dw_cfg = gemm_cfg(d_out, d_in, k);
-    const int64_t dw_tiles = dw_cfg == GEMM_LARGE ? tiles_of(d_out, d_in, ShapeLarge::BM, ShapeLarge::BN)
-                             : dw_cfg == GEMM_TINY ? tiles_of(d_out, d_in, ShapeTiny::BM, ShapeTiny::BN)
-                                                   : tiles_of(d_out, d_in, 128, 128);
+    if (dw_cfg == GEMM_FEW) {
+        const int edge = few_edge(d_out, d_in);
+        return tiles_of(d_out, d_in, edge, edge) + colsum_blocks(d_out, 2) > (edge == 64 ? 256 : 512);
+    }
+    const int64_t dw_tiles = dw_cfg == GEMM_LARGE ? tiles_of(d_out, d_in, ShapeLarge::BM, ShapeLarge::BN) : tiles_of(d_out, d_in, 128, 128);
     if ((256 - dw_tiles % 256) % 256 >= 64) return false;
-    const int64_t blocks_a = gemm_cfg(n, d_in, d_out) == GEMM_LARGE ? tiles_of(n, d_in, ShapeLarge::BM, ShapeLarge::BN)
-                                                                    : tiles_of(n, d_in, ShapeSplit::BM, ShapeSplit::BN);
     const SketchPlan p = plan_pass_sketch(n, d_out, d_in, k);
-    const int64_t total = blocks_a + p.tiles * p.splits;
+    const int64_t total = pair_plain(n, d_in, d_out).tiles + p.tiles * p.splits;
     return (256 - total % 256) % 256 >= 16;
 }
 
@@ -424,13 +448,7 @@ hipError_t launch_backward_pair_bf16(const bf16_t *dY, const bf16_t *W, bf16_t *
     const ColsumArgs gc{dY, dbias, n, d_out, accumulate_dbias ? 1 : 0, colsum_lpr(d_out, 2)};
     const ColsumArgs *gcp = dbias != nullptr ? &gc : nullptr;
     EventPair pev(ev_begin, ev_end, stream);
-    hipError_t e;
-    if (gemm_cfg(ga.M, ga.N, ga.K) == GEMM_LARGE)
-        e = launch_pair_nn_large(p.cfg, kind, ga, gb, (int)tiles_of(ga.M, ga.N, ShapeLarge::BM, ShapeLarge::BN), (int)p.tiles,
-                                 p.splits, stream, gcp);
-    else
-        e = launch_pair_nn_split(p.cfg, kind, ga, gb, (int)tiles_of(ga.M, ga.N, ShapeSplit::BM, ShapeSplit::BN), (int)p.tiles,
-                                 p.splits, stream, gcp);
+    const hipError_t e = launch_pair_nn(pair_plain(ga.M, ga.N, ga.K), p.cfg, kind, ga, gb, (int)p.tiles, p.splits, stream, gcp);
     pev.done();
     if (e != hipSuccess) return e;
     return launch_reduce(ws, G, k, d_out, p.splits, stream);

@@ -7,28 +7,36 @@
 namespace rmm {
 
 // Tile shape a plain product runs with (Shape typedefs of mfma_kernels.hpp) and a sketch product's kernel.
-enum { GEMM_LARGE = 0, GEMM_SPLIT = 1, GEMM_MID = 2, GEMM_TINY = 3 };
-enum { SK_NARROW = 0, SK_WIDE = 1, SK_WIDE64 = 2, SK_MID64 = 3, SK_MID = 4 };
+enum { GEMM_LARGE = 0, GEMM_SPLIT = 1, GEMM_MID = 2, GEMM_FEW = 3 };
+enum { SK_NARROW = 0, SK_WIDE = 1, SK_WIDE64 = 2, SK_MID64 = 3, SK_MID = 4, SK_NARROW64 = 5 };
 
-// One launch for a plain product (`ga`, `blocks_a` tiles) and a sketch product with an
-// LDS-generated tile (`gb`, `tiles_b` tiles x `splits` token slices, fp32 partial results).
-//   nt:       Y = X W^T, 256 x 256 tiles (GEMM_LARGE, prefetch depth 3)
-//   nt_split: Y = X W^T, 128 x 128 x 64 tiles with two wave groups (GEMM_SPLIT, depth 4)
-//   nn_large: dX = dY W, 256 x 256 tiles (GEMM_LARGE, depth 3)
-//   nn_split: dX = dY W, 128 x 128 x 64 tiles with two wave groups (GEMM_SPLIT, depth 4)
-// sk_cfg is one of SK_WIDE, SK_WIDE64, SK_MID64, SK_MID; anything else returns hipErrorInvalidValue.
+// The plain product of a paired launch: 256 x 256 tiles (depth 3) or 128 x 128 x 64 tiles with two wave
+// groups (depth 3 or 4, whichever pads the contraction less), and its number of tiles.
+struct PairPlain {
+    bool large;
+    int depth, tiles;
+};
+
+// One launch for a plain product (`ga`; nt: Y = X W^T, nn: dX = dY W) and a sketch product (`gb`, `tiles_b`
+// tiles x `splits` token slices, fp32 partial results) with the kernel sk_cfg.
 // `gc`, if not null, adds the column blocks of a column-sum problem (colsum.hpp) behind the sketch work-groups.
 // The sketch work-groups are put in front of the plain tiles when the sketch product is unsliced (few, long
 // work-groups) or the plain product fills the chip at least once (256 tiles or more: measured 4 % faster at the
 // RoBERTa-large shapes, 2-3 % slower where the plain product has 192 tiles and the sketch work-groups fill in behind).
-hipError_t launch_pair_nt(int sk_cfg, int kind, const GemmArgs &ga, const GemmArgs &gb, int blocks_a, int tiles_b,
+hipError_t launch_pair_nt(const PairPlain &plain, int sk_cfg, int kind, const GemmArgs &ga, const GemmArgs &gb, int tiles_b,
                           int splits, hipStream_t stream, const ColsumArgs *gc = nullptr);
-hipError_t launch_pair_nt_split(int sk_cfg, int kind, const GemmArgs &ga, const GemmArgs &gb, int blocks_a, int tiles_b,
-                                int splits, hipStream_t stream, const ColsumArgs *gc = nullptr);
-hipError_t launch_pair_nn_large(int sk_cfg, int kind, const GemmArgs &ga, const GemmArgs &gb, int blocks_a, int tiles_b,
-                                int splits, hipStream_t stream, const ColsumArgs *gc = nullptr);
-hipError_t launch_pair_nn_split(int sk_cfg, int kind, const GemmArgs &ga, const GemmArgs &gb, int blocks_a, int tiles_b,
-                                int splits, hipStream_t stream, const ColsumArgs *gc = nullptr);
+hipError_t launch_pair_nn(const PairPlain &plain, int sk_cfg, int kind, const GemmArgs &ga, const GemmArgs &gb, int tiles_b,
+                          int splits, hipStream_t stream, const ColsumArgs *gc = nullptr);
+// (one translation unit for each plain tile: large, split at depth 4, split at depth 3)
+#define RMM_PAIR_DECL(NAME)                                                                                               \
+    hipError_t launch_pair_##NAME(int sk_cfg, int kind, const GemmArgs &ga, const GemmArgs &gb, int blocks_a, int tiles_b, \
+                                  int splits, hipStream_t stream, const ColsumArgs *gc)
+RMM_PAIR_DECL(nt_large);
+RMM_PAIR_DECL(nt_split4);
+RMM_PAIR_DECL(nt_split3);
+RMM_PAIR_DECL(nn_large);
+RMM_PAIR_DECL(nn_split4);
+RMM_PAIR_DECL(nn_split3);
 
 // The same for the SORS sketch kind (mfma_pair_sors.hip): `gs` describes the sketch product, whose
 // strips go two to a work-group; cfg_a is GEMM_LARGE (depth 3) or GEMM_SPLIT (depth 4), row_indexed_b
@@ -38,7 +46,7 @@ struct SorsArgs;
 hipError_t launch_pair_sors(int cfg_a, bool row_indexed_b, const GemmArgs &ga, const SorsArgs &gs, int blocks_a, int chunks,
                             bool sors_first, hipStream_t stream);
 
-// Shared body of launch_pair_nt, _nt_split, _nn_large and _nn_split.
+// Shared body of the six launch_pair_{nt,nn}_*.
 template <typename SA, int BMODE_A, int DA>
 hipError_t launch_pair_impl(int sk_cfg, int kind, const GemmArgs &ga, const GemmArgs &gb, int blocks_a, int tiles_b,
                             int splits, hipStream_t stream, const ColsumArgs *gc) {
@@ -62,6 +70,8 @@ hipError_t launch_pair_impl(int sk_cfg, int kind, const GemmArgs &ga, const Gemm
         RMM_PAIR_CASE(SK_WIDE64, ShapeSkWide64)
         RMM_PAIR_CASE(SK_MID64, ShapeSkMid64)
         RMM_PAIR_CASE(SK_MID, ShapeSkMid)
+        RMM_PAIR_CASE(SK_NARROW64, ShapeSkNarrow64)
+        RMM_PAIR_CASE(SK_NARROW, ShapeSkNarrow)
         default: return hipErrorInvalidValue;
     }
 #undef RMM_PAIR_CASE
