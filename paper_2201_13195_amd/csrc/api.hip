@@ -145,7 +145,7 @@ int forward_impl(const rmm_layer_desc_t *d, SketchState st, const void *X, const
                                                 d->d_in, d->d_out, d->k, d->kind, st, stream));
     }
     if (X_proj != nullptr && sliced_sketch(d) && !separate_stage(ev.stage) &&
-        pass_pair_available(d->n, d->d_in, d->k)) {
+        pass_pair_available(d->k)) {
         const bool timed = ev.stage == RMM_STAGE_FWD_PAIR;
         return from_hip(launch_forward_pair_bf16((const bf16_t *)X, (const bf16_t *)W, (const bf16_t *)bias, (bf16_t *)Y,
                                                  (bf16_t *)X_proj, d->n, d->d_in, d->d_out, d->k, d->kind, st, ws, stream,
@@ -163,7 +163,7 @@ int forward_impl(const rmm_layer_desc_t *d, SketchState st, const void *X, const
         hipError_t e =
             mfma ? launch_linear_nt_bf16((const bf16_t *)X, (const bf16_t *)W, (const bf16_t *)bias, (bf16_t *)Y,
                                          d->n, d->d_in, d->d_out,
-                                         X_proj != nullptr && sliced_sketch(d) && pass_pair_available(d->n, d->d_in, d->k), stream)
+                                         X_proj != nullptr && sliced_sketch(d) && pass_pair_available(d->k), stream)
                  : launch_forward_plain<T>((const T *)X, (const T *)W, (const T *)bias, (T *)Y, nullptr, d->n, d->d_in,
                                            d->d_out, d->k, d->kind, st, stream);
         if (e != hipSuccess) return RMM_ERR_LAUNCH;
@@ -197,12 +197,12 @@ int backward_impl(const rmm_layer_desc_t *d, SketchState st, const void *dY, con
         if (e != hipSuccess) return RMM_ERR_LAUNCH;
     }
     const bool paired = paired_plain || paired_sors || (sliced_sketch(d) && dX != nullptr && !separate_stage(ev.stage) &&
-                                        pass_pair_available(d->n, d->d_out, d->k));
+                                        pass_pair_available(d->k));
     const bool own_db_stage = ev.stage == RMM_STAGE_BWD_DW || ev.stage == RMM_STAGE_BWD_DBIAS;
     bool db_done = paired_plain && ev.stage != RMM_STAGE_BWD_DBIAS;
     if (paired && !paired_sors && !paired_plain) {
         const bool timed = ev.stage == RMM_STAGE_BWD_PAIR;
-        db_done = dbias != nullptr && !own_db_stage && backward_pair_takes_colsum(d->n, d->d_in, d->d_out, d->k);
+        db_done = dbias != nullptr && !own_db_stage && backward_pair_takes_colsum(d->n, d->d_in, d->d_out, d->k, d->kind);
         e = launch_backward_pair_bf16((const bf16_t *)dY, (const bf16_t *)W, (bf16_t *)dX, (bf16_t *)G, d->n, d->d_in,
                                       d->d_out, d->k, d->kind, st, (char *)ws + g_bytes(d), stream,
                                       timed ? ev.begin : nullptr, timed ? ev.end : nullptr,
@@ -212,7 +212,7 @@ int backward_impl(const rmm_layer_desc_t *d, SketchState st, const void *dY, con
     if (!paired && dX != nullptr) {  // dX = dY W: B(kk, c) = W[kk][c]
         StageScope scope(ev, RMM_STAGE_BWD_DX, stream);
         e = mfma ? launch_linear_nn_bf16((const bf16_t *)dY, (const bf16_t *)W, (bf16_t *)dX, d->n, d->d_in, d->d_out,
-                                         sliced_sketch(d) && pass_pair_available(d->n, d->d_out, d->k), stream)
+                                         sliced_sketch(d) && pass_pair_available(d->k), stream)
                  : launch_backward_plain<T>((const T *)dY, (const T *)W, (T *)dX, nullptr, nullptr, d->n, d->d_in,
                                             d->d_out, d->k, d->kind, st, false, stream);
         if (e != hipSuccess) return RMM_ERR_LAUNCH;
@@ -284,8 +284,8 @@ int rmm_uses_paired_launch(const rmm_layer_desc_t *desc, int op) {
         if (op == RMM_OP_BACKWARD) return sors_pair_available(desc->n, desc->d_out, desc->d_in, desc->k) ? 1 : 0;
         return 0;
     }
-    if (op == RMM_OP_FORWARD) return pass_pair_available(desc->n, desc->d_in, desc->k) ? 1 : 0;
-    if (op == RMM_OP_BACKWARD) return pass_pair_available(desc->n, desc->d_out, desc->k) ? 1 : 0;
+    if (op == RMM_OP_FORWARD) return pass_pair_available(desc->k) ? 1 : 0;
+    if (op == RMM_OP_BACKWARD) return pass_pair_available(desc->k) ? 1 : 0;
     return 0;
 }
 

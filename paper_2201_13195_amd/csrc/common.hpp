@@ -83,10 +83,9 @@ hipError_t launch_sketch_bf16(const bf16_t *A, bf16_t *out, int64_t n, int64_t d
 // One launch for the two products of a pass that do not depend on each other: Y = X W^T (+ bias)
 // with the sketch product of X (forward), dX = dY W with the sketch product of dY (backward; G is
 // k x d_out), followed by the sum over the sketch's token slices.  Results are bit-identical to
-// the separate launches above (same kernels, same slices).  Only where pass_pair_available() says so
-// (d_sk = the width of the sketched operand: d_in forward, d_out backward);
+// the separate launches above (same kernels, same slices).  Only where pass_pair_available() says so;
 // the optional event pair brackets the paired kernel alone.
-bool pass_pair_available(int64_t n, int64_t d_sk, int64_t k);
+bool pass_pair_available(int64_t k);
 hipError_t launch_forward_pair_bf16(const bf16_t *X, const bf16_t *W, const bf16_t *bias, bf16_t *Y, bf16_t *X_proj,
                                     int64_t n, int64_t d_in, int64_t d_out, int64_t k, int kind, SketchState st, void *ws,
                                     hipStream_t stream, hipEvent_t ev_begin = nullptr, hipEvent_t ev_end = nullptr);
@@ -96,7 +95,7 @@ hipError_t launch_backward_pair_bf16(const bf16_t *dY, const bf16_t *W, bf16_t *
                                      int64_t d_out, int64_t k, int kind, SketchState st, void *ws, hipStream_t stream,
                                      hipEvent_t ev_begin = nullptr, hipEvent_t ev_end = nullptr, bf16_t *dbias = nullptr,
                                      bool accumulate_dbias = false);
-bool backward_pair_takes_colsum(int64_t n, int64_t d_in, int64_t d_out, int64_t k);
+bool backward_pair_takes_colsum(int64_t n, int64_t d_in, int64_t d_out, int64_t k, int kind);
 
 // SORS sketch kind, bf16 (sors.hip): signs, Walsh-Hadamard transform along the tokens and row
 // selection in one kernel, no workspace.  Usable when sors_fast_ok(): d a multiple of 8 and at most

@@ -1,5 +1,6 @@
 // bf16 MFMA path of the RMM layer: which kernel of mfma_kernels.hpp serves which product at
 // which shape, and the launches.
+#include "../../include/rmm.h"
 #include "mfma_pair.hpp"
 #include "sors_kernels.hpp"
 
@@ -91,74 +92,96 @@ GemmArgs args_nn(const bf16_t *dY, const bf16_t *W, bf16_t *dX, int64_t n, int64
 
 // Which kernel serves a sketch product with k > 64 and how its token dimension is cut.  The work-group
 // generates the sketch tile into LDS and all eight waves read it.
-//   Rows: 64-row tiles for k <= 512 (k = 410 pads to 448 rows instead of 512), and up to k = 1024 while
-//     the contraction is short (at most 8192 tokens: (3001 x 1304, k = 600) 27.5 -> 23.1 us); longer ones
-//     want 128 rows (B tiles are staged half as often: (16384 x 1024, k = 1638) 84 against 100 us).
-//   Columns: of 512, 384 and 256 the one whose padded width costs least (an entry is generated once per
-//     tile column; measured weights), but 256 where even one slice per 128 tokens leaves less than one
-//     work-group per compute unit ((1500 x 3000, k = 150) 18.7 -> 17.0 us).
-// Tokens are cut into `splits` slices of `k_chunk` tokens (a multiple of 128) so that about
-// `target_wgs` work-groups exist (256 = one per compute unit; measured: more or fewer are slower
-// when the product runs alone); with more than one slice the kernel writes fp32 partial results
-// to workspace and reduce_partials_kernel sums them in slice order.
 struct SketchPlan {
     int cfg, splits;
     int64_t k_chunk, tiles;
 };
 
-SketchPlan plan_sketch(int64_t n, int64_t d, int64_t k, int target_wgs = 256) {
-    SketchPlan p;
+// Tokens are cut into `splits` slices of `k_chunk` tokens (a multiple of 128) so that about
+// `target_wgs` work-groups exist (256 = one per compute unit; measured: more or fewer are slower
+// when the product runs alone); with more than one slice the kernel writes fp32 partial results
+// to workspace and reduce_partials_kernel sums them in slice order.
+void slice_sketch(SketchPlan &p, int64_t n, int target_wgs) {
     const int64_t blocks = (n + 127) / 128;
-    const bool rows64 = k <= 512 || (k <= 1024 && n <= 8192);
-    const int64_t bm = rows64 ? 64 : 128;
-    const int64_t w512 = (d + 511) / 512 * 512 * 100, w384 = (d + 383) / 384 * 384 * 103, w256 = (d + 255) / 256 * 256 * 112;
-    int64_t bn = w512 <= w384 && w512 <= w256 ? 512 : w384 <= w256 ? 384 : 256;
-    if (tiles_of(k, d, bm, bn) * blocks < 256) bn = 256;
-    p.cfg = bn == 512 ? (rows64 ? SK_WIDE64 : SK_WIDE) : bn == 384 ? (rows64 ? SK_MID64 : SK_MID) : (rows64 ? SK_NARROW64 : SK_NARROW);
-    p.tiles = tiles_of(k, d, bm, bn);
     int64_t s = target_wgs / p.tiles;
     if (s > blocks) s = blocks;
     if (s > 64) s = 64;
     if (s < 1) s = 1;
     p.k_chunk = (blocks + s - 1) / s * 128;
     p.splits = (int)((n + p.k_chunk - 1) / p.k_chunk);
-    return p;
+}
+
+// The tile is the one of the menu whose time comes out lowest: rounds of 256 work-groups, each as long as
+// its slice's 32-token steps, plus the partial results.  The times of a step on a full chip are a least-squares
+// fit over ten shapes from 4096 x 768, k = 410 to 16384 x 4096, k = 1638 (within 6 % rms); partial results
+// cost 0.13 us per MB written and read (they mostly stay in the last-level cache).  What that weighs: padding
+// of k and d, entries generated once per 512, 384 or 256 columns, operand columns staged once per 128 or 64
+// rows, and filling the chip when tokens are few.  ((3001 x 1304, k = 600) 64 x 512: 22.0 us, 128 x 512: 26.4;
+// (16384 x 4096, k = 410) 98 and 92; (32000 x 512, k = 640), Rademacher, 64 x 512: 50, 128 x 256: 41.)
+SketchPlan plan_sketch(int64_t n, int64_t d, int64_t k, int kind, int target_wgs = 256) {
+    struct Entry {
+        int cfg;
+        int64_t bm, bn;
+        double step_us[2];  // Gaussian, Rademacher
+    };
+    static const Entry menu[] = {{SK_WIDE64, 64, 512, {0.66, 0.63}}, {SK_WIDE, 128, 512, {1.01, 0.83}},
+                                 {SK_MID64, 64, 384, {0.59, 0.56}},  {SK_MID, 128, 384, {0.85, 0.69}},
+                                 {SK_NARROW64, 64, 256, {0.56, 0.53}}, {SK_NARROW, 128, 256, {0.75, 0.60}}};
+    // rmm_sketch_static serves the shapes whose partial results fit RMM_STATIC_SCRATCH_BYTES with the plainest
+    // tiling (rows by k, columns by d); those keep fitting, whichever tile they run with.
+    auto partial_bytes = [&](const SketchPlan &p) { return p.splits > 1 ? (double)p.splits * (double)k * (double)d * 4.0 : 0.0; };
+    SketchPlan plainest;
+    plainest.tiles = d >= 1024 ? tiles_of(k, d, k <= 512 ? 64 : 128, 512) : d % 384 == 0 ? tiles_of(k, d, k <= 512 ? 64 : 128, 384) : tiles_of(k, d, 128, 256);
+    slice_sketch(plainest, n, 256);
+    const double limit = partial_bytes(plainest) <= (double)RMM_STATIC_SCRATCH_BYTES ? (double)RMM_STATIC_SCRATCH_BYTES : 1.0e30;
+    SketchPlan best{};
+    double best_us = -1.0;
+    for (const Entry &e : menu) {
+        SketchPlan p;
+        p.cfg = e.cfg, p.tiles = tiles_of(k, d, e.bm, e.bn);
+        slice_sketch(p, n, 256);
+        if (partial_bytes(p) > limit) continue;  // (never all of them: the plainest tiling is on the menu)
+        const double rounds = (double)((p.tiles * p.splits + 255) / 256), steps = (double)(p.k_chunk / 32);
+        const double us = rounds * steps * e.step_us[kind != 0] + (p.splits > 1 ? (double)p.splits * (double)k * (double)d * 1.05e-6 : 0.0);
+        if (best_us < 0.0 || us < 0.97 * best_us) best = p, best_us = us;  // (ties: the wider tile pairs better)
+    }
+    slice_sketch(best, n, target_wgs);
+    return best;
 }
 
 GemmArgs args_sketch(const bf16_t *A, int64_t n, int64_t d, int64_t k, SketchState st, const SketchPlan &p, bf16_t *out,
-                     void *ws, bool always_partial = false) {
+                     void *ws) {
     GemmArgs g{};
     g.A = nullptr, g.lda = 0, g.B = A, g.ldb = d, g.bias = nullptr;
     g.M = k, g.N = d, g.K = n, g.st = st, g.ldc = d, g.k_chunk = p.k_chunk;
-    if (p.splits == 1 && !always_partial) {
-        g.C = out, g.alpha = 1.0f / sqrtf((float)k);
+    if (p.splits == 1) {
+        g.C = out, g.alpha = 1.0f / sqrtf((float)k), g.direct = 1;
     } else {
         g.C = ws, g.alpha = 1.0f, g.split_stride = k * d;
     }
     return g;
 }
 
-template <int OUT>
 hipError_t launch_sketch_cfg(int cfg, int kind, const GemmArgs &g, int splits, hipStream_t stream) {
     switch (cfg) {
         case SK_WIDE:
-            return kind == 0 ? launch<ShapeSkWide, A_GAUSS_LDS, B_NCONTIG, OUT>(g, splits, stream)
-                             : launch<ShapeSkWide, A_RADEM_LDS, B_NCONTIG, OUT>(g, splits, stream);
+            return kind == 0 ? launch<ShapeSkWide, A_GAUSS_LDS, B_NCONTIG, OUT_F32_PARTIAL>(g, splits, stream)
+                             : launch<ShapeSkWide, A_RADEM_LDS, B_NCONTIG, OUT_F32_PARTIAL>(g, splits, stream);
         case SK_WIDE64:
-            return kind == 0 ? launch<ShapeSkWide64, A_GAUSS_LDS, B_NCONTIG, OUT>(g, splits, stream)
-                             : launch<ShapeSkWide64, A_RADEM_LDS, B_NCONTIG, OUT>(g, splits, stream);
+            return kind == 0 ? launch<ShapeSkWide64, A_GAUSS_LDS, B_NCONTIG, OUT_F32_PARTIAL>(g, splits, stream)
+                             : launch<ShapeSkWide64, A_RADEM_LDS, B_NCONTIG, OUT_F32_PARTIAL>(g, splits, stream);
         case SK_MID64:
-            return kind == 0 ? launch<ShapeSkMid64, A_GAUSS_LDS, B_NCONTIG, OUT>(g, splits, stream)
-                             : launch<ShapeSkMid64, A_RADEM_LDS, B_NCONTIG, OUT>(g, splits, stream);
+            return kind == 0 ? launch<ShapeSkMid64, A_GAUSS_LDS, B_NCONTIG, OUT_F32_PARTIAL>(g, splits, stream)
+                             : launch<ShapeSkMid64, A_RADEM_LDS, B_NCONTIG, OUT_F32_PARTIAL>(g, splits, stream);
         case SK_MID:
-            return kind == 0 ? launch<ShapeSkMid, A_GAUSS_LDS, B_NCONTIG, OUT>(g, splits, stream)
-                             : launch<ShapeSkMid, A_RADEM_LDS, B_NCONTIG, OUT>(g, splits, stream);
+            return kind == 0 ? launch<ShapeSkMid, A_GAUSS_LDS, B_NCONTIG, OUT_F32_PARTIAL>(g, splits, stream)
+                             : launch<ShapeSkMid, A_RADEM_LDS, B_NCONTIG, OUT_F32_PARTIAL>(g, splits, stream);
         case SK_NARROW64:
-            return kind == 0 ? launch<ShapeSkNarrow64, A_GAUSS_LDS, B_NCONTIG, OUT>(g, splits, stream)
-                             : launch<ShapeSkNarrow64, A_RADEM_LDS, B_NCONTIG, OUT>(g, splits, stream);
+            return kind == 0 ? launch<ShapeSkNarrow64, A_GAUSS_LDS, B_NCONTIG, OUT_F32_PARTIAL>(g, splits, stream)
+                             : launch<ShapeSkNarrow64, A_RADEM_LDS, B_NCONTIG, OUT_F32_PARTIAL>(g, splits, stream);
         default:
-            return kind == 0 ? launch<ShapeSkNarrow, A_GAUSS_LDS, B_NCONTIG, OUT>(g, splits, stream)
-                             : launch<ShapeSkNarrow, A_RADEM_LDS, B_NCONTIG, OUT>(g, splits, stream);
+            return kind == 0 ? launch<ShapeSkNarrow, A_GAUSS_LDS, B_NCONTIG, OUT_F32_PARTIAL>(g, splits, stream)
+                             : launch<ShapeSkNarrow, A_RADEM_LDS, B_NCONTIG, OUT_F32_PARTIAL>(g, splits, stream);
     }
 }
 
@@ -228,13 +251,6 @@ PairPlain pair_plain(int64_t m, int64_t n, int64_t kk) {
     return p;
 }
 
-// Whether a sketch product joins its pass's plain product: always with two or more token slices; an
-// unsliced one when it leaves at least 32 compute units idle (the plain tiles run there while its one
-// long round lasts).  The paired kernel always writes fp32 partial results, so a single slice goes
-// through the summing kernel like several would (same bits as the direct bf16 output: one rounding of
-// the same fp32 value).
-bool pair_ok(const SketchPlan &p) { return p.splits >= 2 || (p.tiles > 128 && p.tiles <= 224); }
-
 // Work-groups the sketch product of a pass should aim at when it is launched together with the
 // pass's plain product (`blocks_a` tiles, flops_a flop): if the plain product leaves compute units
 // idle in its last round and runs long enough for the whole sketch product (flops_sk, at about half
@@ -247,19 +263,19 @@ int paired_sketch_target(int64_t blocks_a, double flops_a, double flops_sk) {
 }
 
 // Plan of the sketch product of X (forward) / dY (backward) inside a layer call.
-SketchPlan plan_pass_sketch(int64_t n, int64_t d_sk, int64_t d_other, int64_t k) {
+SketchPlan plan_pass_sketch(int64_t n, int64_t d_sk, int64_t d_other, int64_t k, int kind) {
     // the plain product has an n x d_other output and contracts over d_sk
-    const SketchPlan alone = plan_sketch(n, d_sk, k);
-    if (!pair_ok(alone)) return alone;
+    const SketchPlan alone = plan_sketch(n, d_sk, k, kind);
+    if (alone.splits == 1) return alone;
     const int target = paired_sketch_target(pair_plain(n, d_other, d_sk).tiles, 2.0 * n * d_sk * d_other, 2.0 * n * k * d_sk);
-    SketchPlan paired = plan_sketch(n, d_sk, k, target);
+    SketchPlan paired = plan_sketch(n, d_sk, k, kind, target);
     if (target == 256) {
         // Short slices (at most 1024 tokens) pack better into the time the plain product's work-groups
         // take when there are a quarter more of them; long ones would only add a round.
-        const SketchPlan finer = plan_sketch(n, d_sk, k, 320);
+        const SketchPlan finer = plan_sketch(n, d_sk, k, kind, 320);
         if (finer.splits > paired.splits && finer.k_chunk <= 1024) paired = finer;
     }
-    return pair_ok(paired) ? paired : alone;
+    return paired.splits >= 2 ? paired : alone;
 }
 
 }  // namespace
@@ -361,18 +377,20 @@ hipError_t launch_xty_sumsq_bf16(const bf16_t *X, const bf16_t *dY, double *part
     return launch_gemm<A_MCONTIG, B_NCONTIG, OUT_SUMSQ>(xty_cfg(g.M, g.N, g.K), g, stream);
 }
 
+// The two dense kinds may take different tiles and slices; a workspace serves either.
 size_t sketch_workspace_bf16(int64_t n, int64_t d, int64_t k, int64_t d_other) {
     int64_t k_chunk;
+    size_t most = 0;
     if (k <= kSmallK) {
         const int s = smallk_slices(n, d, k, &k_chunk);
         return s > 1 ? (size_t)s * (size_t)k * (size_t)d * sizeof(float) : 0;
     }
-    if (d_other > 0) {  // inside a pass: a paired launch writes partial results even for a single slice
-        const SketchPlan p = plan_pass_sketch(n, d, d_other, k);
-        return p.splits > 1 || pair_ok(p) ? (size_t)p.splits * (size_t)k * (size_t)d * sizeof(float) : 0;
+    for (int kind = 0; kind < 2; ++kind) {
+        const SketchPlan p = d_other > 0 ? plan_pass_sketch(n, d, d_other, k, kind) : plan_sketch(n, d, k, kind);
+        const size_t bytes = p.splits > 1 ? (size_t)p.splits * (size_t)k * (size_t)d * sizeof(float) : 0;
+        if (bytes > most) most = bytes;
     }
-    const int s = plan_sketch(n, d, k).splits;
-    return s > 1 ? (size_t)s * (size_t)k * (size_t)d * sizeof(float) : 0;
+    return most;
 }
 
 hipError_t launch_sketch_bf16(const bf16_t *A, bf16_t *out, int64_t n, int64_t d, int64_t k, int kind, SketchState st,
@@ -395,27 +413,26 @@ hipError_t launch_sketch_bf16(const bf16_t *A, bf16_t *out, int64_t n, int64_t d
         if (e != hipSuccess || slices == 1) return e;
         return launch_reduce(ws, out, k, d, slices, stream);
     }
-    const SketchPlan p = d_other > 0 ? plan_pass_sketch(n, d, d_other, k) : plan_sketch(n, d, k);
+    const SketchPlan p = d_other > 0 ? plan_pass_sketch(n, d, d_other, k, kind) : plan_sketch(n, d, k, kind);
     const GemmArgs g = args_sketch(A, n, d, k, st, p, out, ws);
-    if (p.splits == 1) return launch_sketch_cfg<OUT_BF16>(p.cfg, kind, g, 1, stream);
-    hipError_t e = launch_sketch_cfg<OUT_F32_PARTIAL>(p.cfg, kind, g, p.splits, stream);
+    hipError_t e = launch_sketch_cfg(p.cfg, kind, g, p.splits, stream);
     pev.done();
-    if (e != hipSuccess) return e;
+    if (e != hipSuccess || p.splits == 1) return e;
     return launch_reduce(ws, out, k, d, p.splits, stream);
 }
 
-bool pass_pair_available(int64_t n, int64_t d_sk, int64_t k) { return k > kSmallK && pair_ok(plan_sketch(n, d_sk, k)); }
+bool pass_pair_available(int64_t k) { return k > kSmallK; }
 
 hipError_t launch_forward_pair_bf16(const bf16_t *X, const bf16_t *W, const bf16_t *bias, bf16_t *Y, bf16_t *X_proj,
                                     int64_t n, int64_t d_in, int64_t d_out, int64_t k, int kind, SketchState st, void *ws,
                                     hipStream_t stream, hipEvent_t ev_begin, hipEvent_t ev_end) {
     const GemmArgs ga = args_nt(X, W, bias, Y, n, d_in, d_out);
-    const SketchPlan p = plan_pass_sketch(n, d_in, d_out, k);
-    const GemmArgs gb = args_sketch(X, n, d_in, k, st, p, X_proj, ws, true);
+    const SketchPlan p = plan_pass_sketch(n, d_in, d_out, k, kind);
+    const GemmArgs gb = args_sketch(X, n, d_in, k, st, p, X_proj, ws);
     EventPair pev(ev_begin, ev_end, stream);
     const hipError_t e = launch_pair_nt(pair_plain(ga.M, ga.N, ga.K), p.cfg, kind, ga, gb, (int)p.tiles, p.splits, stream);
     pev.done();
-    if (e != hipSuccess) return e;
+    if (e != hipSuccess || p.splits == 1) return e;
     return launch_reduce(ws, X_proj, k, d_in, p.splits, stream);
 }
 
@@ -425,8 +442,8 @@ hipError_t launch_forward_pair_bf16(const bf16_t *X, const bf16_t *W, const bf16
 // otherwise into the paired launch when its last round leaves at least 16 idle (the sketch work-groups
 // of that round run for long, and dY is being read there anyway) or dW has no room; otherwise into
 // the launch of dW.
-bool backward_pair_takes_colsum(int64_t n, int64_t d_in, int64_t d_out, int64_t k) {
-    if (!pass_pair_available(n, d_out, k)) return false;
+bool backward_pair_takes_colsum(int64_t n, int64_t d_in, int64_t d_out, int64_t k, int kind) {
+    if (!pass_pair_available(k)) return false;
     const int dw_cfg = gemm_cfg(d_out, d_in, k);
     if (dw_cfg == GEMM_FEW) {
         const int edge = few_edge(d_out, d_in);
@@ -434,7 +451,7 @@ bool backward_pair_takes_colsum(int64_t n, int64_t d_in, int64_t d_out, int64_t 
     }
     const int64_t dw_tiles = dw_cfg == GEMM_LARGE ? tiles_of(d_out, d_in, ShapeLarge::BM, ShapeLarge::BN) : tiles_of(d_out, d_in, 128, 128);
     if ((256 - dw_tiles % 256) % 256 >= 64) return false;
-    const SketchPlan p = plan_pass_sketch(n, d_out, d_in, k);
+    const SketchPlan p = plan_pass_sketch(n, d_out, d_in, k, kind);
     const int64_t total = pair_plain(n, d_in, d_out).tiles + p.tiles * p.splits;
     return (256 - total % 256) % 256 >= 16;
 }
@@ -443,14 +460,14 @@ hipError_t launch_backward_pair_bf16(const bf16_t *dY, const bf16_t *W, bf16_t *
                                      int64_t d_out, int64_t k, int kind, SketchState st, void *ws, hipStream_t stream,
                                      hipEvent_t ev_begin, hipEvent_t ev_end, bf16_t *dbias, bool accumulate_dbias) {
     const GemmArgs ga = args_nn(dY, W, dX, n, d_in, d_out);
-    const SketchPlan p = plan_pass_sketch(n, d_out, d_in, k);
-    const GemmArgs gb = args_sketch(dY, n, d_out, k, st, p, G, ws, true);
+    const SketchPlan p = plan_pass_sketch(n, d_out, d_in, k, kind);
+    const GemmArgs gb = args_sketch(dY, n, d_out, k, st, p, G, ws);
     const ColsumArgs gc{dY, dbias, n, d_out, accumulate_dbias ? 1 : 0, colsum_lpr(d_out, 2)};
     const ColsumArgs *gcp = dbias != nullptr ? &gc : nullptr;
     EventPair pev(ev_begin, ev_end, stream);
     const hipError_t e = launch_pair_nn(pair_plain(ga.M, ga.N, ga.K), p.cfg, kind, ga, gb, (int)p.tiles, p.splits, stream, gcp);
     pev.done();
-    if (e != hipSuccess) return e;
+    if (e != hipSuccess || p.splits == 1) return e;
     return launch_reduce(ws, G, k, d_out, p.splits, stream);
 }
 
