@@ -412,11 +412,11 @@ int rmm_variance_stats(const rmm_layer_desc_t *desc, const void *X, const void *
     double *rows = (double *)ws, *xty = rows + 3 * (size_t)nb;
     hipError_t e;
     if (desc->dtype == RMM_DTYPE_BF16) {
-        e = launch_row_norms<bf16_t>((const bf16_t *)X, (const bf16_t *)dY, desc->n, desc->d_in, desc->d_out, rows, s);
-        if (e != hipSuccess) return RMM_ERR_LAUNCH;
         if (use_mfma(desc)) {
-            e = launch_xty_sumsq_bf16((const bf16_t *)X, (const bf16_t *)dY, xty, desc->n, desc->d_in, desc->d_out, s);
+            e = launch_xty_norms_bf16((const bf16_t *)X, (const bf16_t *)dY, xty, rows, desc->n, desc->d_in, desc->d_out, s);
         } else {
+            e = launch_row_norms<bf16_t>((const bf16_t *)X, (const bf16_t *)dY, desc->n, desc->d_in, desc->d_out, rows, s);
+            if (e != hipSuccess) return RMM_ERR_LAUNCH;
             float *P = (float *)((char *)ws + var_partial_bytes(desc));  // P(i, j) = sum_t X[t][i] dY[t][j]
             e = launch_tn_plain<bf16_t, float>((const bf16_t *)X, (const bf16_t *)dY, P, desc->d_in, desc->d_out, desc->n, s);
             if (e == hipSuccess) e = launch_sumsq(P, desc->d_in * desc->d_out, xty, s);

@@ -124,9 +124,10 @@ hipError_t launch_row_norms(const T *X, const T *Y, int64_t n, int64_t d_in, int
 //   part[b] = per-block sum of squares of an fp32 buffer; sumsq_blocks(elems) blocks.
 int sumsq_blocks(int64_t elems);
 hipError_t launch_sumsq(const float *A, int64_t elems, double *part, hipStream_t stream);
-//   part[t] = sum of squares of tile t of X^T dY (d_in x d_out), bf16 MFMA path; xty_sumsq_tiles() tiles.
+//   part[t] = sum of squares of tile t of X^T dY (d_in x d_out), bf16 MFMA path; xty_sumsq_tiles() tiles;
+//   rows = the row norms (part of launch_row_norms), in the same launch.
 int xty_sumsq_tiles(int64_t n, int64_t d_in, int64_t d_out);
-hipError_t launch_xty_sumsq_bf16(const bf16_t *X, const bf16_t *dY, double *part, int64_t n, int64_t d_in,
+hipError_t launch_xty_norms_bf16(const bf16_t *X, const bf16_t *dY, double *part, double *rows, int64_t n, int64_t d_in,
                                  int64_t d_out, hipStream_t stream);
 hipError_t launch_variance_finalize(const double *rows, int nb, const double *xty, int nt, int64_t n, int64_t k,
                                     int kind, double *out, hipStream_t stream);

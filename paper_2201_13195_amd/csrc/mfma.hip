@@ -369,12 +369,28 @@ int xty_sumsq_tiles(int64_t n, int64_t d_in, int64_t d_out) {
     return (int)tiles_of(d_in, d_out, large ? ShapeLarge::BM : 128, large ? ShapeLarge::BN : 128);
 }
 
-hipError_t launch_xty_sumsq_bf16(const bf16_t *X, const bf16_t *dY, double *part, int64_t n, int64_t d_in,
+template <typename S>
+static hipError_t launch_xty_norms(const GemmArgs &g, const RowNormArgs &r, hipStream_t stream) {
+    const int tiles = (int)tiles_of(g.M, g.N, S::BM, S::BN);
+    const unsigned grid = (unsigned)(tiles + row_norm_blocks(r.n));
+    if (std::is_same<S, ShapeLarge>::value || plain_depth(g.K, S::BK) == 3)
+        xty_norms_kernel<S, 3><<<grid, S::THREADS, 0, stream>>>(g, r, tiles);
+    else if constexpr (!std::is_same<S, ShapeLarge>::value)
+        xty_norms_kernel<S, 4><<<grid, S::THREADS, 0, stream>>>(g, r, tiles);
+    return hipGetLastError();
+}
+
+hipError_t launch_xty_norms_bf16(const bf16_t *X, const bf16_t *dY, double *part, double *rows, int64_t n, int64_t d_in,
                                  int64_t d_out, hipStream_t stream) {
     GemmArgs g{};
     g.A = X, g.lda = d_in, g.B = dY, g.ldb = d_out, g.C = part, g.ldc = d_out, g.bias = nullptr;
     g.M = d_in, g.N = d_out, g.K = n, g.alpha = 1.0f, g.k_chunk = (n + 127) / 128 * 128;
-    return launch_gemm<A_MCONTIG, B_NCONTIG, OUT_SUMSQ>(xty_cfg(g.M, g.N, g.K), g, stream);
+    const RowNormArgs r{X, dY, n, d_in, d_out, 1, rows};
+    switch (xty_cfg(g.M, g.N, g.K)) {
+        case GEMM_LARGE: return launch_xty_norms<ShapeLarge>(g, r, stream);
+        case GEMM_SPLIT: return launch_xty_norms<ShapeSplit>(g, r, stream);
+        default: return launch_xty_norms<ShapeMid>(g, r, stream);
+    }
 }
 
 // The two dense kinds may take different tiles and slices; a workspace serves either.
