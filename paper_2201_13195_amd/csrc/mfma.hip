@@ -68,7 +68,14 @@ hipError_t launch_few(const GemmArgs &g, hipStream_t stream) {
 
 template <int AMODE, int BMODE, int OUT>
 hipError_t launch_gemm(int cfg, const GemmArgs &g, hipStream_t stream) {
-    if (cfg == GEMM_LARGE) return launch<ShapeLarge, AMODE, BMODE, OUT>(g, 1, stream);
+    if (cfg == GEMM_LARGE) {
+        if constexpr (AMODE == A_KCONTIG && OUT == OUT_BF16) {
+            gemm_dma_kernel<BMODE><<<(unsigned)tiles_of(g.M, g.N, DmaTile::BM, DmaTile::BN), DmaTile::THREADS, 0, stream>>>(g);
+            return hipGetLastError();
+        } else {
+            return launch<ShapeLarge, AMODE, BMODE, OUT>(g, 1, stream);
+        }
+    }
     if (cfg == GEMM_SPLIT) return launch<ShapeSplit, AMODE, BMODE, OUT>(g, 1, stream);
     if constexpr (OUT == OUT_BF16)
         if (cfg == GEMM_FEW)

@@ -14,19 +14,19 @@ constexpr int kPairChunkLog = 11;  // chunks of 2048 tokens, as the strip kernel
 template <typename SA, int BMODE_A, int DA>
 __global__ void __launch_bounds__(SA::THREADS) gemm_sors_pair_kernel(GemmArgs ga, SorsArgs gs, int blocks_a, int chunks,
                                                                      int sors_first) {
-    typedef Tile<SA::BM, SA::BN, SA::BK, SA::WM, SA::WN, SA::WK, A_KCONTIG, BMODE_A, OUT_BF16> TA;
+    typedef PlainOfPass<SA, BMODE_A, DA> PA;
     typedef StripShape<kPairChunkLog> SS;
     static_assert(SA::THREADS == 512, "two strips of 256 threads");
-    constexpr int BYTES_A = TA::STAGES * TA::STAGE_ELEMS * 2, PLANE_BYTES = 2 * SS::REGION * 16;
+    constexpr int BYTES_A = PA::LDS_BYTES, PLANE_BYTES = 2 * SS::REGION * 16;
     constexpr int BYTES_S = PLANE_BYTES + 1024 * 4;
-    __shared__ __attribute__((aligned(16))) unsigned char lds[BYTES_A > BYTES_S ? BYTES_A : BYTES_S];
+    __shared__ __attribute__((aligned(1024))) unsigned char lds[BYTES_A > BYTES_S ? BYTES_A : BYTES_S];
     // The strips come last in the grid when they are to fill the compute units the plain product's
     // last round leaves idle, first when the plain product runs several full rounds and the (long)
     // strips should start with it rather than after it.
     const int strips = (int)gridDim.x - blocks_a;
     const int plain = sors_first ? (int)blockIdx.x - strips : (int)blockIdx.x;
     if (plain >= 0 && plain < blocks_a)
-        gemm_tile<SA, A_KCONTIG, BMODE_A, OUT_BF16, DA>(ga, reinterpret_cast<bf16_t *>(lds), plain, blocks_a, 0);
+        PA::run(ga, reinterpret_cast<bf16_t *>(lds), plain, blocks_a);
     else
         sors_strip_body<kPairChunkLog, true, 2>(gs, chunks, reinterpret_cast<float4 *>(lds),
                                                 reinterpret_cast<uint32_t *>(lds + PLANE_BYTES),
