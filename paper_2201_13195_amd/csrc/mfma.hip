@@ -21,7 +21,7 @@ template <typename S, int AMODE, int BMODE, int OUT>
 hipError_t launch(const GemmArgs &g, int splits, hipStream_t stream) {
     const int64_t tiles = ((g.M + S::BM - 1) / S::BM) * ((g.N + S::BN - 1) / S::BN);
     const dim3 grid((unsigned)tiles, 1, (unsigned)splits);
-    if constexpr (AMODE >= A_GAUSS_LDS || std::is_same<S, ShapeLarge>::value) {
+    if constexpr (std::is_same<S, ShapeLarge>::value) {
         gemm_mfma_kernel<S, AMODE, BMODE, OUT, 3><<<grid, S::THREADS, 0, stream>>>(g);
     } else {
         if (plain_depth(g.K < g.k_chunk ? g.K : g.k_chunk, S::BK) == 4)
@@ -169,26 +169,24 @@ GemmArgs args_sketch(const bf16_t *A, int64_t n, int64_t d, int64_t k, SketchSta
     return g;
 }
 
+template <typename S>
+hipError_t launch_sketch_tile(int kind, const GemmArgs &g, int splits, hipStream_t stream) {
+    const dim3 grid((unsigned)tiles_of(g.M, g.N, S::BM, S::BN), 1, (unsigned)splits);
+    if (kind == 0)
+        sketch_kernel<S, 0><<<grid, S::THREADS, 0, stream>>>(g);
+    else
+        sketch_kernel<S, 1><<<grid, S::THREADS, 0, stream>>>(g);
+    return hipGetLastError();
+}
+
 hipError_t launch_sketch_cfg(int cfg, int kind, const GemmArgs &g, int splits, hipStream_t stream) {
     switch (cfg) {
-        case SK_WIDE:
-            return kind == 0 ? launch<ShapeSkWide, A_GAUSS_LDS, B_NCONTIG, OUT_F32_PARTIAL>(g, splits, stream)
-                             : launch<ShapeSkWide, A_RADEM_LDS, B_NCONTIG, OUT_F32_PARTIAL>(g, splits, stream);
-        case SK_WIDE64:
-            return kind == 0 ? launch<ShapeSkWide64, A_GAUSS_LDS, B_NCONTIG, OUT_F32_PARTIAL>(g, splits, stream)
-                             : launch<ShapeSkWide64, A_RADEM_LDS, B_NCONTIG, OUT_F32_PARTIAL>(g, splits, stream);
-        case SK_MID64:
-            return kind == 0 ? launch<ShapeSkMid64, A_GAUSS_LDS, B_NCONTIG, OUT_F32_PARTIAL>(g, splits, stream)
-                             : launch<ShapeSkMid64, A_RADEM_LDS, B_NCONTIG, OUT_F32_PARTIAL>(g, splits, stream);
-        case SK_MID:
-            return kind == 0 ? launch<ShapeSkMid, A_GAUSS_LDS, B_NCONTIG, OUT_F32_PARTIAL>(g, splits, stream)
-                             : launch<ShapeSkMid, A_RADEM_LDS, B_NCONTIG, OUT_F32_PARTIAL>(g, splits, stream);
-        case SK_NARROW64:
-            return kind == 0 ? launch<ShapeSkNarrow64, A_GAUSS_LDS, B_NCONTIG, OUT_F32_PARTIAL>(g, splits, stream)
-                             : launch<ShapeSkNarrow64, A_RADEM_LDS, B_NCONTIG, OUT_F32_PARTIAL>(g, splits, stream);
-        default:
-            return kind == 0 ? launch<ShapeSkNarrow, A_GAUSS_LDS, B_NCONTIG, OUT_F32_PARTIAL>(g, splits, stream)
-                             : launch<ShapeSkNarrow, A_RADEM_LDS, B_NCONTIG, OUT_F32_PARTIAL>(g, splits, stream);
+        case SK_WIDE: return launch_sketch_tile<ShapeSkWide>(kind, g, splits, stream);
+        case SK_WIDE64: return launch_sketch_tile<ShapeSkWide64>(kind, g, splits, stream);
+        case SK_MID64: return launch_sketch_tile<ShapeSkMid64>(kind, g, splits, stream);
+        case SK_MID: return launch_sketch_tile<ShapeSkMid>(kind, g, splits, stream);
+        case SK_NARROW64: return launch_sketch_tile<ShapeSkNarrow64>(kind, g, splits, stream);
+        default: return launch_sketch_tile<ShapeSkNarrow>(kind, g, splits, stream);
     }
 }
 

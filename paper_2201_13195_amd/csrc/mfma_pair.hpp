@@ -58,11 +58,11 @@ hipError_t launch_pair_impl(int sk_cfg, int kind, const GemmArgs &ga, const Gemm
     const int key = sk_cfg * 2 + (kind != 0 ? 1 : 0);
 #define RMM_PAIR_CASE(CFG, SHAPE)                                                                                      \
     case CFG * 2:                                                                                                      \
-        gemm_pair_kernel<SA, BMODE_A, DA, SHAPE, A_GAUSS_LDS, 3>                                                      \
+        gemm_pair_kernel<SA, BMODE_A, DA, SHAPE, 0>                                                                   \
             <<<grid, SA::THREADS, 0, stream>>>(ga, gb, blocks_a, tiles_b, sketch_blocks, col_blocks, sketch_first, c); \
         break;                                                                                                         \
     case CFG * 2 + 1:                                                                                                  \
-        gemm_pair_kernel<SA, BMODE_A, DA, SHAPE, A_RADEM_LDS, 3>                                                      \
+        gemm_pair_kernel<SA, BMODE_A, DA, SHAPE, 1>                                                                   \
             <<<grid, SA::THREADS, 0, stream>>>(ga, gb, blocks_a, tiles_b, sketch_blocks, col_blocks, sketch_first, c); \
         break;
     switch (key) {
