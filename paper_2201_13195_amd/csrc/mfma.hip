@@ -18,13 +18,12 @@ int plain_depth(int64_t contraction, int bk) {
 }
 
 template <typename S, int AMODE, int BMODE, int OUT>
-hipError_t launch(const GemmArgs &g, int splits, hipStream_t stream) {
-    const int64_t tiles = ((g.M + S::BM - 1) / S::BM) * ((g.N + S::BN - 1) / S::BN);
-    const dim3 grid((unsigned)tiles, 1, (unsigned)splits);
+hipError_t launch(const GemmArgs &g, hipStream_t stream) {
+    const dim3 grid((unsigned)(((g.M + S::BM - 1) / S::BM) * ((g.N + S::BN - 1) / S::BN)));
     if constexpr (std::is_same<S, ShapeLarge>::value) {
         gemm_mfma_kernel<S, AMODE, BMODE, OUT, 3><<<grid, S::THREADS, 0, stream>>>(g);
     } else {
-        if (plain_depth(g.K < g.k_chunk ? g.K : g.k_chunk, S::BK) == 4)
+        if (plain_depth(g.K, S::BK) == 4)
             gemm_mfma_kernel<S, AMODE, BMODE, OUT, 4><<<grid, S::THREADS, 0, stream>>>(g);
         else
             gemm_mfma_kernel<S, AMODE, BMODE, OUT, 3><<<grid, S::THREADS, 0, stream>>>(g);
@@ -73,14 +72,14 @@ hipError_t launch_gemm(int cfg, const GemmArgs &g, hipStream_t stream) {
             gemm_dma_kernel<BMODE><<<(unsigned)tiles_of(g.M, g.N, DmaTile::BM, DmaTile::BN), DmaTile::THREADS, 0, stream>>>(g);
             return hipGetLastError();
         } else {
-            return launch<ShapeLarge, AMODE, BMODE, OUT>(g, 1, stream);
+            return launch<ShapeLarge, AMODE, BMODE, OUT>(g, stream);
         }
     }
-    if (cfg == GEMM_SPLIT) return launch<ShapeSplit, AMODE, BMODE, OUT>(g, 1, stream);
+    if (cfg == GEMM_SPLIT) return launch<ShapeSplit, AMODE, BMODE, OUT>(g, stream);
     if constexpr (OUT == OUT_BF16)
         if (cfg == GEMM_FEW)
             return few_edge(g.M, g.N) == 32 ? launch_few<32, AMODE, BMODE>(g, stream) : launch_few<64, AMODE, BMODE>(g, stream);
-    return launch<ShapeMid, AMODE, BMODE, OUT>(g, 1, stream);
+    return launch<ShapeMid, AMODE, BMODE, OUT>(g, stream);
 }
 
 GemmArgs args_nt(const bf16_t *X, const bf16_t *W, const bf16_t *bias, bf16_t *Y, int64_t n, int64_t d_in, int64_t d_out) {
@@ -100,59 +99,78 @@ GemmArgs args_nn(const bf16_t *dY, const bf16_t *W, bf16_t *dX, int64_t n, int64
 // Which kernel serves a sketch product with k > 64 and how its token dimension is cut.  The work-group
 // generates the sketch tile into LDS and all eight waves read it.
 struct SketchPlan {
-    int cfg, splits;
+    int cfg;
+    int slices, per_tail;  // slices of k_chunk tokens of every tile; tiles per work-group that takes short last slices (0: there are none)
+    int splits;            // slices of a tile, the short one included
     int64_t k_chunk, tiles;
+    int shares() const { return slices * (int)tiles + (per_tail > 0 ? (int)((tiles + per_tail - 1) / per_tail) : 0); }
 };
 
-// Tokens are cut into `splits` slices of `k_chunk` tokens (a multiple of 128) so that about
-// `target_wgs` work-groups exist (256 = one per compute unit; measured: more or fewer are slower
-// when the product runs alone); with more than one slice the kernel writes fp32 partial results
-// to workspace and reduce_partials_kernel sums them in slice order.
-void slice_sketch(SketchPlan &p, int64_t n, int target_wgs) {
-    const int64_t blocks = (n + 127) / 128;
+// Tokens are cut into slices of `k_chunk` tokens (a multiple of 64) so that about `target_wgs` work-groups exist
+// (256 = one per compute unit; measured: more or fewer are slower when the product runs alone); with more than
+// one slice the kernel writes fp32 partial results to workspace and reduce_partials_kernel sums them in slice
+// order.  104 tiles would get two slices each, and 48 compute units nothing to do.  So a tile may also get a last,
+// shorter slice; the work-groups left over take those of per_tail tiles each, as long in all as a long slice
+// (16384 x 4096, k = 1638: 111 steps on 243 compute units instead of 128 on 208, 267 -> 252 us).
+// `overhead` is what a tile costs besides its steps, in steps; a tile gets at most `most` slices.
+void slice_sketch(SketchPlan &p, int64_t n, int target_wgs, double overhead, int64_t most) {
+    const int64_t units = (n + 63) / 64;
     int64_t s = target_wgs / p.tiles;
-    if (s > blocks) s = blocks;
-    if (s > 64) s = 64;
+    if (s > (units + 1) / 2) s = (units + 1) / 2;  // (a slice of one step: 1000 x 2000, k = 100 12.9 -> 14.7 us)
+    if (s > most) s = most;
     if (s < 1) s = 1;
-    p.k_chunk = (blocks + s - 1) / s * 128;
-    p.splits = (int)((n + p.k_chunk - 1) / p.k_chunk);
+    int64_t len = (units + s - 1) / s;
+    p.slices = p.splits = (int)((units + len - 1) / len), p.per_tail = 0;
+    const int64_t spare = target_wgs - s * p.tiles;
+    if (spare > 0 && s < most) {
+        const int64_t m = (p.tiles + spare - 1) / spare;
+        const int64_t tail_len = (int64_t)ceil(((double)units + overhead) * (double)m / (double)(s * m + 1));
+        if (s * tail_len < units && (double)tail_len < 0.92 * (double)len)
+            len = tail_len, p.slices = (int)s, p.splits = (int)s + 1, p.per_tail = (int)m;
+    }
+    p.k_chunk = len * 64;
 }
 
 // The tile is the one of the menu whose time comes out lowest: rounds of 256 work-groups, each as long as
-// its slice's 32-token steps, plus the partial results.  The times of a step on a full chip are a least-squares
-// fit over ten shapes from 4096 x 768, k = 410 to 16384 x 4096, k = 1638 (within 6 % rms); partial results
-// cost 0.13 us per MB written and read (they mostly stay in the last-level cache).  What that weighs: padding
-// of k and d, entries generated once per 512, 384 or 256 columns, operand columns staged once per 128 or 64
-// rows, and filling the chip when tokens are few.  ((3001 x 1304, k = 600) 64 x 512: 22.0 us, 128 x 512: 26.4;
-// (16384 x 4096, k = 410) 98 and 92; (32000 x 512, k = 640), Rademacher, 64 x 512: 50, 128 x 256: 41.)
-SketchPlan plan_sketch(int64_t n, int64_t d, int64_t k, int kind, int target_wgs = 256) {
+// its slice's 64-token steps, plus the partial results.  The times of a step on a full chip are a least-squares
+// fit over sixteen shapes from 2000 x 400, k = 100 to 16384 x 4096, k = 1638 (within 6.5 % rms), moved where the
+// choice came out better; partial results cost 0.2 us per MB written and read (they mostly stay in the last-level
+// cache).  What that weighs: padding of k and d, entries generated once per 512, 384 or 256 columns, operand
+// columns staged once per 128 or 64 rows, and filling the chip when tokens are few.  ((16384 x 4096, k = 410)
+// 64 x 512: 83 us, 128 x 512: 88; (32000 x 512, k = 640) 49, 128 x 256: 41; (10000 x 3000, k = 1000) 128 x 384:
+// 84, 128 x 512: 92; 4096 x 3072, k = 3686 unsliced on 128 x 384: 110, 128 x 512: 125.)
+// `limited`: the caller may be rmm_sketch_static.
+SketchPlan plan_sketch(int64_t n, int64_t d, int64_t k, int kind, bool limited, int target_wgs = 256) {
     struct Entry {
         int cfg;
         int64_t bm, bn;
         double step_us[2];  // Gaussian, Rademacher
     };
-    static const Entry menu[] = {{SK_WIDE64, 64, 512, {0.66, 0.63}}, {SK_WIDE, 128, 512, {1.01, 0.83}},
-                                 {SK_MID64, 64, 384, {0.59, 0.56}},  {SK_MID, 128, 384, {0.85, 0.69}},
-                                 {SK_NARROW64, 64, 256, {0.56, 0.53}}, {SK_NARROW, 128, 256, {0.75, 0.60}}};
+    static const Entry menu[] = {{SK_WIDE64, 64, 512, {1.20, 1.04}},   {SK_WIDE, 128, 512, {1.92, 1.63}},
+                                 {SK_MID64, 64, 384, {0.93, 0.86}},    {SK_MID, 128, 384, {1.54, 1.30}},
+                                 {SK_NARROW64, 64, 256, {0.85, 0.61}}, {SK_NARROW, 128, 256, {1.18, 0.91}}};
     // rmm_sketch_static serves the shapes whose partial results fit RMM_STATIC_SCRATCH_BYTES with the plainest
     // tiling (rows by k, columns by d); those keep fitting, whichever tile they run with.
-    auto partial_bytes = [&](const SketchPlan &p) { return p.splits > 1 ? (double)p.splits * (double)k * (double)d * 4.0 : 0.0; };
-    SketchPlan plainest;
-    plainest.tiles = d >= 1024 ? tiles_of(k, d, k <= 512 ? 64 : 128, 512) : d % 384 == 0 ? tiles_of(k, d, k <= 512 ? 64 : 128, 384) : tiles_of(k, d, 128, 256);
-    slice_sketch(plainest, n, 256);
-    const double limit = partial_bytes(plainest) <= (double)RMM_STATIC_SCRATCH_BYTES ? (double)RMM_STATIC_SCRATCH_BYTES : 1.0e30;
+    int64_t most = 64;
+    const double partial_bytes = (double)k * (double)d * 4.0;
+    if (limited) {
+        const int64_t tiles = d >= 1024 ? tiles_of(k, d, k <= 512 ? 64 : 128, 512) : d % 384 == 0 ? tiles_of(k, d, k <= 512 ? 64 : 128, 384) : tiles_of(k, d, 128, 256);
+        const int64_t blocks = (n + 127) / 128, s = tiles >= 256 ? 1 : blocks < 256 / tiles ? blocks : 256 / tiles;
+        const int64_t chunk = (blocks + s - 1) / s, slices = (blocks + chunk - 1) / chunk, fit = (int64_t)((double)RMM_STATIC_SCRATCH_BYTES / partial_bytes);
+        if (slices == 1 || slices <= fit) most = fit < 1 ? 1 : fit < 64 ? fit : 64;
+    }
     SketchPlan best{};
-    double best_us = -1.0;
+    double best_us = -1.0, best_overhead = 0.0;
     for (const Entry &e : menu) {
         SketchPlan p;
         p.cfg = e.cfg, p.tiles = tiles_of(k, d, e.bm, e.bn);
-        slice_sketch(p, n, 256);
-        if (partial_bytes(p) > limit) continue;  // (never all of them: the plainest tiling is on the menu)
-        const double rounds = (double)((p.tiles * p.splits + 255) / 256), steps = (double)(p.k_chunk / 32);
-        const double us = rounds * steps * e.step_us[kind != 0] + (p.splits > 1 ? (double)p.splits * (double)k * (double)d * 1.05e-6 : 0.0);
-        if (best_us < 0.0 || us < 0.97 * best_us) best = p, best_us = us;  // (ties: the wider tile pairs better)
+        const double step_us = e.step_us[kind != 0], overhead = 4.0 / step_us;
+        slice_sketch(p, n, 256, overhead, most);
+        const double us = (double)((p.shares() + 255) / 256) * (double)(p.k_chunk / 64) * step_us + 2.0 * p.per_tail +
+                          (p.splits > 1 ? (double)p.splits * (double)k * (double)d * 0.82e-6 : 0.0);
+        if (best_us < 0.0 || us < 0.98 * best_us) best = p, best_us = us, best_overhead = overhead;  // (ties: the wider tile pairs better)
     }
-    slice_sketch(best, n, target_wgs);
+    if (target_wgs != 256) slice_sketch(best, n, target_wgs, best_overhead, most);
     return best;
 }
 
@@ -160,7 +178,7 @@ GemmArgs args_sketch(const bf16_t *A, int64_t n, int64_t d, int64_t k, SketchSta
                      void *ws) {
     GemmArgs g{};
     g.A = nullptr, g.lda = 0, g.B = A, g.ldb = d, g.bias = nullptr;
-    g.M = k, g.N = d, g.K = n, g.st = st, g.ldc = d, g.k_chunk = p.k_chunk;
+    g.M = k, g.N = d, g.K = n, g.st = st, g.ldc = d, g.k_chunk = p.k_chunk, g.slices = p.slices, g.per_tail = p.per_tail;
     if (p.splits == 1) {
         g.C = out, g.alpha = 1.0f / sqrtf((float)k), g.direct = 1;
     } else {
@@ -170,23 +188,22 @@ GemmArgs args_sketch(const bf16_t *A, int64_t n, int64_t d, int64_t k, SketchSta
 }
 
 template <typename S>
-hipError_t launch_sketch_tile(int kind, const GemmArgs &g, int splits, hipStream_t stream) {
-    const dim3 grid((unsigned)tiles_of(g.M, g.N, S::BM, S::BN), 1, (unsigned)splits);
+hipError_t launch_sketch_tile(int kind, const GemmArgs &g, const SketchPlan &p, hipStream_t stream) {
     if (kind == 0)
-        sketch_kernel<S, 0><<<grid, S::THREADS, 0, stream>>>(g);
+        sketch_kernel<S, 0><<<(unsigned)p.shares(), S::THREADS, 0, stream>>>(g, (int)p.tiles);
     else
-        sketch_kernel<S, 1><<<grid, S::THREADS, 0, stream>>>(g);
+        sketch_kernel<S, 1><<<(unsigned)p.shares(), S::THREADS, 0, stream>>>(g, (int)p.tiles);
     return hipGetLastError();
 }
 
-hipError_t launch_sketch_cfg(int cfg, int kind, const GemmArgs &g, int splits, hipStream_t stream) {
-    switch (cfg) {
-        case SK_WIDE: return launch_sketch_tile<ShapeSkWide>(kind, g, splits, stream);
-        case SK_WIDE64: return launch_sketch_tile<ShapeSkWide64>(kind, g, splits, stream);
-        case SK_MID64: return launch_sketch_tile<ShapeSkMid64>(kind, g, splits, stream);
-        case SK_MID: return launch_sketch_tile<ShapeSkMid>(kind, g, splits, stream);
-        case SK_NARROW64: return launch_sketch_tile<ShapeSkNarrow64>(kind, g, splits, stream);
-        default: return launch_sketch_tile<ShapeSkNarrow>(kind, g, splits, stream);
+hipError_t launch_sketch_plan(const SketchPlan &p, int kind, const GemmArgs &g, hipStream_t stream) {
+    switch (p.cfg) {
+        case SK_WIDE: return launch_sketch_tile<ShapeSkWide>(kind, g, p, stream);
+        case SK_WIDE64: return launch_sketch_tile<ShapeSkWide64>(kind, g, p, stream);
+        case SK_MID64: return launch_sketch_tile<ShapeSkMid64>(kind, g, p, stream);
+        case SK_MID: return launch_sketch_tile<ShapeSkMid>(kind, g, p, stream);
+        case SK_NARROW64: return launch_sketch_tile<ShapeSkNarrow64>(kind, g, p, stream);
+        default: return launch_sketch_tile<ShapeSkNarrow>(kind, g, p, stream);
     }
 }
 
@@ -270,15 +287,15 @@ int paired_sketch_target(int64_t blocks_a, double flops_a, double flops_sk) {
 // Plan of the sketch product of X (forward) / dY (backward) inside a layer call.
 SketchPlan plan_pass_sketch(int64_t n, int64_t d_sk, int64_t d_other, int64_t k, int kind) {
     // the plain product has an n x d_other output and contracts over d_sk
-    const SketchPlan alone = plan_sketch(n, d_sk, k, kind);
+    const SketchPlan alone = plan_sketch(n, d_sk, k, kind, false);
     if (alone.splits == 1) return alone;
     const int target = paired_sketch_target(pair_plain(n, d_other, d_sk).tiles, 2.0 * n * d_sk * d_other, 2.0 * n * k * d_sk);
-    SketchPlan paired = plan_sketch(n, d_sk, k, kind, target);
+    SketchPlan paired = plan_sketch(n, d_sk, k, kind, false, target);
     if (target == 256) {
         // Short slices (at most 1024 tokens) pack better into the time the plain product's work-groups
         // take when there are a quarter more of them; long ones would only add a round.
-        const SketchPlan finer = plan_sketch(n, d_sk, k, kind, 320);
-        if (finer.splits > paired.splits && finer.k_chunk <= 1024) paired = finer;
+        const SketchPlan finer = plan_sketch(n, d_sk, k, kind, false, 320);
+        if (paired.per_tail == 0 && finer.per_tail == 0 && finer.splits > paired.splits && finer.k_chunk <= 1024) paired = finer;
     }
     return paired.splits >= 2 ? paired : alone;
 }
@@ -407,7 +424,7 @@ size_t sketch_workspace_bf16(int64_t n, int64_t d, int64_t k, int64_t d_other) {
         return s > 1 ? (size_t)s * (size_t)k * (size_t)d * sizeof(float) : 0;
     }
     for (int kind = 0; kind < 2; ++kind) {
-        const SketchPlan p = d_other > 0 ? plan_pass_sketch(n, d, d_other, k, kind) : plan_sketch(n, d, k, kind);
+        const SketchPlan p = d_other > 0 ? plan_pass_sketch(n, d, d_other, k, kind) : plan_sketch(n, d, k, kind, true);
         const size_t bytes = p.splits > 1 ? (size_t)p.splits * (size_t)k * (size_t)d * sizeof(float) : 0;
         if (bytes > most) most = bytes;
     }
@@ -434,9 +451,9 @@ hipError_t launch_sketch_bf16(const bf16_t *A, bf16_t *out, int64_t n, int64_t d
         if (e != hipSuccess || slices == 1) return e;
         return launch_reduce(ws, out, k, d, slices, stream);
     }
-    const SketchPlan p = d_other > 0 ? plan_pass_sketch(n, d, d_other, k, kind) : plan_sketch(n, d, k, kind);
+    const SketchPlan p = d_other > 0 ? plan_pass_sketch(n, d, d_other, k, kind) : plan_sketch(n, d, k, kind, true);
     const GemmArgs g = args_sketch(A, n, d, k, st, p, out, ws);
-    hipError_t e = launch_sketch_cfg(p.cfg, kind, g, p.splits, stream);
+    hipError_t e = launch_sketch_plan(p, kind, g, stream);
     pev.done();
     if (e != hipSuccess || p.splits == 1) return e;
     return launch_reduce(ws, out, k, d, p.splits, stream);
@@ -451,7 +468,7 @@ hipError_t launch_forward_pair_bf16(const bf16_t *X, const bf16_t *W, const bf16
     const SketchPlan p = plan_pass_sketch(n, d_in, d_out, k, kind);
     const GemmArgs gb = args_sketch(X, n, d_in, k, st, p, X_proj, ws);
     EventPair pev(ev_begin, ev_end, stream);
-    const hipError_t e = launch_pair_nt(pair_plain(ga.M, ga.N, ga.K), p.cfg, kind, ga, gb, (int)p.tiles, p.splits, stream);
+    const hipError_t e = launch_pair_nt(pair_plain(ga.M, ga.N, ga.K), p.cfg, kind, ga, gb, (int)p.tiles, p.shares(), stream);
     pev.done();
     if (e != hipSuccess || p.splits == 1) return e;
     return launch_reduce(ws, X_proj, k, d_in, p.splits, stream);
@@ -473,7 +490,7 @@ bool backward_pair_takes_colsum(int64_t n, int64_t d_in, int64_t d_out, int64_t 
     const int64_t dw_tiles = dw_cfg == GEMM_LARGE ? tiles_of(d_out, d_in, ShapeLarge::BM, ShapeLarge::BN) : tiles_of(d_out, d_in, 128, 128);
     if ((256 - dw_tiles % 256) % 256 >= 64) return false;
     const SketchPlan p = plan_pass_sketch(n, d_out, d_in, k, kind);
-    const int64_t total = pair_plain(n, d_in, d_out).tiles + p.tiles * p.splits;
+    const int64_t total = pair_plain(n, d_in, d_out).tiles + p.shares();
     return (256 - total % 256) % 256 >= 16;
 }
 
@@ -486,7 +503,7 @@ hipError_t launch_backward_pair_bf16(const bf16_t *dY, const bf16_t *W, bf16_t *
     const ColsumArgs gc{dY, dbias, n, d_out, accumulate_dbias ? 1 : 0, colsum_lpr(d_out, 2)};
     const ColsumArgs *gcp = dbias != nullptr ? &gc : nullptr;
     EventPair pev(ev_begin, ev_end, stream);
-    const hipError_t e = launch_pair_nn(pair_plain(ga.M, ga.N, ga.K), p.cfg, kind, ga, gb, (int)p.tiles, p.splits, stream, gcp);
+    const hipError_t e = launch_pair_nn(pair_plain(ga.M, ga.N, ga.K), p.cfg, kind, ga, gb, (int)p.tiles, p.shares(), stream, gcp);
     pev.done();
     if (e != hipSuccess || p.splits == 1) return e;
     return launch_reduce(ws, G, k, d_out, p.splits, stream);

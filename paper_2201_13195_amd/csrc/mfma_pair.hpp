@@ -18,19 +18,19 @@ struct PairPlain {
 };
 
 // One launch for a plain product (`ga`; nt: Y = X W^T, nn: dX = dY W) and a sketch product (`gb`, `tiles_b`
-// tiles x `splits` token slices, fp32 partial results) with the kernel sk_cfg.
+// tiles in `shares` work-groups, see sketch_share) with the kernel sk_cfg.
 // `gc`, if not null, adds the column blocks of a column-sum problem (colsum.hpp) behind the sketch work-groups.
 // The sketch work-groups are put in front of the plain tiles when the sketch product is unsliced (few, long
 // work-groups) or the plain product fills the chip at least once (256 tiles or more: measured 4 % faster at the
 // RoBERTa-large shapes, 2-3 % slower where the plain product has 192 tiles and the sketch work-groups fill in behind).
 hipError_t launch_pair_nt(const PairPlain &plain, int sk_cfg, int kind, const GemmArgs &ga, const GemmArgs &gb, int tiles_b,
-                          int splits, hipStream_t stream, const ColsumArgs *gc = nullptr);
+                          int shares, hipStream_t stream, const ColsumArgs *gc = nullptr);
 hipError_t launch_pair_nn(const PairPlain &plain, int sk_cfg, int kind, const GemmArgs &ga, const GemmArgs &gb, int tiles_b,
-                          int splits, hipStream_t stream, const ColsumArgs *gc = nullptr);
+                          int shares, hipStream_t stream, const ColsumArgs *gc = nullptr);
 // (one translation unit for each plain tile: large, split at depth 4, split at depth 3)
 #define RMM_PAIR_DECL(NAME)                                                                                               \
     hipError_t launch_pair_##NAME(int sk_cfg, int kind, const GemmArgs &ga, const GemmArgs &gb, int blocks_a, int tiles_b, \
-                                  int splits, hipStream_t stream, const ColsumArgs *gc)
+                                  int shares, hipStream_t stream, const ColsumArgs *gc)
 RMM_PAIR_DECL(nt_large);
 RMM_PAIR_DECL(nt_split4);
 RMM_PAIR_DECL(nt_split3);
@@ -49,9 +49,9 @@ hipError_t launch_pair_sors(int cfg_a, bool row_indexed_b, const GemmArgs &ga, c
 // Shared body of the six launch_pair_{nt,nn}_*.
 template <typename SA, int BMODE_A, int DA>
 hipError_t launch_pair_impl(int sk_cfg, int kind, const GemmArgs &ga, const GemmArgs &gb, int blocks_a, int tiles_b,
-                            int splits, hipStream_t stream, const ColsumArgs *gc) {
-    const int sketch_blocks = tiles_b * splits;
-    const int sketch_first = splits == 1 || blocks_a >= 256 ? 1 : 0;
+                            int shares, hipStream_t stream, const ColsumArgs *gc) {
+    const int sketch_blocks = shares;
+    const int sketch_first = gb.slices == 1 || blocks_a >= 256 ? 1 : 0;
     const ColsumArgs c = gc != nullptr ? *gc : ColsumArgs{};
     const int col_blocks = gc != nullptr ? (int)colsum_blocks(c.d, 2) : 0;
     const dim3 grid((unsigned)(blocks_a + sketch_blocks + col_blocks));

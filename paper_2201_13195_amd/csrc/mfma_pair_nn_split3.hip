@@ -4,7 +4,7 @@
 namespace rmm {
 
 RMM_PAIR_DECL(nn_split3) {
-    return launch_pair_impl<ShapeSplit, B_NCONTIG, 3>(sk_cfg, kind, ga, gb, blocks_a, tiles_b, splits, stream, gc);
+    return launch_pair_impl<ShapeSplit, B_NCONTIG, 3>(sk_cfg, kind, ga, gb, blocks_a, tiles_b, shares, stream, gc);
 }
 
 }  // namespace rmm

@@ -4,13 +4,13 @@
 namespace rmm {
 
 RMM_PAIR_DECL(nt_large) {
-    return launch_pair_impl<ShapeLarge, B_KCONTIG, 3>(sk_cfg, kind, ga, gb, blocks_a, tiles_b, splits, stream, gc);
+    return launch_pair_impl<ShapeLarge, B_KCONTIG, 3>(sk_cfg, kind, ga, gb, blocks_a, tiles_b, shares, stream, gc);
 }
 
 hipError_t launch_pair_nt(const PairPlain &plain, int sk_cfg, int kind, const GemmArgs &ga, const GemmArgs &gb, int tiles_b,
-                          int splits, hipStream_t stream, const ColsumArgs *gc) {
+                          int shares, hipStream_t stream, const ColsumArgs *gc) {
     return (plain.large ? launch_pair_nt_large : plain.depth == 4 ? launch_pair_nt_split4 : launch_pair_nt_split3)(
-        sk_cfg, kind, ga, gb, plain.tiles, tiles_b, splits, stream, gc);
+        sk_cfg, kind, ga, gb, plain.tiles, tiles_b, shares, stream, gc);
 }
 
 }  // namespace rmm
