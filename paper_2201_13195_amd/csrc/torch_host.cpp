@@ -13,6 +13,7 @@
 #include <torch/csrc/autograd/python_cpp_function.h>
 #include <torch/csrc/autograd/python_variable.h>
 #include <torch/csrc/autograd/saved_variable.h>
+#include <torch/csrc/jit/frontend/tracer.h>
 #include <ATen/ATen.h>
 #include <ATen/hip/impl/HIPStreamMasqueradingAsCUDA.h>
 
@@ -307,6 +308,18 @@ PyObject *py_variance_stats(PyObject *, PyObject *const *a, Py_ssize_t nargs) {
     RMM_END
 }
 
+// The layer calls below make their output without torch operators and hang their own node on it, so whatever
+// watches operators or Python autograd functions would see nothing of them: a trace would hold an allocation that
+// nobody fills, a forward-mode derivative would be dropped without a word, and a transform's wrapper has no memory.
+// Such calls take the Python function, which torch records or refuses as any other.
+bool watched(const Tensor &t) {
+    return t.defined() && (t._fw_grad(/*level=*/0).defined() || !t.has_storage());
+}
+void need_unwatched(const Tensor &X, const Tensor &W, const Tensor &bias) {
+    need(!torch::jit::tracer::isTracing() && !watched(X) && !watched(W) && !watched(bias) &&
+         !c10::impl::tls_is_dispatch_key_included(c10::DispatchKey::FuncTorchDynamicLayerFrontMode));
+}
+
 // X as a dense n x d_in matrix
 Tensor rows_of(const Tensor &X, const Tensor &W) {
     need(X.is_cuda() && X.dim() >= 1 && dtype_code(X) >= 0 && X.numel() > 0 && W.dim() == 2 && X.size(-1) == W.size(1));
@@ -327,6 +340,7 @@ PyObject *py_linear(PyObject *, PyObject *const *a, Py_ssize_t nargs) {
     const int kind = arg_kind(a[4]);
     const rmm_rng_state_t st = {arg_u64(a[5]), arg_u64(a[6])};
     need(k >= 1);
+    need_unwatched(X, W, bias);
     Tensor Y, X_proj, Wc;
     {
         at::NoGradGuard no_grad;

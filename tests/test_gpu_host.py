@@ -2,6 +2,7 @@
 same autograd behaviour, same errors."""
 import pytest
 import torch
+from torch.autograd import forward_ad
 
 import paper_2201_13195_amd as rmm
 from paper_2201_13195_amd import binding
@@ -81,4 +82,51 @@ def test_same_errors(monkeypatch):
                 with pytest.raises(error) as e:
                     call()
             raised.append(str(e.value))
+        assert raised[0] == raised[1]
+
+
+@pytest.mark.parametrize("bias", [True, False])
+def test_tracing_records_the_layer(bias):
+    """A traced module computes what the module computes, with its gradients: the graph holds the call
+    itself, not the allocation of an output that native code fills behind the tracer's back."""
+    lin = rmm.RMMLinear(64, 24, bias=bias, k=20, seed=3, layer_id=1)
+    X, X2 = (torch.randn(30, 64, device=DEV, dtype=torch.bfloat16) for _ in range(2))
+    traced = torch.jit.trace(lin, (X,), check_trace=False)
+    seed, offset = lin.last_state
+    for x in (X, X2):
+        Y = traced(x)
+        want = rmm.RMMLinearFunction.apply(x, lin.weight, lin.bias, 20, lin.kind, seed, offset)
+        assert torch.equal(Y, want)
+        assert torch.equal(torch.autograd.grad(Y.float().sum(), lin.weight)[0],
+                           torch.autograd.grad(want.float().sum(), lin.weight)[0])
+
+
+def test_forward_mode_is_refused():
+    """There is no forward-mode derivative: an input with a tangent is an error, not an output without one."""
+    lin = rmm.RMMLinear(64, 24, k=20, seed=3, layer_id=1)
+    X = torch.randn(30, 64, device=DEV, dtype=torch.bfloat16)
+    with forward_ad.dual_level():
+        for x, W in ((forward_ad.make_dual(X, torch.ones_like(X)), lin.weight),
+                     (X, forward_ad.make_dual(lin.weight.detach(), torch.ones_like(lin.weight)))):
+            with pytest.raises(NotImplementedError):
+                rmm.RMMLinearFunction.apply(x, W, lin.bias, 20, rmm.GAUSSIAN, 3, 4)
+
+
+def test_function_transforms_are_refused_alike(monkeypatch):
+    """vmap and the derivative transforms of torch.func raise what they raise for a Python autograd function."""
+    W = torch.randn(24, 64, device=DEV)
+    X = torch.randn(2, 30, 64, device=DEV)
+
+    def call(x):
+        return rmm.RMMLinearFunction.apply(x, W, None, 20, rmm.GAUSSIAN, 3, 4)
+    for transformed in (lambda: torch.vmap(call)(X), lambda: torch.func.grad(lambda x: call(x).sum())(X[0]),
+                        lambda: torch.func.jvp(call, (X[0],), (X[1],))):
+        raised = []
+        for native in (True, False):
+            with monkeypatch.context() as m:
+                if not native:
+                    m.setattr(binding, "_native", lambda *args: None)
+                with pytest.raises(RuntimeError) as e:
+                    transformed()
+            raised.append((e.type, str(e.value)))
         assert raised[0] == raised[1]
