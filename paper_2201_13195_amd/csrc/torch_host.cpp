@@ -370,6 +370,7 @@ PyObject *py_infer(PyObject *, PyObject *const *a, Py_ssize_t nargs) {
     RMM_BEGIN(4)
     const Tensor X = arg_tensor(a[0]), W = arg_tensor(a[1]), bias = arg_tensor(a[2], true);
     const int kind = arg_kind(a[3]);
+    need_unwatched(X, W, bias);
     at::NoGradGuard no_grad;
     const Tensor X2 = rows_of(X, W), Wc = W.contiguous();
     need(is_matrix(Wc, W.size(0), W.size(1), X2) && (!bias.defined() || is_matrix(bias, W.size(0), -1, X2)));

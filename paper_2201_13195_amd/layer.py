@@ -50,6 +50,21 @@ class RMMLinearFunction(torch.autograd.Function):
         return dX, dW, db, None, None, None, None
 
 
+class RMMInferFunction(torch.autograd.Function):
+    """Y alone (Eq. 1), as a call that a trace records and that refuses forward-mode tangents."""
+
+    @classmethod
+    def apply(cls, X, W, bias, kind):
+        Y = binding._native("infer", X, W, bias, kind)
+        return super().apply(X, W, bias, kind) if Y is None else Y
+
+    @staticmethod
+    def forward(ctx, X, W, bias, kind):
+        Y, _ = binding.rmm_forward(X.reshape(-1, X.shape[-1]).contiguous(), W.detach().contiguous(), bias, 1, kind, 0, 0,
+                                   need_xproj=False)
+        return Y.reshape(*X.shape[:-1], W.shape[0])
+
+
 class RMMLinear(torch.nn.Module):
     """`nn.Linear` replacement.  The sketch size is `k` tokens, or `round(rho * n)` of the n
     tokens of each call (clamped to [1, n]); every forward call that will be followed by a
@@ -80,13 +95,7 @@ class RMMLinear(torch.nn.Module):
 
     def forward(self, X):
         if not torch.is_grad_enabled():        # nothing will be kept for a backward pass: Y alone
-            Y = binding._native("infer", X, self.weight, self.bias, self.kind)
-            if Y is not None:
-                return Y
-            X2 = X.reshape(-1, X.shape[-1]).contiguous()
-            Y, _ = binding.rmm_forward(X2, self.weight.detach().contiguous(), self.bias, 1, self.kind, 0, 0,
-                                       need_xproj=False)
-            return Y.reshape(*X.shape[:-1], self.out_features)
+            return RMMInferFunction.apply(X, self.weight, self.bias, self.kind)
         n = X.numel() // X.shape[-1]
         seed, offset = self.__dict__["last_state"] = self.next_state()
         return RMMLinearFunction.apply(X, self.weight, self.bias, self.sketch_size(n), self.kind, seed, offset)

@@ -130,3 +130,15 @@ def test_function_transforms_are_refused_alike(monkeypatch):
                     transformed()
             raised.append((e.type, str(e.value)))
         assert raised[0] == raised[1]
+
+
+def test_calls_without_gradients_are_traced_and_refuse_tangents():
+    lin = rmm.RMMLinear(64, 24, k=20, seed=3, layer_id=1)
+    X, X2 = (torch.randn(3, 10, 64, device=DEV, dtype=torch.bfloat16) for _ in range(2))
+    with torch.no_grad():
+        traced = torch.jit.trace(lin, (X,), check_trace=False)
+        for x in (X, X2):
+            assert torch.equal(traced(x), lin(x))
+        with forward_ad.dual_level(), pytest.raises(NotImplementedError):
+            lin(forward_ad.make_dual(X, torch.ones_like(X)))
+    assert lin.calls == 0
