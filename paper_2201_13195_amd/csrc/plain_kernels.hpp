@@ -21,6 +21,7 @@
 
 #include "colsum.hpp"
 #include "mfma_frag.hpp"
+#include "tile_range.hpp"
 
 namespace rmm {
 
@@ -126,16 +127,15 @@ struct PlainLoader {
     const T *p[MODE == 0 ? CHUNKS : 1];
     const T *base;
     int64_t ld, rows_left;
+    uint32_t skew = 0;  // bytes between the base and the first element
     int clamp[MODE == 0 ? CHUNKS : 1];
 
     __device__ __forceinline__ void init(const T *operand, int64_t ld_, int64_t row0, int64_t rows, int tid) {
         ld = ld_, rows_left = rows - row0;
         base = operand + (MODE == 0 ? 0 : row0 * (KROWS ? ld : 1));
-        uint32_t skew = 0;
         if constexpr (ES == 2 && MODE != 0) {  // descriptors start on a dword
             skew = (uint32_t)(reinterpret_cast<uintptr_t>(base) & 2u);
             base -= skew / 2;
-            rows_left += KROWS ? 0 : skew / 2;  // (columns counted from the new base)
         }
 #pragma unroll
         for (int q = 0; q < CHUNKS; ++q) {
@@ -166,8 +166,7 @@ struct PlainLoader {
             }
         } else {
             const int l = (int)(left < 0 ? 0 : left < BK ? left : BK);
-            const int64_t elems = KROWS ? (min(rows_left, (int64_t)ROWS) - 1) * ld + l : (l > 0 ? (l - 1) * ld + rows_left : 0);
-            const int64_t bytes = (elems * ES + (ES == 2 && KROWS ? 2 : 0) + 3) & ~(int64_t)3;  // (+2: a skewed base)
+            const int64_t bytes = tile_range_bytes<ES, KROWS>(rows_left, ROWS, ld, l, skew / ES);
             const __amdgpu_buffer_rsrc_t rsrc =
                 __builtin_amdgcn_make_buffer_rsrc(const_cast<T *>(base), (short)0,
                                                   __builtin_amdgcn_readfirstlane((int)min(bytes, (int64_t)0x7FFFFFFC)), 0x00020000);

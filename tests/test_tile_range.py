@@ -1,0 +1,55 @@
+"""CPU: the range of the buffer descriptors that load operand tiles (csrc/tile_range.hpp, compiled for the
+host): to the end of the dword that holds the last element of the tile, and never past the operand's."""
+import ctypes
+import itertools
+import os
+import shutil
+import subprocess
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+HEADER = os.path.join(HERE, "..", "paper_2201_13195_amd", "csrc", "tile_range.hpp")
+SOURCE = """
+#include "%s"
+extern "C" int64_t range_bytes(int es, int krows, int64_t rows_left, int64_t tile_rows, int64_t ld, int64_t left, int64_t skew) {
+    if (es == 2) return krows ? rmm::tile_range_bytes<2, true>(rows_left, tile_rows, ld, left, skew)
+                              : rmm::tile_range_bytes<2, false>(rows_left, tile_rows, ld, left, skew);
+    return krows ? rmm::tile_range_bytes<4, true>(rows_left, tile_rows, ld, left, skew)
+                 : rmm::tile_range_bytes<4, false>(rows_left, tile_rows, ld, left, skew);
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def range_bytes(tmp_path_factory):
+    if shutil.which("g++") is None:
+        pytest.skip("no host compiler")
+    where = tmp_path_factory.mktemp("range")
+    src, lib = str(where / "range.cpp"), str(where / "range.so")
+    with open(src, "w") as f:
+        f.write(SOURCE % HEADER)
+    subprocess.run(["g++", "-std=c++17", "-shared", "-fPIC", src, "-o", lib], check=True)
+    f = ctypes.CDLL(lib).range_bytes
+    f.restype, f.argtypes = ctypes.c_int64, [ctypes.c_int, ctypes.c_int] + [ctypes.c_int64] * 5
+    return f
+
+
+@pytest.mark.parametrize("es", [2, 4])
+@pytest.mark.parametrize("krows", [True, False])
+def test_ranges_end_with_the_last_element(range_bytes, es, krows):
+    """Operands of `outer` rows of `ld` elements at address 0, walked in tiles as the kernels walk them."""
+    tile, bk = 8, 4           # (an even contraction step, as the kernels' are)
+    for outer, ld in itertools.product((1, 2, 3, 7, 8, 9, 16, 17), repeat=2):
+        rows, kk = (outer, ld) if krows else (ld, outer)
+        end = (outer * ld * es + 3) // 4 * 4
+        for row0, done in itertools.product(range(0, rows, tile), range(0, kk + 2 * bk, bk)):
+            first = row0 * (ld if krows else 1) + done * (1 if krows else ld)
+            skew = (first * es % 4) // es
+            base, left = first * es - skew * es, min(kk - done, bk)
+            reach = range_bytes(es, krows, rows - row0, tile, ld, left, skew)
+            if left <= 0:
+                assert reach == 0
+                continue
+            last = first + ((min(rows - row0, tile) - 1) * ld + left - 1 if krows else (left - 1) * ld + rows - row0 - 1)
+            assert base % 4 == 0 and base + reach == (last * es + es + 3) // 4 * 4 <= end, (outer, ld, row0, done)
