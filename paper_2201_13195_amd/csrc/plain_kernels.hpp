@@ -12,6 +12,12 @@
 // an fp32 multiply-add.  Operands that are bf16 already, and the +-1 entries of the Rademacher and
 // SORS sketches, are one plane.
 //
+// The whole range of fp32 is served.  bf16 has fp32's exponents, so below 2^-110 the lower planes would lose
+// bits: fp32 operands are multiplied by 2^24 before they are split (fp32's smallest number becomes 2^-125), and the
+// sums by the inverse.  Operands from about 2^104 up, infinities and sums that leave fp32 with the factors on them
+// then end as an infinity or NaN in the accumulator, NaN operands as NaN: the outputs where that happened are
+// computed again with fp32 multiply-adds, element by element (plain_dot), and get what those give.
+//
 // Why not v_mfma_f32_32x32x2_f32: it runs on the vector units' fp32 multipliers (measured on this
 // chip: 72 cycles plus 4 for every vector instruction beside it), 576 cycles for the block that takes
 // 8 x 32 here, and address arithmetic, splitting and the sketch generator would add to that instead of
@@ -78,14 +84,14 @@ struct PlainTile {
     static constexpr int LDS_BYTES = 2 * STAGE * 2 > RED_BYTES ? 2 * STAGE * 2 : RED_BYTES;
 };
 
-// Eight fp32 values as PLANES bf16 vectors whose sum they are.
-template <int PLANES>
-__device__ __forceinline__ void split_eight(const float (&x)[8], bf16x8_t (&out)[PLANES]) {
+// Eight fp32 values as three bf16 vectors whose sum they are.  (An infinity, or a number that rounds to one
+// in bf16: infinity, NaN, NaN.)
+__device__ __forceinline__ void split_eight(const float (&x)[8], bf16x8_t (&out)[3]) {
     float r[8];
 #pragma unroll
     for (int u = 0; u < 8; ++u) r[u] = x[u];
 #pragma unroll
-    for (int p = 0; p < PLANES; ++p) {
+    for (int p = 0; p < 3; ++p) {
         union {
             bf16x8_t v;
             bf16x2_t h[4];
@@ -94,7 +100,7 @@ __device__ __forceinline__ void split_eight(const float (&x)[8], bf16x8_t (&out)
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             o.h[q] = __builtin_convertvector((f32x2_t){r[2 * q], r[2 * q + 1]}, bf16x2_t);  // nearest even
-            if (p + 1 < PLANES) {
+            if (p < 2) {
                 r[2 * q] -= __uint_as_float(o.w[q] << 16);
                 r[2 * q + 1] -= __uint_as_float(o.w[q] & 0xFFFF0000u);
             }
@@ -102,6 +108,7 @@ __device__ __forceinline__ void split_eight(const float (&x)[8], bf16x8_t (&out)
         out[p] = o.v;
     }
 }
+constexpr float kSplitUp = 0x1p24f, kSplitDown = 0x1p-24f;
 
 // One operand tile (ROWS rows or columns of the product x BK contraction elements) on its way from
 // memory to LDS, in chunks of eight elements that are neighbours in memory.  KROWS: the chunk runs
@@ -115,7 +122,7 @@ __device__ __forceinline__ void split_eight(const float (&x)[8], bf16x8_t (&out)
 // chunk), and what a chunk holds beyond the end of its row is cleared in store().
 template <typename T, int ROWS, int BK, bool KROWS, int MODE, int STRIDE, int PLANE>
 struct PlainLoader {
-    static constexpr int CHUNKS = ROWS * BK / 8 / kPlainThreads, PLANES = plain_planes<T>(), ES = (int)sizeof(T);
+    static constexpr int CHUNKS = ROWS * BK / 8 / kPlainThreads, ES = (int)sizeof(T);
     static constexpr int WORDS = MODE == 0 ? 8 : ES == 4 ? 8 : 5;  // registers of a chunk in flight
     static_assert(ROWS * BK % (8 * kPlainThreads) == 0, "whole chunks per thread");
     static_assert(MODE != 4 || ES == 4, "bf16 rows on 16 bytes are the other kernels' business");
@@ -213,11 +220,12 @@ struct PlainLoader {
                 for (int u = 0; u < 8; ++u) {
                     x[u] = __uint_as_float(g.v[q][u]);
                     if constexpr (MODE == 0 || (MODE == 3 && KROWS)) x[u] = u < valid ? x[u] : 0.0f;
+                    x[u] *= kSplitUp;
                 }
-                bf16x8_t o[PLANES];
-                split_eight<PLANES>(x, o);
+                bf16x8_t o[3];
+                split_eight(x, o);
 #pragma unroll
-                for (int s = 0; s < PLANES; ++s) *reinterpret_cast<bf16x8_t *>(tile + s * PLANE + at[q]) = o[s];
+                for (int s = 0; s < 3; ++s) *reinterpret_cast<bf16x8_t *>(tile + s * PLANE + at[q]) = o[s];
             }
         }
     }
@@ -250,6 +258,25 @@ __device__ __forceinline__ bf16x8_t sign_eight(int kind, const SketchState &st, 
     for (int q = 0; q < 4; ++q)
         out.d[q] = 0x3F803F80u | (((bits >> (2 * q)) & 1u) << 15) | (((bits >> (2 * q + 1)) & 1u) << 31);
     return out.v;
+}
+
+// One output by fp32 multiply-adds, unscaled; ends early where nothing can change the result any more.
+template <typename T, int AMODE, int BMODE>
+__device__ __forceinline__ float plain_dot(const PlainArgs &g, int64_t r, int64_t c) {
+    const T *A = reinterpret_cast<const T *>(g.A), *B = reinterpret_cast<const T *>(g.B);
+    float sum = 0.0f;
+#pragma unroll 1
+    for (int64_t kk = 0; kk < g.K && sum == sum; ++kk) {
+        float a;
+        if constexpr (AMODE == PA_K)
+            a = load_f32<T>(A + r * g.lda + kk);
+        else if constexpr (AMODE == PA_M)
+            a = load_f32<T>(A + kk * g.lda + r);
+        else
+            a = sketch_entry_precise(g.kind, g.st, kk, r);
+        sum = fmaf(a, load_f32<T>(BMODE == PB_K ? B + c * g.ldb + kk : B + kk * g.ldb + c), sum);
+    }
+    return sum;
 }
 
 // Output tile number `block` of `blocks`.
@@ -313,7 +340,7 @@ __device__ __forceinline__ void plain_tile(const PlainArgs &g, bf16_t *lds, int6
                     float e[8];
                     gauss_eight_precise(g.st, tok, col, e);
                     bf16x8_t o[PA];
-                    split_eight<PA>(e, o);
+                    split_eight(e, o);
 #pragma unroll
                     for (int s = 0; s < PA; ++s) *reinterpret_cast<bf16x8_t *>(to + s * L::A_PLANE) = o[s];
                 } else {
@@ -395,41 +422,62 @@ __device__ __forceinline__ void plain_tile(const PlainArgs &g, bf16_t *lds, int6
     Tout *C = reinterpret_cast<Tout *>(g.C);
     const T *bias = reinterpret_cast<const T *>(g.bias);
     const int half = lane >> 5;
-    auto put_out = [&](int64_t r, int64_t c, float x, float bv) {
-        if (r >= g.M || c >= g.N) return;
-        x = g.alpha * x;
+    constexpr bool SPLIT = PA + PB > 2;  // planes: sums that are not finite are made again
+    const float alpha = g.alpha * (PA == 3 && !GEN ? kSplitDown : 1.0f) * (PB == 3 ? kSplitDown : 1.0f);  // (exact)
+    auto write = [&](int64_t r, int64_t c, float x, float bv) {
         if (g.bias != nullptr) x += bv;
         if (g.accumulate) x += load_f32<Tout>(C + r * g.ldc + c);
         store_f32<Tout>(C + r * g.ldc + c, x);
     };
+    uint32_t open = 0;  // bit e: this lane's output number e is still to be made
+    auto put_out = [&](int e, int64_t r, int64_t c, float x, float bv) {
+        if (r >= g.M || c >= g.N) return;
+        if (SPLIT && !__builtin_isfinite(x))
+            open |= 1u << e;
+        else
+            write(r, c, alpha * x, bv);
+    };
+    auto bias_at = [&](int64_t c) { return bias != nullptr && c < g.N ? load_f32<T>(bias + c) : 0.0f; };
+    auto row_of = [&](int v) { return 8 * (v / 4) + 4 * half + v % 4; };
+    constexpr int OWN = 16 / S::WK;
     if constexpr (S::WK > 1) {
         // The waves that shared a 32x32 tile's contraction each finish 16 / WK of its registers.
         static_assert(TM == 1 && TN == 1, "one 32x32 tile per wave");
-        constexpr int OWN = 16 / S::WK, WAVES = S::WM * S::WN;
+        constexpr int WAVES = S::WM * S::WN;
         float *red = reinterpret_cast<float *>(lds);
 #pragma unroll
         for (int v = 0; v < 16; ++v) red[(wave * 16 + v) * 64 + lane] = acc[0][0][v];
         __syncthreads();
         const int64_t c = n0 + wn * 32 + (lane & 31);
-        const float bv = bias != nullptr && c < g.N ? load_f32<T>(bias + c) : 0.0f;
+        const float bv = bias_at(c);
 #pragma unroll
         for (int u = 0; u < OWN; ++u) {
             const int v = kg * OWN + u;
             float x = 0.0f;
 #pragma unroll
             for (int p = 0; p < S::WK; ++p) x += red[((p * WAVES + wave % WAVES) * 16 + v) * 64 + lane];
-            put_out(m0 + wm * 32 + 8 * (v / 4) + 4 * half + v % 4, c, x, bv);
+            put_out(u, m0 + wm * 32 + row_of(v), c, x, bv);
         }
     } else {
+        static_assert(TM * TN * 16 <= 32, "one bit per output of a lane");
 #pragma unroll
         for (int w = 0; w < TN; ++w) {
             const int64_t c = n0 + wn * (BN / S::WN) + w * 32 + (lane & 31);
-            const float bv = bias != nullptr && c < g.N ? load_f32<T>(bias + c) : 0.0f;
+            const float bv = bias_at(c);
 #pragma unroll
             for (int u = 0; u < TM; ++u)
 #pragma unroll
                 for (int v = 0; v < 16; ++v)
-                    put_out(m0 + wm * (BM / S::WM) + u * 32 + 8 * (v / 4) + 4 * half + v % 4, c, acc[u][w][v], bv);
+                    put_out((w * TM + u) * 16 + v, m0 + wm * (BM / S::WM) + u * 32 + row_of(v), c, acc[u][w][v], bv);
+        }
+    }
+    if constexpr (SPLIT) {
+        while (open != 0) {
+            const int e = __ffs(open) - 1, v = S::WK > 1 ? kg * OWN + e : e % 16, u = S::WK > 1 ? 0 : e / 16 % TM,
+                      w = S::WK > 1 ? 0 : e / 16 / TM;
+            open &= open - 1;
+            const int64_t r = m0 + wm * (BM / S::WM) + u * 32 + row_of(v), c = n0 + wn * (BN / S::WN) + w * 32 + (lane & 31);
+            write(r, c, g.alpha * plain_dot<T, AMODE, BMODE>(g, r, c), bias_at(c));
         }
     }
 }
