@@ -96,6 +96,21 @@ def test_gaussian_tile_fp32(i0, j0, rows, cols):
     assert rel_fro(got, want) < 1e-6
 
 
+def test_gaussian_entries_of_the_fp32_path_are_as_exact_as_library_functions():
+    """Error against fp64 in units of the last place, over 2^22 entries (every radius and every angle many
+    times).  sqrtf, logf and sincospif give 0.634 rms.  Largest: the factors are within 1.5 and 0.9 ulp, up to
+    twice as much in ulps of their product, plus its rounding."""
+    seed, offset, n, k = 0x5EED0051, 9, 4096, 1024
+    got = rmm.rmm_debug_sketch_tile(rmm.GAUSSIAN, seed, offset, 0, 0, n, k).cpu().numpy().astype(np.float64)
+    want = o_sketch.sketch_P(n, k, o_sketch.GAUSSIAN, seed, offset)
+    ulp = np.exp2(np.floor(np.log2(np.maximum(np.abs(want), 2.0 ** -60))) - 23)
+    some = np.abs(want) > 1e-6                # (at a quarter turn the oracle's own rounded angle gives 1e-16, not 0)
+    err = np.abs(got - want)[some] / ulp[some]
+    print("rms %.4f ulp, largest %.3f" % (np.sqrt(np.mean(err ** 2)), err.max()), flush=True)
+    assert np.all(np.abs(got[~some]) < 1e-6)
+    assert np.sqrt(np.mean(err ** 2)) <= 0.60 and err.max() <= 5.3
+
+
 @pytest.mark.parametrize("kind", [rmm.GAUSSIAN, rmm.RADEMACHER])
 @pytest.mark.parametrize("n,k", [(1024, 520), (1024, 200), (768, 600), (768, 100), (520, 130), (1032, 40), (1032, 17),
                                  (4096, 410), (2056, 1638), (392, 65)])
