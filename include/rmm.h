@@ -146,7 +146,8 @@ int rmm_forward(const rmm_layer_desc_t *desc, rmm_rng_state_t state, const void 
 /* Algorithm 1, Backward, with the state given to the forward call:
  * dX[n x d_in] = dY[n x d_out] W (Eq. 2), dW[d_out x d_in] = (S^T dY)^T X_proj,
  * and, if dbias != NULL, dbias[d_out] = dY^T 1 (Eq. 3).  dX may be NULL to skip
- * the input gradient (first layer of a network). */
+ * the input gradient (first layer of a network).  With dbias the tokens may be cut into other
+ * slices, so dW can differ in its last bits from a call without. */
 int rmm_backward(const rmm_layer_desc_t *desc, rmm_rng_state_t state, const void *dY, const void *W,
                  const void *X_proj, void *dX, void *dW, void *dbias, void *ws, size_t ws_bytes,
                  void *stream);

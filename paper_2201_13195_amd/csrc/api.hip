@@ -122,7 +122,7 @@ private:
 template <typename T>
 int sketch_impl(int64_t n, int64_t d, int64_t k, int kind, SketchState st, const void *A, void *out, bool mfma,
                 void *ws, hipStream_t stream, const StageEvents &ev = StageEvents(), int product_stage = RMM_STAGE_NONE,
-                int64_t d_other = 0) {
+                int64_t d_other = 0, bool with_dbias = false) {
     const bool timed = product_stage != RMM_STAGE_NONE && ev.stage == product_stage;
     if (kind == RMM_SKETCH_SORS && mfma && sors_fast_ok(n, d)) {  // fast transform; otherwise S is applied densely below
         StageScope scope(ev, product_stage, stream);
@@ -130,7 +130,7 @@ int sketch_impl(int64_t n, int64_t d, int64_t k, int kind, SketchState st, const
     }
     if (mfma && kind != RMM_SKETCH_SORS)
         return from_hip(launch_sketch_bf16((const bf16_t *)A, (bf16_t *)out, n, d, k, kind, st, ws, stream,
-                                           timed ? ev.begin : nullptr, timed ? ev.end : nullptr, d_other));
+                                           timed ? ev.begin : nullptr, timed ? ev.end : nullptr, d_other, with_dbias));
     StageScope scope(ev, product_stage, stream);  // the plain path is one kernel
     return from_hip(launch_forward_plain<T>((const T *)A, nullptr, nullptr, nullptr, (T *)out, n, d, d, k, kind, st, stream));
 }
@@ -205,7 +205,7 @@ int backward_impl(const rmm_layer_desc_t *d, SketchState st, const void *dY, con
         db_done = dbias != nullptr && !own_db_stage && backward_pair_takes_colsum(d->n, d->d_in, d->d_out, d->k, d->kind);
         e = launch_backward_pair_bf16((const bf16_t *)dY, (const bf16_t *)W, (bf16_t *)dX, (bf16_t *)G, d->n, d->d_in,
                                       d->d_out, d->k, d->kind, st, (char *)ws + g_bytes(d), stream,
-                                      timed ? ev.begin : nullptr, timed ? ev.end : nullptr,
+                                      timed ? ev.begin : nullptr, timed ? ev.end : nullptr, dbias != nullptr,
                                       db_done ? (bf16_t *)dbias : nullptr, accumulate);
         if (e != hipSuccess) return RMM_ERR_LAUNCH;
     }
@@ -220,7 +220,7 @@ int backward_impl(const rmm_layer_desc_t *d, SketchState st, const void *dY, con
     if (!paired) {
         StageScope scope(ev, RMM_STAGE_BWD_G, stream);
         int rc = sketch_impl<T>(d->n, d->d_out, d->k, d->kind, st, dY, G, mfma, (char *)ws + g_bytes(d), stream, ev,
-                                RMM_STAGE_BWD_G_PRODUCT, d->d_in);
+                                RMM_STAGE_BWD_G_PRODUCT, d->d_in, dbias != nullptr);
         if (rc != RMM_OK) return rc;
     }
     if (mfma && dbias != nullptr && !db_done && !own_db_stage) {

@@ -74,11 +74,12 @@ hipError_t launch_dw_colsum_bf16(const bf16_t *G, const bf16_t *X_proj, bf16_t *
 // `d_other` > 0 says that the sketch product belongs to a layer pass whose plain product has an
 // n x d_other output (forward: d = d_in, d_other = d_out; backward: d = d_out, d_other = d_in): the
 // token slicing is then the one the paired launch of that pass uses, so that the separate and the
-// paired launches give the same bits.  0 = the product on its own (rmm_sketch).
+// paired launches give the same bits.  0 = the product on its own (rmm_sketch).  `with_dbias`: a backward
+// pass that also makes the bias gradient (it may slice the tokens otherwise).
 size_t sketch_workspace_bf16(int64_t n, int64_t d, int64_t k, int64_t d_other = 0);
 hipError_t launch_sketch_bf16(const bf16_t *A, bf16_t *out, int64_t n, int64_t d, int64_t k, int kind, SketchState st,
                               void *ws, hipStream_t stream, hipEvent_t ev_begin = nullptr,
-                              hipEvent_t ev_end = nullptr, int64_t d_other = 0);
+                              hipEvent_t ev_end = nullptr, int64_t d_other = 0, bool with_dbias = false);
 
 // One launch for the two products of a pass that do not depend on each other: Y = X W^T (+ bias)
 // with the sketch product of X (forward), dX = dY W with the sketch product of dY (backward; G is
@@ -89,12 +90,13 @@ bool pass_pair_available(int64_t k);
 hipError_t launch_forward_pair_bf16(const bf16_t *X, const bf16_t *W, const bf16_t *bias, bf16_t *Y, bf16_t *X_proj,
                                     int64_t n, int64_t d_in, int64_t d_out, int64_t k, int kind, SketchState st, void *ws,
                                     hipStream_t stream, hipEvent_t ev_begin = nullptr, hipEvent_t ev_end = nullptr);
-// With `dbias` the launch also takes the column sums of dY (the bias gradient), on the compute units
-// its last round leaves idle; backward_pair_takes_colsum() says where that beats the launch of dW.
+// `with_dbias`: the pass makes the bias gradient, in whichever launch.  With `dbias` this launch takes the
+// column sums of dY, on the compute units its last round leaves idle; backward_pair_takes_colsum() says where that
+// beats the launch of dW.
 hipError_t launch_backward_pair_bf16(const bf16_t *dY, const bf16_t *W, bf16_t *dX, bf16_t *G, int64_t n, int64_t d_in,
                                      int64_t d_out, int64_t k, int kind, SketchState st, void *ws, hipStream_t stream,
-                                     hipEvent_t ev_begin = nullptr, hipEvent_t ev_end = nullptr, bf16_t *dbias = nullptr,
-                                     bool accumulate_dbias = false);
+                                     hipEvent_t ev_begin, hipEvent_t ev_end, bool with_dbias, bf16_t *dbias,
+                                     bool accumulate_dbias);
 bool backward_pair_takes_colsum(int64_t n, int64_t d_in, int64_t d_out, int64_t k, int kind);
 
 // SORS sketch kind, bf16 (sors.hip): signs, Walsh-Hadamard transform along the tokens and row

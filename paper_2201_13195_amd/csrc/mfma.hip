@@ -300,6 +300,34 @@ SketchPlan plan_pass_sketch(int64_t n, int64_t d_sk, int64_t d_other, int64_t k,
     return paired.splits >= 2 ? paired : alone;
 }
 
+// Whether the launch of dW has room for the column sums of the bias gradient beside it.
+bool dw_takes_colsum(int64_t d_in, int64_t d_out, int64_t k) {
+    const int dw_cfg = gemm_cfg(d_out, d_in, k);
+    if (dw_cfg == GEMM_FEW) {
+        const int edge = few_edge(d_out, d_in);
+        return tiles_of(d_out, d_in, edge, edge) + colsum_blocks(d_out, 2) <= (edge == 64 ? 256 : 512);
+    }
+    const int64_t dw_tiles = dw_cfg == GEMM_LARGE ? tiles_of(d_out, d_in, ShapeLarge::BM, ShapeLarge::BN) : tiles_of(d_out, d_in, 128, 128);
+    return (256 - dw_tiles % 256) % 256 >= 64;
+}
+
+// Compute units that the last round of a backward pass's paired launch leaves idle.
+int64_t pair_idle(int64_t n, int64_t d_in, int64_t d_out, const SketchPlan &p) {
+    return (256 - (pair_plain(n, d_in, d_out).tiles + p.shares()) % 256) % 256;
+}
+
+// Plan of the sketch product of dY.  With a bias gradient that the launch of dW has no room for, short last slices
+// that take the compute units its column sums need are given up (16384 x 1024 -> 4096, k = 1638: 208 sketch
+// work-groups instead of 243).
+SketchPlan plan_backward_sketch(int64_t n, int64_t d_in, int64_t d_out, int64_t k, int kind, bool with_dbias) {
+    const SketchPlan p = plan_pass_sketch(n, d_out, d_in, k, kind);
+    if (!with_dbias || p.per_tail == 0 || p.slices < 2 || dw_takes_colsum(d_in, d_out, k) || pair_idle(n, d_in, d_out, p) >= 16) return p;
+    SketchPlan even = p;
+    const int64_t units = (n + 63) / 64, len = (units + p.slices - 1) / p.slices;
+    even.per_tail = 0, even.k_chunk = len * 64, even.slices = even.splits = (int)((units + len - 1) / len);
+    return even.splits >= 2 && pair_idle(n, d_in, d_out, even) >= 16 ? even : p;
+}
+
 }  // namespace
 
 bool mfma_shape_ok(int64_t n, int64_t d_in, int64_t d_out, int64_t k) {
@@ -415,7 +443,8 @@ hipError_t launch_xty_norms_bf16(const bf16_t *X, const bf16_t *dY, double *part
     }
 }
 
-// The two dense kinds may take different tiles and slices; a workspace serves either.
+// The two dense kinds may take different tiles and slices; a workspace serves either (and both plans of
+// plan_backward_sketch: the one with a bias gradient has fewer slices).
 size_t sketch_workspace_bf16(int64_t n, int64_t d, int64_t k, int64_t d_other) {
     int64_t k_chunk;
     size_t most = 0;
@@ -432,7 +461,8 @@ size_t sketch_workspace_bf16(int64_t n, int64_t d, int64_t k, int64_t d_other) {
 }
 
 hipError_t launch_sketch_bf16(const bf16_t *A, bf16_t *out, int64_t n, int64_t d, int64_t k, int kind, SketchState st,
-                              void *ws, hipStream_t stream, hipEvent_t ev_begin, hipEvent_t ev_end, int64_t d_other) {
+                              void *ws, hipStream_t stream, hipEvent_t ev_begin, hipEvent_t ev_end, int64_t d_other,
+                              bool with_dbias) {
     EventPair pev(ev_begin, ev_end, stream);
     if (k <= kSmallK) {  // bound by one pass over A: streaming kernel
         SmallkArgs a{};
@@ -451,7 +481,9 @@ hipError_t launch_sketch_bf16(const bf16_t *A, bf16_t *out, int64_t n, int64_t d
         if (e != hipSuccess || slices == 1) return e;
         return launch_reduce(ws, out, k, d, slices, stream);
     }
-    const SketchPlan p = d_other > 0 ? plan_pass_sketch(n, d, d_other, k, kind) : plan_sketch(n, d, k, kind, true);
+    const SketchPlan p = with_dbias    ? plan_backward_sketch(n, d_other, d, k, kind, true)
+                         : d_other > 0 ? plan_pass_sketch(n, d, d_other, k, kind)
+                                       : plan_sketch(n, d, k, kind, true);
     const GemmArgs g = args_sketch(A, n, d, k, st, p, out, ws);
     hipError_t e = launch_sketch_plan(p, kind, g, stream);
     pev.done();
@@ -478,27 +510,21 @@ hipError_t launch_forward_pair_bf16(const bf16_t *X, const bf16_t *W, const bf16
 // dW when that leaves at least 64 compute units idle (dW is short and mostly latency; where it runs on
 // few_tile, whose work-groups want a compute unit each, when the column blocks fit beside them);
 // otherwise into the paired launch when its last round leaves at least 16 idle (the sketch work-groups
-// of that round run for long, and dY is being read there anyway) or dW has no room; otherwise into
-// the launch of dW.
+// of that round run for long, and dY is being read there anyway; plan_backward_sketch sees to it where it
+// can); otherwise into the launch of dW.
 bool backward_pair_takes_colsum(int64_t n, int64_t d_in, int64_t d_out, int64_t k, int kind) {
     if (!pass_pair_available(k)) return false;
-    const int dw_cfg = gemm_cfg(d_out, d_in, k);
-    if (dw_cfg == GEMM_FEW) {
-        const int edge = few_edge(d_out, d_in);
-        return tiles_of(d_out, d_in, edge, edge) + colsum_blocks(d_out, 2) > (edge == 64 ? 256 : 512);
-    }
-    const int64_t dw_tiles = dw_cfg == GEMM_LARGE ? tiles_of(d_out, d_in, ShapeLarge::BM, ShapeLarge::BN) : tiles_of(d_out, d_in, 128, 128);
-    if ((256 - dw_tiles % 256) % 256 >= 64) return false;
-    const SketchPlan p = plan_pass_sketch(n, d_out, d_in, k, kind);
-    const int64_t total = pair_plain(n, d_in, d_out).tiles + p.shares();
-    return (256 - total % 256) % 256 >= 16;
+    return !dw_takes_colsum(d_in, d_out, k) &&
+           (gemm_cfg(d_out, d_in, k) == GEMM_FEW ||
+            pair_idle(n, d_in, d_out, plan_backward_sketch(n, d_in, d_out, k, kind, true)) >= 16);
 }
 
 hipError_t launch_backward_pair_bf16(const bf16_t *dY, const bf16_t *W, bf16_t *dX, bf16_t *G, int64_t n, int64_t d_in,
                                      int64_t d_out, int64_t k, int kind, SketchState st, void *ws, hipStream_t stream,
-                                     hipEvent_t ev_begin, hipEvent_t ev_end, bf16_t *dbias, bool accumulate_dbias) {
+                                     hipEvent_t ev_begin, hipEvent_t ev_end, bool with_dbias, bf16_t *dbias,
+                                     bool accumulate_dbias) {
     const GemmArgs ga = args_nn(dY, W, dX, n, d_in, d_out);
-    const SketchPlan p = plan_pass_sketch(n, d_out, d_in, k, kind);
+    const SketchPlan p = plan_backward_sketch(n, d_in, d_out, k, kind, with_dbias);
     const GemmArgs gb = args_sketch(dY, n, d_out, k, st, p, G, ws);
     const ColsumArgs gc{dY, dbias, n, d_out, accumulate_dbias ? 1 : 0, colsum_lpr(d_out, 2)};
     const ColsumArgs *gcp = dbias != nullptr ? &gc : nullptr;

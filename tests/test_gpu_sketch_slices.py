@@ -3,9 +3,10 @@ work-group), with ragged token counts and edges, against the fp64 oracle."""
 import math
 
 import pytest
+import torch
 
 import paper_2201_13195_amd as rmm
-from paper_2201_13195_amd import synth
+from paper_2201_13195_amd import binding, synth
 from test_gpu_parity import check_layer
 
 pytestmark = pytest.mark.gpu
@@ -20,3 +21,23 @@ def test_long_and_short_slices(shape, kind):
     n, d_in, d_out, k = shape
     X, W, dY = synth.layer_inputs(n, d_in, d_out, "bf16", (n, d_in + 1, d_out + 2), w_std=1.0 / math.sqrt(d_in))
     check_layer(X, W, dY, k, kind, 0x5EED0061, 11, "bf16", label="slices %s" % (shape,))
+
+
+@pytest.mark.parametrize("kind", [rmm.GAUSSIAN, rmm.RADEMACHER])
+def test_slices_of_a_pass_with_a_bias_gradient(kind):
+    """Short last slices given up for the column sums of dY: G differs from the pass without bias in the order of its
+    sums only, and asking for a stage's events (separate launches) changes no bit."""
+    n, d_in, d_out, k = 8192, 1000, 4000, 800
+    X, W, dY = synth.layer_inputs(n, d_in, d_out, "bf16", (71, 72, 73), w_std=1.0 / math.sqrt(d_in))
+    bias = synth.to_torch(synth.normal((d_out,), 17), "bf16")
+    check_layer(X, W, dY, k, kind, 0x5EED0062, 12, "bf16", bias=bias, label="slices with bias")
+    dev = [t.to("cuda") for t in (dY, W)]
+    Xp = rmm.rmm_sketch(X.to("cuda"), k, kind, 0x5EED0062, 12)
+    a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    a.record(); b.record()
+    torch.cuda.synchronize()
+    one = rmm.rmm_backward(*dev, Xp, kind, 0x5EED0062, 12, need_dbias=True)
+    for stage in (binding.STAGE_BWD_DX, binding.STAGE_BWD_G, binding.STAGE_BWD_DW, binding.STAGE_BWD_DBIAS):
+        for x, y in zip(one, rmm.rmm_backward(*dev, Xp, kind, 0x5EED0062, 12, need_dbias=True, profile=(stage, a, b))):
+            assert torch.equal(x, y), stage
+    assert torch.equal(one[1], rmm.rmm_backward(*dev, Xp, kind, 0x5EED0062, 12, need_dX=False, need_dbias=True)[1])
