@@ -85,14 +85,14 @@ hipError_t launch_gemm(int cfg, const GemmArgs &g, hipStream_t stream) {
 GemmArgs args_nt(const bf16_t *X, const bf16_t *W, const bf16_t *bias, bf16_t *Y, int64_t n, int64_t d_in, int64_t d_out) {
     GemmArgs g{};
     g.A = X, g.lda = d_in, g.B = W, g.ldb = d_in, g.C = Y, g.ldc = d_out, g.bias = bias;
-    g.M = n, g.N = d_out, g.K = d_in, g.alpha = 1.0f, g.k_chunk = (d_in + 127) / 128 * 128;
+    g.M = n, g.N = d_out, g.K = d_in, g.alpha = 1.0f;
     return g;
 }
 
 GemmArgs args_nn(const bf16_t *dY, const bf16_t *W, bf16_t *dX, int64_t n, int64_t d_in, int64_t d_out) {
     GemmArgs g{};
     g.A = dY, g.lda = d_out, g.B = W, g.ldb = d_in, g.C = dX, g.ldc = d_in, g.bias = nullptr;
-    g.M = n, g.N = d_in, g.K = d_out, g.alpha = 1.0f, g.k_chunk = (d_out + 127) / 128 * 128;
+    g.M = n, g.N = d_in, g.K = d_out, g.alpha = 1.0f;
     return g;
 }
 
@@ -362,7 +362,7 @@ hipError_t launch_dw_bf16(const bf16_t *G, const bf16_t *X_proj, bf16_t *dW, int
     GemmArgs g{};
     g.accumulate = accumulate ? 1 : 0;
     g.A = G, g.lda = d_out, g.B = X_proj, g.ldb = d_in, g.C = dW, g.ldc = d_in, g.bias = nullptr;
-    g.M = d_out, g.N = d_in, g.K = k, g.alpha = 1.0f, g.k_chunk = (k + 127) / 128 * 128;
+    g.M = d_out, g.N = d_in, g.K = k, g.alpha = 1.0f;
     return launch_gemm<A_MCONTIG, B_NCONTIG, OUT_BF16>(gemm_cfg(g.M, g.N, g.K), g, stream);
 }
 
@@ -393,7 +393,7 @@ hipError_t launch_dw_colsum_bf16(const bf16_t *G, const bf16_t *X_proj, bf16_t *
     GemmArgs g{};
     g.accumulate = accumulate ? 1 : 0;
     g.A = G, g.lda = d_out, g.B = X_proj, g.ldb = d_in, g.C = dW, g.ldc = d_in, g.bias = nullptr;
-    g.M = d_out, g.N = d_in, g.K = k, g.alpha = 1.0f, g.k_chunk = (k + 127) / 128 * 128;
+    g.M = d_out, g.N = d_in, g.K = k, g.alpha = 1.0f;
     const ColsumArgs c{dY, dbias, n, d_out, accumulate ? 1 : 0, colsum_lpr(d_out, 2)};
     switch (gemm_cfg(g.M, g.N, g.K)) {  // the tile dW runs with on its own
         case GEMM_LARGE: {  // 160 or more tiles of 256 x 256: dW fills the chip, the column sums follow as a launch of their own
@@ -434,7 +434,7 @@ hipError_t launch_xty_norms_bf16(const bf16_t *X, const bf16_t *dY, double *part
                                  int64_t d_out, hipStream_t stream) {
     GemmArgs g{};
     g.A = X, g.lda = d_in, g.B = dY, g.ldb = d_out, g.C = part, g.ldc = d_out, g.bias = nullptr;
-    g.M = d_in, g.N = d_out, g.K = n, g.alpha = 1.0f, g.k_chunk = (n + 127) / 128 * 128;
+    g.M = d_in, g.N = d_out, g.K = n, g.alpha = 1.0f;
     const RowNormArgs r{X, dY, n, d_in, d_out, 1, rows};
     switch (xty_cfg(g.M, g.N, g.K)) {
         case GEMM_LARGE: return launch_xty_norms<ShapeLarge>(g, r, stream);

@@ -1,26 +1,28 @@
-// bf16 MFMA kernels of the RMM layer (gfx950).
-//
-// One tiled-GEMM body (gemm_tile) covers the five products of Algorithm 1:
+// bf16 MFMA kernels of the RMM layer (gfx950): the five products of Algorithm 1,
 //
 //   Y      = X W^T          A = X  (K-contiguous rows)      B = W      (K-contiguous rows)
-//   dX     = dY W           A = dY (K-contiguous rows)      B = W      (N-contiguous rows)
-//   X_proj = S^T X          A = P^T generated on chip       B = X      (N-contiguous rows)
-//   G      = S^T dY         A = P^T generated on chip       B = dY     (N-contiguous rows)
-//   dW     = G^T X_proj     A = G  (M-contiguous rows)      B = X_proj (N-contiguous rows)
+//   dX     = dY W           A = dY (K-contiguous rows)      B = W      (row-indexed)
+//   X_proj = S^T X          A = P^T generated on chip       B = X      (row-indexed)
+//   G      = S^T dY         A = P^T generated on chip       B = dY     (row-indexed)
+//   dW     = G^T X_proj     A = G  (row-indexed)            B = X_proj (row-indexed)
 //
-// with C[M x N] = alpha * sum_kk A(m, kk) B(kk, n).  The contraction runs on
-// v_mfma_f32_32x32x16_bf16 with fp32 accumulators.  Memory operands go through LDS in 16-byte
-// chunks, three stages deep, with up to four more tiles in flight in registers.  An operand
-// whose contraction index is its row index ("N-contiguous" / "M-contiguous") is read back from
-// LDS with the transposing load ds_read_b64_tr_b16, which hands every lane four consecutive
-// contraction elements of one column.  The sketch operand is never in memory: the work-group
-// generates its tile of P^T into LDS (one 16-byte chunk = 8 consecutive tokens of one sketch column
-// = one Philox-4x32-10 call for the Gaussian kind, one byte of a call's 128 sign bits for the
-// Rademacher kind).  The 1/sqrt(k) of S = P/sqrt(k) is applied to the fp32 accumulator, so
-// P is exact in bf16 for Rademacher and rounded once for Gaussian.
-// gemm_mfma_kernel runs the body for one product, gemm_pair_kernel for the two independent
-// products of a pass in one grid; sketch_smallk_kernel is the streaming kernel of small sketch
-// sizes; reduce_partials_kernel sums the partial results of token slices.
+// with C[M x N] = alpha * sum_kk A(m, kk) B(kk, n) on v_mfma_f32_32x32x16_bf16, fp32 accumulators.  An
+// operand whose contraction index is its row index is read back from LDS with the transposing load
+// ds_read_b64_tr_b16, which hands every lane four consecutive contraction elements of one column.
+//
+//   gemm_tile_dma   Y and dX on 256 x 256 tiles: memory straight into LDS, two stages of 64 contraction elements
+//   gemm_tile       Y, dX, dW and X^T dY on 128 x 128 tiles (X^T dY also on 256 x 256): 16-byte chunks through
+//                   registers into three LDS stages, up to four more tiles in flight in registers
+//   few_tile        products with few output tiles: the waves of a work-group share the contraction, no barriers
+//   sketch_tile     sketch products with k > 64, in the pipeline of gemm_tile_dma.  The sketch operand is never in
+//                   memory: the work-group generates its tile of P^T into LDS (one 16-byte chunk = 8 consecutive
+//                   tokens of one sketch column = one Philox-4x32-10 call for the Gaussian kind, one byte of a
+//                   call's 128 sign bits for the Rademacher kind).  The 1/sqrt(k) of S = P/sqrt(k) is applied to
+//                   the fp32 accumulator, so P is exact in bf16 for Rademacher and rounded once for Gaussian
+//   sketch_smallk_kernel    the streaming kernel of small sketch sizes
+//   reduce_partials_kernel  sums the partial results of token slices
+//
+// gemm_pair_kernel runs a plain product and the sketch product of a pass in one grid.
 #pragma once
 #include <type_traits>
 
@@ -42,7 +44,7 @@ struct GemmArgs {
     float alpha;
     int accumulate;        // bf16 output only: add the value C holds (in fp32, before the one rounding)
     SketchState st;
-    int64_t k_chunk;       // sketch products: tokens per slice (multiple of 64); others: at least K
+    int64_t k_chunk;       // sketch products: tokens per slice (multiple of 64)
     int slices, per_tail;  // sketch products: slices of k_chunk tokens of every tile; tiles whose last, short slice a further work-group takes
     int64_t split_stride;  // fp32 elements between the partial results of two slices
     int direct;            // partial-result kernels: there is one slice, write the bf16 result itself
@@ -50,11 +52,10 @@ struct GemmArgs {
 
 namespace {
 
-// A operand: loaded K-contiguous / loaded row-indexed / sketch generated by the whole work-group into
-// the K-contiguous LDS tile.
+// Operands: rows along the contraction / rows across it (the contraction index is the row).
 enum { A_KCONTIG = 0, A_MCONTIG = 1 };
 enum { B_KCONTIG = 0, B_NCONTIG = 1 };
-// Output: rounded to bf16 / fp32 partial result of a contraction slice (bf16 if the only one) / no matrix at all, only
+// Output: rounded to bf16 / fp32 partial result of a token slice (streaming sketch kernel) / no matrix at all, only
 // the sum of squares of the tile (one double per work-group, C = double[work-groups]).
 enum { OUT_BF16 = 0, OUT_F32_PARTIAL = 1, OUT_SUMSQ = 2 };
 
@@ -142,7 +143,7 @@ struct Tile {
 constexpr int kStripBytes = 32 * (128 + 16);
 template <bool BF16, bool BIAS, bool ACCUMULATE, int TM, int TN, int WAVES_K>
 __device__ __forceinline__ void write_tile(const GemmArgs &g, const f32x16_t (&acc)[TM][TN], char *stage, int64_t m0, int64_t n0,
-                                           int wm, int wn, int kg, int lane, int slice) {
+                                           int wm, int wn, int kg, int lane, int slice = 0) {
     constexpr int WTM = 32 * TM, WTN = 32 * TN;
     constexpr int OWN = TM * TN / WAVES_K;               // tiles of a wave when WAVES_K groups share them
     constexpr int EB = BF16 ? 2 : 4;                     // bytes per output element
@@ -237,9 +238,9 @@ __device__ __forceinline__ void write_tile(const GemmArgs &g, const f32x16_t (&a
 }
 
 // One work-group's share of a product: output tile number `block` of `blocks` (before the
-// renumbering below), contraction slice `slice`.  `lds` holds Tile::LDS_BYTES bytes.
+// renumbering below).  `lds` holds Tile::LDS_BYTES bytes.
 template <typename S, int AMODE, int BMODE, int OUT, int D>
-__device__ __forceinline__ void gemm_tile(const GemmArgs &g, bf16_t *lds, int64_t block, int64_t blocks, int slice) {
+__device__ __forceinline__ void gemm_tile(const GemmArgs &g, bf16_t *lds, int64_t block, int64_t blocks) {
     constexpr int BM = S::BM, BN = S::BN, BK = S::BK, WAVES_M = S::WM, WAVES_N = S::WN, WAVES_K = S::WK;
     typedef Tile<BM, BN, BK, WAVES_M, WAVES_N, WAVES_K, AMODE, BMODE, OUT> T;
 
@@ -263,9 +264,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &g, bf16_t *lds, int64_
     const int64_t band = tile / (GROUP_M * tiles_n), in_band = tile % (GROUP_M * tiles_n);
     const int64_t band_rows = min(GROUP_M, tiles_m - band * GROUP_M);
     const int64_t m0 = (band * GROUP_M + in_band % band_rows) * BM, n0 = (in_band / band_rows) * BN;
-    const int64_t kk_begin = (int64_t)slice * g.k_chunk;
-    const int64_t kk_end = min(g.K, kk_begin + g.k_chunk);
-    const int num_tiles = kk_end > kk_begin ? (int)((kk_end - kk_begin + BK - 1) / BK) : 0;
+    const int kk_len = (int)g.K, num_tiles = (kk_len + BK - 1) / BK;
 
     f32x16_t acc[T::TM][T::TN];
 #pragma unroll
@@ -281,7 +280,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &g, bf16_t *lds, int64_
     // the whole operand, only what this work-group reads of it, so that its 32-bit offsets suffice
     // for operands of any size: a K-contiguous operand is described from the first row of the tile
     // (BM or BN rows, fixed for the kernel), a row-indexed operand from the first contraction row
-    // of each tile (BK rows, re-based at every step; rows beyond the slice fall outside the range).
+    // of each tile (BK rows, re-based at every step; rows beyond the contraction fall outside the range).
     constexpr uint32_t OOB = 0x80000000u;
     auto rows_rsrc = [](const bf16_t *base, int64_t ld, int64_t rows) {  // `rows` rows of pitch ld starting at base
         // (the byte count is the same in every lane; saying so keeps the descriptor in scalar registers)
@@ -289,7 +288,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &g, bf16_t *lds, int64_
         return __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(base), (short)0, bytes, 0x00020000);
     };
 
-    // Per 16-byte chunk of a tile: byte offset in the operand for the first tile of this slice,
+    // Per 16-byte chunk of a tile: byte offset in the operand for the first tile,
     // whether its row / column group exists at all, and its position along the contraction.
     uint32_t a_off[T::A_CHUNKS], b_off[T::B_CHUNKS];
     bool a_ok[T::A_CHUNKS], b_ok[T::B_CHUNKS];
@@ -301,7 +300,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &g, bf16_t *lds, int64_
             const int c = tid + T::THREADS * q, row = c / (BK / 8), kc = c % (BK / 8);
             a_ok[q] = m0 + row < g.M;
             a_kk[q] = kc * 8;
-            a_off[q] = (uint32_t)((row * g.lda + kk_begin + kc * 8) * 2);  // from row m0
+            a_off[q] = (uint32_t)((row * g.lda + kc * 8) * 2);  // from row m0
             a_lds[q] = row * T::A_STRIDE + kchunk_pos<BK>(row, kc) * 8;
         }
     } else if constexpr (AMODE == A_MCONTIG) {  // A stored [kk][m], tile BK x BM
@@ -320,7 +319,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &g, bf16_t *lds, int64_
             const int c = tid + T::THREADS * q, row = c / (BK / 8), kc = c % (BK / 8);
             b_ok[q] = n0 + row < g.N;
             b_kk[q] = kc * 8;
-            b_off[q] = (uint32_t)((row * g.ldb + kk_begin + kc * 8) * 2);  // from row n0
+            b_off[q] = (uint32_t)((row * g.ldb + kc * 8) * 2);  // from row n0
             b_lds[q] = row * T::B_STRIDE + kchunk_pos<BK>(row, kc) * 8;
         }
     } else {  // B stored [kk][n], tile BK x BN
@@ -333,7 +332,6 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &g, bf16_t *lds, int64_
             b_lds[q] = row * T::B_STRIDE + nc * 8;
         }
     }
-    const int kk_len = (int)(kk_end - kk_begin);  // contraction elements of this slice (may be <= 0)
 
     // D register sets hold the tiles in flight: tile t + D is requested while tile t is computed.
     u32x4_t ra[D][T::A_CHUNKS], rb[D][T::B_CHUNKS];
@@ -343,13 +341,13 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &g, bf16_t *lds, int64_
     // rotation spreads concurrently running work-groups over the channels.  The eight tiles of one
     // band column (same B column block, neighbouring A row blocks) share a starting tile so that
     // their common operand is fetched once into L2.
-    const int stagger = num_tiles > 0 ? (int)((tile / 8) % num_tiles) : 0;
+    const int stagger = (int)((tile / 8) % num_tiles);
     auto rotated = [&](int t) { return t + stagger - (t + stagger >= num_tiles ? num_tiles : 0); };
 
     __amdgpu_buffer_rsrc_t rsrc_a_fixed, rsrc_b_fixed;  // K-contiguous operands
     if constexpr (AMODE == A_KCONTIG) rsrc_a_fixed = rows_rsrc(g.A + m0 * g.lda, g.lda, min((int64_t)BM, g.M - m0));
     if constexpr (BMODE == B_KCONTIG) rsrc_b_fixed = rows_rsrc(g.B + n0 * g.ldb, g.ldb, min((int64_t)BN, g.N - n0));
-    auto issue = [&](int set, int t_seq) {  // request the t_seq-th tile of this slice into register set `set`
+    auto issue = [&](int set, int t_seq) {  // request the t_seq-th tile into register set `set`
         const int t = t_seq < num_tiles ? rotated(t_seq) : t_seq;  // past the end: stays out of range, reads zeros
         const int kk_tile = t * BK;
         if constexpr (AMODE == A_KCONTIG) {
@@ -359,7 +357,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &g, bf16_t *lds, int64_
                 ra[set][q] = __builtin_amdgcn_raw_buffer_load_b128(rsrc_a_fixed, ok ? a_off[q] + (uint32_t)kk_tile * 2 : OOB, 0, 0);
             }
         } else if constexpr (AMODE == A_MCONTIG) {
-            const __amdgpu_buffer_rsrc_t rsrc = rows_rsrc(g.A + (kk_begin + kk_tile) * g.lda, g.lda, min(BK, kk_len - kk_tile));
+            const __amdgpu_buffer_rsrc_t rsrc = rows_rsrc(g.A + (int64_t)kk_tile * g.lda, g.lda, min(BK, kk_len - kk_tile));
 #pragma unroll
             for (int q = 0; q < T::A_CHUNKS; ++q)
                 ra[set][q] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, a_ok[q] ? a_off[q] : OOB, 0, 0);
@@ -371,14 +369,14 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &g, bf16_t *lds, int64_
                 rb[set][q] = __builtin_amdgcn_raw_buffer_load_b128(rsrc_b_fixed, ok ? b_off[q] + (uint32_t)kk_tile * 2 : OOB, 0, 0);
             }
         } else {
-            const __amdgpu_buffer_rsrc_t rsrc = rows_rsrc(g.B + (kk_begin + kk_tile) * g.ldb, g.ldb, min(BK, kk_len - kk_tile));
+            const __amdgpu_buffer_rsrc_t rsrc = rows_rsrc(g.B + (int64_t)kk_tile * g.ldb, g.ldb, min(BK, kk_len - kk_tile));
 #pragma unroll
             for (int q = 0; q < T::B_CHUNKS; ++q)
                 rb[set][q] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, b_ok[q] ? b_off[q] : OOB, 0, 0);
         }
     };
 
-    // Writes the t_seq-th tile of the slice (held in register set `set`) into LDS stage `stage`.
+    // Writes the t_seq-th tile (held in register set `set`) into LDS stage `stage`.
     auto store_lds = [&](int set, int stage, int t_seq) {
         bf16_t *As = lds + stage * T::STAGE_ELEMS;
         bf16_t *Bs = As + T::A_ELEMS;
@@ -556,7 +554,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &g, bf16_t *lds, int64_
         static_assert(T::THREADS / 64 * kStripBytes <= T::LDS_BYTES, "staging area fits in LDS");
         char *stage = reinterpret_cast<char *>(lds) + wave * kStripBytes;
         write_tile<true, AMODE == A_KCONTIG && BMODE == B_KCONTIG, AMODE == A_MCONTIG, T::TM, T::TN, WAVES_K>(g, acc, stage, m0, n0, wm, wn,
-                                                                                                           kg, lane, slice);
+                                                                                                           kg, lane);
     }
 }
 
@@ -934,7 +932,7 @@ __device__ __forceinline__ void gemm_tile_dma(const GemmArgs &g, bf16_t *lds, in
     }
     __syncthreads();
     write_tile<true, BMODE == B_KCONTIG, false, T::TM, T::TN, 1>(g, acc, reinterpret_cast<char *>(lds) + wave * kStripBytes, m0, n0, wm, wn, 0,
-                                                                lane, 0);
+                                                                lane);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1131,7 +1129,7 @@ struct PlainOfPass {
         if constexpr (DMA)
             gemm_tile_dma<BMODE>(g, lds, block, blocks);
         else
-            gemm_tile<S, A_KCONTIG, BMODE, OUT_BF16, D>(g, lds, block, blocks, 0);
+            gemm_tile<S, A_KCONTIG, BMODE, OUT_BF16, D>(g, lds, block, blocks);
     }
 };
 
@@ -1145,7 +1143,7 @@ template <typename S, int AMODE, int BMODE, int OUT, int D>
 __global__ void __launch_bounds__(S::THREADS) gemm_mfma_kernel(GemmArgs g) {
     typedef Tile<S::BM, S::BN, S::BK, S::WM, S::WN, S::WK, AMODE, BMODE, OUT> T;
     __shared__ __attribute__((aligned(16))) bf16_t lds[T::STAGES * T::STAGE_ELEMS];
-    gemm_tile<S, AMODE, BMODE, OUT, D>(g, lds, blockIdx.x, gridDim.x, blockIdx.z);
+    gemm_tile<S, AMODE, BMODE, OUT, D>(g, lds, blockIdx.x, gridDim.x);
 }
 
 // Two independent products in one launch: `blocks_a` work-groups are the tiles of a plain product
@@ -1195,7 +1193,7 @@ __global__ void __launch_bounds__(S::THREADS) dw_colsum_kernel(GemmArgs g, Colsu
     constexpr int ELEMS = T::STAGES * T::STAGE_ELEMS, MIN_ELEMS = kColsumLdsFloats * 2;
     __shared__ __attribute__((aligned(16))) bf16_t lds[ELEMS > MIN_ELEMS ? ELEMS : MIN_ELEMS];
     if ((int)blockIdx.x < blocks_a)
-        gemm_tile<S, A_MCONTIG, B_NCONTIG, OUT_BF16, D>(g, lds, blockIdx.x, blocks_a, 0);
+        gemm_tile<S, A_MCONTIG, B_NCONTIG, OUT_BF16, D>(g, lds, blockIdx.x, blocks_a);
     else
         colsum_body<bf16_t>(c, reinterpret_cast<float *>(lds), (int64_t)blockIdx.x - blocks_a, (int64_t)gridDim.x - blocks_a);
 }
@@ -1208,7 +1206,7 @@ __global__ void __launch_bounds__(S::THREADS) xty_norms_kernel(GemmArgs g, RowNo
     typedef Tile<S::BM, S::BN, S::BK, S::WM, S::WN, S::WK, A_MCONTIG, B_NCONTIG, OUT_SUMSQ> T;
     __shared__ __attribute__((aligned(16))) bf16_t lds[T::STAGES * T::STAGE_ELEMS];
     if ((int)blockIdx.x < tiles)
-        gemm_tile<S, A_MCONTIG, B_NCONTIG, OUT_SUMSQ, D>(g, lds, blockIdx.x, tiles, 0);
+        gemm_tile<S, A_MCONTIG, B_NCONTIG, OUT_SUMSQ, D>(g, lds, blockIdx.x, tiles);
     else
         row_norms_body<bf16_t>(r, reinterpret_cast<double *>(lds), (int64_t)blockIdx.x - tiles, (int64_t)gridDim.x - tiles);
 }
