@@ -387,6 +387,7 @@ PyMethodDef methods[] = {RMM_METHOD(forward), RMM_METHOD(backward), RMM_METHOD(s
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_rmm_host", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
 
 PyTypeObject node_type;
+// (torch's own table of these, THP_FUNCTION_DEFAULT_METHODS, names a function that its headers do not declare)
 PyMethodDef node_methods[] = {{"_register_hook_dict", THPCppFunction_register_hook_dict, METH_O, nullptr},
                               {"register_hook", THPCppFunction_register_hook, METH_O, nullptr},
                               {"register_prehook", THPCppFunction_register_prehook, METH_O, nullptr},
