@@ -11,8 +11,11 @@ executes, the roofline of the slowest stage (timed with HIP events inside the
 timed region), and the fp64 oracle timed on the host cores as a plain baseline.
 """
 import argparse
+import glob
+import hashlib
 import json
 import os
+import re
 import sys
 import time
 
@@ -20,7 +23,7 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 PEAK_BF16_TFLOPS = 2500.0     # MI355X dense bf16 MFMA
-PEAK_F32_TFLOPS = 157.3       # MI355X fp32 vector
+PEAK_F32_TFLOPS = PEAK_BF16_TFLOPS / 8   # the fp32 path: eight bf16 MFMAs for a product of two fp32 operands (three planes each)
 PEAK_HBM_GBS = 8000.0
 CLOCK_WARMUP_S = 0.05          # untimed steps before the warm-up steps (GPU back from idle clocks)
 
@@ -34,9 +37,9 @@ KERNEL_STAGE_ID = {"fwd_Y": 0, "fwd_Xproj": 6, "bwd_dX": 2, "bwd_G": 7, "bwd_dW"
 # separate-launch path (same kernels, one after the other).
 PAIR_STAGE_ID = {"fwd_pair": 8, "bwd_pair": 9}
 PAIR_PARTS = {"fwd_pair": ("fwd_Y", "fwd_Xproj"), "bwd_pair": ("bwd_dX", "bwd_G")}
-KERNEL_NAME = {"fwd_Y": "gemm_mfma_kernel (X, W^T operands)", "fwd_Xproj": "sketch product kernel on X",
-               "bwd_dX": "gemm_mfma_kernel (dY, W operands)", "bwd_G": "sketch product kernel on dY",
-               "bwd_dW": "gemm_mfma_kernel (G^T, X_proj operands)",
+KERNEL_NAME = {"fwd_Y": "gemm_dma_kernel or gemm_mfma_kernel, by size (X, W^T operands)", "fwd_Xproj": "sketch product kernel on X",
+               "bwd_dX": "gemm_dma_kernel or gemm_mfma_kernel, by size (dY, W operands)", "bwd_G": "sketch product kernel on dY",
+               "bwd_dW": "gemm_mfma_kernel or few_tile_kernel, by size (G^T, X_proj operands)",
                "fwd_pair": "gemm_pair_kernel (Y = X W^T with the sketch product of X, one launch)",
                "bwd_pair": "gemm_pair_kernel (dX = dY W with the sketch product of dY, one launch)"}
 
@@ -62,22 +65,31 @@ def with_pairs(per_stage, shared):
     return out
 
 
-def read_traffic(workload, stage, kernels_version):
+def kernels_digest():
+    """Digest of the kernel sources without comments and layout: what a counter figure was measured on."""
+    h = hashlib.sha256()
+    for path in sorted(glob.glob(os.path.join(ROOT, "paper_2201_13195_amd", "csrc", "*.h*"))):
+        with open(path) as f:
+            h.update(os.path.basename(path).encode() + b"\n" + "".join(re.sub(r"//[^\n]*", "", f.read()).split()).encode())
+    return h.hexdigest()[:16]
+
+
+def read_traffic(workload, stage, digest):
     """HBM bytes per launch of `stage` from the committed counter summary (line
     `traffic_bytes_per_launch <workload> <stage> <bytes>` in profiles/hbm_traffic.txt), or None when
-    there is none or when it was measured on another version of the kernels (line
-    `kernels_version <rmm_version()>`): a stale figure is worse than none."""
+    there is none or when it was measured on other kernels than these (line
+    `kernels_digest <kernels_digest()>`): a stale figure is worse than none."""
     path = os.path.join(ROOT, "profiles", "hbm_traffic.txt")
     if not os.path.exists(path):
         return None
-    found, version = None, None
+    found, measured_on = None, None
     for line in open(path):
         t = line.split()
-        if len(t) == 2 and t[0] == "kernels_version":
-            version = int(t[1])
+        if len(t) == 2 and t[0] == "kernels_digest":
+            measured_on = t[1]
         if len(t) == 4 and t[0] == "traffic_bytes_per_launch" and t[1] == workload and t[2] == stage:
             found = float(t[3])
-    return found if version == kernels_version else None
+    return found if measured_on == digest else None
 
 
 def cpu_baseline(cfg, kind, budget_s=10.0):
@@ -112,7 +124,7 @@ def cpu_baseline(cfg, kind, budget_s=10.0):
             "ms_per_step": dt / reps * 1e3}
 
 
-def sketch_roofline(torch, rmm, binding, dev, kind, kind_name, version, n=16384, d=4096, k=32, reps=30):
+def sketch_roofline(torch, rmm, binding, dev, kind, kind_name, digest, n=16384, d=4096, k=32, reps=30):
     """rmm_sketch (S^T A) at small k on a RoBERTa-large sized operand: bound by one read of A.
     Three operands are rotated (402 MB) so that no call finds its input in the last-level cache.
     `achieved` is that of the streaming product kernel alone (events recorded by the library
@@ -146,13 +158,13 @@ def sketch_roofline(torch, rmm, binding, dev, kind, kind_name, version, n=16384,
     return {"workload": "rmm_sketch N=%d d=%d k=%d (%s), bf16" % (n, d, k, kind_name), "bound": "hbm",
             "kernel": "sketch_smallk_kernel", "achieved": nbytes / (kms * 1e-3) / 1e9, "peak": PEAK_HBM_GBS,
             "unit": "GB/s", "frac": nbytes / (kms * 1e-3) / 1e9 / PEAK_HBM_GBS,
-            "traffic": read_traffic("sketch_n%d_d%d_k%d" % (n, d, k), "product", version), "avg_launch_ms": kms,
+            "traffic": read_traffic("sketch_n%d_d%d_k%d" % (n, d, k), "product", digest), "avg_launch_ms": kms,
             "avg_call_ms": cms, "algorithmic_bytes_per_launch": nbytes}
 
 
 def variance_monitor(torch, rmm, X, dY, k, kind, reps=30):
-    """rmm_variance_stats (Section 2.3 monitors) on the workload's X and dY: one HBM pass for the
-    row norms, the X^T dY product with a squared-norm epilogue, a one-wave finalize."""
+    """rmm_variance_stats (Section 2.3 monitors) on the workload's X and dY: one launch for the
+    row norms and the X^T dY product with a squared-norm epilogue, one for the closing sums."""
     n, d_in = X.shape
     d_out = dY.shape[1]
     out = torch.empty((8,), dtype=torch.float64, device=X.device)
@@ -489,7 +501,7 @@ def main():
     kind = rmm.GAUSSIAN if args.kind == "gaussian" else rmm.RADEMACHER
     n, d_in, d_out, k = cfg["n"], cfg["d_in"], cfg["d_out"], cfg["k"]
     esize = 2 if cfg["dtype"] == "bf16" else 4
-    version = rmm.rmm_version()
+    version, digest = rmm.rmm_version(), kernels_digest()
 
     run = LayerRun(torch, rmm, binding, synth, dev, cfg, kind, args.sets)
     # The inputs were made on the host, which takes seconds: the GPU has been idle and sits at its idle
@@ -556,11 +568,12 @@ def main():
                    "flops_per_step": total_flops,
                    "saved_activation_bytes": saved, "plain_layer_saved_bytes": n * d_in * esize,
                    "saved_fraction": saved / (n * d_in * esize), "kernels_version": version,
+                   "kernels_digest": digest,
                    "clock_warmup_ms": CLOCK_WARMUP_S * 1e3},
-        "roofline": {"bound": "mfma" if cfg["dtype"] == "bf16" else "alu",
-                     "kernel": KERNEL_NAME[dominant] if cfg["dtype"] == "bf16" else "gemm_plain_kernel (%s)" % dominant,
+        "roofline": {"bound": "mfma",
+                     "kernel": KERNEL_NAME[dominant] if cfg["dtype"] == "bf16" else "plain_pass_kernel / plain_tn_kernel (%s)" % dominant,
                      "stage": dominant, "achieved": achieved, "peak": peak, "unit": "TFLOP/s",
-                     "frac": achieved / peak, "traffic": read_traffic(args.workload, dominant, version),
+                     "frac": achieved / peak, "traffic": read_traffic(args.workload, dominant, digest),
                      "avg_launch_ms": dom_ms, "launches_timed": len(evs), "empty_event_pair_ms": empty_pair_ms,
                      "flops_per_launch": fl[dominant],
                      "algorithmic_bytes_per_launch": by[dominant]},
@@ -601,16 +614,16 @@ def main():
                                           ms_per_step),
             "large_shape": sors_report(LayerRun(torch, rmm, binding, synth, dev, big, rmm.SORS, 2), big, 20,
                                        out["large_shape"]["ms_per_step"])}
-        # the fp32 data path (plain FMA kernels, full-precision generator) on the headline shape
+        # the fp32 data path (operands split into three bf16 planes, full-precision generator) on the headline shape
         f32 = dict(cfg, dtype="f32")
         run32 = LayerRun(torch, rmm, binding, synth, dev, f32, kind, 2)
         ms32 = run32.step_ms(5)
         out["fp32_path"] = {"workload": "N=%d tokens, d_in=%d, d_out=%d, k=%d (%s sketch), f32" % (n, d_in, d_out, k, args.kind),
-                            "ms_per_step": ms32, "tflops": total_flops / (ms32 * 1e-3) / 1e12, "bound": "alu",
+                            "ms_per_step": ms32, "tflops": total_flops / (ms32 * 1e-3) / 1e12, "bound": "mfma",
                             "peak": PEAK_F32_TFLOPS, "frac": total_flops / (ms32 * 1e-3) / 1e12 / PEAK_F32_TFLOPS, "steps": 5}
         del run32
     if not args.no_sketch_roofline:
-        out["sketch_hbm_roofline"] = sketch_roofline(torch, rmm, binding, dev, kind, args.kind, version)
+        out["sketch_hbm_roofline"] = sketch_roofline(torch, rmm, binding, dev, kind, args.kind, digest)
     if not args.no_variance_monitor and bf16:
         out["variance_monitor"] = variance_monitor(torch, rmm, run.sets[0]["X"], run.sets[0]["dY"], k, kind)
     if not args.no_measured_peaks:
