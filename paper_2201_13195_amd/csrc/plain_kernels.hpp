@@ -8,8 +8,10 @@
 // nearest, subtract, round, subtract; the last rest fits), so an fp32 product runs on the bf16 matrix
 // pipes: the operand tiles are split on their way into LDS (three planes) and a 32x32x16 block is the
 // sum of eight bf16 MFMAs, every pair of planes but the last with the last, whose share is below 2^-32
-// of a product.  Each plane product is exact in fp32, so what rounds is the fp32 accumulation, as with
-// an fp32 multiply-add.  Operands that are bf16 already, and the +-1 entries of the Rademacher and
+// of a product.  Each plane product is exact in fp32, so what rounds is the fp32 accumulation; with the
+// products of the two first planes summed apart from the smaller ones its error is below that of a chain of fp32
+// multiply-adds at every size looked at (a third of it at 4096 x 768 -> 3072 with normal entries; in one sum it was
+// 12 % above it there with entries over 40 binades).  Operands that are bf16 already, and the +-1 entries of the Rademacher and
 // SORS sketches, are one plane.
 //
 // The whole range of fp32 is served.  bf16 has fp32's exponents, so below 2^-110 the lower planes would lose
@@ -301,13 +303,19 @@ __device__ __forceinline__ void plain_tile(const PlainArgs &g, bf16_t *lds, int6
     const int64_t band_rows = min((int64_t)8, tiles_m - band * 8);
     const int64_t m0 = (band * 8 + in_band % band_rows) * BM, n0 = (in_band / band_rows) * BN;
 
-    f32x16_t acc[TM][TN];
+    // With planes, the products of the two first planes are summed apart from the others, which are 2^-8 of them:
+    // the large sum is then rounded once per 16 contraction elements instead of eight times.
+    constexpr bool PLANES = PA + PB > 2;
+    f32x16_t acc[TM][TN], low[PLANES ? TM : 1][PLANES ? TN : 1];
 #pragma unroll
     for (int a = 0; a < TM; ++a)
 #pragma unroll
         for (int b = 0; b < TN; ++b)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) acc[a][b][v] = 0.0f;
+            for (int v = 0; v < 16; ++v) {
+                acc[a][b][v] = 0.0f;
+                if constexpr (PLANES) low[a][b][v] = 0.0f;
+            }
 
     constexpr bool GEN = AMODE == PA_GAUSS || AMODE == PA_SIGN;
     typedef PlainLoader<T, BN, BK, BMODE == PB_K, MODE, L::SB, L::B_PLANE> LoadB;
@@ -388,8 +396,10 @@ __device__ __forceinline__ void plain_tile(const PlainArgs &g, bf16_t *lds, int6
 #pragma unroll
                 for (int u = 0; u < TM; ++u)
 #pragma unroll
-                    for (int w = 0; w < TN; ++w)
-                        acc[u][w] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.a[s][u], f.b[r][w], acc[u][w], 0, 0, 0);
+                    for (int w = 0; w < TN; ++w) {
+                        f32x16_t &sum = order > 0 ? low[PLANES ? u : 0][PLANES ? w : 0] : acc[u][w];
+                        sum = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.a[s][u], f.b[r][w], sum, 0, 0, 0);
+                    }
             }
     };
 
@@ -419,12 +429,18 @@ __device__ __forceinline__ void plain_tile(const PlainArgs &g, bf16_t *lds, int6
         }
     }
 
+    if constexpr (PLANES) {
+#pragma unroll
+        for (int u = 0; u < TM; ++u)
+#pragma unroll
+            for (int w = 0; w < TN; ++w) acc[u][w] += low[u][w];
+    }
+
     // Register v of lane l is C(8*(v/4) + 4*(l/32) + v%4, l % 32) of a 32x32 tile: a store instruction
     // writes two rows of 32 consecutive elements, whatever the alignment of the rows.
     Tout *C = reinterpret_cast<Tout *>(g.C);
     const T *bias = reinterpret_cast<const T *>(g.bias);
     const int half = lane >> 5;
-    constexpr bool SPLIT = PA + PB > 2;  // planes: sums that are not finite are made again
     const float alpha = g.alpha * (PA == 3 && !GEN ? kSplitDown : 1.0f) * (PB == 3 ? kSplitDown : 1.0f);  // (exact)
     auto write = [&](int64_t r, int64_t c, float x, float bv) {
         if (g.bias != nullptr) x += bv;
@@ -434,7 +450,7 @@ __device__ __forceinline__ void plain_tile(const PlainArgs &g, bf16_t *lds, int6
     uint32_t open = 0;  // bit e: this lane's output number e is still to be made
     auto put_out = [&](int e, int64_t r, int64_t c, float x, float bv) {
         if (r >= g.M || c >= g.N) return;
-        if (SPLIT && !__builtin_isfinite(x))
+        if (PLANES && !__builtin_isfinite(x))  // made again below
             open |= 1u << e;
         else
             write(r, c, alpha * x, bv);
@@ -473,7 +489,7 @@ __device__ __forceinline__ void plain_tile(const PlainArgs &g, bf16_t *lds, int6
                     put_out((w * TM + u) * 16 + v, m0 + wm * (BM / S::WM) + u * 32 + row_of(v), c, acc[u][w][v], bv);
         }
     }
-    if constexpr (SPLIT) {
+    if constexpr (PLANES) {
         while (open != 0) {
             const int e = __ffs(open) - 1, v = S::WK > 1 ? kg * OWN + e : e % 16, u = S::WK > 1 ? 0 : e / 16 % TM,
                       w = S::WK > 1 ? 0 : e / 16 / TM;

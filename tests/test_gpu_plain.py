@@ -64,3 +64,26 @@ def test_fp32_products_are_as_exact_as_fp32_multiply_adds(n, d_in, d_out):
     err = np.abs(synth.to_f64(Y) - X64 @ W64.T) / (np.abs(X64) @ np.abs(W64).T)
     print("K=%d: largest error / sum of magnitudes = %.2f * 2^-24" % (d_in, err.max() * 2.0 ** 24), flush=True)
     assert err.max() <= 2.0 ** -24 * (2.0 + math.sqrt(d_in))
+
+
+@pytest.mark.parametrize("spread", [0, 20])
+@pytest.mark.parametrize("n,d_in,d_out", [(256, 128, 256), (1024, 768, 1024), (4096, 768, 3072)])
+def test_fp32_products_are_no_further_off_than_a_chain_of_multiply_adds(n, d_in, d_out, spread):
+    """Every tile size of the plain products: error against fp64, relative to the sum of the terms' magnitudes,
+    beside that of fp32 multiply-adds in order (64 rows), for entries of one size and over 40 binades."""
+    g = np.random.default_rng(6)
+
+    def draw(*shape):
+        x = g.standard_normal(shape)
+        return (x * np.exp2(g.integers(-spread, spread + 1, shape)) if spread else x).astype(np.float32)
+    X, W = draw(n, d_in), draw(d_out, d_in)
+    Y, _ = rmm.rmm_forward(torch.from_numpy(X).to(DEV), torch.from_numpy(W).to(DEV), None, 1, 0, 1, 2, need_xproj=False)
+    rows = np.arange(64) * (n // 64)
+    X64, W64 = X[rows].astype(np.float64), W.astype(np.float64)
+    want, size = X64 @ W64.T, np.abs(X64) @ np.abs(W64.T)
+    chain = np.zeros((64, d_out))
+    for j in range(d_in):
+        chain = (chain + X64[:, j:j + 1] * W64[:, j]).astype(np.float32).astype(np.float64)
+    rms = [float(np.sqrt(np.mean(((a - want) / size) ** 2)) * 2.0 ** 24) for a in (synth.to_f64(Y)[rows], chain)]
+    print("%s spread %d: %.3f, chain %.3f (rms, 2^-24 of the sum of magnitudes)" % ((n, d_in, d_out), spread, *rms), flush=True)
+    assert rms[0] <= rms[1]
