@@ -8,9 +8,9 @@ namespace rmm {
 
 namespace {
 
-// Prefetch depth (register sets of tiles in flight).  The kernels run whole groups of `depth`
-// tiles, so a plain product takes the one of 4 and 3 that pads its contraction less; the
-// 256 x 256 kernel and the sketch kernels need their registers for wide wave tiles and use 3.
+// Prefetch depth of gemm_tile (register sets of tiles in flight).  It runs whole groups of `depth` tiles, so a
+// product takes the one of 4 and 3 that pads its contraction less; on 256 x 256 tiles (dW and X^T dY) the
+// registers go to wide wave tiles, and it is 3.
 int plain_depth(int64_t contraction, int bk) {
     const int64_t kt = (contraction + bk - 1) / bk;
     const int64_t pad4 = (kt + 3) / 4 * 4 - kt, pad3 = (kt + 2) / 3 * 3 - kt;
@@ -37,7 +37,7 @@ int64_t tiles_of(int64_t m, int64_t n, int64_t bm, int64_t bn) { return ((m + bm
 //   256 x 256 (8 waves, one work-group per compute unit) once there are at least 160 such tiles:
 //     half the operand traffic per flop of the 128 x 128 tile, which needs more bytes per clock
 //     from L2 than it delivers at full MFMA rate;
-//   64 x 64, or 32 x 32 while those give at most one work-group per compute unit, with the contraction
+//   64 x 64, or 32 x 32 while those give at most two work-groups per compute unit, with the contraction
 //     split over eight waves (few_tile) when there are fewer than 65 tiles of 128 x 128 (a quarter of
 //     the compute units);
 //   128 x 128 x 64 with two wave groups splitting the contraction when there are at most 256
@@ -111,7 +111,8 @@ struct SketchPlan {
 // one slice the kernel writes fp32 partial results to workspace and reduce_partials_kernel sums them in slice
 // order.  104 tiles would get two slices each, and 48 compute units nothing to do.  So a tile may also get a last,
 // shorter slice; the work-groups left over take those of per_tail tiles each, as long in all as a long slice
-// (16384 x 4096, k = 1638: 111 steps on 243 compute units instead of 128 on 208, 267 -> 252 us).
+// (16384 x 4096, k = 1638: 111 steps on 243 compute units instead of 128 on 208, with the sum of the slices 264 ->
+// 246 us, Rademacher 220 -> 205; k = 819 140 -> 138 and 120 -> 115).
 // `overhead` is what a tile costs besides its steps, in steps; a tile gets at most `most` slices.
 void slice_sketch(SketchPlan &p, int64_t n, int target_wgs, double overhead, int64_t most) {
     const int64_t units = (n + 63) / 64;
@@ -132,13 +133,16 @@ void slice_sketch(SketchPlan &p, int64_t n, int target_wgs, double overhead, int
 }
 
 // The tile is the one of the menu whose time comes out lowest: rounds of 256 work-groups, each as long as
-// its slice's 64-token steps, plus the partial results.  The times of a step on a full chip are a least-squares
-// fit over sixteen shapes from 2000 x 400, k = 100 to 16384 x 4096, k = 1638 (within 6.5 % rms), moved where the
-// choice came out better; partial results cost 0.2 us per MB written and read (they mostly stay in the last-level
-// cache).  What that weighs: padding of k and d, entries generated once per 512, 384 or 256 columns, operand
-// columns staged once per 128 or 64 rows, and filling the chip when tokens are few.  ((16384 x 4096, k = 410)
-// 64 x 512: 83 us, 128 x 512: 88; (32000 x 512, k = 640) 49, 128 x 256: 41; (10000 x 3000, k = 1000) 128 x 384:
-// 84, 128 x 512: 92; 4096 x 3072, k = 3686 unsliced on 128 x 384: 110, 128 x 512: 125.)
+// its slice's 64-token steps, plus the partial results.  The times of a step on a full chip come from a fit over
+// measured shapes, adjusted by hand where another choice was faster; partial results cost 0.2 us per MB written and
+// read (they mostly stay in the last-level cache).  What that weighs: padding of k and d, entries generated once per
+// 512, 384 or 256 columns, operand columns staged once per 128 or 64 rows, and filling the chip when tokens are few.
+// It ranks the tiles and does not predict: what every tile costs alike (launch, first step, 8 us and more at small
+// sizes) is left out.  All six tiles timed at sixteen shapes from 2000 x 400, k = 100 to 16384 x 4096, k = 1638
+// (profiles/sketch_products.txt): the one taken is 1.7 % slower than the fastest on average with the Gaussian kind,
+// 17 % at most (32000 x 512, k = 640: 49 us, 128 x 256 42), 0.6 and 3.9 % with Rademacher.  ((16384 x 4096, k = 410)
+// 64 x 512: 83 us, 128 x 512: 126; (10000 x 3000, k = 1000) 128 x 384: 85, 64 x 256: 114; 4096 x 3072, k = 3686
+// unsliced on 128 x 384: 107, 128 x 512: 119.)
 // `limited`: the caller may be rmm_sketch_static.
 SketchPlan plan_sketch(int64_t n, int64_t d, int64_t k, int kind, bool limited, int target_wgs = 256) {
     struct Entry {

@@ -768,11 +768,12 @@ __global__ void __launch_bounds__(kFewThreads) few_tile_kernel(GemmArgs g) {
 // when it ends.  LDS is laid out by the load, so what keeps bank conflicts away is which chunk a lane asks
 // for: rows of 64 elements hold chunk c at c ^ (row / 2) % 8 (kchunk_pos), rows of 256 columns hold
 // chunk c at c ^ 4 * (row % 4), so that the four rows of a transposing read fall on different 64 bytes.
-// Bound by the MFMAs, which are busy for two thirds of a work-group's cycles; what is left is the first load,
-// the write of the tile and a chip that lowers its clock.  Against loads through registers into padded tiles
-// of 32 contraction elements (us): Y 16384 x 1024 -> 4096 167 -> 152 (0.91 PFLOP/s), 16384 x 4096 -> 1024
-// 127 -> 114 (1.2), 8192 x 2048 -> 2048 67 -> 60, dX 16384 x 4096 -> 1024 118 -> 112.  Four waves of
-// 128 x 128 outputs read a third less LDS but hide less: 172 and 126.
+// Of a dispatch's MFMA cycles 55 % are busy (dX 16384 x 4096 -> 1024, one tile per compute unit) and 45 % (Y 1024 ->
+// 4096, four); the rest is the first load, the write of the tile and waves that wait
+// (profiles/mfma_valu_lds_counters.txt).  Against loads through registers into padded tiles of 32 contraction
+// elements (us): Y 16384 x 1024 -> 4096 167 -> 152 (0.91 PFLOP/s), 16384 x 4096 -> 1024 127 -> 114 (1.2), 8192 x
+// 2048 -> 2048 67 -> 60, dX 16384 x 4096 -> 1024 118 -> 112.  Four waves of 128 x 128 outputs read a third less LDS
+// but hide less: 172 and 126.
 struct DmaTile {
     static constexpr int BM = 256, BN = 256, BK = 64, WM = 2, WN = 4, THREADS = 64 * WM * WN;
     static constexpr int TM = BM / WM / 32, TN = BN / WN / 32;
@@ -937,13 +938,14 @@ __device__ __forceinline__ void gemm_tile_dma(const GemmArgs &g, bf16_t *lds, in
 
 // ---------------------------------------------------------------------------------------------
 // Sketch products: S^T (generated by the work-group into LDS) times A [token][column], in the pipeline of
-// gemm_tile_dma: steps of 64 tokens, two stages, one barrier, A loaded straight into LDS.  What bounds them is
-// how far MFMAs and generator share a step: with 128 x 512 tiles at 16384 x 4096, k = 1638 the MFMAs of a step
-// alone take 141 us per launch, without the generator it is 198, complete 253 (0.87 PFLOP/s; 270 with A through
-// registers into three stages of 32 tokens).  The generator's instructions are therefore laid out between the
-// MFMAs of the first quarters.  Generating in one half of the waves while the other half multiplies was slower:
-// 264 with steps of 64 tokens, 277 with 32.  So were 32-token steps in a ring of four stages (256; more barriers)
-// and wave tiles of 64 x 128 (A fragments are cheap, B fragments cost two transposing reads: + 5 %).
+// gemm_tile_dma: steps of 64 tokens, two stages, one barrier, A loaded straight into LDS (7 % faster than through
+// registers into three stages of 32 tokens).  What bounds them is how far MFMAs and generator share a step: with
+// 128 x 512 tiles at 16384 x 4096, k = 1638 the MFMAs of a step alone take 161 us per launch, without the generator
+// it is 217, complete 272 (Rademacher 138, 173, 215; one run, profiles/sketch_products.txt).  The generator's
+// instructions are therefore laid out between the MFMAs of the first quarters.  Generating in one half of the waves
+// while the other half multiplies was 4 % slower with steps of 64 tokens, 9 % with 32; 32-token steps in a ring of
+// four stages 1 % (more barriers); wave tiles of 64 x 128 5 % (A fragments are cheap, B fragments cost two
+// transposing reads).
 template <typename S>
 struct SketchTile {
     static constexpr int BM = S::BM, BN = S::BN, BK = S::BK, WM = S::WM, WN = S::WN, THREADS = S::THREADS;

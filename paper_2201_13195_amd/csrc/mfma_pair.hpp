@@ -10,7 +10,7 @@ namespace rmm {
 enum { GEMM_LARGE = 0, GEMM_SPLIT = 1, GEMM_MID = 2, GEMM_FEW = 3 };
 enum { SK_NARROW = 0, SK_WIDE = 1, SK_WIDE64 = 2, SK_MID64 = 3, SK_MID = 4, SK_NARROW64 = 5 };
 
-// The plain product of a paired launch: 256 x 256 tiles (depth 3) or 128 x 128 x 64 tiles with two wave
+// The plain product of a paired launch: 256 x 256 tiles (gemm_tile_dma, no depth) or 128 x 128 x 64 tiles with two wave
 // groups (depth 3 or 4, whichever pads the contraction less), and its number of tiles.
 struct PairPlain {
     bool large;
