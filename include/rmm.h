@@ -33,7 +33,9 @@
  *     nearest even from fp32 accumulators); bias / dbias are bfloat16 too and,
  *     like every other pointer, 16-byte aligned (a misaligned one is
  *     RMM_ERR_INVALID_ARG).
- *     dtype RMM_DTYPE_F32: everything is fp32.
+ *     dtype RMM_DTYPE_F32: everything is fp32, over its whole range: infinities, NaN and
+ *     numbers below the normal ones count as in fp32 multiply-adds.  (Operands from 2^104 or
+ *     sums from 2^79 up are served by a slow path, output by output.)
  *
  * The sketch.  state = (seed, offset).  Entry (i, j) of S (token i, sketch
  * column j) is P[i][j] / sqrt(k), with P a pure function of (state, i, j) built
