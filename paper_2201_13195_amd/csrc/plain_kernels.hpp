@@ -19,8 +19,8 @@
 // sums by the inverse.  Operands from about 2^104 up, infinities and sums that leave fp32 with the factors on them
 // then end as an infinity or NaN in the accumulator, NaN operands as NaN: the outputs where that happened are
 // computed again with fp32 multiply-adds, element by element (plain_dot), and get what those give.  That is slow
-// where it is many: 4096 x 768 -> 3072 forward, 0.21 ms; all of X NaN 0.22 (a NaN ends its sum at once), one row of X
-// at the lowest fp32 value 18 (every sketch sum meets it), all of X around 1e34 28 ms.
+// where it is many: 4096 x 768 -> 3072 forward, 0.21 ms; all of X NaN 0.23 (a NaN ends its sum at once), one row of X
+// at the lowest fp32 value 3.6 (every sketch sum meets it), all of X around 1e34 21 ms.
 //
 // Why not v_mfma_f32_32x32x2_f32: it runs on the vector units' fp32 multipliers (measured on this
 // chip: 72 cycles plus 4 for every vector instruction beside it), 576 cycles for the block that takes
@@ -264,21 +264,32 @@ __device__ __forceinline__ bf16x8_t sign_eight(int kind, const SketchState &st, 
     return out.v;
 }
 
-// One output by fp32 multiply-adds, unscaled; ends early where nothing can change the result any more.
+// One output by fp32 multiply-adds, unscaled; ends early where nothing can change the result any more.  A
+// generated operand is made eight entries at a time (one generator call, eight loads of B in flight).
 template <typename T, int AMODE, int BMODE>
 __device__ __forceinline__ float plain_dot(const PlainArgs &g, int64_t r, int64_t c) {
+    constexpr bool GEN = AMODE == PA_GAUSS || AMODE == PA_SIGN;
+    constexpr int STEP = GEN ? 8 : 1;
     const T *A = reinterpret_cast<const T *>(g.A), *B = reinterpret_cast<const T *>(g.B);
     float sum = 0.0f;
 #pragma unroll 1
-    for (int64_t kk = 0; kk < g.K && sum == sum; ++kk) {
-        float a;
-        if constexpr (AMODE == PA_K)
-            a = load_f32<T>(A + r * g.lda + kk);
-        else if constexpr (AMODE == PA_M)
-            a = load_f32<T>(A + kk * g.lda + r);
-        else
-            a = sketch_entry_precise(g.kind, g.st, kk, r);
-        sum = fmaf(a, load_f32<T>(BMODE == PB_K ? B + c * g.ldb + kk : B + kk * g.ldb + c), sum);
+    for (int64_t k0 = 0; k0 < g.K && sum == sum; k0 += STEP) {
+        float a[STEP];
+        if constexpr (AMODE == PA_GAUSS) {
+            gauss_eight_precise(g.st, (uint32_t)k0, (uint32_t)r, a);
+        } else if constexpr (AMODE == PA_SIGN) {
+            const bf16x8_t s = sign_eight(g.kind, g.st, (uint32_t)k0, (uint32_t)r);
+#pragma unroll
+            for (int u = 0; u < 8; ++u) a[u] = (float)s[u];
+        } else {
+            a[0] = load_f32<T>(AMODE == PA_K ? A + r * g.lda + k0 : A + k0 * g.lda + r);
+        }
+        float b[STEP];
+#pragma unroll
+        for (int u = 0; u < STEP; ++u)  // (entries beyond the contraction meet zeros)
+            b[u] = !GEN || k0 + u < g.K ? load_f32<T>(BMODE == PB_K ? B + c * g.ldb + k0 + u : B + (k0 + u) * g.ldb + c) : 0.0f;
+#pragma unroll
+        for (int u = 0; u < STEP; ++u) sum = fmaf(a[u], b[u], sum);
     }
     return sum;
 }
