@@ -135,6 +135,13 @@ int sketch_impl(int64_t n, int64_t d, int64_t k, int kind, SketchState st, const
     return from_hip(launch_forward_plain<T>((const T *)A, nullptr, nullptr, nullptr, (T *)out, n, d, d, k, kind, st, stream));
 }
 
+// Whether a pass on the bf16 kernels launches its plain product together with its sketch product.
+bool pass_is_paired(const rmm_layer_desc_t *d, int op) {
+    if (d->kind == RMM_SKETCH_SORS)
+        return op == RMM_OP_FORWARD ? sors_pair_available(d->n, d->d_in, d->d_out, d->k) : sors_pair_available(d->n, d->d_out, d->d_in, d->k);
+    return pass_pair_available(d->k);
+}
+
 template <typename T>
 int forward_impl(const rmm_layer_desc_t *d, SketchState st, const void *X, const void *W, const void *bias, void *Y,
                  void *X_proj, void *ws, hipStream_t stream, const StageEvents &ev) {
@@ -163,7 +170,7 @@ int forward_impl(const rmm_layer_desc_t *d, SketchState st, const void *X, const
         hipError_t e =
             mfma ? launch_linear_nt_bf16((const bf16_t *)X, (const bf16_t *)W, (const bf16_t *)bias, (bf16_t *)Y,
                                          d->n, d->d_in, d->d_out,
-                                         X_proj != nullptr && sliced_sketch(d) && pass_pair_available(d->k), stream)
+                                         X_proj != nullptr && pass_is_paired(d, RMM_OP_FORWARD), stream)
                  : launch_forward_plain<T>((const T *)X, (const T *)W, (const T *)bias, (T *)Y, nullptr, d->n, d->d_in,
                                            d->d_out, d->k, d->kind, st, stream);
         if (e != hipSuccess) return RMM_ERR_LAUNCH;
@@ -212,7 +219,7 @@ int backward_impl(const rmm_layer_desc_t *d, SketchState st, const void *dY, con
     if (!paired && dX != nullptr) {  // dX = dY W: B(kk, c) = W[kk][c]
         StageScope scope(ev, RMM_STAGE_BWD_DX, stream);
         e = mfma ? launch_linear_nn_bf16((const bf16_t *)dY, (const bf16_t *)W, (bf16_t *)dX, d->n, d->d_in, d->d_out,
-                                         sliced_sketch(d) && pass_pair_available(d->k), stream)
+                                         pass_is_paired(d, RMM_OP_BACKWARD), stream)
                  : launch_backward_plain<T>((const T *)dY, (const T *)W, (T *)dX, nullptr, nullptr, d->n, d->d_in,
                                             d->d_out, d->k, d->kind, st, false, stream);
         if (e != hipSuccess) return RMM_ERR_LAUNCH;
@@ -279,14 +286,7 @@ size_t rmm_workspace_bytes(const rmm_layer_desc_t *desc, int op) {
 int rmm_uses_paired_launch(const rmm_layer_desc_t *desc, int op) {
     if (!desc_ok(desc) || (op != RMM_OP_FORWARD && op != RMM_OP_BACKWARD)) return 0;
     if (!use_mfma(desc)) return 1;
-    if (desc->kind == RMM_SKETCH_SORS) {
-        if (op == RMM_OP_FORWARD) return sors_pair_available(desc->n, desc->d_in, desc->d_out, desc->k) ? 1 : 0;
-        if (op == RMM_OP_BACKWARD) return sors_pair_available(desc->n, desc->d_out, desc->d_in, desc->k) ? 1 : 0;
-        return 0;
-    }
-    if (op == RMM_OP_FORWARD) return pass_pair_available(desc->k) ? 1 : 0;
-    if (op == RMM_OP_BACKWARD) return pass_pair_available(desc->k) ? 1 : 0;
-    return 0;
+    return pass_is_paired(desc, op) ? 1 : 0;
 }
 
 int rmm_sketch_profiled(int64_t n, int64_t d, int64_t k, int dtype, int kind, rmm_rng_state_t state, const void *A,

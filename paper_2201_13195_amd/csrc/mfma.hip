@@ -8,78 +8,90 @@ namespace rmm {
 
 namespace {
 
-// Prefetch depth of gemm_tile (register sets of tiles in flight).  It runs whole groups of `depth` tiles, so a
-// product takes the one of 4 and 3 that pads its contraction less; on 256 x 256 tiles (dW and X^T dY) the
-// registers go to wide wave tiles, and it is 3.
-int plain_depth(int64_t contraction, int bk) {
-    const int64_t kt = (contraction + bk - 1) / bk;
-    const int64_t pad4 = (kt + 3) / 4 * 4 - kt, pad3 = (kt + 2) / 3 * 3 - kt;
-    return pad4 <= pad3 ? 4 : 3;
+int64_t tiles_of(int64_t m, int64_t n, int64_t bm, int64_t bn) { return ((m + bm - 1) / bm) * ((n + bn - 1) / bn); }
+
+template <typename S>
+int64_t tiles_in(int64_t m, int64_t n) { return tiles_of(m, n, S::BM, S::BN); }
+
+// Time of a product on a menu of tiles, to choose between them (us, fitted to products from 256 x 384 to 16384 x 4096
+// outputs and contractions from 51 to 4096): a launch, then rounds of 256 work-groups, each `fix` for the first loads and
+// the writing of the tile and `step` for every 64 contraction elements.  Of the small tiles two share a compute unit: a
+// full round of 512 takes 1.9 times the time of one of up to 256, one of 257 to 511 from 1.4 times on.
+struct TileTime {
+    int64_t bm, bn;
+    double fix, step;
+    bool shared;
+};
+double tile_us(const TileTime &t, int64_t m, int64_t n, int64_t kk) {
+    const int64_t tiles = tiles_of(m, n, t.bm, t.bn), rest = tiles % 512;
+    const double rounds = !t.shared ? (double)((tiles + 255) / 256)
+                                    : 1.9 * (double)(tiles / 512) + (rest == 0 ? 0.0 : rest <= 256 ? 1.0 : 1.4 + 0.5 * (double)(rest - 256) / 256.0);
+    return 2.5 + rounds * (t.fix + (double)((kk + 63) / 64) * t.step);
+}
+
+// Tile of a plain product with an m x n output and contraction kk.  32 x 32 tiles whose contraction is shared by eight
+// waves (few_tile) only while there are at most 512 of them.  256 x 256 tiles from 160 of them on whatever the model
+// says: they need half the bytes per flop of 128 x 128 tiles, which a full chip cannot bring into its LDS at MFMA rate.
+int gemm_cfg(int64_t m, int64_t n, int64_t kk) {
+    if (tiles_in<ShapeLarge>(m, n) >= 160) return GEMM_LARGE;
+    static const struct {
+        int cfg;
+        TileTime t;
+    } menu[] = {{GEMM_WIDE, {ShapeWide::BM, ShapeWide::BN, 3.0, 0.90, false}},
+                {GEMM_SPLIT, {ShapeSplit::BM, ShapeSplit::BN, 2.4, 0.47, false}},
+                {GEMM_MID, {ShapeMid::BM, ShapeMid::BN, 2.0, 0.50, false}},
+                {GEMM_FLAT, {ShapeFlat::BM, ShapeFlat::BN, 1.0, 0.42, true}},
+                {GEMM_SMALL, {ShapeSmall::BM, ShapeSmall::BN, 1.0, 0.27, true}}};
+    int best = GEMM_FEW;
+    double best_us = -1.0;
+    const int64_t few = tiles_of(m, n, FewTile::E, FewTile::E);
+    if (few <= 512) best_us = 2.5 + ceil((double)few / 256.0) * (1.0 + 0.85 * (double)kk / (double)kFewSingle);
+    for (const auto &e : menu) {
+        const double us = tile_us(e.t, m, n, kk);
+        if (best_us < 0.0 || us < best_us) best = e.cfg, best_us = us;
+    }
+    return best;
+}
+
+int64_t gemm_tiles(int cfg, int64_t m, int64_t n) {
+    switch (cfg) {
+        case GEMM_LARGE: return tiles_in<ShapeLarge>(m, n);
+        case GEMM_WIDE: return tiles_in<ShapeWide>(m, n);
+        case GEMM_SPLIT: return tiles_in<ShapeSplit>(m, n);
+        case GEMM_MID: return tiles_in<ShapeMid>(m, n);
+        case GEMM_FLAT: return tiles_in<ShapeFlat>(m, n);
+        case GEMM_SMALL: return tiles_in<ShapeSmall>(m, n);
+        default: return tiles_of(m, n, FewTile::E, FewTile::E);
+    }
 }
 
 template <typename S, int AMODE, int BMODE, int OUT>
 hipError_t launch(const GemmArgs &g, hipStream_t stream) {
-    const dim3 grid((unsigned)(((g.M + S::BM - 1) / S::BM) * ((g.N + S::BN - 1) / S::BN)));
-    if constexpr (std::is_same<S, ShapeLarge>::value) {
-        gemm_mfma_kernel<S, AMODE, BMODE, OUT, 3><<<grid, S::THREADS, 0, stream>>>(g);
-    } else {
-        if (plain_depth(g.K, S::BK) == 4)
-            gemm_mfma_kernel<S, AMODE, BMODE, OUT, 4><<<grid, S::THREADS, 0, stream>>>(g);
-        else
-            gemm_mfma_kernel<S, AMODE, BMODE, OUT, 3><<<grid, S::THREADS, 0, stream>>>(g);
-    }
+    gemm_mfma_kernel<S, AMODE, BMODE, OUT><<<(unsigned)tiles_in<S>(g.M, g.N), S::THREADS, 0, stream>>>(g);
     return hipGetLastError();
 }
 
-int64_t tiles_of(int64_t m, int64_t n, int64_t bm, int64_t bn) { return ((m + bm - 1) / bm) * ((n + bn - 1) / bn); }
-
-// Tile shape of a plain product with an m x n output and contraction kk.
-//   256 x 256 (8 waves, one work-group per compute unit) once there are at least 160 such tiles:
-//     half the operand traffic per flop of the 128 x 128 tile, which needs more bytes per clock
-//     from L2 than it delivers at full MFMA rate;
-//   64 x 64, or 32 x 32 while those give at most two work-groups per compute unit, with the contraction
-//     split over eight waves (few_tile) when there are fewer than 65 tiles of 128 x 128 (a quarter of
-//     the compute units);
-//   128 x 128 x 64 with two wave groups splitting the contraction when there are at most 256
-//     tiles and the contraction is 768 or longer (a compute unit then still holds 8 waves; at 768
-//     it runs like the 4-wave tile on its own, and its 512 threads allow the paired launch);
-//   128 x 128 x 32 with 4 waves otherwise (two work-groups per compute unit).
-int gemm_cfg(int64_t m, int64_t n, int64_t kk) {
-    if (tiles_of(m, n, ShapeLarge::BM, ShapeLarge::BN) >= 160) return GEMM_LARGE;
-    const int64_t t128 = tiles_of(m, n, 128, 128);
-    if (t128 < 65) return GEMM_FEW;
-    if (t128 <= 256 && kk >= 768) return GEMM_SPLIT;
-    return GEMM_MID;
-}
-
-// Edge of the tile of few_tile: 32 while that gives at most two work-groups per compute unit.
-int few_edge(int64_t m, int64_t n) { return tiles_of(m, n, 32, 32) <= 512 ? 32 : 64; }
-
-template <int E, int AMODE, int BMODE>
+template <int AMODE, int BMODE>
 hipError_t launch_few(const GemmArgs &g, hipStream_t stream) {
-    const unsigned grid = (unsigned)tiles_of(g.M, g.N, E, E);
+    const unsigned grid = (unsigned)tiles_of(g.M, g.N, FewTile::E, FewTile::E);
     if (g.K <= kFewSingle)
-        few_tile_kernel<E, AMODE, BMODE, true><<<grid, kFewThreads, 0, stream>>>(g);
+        few_tile_kernel<AMODE, BMODE, true><<<grid, kFewThreads, 0, stream>>>(g);
     else
-        few_tile_kernel<E, AMODE, BMODE, false><<<grid, kFewThreads, 0, stream>>>(g);
+        few_tile_kernel<AMODE, BMODE, false><<<grid, kFewThreads, 0, stream>>>(g);
     return hipGetLastError();
 }
 
-template <int AMODE, int BMODE, int OUT>
+template <int AMODE, int BMODE>
 hipError_t launch_gemm(int cfg, const GemmArgs &g, hipStream_t stream) {
-    if (cfg == GEMM_LARGE) {
-        if constexpr (AMODE == A_KCONTIG && OUT == OUT_BF16) {
-            gemm_dma_kernel<BMODE><<<(unsigned)tiles_of(g.M, g.N, DmaTile::BM, DmaTile::BN), DmaTile::THREADS, 0, stream>>>(g);
-            return hipGetLastError();
-        } else {
-            return launch<ShapeLarge, AMODE, BMODE, OUT>(g, stream);
-        }
+    switch (cfg) {
+        case GEMM_LARGE: return launch<ShapeLarge, AMODE, BMODE, OUT_BF16>(g, stream);
+        case GEMM_WIDE: return launch<ShapeWide, AMODE, BMODE, OUT_BF16>(g, stream);
+        case GEMM_SPLIT: return launch<ShapeSplit, AMODE, BMODE, OUT_BF16>(g, stream);
+        case GEMM_MID: return launch<ShapeMid, AMODE, BMODE, OUT_BF16>(g, stream);
+        case GEMM_FLAT: return launch<ShapeFlat, AMODE, BMODE, OUT_BF16>(g, stream);
+        case GEMM_SMALL: return launch<ShapeSmall, AMODE, BMODE, OUT_BF16>(g, stream);
+        default: return launch_few<AMODE, BMODE>(g, stream);
     }
-    if (cfg == GEMM_SPLIT) return launch<ShapeSplit, AMODE, BMODE, OUT>(g, stream);
-    if constexpr (OUT == OUT_BF16)
-        if (cfg == GEMM_FEW)
-            return few_edge(g.M, g.N) == 32 ? launch_few<32, AMODE, BMODE>(g, stream) : launch_few<64, AMODE, BMODE>(g, stream);
-    return launch<ShapeMid, AMODE, BMODE, OUT>(g, stream);
 }
 
 GemmArgs args_nt(const bf16_t *X, const bf16_t *W, const bf16_t *bias, bf16_t *Y, int64_t n, int64_t d_in, int64_t d_out) {
@@ -266,15 +278,16 @@ struct EventPair {
     ~EventPair() { done(); }
 };
 
-// The plain product of a pass that is launched together with the pass's sketch product: 256 x 256
-// tiles where it fills the chip with them, else the 128 x 128 x 64 split tiles, whatever it would use
-// alone (both run with 512 threads, like the sketch kernels).
+// The plain product of a pass that is launched together with the pass's sketch product: 256 x 256 tiles where it
+// fills the chip with them, else 128 x 128, whatever it would use alone (all run with 512 threads, like the sketch
+// kernels); with two wave groups where the contraction is long (4096 x 3072 -> 768 alone: 25.0 us, without 25.5; 768 -> 768:
+// 10.3, without 9.7).
+int pair_cfg(int64_t m, int64_t n, int64_t kk) {
+    return tiles_in<ShapeLarge>(m, n) >= 160 ? GEMM_LARGE : kk >= 1536 ? GEMM_SPLIT : GEMM_MID;
+}
 PairPlain pair_plain(int64_t m, int64_t n, int64_t kk) {
-    PairPlain p;
-    p.large = tiles_of(m, n, ShapeLarge::BM, ShapeLarge::BN) >= 160;
-    p.depth = p.large ? 3 : plain_depth(kk, ShapeSplit::BK);
-    p.tiles = (int)(p.large ? tiles_of(m, n, ShapeLarge::BM, ShapeLarge::BN) : tiles_of(m, n, ShapeSplit::BM, ShapeSplit::BN));
-    return p;
+    const int cfg = pair_cfg(m, n, kk);
+    return PairPlain{cfg, (int)gemm_tiles(cfg, m, n)};
 }
 
 // Work-groups the sketch product of a pass should aim at when it is launched together with the
@@ -306,13 +319,10 @@ SketchPlan plan_pass_sketch(int64_t n, int64_t d_sk, int64_t d_other, int64_t k,
 
 // Whether the launch of dW has room for the column sums of the bias gradient beside it.
 bool dw_takes_colsum(int64_t d_in, int64_t d_out, int64_t k) {
-    const int dw_cfg = gemm_cfg(d_out, d_in, k);
-    if (dw_cfg == GEMM_FEW) {
-        const int edge = few_edge(d_out, d_in);
-        return tiles_of(d_out, d_in, edge, edge) + colsum_blocks(d_out, 2) <= (edge == 64 ? 256 : 512);
-    }
-    const int64_t dw_tiles = dw_cfg == GEMM_LARGE ? tiles_of(d_out, d_in, ShapeLarge::BM, ShapeLarge::BN) : tiles_of(d_out, d_in, 128, 128);
-    return (256 - dw_tiles % 256) % 256 >= 64;
+    const int cfg = gemm_cfg(d_out, d_in, k);
+    const int64_t tiles = gemm_tiles(cfg, d_out, d_in);
+    if (cfg == GEMM_FEW || cfg == GEMM_SMALL || cfg == GEMM_FLAT) return tiles + colsum_blocks(d_out, 2) <= 512;  // (two on a compute unit)
+    return (256 - tiles % 256) % 256 >= 64;
 }
 
 // Compute units that the last round of a backward pass's paired launch leaves idle.
@@ -347,8 +357,7 @@ bool mfma_shape_ok(int64_t n, int64_t d_in, int64_t d_out, int64_t k) {
 // are launched one by one (to be timed) gives the same bits.
 template <int BMODE>
 static hipError_t launch_plain_of_pass(const GemmArgs &g, bool as_pair, hipStream_t stream) {
-    if (!as_pair) return launch_gemm<A_KCONTIG, BMODE, OUT_BF16>(gemm_cfg(g.M, g.N, g.K), g, stream);
-    return launch_gemm<A_KCONTIG, BMODE, OUT_BF16>(pair_plain(g.M, g.N, g.K).large ? GEMM_LARGE : GEMM_SPLIT, g, stream);
+    return launch_gemm<A_KCONTIG, BMODE>((as_pair ? pair_cfg : gemm_cfg)(g.M, g.N, g.K), g, stream);
 }
 
 hipError_t launch_linear_nt_bf16(const bf16_t *X, const bf16_t *W, const bf16_t *bias, bf16_t *Y, int64_t n,
@@ -367,28 +376,23 @@ hipError_t launch_dw_bf16(const bf16_t *G, const bf16_t *X_proj, bf16_t *dW, int
     g.accumulate = accumulate ? 1 : 0;
     g.A = G, g.lda = d_out, g.B = X_proj, g.ldb = d_in, g.C = dW, g.ldc = d_in, g.bias = nullptr;
     g.M = d_out, g.N = d_in, g.K = k, g.alpha = 1.0f;
-    return launch_gemm<A_MCONTIG, B_NCONTIG, OUT_BF16>(gemm_cfg(g.M, g.N, g.K), g, stream);
+    return launch_gemm<A_MCONTIG, B_NCONTIG>(gemm_cfg(g.M, g.N, g.K), g, stream);
 }
 
 template <typename S>
 static hipError_t launch_dw_colsum(const GemmArgs &g, const ColsumArgs &c, hipStream_t stream) {
-    const int blocks_a = (int)tiles_of(g.M, g.N, S::BM, S::BN);
-    const dim3 grid((unsigned)(blocks_a + colsum_blocks(c.d, 2)));
-    if (plain_depth(g.K, S::BK) == 3)
-        dw_colsum_kernel<S, 3><<<grid, S::THREADS, 0, stream>>>(g, c, blocks_a);
-    else
-        dw_colsum_kernel<S, 4><<<grid, S::THREADS, 0, stream>>>(g, c, blocks_a);
+    const int blocks_a = (int)tiles_in<S>(g.M, g.N);
+    dw_colsum_kernel<S><<<(unsigned)(blocks_a + colsum_blocks(c.d, 2)), S::THREADS, 0, stream>>>(g, c, blocks_a);
     return hipGetLastError();
 }
 
-template <int E>
 static hipError_t launch_few_dw_colsum(const GemmArgs &g, const ColsumArgs &c, hipStream_t stream) {
-    const int blocks_a = (int)tiles_of(g.M, g.N, E, E);
+    const int blocks_a = (int)tiles_of(g.M, g.N, FewTile::E, FewTile::E);
     const unsigned grid = (unsigned)(blocks_a + colsum_blocks(c.d, 2));
     if (g.K <= kFewSingle)
-        few_dw_colsum_kernel<E, true><<<grid, kFewThreads, 0, stream>>>(g, c, blocks_a);
+        few_dw_colsum_kernel<true><<<grid, kFewThreads, 0, stream>>>(g, c, blocks_a);
     else
-        few_dw_colsum_kernel<E, false><<<grid, kFewThreads, 0, stream>>>(g, c, blocks_a);
+        few_dw_colsum_kernel<false><<<grid, kFewThreads, 0, stream>>>(g, c, blocks_a);
     return hipGetLastError();
 }
 
@@ -404,33 +408,28 @@ hipError_t launch_dw_colsum_bf16(const bf16_t *G, const bf16_t *X_proj, bf16_t *
             const hipError_t e = launch_dw_bf16(G, X_proj, dW, k, d_in, d_out, stream, accumulate);
             return e != hipSuccess ? e : launch_colsum<bf16_t>(dY, dbias, n, d_out, stream, accumulate);
         }
+        case GEMM_WIDE: return launch_dw_colsum<ShapeWide>(g, c, stream);
         case GEMM_SPLIT: return launch_dw_colsum<ShapeSplit>(g, c, stream);
-        case GEMM_FEW: return few_edge(g.M, g.N) == 32 ? launch_few_dw_colsum<32>(g, c, stream) : launch_few_dw_colsum<64>(g, c, stream);
-        default: return launch_dw_colsum<ShapeMid>(g, c, stream);
+        case GEMM_MID: return launch_dw_colsum<ShapeMid>(g, c, stream);
+        case GEMM_FLAT: return launch_dw_colsum<ShapeFlat>(g, c, stream);
+        case GEMM_SMALL: return launch_dw_colsum<ShapeSmall>(g, c, stream);
+        default: return launch_few_dw_colsum(g, c, stream);
     }
 }
 
 // |X^T dY|_F^2 per tile for the variance monitors: the dW-type product (both operands stored
-// [token][feature]) with the squared-norm epilogue; the tile menu of the other products without
-// its entry for few tiles.
+// [token][feature]) with the squared-norm epilogue; the tiles of the other products, but for 32 x 32.
 static int xty_cfg(int64_t m, int64_t n, int64_t kk) {
     const int cfg = gemm_cfg(m, n, kk);
-    return cfg == GEMM_FEW ? (kk >= 1536 ? GEMM_SPLIT : GEMM_MID) : cfg;
+    return cfg == GEMM_FEW ? GEMM_SMALL : cfg;
 }
 
-int xty_sumsq_tiles(int64_t n, int64_t d_in, int64_t d_out) {
-    const bool large = xty_cfg(d_in, d_out, n) == GEMM_LARGE;
-    return (int)tiles_of(d_in, d_out, large ? ShapeLarge::BM : 128, large ? ShapeLarge::BN : 128);
-}
+int xty_sumsq_tiles(int64_t n, int64_t d_in, int64_t d_out) { return (int)gemm_tiles(xty_cfg(d_in, d_out, n), d_in, d_out); }
 
 template <typename S>
 static hipError_t launch_xty_norms(const GemmArgs &g, const RowNormArgs &r, hipStream_t stream) {
-    const int tiles = (int)tiles_of(g.M, g.N, S::BM, S::BN);
-    const unsigned grid = (unsigned)(tiles + row_norm_blocks(r.n));
-    if (std::is_same<S, ShapeLarge>::value || plain_depth(g.K, S::BK) == 3)
-        xty_norms_kernel<S, 3><<<grid, S::THREADS, 0, stream>>>(g, r, tiles);
-    else if constexpr (!std::is_same<S, ShapeLarge>::value)
-        xty_norms_kernel<S, 4><<<grid, S::THREADS, 0, stream>>>(g, r, tiles);
+    const int tiles = (int)tiles_in<S>(g.M, g.N);
+    xty_norms_kernel<S><<<(unsigned)(tiles + row_norm_blocks(r.n)), S::THREADS, 0, stream>>>(g, r, tiles);
     return hipGetLastError();
 }
 
@@ -442,8 +441,11 @@ hipError_t launch_xty_norms_bf16(const bf16_t *X, const bf16_t *dY, double *part
     const RowNormArgs r{X, dY, n, d_in, d_out, 1, rows};
     switch (xty_cfg(g.M, g.N, g.K)) {
         case GEMM_LARGE: return launch_xty_norms<ShapeLarge>(g, r, stream);
+        case GEMM_WIDE: return launch_xty_norms<ShapeWide>(g, r, stream);
         case GEMM_SPLIT: return launch_xty_norms<ShapeSplit>(g, r, stream);
-        default: return launch_xty_norms<ShapeMid>(g, r, stream);
+        case GEMM_MID: return launch_xty_norms<ShapeMid>(g, r, stream);
+        case GEMM_FLAT: return launch_xty_norms<ShapeFlat>(g, r, stream);
+        default: return launch_xty_norms<ShapeSmall>(g, r, stream);
     }
 }
 
@@ -560,22 +562,18 @@ static int sors_pair_order(int64_t blocks_a, int64_t strip_groups) {
 
 bool sors_pair_available(int64_t n, int64_t d_sk, int64_t d_other, int64_t k) {
     if (!sors_fast_ok(n, d_sk) || sors_chunks(n) == 0 || k > 2048) return false;
-    const int cfg = gemm_cfg(n, d_other, d_sk);
-    if (!(cfg == GEMM_LARGE || (cfg == GEMM_SPLIT && plain_depth(d_sk, ShapeSplit::BK) == 4))) return false;
-    const int64_t blocks_a = cfg == GEMM_LARGE ? tiles_of(n, d_other, ShapeLarge::BM, ShapeLarge::BN)
-                                               : tiles_of(n, d_other, ShapeSplit::BM, ShapeSplit::BN);
-    return sors_pair_order(blocks_a, (d_sk / 8 + 1) / 2) != 0;
+    const PairPlain plain = pair_plain(n, d_other, d_sk);
+    // 128 x 128 tiles: one round of them, long enough for the strips to finish beside it
+    if (plain.cfg != GEMM_LARGE && (plain.tiles < 65 || plain.tiles > 256 || d_sk < 768)) return false;
+    return sors_pair_order(plain.tiles, (d_sk / 8 + 1) / 2) != 0;
 }
 
 static hipError_t launch_pass_sors(const GemmArgs &ga, bool row_indexed_b, const bf16_t *A, bf16_t *out, int64_t n, int64_t d_sk,
                                    int64_t k, SketchState st, hipStream_t stream, hipEvent_t ev_begin, hipEvent_t ev_end) {
-    const int cfg = gemm_cfg(ga.M, ga.N, ga.K);
-    const int blocks_a = (int)(cfg == GEMM_LARGE ? tiles_of(ga.M, ga.N, ShapeLarge::BM, ShapeLarge::BN)
-                                                 : tiles_of(ga.M, ga.N, ShapeSplit::BM, ShapeSplit::BN));
+    const PairPlain plain = pair_plain(ga.M, ga.N, ga.K);
     const SorsArgs gs{A, out, n, d_sk, k, st, 1.0f / sqrtf((float)k)};
     EventPair pev(ev_begin, ev_end, stream);
-    return launch_pair_sors(cfg, row_indexed_b, ga, gs, blocks_a, sors_chunks(n), sors_pair_order(blocks_a, (d_sk / 8 + 1) / 2) == 2,
-                            stream);
+    return launch_pair_sors(plain, row_indexed_b, ga, gs, sors_chunks(n), sors_pair_order(plain.tiles, (d_sk / 8 + 1) / 2) == 2, stream);
 }
 
 hipError_t launch_forward_pair_sors_bf16(const bf16_t *X, const bf16_t *W, const bf16_t *bias, bf16_t *Y, bf16_t *X_proj,

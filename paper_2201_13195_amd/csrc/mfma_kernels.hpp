@@ -10,11 +10,10 @@
 // operand whose contraction index is its row index is read back from LDS with the transposing load
 // ds_read_b64_tr_b16, which hands every lane four consecutive contraction elements of one column.
 //
-//   gemm_tile_dma   Y and dX on 256 x 256 tiles: memory straight into LDS, two stages of 64 contraction elements
-//   gemm_tile       Y, dX, dW and X^T dY on 128 x 128 tiles (X^T dY also on 256 x 256): 16-byte chunks through
-//                   registers into three LDS stages, up to four more tiles in flight in registers
-//   few_tile        products with few output tiles: the waves of a work-group share the contraction, no barriers
-//   sketch_tile     sketch products with k > 64, in the pipeline of gemm_tile_dma.  The sketch operand is never in
+//   gemm_tile       Y, dX, dW and X^T dY on tiles from 64 x 64 to 256 x 256: memory straight into LDS, two to four
+//                   stages of 64 contraction elements
+//   few_tile        products with very few output tiles: the waves of a work-group share the contraction, no barriers
+//   sketch_tile     sketch products with k > 64, in the same kind of pipeline.  The sketch operand is never in
 //                   memory: the work-group generates its tile of P^T into LDS (one 16-byte chunk = 8 consecutive
 //                   tokens of one sketch column = one Philox-4x32-10 call for the Gaussian kind, one byte of a
 //                   call's 128 sign bits for the Rademacher kind).  The 1/sqrt(k) of S = P/sqrt(k) is applied to
@@ -59,16 +58,34 @@ enum { B_KCONTIG = 0, B_NCONTIG = 1 };
 // the sum of squares of the tile (one double per work-group, C = double[work-groups]).
 enum { OUT_BF16 = 0, OUT_F32_PARTIAL = 1, OUT_SUMSQ = 2 };
 
-// Work-group tile shapes: BM x BN outputs, BK contraction elements per LDS tile, WM x WN waves
-// over the tile, WK groups of waves that split the contraction of a tile.
+// Tiles of a plain product (gemm_tile): BM x BN outputs, WM x WN waves over the tile, WK groups of waves that take
+// every other 16-deep contraction step, SA / SB LDS stages of the two operands, SP loads per wave and 16-deep step.
+template <int BM_, int BN_, int WM_, int WN_, int WK_, int SA_, int SB_, int SP_>
+struct TileShape {
+    static constexpr int BM = BM_, BN = BN_, BK = 64, WM = WM_, WN = WN_, WK = WK_, SA = SA_, SB = SB_, SP = SP_;
+    static constexpr int WAVES = WM * WN * WK, THREADS = 64 * WAVES;
+    static constexpr int TM = BM / WM / 32, TN = BN / WN / 32;             // 32 x 32 MFMA tiles per wave
+    static constexpr int A_ELEMS = BM * BK, B_ELEMS = BN * BK;             // of a stage
+    static constexpr int A_LOADS = BM / 8 / WAVES, B_LOADS = BN / 8 / WAVES;  // 1 KB loads per wave and step
+    static constexpr int LDS_BYTES = (SA * A_ELEMS + SB * B_ELEMS) * 2;
+    static_assert(BM % (32 * WM) == 0 && BN % (32 * WN) == 0 && BM % (8 * WAVES) == 0 && BN % (8 * WAVES) == 0, "shares of a wave");
+    static_assert(SB >= 2 && (SA == SB || SA == SB + 1) && SP * (4 / WK) >= A_LOADS + B_LOADS, "the loads of a step fit into it");
+    static_assert(WK <= 2 && LDS_BYTES <= 160 * 1024, "LDS of a compute unit");
+};
+// (which product takes which: gemm_cfg and pair_plain in mfma.hip)
+typedef TileShape<256, 256, 2, 4, 1, 3, 2, 4> ShapeLarge;
+typedef TileShape<128, 256, 2, 4, 1, 3, 3, 2> ShapeWide;
+typedef TileShape<128, 128, 2, 2, 2, 3, 3, 3> ShapeSplit;
+typedef TileShape<128, 128, 2, 4, 1, 3, 3, 1> ShapeMid;
+typedef TileShape<64, 128, 2, 4, 1, 3, 3, 1> ShapeFlat;
+typedef TileShape<64, 64, 2, 2, 1, 4, 4, 1> ShapeSmall;
+
+// Tiles of a sketch product (sketch_tile).
 template <int BM_, int BN_, int BK_, int WM_, int WN_, int WK_>
 struct Shape {
     static constexpr int BM = BM_, BN = BN_, BK = BK_, WM = WM_, WN = WN_, WK = WK_;
     static constexpr int THREADS = 64 * WM * WN * WK;
 };
-typedef Shape<256, 256, 32, 2, 4, 1> ShapeLarge;     // outputs with at least 160 such tiles: half the operand traffic per flop
-typedef Shape<128, 128, 64, 2, 2, 2> ShapeSplit;     // at most 256 tiles of 128 x 128 and a contraction of 768 or more
-typedef Shape<128, 128, 32, 2, 2, 1> ShapeMid;       // everything else; two work-groups per compute unit
 typedef Shape<128, 512, 64, 1, 8, 1> ShapeSkWide;      // sketch products, tile generated into LDS;
 typedef Shape<64, 512, 64, 1, 8, 1> ShapeSkWide64;     //   eight waves side by side: no two waves read the same B fragment
                                                        //   (64 instead of 80 KB of LDS reads per step)
@@ -111,28 +128,6 @@ __device__ __forceinline__ bf16x8_t radem_operand(const Words4 &r, uint32_t t0) 
         out.d[q] = 0x3F803F80u | (((bits >> (2 * q)) & 1u) << 15) | (((bits >> (2 * q + 1)) & 1u) << 31);
     return out.v;
 }
-
-template <int BM, int BN, int BK, int WAVES_M, int WAVES_N, int WAVES_K, int AMODE, int BMODE, int OUT>
-struct Tile {
-    static constexpr int THREADS = 64 * WAVES_M * WAVES_N * WAVES_K;  // WAVES_K groups of waves split the contraction
-    static constexpr int WTM = BM / WAVES_M, WTN = BN / WAVES_N;  // wave tile
-    static constexpr int TM = WTM / 32, TN = WTN / 32;            // 32x32 MFMA tiles per wave
-    static constexpr bool A_KLAYOUT = AMODE == A_KCONTIG;  // LDS tile [row][contraction]
-    static constexpr int A_STRIDE = A_KLAYOUT ? BK : BM + TPAD;  // elements per LDS row
-    static constexpr int A_ROWS = A_KLAYOUT ? BM : BK;
-    static constexpr int B_STRIDE = BMODE == B_KCONTIG ? BK : BN + TPAD;
-    static constexpr int B_ROWS = BMODE == B_KCONTIG ? BN : BK;
-    static constexpr int A_ELEMS = A_ROWS * A_STRIDE;
-    static constexpr int B_ELEMS = B_ROWS * B_STRIDE;
-    static constexpr int STAGE_ELEMS = A_ELEMS + B_ELEMS;
-    static constexpr int STAGES = 3;  // LDS stages: tile t is computed while tile t+2 is written
-    static constexpr int LDS_BYTES = STAGES * STAGE_ELEMS * 2;
-    // 16-byte chunks per thread and tile
-    static constexpr int A_CHUNKS = BM * BK / 8 / THREADS;
-    static constexpr int B_CHUNKS = BN * BK / 8 / THREADS;
-    static_assert(BM % (32 * WAVES_M) == 0 && BN % (32 * WAVES_N) == 0 && BK % (16 * WAVES_K) == 0, "tile shape");
-    static_assert((BM * BK / 8) % THREADS == 0 && (BN * BK / 8) % THREADS == 0, "chunks per thread");
-};
 
 // The output tile of a wave.  The MFMA was issued with the operands swapped (B fragment first), so the
 // accumulators hold C^T tiles: register v of lane l is C(l % 32, 8*(v/4) + 4*(l/32) + v%4)
@@ -237,276 +232,273 @@ __device__ __forceinline__ void write_tile(const GemmArgs &g, const f32x16_t (&a
     }
 }
 
-// One work-group's share of a product: output tile number `block` of `blocks` (before the
-// renumbering below).  `lds` holds Tile::LDS_BYTES bytes.
-template <typename S, int AMODE, int BMODE, int OUT, int D>
-__device__ __forceinline__ void gemm_tile(const GemmArgs &g, bf16_t *lds, int64_t block, int64_t blocks) {
-    constexpr int BM = S::BM, BN = S::BN, BK = S::BK, WAVES_M = S::WM, WAVES_N = S::WN, WAVES_K = S::WK;
-    typedef Tile<BM, BN, BK, WAVES_M, WAVES_N, WAVES_K, AMODE, BMODE, OUT> T;
+// ---------------------------------------------------------------------------------------------
+// The plain products.  Memory -> LDS without registers in between (buffer_load ... lds, 16 bytes per lane, a wave's
+// 64 lanes = 1 KB of consecutive LDS), in steps of 64 contraction elements: whole 128-byte lines of K-contiguous
+// rows.  What bounds it is that path: a compute unit takes at most 64 bytes per clock from L2, about 40 where the whole
+// chip pulls 256 x 256 tiles (a loop of these loads alone, 64 KB in flight), against the 32 its MFMAs need with such
+// tiles and the 64 with 128 x 128; and that the first load of a line waits for HBM.  So
+//   - the tile is as large as the number of tiles allows;
+//   - the loads of a step are spread between the MFMAs of two 16-deep steps, SP per wave and 16-deep step, instead of
+//     being issued in one burst behind the barrier, where the MFMAs behind them in the instruction stream wait until the
+//     burst is taken (256 x 256, 16384 x 4096 -> 1024: 125 -> 113 us; 128 x 128, 4096 x 3072 -> 768: 28 -> 26);
+//   - the operand that streams (A: tokens) gets one LDS stage more than the weights where all of LDS is one tile's (256 x
+//     256: 113 -> 108 us), and smaller tiles have three or four stages.
+// Every instruction of a step has its place: an MFMA, then the LDS reads and loads that go with it (sched_barrier);
+// left to itself the compiler bunches the reads in front of their use.
+//
+// LDS is laid out by the load, so what keeps bank conflicts away is which chunk a lane asks for: rows of 64 contraction
+// elements hold chunk c at kchunk_pos, rows of columns at col_chunk.
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    // Wave w works on the (wm, wn) part of the tile and, of every 16-deep contraction step s,
-    // on those with s % WAVES_K == kg.
-    const int kg = wave / (WAVES_M * WAVES_N), wmn = wave % (WAVES_M * WAVES_N);
-    const int wm = wmn / WAVES_N, wn = wmn % WAVES_N;
+// One wave's load of 1 KB into LDS from byte `to` on, 16 bytes from `off` + `soff` per lane.  The compiler does
+// not see that it writes LDS (it would wait for it before every LDS read): the explicit waits and barriers order them.
+__device__ __forceinline__ void load_to_lds(__amdgpu_buffer_rsrc_t rsrc, uint32_t to, uint32_t off, uint32_t soff) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(to), "v"(off), "s"(rsrc), "s"(soff) : "m0");
+}
+// Waits until at most N of this wave's loads are outstanding.
+template <int N>
+__device__ __forceinline__ void wait_for_loads() {
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+// A descriptor of `rows` rows of pitch ld from `base` on.  (The byte count is the same in every lane; saying so keeps it in
+// scalar registers.  The asm holds the wait states between a vector instruction that writes a scalar register and a load
+// that reads it: the compiler does not look for them in front of load_to_lds.)
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t rows_descriptor(const bf16_t *base, int64_t ld, int64_t rows) {
+    __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<bf16_t *>(base), (short)0, __builtin_amdgcn_readfirstlane((int)((rows > 0 ? rows : 0) * ld * 2)), 0x00020000);
+    asm volatile("s_nop 4" : "+s"(r));
+    return r;
+}
+// Rows of C columns, contraction row k: chunk c (eight columns) sits at position col_chunk(k, c) and the other way round.
+// The four rows of a transposing read (k, k + 1, k + 2, k + 3) then fall on different 64 bytes of the banks.
+template <int C>
+__device__ __forceinline__ int col_chunk(int k, int chunk) {
+    return chunk ^ (C >= 128 ? (k & 3) << 2 : (k & 2) << 1);
+}
+// (see frag_transposed) from rows of C columns placed like that
+template <int C>
+__device__ __forceinline__ bf16x8_t frag_columns(const bf16_t *tile, int col0, int kk0, int lane) {
+    const int blk = lane >> 4, i = lane & 15, k = kk0 + ((blk >> 1) << 3) + (i >> 2), col = col0 + ((blk & 1) << 4) + ((i & 3) << 2);
+    const bf16_t *p = tile + k * C + (col_chunk<C>(k, col >> 3) << 3) + (col & 7);
+    typedef __attribute__((address_space(3))) s16x4_t *lds_ptr_t;
+    const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr_t)(p));
+    const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr_t)(p + 4 * C));  // (row k + 4: same k % 4)
+    union {
+        s16x8_t s;
+        bf16x8_t v;
+    } out;
+    out.s = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+    return out.v;
+}
+
+// One operand of a tile on its way into LDS: E rows of 64 contraction elements (KROWS) or 64 contraction rows of E
+// columns, J loads of 1 KB per wave.  An offset at or beyond the descriptor's byte range writes zeros without touching
+// memory, so edges and tails need no branches (a chunk that must read as zero gets the offset 2^31).  A descriptor spans
+// only what the work-group reads of the operand, so that 32-bit offsets suffice for operands of any size: the tile's rows,
+// fixed for the kernel, or the 64 contraction rows of a step.
+template <int E, int J, bool KROWS>
+struct OperandLoads {
+    static constexpr uint32_t OOB = 0x80000000u;
+    uint32_t off[J];
+    int kk[J];
+    const bf16_t *base;
+    int64_t ld;
+    __amdgpu_buffer_rsrc_t rsrc;  // of the step that is being requested
+    uint32_t to, soff;
+    int left;
+    __device__ __forceinline__ void init(const bf16_t *operand, int64_t ld_, int64_t row0, int64_t rows, int wave, int lane) {
+        base = operand, ld = ld_;
+#pragma unroll
+        for (int j = 0; j < J; ++j) {
+            if constexpr (KROWS) {
+                const int row = (wave * J + j) * 8 + (lane >> 3), chunk = kchunk_pos<64>(row, lane & 7);
+                kk[j] = chunk * 8;
+                off[j] = row0 + row < rows ? (uint32_t)((row * ld + chunk * 8) * 2) : OOB;
+            } else {
+                const int c = (wave * J + j) * 64 + lane, k = c / (E / 8), col = col_chunk<E>(k, c % (E / 8)) * 8;
+                off[j] = row0 + col < rows ? (uint32_t)((k * ld + row0 + col) * 2) : OOB;
+            }
+        }
+        if constexpr (KROWS) rsrc = rows_descriptor(operand + row0 * ld, ld, min((int64_t)E, rows - row0));
+    }
+    // The step from contraction element k0 on, of which `left_` exist (<= 0: zeros), goes to LDS byte `to_` (of this wave's share).
+    __device__ __forceinline__ void begin(uint32_t to_, int k0, int left_) {
+        if constexpr (!KROWS) rsrc = rows_descriptor(base + (int64_t)k0 * ld, ld, min(64, left_));
+        to = to_, soff = KROWS ? (uint32_t)k0 * 2 : 0u, left = left_;
+    }
+    __device__ __forceinline__ void load(int j) const { load_to_lds(rsrc, to + j * 1024, !KROWS || kk[j] < left ? off[j] : OOB, soff); }
+};
+
+// One work-group's share of a product: output tile number `block` of `blocks`.  `lds` holds S::LDS_BYTES bytes.
+template <typename S, int AMODE, int BMODE, int OUT>
+__device__ __forceinline__ void gemm_tile(const GemmArgs &g, bf16_t *lds, int64_t block, int64_t blocks) {
+    constexpr int BM = S::BM, BN = S::BN, BK = S::BK, SA = S::SA, SB = S::SB, SP = S::SP, TM = S::TM, TN = S::TN;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // Wave w works on the (wm, wn) part of the tile and, of every 16-deep contraction step s, on those with s % WK == kg.
+    const int kg = wave / (S::WM * S::WN), wmn = wave % (S::WM * S::WN), wm = wmn / S::WN, wn = wmn % S::WN;
     // Tile order.  Work-groups are dealt round-robin to the 8 XCDs (each with its own L2), so first
     // renumber them such that one XCD owns a contiguous run of positions; then walk the tile grid
     // in bands of GROUP_M tile rows, column by column, so that the work-groups resident on one XCD
     // at the same time form a compact block that shares A row blocks and B column blocks in L2.
     const int64_t tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN;
-    const int64_t tiles = blocks;
-    int64_t tile = block;
+    int64_t tile;
     {
-        const int64_t per = tiles / 8, rem = tiles % 8, x = tile % 8, r = tile / 8;
+        const int64_t per = blocks / 8, rem = blocks % 8, x = block % 8, r = block / 8;
         tile = x * per + (x < rem ? x : rem) + r;   // XCD x owns `per` (+1 for the first `rem`) consecutive positions
     }
     constexpr int64_t GROUP_M = 8;
     const int64_t band = tile / (GROUP_M * tiles_n), in_band = tile % (GROUP_M * tiles_n);
     const int64_t band_rows = min(GROUP_M, tiles_m - band * GROUP_M);
     const int64_t m0 = (band * GROUP_M + in_band % band_rows) * BM, n0 = (in_band / band_rows) * BN;
-    const int kk_len = (int)g.K, num_tiles = (kk_len + BK - 1) / BK;
-
-    f32x16_t acc[T::TM][T::TN];
-#pragma unroll
-    for (int a = 0; a < T::TM; ++a)
-#pragma unroll
-        for (int b = 0; b < T::TN; ++b)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[a][b][v] = 0.0f;
-
-    // Global loads are buffer loads: an offset at or beyond the descriptor's byte range returns
-    // zeros without touching memory, so tile edges and the tail of the contraction need no branches
-    // (a chunk that must read as zero is simply given the offset 2^31).  A descriptor never spans
-    // the whole operand, only what this work-group reads of it, so that its 32-bit offsets suffice
-    // for operands of any size: a K-contiguous operand is described from the first row of the tile
-    // (BM or BN rows, fixed for the kernel), a row-indexed operand from the first contraction row
-    // of each tile (BK rows, re-based at every step; rows beyond the contraction fall outside the range).
-    constexpr uint32_t OOB = 0x80000000u;
-    auto rows_rsrc = [](const bf16_t *base, int64_t ld, int64_t rows) {  // `rows` rows of pitch ld starting at base
-        // (the byte count is the same in every lane; saying so keeps the descriptor in scalar registers)
-        const int bytes = __builtin_amdgcn_readfirstlane((int)((rows > 0 ? rows : 0) * ld * 2));
-        return __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(base), (short)0, bytes, 0x00020000);
-    };
-
-    // Per 16-byte chunk of a tile: byte offset in the operand for the first tile,
-    // whether its row / column group exists at all, and its position along the contraction.
-    uint32_t a_off[T::A_CHUNKS], b_off[T::B_CHUNKS];
-    bool a_ok[T::A_CHUNKS], b_ok[T::B_CHUNKS];
-    int a_kk[T::A_CHUNKS], b_kk[T::B_CHUNKS];
-    int a_lds[T::A_CHUNKS], b_lds[T::B_CHUNKS];
-    if constexpr (AMODE == A_KCONTIG) {  // A[m][kk], tile BM x BK
-#pragma unroll
-        for (int q = 0; q < T::A_CHUNKS; ++q) {
-            const int c = tid + T::THREADS * q, row = c / (BK / 8), kc = c % (BK / 8);
-            a_ok[q] = m0 + row < g.M;
-            a_kk[q] = kc * 8;
-            a_off[q] = (uint32_t)((row * g.lda + kc * 8) * 2);  // from row m0
-            a_lds[q] = row * T::A_STRIDE + kchunk_pos<BK>(row, kc) * 8;
-        }
-    } else if constexpr (AMODE == A_MCONTIG) {  // A stored [kk][m], tile BK x BM
-#pragma unroll
-        for (int q = 0; q < T::A_CHUNKS; ++q) {
-            const int c = tid + T::THREADS * q, row = c / (BM / 8), mc = c % (BM / 8);
-            a_ok[q] = m0 + mc * 8 < g.M;
-            a_kk[q] = row;
-            a_off[q] = (uint32_t)((row * g.lda + m0 + mc * 8) * 2);  // from the tile's first contraction row
-            a_lds[q] = row * T::A_STRIDE + mc * 8;
-        }
-    }
-    if constexpr (BMODE == B_KCONTIG) {  // B stored [n][kk], tile BN x BK
-#pragma unroll
-        for (int q = 0; q < T::B_CHUNKS; ++q) {
-            const int c = tid + T::THREADS * q, row = c / (BK / 8), kc = c % (BK / 8);
-            b_ok[q] = n0 + row < g.N;
-            b_kk[q] = kc * 8;
-            b_off[q] = (uint32_t)((row * g.ldb + kc * 8) * 2);  // from row n0
-            b_lds[q] = row * T::B_STRIDE + kchunk_pos<BK>(row, kc) * 8;
-        }
-    } else {  // B stored [kk][n], tile BK x BN
-#pragma unroll
-        for (int q = 0; q < T::B_CHUNKS; ++q) {
-            const int c = tid + T::THREADS * q, row = c / (BN / 8), nc = c % (BN / 8);
-            b_ok[q] = n0 + nc * 8 < g.N;
-            b_kk[q] = row;
-            b_off[q] = (uint32_t)((row * g.ldb + n0 + nc * 8) * 2);  // from the tile's first contraction row
-            b_lds[q] = row * T::B_STRIDE + nc * 8;
-        }
-    }
-
-    // D register sets hold the tiles in flight: tile t + D is requested while tile t is computed.
-    u32x4_t ra[D][T::A_CHUNKS], rb[D][T::B_CHUNKS];
-
-    // Work-groups walk the contraction from different starting tiles (and wrap around): with a
+    const int kk = (int)g.K, steps = (kk + BK - 1) / BK;
+    // Work-groups walk the contraction from different starting steps (and wrap around): with a
     // power-of-two row pitch all rows of a tile fall on the same one or two L2 channels, and the
     // rotation spreads concurrently running work-groups over the channels.  The eight tiles of one
-    // band column (same B column block, neighbouring A row blocks) share a starting tile so that
+    // band column (same B column block, neighbouring A row blocks) share a starting step so that
     // their common operand is fetched once into L2.
-    const int stagger = (int)((tile / 8) % num_tiles);
-    auto rotated = [&](int t) { return t + stagger - (t + stagger >= num_tiles ? num_tiles : 0); };
+    const int stagger = (int)((tile / 8) % steps);
 
-    __amdgpu_buffer_rsrc_t rsrc_a_fixed, rsrc_b_fixed;  // K-contiguous operands
-    if constexpr (AMODE == A_KCONTIG) rsrc_a_fixed = rows_rsrc(g.A + m0 * g.lda, g.lda, min((int64_t)BM, g.M - m0));
-    if constexpr (BMODE == B_KCONTIG) rsrc_b_fixed = rows_rsrc(g.B + n0 * g.ldb, g.ldb, min((int64_t)BN, g.N - n0));
-    auto issue = [&](int set, int t_seq) {  // request the t_seq-th tile into register set `set`
-        const int t = t_seq < num_tiles ? rotated(t_seq) : t_seq;  // past the end: stays out of range, reads zeros
-        const int kk_tile = t * BK;
-        if constexpr (AMODE == A_KCONTIG) {
-#pragma unroll
-            for (int q = 0; q < T::A_CHUNKS; ++q) {
-                const bool ok = a_ok[q] && kk_tile + a_kk[q] < kk_len;
-                ra[set][q] = __builtin_amdgcn_raw_buffer_load_b128(rsrc_a_fixed, ok ? a_off[q] + (uint32_t)kk_tile * 2 : OOB, 0, 0);
-            }
-        } else if constexpr (AMODE == A_MCONTIG) {
-            const __amdgpu_buffer_rsrc_t rsrc = rows_rsrc(g.A + (int64_t)kk_tile * g.lda, g.lda, min(BK, kk_len - kk_tile));
-#pragma unroll
-            for (int q = 0; q < T::A_CHUNKS; ++q)
-                ra[set][q] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, a_ok[q] ? a_off[q] : OOB, 0, 0);
-        }
-        if constexpr (BMODE == B_KCONTIG) {
-#pragma unroll
-            for (int q = 0; q < T::B_CHUNKS; ++q) {
-                const bool ok = b_ok[q] && kk_tile + b_kk[q] < kk_len;
-                rb[set][q] = __builtin_amdgcn_raw_buffer_load_b128(rsrc_b_fixed, ok ? b_off[q] + (uint32_t)kk_tile * 2 : OOB, 0, 0);
-            }
-        } else {
-            const __amdgpu_buffer_rsrc_t rsrc = rows_rsrc(g.B + (int64_t)kk_tile * g.ldb, g.ldb, min(BK, kk_len - kk_tile));
-#pragma unroll
-            for (int q = 0; q < T::B_CHUNKS; ++q)
-                rb[set][q] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, b_ok[q] ? b_off[q] : OOB, 0, 0);
-        }
+    constexpr int JA = S::A_LOADS, JB = S::B_LOADS, LOADS = JA + JB;
+    OperandLoads<BM, JA, AMODE == A_KCONTIG> la;
+    OperandLoads<BN, JB, BMODE == B_KCONTIG> lb;
+    la.init(g.A, g.lda, m0, g.M, wave, lane);
+    lb.init(g.B, g.ldb, n0, g.N, wave, lane);
+    typedef __attribute__((address_space(3))) bf16_t *lds_ptr_t;
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_ptr_t)lds;
+    auto first = [&](int t) { return t >= steps ? kk : (t + stagger >= steps ? t + stagger - steps : t + stagger) * BK; };
+    auto begin_a = [&](int t, int stage) { la.begin(lds0 + (uint32_t)(stage * S::A_ELEMS * 2 + wave * JA * 1024), first(t), kk - first(t)); };
+    auto begin_b = [&](int t, int stage) {
+        lb.begin(lds0 + (uint32_t)((SA * S::A_ELEMS + stage * S::B_ELEMS) * 2 + wave * JB * 1024), first(t), kk - first(t));
+    };
+    auto load = [&](int i) {  // load i of a step: B's come first (with SA > SB they are waited for first)
+        if (i < JB)
+            lb.load(i);
+        else if (i < LOADS)
+            la.load(i - JB);
     };
 
-    // Writes the t_seq-th tile (held in register set `set`) into LDS stage `stage`.
-    auto store_lds = [&](int set, int stage, int t_seq) {
-        bf16_t *As = lds + stage * T::STAGE_ELEMS;
-        bf16_t *Bs = As + T::A_ELEMS;
+    f32x16_t acc[TM][TN];
 #pragma unroll
-        for (int q = 0; q < T::A_CHUNKS; ++q) *reinterpret_cast<u32x4_t *>(As + a_lds[q]) = ra[set][q];
+    for (int a = 0; a < TM; ++a)
 #pragma unroll
-        for (int q = 0; q < T::B_CHUNKS; ++q) *reinterpret_cast<u32x4_t *>(Bs + b_lds[q]) = rb[set][q];
-    };
-
-    // Operand fragments of one 16-deep contraction step.
+        for (int b = 0; b < TN; ++b)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[a][b][v] = 0.0f;
     struct Frags {
-        bf16x8_t a[T::TM], b[T::TN];
+        bf16x8_t a[TM], b[TN];
     };
-    constexpr int KS = BK / 16 / WAVES_K;  // 16-deep contraction steps per tile and wave: kg, kg + WAVES_K, ...
-    static_assert(KS >= 2, "the pipeline needs two contraction steps per tile and wave");
-
-    // Fragments of step `ks` of the tile whose data sits in LDS stage `stage`.  LDS reads issued here run
-    // under the MFMAs of the step before.
-    auto load_frags = [&](Frags &f, int stage, int ks_local) {
-        const int ks = ks_local * WAVES_K + kg;  // this wave's ks_local-th step of the tile
-        const bf16_t *As = lds + stage * T::STAGE_ELEMS;
-        const bf16_t *Bs = As + T::A_ELEMS;
-#pragma unroll
-        for (int a = 0; a < T::TM; ++a) {
-            const int row0 = wm * T::WTM + a * 32;
-            if constexpr (T::A_KLAYOUT)
-                f.a[a] = frag_kcontig<BK>(As, row0, ks * 16, lane);
-            else
-                f.a[a] = frag_transposed(As, T::A_STRIDE, row0, ks * 16, lane);
-        }
-#pragma unroll
-        for (int b = 0; b < T::TN; ++b) {
-            const int col0 = wn * T::WTN + b * 32;
+    constexpr int FRAGS = TM + TN, MFMAS = TM * TN, KS = BK / 16 / S::WK;
+    static_assert(KS % 2 == 0, "the first fragments of a step are always in f[0]");
+    // Fragment i of this wave's ks-th 16-deep step of the tile in stages (sa, sb).
+    auto read = [&](Frags &f, int sa, int sb, int ks, int i) {
+        const int k0 = (ks * S::WK + kg) * 16;
+        if (i < TN) {
+            const bf16_t *Bs = lds + SA * S::A_ELEMS + sb * S::B_ELEMS;
+            const int col0 = wn * (BN / S::WN) + i * 32;
             if constexpr (BMODE == B_KCONTIG)
-                f.b[b] = frag_kcontig<BK>(Bs, col0, ks * 16, lane);
+                f.b[i] = frag_kcontig<BK>(Bs, col0, k0, lane);
             else
-                f.b[b] = frag_transposed(Bs, T::B_STRIDE, col0, ks * 16, lane);
+                f.b[i] = frag_columns<BN>(Bs, col0, k0, lane);
+        } else {
+            const bf16_t *As = lds + sa * S::A_ELEMS;
+            const int row0 = wm * (BM / S::WM) + (i - TN) * 32;
+            if constexpr (AMODE == A_KCONTIG)
+                f.a[i - TN] = frag_kcontig<BK>(As, row0, k0, lane);
+            else
+                f.a[i - TN] = frag_columns<BM>(As, row0, k0, lane);
+        }
+    };
+    // One 16-deep step: multiplies `now`, reads the fragments of the one behind it and issues SP loads from load l0 on.
+    auto sixteen = [&](const Frags &now, Frags &next, int sa, int sb, int ks, int l0) {
+#pragma unroll
+        for (int i = 0; i < MFMAS; ++i) {
+            const int a = i / TN, b = i % TN;
+            acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(now.b[b], now.a[a], acc[a][b], 0, 0, 0);
+#pragma unroll
+            for (int r = i * FRAGS / MFMAS; r < (i + 1) * FRAGS / MFMAS; ++r) read(next, sa, sb, ks, r);
+#pragma unroll
+            for (int r = i * SP / MFMAS; r < (i + 1) * SP / MFMAS; ++r) load(l0 + r);
+            __builtin_amdgcn_sched_barrier(0);
         }
     };
 
-    auto multiply = [&](const Frags &f) {
+    // Step t of A is in stage t % SA, of B in stage t % SB.  The one barrier of a step stands in front of its last 16-deep
+    // step: by then every wave holds that one's fragments in registers, so the stages can be overwritten (step t + SA of A
+    // and t + SB of B are requested from here on), and the data of step t + 1 has been waited for, so its first fragments
+    // are read under the MFMAs of the last 16-deep step: no step begins by waiting for LDS.  Steps past the end are
+    // requested as zeros, which keeps the number of outstanding loads the same.
+    constexpr int OUTSTANDING = (SB - 2) * LOADS + (SA > SB ? JA : 0);  // behind the loads of step t + 1
+    Frags f[2];
 #pragma unroll
-        for (int a = 0; a < T::TM; ++a)
+    for (int s = 0; s < SA - 1; ++s) {
+        begin_a(s, s);
 #pragma unroll
-            for (int b = 0; b < T::TN; ++b)
-                acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.b[b], f.a[a], acc[a][b], 0, 0, 0);
-    };
-
-    // Pipeline.  Global side: tiles t+3 .. t+D-1 are in flight in D register sets (tile u in set
-    // u % D) while tile t is computed; the loop runs over whole groups of D tiles so that every
-    // load's register set is fixed at compile time, and tiles past the end read as zeros.  LDS side:
-    // three stages (tile u in stage u % 3).  During step t tile t+2 is written: its stage was last
-    // read in step t-1, which every wave has left, and it is first read at the end of step t+1,
-    // after the barrier that closes step t+1 ... so ONE barrier per step is enough, and the
-    // fragments of the next 16-deep contraction step are always fetched before the MFMAs of the
-    // current one are issued, also across the tile boundary.
-    static_assert(D >= 3, "tile t+2 must have been requested before step t");
+        for (int j = 0; j < JA; ++j) la.load(j);
+        if (s < SB - 1) {
+            begin_b(s, s);
 #pragma unroll
-    for (int s = 0; s < D; ++s) issue(s, s);
-    store_lds(0, 0, 0);
-    store_lds(1, 1, 1);
-    __syncthreads();
-    Frags cur, nxt;
-    load_frags(cur, 0, 0);
-    const int groups = (num_tiles + D - 1) / D;
-    int st_cur = 0;  // stage of tile t
-    for (int grp = 0; grp < groups; ++grp) {
-#pragma unroll
-        for (int s = 0; s < D; ++s) {
-            const int t = grp * D + s;
-            const int st_next = st_cur == 2 ? 0 : st_cur + 1, st_write = st_next == 2 ? 0 : st_next + 1;
-            issue(s, t + D);
-#pragma unroll
-            for (int ks = 0; ks < KS; ++ks) {
-                if (ks == KS - 1)
-                    load_frags(nxt, st_next, 0);
-                else
-                    load_frags(nxt, st_cur, ks + 1);
-                multiply(cur);  // tiles past the end are all zeros: no branch, the step stays one basic block
-                cur = nxt;
-                // Tile t+2 goes to LDS during the second contraction step: its global loads (issued
-                // one tile step earlier) get most of this step as extra time to arrive.
-                if (ks == 1) store_lds((s + 2) % D, st_write, t + 2);
-            }
-            __builtin_amdgcn_iglp_opt(0);  // ask the scheduler to interleave LDS / global traffic with the MFMAs
-            __syncthreads();
-            st_cur = st_next;
+            for (int j = 0; j < JB; ++j) lb.load(j);
         }
     }
+    wait_for_loads<(SA - 2) * JA + (SB - 2) * JB>();
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < FRAGS; ++i) read(f[0], 0, 0, 0, i);
+    begin_b(SB - 1, SB - 1), begin_a(SA - 1, SA - 1);
+#pragma unroll
+    for (int i = 0; i < SP; ++i) load(i);
+    int sa = 0, sb = 0;
+    for (int t = 0; t < steps; ++t) {
+        const int next_a = sa == SA - 1 ? 0 : sa + 1, next_b = sb == SB - 1 ? 0 : sb + 1;
+#pragma unroll
+        for (int ks = 0; ks < KS - 1; ++ks) sixteen(f[ks & 1], f[(ks + 1) & 1], sa, sb, ks + 1, (ks + 1) * SP);
+        wait_for_loads<OUTSTANDING>();
+        __syncthreads();
+        begin_b(t + SB, sb), begin_a(t + SA, sa);
+        sixteen(f[1], f[0], next_a, next_b, 0, 0);  // (past the end: zeros, not used)
+        sa = next_a, sb = next_b;
+    }
+    wait_for_loads<0>();
+    __syncthreads();  // LDS is free
 
-    __syncthreads();  // all fragment reads of the main loop are done; LDS is free
     // Two wave groups that split the contraction each end up owning half of the 32x32 tiles of
     // their (identical) wave tile: a group parks the tiles the other one owns in LDS, 16 bytes per
     // lane and run with consecutive lanes consecutive, in rounds that fit the LDS, and adds what
     // the other group parked for it.  Both groups then write their halves.
-    static_assert(WAVES_K <= 2, "the cross-group sum is written for two groups");
-    constexpr int P = T::TM * T::TN;  // tiles per wave, numbered a * TN + b
-    constexpr int OWN = P / WAVES_K;  // group kg owns tiles kg*OWN .. kg*OWN + OWN - 1
-    if constexpr (WAVES_K == 2) {
+    constexpr int P = TM * TN;       // tiles per wave, numbered a * TN + b
+    constexpr int OWN = P / S::WK;  // group kg owns tiles kg*OWN .. kg*OWN + OWN - 1
+    if constexpr (S::WK == 2) {
         static_assert(P % 2 == 0, "an even number of tiles per wave");
-        constexpr int CH_MAX = T::LDS_BYTES / (64 * T::THREADS);  // tiles per thread and round that fit
+        constexpr int CH_MAX = S::LDS_BYTES / (64 * S::THREADS);  // tiles per thread and round that fit
         static_assert(CH_MAX >= 1, "one tile per thread fits in LDS");
         constexpr int CH = OWN < CH_MAX ? OWN : CH_MAX;
         float4 *park = reinterpret_cast<float4 *>(lds);
-        constexpr int GROUP_THREADS = T::THREADS / 2;
+        constexpr int GROUP_THREADS = S::THREADS / 2;
         const int partner = kg == 0 ? tid + GROUP_THREADS : tid - GROUP_THREADS;
-        // `first` is a literal at every call, so all accumulator indices are static after unrolling.
-        auto park_tiles = [&](auto first, int c0) {
+        // `from` is a literal at every call, so all accumulator indices are static after unrolling.
+        auto park_tiles = [&](auto from, int c0) {
 #pragma unroll
             for (int c = 0; c < CH; ++c) {
-                const int p = decltype(first)::value + c0 + c;
+                const int p = decltype(from)::value + c0 + c;
                 if (c0 + c < OWN) {
 #pragma unroll
                     for (int q = 0; q < 4; ++q)
-                        park[(c * 4 + q) * T::THREADS + tid] =
-                            make_float4(acc[p / T::TN][p % T::TN][4 * q], acc[p / T::TN][p % T::TN][4 * q + 1],
-                                        acc[p / T::TN][p % T::TN][4 * q + 2], acc[p / T::TN][p % T::TN][4 * q + 3]);
+                        park[(c * 4 + q) * S::THREADS + tid] =
+                            make_float4(acc[p / TN][p % TN][4 * q], acc[p / TN][p % TN][4 * q + 1], acc[p / TN][p % TN][4 * q + 2],
+                                        acc[p / TN][p % TN][4 * q + 3]);
                 }
             }
         };
-        auto add_tiles = [&](auto first, int c0) {
+        auto add_tiles = [&](auto from, int c0) {
 #pragma unroll
             for (int c = 0; c < CH; ++c) {
-                const int p = decltype(first)::value + c0 + c;
+                const int p = decltype(from)::value + c0 + c;
                 if (c0 + c < OWN) {
 #pragma unroll
                     for (int q = 0; q < 4; ++q) {
-                        const float4 pv = park[(c * 4 + q) * T::THREADS + partner];
-                        acc[p / T::TN][p % T::TN][4 * q] += pv.x, acc[p / T::TN][p % T::TN][4 * q + 1] += pv.y;
-                        acc[p / T::TN][p % T::TN][4 * q + 2] += pv.z, acc[p / T::TN][p % T::TN][4 * q + 3] += pv.w;
+                        const float4 pv = park[(c * 4 + q) * S::THREADS + partner];
+                        acc[p / TN][p % TN][4 * q] += pv.x, acc[p / TN][p % TN][4 * q + 1] += pv.y;
+                        acc[p / TN][p % TN][4 * q + 2] += pv.z, acc[p / TN][p % TN][4 * q + 3] += pv.w;
                     }
                 }
             }
@@ -532,10 +524,10 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &g, bf16_t *lds, int64_
         // zeros, so they add nothing.  Per-lane sums, wave reduction, then the waves' sums in fp64.
         float sq = 0.0f;
 #pragma unroll
-        for (int a = 0; a < T::TM; ++a)
+        for (int a = 0; a < TM; ++a)
 #pragma unroll
-            for (int b = 0; b < T::TN; ++b) {
-                if (WAVES_K > 1 && (a * T::TN + b) / OWN != kg) continue;  // the other group's tiles
+            for (int b = 0; b < TN; ++b) {
+                if (S::WK > 1 && (a * TN + b) / OWN != kg) continue;  // the other group's tiles
 #pragma unroll
                 for (int v = 0; v < 16; ++v) sq += acc[a][b][v] * acc[a][b][v];
             }
@@ -547,14 +539,13 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &g, bf16_t *lds, int64_
         if (tid == 0) {
             double t = 0.0;
 #pragma unroll
-            for (int w = 0; w < T::THREADS / 64; ++w) t += red[w];
+            for (int w = 0; w < S::WAVES; ++w) t += red[w];
             reinterpret_cast<double *>(g.C)[block] = t;
         }
     } else {
-        static_assert(T::THREADS / 64 * kStripBytes <= T::LDS_BYTES, "staging area fits in LDS");
-        char *stage = reinterpret_cast<char *>(lds) + wave * kStripBytes;
-        write_tile<true, AMODE == A_KCONTIG && BMODE == B_KCONTIG, AMODE == A_MCONTIG, T::TM, T::TN, WAVES_K>(g, acc, stage, m0, n0, wm, wn,
-                                                                                                           kg, lane);
+        static_assert(S::WAVES * kStripBytes <= S::LDS_BYTES, "staging area fits in LDS");
+        char *strip = reinterpret_cast<char *>(lds) + wave * kStripBytes;
+        write_tile<true, AMODE == A_KCONTIG && BMODE == B_KCONTIG, AMODE == A_MCONTIG, TM, TN, S::WK>(g, acc, strip, m0, n0, wm, wn, kg, lane);
     }
 }
 
@@ -567,43 +558,19 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &g, bf16_t *lds, int64_
 // eight partial tiles meet once, in LDS, in wave order.
 // 24 x 768 -> 3072: kernel 8.3 us with 64 x 64 tiles and a barrier every 32 elements, call 9.5 -> 5.2 us.
 constexpr int kFewThreads = 512;
-template <int E>
 struct FewTile {
-    static constexpr int BK = 64;                   // contraction elements per step of a wave
-    static constexpr int T = E / 32;                // 32 x 32 MFMA tiles per side
+    static constexpr int E = 32, BK = 64;           // edge of the tile; contraction elements per step of a wave
     static constexpr int LOADS = E * BK / 8 / 64;   // 16-byte loads per lane, operand and step
     static constexpr int PATCH = BK * E;            // elements of a wave's piece of one operand
     static constexpr int LDS_BYTES = 8 * 2 * PATCH * 2;
     static_assert(LDS_BYTES >= 8 * E * E * 4, "room for the partial tiles");
 };
-constexpr int64_t kFewSingle = 8 * FewTile<64>::BK;  // the longest contraction that is one step of every wave
+constexpr int64_t kFewSingle = 8 * FewTile::BK;  // the longest contraction that is one step of every wave
 
-// Where element (k, c) of a row-indexed operand sits in its piece of LDS: rows of E elements; with 128-byte
-// rows the halves of every second pair of rows change places, so that the four rows of a transposing read
-// fall on different banks.
-template <int E>
-__device__ __forceinline__ int few_at(int k, int c) {
-    return k * E + (E == 64 ? c ^ ((k & 2) << 4) : c);
-}
-template <int E>
-__device__ __forceinline__ bf16x8_t few_frag_transposed(const bf16_t *patch, int col0, int kk0, int lane) {
-    const int blk = lane >> 4, i = lane & 15;  // (see frag_transposed)
-    const bf16_t *p = patch + few_at<E>(kk0 + ((blk >> 1) << 3) + (i >> 2), col0 + ((blk & 1) << 4) + ((i & 3) << 2));
-    typedef __attribute__((address_space(3))) s16x4_t *lds_ptr_t;
-    const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr_t)(p));
-    const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr_t)(p + 4 * E));  // (row k + 4: same bit 1)
-    union {
-        s16x8_t s;
-        bf16x8_t v;
-    } out;
-    out.s = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-    return out.v;
-}
-
-template <int E, int AMODE, int BMODE, bool SINGLE>
+template <int AMODE, int BMODE, bool SINGLE>
 __device__ __forceinline__ void few_tile(const GemmArgs &g, unsigned char *lds, int64_t block, int64_t blocks) {
-    typedef FewTile<E> F;
-    constexpr int BK = F::BK, T = F::T, L = F::LOADS;
+    typedef FewTile F;
+    constexpr int E = F::E, BK = F::BK, L = F::LOADS;
     constexpr bool A_K = AMODE == A_KCONTIG, B_K = BMODE == B_KCONTIG;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int64_t tiles_m = (g.M + E - 1) / E;
@@ -631,7 +598,7 @@ __device__ __forceinline__ void few_tile(const GemmArgs &g, unsigned char *lds, 
 #pragma unroll
     for (int u = 0; u < L; ++u) {
         const int rk = 8 * u + kr, rn = 64 / CPR * u + nr;
-        const int at_k = rk * BK + kchunk_pos<BK>(rk, lane & 7) * 8, at_n = few_at<E>(rn, nc);
+        const int at_k = rk * BK + kchunk_pos<BK>(rk, lane & 7) * 8, at_n = rn * E + nc;
         a_off[u] = A_K ? (m0 + rk < g.M ? (uint32_t)((rk * g.lda + kc) * 2) : OOB) : (m0 + nc < g.M ? (uint32_t)((rn * g.lda + nc) * 2) : OOB);
         b_off[u] = B_K ? (n0 + rk < g.N ? (uint32_t)((rk * g.ldb + kc) * 2) : OOB) : (n0 + nc < g.N ? (uint32_t)((rn * g.ldb + nc) * 2) : OOB);
         a_at[u] = A_K ? at_k : at_n, b_at[u] = B_K ? at_k : at_n;
@@ -658,13 +625,9 @@ __device__ __forceinline__ void few_tile(const GemmArgs &g, unsigned char *lds, 
             q.b[u] = __builtin_amdgcn_raw_buffer_load_b128(rb, !B_K || ok_k ? b_off[u] : OOB, 0, 0);
         }
     };
-    f32x16_t acc[T][T];
+    f32x16_t acc;
 #pragma unroll
-    for (int a = 0; a < T; ++a)
-#pragma unroll
-        for (int b = 0; b < T; ++b)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[a][b][v] = 0.0f;
+    for (int v = 0; v < 16; ++v) acc[v] = 0.0f;
     auto wave_sync = [] {  // orders a wave's own LDS accesses (LDS serves a wave's instructions in order)
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
@@ -680,16 +643,9 @@ __device__ __forceinline__ void few_tile(const GemmArgs &g, unsigned char *lds, 
         wave_sync();
 #pragma unroll
         for (int u = 0; u < BK / 16; ++u) {
-            bf16x8_t a[T], b[T];
-#pragma unroll
-            for (int t = 0; t < T; ++t) {
-                a[t] = A_K ? frag_kcontig<BK>(patch_a, 32 * t, 16 * u, lane) : few_frag_transposed<E>(patch_a, 32 * t, 16 * u, lane);
-                b[t] = B_K ? frag_kcontig<BK>(patch_b, 32 * t, 16 * u, lane) : few_frag_transposed<E>(patch_b, 32 * t, 16 * u, lane);
-            }
-#pragma unroll
-            for (int x = 0; x < T; ++x)
-#pragma unroll
-                for (int y = 0; y < T; ++y) acc[x][y] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[x], b[y], acc[x][y], 0, 0, 0);
+            const bf16x8_t a = A_K ? frag_kcontig<BK>(patch_a, 0, 16 * u, lane) : frag_transposed(patch_a, E, 0, 16 * u, lane);
+            const bf16x8_t b = B_K ? frag_kcontig<BK>(patch_b, 0, 16 * u, lane) : frag_transposed(patch_b, E, 0, 16 * u, lane);
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc, 0, 0, 0);
         }
     };
     if constexpr (SINGLE) {  // a contraction of at most 8 * BK: nothing to prefetch
@@ -711,234 +667,49 @@ __device__ __forceinline__ void few_tile(const GemmArgs &g, unsigned char *lds, 
     // Register v of lane l is C(8*(v/4) + 4*(l/32) + v%4, l % 32) of a 32 x 32 tile.
     float *red = reinterpret_cast<float *>(lds);
 #pragma unroll
-    for (int x = 0; x < T; ++x)
-#pragma unroll
-        for (int y = 0; y < T; ++y)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) red[((wave * T + x) * T + y) * 1024 + v * 64 + lane] = acc[x][y][v];
+    for (int v = 0; v < 16; ++v) red[wave * 1024 + v * 64 + lane] = acc[v];
     __syncthreads();
     // A thread finishes two neighbouring columns of rows tid / (E/2), ...
-    constexpr int PAIRS = E / 2, ROWS = kFewThreads / PAIRS;
-    const int c = tid % PAIRS * 2;
+    const int r = tid / (E / 2), c = tid % (E / 2) * 2;
     const int64_t col = n0 + c;
     float b0 = 0.0f, b1 = 0.0f;
     if (g.bias != nullptr && col < g.N) {
         const uint32_t o = *reinterpret_cast<const uint32_t *>(g.bias + col);
         b0 = __uint_as_float(o << 16), b1 = __uint_as_float(o & 0xFFFF0000u);
     }
+    const int at = ((r >> 3) * 4 + (r & 3)) * 64 + ((r >> 2) & 1) * 32 + c;
+    float x0 = 0.0f, x1 = 0.0f;
 #pragma unroll
-    for (int i = 0; i < E / ROWS; ++i) {
-        const int r = tid / PAIRS + i * ROWS, rr = r & 31;
-        const int at = ((r >> 5) * T + (c >> 5)) * 1024 + ((rr >> 3) * 4 + (rr & 3)) * 64 + ((rr >> 2) & 1) * 32 + (c & 31);
-        float x0 = 0.0f, x1 = 0.0f;
-#pragma unroll
-        for (int w = 0; w < 8; ++w) {
-            const float2 p = *reinterpret_cast<const float2 *>(red + w * T * T * 1024 + at);
-            x0 += p.x, x1 += p.y;
-        }
-        const int64_t row = m0 + r;
-        if (row >= g.M || col >= g.N) continue;  // N is a multiple of 8
-        bf16_t *out = reinterpret_cast<bf16_t *>(g.C) + row * g.ldc + col;
-        x0 *= g.alpha, x1 *= g.alpha;
-        if (g.accumulate) {
-            const uint32_t o = *reinterpret_cast<const uint32_t *>(out);
-            x0 += __uint_as_float(o << 16), x1 += __uint_as_float(o & 0xFFFF0000u);
-        }
-        if (g.bias != nullptr) x0 += b0, x1 += b1;
-        union {
-            bf16x2_t h;
-            uint32_t u;
-        } o;
-        o.h = __builtin_convertvector((f32x2_t){x0, x1}, bf16x2_t);  // nearest even
-        *reinterpret_cast<uint32_t *>(out) = o.u;
+    for (int w = 0; w < 8; ++w) {
+        const float2 p = *reinterpret_cast<const float2 *>(red + w * 1024 + at);
+        x0 += p.x, x1 += p.y;
     }
-}
-
-template <int E, int AMODE, int BMODE, bool SINGLE>
-__global__ void __launch_bounds__(kFewThreads) few_tile_kernel(GemmArgs g) {
-    __shared__ __attribute__((aligned(16))) unsigned char lds[FewTile<E>::LDS_BYTES];
-    few_tile<E, AMODE, BMODE, SINGLE>(g, lds, blockIdx.x, gridDim.x);
-}
-
-// ---------------------------------------------------------------------------------------------
-// The plain products on 256 x 256 tiles (Y = X W^T, dX = dY W at the sizes that fill the chip).  Memory ->
-// LDS without registers in between (buffer_load ... lds, 16 bytes per lane, a wave's 64 lanes = 1 KB of
-// consecutive LDS), so a step can be 64 contraction elements deep: whole 128-byte lines of K-contiguous
-// rows.  Two LDS stages of 64 KB; the loads of step t+1 are issued when step t begins and waited for
-// when it ends.  LDS is laid out by the load, so what keeps bank conflicts away is which chunk a lane asks
-// for: rows of 64 elements hold chunk c at c ^ (row / 2) % 8 (kchunk_pos), rows of 256 columns hold
-// chunk c at c ^ 4 * (row % 4), so that the four rows of a transposing read fall on different 64 bytes.
-// Of a dispatch's MFMA cycles 55 % are busy (dX 16384 x 4096 -> 1024, one tile per compute unit) and 45 % (Y 1024 ->
-// 4096, four); the rest is the first load, the write of the tile and waves that wait
-// (profiles/mfma_valu_lds_counters.txt).  Against loads through registers into padded tiles of 32 contraction
-// elements (us): Y 16384 x 1024 -> 4096 167 -> 152 (0.91 PFLOP/s), 16384 x 4096 -> 1024 127 -> 114 (1.2), 8192 x
-// 2048 -> 2048 67 -> 60, dX 16384 x 4096 -> 1024 118 -> 112.  Four waves of 128 x 128 outputs read a third less LDS
-// but hide less: 172 and 126.
-struct DmaTile {
-    static constexpr int BM = 256, BN = 256, BK = 64, WM = 2, WN = 4, THREADS = 64 * WM * WN;
-    static constexpr int TM = BM / WM / 32, TN = BN / WN / 32;
-    static constexpr int A_ELEMS = BM * BK, STAGE_ELEMS = (BM + BN) * BK, LDS_BYTES = 2 * STAGE_ELEMS * 2;
-};
-
-// One wave's load of 1 KB into LDS from byte `to` on, 16 bytes from `off` + `soff` per lane.  The compiler does
-// not see that it writes LDS (it would wait for it before every LDS read): the explicit wait and barrier at the
-// end of a step order them.
-__device__ __forceinline__ void load_to_lds(__amdgpu_buffer_rsrc_t rsrc, uint32_t to, uint32_t off, uint32_t soff) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(to), "v"(off), "s"(rsrc), "s"(soff) : "m0");
-}
-// (see frag_transposed) from rows of BN columns whose chunks are placed as above
-template <int BN>
-__device__ __forceinline__ bf16x8_t dma_frag_transposed(const bf16_t *tile, int col0, int kk0, int lane) {
-    const int blk = lane >> 4, i = lane & 15, k = kk0 + ((blk >> 1) << 3) + (i >> 2), col = col0 + ((blk & 1) << 4) + ((i & 3) << 2);
-    const bf16_t *p = tile + k * BN + (((col >> 3) ^ ((k & 3) << 2)) << 3) + (col & 7);
-    typedef __attribute__((address_space(3))) s16x4_t *lds_ptr_t;
-    const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr_t)(p));
-    const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr_t)(p + 4 * BN));  // (row k + 4: same k % 4)
+    const int64_t row = m0 + r;
+    if (row >= g.M || col >= g.N) return;  // N is a multiple of 8
+    bf16_t *out = reinterpret_cast<bf16_t *>(g.C) + row * g.ldc + col;
+    x0 *= g.alpha, x1 *= g.alpha;
+    if (g.accumulate) {
+        const uint32_t o = *reinterpret_cast<const uint32_t *>(out);
+        x0 += __uint_as_float(o << 16), x1 += __uint_as_float(o & 0xFFFF0000u);
+    }
+    if (g.bias != nullptr) x0 += b0, x1 += b1;
     union {
-        s16x8_t s;
-        bf16x8_t v;
-    } out;
-    out.s = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-    return out.v;
+        bf16x2_t h;
+        uint32_t u;
+    } o;
+    o.h = __builtin_convertvector((f32x2_t){x0, x1}, bf16x2_t);  // nearest even
+    *reinterpret_cast<uint32_t *>(out) = o.u;
 }
 
-template <int BMODE>
-__device__ __forceinline__ void gemm_tile_dma(const GemmArgs &g, bf16_t *lds, int64_t block, int64_t blocks) {
-    typedef DmaTile T;
-    constexpr int BM = T::BM, BN = T::BN, BK = T::BK;
-    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave / T::WN, wn = wave % T::WN;
-    const int64_t tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN;  // (tile order: see gemm_tile)
-    int64_t tile;
-    {
-        const int64_t per = blocks / 8, rem = blocks % 8, x = block % 8, r = block / 8;
-        tile = x * per + (x < rem ? x : rem) + r;
-    }
-    constexpr int64_t GROUP_M = 8;
-    const int64_t band = tile / (GROUP_M * tiles_n), in_band = tile % (GROUP_M * tiles_n);
-    const int64_t band_rows = min(GROUP_M, tiles_m - band * GROUP_M);
-    const int64_t m0 = (band * GROUP_M + in_band % band_rows) * BM, n0 = (in_band / band_rows) * BN;
-    const int kk = (int)g.K, steps = (kk + BK - 1) / BK;
-    const int stagger = (int)((tile / 8) % steps);
-
-    constexpr uint32_t OOB = 0x80000000u;
-    auto rows_rsrc = [](const bf16_t *base, int64_t ld, int64_t rows) {
-        return __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(base), (short)0,
-                                                 __builtin_amdgcn_readfirstlane((int)((rows > 0 ? rows : 0) * ld * 2)), 0x00020000);
-    };
-    // Load j of a wave fills 1 KB: eight rows of a K-contiguous operand, two of a row-indexed one.
-    constexpr int J = BM * BK * 2 / 1024 / (T::THREADS / 64);  // loads per wave, operand and step
-    uint32_t a_off[J], b_off[J];
-    int a_kk[J], b_kk[J];
-#pragma unroll
-    for (int j = 0; j < J; ++j) {
-        const int row = (wave * J + j) * 8 + (lane >> 3), chunk = kchunk_pos<BK>(row, lane & 7);
-        a_kk[j] = chunk * 8;
-        a_off[j] = m0 + row < g.M ? (uint32_t)((row * g.lda + chunk * 8) * 2) : OOB;
-        if constexpr (BMODE == B_KCONTIG) {
-            b_kk[j] = chunk * 8;
-            b_off[j] = n0 + row < g.N ? (uint32_t)((row * g.ldb + chunk * 8) * 2) : OOB;
-        } else {
-            const int k = (wave * J + j) * 2 + (lane >> 5), col = ((lane & 31) ^ ((k & 3) << 2)) * 8;
-            b_kk[j] = k;
-            b_off[j] = n0 + col < g.N ? (uint32_t)((k * g.ldb + n0 + col) * 2) : OOB;
-        }
-    }
-    const __amdgpu_buffer_rsrc_t rsrc_a = rows_rsrc(g.A + m0 * g.lda, g.lda, min((int64_t)BM, g.M - m0));
-    __amdgpu_buffer_rsrc_t rsrc_b_fixed;
-    if constexpr (BMODE == B_KCONTIG) rsrc_b_fixed = rows_rsrc(g.B + n0 * g.ldb, g.ldb, min((int64_t)BN, g.N - n0));
-    typedef __attribute__((address_space(3))) bf16_t *lds_ptr_t;
-    const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_ptr_t)lds;
-    auto issue = [&](int t, int stage) {
-        const int k0 = (t + stagger >= steps ? t + stagger - steps : t + stagger) * BK, left = kk - k0;
-        const uint32_t to = lds0 + (uint32_t)(stage * T::STAGE_ELEMS * 2 + wave * J * 1024);
-        __amdgpu_buffer_rsrc_t rsrc_b;
-        if constexpr (BMODE == B_KCONTIG)
-            rsrc_b = rsrc_b_fixed;
-        else
-            rsrc_b = rows_rsrc(g.B + (int64_t)k0 * g.ldb, g.ldb, min(BK, left));
-#pragma unroll
-        for (int j = 0; j < J; ++j) {
-            load_to_lds(rsrc_a, to + j * 1024, a_kk[j] < left ? a_off[j] : OOB, (uint32_t)k0 * 2);
-            load_to_lds(rsrc_b, to + T::A_ELEMS * 2 + j * 1024, BMODE == B_NCONTIG || b_kk[j] < left ? b_off[j] : OOB,
-                        BMODE == B_KCONTIG ? (uint32_t)k0 * 2 : 0u);
-        }
-    };
-
-    f32x16_t acc[T::TM][T::TN];
-#pragma unroll
-    for (int a = 0; a < T::TM; ++a)
-#pragma unroll
-        for (int b = 0; b < T::TN; ++b)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[a][b][v] = 0.0f;
-    struct Frags {
-        bf16x8_t a[T::TM], b[T::TN];
-    };
-    auto load_frags = [&](Frags &f, int stage, int ks) {
-        const bf16_t *As = lds + stage * T::STAGE_ELEMS, *Bs = As + T::A_ELEMS;
-#pragma unroll
-        for (int b = 0; b < T::TN; ++b) {
-            const int col0 = wn * (BN / T::WN) + b * 32;
-            if constexpr (BMODE == B_KCONTIG) {
-                f.b[b] = frag_kcontig<BK>(Bs, col0, ks * 16, lane);
-            } else {
-                f.b[b] = dma_frag_transposed<BN>(Bs, col0, ks * 16, lane);
-            }
-        }
-#pragma unroll
-        for (int a = 0; a < T::TM; ++a) f.a[a] = frag_kcontig<BK>(As, wm * (BM / T::WM) + a * 32, ks * 16, lane);
-    };
-    auto multiply = [&](const Frags &f) {
-#pragma unroll
-        for (int a = 0; a < T::TM; ++a)
-#pragma unroll
-            for (int b = 0; b < T::TN; ++b)
-                acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.b[b], f.a[a], acc[a][b], 0, 0, 0);
-        // One LDS read behind each MFMA (or pair): left to itself the compiler bunches them in front of
-        // their use and the MFMAs wait (16384 x 4096 -> 1024: 120 -> 114 us).
-        constexpr int READS = T::TM + T::TN * (BMODE == B_KCONTIG ? 1 : 2), MFMAS = T::TM * T::TN;
-#pragma unroll
-        for (int i = 0; i < READS; ++i) {
-            __builtin_amdgcn_sched_group_barrier(0x008, MFMAS / READS, 0);
-            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-        }
-        if constexpr (MFMAS % READS > 0) __builtin_amdgcn_sched_group_barrier(0x008, MFMAS % READS, 0);
-    };
-    // The one barrier of a step stands in front of its last quarter: by then every wave has that quarter's
-    // fragments in registers, so the stage can be overwritten (the loads of step t+2 start here and have a
-    // whole step to arrive), and the data of step t+1 has been waited for, so its first fragments are read
-    // under the MFMAs of the last quarter: no step begins by waiting for LDS.
-    auto meet = [] {
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        __syncthreads();
-    };
-    constexpr int KS = BK / 16;
-    static_assert(KS % 2 == 0, "the first fragments of a step are always in f[0]");
-    Frags f[2];
-    issue(0, 0);
-    meet();
-    load_frags(f[0], 0, 0);
-    if (steps > 1) issue(1, 1);
-    for (int t = 0; t < steps; ++t) {
-        const int stage = t & 1;
-#pragma unroll
-        for (int ks = 0; ks < KS - 1; ++ks) {
-            load_frags(f[(ks + 1) & 1], stage, ks + 1);
-            multiply(f[ks & 1]);
-        }
-        meet();
-        if (t + 2 < steps) issue(t + 2, stage);
-        load_frags(f[0], stage ^ 1, 0);  // (past the end: what the stage holds, not used)
-        multiply(f[1]);
-    }
-    __syncthreads();
-    write_tile<true, BMODE == B_KCONTIG, false, T::TM, T::TN, 1>(g, acc, reinterpret_cast<char *>(lds) + wave * kStripBytes, m0, n0, wm, wn, 0,
-                                                                lane);
+template <int AMODE, int BMODE, bool SINGLE>
+__global__ void __launch_bounds__(kFewThreads) few_tile_kernel(GemmArgs g) {
+    __shared__ __attribute__((aligned(16))) unsigned char lds[FewTile::LDS_BYTES];
+    few_tile<AMODE, BMODE, SINGLE>(g, lds, blockIdx.x, gridDim.x);
 }
 
 // ---------------------------------------------------------------------------------------------
-// Sketch products: S^T (generated by the work-group into LDS) times A [token][column], in the pipeline of
-// gemm_tile_dma: steps of 64 tokens, two stages, one barrier, A loaded straight into LDS (7 % faster than through
+// Sketch products: S^T (generated by the work-group into LDS) times A [token][column], in a pipeline like that of
+// gemm_tile: steps of 64 tokens, two stages, one barrier, A loaded straight into LDS (7 % faster than through
 // registers into three stages of 32 tokens).  What bounds them is how far MFMAs and generator share a step: with
 // 128 x 512 tiles at 16384 x 4096, k = 1638 the MFMAs of a step alone take 161 us per launch, without the generator
 // it is 217, complete 272 (Rademacher 138, 173, 215; one run, profiles/sketch_products.txt).  The generator's
@@ -977,7 +748,7 @@ __device__ __forceinline__ void sketch_tile(const GemmArgs &g, bf16_t *lds, int6
     uint32_t b_off[T::LOADS];
 #pragma unroll
     for (int j = 0; j < T::LOADS; ++j) {
-        const int c = (wave * T::LOADS + j) * 64 + lane, row = c / CPR, col = (c % CPR ^ ((row & 3) << 2)) * 8;
+        const int c = (wave * T::LOADS + j) * 64 + lane, row = c / CPR, col = col_chunk<BN>(row, c % CPR) * 8;
         b_off[j] = n0 + col < g.N ? (uint32_t)((row * g.ldb + n0 + col) * 2) : OOB;
     }
     typedef __attribute__((address_space(3))) bf16_t *lds_ptr_t;
@@ -1029,7 +800,7 @@ __device__ __forceinline__ void sketch_tile(const GemmArgs &g, bf16_t *lds, int6
     auto load_frags = [&](Frags &f, int stage, int ks) {
         const bf16_t *As = lds + stage * T::STAGE_ELEMS, *Bs = As + T::A_ELEMS;
 #pragma unroll
-        for (int b = 0; b < T::TN; ++b) f.b[b] = dma_frag_transposed<BN>(Bs, wn * (BN / T::WN) + b * 32, ks * 16, lane);
+        for (int b = 0; b < T::TN; ++b) f.b[b] = frag_columns<BN>(Bs, wn * (BN / T::WN) + b * 32, ks * 16, lane);
 #pragma unroll
         for (int a = 0; a < T::TM; ++a) f.a[a] = frag_kcontig<BK>(As, wm * (BM / T::WM) + a * 32, ks * 16, lane);
     };
@@ -1121,31 +892,10 @@ __global__ void __launch_bounds__(S::THREADS) sketch_kernel(GemmArgs g, int tile
     sketch_share<S, KIND>(g, lds, blockIdx.x, tiles);
 }
 
-// The plain product of a pass: 256 x 256 tiles through gemm_tile_dma, others through gemm_tile.
-template <typename S, int BMODE, int D>
-struct PlainOfPass {
-    static constexpr bool DMA = std::is_same<S, ShapeLarge>::value;
-    typedef Tile<S::BM, S::BN, S::BK, S::WM, S::WN, S::WK, A_KCONTIG, BMODE, OUT_BF16> T;
-    static constexpr int LDS_BYTES = DMA ? DmaTile::LDS_BYTES : T::LDS_BYTES;
-    static __device__ __forceinline__ void run(const GemmArgs &g, bf16_t *lds, int64_t block, int64_t blocks) {
-        if constexpr (DMA)
-            gemm_tile_dma<BMODE>(g, lds, block, blocks);
-        else
-            gemm_tile<S, A_KCONTIG, BMODE, OUT_BF16, D>(g, lds, block, blocks);
-    }
-};
-
-template <int BMODE>
-__global__ void __launch_bounds__(DmaTile::THREADS) gemm_dma_kernel(GemmArgs g) {
-    __shared__ __attribute__((aligned(1024))) bf16_t lds[DmaTile::LDS_BYTES / 2];
-    gemm_tile_dma<BMODE>(g, lds, blockIdx.x, gridDim.x);
-}
-
-template <typename S, int AMODE, int BMODE, int OUT, int D>
+template <typename S, int AMODE, int BMODE, int OUT>
 __global__ void __launch_bounds__(S::THREADS) gemm_mfma_kernel(GemmArgs g) {
-    typedef Tile<S::BM, S::BN, S::BK, S::WM, S::WN, S::WK, AMODE, BMODE, OUT> T;
-    __shared__ __attribute__((aligned(16))) bf16_t lds[T::STAGES * T::STAGE_ELEMS];
-    gemm_tile<S, AMODE, BMODE, OUT, D>(g, lds, blockIdx.x, gridDim.x);
+    __shared__ __attribute__((aligned(1024))) bf16_t lds[S::LDS_BYTES / 2];
+    gemm_tile<S, AMODE, BMODE, OUT>(g, lds, blockIdx.x, gridDim.x);
 }
 
 // Two independent products in one launch: `blocks_a` work-groups are the tiles of a plain product
@@ -1163,14 +913,13 @@ __global__ void __launch_bounds__(S::THREADS) gemm_mfma_kernel(GemmArgs g) {
 // product that fills the chip by itself) sketch work-groups, column blocks, plain tiles: the
 // column blocks then start on the compute units the sketch product leaves free, ahead of the
 // plain tiles, instead of competing with the last round of plain tiles for memory.
-template <typename SA, int BMODE_A, int DA, typename SB, int KIND>
+template <typename SA, int BMODE_A, typename SB, int KIND>
 __global__ void __launch_bounds__(SA::THREADS) gemm_pair_kernel(GemmArgs ga, GemmArgs gb, int blocks_a, int tiles_b,
                                                                  int sketch_blocks, int colsum_blocks, int sketch_first,
                                                                  ColsumArgs gc) {
-    typedef PlainOfPass<SA, BMODE_A, DA> PA;
     typedef SketchTile<SB> TB;
     static_assert(SA::THREADS == SB::THREADS, "both halves run with the same work-group size");
-    constexpr int BYTES = PA::LDS_BYTES > TB::LDS_BYTES ? PA::LDS_BYTES : TB::LDS_BYTES;
+    constexpr int BYTES = SA::LDS_BYTES > TB::LDS_BYTES ? SA::LDS_BYTES : TB::LDS_BYTES;
     static_assert(BYTES >= kColsumLdsFloats * 4, "room for the column sums");
     __shared__ __attribute__((aligned(1024))) bf16_t lds[BYTES / 2];
     const int b = (int)blockIdx.x;
@@ -1178,7 +927,7 @@ __global__ void __launch_bounds__(SA::THREADS) gemm_pair_kernel(GemmArgs ga, Gem
     const int i = sketch_first ? b : b - blocks_a;                       // index among the sketch work-groups
     const int c = sketch_first ? b - sketch_blocks : b - blocks_a - sketch_blocks;  // index among the column blocks
     if (a >= 0 && a < blocks_a)
-        PA::run(ga, lds, a, blocks_a);
+        gemm_tile<SA, A_KCONTIG, BMODE_A, OUT_BF16>(ga, lds, a, blocks_a);
     else if (i >= 0 && i < sketch_blocks)
         sketch_share<SB, KIND>(gb, lds, i, tiles_b);
     else
@@ -1189,13 +938,12 @@ __global__ void __launch_bounds__(SA::THREADS) gemm_pair_kernel(GemmArgs ga, Gem
 // dW, the others the column blocks of dY.  The two do not depend on each other; dW has few tiles
 // and a short contraction (k), so its launch leaves compute units idle and is over in a few
 // microseconds, most of them latency: the column sums, bound by memory, run beside it for free.
-template <typename S, int D>
+template <typename S>
 __global__ void __launch_bounds__(S::THREADS) dw_colsum_kernel(GemmArgs g, ColsumArgs c, int blocks_a) {
-    typedef Tile<S::BM, S::BN, S::BK, S::WM, S::WN, S::WK, A_MCONTIG, B_NCONTIG, OUT_BF16> T;
-    constexpr int ELEMS = T::STAGES * T::STAGE_ELEMS, MIN_ELEMS = kColsumLdsFloats * 2;
-    __shared__ __attribute__((aligned(16))) bf16_t lds[ELEMS > MIN_ELEMS ? ELEMS : MIN_ELEMS];
+    static_assert(S::LDS_BYTES >= kColsumLdsFloats * 4, "room for the column sums");
+    __shared__ __attribute__((aligned(1024))) bf16_t lds[S::LDS_BYTES / 2];
     if ((int)blockIdx.x < blocks_a)
-        gemm_tile<S, A_MCONTIG, B_NCONTIG, OUT_BF16, D>(g, lds, blockIdx.x, blocks_a);
+        gemm_tile<S, A_MCONTIG, B_NCONTIG, OUT_BF16>(g, lds, blockIdx.x, blocks_a);
     else
         colsum_body<bf16_t>(c, reinterpret_cast<float *>(lds), (int64_t)blockIdx.x - blocks_a, (int64_t)gridDim.x - blocks_a);
 }
@@ -1203,24 +951,23 @@ __global__ void __launch_bounds__(S::THREADS) dw_colsum_kernel(GemmArgs g, Colsu
 // |X^T dY|_F^2 per tile and the row norms of X and dY (variance monitors) in one launch: the product has
 // few tiles and a long contraction, so the row norms, bound by memory, run on the compute units it leaves
 // idle (or ahead of its last round) instead of in a pass of their own.
-template <typename S, int D>
+template <typename S>
 __global__ void __launch_bounds__(S::THREADS) xty_norms_kernel(GemmArgs g, RowNormArgs r, int tiles) {
-    typedef Tile<S::BM, S::BN, S::BK, S::WM, S::WN, S::WK, A_MCONTIG, B_NCONTIG, OUT_SUMSQ> T;
-    __shared__ __attribute__((aligned(16))) bf16_t lds[T::STAGES * T::STAGE_ELEMS];
+    __shared__ __attribute__((aligned(1024))) bf16_t lds[S::LDS_BYTES / 2];
     if ((int)blockIdx.x < tiles)
-        gemm_tile<S, A_MCONTIG, B_NCONTIG, OUT_SUMSQ, D>(g, lds, blockIdx.x, tiles);
+        gemm_tile<S, A_MCONTIG, B_NCONTIG, OUT_SUMSQ>(g, lds, blockIdx.x, tiles);
     else
         row_norms_body<bf16_t>(r, reinterpret_cast<double *>(lds), (int64_t)blockIdx.x - tiles, (int64_t)gridDim.x - tiles);
 }
 
-// The same where dW itself runs on few_tile.
-template <int E, bool SINGLE>
+// dW and db where dW runs on few_tile.
+template <bool SINGLE>
 __global__ void __launch_bounds__(kFewThreads) few_dw_colsum_kernel(GemmArgs g, ColsumArgs c, int blocks_a) {
-    constexpr int BYTES = FewTile<E>::LDS_BYTES;
+    constexpr int BYTES = FewTile::LDS_BYTES;
     static_assert(BYTES >= kColsumLdsFloats * 4, "room for the column sums");
     __shared__ __attribute__((aligned(16))) unsigned char lds[BYTES];
     if ((int)blockIdx.x < blocks_a)
-        few_tile<E, A_MCONTIG, B_NCONTIG, SINGLE>(g, lds, blockIdx.x, blocks_a);
+        few_tile<A_MCONTIG, B_NCONTIG, SINGLE>(g, lds, blockIdx.x, blocks_a);
     else
         colsum_body<bf16_t>(c, reinterpret_cast<float *>(lds), (int64_t)blockIdx.x - blocks_a, (int64_t)gridDim.x - blocks_a);
 }

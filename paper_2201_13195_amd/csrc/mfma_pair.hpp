@@ -6,15 +6,13 @@
 
 namespace rmm {
 
-// Tile shape a plain product runs with (Shape typedefs of mfma_kernels.hpp) and a sketch product's kernel.
-enum { GEMM_LARGE = 0, GEMM_SPLIT = 1, GEMM_MID = 2, GEMM_FEW = 3 };
+// Tile a plain product runs with (typedefs of mfma_kernels.hpp) and a sketch product's kernel.
+enum { GEMM_LARGE = 0, GEMM_WIDE = 1, GEMM_SPLIT = 2, GEMM_MID = 3, GEMM_FLAT = 4, GEMM_SMALL = 5, GEMM_FEW = 6 };
 enum { SK_NARROW = 0, SK_WIDE = 1, SK_WIDE64 = 2, SK_MID64 = 3, SK_MID = 4, SK_NARROW64 = 5 };
 
-// The plain product of a paired launch: 256 x 256 tiles (gemm_tile_dma, no depth) or 128 x 128 x 64 tiles with two wave
-// groups (depth 3 or 4, whichever pads the contraction less), and its number of tiles.
+// The plain product of a paired launch: its tile (GEMM_LARGE, GEMM_SPLIT or GEMM_MID) and number of tiles.
 struct PairPlain {
-    bool large;
-    int depth, tiles;
+    int cfg, tiles;
 };
 
 // One launch for a plain product (`ga`; nt: Y = X W^T, nn: dX = dY W) and a sketch product (`gb`, `tiles_b`
@@ -27,27 +25,26 @@ hipError_t launch_pair_nt(const PairPlain &plain, int sk_cfg, int kind, const Ge
                           int shares, hipStream_t stream, const ColsumArgs *gc = nullptr);
 hipError_t launch_pair_nn(const PairPlain &plain, int sk_cfg, int kind, const GemmArgs &ga, const GemmArgs &gb, int tiles_b,
                           int shares, hipStream_t stream, const ColsumArgs *gc = nullptr);
-// (one translation unit for each plain tile: large, split at depth 4, split at depth 3)
+// (one translation unit for each plain tile)
 #define RMM_PAIR_DECL(NAME)                                                                                               \
     hipError_t launch_pair_##NAME(int sk_cfg, int kind, const GemmArgs &ga, const GemmArgs &gb, int blocks_a, int tiles_b, \
                                   int shares, hipStream_t stream, const ColsumArgs *gc)
 RMM_PAIR_DECL(nt_large);
-RMM_PAIR_DECL(nt_split4);
-RMM_PAIR_DECL(nt_split3);
+RMM_PAIR_DECL(nt_split);
+RMM_PAIR_DECL(nt_mid);
 RMM_PAIR_DECL(nn_large);
-RMM_PAIR_DECL(nn_split4);
-RMM_PAIR_DECL(nn_split3);
+RMM_PAIR_DECL(nn_split);
+RMM_PAIR_DECL(nn_mid);
 
 // The same for the SORS sketch kind (mfma_pair_sors.hip): `gs` describes the sketch product, whose
-// strips go two to a work-group; cfg_a is GEMM_LARGE (depth 3) or GEMM_SPLIT (depth 4), row_indexed_b
-// says whether the plain product is dX = dY W (true) or Y = X W^T (false); `chunks` chunks of 2048 tokens;
-// sors_first puts the strips' work-groups at the front of the grid instead of the back.
+// strips go two to a work-group; row_indexed_b says whether the plain product is dX = dY W (true) or Y = X W^T (false);
+// `chunks` chunks of 2048 tokens; sors_first puts the strips' work-groups at the front of the grid instead of the back.
 struct SorsArgs;
-hipError_t launch_pair_sors(int cfg_a, bool row_indexed_b, const GemmArgs &ga, const SorsArgs &gs, int blocks_a, int chunks,
+hipError_t launch_pair_sors(const PairPlain &plain, bool row_indexed_b, const GemmArgs &ga, const SorsArgs &gs, int chunks,
                             bool sors_first, hipStream_t stream);
 
 // Shared body of the six launch_pair_{nt,nn}_*.
-template <typename SA, int BMODE_A, int DA>
+template <typename SA, int BMODE_A>
 hipError_t launch_pair_impl(int sk_cfg, int kind, const GemmArgs &ga, const GemmArgs &gb, int blocks_a, int tiles_b,
                             int shares, hipStream_t stream, const ColsumArgs *gc) {
     const int sketch_blocks = shares;
@@ -58,11 +55,11 @@ hipError_t launch_pair_impl(int sk_cfg, int kind, const GemmArgs &ga, const Gemm
     const int key = sk_cfg * 2 + (kind != 0 ? 1 : 0);
 #define RMM_PAIR_CASE(CFG, SHAPE)                                                                                      \
     case CFG * 2:                                                                                                      \
-        gemm_pair_kernel<SA, BMODE_A, DA, SHAPE, 0>                                                                   \
+        gemm_pair_kernel<SA, BMODE_A, SHAPE, 0>                                                                   \
             <<<grid, SA::THREADS, 0, stream>>>(ga, gb, blocks_a, tiles_b, sketch_blocks, col_blocks, sketch_first, c); \
         break;                                                                                                         \
     case CFG * 2 + 1:                                                                                                  \
-        gemm_pair_kernel<SA, BMODE_A, DA, SHAPE, 1>                                                                   \
+        gemm_pair_kernel<SA, BMODE_A, SHAPE, 1>                                                                   \
             <<<grid, SA::THREADS, 0, stream>>>(ga, gb, blocks_a, tiles_b, sketch_blocks, col_blocks, sketch_first, c); \
         break;
     switch (key) {

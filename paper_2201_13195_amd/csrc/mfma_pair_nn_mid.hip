@@ -1,0 +1,10 @@
+// Paired-launch kernels (see mfma_pair.hpp): launch_pair_nn_mid.
+#include "mfma_pair.hpp"
+
+namespace rmm {
+
+RMM_PAIR_DECL(nn_mid) {
+    return launch_pair_impl<ShapeMid, B_NCONTIG>(sk_cfg, kind, ga, gb, blocks_a, tiles_b, shares, stream, gc);
+}
+
+}  // namespace rmm

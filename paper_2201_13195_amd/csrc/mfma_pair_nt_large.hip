@@ -4,12 +4,12 @@
 namespace rmm {
 
 RMM_PAIR_DECL(nt_large) {
-    return launch_pair_impl<ShapeLarge, B_KCONTIG, 3>(sk_cfg, kind, ga, gb, blocks_a, tiles_b, shares, stream, gc);
+    return launch_pair_impl<ShapeLarge, B_KCONTIG>(sk_cfg, kind, ga, gb, blocks_a, tiles_b, shares, stream, gc);
 }
 
 hipError_t launch_pair_nt(const PairPlain &plain, int sk_cfg, int kind, const GemmArgs &ga, const GemmArgs &gb, int tiles_b,
                           int shares, hipStream_t stream, const ColsumArgs *gc) {
-    return (plain.large ? launch_pair_nt_large : plain.depth == 4 ? launch_pair_nt_split4 : launch_pair_nt_split3)(
+    return (plain.cfg == GEMM_LARGE ? launch_pair_nt_large : plain.cfg == GEMM_SPLIT ? launch_pair_nt_split : launch_pair_nt_mid)(
         sk_cfg, kind, ga, gb, plain.tiles, tiles_b, shares, stream, gc);
 }
 

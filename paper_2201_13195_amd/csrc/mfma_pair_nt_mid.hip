@@ -1,0 +1,10 @@
+// Paired-launch kernels (see mfma_pair.hpp): launch_pair_nt_mid.
+#include "mfma_pair.hpp"
+
+namespace rmm {
+
+RMM_PAIR_DECL(nt_mid) {
+    return launch_pair_impl<ShapeMid, B_KCONTIG>(sk_cfg, kind, ga, gb, blocks_a, tiles_b, shares, stream, gc);
+}
+
+}  // namespace rmm
