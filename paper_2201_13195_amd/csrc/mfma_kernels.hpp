@@ -94,6 +94,16 @@ typedef Shape<64, 384, 64, 2, 4, 1> ShapeSkMid64;
 typedef Shape<128, 256, 64, 2, 4, 1> ShapeSkNarrow;
 typedef Shape<64, 256, 64, 2, 4, 1> ShapeSkNarrow64;
 
+// A Box-Muller pair of bf16 entries from one word of a Philox call: the radius, then the pair.
+__device__ __forceinline__ float gauss_radius(uint32_t w) {
+    const float u1 = (float)(2u * (w >> 16) + 1u) * (1.0f / 131072.0f);
+    return __builtin_amdgcn_sqrtf(-1.3862943611198906f * __builtin_amdgcn_logf(u1));  // -2 ln2 log2 u1
+}
+__device__ __forceinline__ bf16x2_t gauss_pair(uint32_t w, float rad) {
+    const float u2 = (float)(w & 0xFFFFu) * (1.0f / 65536.0f);  // revolutions
+    const f32x2_t z = {rad * __builtin_amdgcn_cosf(u2), rad * __builtin_amdgcn_sinf(u2)};
+    return __builtin_convertvector(z, bf16x2_t);
+}
 // Eight unscaled Gaussian entries P[8*c0 .. 8*c0+7][j] as a bf16 MFMA operand.
 __device__ __forceinline__ bf16x8_t gauss_operand(const SketchState &st, uint32_t c0, uint32_t j) {
     const Words4 r = philox4x32_10(c0, j, st.off0, st.off1, st.key0, st.key1);
@@ -102,23 +112,12 @@ __device__ __forceinline__ bf16x8_t gauss_operand(const SketchState &st, uint32_
         bf16x2_t p[4];
     } out;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const uint32_t w = r.w[q];
-        const float u1 = (float)(2u * (w >> 16) + 1u) * (1.0f / 131072.0f);
-        const float u2 = (float)(w & 0xFFFFu) * (1.0f / 65536.0f);                            // revolutions
-        const float rad = __builtin_amdgcn_sqrtf(-1.3862943611198906f * __builtin_amdgcn_logf(u1));  // -2 ln2 log2 u1
-        f32x2_t z = {rad * __builtin_amdgcn_cosf(u2), rad * __builtin_amdgcn_sinf(u2)};
-        out.p[q] = __builtin_convertvector(z, bf16x2_t);
-    }
+    for (int q = 0; q < 4; ++q) out.p[q] = gauss_pair(r.w[q], gauss_radius(r.w[q]));
     return out.v;
 }
 
-// Eight Rademacher entries for tokens t0 .. t0+7 (t0 a multiple of 8) of column j,
-// given the four words of the call that covers tokens 128*(t0/128) .. +127.
-__device__ __forceinline__ bf16x8_t radem_operand(const Words4 &r, uint32_t t0) {
-    const uint32_t t = t0 & 127u;
-    const uint32_t word = (t >> 5) == 0 ? r.w[0] : (t >> 5) == 1 ? r.w[1] : (t >> 5) == 2 ? r.w[2] : r.w[3];
-    const uint32_t bits = (word >> (t & 31u)) & 0xFFu;
+// Eight Rademacher entries from the lowest eight bits of `bits`.
+__device__ __forceinline__ bf16x8_t radem_operand(uint32_t bits) {
     union {
         bf16x8_t v;
         uint32_t d[4];
@@ -127,6 +126,13 @@ __device__ __forceinline__ bf16x8_t radem_operand(const Words4 &r, uint32_t t0) 
     for (int q = 0; q < 4; ++q)
         out.d[q] = 0x3F803F80u | (((bits >> (2 * q)) & 1u) << 15) | (((bits >> (2 * q + 1)) & 1u) << 31);
     return out.v;
+}
+// The same for tokens t0 .. t0+7 (t0 a multiple of 8) of column j, given the four words of the call that covers
+// tokens 128*(t0/128) .. +127.
+__device__ __forceinline__ bf16x8_t radem_operand(const Words4 &r, uint32_t t0) {
+    const uint32_t t = t0 & 127u;
+    const uint32_t word = (t >> 5) == 0 ? r.w[0] : (t >> 5) == 1 ? r.w[1] : (t >> 5) == 2 ? r.w[2] : r.w[3];
+    return radem_operand(word >> (t & 31u));
 }
 
 // The output tile of a wave.  The MFMA was issued with the operands swapped (B fragment first), so the
@@ -709,14 +715,39 @@ __global__ void __launch_bounds__(kFewThreads) few_tile_kernel(GemmArgs g) {
 
 // ---------------------------------------------------------------------------------------------
 // Sketch products: S^T (generated by the work-group into LDS) times A [token][column], in a pipeline like that of
-// gemm_tile: steps of 64 tokens, two stages, one barrier, A loaded straight into LDS (7 % faster than through
-// registers into three stages of 32 tokens).  What bounds them is how far MFMAs and generator share a step: with
-// 128 x 512 tiles at 16384 x 4096, k = 1638 the MFMAs of a step alone take 161 us per launch, without the generator
-// it is 217, complete 272 (Rademacher 138, 173, 215; one run, profiles/sketch_products.txt).  The generator's
-// instructions are therefore laid out between the MFMAs of the first quarters.  Generating in one half of the waves
-// while the other half multiplies was 4 % slower with steps of 64 tokens, 9 % with 32; 32-token steps in a ring of
-// four stages 1 % (more barriers); wave tiles of 64 x 128 5 % (A fragments are cheap, B fragments cost two
-// transposing reads).
+// gemm_tile: steps of 64 tokens, two stages, one barrier, A loaded straight into LDS, every instruction in its place.  A
+// step of a 128 x 512 tile needs the matrix pipes for 2048 cycles, the vector units for 1700 (Gaussian entries: two chunks of
+// eight per thread, a Philox call and four Box-Muller pairs each), and 64 KB from L2, which take about as long; they
+// only fit beside each other if all three run all the time.  So the making of a step's entries is cut into units (a Philox
+// round, half a Box-Muller pair) that are dealt evenly over the MFMAs between two barriers, from the last 16-deep step
+// before one to the one in front of the next, and so are the loads over its first half.
+// Rademacher: a thread's eight neighbours of one sketch column hold the calls of eight blocks of 128 tokens, one each
+// (sixteen steps), and pass the words around.
+
+// Eight Gaussian entries of one sketch column in the making.
+struct GaussChunk {
+    static constexpr int ROUNDS = 10, UNITS = ROUNDS + 8;
+    uint32_t c0, c1, c2, c3;
+    float rad;
+    union {
+        bf16x8_t v;
+        bf16x2_t p[4];
+    } out;
+    __device__ __forceinline__ void unit(const SketchState &st, uint32_t block, uint32_t j, int u) {
+        if (u == 0) c0 = block, c1 = j, c2 = st.off0, c3 = st.off1;
+        if (u < ROUNDS) {
+            philox_round(c0, c1, c2, c3, st.key0 + (uint32_t)u * kPhiloxBump0, st.key1 + (uint32_t)u * kPhiloxBump1);
+            return;
+        }
+        const int q = (u - ROUNDS) / 2;
+        const uint32_t w = q == 0 ? c0 : q == 1 ? c1 : q == 2 ? c2 : c3;
+        if ((u - ROUNDS) % 2 == 0)
+            rad = gauss_radius(w);
+        else
+            out.p[q] = gauss_pair(w, rad);
+    }
+};
+
 template <typename S>
 struct SketchTile {
     static constexpr int BM = S::BM, BN = S::BN, BK = S::BK, WM = S::WM, WN = S::WN, THREADS = S::THREADS;
@@ -732,7 +763,7 @@ struct SketchTile {
 template <typename S, int KIND>
 __device__ __forceinline__ void sketch_tile(const GemmArgs &g, bf16_t *lds, int64_t tile, int64_t kk_begin, int kk, int slice) {
     typedef SketchTile<S> T;
-    constexpr int BM = T::BM, BN = T::BN, BK = T::BK;
+    constexpr int BM = T::BM, BN = T::BN, BK = T::BK, TM = T::TM, TN = T::TN;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave / T::WN, wn = wave % T::WN;
     const int64_t tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN;
     constexpr int64_t GROUP_M = 8;  // (tile order: see gemm_tile)
@@ -753,112 +784,130 @@ __device__ __forceinline__ void sketch_tile(const GemmArgs &g, bf16_t *lds, int6
     }
     typedef __attribute__((address_space(3))) bf16_t *lds_ptr_t;
     const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_ptr_t)lds;
-    auto issue = [&](int t, int stage) {
-        const int k0 = first(t);
-        const uint32_t to = lds0 + (uint32_t)((stage * T::STAGE_ELEMS + T::A_ELEMS) * 2 + wave * T::LOADS * 1024);
-        const __amdgpu_buffer_rsrc_t rsrc =
-            __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(g.B + (kk_begin + k0) * g.ldb), (short)0,
-                                              __builtin_amdgcn_readfirstlane((int)(min(BK, kk - k0) * g.ldb * 2)), 0x00020000);
-#pragma unroll
-        for (int j = 0; j < T::LOADS; ++j) load_to_lds(rsrc, to + j * 1024, b_off[j], 0);
+    __amdgpu_buffer_rsrc_t rsrc;  // of the step of A that is being requested
+    uint32_t to;
+    auto begin_loads = [&](int t, int stage) {  // (past the end: zeros)
+        const int k0 = t < steps ? first(t) : kk;
+        to = lds0 + (uint32_t)((stage * T::STAGE_ELEMS + T::A_ELEMS) * 2 + wave * T::LOADS * 1024);
+        rsrc = rows_descriptor(g.B + (kk_begin + k0) * g.ldb, g.ldb, min(BK, kk - k0));
     };
-    // Chunk q of this thread: eight tokens of one sketch column.  Tokens past the slice are generated too: their
-    // rows of A are zeros.  Rademacher: a Philox call covers the 128 tokens of a block, two steps.
-    constexpr int ROWS = T::THREADS / (BK / 8);  // columns between two chunks of a thread
+    auto load = [&](int j) { load_to_lds(rsrc, to + j * 1024, b_off[j], 0); };
+
+    // Chunk q of this thread: tokens gen_k * 8 .. + 7 of the step, sketch column m0 + gen_row + q * ROWS.  Tokens past the
+    // slice are generated too: their rows of A are zeros.
+    constexpr int ROWS = T::THREADS / (BK / 8);
     const int gen_row = tid / (BK / 8), gen_k = tid % (BK / 8);
-    Words4 words[KIND == 0 ? 1 : T::GEN];
-    int64_t block_of_words = -1;
-    auto generate = [&](int t, int stage, int q) {
-        const int64_t tok = kk_begin + first(t) + gen_k * 8;
-        const int row = gen_row + q * ROWS;
-        bf16x8_t v;
-        if constexpr (KIND == 0) {
-            v = gauss_operand(g.st, (uint32_t)(tok >> 3), (uint32_t)(m0 + row));
-        } else {
-            const int64_t blk = (kk_begin + first(t)) >> 7;
-            if (q == 0 && blk != block_of_words) {
-                block_of_words = blk;
+    constexpr int UNITS = KIND == 0 ? GaussChunk::UNITS : 2;  // per chunk
+    GaussChunk gauss;
+    uint32_t words[KIND == 0 ? 1 : T::GEN][4] = {};  // Rademacher: of block 8 * held + gen_k
+    uint32_t low = 0, high = 0;
+    int64_t held = -1, making = 0;  // first token of the step whose entries are being made
+    bf16_t *made = lds;
+    auto begin_entries = [&](int t, int stage) {  // (past the end: a step that exists, not used)
+        making = kk_begin + first(min(t, steps - 1));
+        made = lds + stage * T::STAGE_ELEMS;
+        if constexpr (KIND != 0) {
+            if ((making >> 10) != held) {
+                held = making >> 10;
 #pragma unroll
-                for (int u = 0; u < T::GEN; ++u)
-                    words[u] = philox4x32_10((uint32_t)blk, (uint32_t)(m0 + gen_row + u * ROWS), g.st.off0, g.st.off1, g.st.key0, g.st.key1);
+                for (int q = 0; q < T::GEN; ++q) {
+                    const Words4 w = philox4x32_10((uint32_t)(held * 8 + gen_k), (uint32_t)(m0 + gen_row + q * ROWS), g.st.off0,
+                                                   g.st.off1, g.st.key0, g.st.key1);
+#pragma unroll
+                    for (int x = 0; x < 4; ++x) words[q][x] = w.w[x];
+                }
             }
-            v = radem_operand(words[q], (uint32_t)tok);
         }
-        *reinterpret_cast<bf16x8_t *>(lds + stage * T::STAGE_ELEMS + row * BK + kchunk_pos<BK>(row, gen_k) * 8) = v;
+    };
+    auto unit = [&](int u) {
+        const int q = u / UNITS, part = u % UNITS, row = gen_row + q * ROWS;
+        bf16_t *dst = made + row * BK + kchunk_pos<BK>(row, gen_k) * 8;
+        if constexpr (KIND == 0) {
+            gauss.unit(g.st, (uint32_t)(making >> 3) + gen_k, (uint32_t)(m0 + row), part);
+            if (part == UNITS - 1) *reinterpret_cast<bf16x8_t *>(dst) = gauss.out.v;
+        } else if (part == 0) {
+            // the two words of the step's 64 tokens, from the neighbour that holds their block
+            const int from = (lane & ~7) | (int)((making >> 7) & 7);
+            const bool second = (making & 64) != 0;
+            const uint32_t w0 = words[q][0], w1 = words[q][1], w2 = words[q][2], w3 = words[q][3];
+            low = __shfl(second ? w2 : w0, from, 64);
+            high = __shfl(second ? w3 : w1, from, 64);
+        } else {
+            *reinterpret_cast<bf16x8_t *>(dst) = radem_operand(((gen_k & 4) != 0 ? high : low) >> (8 * (gen_k & 3)));
+        }
     };
 
-    f32x16_t acc[T::TM][T::TN];
+    f32x16_t acc[TM][TN];
 #pragma unroll
-    for (int a = 0; a < T::TM; ++a)
+    for (int a = 0; a < TM; ++a)
 #pragma unroll
-        for (int b = 0; b < T::TN; ++b)
+        for (int b = 0; b < TN; ++b)
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[a][b][v] = 0.0f;
     struct Frags {
-        bf16x8_t a[T::TM], b[T::TN];
+        bf16x8_t a[TM], b[TN];
     };
-    auto load_frags = [&](Frags &f, int stage, int ks) {
+    auto read = [&](Frags &f, int stage, int ks, int i) {  // fragment i of a 16-deep step
         const bf16_t *As = lds + stage * T::STAGE_ELEMS, *Bs = As + T::A_ELEMS;
-#pragma unroll
-        for (int b = 0; b < T::TN; ++b) f.b[b] = frag_columns<BN>(Bs, wn * (BN / T::WN) + b * 32, ks * 16, lane);
-#pragma unroll
-        for (int a = 0; a < T::TM; ++a) f.a[a] = frag_kcontig<BK>(As, wm * (BM / T::WM) + a * 32, ks * 16, lane);
+        if (i < TN)
+            f.b[i] = frag_columns<BN>(Bs, wn * (BN / T::WN) + i * 32, ks * 16, lane);
+        else
+            f.a[i - TN] = frag_kcontig<BK>(As, wm * (BM / T::WM) + (i - TN) * 32, ks * 16, lane);
     };
-    auto multiply = [&](const Frags &f) {
-#pragma unroll
-        for (int a = 0; a < T::TM; ++a)
-#pragma unroll
-            for (int b = 0; b < T::TN; ++b)
-                acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.b[b], f.a[a], acc[a][b], 0, 0, 0);
-    };
-    auto meet = [] {
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        __syncthreads();
-    };
-    // Instructions of a quarter step in the order MFMA, LDS reads, a piece of the generator (some 190 vector
-    // instructions per chunk): MFMAs and vector work of one wave then run side by side.
-    constexpr int READS = T::TM + 2 * T::TN, MFMAS = T::TM * T::TN;
-    auto interleave = [](auto generates) {
+    constexpr int FRAGS = TM + TN, MFMAS = TM * TN, KS = BK / 16, SLOTS = KS * MFMAS, ALL = T::GEN * UNITS, HALF = (T::LOADS + 1) / 2;
+    // One 16-deep step, number `place` of the four from barrier to barrier: multiplies `now`, reads the fragments of the one behind it.
+    auto sixteen = [&](const Frags &now, Frags &next, int stage, int ks, int place) {
 #pragma unroll
         for (int i = 0; i < MFMAS; ++i) {
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-            __builtin_amdgcn_sched_group_barrier(0x100, (READS + MFMAS - 1) / MFMAS, 0);
-            if (decltype(generates)::value) __builtin_amdgcn_sched_group_barrier(0x402, 192 / MFMAS, 0);
+            const int a = i / TN, b = i % TN, slot = place * MFMAS + i;
+            acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(now.b[b], now.a[a], acc[a][b], 0, 0, 0);
+#pragma unroll
+            for (int r = i * FRAGS / MFMAS; r < (i + 1) * FRAGS / MFMAS; ++r) read(next, stage, ks, r);
+            if (place < 2) {
+#pragma unroll
+                for (int r = i * HALF / MFMAS; r < (i + 1) * HALF / MFMAS; ++r)
+                    if (place * HALF + r < T::LOADS) load(place * HALF + r);
+            }
+#pragma unroll
+            for (int u = slot * ALL / SLOTS; u < (slot + 1) * ALL / SLOTS; ++u) unit(u);
+            __builtin_amdgcn_sched_barrier(0);
         }
     };
-    constexpr int KS = BK / 16;
+    // (the order of barrier, reads and loads: see gemm_tile)
+    auto meet = [] {
+        wait_for_loads<0>();
+        __syncthreads();
+    };
     Frags f[2];
-    issue(0, 0);
+    begin_loads(0, 0);
 #pragma unroll
-    for (int q = 0; q < T::GEN; ++q) generate(0, 0, q);
+    for (int j = 0; j < T::LOADS; ++j) load(j);
+    begin_entries(0, 0);
+#pragma unroll
+    for (int u = 0; u < ALL; ++u) unit(u);
     meet();
-    load_frags(f[0], 0, 0);
-    if (steps > 1) issue(1, 1);
+#pragma unroll
+    for (int i = 0; i < FRAGS; ++i) read(f[0], 0, 0, i);
+    begin_loads(1, 1), begin_entries(1, 1);
+#pragma unroll
+    for (int j = 0; j < HALF; ++j) load(j);
+#pragma unroll
+    for (int u = 0; u < MFMAS * ALL / SLOTS; ++u) unit(u);
     for (int t = 0; t < steps; ++t) {
         const int stage = t & 1;
 #pragma unroll
-        for (int ks = 0; ks < KS - 1; ++ks) {
-            load_frags(f[(ks + 1) & 1], stage, ks + 1);
-            multiply(f[ks & 1]);
-            if (ks < T::GEN) {
-                generate(t + 1 < steps ? t + 1 : t, stage ^ 1, ks);  // (the last step's: not used; no branch)
-                interleave(std::true_type());
-            } else {
-                interleave(std::false_type());
-            }
-        }
+        for (int ks = 0; ks < KS - 1; ++ks) sixteen(f[ks & 1], f[(ks + 1) & 1], stage, ks + 1, ks + 1);
         meet();
-        if (t + 2 < steps) issue(t + 2, stage);
-        load_frags(f[0], stage ^ 1, 0);  // (past the end: what the stage holds, not used)
-        multiply(f[1]);
-        interleave(std::false_type());
+        begin_loads(t + 2, stage), begin_entries(t + 2, stage);
+        sixteen(f[1], f[0], stage ^ 1, 0, 0);  // (past the end: what the stage holds, not used)
     }
+    wait_for_loads<0>();
     __syncthreads();
     char *strip = reinterpret_cast<char *>(lds) + wave * kStripBytes;
     if (g.direct)
-        write_tile<true, false, false, T::TM, T::TN, 1>(g, acc, strip, m0, n0, wm, wn, 0, lane, slice);
+        write_tile<true, false, false, TM, TN, 1>(g, acc, strip, m0, n0, wm, wn, 0, lane, slice);
     else
-        write_tile<false, false, false, T::TM, T::TN, 1>(g, acc, strip, m0, n0, wm, wn, 0, lane, slice);
+        write_tile<false, false, false, TM, TN, 1>(g, acc, strip, m0, n0, wm, wn, 0, lane, slice);
 }
 
 // Share `work` of a sketch product: a slice of a tile, or (the last ones) the short last slices of per_tail tiles.
