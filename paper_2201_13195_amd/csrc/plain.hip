@@ -13,11 +13,16 @@ int64_t tiles_of(const PlainArgs &g, int64_t bm, int64_t bn) { return ((g.M + bm
 // Tile shape of a plain product.  What counts is how evenly the tiles share the 256 compute units (one
 // work-group each): the 128 x 128 tile where its last round costs no more than that of the 64 x 64 tile
 // (it moves and splits half as many operand bytes per flop), the 64 x 64 tile otherwise, and below one
-// 64 x 64 tile per compute unit the 32 x 32 tile, whose eight waves split the contraction.
-int plain_cfg(const PlainArgs &g) {
+// 64 x 64 tile per compute unit the 32 x 32 tile, whose eight waves split the contraction.  fp32 operands are what
+// splitting costs most: there a 128 x 128 tile takes 2.6 times as long as a 64 x 64 tile, not four times (dX 4096 x 3072 ->
+// 768 with G beside it, k = 410: 328 -> 280 us; dW 768 -> 3072 38 -> 30).  `two_sums`: the 128 x 128 tile keeps two sums
+// (plain_tile); with one, which is rounded twice as often, it stays where it was.
+template <typename T>
+int plain_cfg(const PlainArgs &g, bool two_sums) {
     const int64_t big = tiles_of(g, 128, 128), mid = tiles_of(g, 64, 64);
     if (mid < 256) return PLAIN_TINY;
-    return (big + 255) / 256 * 4 <= (mid + 255) / 256 ? PLAIN_BIG : PLAIN_MID;
+    const double times = sizeof(T) == 4 && two_sums ? 2.6 : 4.0;
+    return times * (double)((big + 255) / 256) <= (double)((mid + 255) / 256) ? PLAIN_BIG : PLAIN_MID;
 }
 int64_t cfg_tiles(const PlainArgs &g, int cfg) {
     const int64_t e = cfg == PLAIN_BIG ? 128 : cfg == PLAIN_MID ? 64 : 32;
@@ -48,7 +53,7 @@ ColsumArgs colsum_args(const T *A, T *out, int64_t n, int64_t d, bool accumulate
 
 template <typename T>
 hipError_t launch_pass(PlainLaunch &p, bool has_plain, bool has_sketch, bool b_rows_k, int mode, hipStream_t stream) {
-    p.cfg = mode == 0 ? PLAIN_TINY : has_plain ? plain_cfg(p.ga) : PLAIN_MID;
+    p.cfg = mode == 0 ? PLAIN_TINY : has_plain ? plain_cfg<T>(p.ga, b_rows_k) : PLAIN_MID;
     p.plain_blocks = has_plain ? (int)cfg_tiles(p.ga, p.cfg) : 0;
     p.sketch_blocks = 0;
     p.sketch_small = false;
@@ -75,7 +80,7 @@ PlainArgs sketch_args(const T *A, T *out, int64_t n, int64_t d, int64_t k, int k
 
 template <typename T, typename Tout, int MODE>
 hipError_t launch_tn(const PlainArgs &g, hipStream_t stream) {
-    const int cfg = MODE == 0 ? PLAIN_TINY : plain_cfg(g);
+    const int cfg = MODE == 0 ? PLAIN_TINY : plain_cfg<T>(g, true);
     const unsigned grid = (unsigned)cfg_tiles(g, cfg);
     if constexpr (MODE != 0) {
         if (cfg == PLAIN_BIG) {

@@ -314,17 +314,21 @@ __device__ __forceinline__ void plain_tile(const PlainArgs &g, bf16_t *lds, int6
     const int64_t band_rows = min((int64_t)8, tiles_m - band * 8);
     const int64_t m0 = (band * 8 + in_band % band_rows) * BM, n0 = (in_band / band_rows) * BN;
 
-    // With planes, the products of the two first planes are summed apart from the others, which are 2^-8 of them:
-    // the large sum is then rounded once per 16 contraction elements instead of eight times.
+    // With planes, the products of the two first planes are summed apart from the others, which are 2^-8 of them, and where a
+    // wave has the whole contraction of a row-indexed operand (dX, dW) those of every other 16 elements in a sum of their
+    // own: a large sum is then rounded once per 32 contraction elements instead of sixteen times, as it is on tiles whose
+    // contraction two waves share.  (Y has always taken these tiles with one sum; a second one costs it 8 %.)
     constexpr bool PLANES = PA + PB > 2;
-    f32x16_t acc[TM][TN], low[PLANES ? TM : 1][PLANES ? TN : 1];
+    constexpr int SUMS = PLANES && S::WK == 1 && BMODE == PB_N ? 2 : 1;
+    f32x16_t acc[SUMS][TM][TN], low[PLANES ? TM : 1][PLANES ? TN : 1];
 #pragma unroll
     for (int a = 0; a < TM; ++a)
 #pragma unroll
         for (int b = 0; b < TN; ++b)
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
-                acc[a][b][v] = 0.0f;
+#pragma unroll
+                for (int x = 0; x < SUMS; ++x) acc[x][a][b][v] = 0.0f;
                 if constexpr (PLANES) low[a][b][v] = 0.0f;
             }
 
@@ -397,7 +401,7 @@ __device__ __forceinline__ void plain_tile(const PlainArgs &g, bf16_t *lds, int6
                                        : frag_transposed(Bs + s * L::B_PLANE, L::SB, c0, k0, lane);
             }
     };
-    auto multiply = [&](const Frags &f) {  // smallest products first
+    auto multiply = [&](const Frags &f, int sum) {  // smallest products first
 #pragma unroll
         for (int order = PA + PB - 2; order >= 0; --order)
 #pragma unroll
@@ -408,15 +412,18 @@ __device__ __forceinline__ void plain_tile(const PlainArgs &g, bf16_t *lds, int6
                 for (int u = 0; u < TM; ++u)
 #pragma unroll
                     for (int w = 0; w < TN; ++w) {
-                        f32x16_t &sum = order > 0 ? low[PLANES ? u : 0][PLANES ? w : 0] : acc[u][w];
-                        sum = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.a[s][u], f.b[r][w], sum, 0, 0, 0);
+                        f32x16_t &to = order > 0 ? low[PLANES ? u : 0][PLANES ? w : 0] : acc[SUMS == 2 ? sum : 0][u][w];
+                        to = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.a[s][u], f.b[r][w], to, 0, 0, 0);
                     }
             }
     };
 
     // Two LDS stages, two register sets: while tile t is multiplied, t+1 goes from registers to LDS and
-    // t+3 is requested.  Tiles past the end are zeros.
+    // t+3 is requested (past the end: zeros).
     const int64_t num = (g.K + BK - 1) / BK;
+    // Short chains of fp32 tiles: those past the end are not split (256 x 128 -> 128: 18.6 -> 16 us a step).  Elsewhere the
+    // branch costs more (Y 4096 x 768 -> 3072: 162 -> 175 us).
+    constexpr bool SKIP = PB == 3 && S::WK == 8;
     issue(0);
     issue(1);
     put(0, 0);
@@ -425,13 +432,14 @@ __device__ __forceinline__ void plain_tile(const PlainArgs &g, bf16_t *lds, int6
     for (int64_t t = 0; t < num; t += 2) {
 #pragma unroll
         for (int s = 0; s < 2; ++s) {
+            if (SKIP && s == 1 && t + 1 >= num) break;
             Frags f[2];
             fetch(f[0], s, 0);
 #pragma unroll
             for (int step = 0; step < STEPS; ++step) {
                 if (step + 1 < STEPS) fetch(f[(step + 1) & 1], s, step + 1);
-                multiply(f[step & 1]);
-                if (step == 0) {
+                multiply(f[step & 1], step & 1);
+                if (step == 0 && (!SKIP || t + s + 1 < num)) {
                     put(s ^ 1, t + s + 1);
                     issue(s ^ 1);
                 }
@@ -444,7 +452,10 @@ __device__ __forceinline__ void plain_tile(const PlainArgs &g, bf16_t *lds, int6
 #pragma unroll
         for (int u = 0; u < TM; ++u)
 #pragma unroll
-            for (int w = 0; w < TN; ++w) acc[u][w] += low[u][w];
+            for (int w = 0; w < TN; ++w) {
+                if constexpr (SUMS == 2) acc[0][u][w] += acc[SUMS - 1][u][w];
+                acc[0][u][w] += low[u][w];
+            }
     }
 
     // Register v of lane l is C(8*(v/4) + 4*(l/32) + v%4, l % 32) of a 32x32 tile: a store instruction
@@ -475,7 +486,7 @@ __device__ __forceinline__ void plain_tile(const PlainArgs &g, bf16_t *lds, int6
         constexpr int WAVES = S::WM * S::WN;
         float *red = reinterpret_cast<float *>(lds);
 #pragma unroll
-        for (int v = 0; v < 16; ++v) red[(wave * 16 + v) * 64 + lane] = acc[0][0][v];
+        for (int v = 0; v < 16; ++v) red[(wave * 16 + v) * 64 + lane] = acc[0][0][0][v];
         __syncthreads();
         const int64_t c = n0 + wn * 32 + (lane & 31);
         const float bv = bias_at(c);
@@ -497,7 +508,7 @@ __device__ __forceinline__ void plain_tile(const PlainArgs &g, bf16_t *lds, int6
             for (int u = 0; u < TM; ++u)
 #pragma unroll
                 for (int v = 0; v < 16; ++v)
-                    put_out((w * TM + u) * 16 + v, m0 + wm * (BM / S::WM) + u * 32 + row_of(v), c, acc[u][w][v], bv);
+                    put_out((w * TM + u) * 16 + v, m0 + wm * (BM / S::WM) + u * 32 + row_of(v), c, acc[0][u][w][v], bv);
         }
     }
     if constexpr (PLANES) {

@@ -33,6 +33,15 @@ def test_fp32_tiles_and_load_modes(shape, kind):
     check_layer(X, W, dY, k, kind, 0x5EED0031, 5, "f32", bias=bias, label="f32 %s kind=%d" % (shape, kind))
 
 
+# dX and dW on 128 x 128 tiles with two sums: contractions of one 16-deep step, one tile, an odd number of tiles and a ragged last one
+@pytest.mark.parametrize("shape", [(2041, 1928, 12, 9), (2041, 1928, 36, 9), (1100, 4000, 100, 9), (64, 2052, 1990, 5),
+                                   (64, 2052, 1990, 33), (96, 2052, 1990, 90)])
+def test_fp32_large_tiles_of_the_gradients(shape):
+    n, d_in, d_out, k = shape
+    X, W, dY = synth.layer_inputs(n, d_in, d_out, "f32", (n, d_in + 1, d_out + 2), w_std=1.0 / math.sqrt(d_in))
+    check_layer(X, W, dY, k, rmm.RADEMACHER, 0x5EED0033, 5, "f32", label="f32 large %s" % (shape,))
+
+
 @pytest.mark.parametrize("kind", [rmm.GAUSSIAN, rmm.RADEMACHER, rmm.SORS])
 @pytest.mark.parametrize("shape", [(33, 35, 31, 5), (1030, 1028, 1004, 70), (2049, 515, 1030, 290), (3000, 768, 1001, 300),
                                    (4096, 261, 1032, 33)])
