@@ -170,7 +170,7 @@ int forward_impl(const rmm_layer_desc_t *d, SketchState st, const void *X, const
         hipError_t e =
             mfma ? launch_linear_nt_bf16((const bf16_t *)X, (const bf16_t *)W, (const bf16_t *)bias, (bf16_t *)Y,
                                          d->n, d->d_in, d->d_out,
-                                         X_proj != nullptr && pass_is_paired(d, RMM_OP_FORWARD), stream)
+                                         X_proj != nullptr && pass_is_paired(d, RMM_OP_FORWARD) ? d->k : 0, d->kind, stream)
                  : launch_forward_plain<T>((const T *)X, (const T *)W, (const T *)bias, (T *)Y, nullptr, d->n, d->d_in,
                                            d->d_out, d->k, d->kind, st, stream);
         if (e != hipSuccess) return RMM_ERR_LAUNCH;
@@ -219,7 +219,7 @@ int backward_impl(const rmm_layer_desc_t *d, SketchState st, const void *dY, con
     if (!paired && dX != nullptr) {  // dX = dY W: B(kk, c) = W[kk][c]
         StageScope scope(ev, RMM_STAGE_BWD_DX, stream);
         e = mfma ? launch_linear_nn_bf16((const bf16_t *)dY, (const bf16_t *)W, (bf16_t *)dX, d->n, d->d_in, d->d_out,
-                                         pass_is_paired(d, RMM_OP_BACKWARD), stream)
+                                         pass_is_paired(d, RMM_OP_BACKWARD) ? d->k : 0, d->kind, stream)
                  : launch_backward_plain<T>((const T *)dY, (const T *)W, (T *)dX, nullptr, nullptr, d->n, d->d_in,
                                             d->d_out, d->k, d->kind, st, false, stream);
         if (e != hipSuccess) return RMM_ERR_LAUNCH;

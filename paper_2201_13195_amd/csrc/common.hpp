@@ -60,11 +60,12 @@ hipError_t launch_colsum(const T *A, T *out, int64_t n, int64_t d, hipStream_t s
 // launch_sketch_bf16 records the optional event pair around its product kernel
 // alone (the sum over token slices, when there is one, comes after `ev_end`).
 bool mfma_shape_ok(int64_t n, int64_t d_in, int64_t d_out, int64_t k);
-// (`as_pair`: with the tiles of the pass's paired launch, for passes that launch their products one by one)
+// (`pair_k`, if not 0: with the tiles of the pass's paired launch with a sketch of pair_k columns, for passes that launch
+// their products one by one)
 hipError_t launch_linear_nt_bf16(const bf16_t *X, const bf16_t *W, const bf16_t *bias, bf16_t *Y, int64_t n,
-                                 int64_t d_in, int64_t d_out, bool as_pair, hipStream_t stream);
+                                 int64_t d_in, int64_t d_out, int64_t pair_k, int kind, hipStream_t stream);
 hipError_t launch_linear_nn_bf16(const bf16_t *dY, const bf16_t *W, bf16_t *dX, int64_t n, int64_t d_in,
-                                 int64_t d_out, bool as_pair, hipStream_t stream);
+                                 int64_t d_out, int64_t pair_k, int kind, hipStream_t stream);
 hipError_t launch_dw_bf16(const bf16_t *G, const bf16_t *X_proj, bf16_t *dW, int64_t k, int64_t d_in, int64_t d_out,
                           hipStream_t stream, bool accumulate = false);
 // dW together with db = column sums of dY (n x d_out, 16-byte aligned, d_out a multiple of 8) in

@@ -58,6 +58,7 @@ int64_t gemm_tiles(int cfg, int64_t m, int64_t n) {
         case GEMM_LARGE: return tiles_in<ShapeLarge>(m, n);
         case GEMM_WIDE: return tiles_in<ShapeWide>(m, n);
         case GEMM_SPLIT: return tiles_in<ShapeSplit>(m, n);
+        case GEMM_COMPACT:
         case GEMM_MID: return tiles_in<ShapeMid>(m, n);
         case GEMM_FLAT: return tiles_in<ShapeFlat>(m, n);
         case GEMM_SMALL: return tiles_in<ShapeSmall>(m, n);
@@ -144,6 +145,18 @@ void slice_sketch(SketchPlan &p, int64_t n, int target_wgs, double overhead, int
     p.k_chunk = len * 64;
 }
 
+// The tiles of a sketch product, and the time of a 64-token step on a full chip (alone).
+struct SketchMenu {
+    int64_t bm, bn;
+    double step_us[2];  // Gaussian, Rademacher
+};
+constexpr int kSketchTiles = 6;
+const SketchMenu &sketch_menu(int cfg) {
+    static const SketchMenu menu[kSketchTiles] = {{128, 256, {1.18, 0.91}}, {128, 512, {1.92, 1.63}}, {64, 512, {1.20, 1.04}},
+                                                  {64, 384, {0.93, 0.86}},  {128, 384, {1.54, 1.30}}, {64, 256, {0.85, 0.61}}};
+    return menu[cfg];  // (in the order of SK_NARROW ..)
+}
+
 // The tile is the one of the menu whose time comes out lowest: rounds of 256 work-groups, each as long as
 // its slice's 64-token steps, plus the partial results.  The times of a step on a full chip come from a fit over
 // measured shapes, adjusted by hand where another choice was faster; partial results cost 0.2 us per MB written and
@@ -156,15 +169,7 @@ void slice_sketch(SketchPlan &p, int64_t n, int target_wgs, double overhead, int
 // 64 x 512: 83 us, 128 x 512: 126; (10000 x 3000, k = 1000) 128 x 384: 85, 64 x 256: 114; 4096 x 3072, k = 3686
 // unsliced on 128 x 384: 107, 128 x 512: 119.)
 // `limited`: the caller may be rmm_sketch_static.
-SketchPlan plan_sketch(int64_t n, int64_t d, int64_t k, int kind, bool limited, int target_wgs = 256) {
-    struct Entry {
-        int cfg;
-        int64_t bm, bn;
-        double step_us[2];  // Gaussian, Rademacher
-    };
-    static const Entry menu[] = {{SK_WIDE64, 64, 512, {1.20, 1.04}},   {SK_WIDE, 128, 512, {1.92, 1.63}},
-                                 {SK_MID64, 64, 384, {0.93, 0.86}},    {SK_MID, 128, 384, {1.54, 1.30}},
-                                 {SK_NARROW64, 64, 256, {0.85, 0.61}}, {SK_NARROW, 128, 256, {1.18, 0.91}}};
+SketchPlan plan_sketch(int64_t n, int64_t d, int64_t k, int kind, bool limited) {
     // rmm_sketch_static serves the shapes whose partial results fit RMM_STATIC_SCRATCH_BYTES with the plainest
     // tiling (rows by k, columns by d); those keep fitting, whichever tile they run with.
     int64_t most = 64;
@@ -176,17 +181,18 @@ SketchPlan plan_sketch(int64_t n, int64_t d, int64_t k, int kind, bool limited, 
         if (slices == 1 || slices <= fit) most = fit < 1 ? 1 : fit < 64 ? fit : 64;
     }
     SketchPlan best{};
-    double best_us = -1.0, best_overhead = 0.0;
-    for (const Entry &e : menu) {
+    double best_us = -1.0;
+    static const int order[kSketchTiles] = {SK_WIDE64, SK_WIDE, SK_MID64, SK_MID, SK_NARROW64, SK_NARROW};
+    for (int cfg : order) {
+        const SketchMenu &e = sketch_menu(cfg);
         SketchPlan p;
-        p.cfg = e.cfg, p.tiles = tiles_of(k, d, e.bm, e.bn);
-        const double step_us = e.step_us[kind != 0], overhead = 4.0 / step_us;
-        slice_sketch(p, n, 256, overhead, most);
+        p.cfg = cfg, p.tiles = tiles_of(k, d, e.bm, e.bn);
+        const double step_us = e.step_us[kind != 0];
+        slice_sketch(p, n, 256, 4.0 / step_us, most);
         const double us = (double)((p.shares() + 255) / 256) * (double)(p.k_chunk / 64) * step_us + 2.0 * p.per_tail +
                           (p.splits > 1 ? (double)p.splits * (double)k * (double)d * 0.82e-6 : 0.0);
-        if (best_us < 0.0 || us < 0.98 * best_us) best = p, best_us = us, best_overhead = overhead;  // (ties: the wider tile pairs better)
+        if (best_us < 0.0 || us < 0.98 * best_us) best = p, best_us = us;  // (ties: the wider tile)
     }
-    if (target_wgs != 256) slice_sketch(best, n, target_wgs, best_overhead, most);
     return best;
 }
 
@@ -278,43 +284,111 @@ struct EventPair {
     ~EventPair() { done(); }
 };
 
-// The plain product of a pass that is launched together with the pass's sketch product: 256 x 256 tiles where it
-// fills the chip with them, else 128 x 128, whatever it would use alone (all run with 512 threads, like the sketch
-// kernels); with two wave groups where the contraction is long (4096 x 3072 -> 768 alone: 25.0 us, without 25.5; 768 -> 768:
-// 10.3, without 9.7).
-int pair_cfg(int64_t m, int64_t n, int64_t kk) {
-    return tiles_in<ShapeLarge>(m, n) >= 160 ? GEMM_LARGE : kk >= 1536 ? GEMM_SPLIT : GEMM_MID;
-}
-PairPlain pair_plain(int64_t m, int64_t n, int64_t kk) {
-    const int cfg = pair_cfg(m, n, kk);
-    return PairPlain{cfg, (int)gemm_tiles(cfg, m, n)};
-}
+// ---- Paired launches: which tiles and slices a pass takes.
 
-// Work-groups the sketch product of a pass should aim at when it is launched together with the
-// pass's plain product (`blocks_a` tiles, flops_a flop): if the plain product leaves compute units
-// idle in its last round and runs long enough for the whole sketch product (flops_sk, at about half
-// the plain product's rate per compute unit) to finish on them, one work-group per idle compute
-// unit (fewer, longer work-groups: less prologue, fewer partial sums); otherwise 256.
-int paired_sketch_target(int64_t blocks_a, double flops_a, double flops_sk) {
-    const int64_t idle = (256 - blocks_a % 256) % 256;
-    if (idle >= 32 && 2.0 * flops_sk * (double)blocks_a <= (double)idle * flops_a) return (int)idle;
-    return 256;
-}
-
-// Plan of the sketch product of X (forward) / dY (backward) inside a layer call.
-SketchPlan plan_pass_sketch(int64_t n, int64_t d_sk, int64_t d_other, int64_t k, int kind) {
-    // the plain product has an n x d_other output and contracts over d_sk
-    const SketchPlan alone = plan_sketch(n, d_sk, k, kind, false);
-    if (alone.splits == 1) return alone;
-    const int target = paired_sketch_target(pair_plain(n, d_other, d_sk).tiles, 2.0 * n * d_sk * d_other, 2.0 * n * k * d_sk);
-    SketchPlan paired = plan_sketch(n, d_sk, k, kind, false, target);
-    if (target == 256) {
-        // Short slices (at most 1024 tokens) pack better into the time the plain product's work-groups
-        // take when there are a quarter more of them; long ones would only add a round.
-        const SketchPlan finer = plan_sketch(n, d_sk, k, kind, false, 320);
-        if (paired.per_tail == 0 && finer.per_tail == 0 && finer.splits > paired.splits && finer.k_chunk <= 1024) paired = finer;
+// Time until `second` jobs of t2 us each are done that follow `first` jobs of t1 us on `slots` equal slots.
+double makespan(int64_t first, double t1, int64_t second, double t2, int64_t slots) {
+    const int64_t late = first % slots, early = slots - late;  // slots that become free a round later / at once
+    const double base = (double)(first / slots) * t1;
+    double t = 0.0;
+    for (int64_t i = 0, j = 0, done = 0; done < second;) {  // rounds of the early slots and of the late ones, by the time they end
+        const double e = (double)(i + 1) * t2, l = late > 0 ? t1 + (double)(j + 1) * t2 : 1e30;
+        if (e <= l)
+            t = e, ++i, done += early;
+        else
+            t = l, ++j, done += late;
     }
-    return paired.splits >= 2 ? paired : alone;
+    return base + (late > 0 && t < t1 ? t1 : t);
+}
+
+// us of a paired launch and the sum of its slices: work-groups of either kind take a time of their own (first loads and
+// writing, and every step of 64 contraction elements) and are dealt to 256 slots in grid order, or to 512 where two share
+// a compute unit.  The times are fitted to 4300 launches of 60 passes (256 to 16384 tokens, widths 256 to 4096,
+// k = 73 to 6911; all sketch tiles, 64 to 512 work-groups): 7 % rms off.  Over those passes the plan it leads to is 3.3 % slower than the
+// best one on average and 30 % at most; plans made for the sketch product alone were 12 and 50 %.
+double pair_us(const PairPlain &plain, int64_t kk, const SketchPlan &p, int kind, double partial_mb) {
+    struct Times {
+        double fix, step;
+    };
+    static const Times large{6.3, 1.405}, split{4.0, 0.478}, mid{3.4, 0.487}, compact{5.4, 0.733};
+    struct SketchTimes {
+        double fix, step[2];  // Gaussian, Rademacher
+    };
+    static const SketchTimes sk_compact{5.5, {1.009, 0.935}};
+    static const SketchTimes sk[] = {{5.3, {1.288, 0.957}}, {7.2, {1.651, 1.476}}, {5.1, {1.078, 1.080}},   // (in the order of SK_NARROW ..)
+                                     {5.0, {0.929, 0.910}}, {6.3, {1.490, 1.192}}, {4.05, {0.780, 0.722}}};
+    const bool two = plain.cfg == GEMM_COMPACT;
+    const Times &a = plain.cfg == GEMM_LARGE ? large : plain.cfg == GEMM_SPLIT ? split : two ? compact : mid;
+    const SketchTimes &b = two ? sk_compact : sk[p.cfg];
+    const double ta = a.fix + a.step * (double)((kk + 63) / 64), tb = b.fix + b.step[kind != 0] * (double)(p.k_chunk / 64);
+    const int64_t slots = two ? 512 : 256;
+    const double t = sketch_goes_first(plain.tiles, p.slices) ? makespan(p.shares(), tb, plain.tiles, ta, slots)
+                                                              : makespan(plain.tiles, ta, p.shares(), tb, slots);
+    return t + (p.splits > 1 ? 2.6 + 0.213 * (double)p.splits * partial_mb : 0.0);
+}
+
+struct PassPlan {
+    PairPlain plain;
+    SketchPlan sketch;
+};
+
+// The plain product of a pass (contraction kk, n x m outputs) beside a sketch product on one work-group per compute unit:
+// 256 x 256 tiles where it fills the chip with them, else 128 x 128; with two wave groups where the contraction is long (4096 x
+// 3072 -> 768 alone: 25.0 us, without 25.5; 768 -> 768: 10.3, without 9.7).
+PairPlain pair_plain(int64_t n, int64_t m, int64_t kk) {
+    const int cfg = tiles_in<ShapeLarge>(n, m) >= 160 ? GEMM_LARGE : kk >= 1536 ? GEMM_SPLIT : GEMM_MID;
+    return PairPlain{cfg, (int)gemm_tiles(cfg, n, m)};
+}
+
+// Plan of a pass: sketch of the n x d_sk operand, plain product n x d_other over d_sk.  Every sketch tile with slices for 64
+// to 320 work-groups, and 64 x 256 tiles with ShapeCompact where all work-groups are resident at once.  (4096 x 768 ->
+// 768, k = 410, with the sum of its slices: 26.9 -> 21.3 us; 4096 x 3072 -> 768, k = 2048, Rademacher 82 -> 69; 3001 x 1304 ->
+// 520, k = 600: 32 -> 24.)  At most a quarter more slices than alone: no pass needs much more workspace than its sketch
+// product.  Less than 0.8 us, which is what the model is off by at the smallest sizes, is not worth another order of additions
+// than that of the product alone.
+PassPlan make_pass_plan(int64_t n, int64_t d_sk, int64_t d_other, int64_t k, int kind) {
+    const SketchPlan alone = plan_sketch(n, d_sk, k, kind, true);
+    const double partial_mb = (double)k * (double)d_sk * 4e-6;
+    const PairPlain usual = pair_plain(n, d_other, d_sk);
+    const PairPlain compact{GEMM_COMPACT, (int)gemm_tiles(GEMM_COMPACT, n, d_other)};
+    PassPlan best{usual, alone};
+    double best_us = pair_us(usual, d_sk, alone, kind, partial_mb) - 0.8;
+    for (int cfg = 0; cfg < kSketchTiles; ++cfg) {
+        int slices = -1, per_tail = -1;
+        for (int target : {64, 96, 128, 192, 256, 320}) {
+            SketchPlan p;
+            p.cfg = cfg, p.tiles = tiles_of(k, d_sk, sketch_menu(cfg).bm, sketch_menu(cfg).bn);
+            slice_sketch(p, n, target, 4.0 / sketch_menu(cfg).step_us[kind != 0], 64);
+            if (p.slices == slices && p.per_tail == per_tail) continue;
+            slices = p.slices, per_tail = p.per_tail;
+            if (p.splits > 1 && (alone.splits == 1 || 4 * (p.splits - 1) > 5 * alone.splits)) continue;
+            double us = pair_us(usual, d_sk, p, kind, partial_mb);
+            if (us < best_us) best = PassPlan{usual, p}, best_us = us;
+            if (cfg != SK_NARROW64 || usual.cfg == GEMM_LARGE || compact.tiles + p.shares() > 512) continue;
+            us = pair_us(compact, d_sk, p, kind, partial_mb);
+            if (us < best_us) best = PassPlan{compact, p}, best_us = us;
+        }
+    }
+    return best;
+}
+
+// The same, remembered: a pass asks for its plan three times (workspace of either kind, launch), and it depends on the
+// sizes alone.
+PassPlan plan_pass(int64_t n, int64_t d_sk, int64_t d_other, int64_t k, int kind) {
+    struct Entry {
+        int64_t n, d_sk, d_other, k;
+        int kind;
+        PassPlan plan;
+    };
+    constexpr size_t ENTRIES = 64;
+    static thread_local Entry memo[ENTRIES];  // (n = 0: empty)
+    kind = kind != 0;
+    const uint64_t h = ((uint64_t)n * 0x9E3779B97F4A7C15u ^ (uint64_t)d_sk * 0xC2B2AE3D27D4EB4Fu ^ (uint64_t)d_other * 0x165667B19E3779F9u ^
+                        (uint64_t)k * 0x27D4EB2F165667C5u) + (uint64_t)kind;
+    Entry &e = memo[(h ^ h >> 32) % ENTRIES];
+    if (e.n != n || e.d_sk != d_sk || e.d_other != d_other || e.k != k || e.kind != kind)
+        e = Entry{n, d_sk, d_other, k, kind, make_pass_plan(n, d_sk, d_other, k, kind)};
+    return e.plan;
 }
 
 // Whether the launch of dW has room for the column sums of the bias gradient beside it.
@@ -325,21 +399,22 @@ bool dw_takes_colsum(int64_t d_in, int64_t d_out, int64_t k) {
     return (256 - tiles % 256) % 256 >= 64;
 }
 
-// Compute units that the last round of a backward pass's paired launch leaves idle.
-int64_t pair_idle(int64_t n, int64_t d_in, int64_t d_out, const SketchPlan &p) {
-    return (256 - (pair_plain(n, d_in, d_out).tiles + p.shares()) % 256) % 256;
+// Places for a work-group that the last round of a pass's paired launch leaves empty.
+int64_t pair_idle(const PassPlan &p) {
+    const int64_t slots = p.plain.cfg == GEMM_COMPACT ? 512 : 256;
+    return (slots - (p.plain.tiles + p.sketch.shares()) % slots) % slots;
 }
 
-// Plan of the sketch product of dY.  With a bias gradient that the launch of dW has no room for, short last slices
+// Plan of a backward pass.  With a bias gradient that the launch of dW has no room for, short last slices
 // that take the compute units its column sums need are given up (16384 x 1024 -> 4096, k = 1638: 208 sketch
 // work-groups instead of 243).
-SketchPlan plan_backward_sketch(int64_t n, int64_t d_in, int64_t d_out, int64_t k, int kind, bool with_dbias) {
-    const SketchPlan p = plan_pass_sketch(n, d_out, d_in, k, kind);
-    if (!with_dbias || p.per_tail == 0 || p.slices < 2 || dw_takes_colsum(d_in, d_out, k) || pair_idle(n, d_in, d_out, p) >= 16) return p;
-    SketchPlan even = p;
-    const int64_t units = (n + 63) / 64, len = (units + p.slices - 1) / p.slices;
-    even.per_tail = 0, even.k_chunk = len * 64, even.slices = even.splits = (int)((units + len - 1) / len);
-    return even.splits >= 2 && pair_idle(n, d_in, d_out, even) >= 16 ? even : p;
+PassPlan plan_backward(int64_t n, int64_t d_in, int64_t d_out, int64_t k, int kind, bool with_dbias) {
+    const PassPlan p = plan_pass(n, d_out, d_in, k, kind);
+    if (!with_dbias || p.sketch.per_tail == 0 || p.sketch.slices < 2 || dw_takes_colsum(d_in, d_out, k) || pair_idle(p) >= 16) return p;
+    PassPlan even = p;
+    const int64_t units = (n + 63) / 64, len = (units + p.sketch.slices - 1) / p.sketch.slices;
+    even.sketch.per_tail = 0, even.sketch.k_chunk = len * 64, even.sketch.slices = even.sketch.splits = (int)((units + len - 1) / len);
+    return even.sketch.splits >= 2 && pair_idle(even) >= 16 ? even : p;
 }
 
 }  // namespace
@@ -353,21 +428,23 @@ bool mfma_shape_ok(int64_t n, int64_t d_in, int64_t d_out, int64_t k) {
     return d_in % 8 == 0 && d_out % 8 == 0 && d_in < lim && d_out < lim;
 }
 
-// `as_pair`: with the tiles the product has in its pass's paired launch, so that a pass whose products
-// are launched one by one (to be timed) gives the same bits.
+// `pair_k`, if not 0: with the tiles the product has in its pass's paired launch with a sketch of pair_k columns, so that a
+// pass whose products are launched one by one (to be timed) gives the same bits.  (ShapeCompact adds in ShapeMid's order.)
 template <int BMODE>
-static hipError_t launch_plain_of_pass(const GemmArgs &g, bool as_pair, hipStream_t stream) {
-    return launch_gemm<A_KCONTIG, BMODE>((as_pair ? pair_cfg : gemm_cfg)(g.M, g.N, g.K), g, stream);
+static hipError_t launch_plain_of_pass(const GemmArgs &g, int64_t pair_k, int kind, hipStream_t stream) {
+    if (pair_k == 0) return launch_gemm<A_KCONTIG, BMODE>(gemm_cfg(g.M, g.N, g.K), g, stream);
+    const int cfg = (kind == RMM_SKETCH_SORS ? pair_plain(g.M, g.N, g.K) : plan_pass(g.M, g.K, g.N, pair_k, kind).plain).cfg;
+    return launch_gemm<A_KCONTIG, BMODE>(cfg == GEMM_COMPACT ? GEMM_MID : cfg, g, stream);
 }
 
 hipError_t launch_linear_nt_bf16(const bf16_t *X, const bf16_t *W, const bf16_t *bias, bf16_t *Y, int64_t n,
-                                 int64_t d_in, int64_t d_out, bool as_pair, hipStream_t stream) {
-    return launch_plain_of_pass<B_KCONTIG>(args_nt(X, W, bias, Y, n, d_in, d_out), as_pair, stream);
+                                 int64_t d_in, int64_t d_out, int64_t pair_k, int kind, hipStream_t stream) {
+    return launch_plain_of_pass<B_KCONTIG>(args_nt(X, W, bias, Y, n, d_in, d_out), pair_k, kind, stream);
 }
 
 hipError_t launch_linear_nn_bf16(const bf16_t *dY, const bf16_t *W, bf16_t *dX, int64_t n, int64_t d_in,
-                                 int64_t d_out, bool as_pair, hipStream_t stream) {
-    return launch_plain_of_pass<B_NCONTIG>(args_nn(dY, W, dX, n, d_in, d_out), as_pair, stream);
+                                 int64_t d_out, int64_t pair_k, int kind, hipStream_t stream) {
+    return launch_plain_of_pass<B_NCONTIG>(args_nn(dY, W, dX, n, d_in, d_out), pair_k, kind, stream);
 }
 
 hipError_t launch_dw_bf16(const bf16_t *G, const bf16_t *X_proj, bf16_t *dW, int64_t k, int64_t d_in, int64_t d_out,
@@ -450,7 +527,7 @@ hipError_t launch_xty_norms_bf16(const bf16_t *X, const bf16_t *dY, double *part
 }
 
 // The two dense kinds may take different tiles and slices; a workspace serves either (and both plans of
-// plan_backward_sketch: the one with a bias gradient has fewer slices).
+// plan_backward: the one with a bias gradient has fewer slices).
 size_t sketch_workspace_bf16(int64_t n, int64_t d, int64_t k, int64_t d_other) {
     int64_t k_chunk;
     size_t most = 0;
@@ -459,7 +536,7 @@ size_t sketch_workspace_bf16(int64_t n, int64_t d, int64_t k, int64_t d_other) {
         return s > 1 ? (size_t)s * (size_t)k * (size_t)d * sizeof(float) : 0;
     }
     for (int kind = 0; kind < 2; ++kind) {
-        const SketchPlan p = d_other > 0 ? plan_pass_sketch(n, d, d_other, k, kind) : plan_sketch(n, d, k, kind, true);
+        const SketchPlan p = d_other > 0 ? plan_pass(n, d, d_other, k, kind).sketch : plan_sketch(n, d, k, kind, true);
         const size_t bytes = p.splits > 1 ? (size_t)p.splits * (size_t)k * (size_t)d * sizeof(float) : 0;
         if (bytes > most) most = bytes;
     }
@@ -487,8 +564,8 @@ hipError_t launch_sketch_bf16(const bf16_t *A, bf16_t *out, int64_t n, int64_t d
         if (e != hipSuccess || slices == 1) return e;
         return launch_reduce(ws, out, k, d, slices, stream);
     }
-    const SketchPlan p = with_dbias    ? plan_backward_sketch(n, d_other, d, k, kind, true)
-                         : d_other > 0 ? plan_pass_sketch(n, d, d_other, k, kind)
+    const SketchPlan p = with_dbias    ? plan_backward(n, d_other, d, k, kind, true).sketch
+                         : d_other > 0 ? plan_pass(n, d, d_other, k, kind).sketch
                                        : plan_sketch(n, d, k, kind, true);
     const GemmArgs g = args_sketch(A, n, d, k, st, p, out, ws);
     hipError_t e = launch_sketch_plan(p, kind, g, stream);
@@ -503,10 +580,11 @@ hipError_t launch_forward_pair_bf16(const bf16_t *X, const bf16_t *W, const bf16
                                     int64_t n, int64_t d_in, int64_t d_out, int64_t k, int kind, SketchState st, void *ws,
                                     hipStream_t stream, hipEvent_t ev_begin, hipEvent_t ev_end) {
     const GemmArgs ga = args_nt(X, W, bias, Y, n, d_in, d_out);
-    const SketchPlan p = plan_pass_sketch(n, d_in, d_out, k, kind);
+    const PassPlan pass = plan_pass(n, d_in, d_out, k, kind);
+    const SketchPlan &p = pass.sketch;
     const GemmArgs gb = args_sketch(X, n, d_in, k, st, p, X_proj, ws);
     EventPair pev(ev_begin, ev_end, stream);
-    const hipError_t e = launch_pair_nt(pair_plain(ga.M, ga.N, ga.K), p.cfg, kind, ga, gb, (int)p.tiles, p.shares(), stream);
+    const hipError_t e = launch_pair_nt(pass.plain, p.cfg, kind, ga, gb, (int)p.tiles, p.shares(), stream);
     pev.done();
     if (e != hipSuccess || p.splits == 1) return e;
     return launch_reduce(ws, X_proj, k, d_in, p.splits, stream);
@@ -516,13 +594,13 @@ hipError_t launch_forward_pair_bf16(const bf16_t *X, const bf16_t *W, const bf16
 // dW when that leaves at least 64 compute units idle (dW is short and mostly latency; where it runs on
 // few_tile, whose work-groups want a compute unit each, when the column blocks fit beside them);
 // otherwise into the paired launch when its last round leaves at least 16 idle (the sketch work-groups
-// of that round run for long, and dY is being read there anyway; plan_backward_sketch sees to it where it
+// of that round run for long, and dY is being read there anyway; plan_backward sees to it where it
 // can); otherwise into the launch of dW.
 bool backward_pair_takes_colsum(int64_t n, int64_t d_in, int64_t d_out, int64_t k, int kind) {
     if (!pass_pair_available(k)) return false;
     return !dw_takes_colsum(d_in, d_out, k) &&
            (gemm_cfg(d_out, d_in, k) == GEMM_FEW ||
-            pair_idle(n, d_in, d_out, plan_backward_sketch(n, d_in, d_out, k, kind, true)) >= 16);
+            pair_idle(plan_backward(n, d_in, d_out, k, kind, true)) >= 16);
 }
 
 hipError_t launch_backward_pair_bf16(const bf16_t *dY, const bf16_t *W, bf16_t *dX, bf16_t *G, int64_t n, int64_t d_in,
@@ -530,12 +608,13 @@ hipError_t launch_backward_pair_bf16(const bf16_t *dY, const bf16_t *W, bf16_t *
                                      hipEvent_t ev_begin, hipEvent_t ev_end, bool with_dbias, bf16_t *dbias,
                                      bool accumulate_dbias) {
     const GemmArgs ga = args_nn(dY, W, dX, n, d_in, d_out);
-    const SketchPlan p = plan_backward_sketch(n, d_in, d_out, k, kind, with_dbias);
+    const PassPlan pass = plan_backward(n, d_in, d_out, k, kind, with_dbias);
+    const SketchPlan &p = pass.sketch;
     const GemmArgs gb = args_sketch(dY, n, d_out, k, st, p, G, ws);
     const ColsumArgs gc{dY, dbias, n, d_out, accumulate_dbias ? 1 : 0, colsum_lpr(d_out, 2)};
     const ColsumArgs *gcp = dbias != nullptr ? &gc : nullptr;
     EventPair pev(ev_begin, ev_end, stream);
-    const hipError_t e = launch_pair_nn(pair_plain(ga.M, ga.N, ga.K), p.cfg, kind, ga, gb, (int)p.tiles, p.shares(), stream, gcp);
+    const hipError_t e = launch_pair_nn(pass.plain, p.cfg, kind, ga, gb, (int)p.tiles, p.shares(), stream, gcp);
     pev.done();
     if (e != hipSuccess || p.splits == 1) return e;
     return launch_reduce(ws, G, k, d_out, p.splits, stream);

@@ -77,6 +77,7 @@ typedef TileShape<256, 256, 2, 4, 1, 3, 2, 4> ShapeLarge;
 typedef TileShape<128, 256, 2, 4, 1, 3, 3, 2> ShapeWide;
 typedef TileShape<128, 128, 2, 2, 2, 3, 3, 3> ShapeSplit;
 typedef TileShape<128, 128, 2, 4, 1, 3, 3, 1> ShapeMid;
+typedef TileShape<128, 128, 2, 4, 1, 2, 2, 2> ShapeCompact;  // half of LDS: paired launches only
 typedef TileShape<64, 128, 2, 4, 1, 3, 3, 1> ShapeFlat;
 typedef TileShape<64, 64, 2, 2, 1, 4, 4, 1> ShapeSmall;
 
@@ -962,8 +963,12 @@ __global__ void __launch_bounds__(S::THREADS) gemm_mfma_kernel(GemmArgs g) {
 // product that fills the chip by itself) sketch work-groups, column blocks, plain tiles: the
 // column blocks then start on the compute units the sketch product leaves free, ahead of the
 // plain tiles, instead of competing with the last round of plain tiles for memory.
+// ShapeCompact with 64 x 256 sketch tiles: either needs half of a compute unit's LDS and registers, so two work-groups
+// share one, and what one waits for (first loads, first entries, the writing of its tile) the other fills.
+template <typename SA, typename SB>
+constexpr int pair_waves_per_simd() { return SA::LDS_BYTES <= 80 * 1024 && SketchTile<SB>::LDS_BYTES <= 80 * 1024 ? 4 : 1; }
 template <typename SA, int BMODE_A, typename SB, int KIND>
-__global__ void __launch_bounds__(SA::THREADS) gemm_pair_kernel(GemmArgs ga, GemmArgs gb, int blocks_a, int tiles_b,
+__global__ void __launch_bounds__(SA::THREADS, (pair_waves_per_simd<SA, SB>())) gemm_pair_kernel(GemmArgs ga, GemmArgs gb, int blocks_a, int tiles_b,
                                                                  int sketch_blocks, int colsum_blocks, int sketch_first,
                                                                  ColsumArgs gc) {
     typedef SketchTile<SB> TB;

@@ -7,10 +7,11 @@
 namespace rmm {
 
 // Tile a plain product runs with (typedefs of mfma_kernels.hpp) and a sketch product's kernel.
-enum { GEMM_LARGE = 0, GEMM_WIDE = 1, GEMM_SPLIT = 2, GEMM_MID = 3, GEMM_FLAT = 4, GEMM_SMALL = 5, GEMM_FEW = 6 };
+enum { GEMM_LARGE = 0, GEMM_WIDE = 1, GEMM_SPLIT = 2, GEMM_MID = 3, GEMM_FLAT = 4, GEMM_SMALL = 5, GEMM_FEW = 6, GEMM_COMPACT = 7 };
 enum { SK_NARROW = 0, SK_WIDE = 1, SK_WIDE64 = 2, SK_MID64 = 3, SK_MID = 4, SK_NARROW64 = 5 };
 
-// The plain product of a paired launch: its tile (GEMM_LARGE, GEMM_SPLIT or GEMM_MID) and number of tiles.
+// The plain product of a paired launch: its tile (GEMM_LARGE, GEMM_SPLIT, GEMM_MID or, with SK_NARROW64, GEMM_COMPACT) and
+// number of tiles.
 struct PairPlain {
     int cfg, tiles;
 };
@@ -21,6 +22,7 @@ struct PairPlain {
 // The sketch work-groups are put in front of the plain tiles when the sketch product is unsliced (few, long
 // work-groups) or the plain product fills the chip at least once (256 tiles or more: measured 4 % faster at the
 // RoBERTa-large shapes, 2-3 % slower where the plain product has 192 tiles and the sketch work-groups fill in behind).
+inline bool sketch_goes_first(int64_t plain_tiles, int slices) { return slices == 1 || plain_tiles >= 256; }
 hipError_t launch_pair_nt(const PairPlain &plain, int sk_cfg, int kind, const GemmArgs &ga, const GemmArgs &gb, int tiles_b,
                           int shares, hipStream_t stream, const ColsumArgs *gc = nullptr);
 hipError_t launch_pair_nn(const PairPlain &plain, int sk_cfg, int kind, const GemmArgs &ga, const GemmArgs &gb, int tiles_b,
@@ -32,9 +34,11 @@ hipError_t launch_pair_nn(const PairPlain &plain, int sk_cfg, int kind, const Ge
 RMM_PAIR_DECL(nt_large);
 RMM_PAIR_DECL(nt_split);
 RMM_PAIR_DECL(nt_mid);
+RMM_PAIR_DECL(nt_compact);
 RMM_PAIR_DECL(nn_large);
 RMM_PAIR_DECL(nn_split);
 RMM_PAIR_DECL(nn_mid);
+RMM_PAIR_DECL(nn_compact);
 
 // The same for the SORS sketch kind (mfma_pair_sors.hip): `gs` describes the sketch product, whose
 // strips go two to a work-group; row_indexed_b says whether the plain product is dX = dY W (true) or Y = X W^T (false);
@@ -43,36 +47,33 @@ struct SorsArgs;
 hipError_t launch_pair_sors(const PairPlain &plain, bool row_indexed_b, const GemmArgs &ga, const SorsArgs &gs, int chunks,
                             bool sors_first, hipStream_t stream);
 
-// Shared body of the six launch_pair_{nt,nn}_*.
+// Shared bodies of launch_pair_{nt,nn}_*.
+template <typename SA, int BMODE_A, typename SB>
+hipError_t launch_pair_tiles(int kind, const GemmArgs &ga, const GemmArgs &gb, int blocks_a, int tiles_b, int shares,
+                             hipStream_t stream, const ColsumArgs *gc) {
+    const int sketch_first = sketch_goes_first(blocks_a, gb.slices) ? 1 : 0;
+    const ColsumArgs c = gc != nullptr ? *gc : ColsumArgs{};
+    const int col_blocks = gc != nullptr ? (int)colsum_blocks(c.d, 2) : 0;
+    const unsigned grid = (unsigned)(blocks_a + shares + col_blocks);
+    if (kind == 0)
+        gemm_pair_kernel<SA, BMODE_A, SB, 0><<<grid, SA::THREADS, 0, stream>>>(ga, gb, blocks_a, tiles_b, shares, col_blocks, sketch_first, c);
+    else
+        gemm_pair_kernel<SA, BMODE_A, SB, 1><<<grid, SA::THREADS, 0, stream>>>(ga, gb, blocks_a, tiles_b, shares, col_blocks, sketch_first, c);
+    return hipGetLastError();
+}
+
 template <typename SA, int BMODE_A>
 hipError_t launch_pair_impl(int sk_cfg, int kind, const GemmArgs &ga, const GemmArgs &gb, int blocks_a, int tiles_b,
                             int shares, hipStream_t stream, const ColsumArgs *gc) {
-    const int sketch_blocks = shares;
-    const int sketch_first = gb.slices == 1 || blocks_a >= 256 ? 1 : 0;
-    const ColsumArgs c = gc != nullptr ? *gc : ColsumArgs{};
-    const int col_blocks = gc != nullptr ? (int)colsum_blocks(c.d, 2) : 0;
-    const dim3 grid((unsigned)(blocks_a + sketch_blocks + col_blocks));
-    const int key = sk_cfg * 2 + (kind != 0 ? 1 : 0);
-#define RMM_PAIR_CASE(CFG, SHAPE)                                                                                      \
-    case CFG * 2:                                                                                                      \
-        gemm_pair_kernel<SA, BMODE_A, SHAPE, 0>                                                                   \
-            <<<grid, SA::THREADS, 0, stream>>>(ga, gb, blocks_a, tiles_b, sketch_blocks, col_blocks, sketch_first, c); \
-        break;                                                                                                         \
-    case CFG * 2 + 1:                                                                                                  \
-        gemm_pair_kernel<SA, BMODE_A, SHAPE, 1>                                                                   \
-            <<<grid, SA::THREADS, 0, stream>>>(ga, gb, blocks_a, tiles_b, sketch_blocks, col_blocks, sketch_first, c); \
-        break;
-    switch (key) {
-        RMM_PAIR_CASE(SK_WIDE, ShapeSkWide)
-        RMM_PAIR_CASE(SK_WIDE64, ShapeSkWide64)
-        RMM_PAIR_CASE(SK_MID64, ShapeSkMid64)
-        RMM_PAIR_CASE(SK_MID, ShapeSkMid)
-        RMM_PAIR_CASE(SK_NARROW64, ShapeSkNarrow64)
-        RMM_PAIR_CASE(SK_NARROW, ShapeSkNarrow)
+    switch (sk_cfg) {
+        case SK_WIDE: return launch_pair_tiles<SA, BMODE_A, ShapeSkWide>(kind, ga, gb, blocks_a, tiles_b, shares, stream, gc);
+        case SK_WIDE64: return launch_pair_tiles<SA, BMODE_A, ShapeSkWide64>(kind, ga, gb, blocks_a, tiles_b, shares, stream, gc);
+        case SK_MID64: return launch_pair_tiles<SA, BMODE_A, ShapeSkMid64>(kind, ga, gb, blocks_a, tiles_b, shares, stream, gc);
+        case SK_MID: return launch_pair_tiles<SA, BMODE_A, ShapeSkMid>(kind, ga, gb, blocks_a, tiles_b, shares, stream, gc);
+        case SK_NARROW64: return launch_pair_tiles<SA, BMODE_A, ShapeSkNarrow64>(kind, ga, gb, blocks_a, tiles_b, shares, stream, gc);
+        case SK_NARROW: return launch_pair_tiles<SA, BMODE_A, ShapeSkNarrow>(kind, ga, gb, blocks_a, tiles_b, shares, stream, gc);
         default: return hipErrorInvalidValue;
     }
-#undef RMM_PAIR_CASE
-    return hipGetLastError();
 }
 
 }  // namespace rmm

@@ -9,8 +9,12 @@ RMM_PAIR_DECL(nn_large) {
 
 hipError_t launch_pair_nn(const PairPlain &plain, int sk_cfg, int kind, const GemmArgs &ga, const GemmArgs &gb, int tiles_b,
                           int shares, hipStream_t stream, const ColsumArgs *gc) {
-    return (plain.cfg == GEMM_LARGE ? launch_pair_nn_large : plain.cfg == GEMM_SPLIT ? launch_pair_nn_split : launch_pair_nn_mid)(
-        sk_cfg, kind, ga, gb, plain.tiles, tiles_b, shares, stream, gc);
+    switch (plain.cfg) {
+        case GEMM_LARGE: return launch_pair_nn_large(sk_cfg, kind, ga, gb, plain.tiles, tiles_b, shares, stream, gc);
+        case GEMM_SPLIT: return launch_pair_nn_split(sk_cfg, kind, ga, gb, plain.tiles, tiles_b, shares, stream, gc);
+        case GEMM_COMPACT: return launch_pair_nn_compact(sk_cfg, kind, ga, gb, plain.tiles, tiles_b, shares, stream, gc);
+        default: return launch_pair_nn_mid(sk_cfg, kind, ga, gb, plain.tiles, tiles_b, shares, stream, gc);
+    }
 }
 
 }  // namespace rmm

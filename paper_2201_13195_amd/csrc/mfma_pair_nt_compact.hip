@@ -1,0 +1,11 @@
+// Paired-launch kernels (see mfma_pair.hpp): launch_pair_nt_compact.
+#include "mfma_pair.hpp"
+
+namespace rmm {
+
+RMM_PAIR_DECL(nt_compact) {
+    return sk_cfg == SK_NARROW64 ? launch_pair_tiles<ShapeCompact, B_KCONTIG, ShapeSkNarrow64>(kind, ga, gb, blocks_a, tiles_b, shares, stream, gc)
+                                 : hipErrorInvalidValue;
+}
+
+}  // namespace rmm
