@@ -122,11 +122,11 @@ private:
 template <typename T>
 int sketch_impl(int64_t n, int64_t d, int64_t k, int kind, SketchState st, const void *A, void *out, bool mfma,
                 void *ws, hipStream_t stream, const StageEvents &ev = StageEvents(), int product_stage = RMM_STAGE_NONE,
-                int64_t d_other = 0, bool with_dbias = false) {
+                int64_t d_other = 0, bool with_dbias = false, bf16_t *colsum = nullptr, bool accumulate = false) {
     const bool timed = product_stage != RMM_STAGE_NONE && ev.stage == product_stage;
     if (kind == RMM_SKETCH_SORS && mfma && sors_fast_ok(n, d)) {  // fast transform; otherwise S is applied densely below
         StageScope scope(ev, product_stage, stream);
-        return from_hip(launch_sors_bf16((const bf16_t *)A, (bf16_t *)out, n, d, k, st, stream));
+        return from_hip(launch_sors_bf16((const bf16_t *)A, (bf16_t *)out, n, d, k, st, stream, colsum, accumulate));
     }
     if (mfma && kind != RMM_SKETCH_SORS)
         return from_hip(launch_sketch_bf16((const bf16_t *)A, (bf16_t *)out, n, d, k, kind, st, ws, stream,
@@ -190,10 +190,15 @@ int backward_impl(const rmm_layer_desc_t *d, SketchState st, const void *dY, con
     T *G = (T *)ws;  // G = S^T dY, k x d_out
     const bool paired_sors = mfma && d->kind == RMM_SKETCH_SORS && dX != nullptr && !separate_stage(ev.stage) &&
                              sors_pair_available(d->n, d->d_out, d->d_in, d->k);
+    const bool own_db_stage = ev.stage == RMM_STAGE_BWD_DW || ev.stage == RMM_STAGE_BWD_DBIAS;
+    // the strips of the SORS kind read all of dY once and take its column sums on the way
+    const bool sors_db = mfma && d->kind == RMM_SKETCH_SORS && dbias != nullptr && !own_db_stage && sors_fast_ok(d->n, d->d_out) &&
+                         sors_takes_colsum(d->n, d->k);
     if (paired_sors) {
         const bool timed = ev.stage == RMM_STAGE_BWD_PAIR;
         e = launch_backward_pair_sors_bf16((const bf16_t *)dY, (const bf16_t *)W, (bf16_t *)dX, (bf16_t *)G, d->n, d->d_in,
-                                           d->d_out, d->k, st, stream, timed ? ev.begin : nullptr, timed ? ev.end : nullptr);
+                                           d->d_out, d->k, st, sors_db ? (bf16_t *)dbias : nullptr, accumulate, stream,
+                                           timed ? ev.begin : nullptr, timed ? ev.end : nullptr);
         if (e != hipSuccess) return RMM_ERR_LAUNCH;
     }
     const bool paired_plain = !mfma && !separate_stage(ev.stage);
@@ -205,8 +210,7 @@ int backward_impl(const rmm_layer_desc_t *d, SketchState st, const void *dY, con
     }
     const bool paired = paired_plain || paired_sors || (sliced_sketch(d) && dX != nullptr && !separate_stage(ev.stage) &&
                                         pass_pair_available(d->k));
-    const bool own_db_stage = ev.stage == RMM_STAGE_BWD_DW || ev.stage == RMM_STAGE_BWD_DBIAS;
-    bool db_done = paired_plain && ev.stage != RMM_STAGE_BWD_DBIAS;
+    bool db_done = sors_db || (paired_plain && ev.stage != RMM_STAGE_BWD_DBIAS);
     if (paired && !paired_sors && !paired_plain) {
         const bool timed = ev.stage == RMM_STAGE_BWD_PAIR;
         db_done = dbias != nullptr && !own_db_stage && backward_pair_takes_colsum(d->n, d->d_in, d->d_out, d->k, d->kind);
@@ -227,7 +231,7 @@ int backward_impl(const rmm_layer_desc_t *d, SketchState st, const void *dY, con
     if (!paired) {
         StageScope scope(ev, RMM_STAGE_BWD_G, stream);
         int rc = sketch_impl<T>(d->n, d->d_out, d->k, d->kind, st, dY, G, mfma, (char *)ws + g_bytes(d), stream, ev,
-                                RMM_STAGE_BWD_G_PRODUCT, d->d_in, dbias != nullptr);
+                                RMM_STAGE_BWD_G_PRODUCT, d->d_in, dbias != nullptr, sors_db ? (bf16_t *)dbias : nullptr, accumulate);
         if (rc != RMM_OK) return rc;
     }
     if (mfma && dbias != nullptr && !db_done && !own_db_stage) {

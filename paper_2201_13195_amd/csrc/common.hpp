@@ -103,9 +103,11 @@ bool backward_pair_takes_colsum(int64_t n, int64_t d_in, int64_t d_out, int64_t 
 // SORS sketch kind, bf16 (sors.hip): signs, Walsh-Hadamard transform along the tokens and row
 // selection in one kernel, no workspace.  Usable when sors_fast_ok(): d a multiple of 8 and at most
 // 32768 tokens (the strip of one work-group has to fit in LDS); `st` made with the token count.
+// `colsum`, if not null, gets the column sums of A from the same pass over it; only where sors_takes_colsum() says so.
 bool sors_fast_ok(int64_t n, int64_t d);
+bool sors_takes_colsum(int64_t n, int64_t k);
 hipError_t launch_sors_bf16(const bf16_t *A, bf16_t *out, int64_t n, int64_t d, int64_t k, SketchState st,
-                            hipStream_t stream);
+                            hipStream_t stream, bf16_t *colsum = nullptr, bool accumulate = false);
 
 // One launch for the plain product of a pass and the SORS sketch product of the same pass, where
 // the plain product leaves compute units idle (mfma.hip decides, mfma_pair_sors.hip holds the
@@ -115,8 +117,9 @@ hipError_t launch_forward_pair_sors_bf16(const bf16_t *X, const bf16_t *W, const
                                          int64_t n, int64_t d_in, int64_t d_out, int64_t k, SketchState st,
                                          hipStream_t stream, hipEvent_t ev_begin = nullptr, hipEvent_t ev_end = nullptr);
 hipError_t launch_backward_pair_sors_bf16(const bf16_t *dY, const bf16_t *W, bf16_t *dX, bf16_t *G, int64_t n,
-                                          int64_t d_in, int64_t d_out, int64_t k, SketchState st, hipStream_t stream,
-                                          hipEvent_t ev_begin = nullptr, hipEvent_t ev_end = nullptr);
+                                          int64_t d_in, int64_t d_out, int64_t k, SketchState st, bf16_t *dbias,
+                                          bool accumulate_dbias, hipStream_t stream, hipEvent_t ev_begin = nullptr,
+                                          hipEvent_t ev_end = nullptr);
 
 // Variance monitors (variance.hip, and the squared-norm epilogue of the MFMA kernel).
 //   part[3*b..] = per-block (sum |x_k|^2, sum |y_k|^2, sum |x_k|^2 |y_k|^2); row_norm_blocks(n) blocks.

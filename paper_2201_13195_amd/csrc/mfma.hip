@@ -647,24 +647,25 @@ bool sors_pair_available(int64_t n, int64_t d_sk, int64_t d_other, int64_t k) {
     return sors_pair_order(plain.tiles, (d_sk / 8 + 1) / 2) != 0;
 }
 
-static hipError_t launch_pass_sors(const GemmArgs &ga, bool row_indexed_b, const bf16_t *A, bf16_t *out, int64_t n, int64_t d_sk,
-                                   int64_t k, SketchState st, hipStream_t stream, hipEvent_t ev_begin, hipEvent_t ev_end) {
+static hipError_t launch_pass_sors(const GemmArgs &ga, bool row_indexed_b, const SorsArgs &gs, hipStream_t stream, hipEvent_t ev_begin,
+                                   hipEvent_t ev_end) {
     const PairPlain plain = pair_plain(ga.M, ga.N, ga.K);
-    const SorsArgs gs{A, out, n, d_sk, k, st, 1.0f / sqrtf((float)k)};
     EventPair pev(ev_begin, ev_end, stream);
-    return launch_pair_sors(plain, row_indexed_b, ga, gs, sors_chunks(n), sors_pair_order(plain.tiles, (d_sk / 8 + 1) / 2) == 2, stream);
+    return launch_pair_sors(plain, row_indexed_b, ga, gs, sors_chunks(gs.n), sors_pair_order(plain.tiles, (gs.d / 8 + 1) / 2) == 2, stream);
 }
 
 hipError_t launch_forward_pair_sors_bf16(const bf16_t *X, const bf16_t *W, const bf16_t *bias, bf16_t *Y, bf16_t *X_proj,
                                          int64_t n, int64_t d_in, int64_t d_out, int64_t k, SketchState st,
                                          hipStream_t stream, hipEvent_t ev_begin, hipEvent_t ev_end) {
-    return launch_pass_sors(args_nt(X, W, bias, Y, n, d_in, d_out), false, X, X_proj, n, d_in, k, st, stream, ev_begin, ev_end);
+    const SorsArgs gs{X, X_proj, n, d_in, k, st, 1.0f / sqrtf((float)k), nullptr, 0};
+    return launch_pass_sors(args_nt(X, W, bias, Y, n, d_in, d_out), false, gs, stream, ev_begin, ev_end);
 }
 
 hipError_t launch_backward_pair_sors_bf16(const bf16_t *dY, const bf16_t *W, bf16_t *dX, bf16_t *G, int64_t n,
-                                          int64_t d_in, int64_t d_out, int64_t k, SketchState st, hipStream_t stream,
-                                          hipEvent_t ev_begin, hipEvent_t ev_end) {
-    return launch_pass_sors(args_nn(dY, W, dX, n, d_in, d_out), true, dY, G, n, d_out, k, st, stream, ev_begin, ev_end);
+                                          int64_t d_in, int64_t d_out, int64_t k, SketchState st, bf16_t *dbias,
+                                          bool accumulate_dbias, hipStream_t stream, hipEvent_t ev_begin, hipEvent_t ev_end) {
+    const SorsArgs gs{dY, G, n, d_out, k, st, 1.0f / sqrtf((float)k), dbias, accumulate_dbias ? 1 : 0};
+    return launch_pass_sors(args_nn(dY, W, dX, n, d_in, d_out), true, gs, stream, ev_begin, ev_end);
 }
 
 }  // namespace rmm

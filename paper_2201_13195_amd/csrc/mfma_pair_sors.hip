@@ -11,7 +11,7 @@ namespace {
 
 constexpr int kPairChunkLog = 11;  // chunks of 2048 tokens, as the strip kernel on its own
 
-template <typename SA, int BMODE_A>
+template <typename SA, int BMODE_A, bool SUMS>
 __global__ void __launch_bounds__(SA::THREADS) gemm_sors_pair_kernel(GemmArgs ga, SorsArgs gs, int blocks_a, int chunks,
                                                                      int sors_first) {
     typedef StripShape<kPairChunkLog> SS;
@@ -27,7 +27,7 @@ __global__ void __launch_bounds__(SA::THREADS) gemm_sors_pair_kernel(GemmArgs ga
     if (plain >= 0 && plain < blocks_a)
         gemm_tile<SA, A_KCONTIG, BMODE_A, OUT_BF16>(ga, reinterpret_cast<bf16_t *>(lds), plain, blocks_a);
     else
-        sors_strip_body<kPairChunkLog, true, 2>(gs, chunks, reinterpret_cast<float4 *>(lds),
+        sors_strip_body<kPairChunkLog, true, 2, SUMS>(gs, chunks, reinterpret_cast<float4 *>(lds),
                                                 reinterpret_cast<uint32_t *>(lds + PLANE_BYTES),
                                                 sors_first ? (int64_t)blockIdx.x : (int64_t)blockIdx.x - blocks_a, strips);
 }
@@ -35,8 +35,13 @@ __global__ void __launch_bounds__(SA::THREADS) gemm_sors_pair_kernel(GemmArgs ga
 template <typename SA, int BMODE_A>
 hipError_t launch_impl(const GemmArgs &ga, const SorsArgs &gs, int blocks_a, int chunks, int sors_first, hipStream_t stream) {
     const unsigned strips2 = (unsigned)((gs.d / 8 + 1) / 2);
-    gemm_sors_pair_kernel<SA, BMODE_A><<<(unsigned)blocks_a + strips2, SA::THREADS, 0, stream>>>(ga, gs, blocks_a, chunks,
-                                                                                                    sors_first);
+    const unsigned grid = (unsigned)blocks_a + strips2;
+    if constexpr (BMODE_A == B_NCONTIG)
+        if (gs.colsum != nullptr) {
+            gemm_sors_pair_kernel<SA, BMODE_A, true><<<grid, SA::THREADS, 0, stream>>>(ga, gs, blocks_a, chunks, sors_first);
+            return hipGetLastError();
+        }
+    gemm_sors_pair_kernel<SA, BMODE_A, false><<<grid, SA::THREADS, 0, stream>>>(ga, gs, blocks_a, chunks, sors_first);
     return hipGetLastError();
 }
 

@@ -168,16 +168,19 @@ __global__ void __launch_bounds__(256) sors_kernel(SorsArgs g) {
     }
 }
 
-template <int LC, bool ACC, int NPROB>
-__global__ void __launch_bounds__(256 * NPROB) sors_strip_kernel(SorsArgs g, int chunks) {
-    __shared__ float4 planes[NPROB * StripShape<LC>::REGION];
+template <int LC, bool ACC, bool SUMS>
+__global__ void __launch_bounds__(256) sors_strip_kernel(SorsArgs g, int chunks) {
+    __shared__ float4 planes[StripShape<LC>::REGION];
     __shared__ uint32_t sign_words[1024];  // up to 32768 tokens
-    sors_strip_body<LC, ACC, NPROB>(g, chunks, planes, sign_words, blockIdx.x, gridDim.x);
+    sors_strip_body<LC, ACC, 1, SUMS>(g, chunks, planes, sign_words, blockIdx.x, gridDim.x);
 }
 
 template <int LC, bool ACC>
 hipError_t launch_strip(const SorsArgs &g, int chunks, hipStream_t stream) {
-    sors_strip_kernel<LC, ACC, 1><<<(unsigned)(g.d / 8), 256, 0, stream>>>(g, chunks);
+    if (g.colsum != nullptr)
+        sors_strip_kernel<LC, ACC, true><<<(unsigned)(g.d / 8), 256, 0, stream>>>(g, chunks);
+    else
+        sors_strip_kernel<LC, ACC, false><<<(unsigned)(g.d / 8), 256, 0, stream>>>(g, chunks);
     return hipGetLastError();
 }
 
@@ -195,11 +198,14 @@ int log2_ceil(int64_t n) {
 
 }  // namespace
 
-bool sors_fast_ok(int64_t n, int64_t d) { return d % 8 == 0 && n >= 1 && n <= 32768; }
+// (d: 256 rows stay inside one buffer descriptor's 2^31 bytes)
+bool sors_fast_ok(int64_t n, int64_t d) { return d % 8 == 0 && d < (1 << 22) && n >= 1 && n <= 32768; }
+
+bool sors_takes_colsum(int64_t n, int64_t k) { return k <= kSorsAccMaxK || n <= 4096; }
 
 hipError_t launch_sors_bf16(const bf16_t *A, bf16_t *out, int64_t n, int64_t d, int64_t k, SketchState st,
-                            hipStream_t stream) {
-    SorsArgs g{A, out, n, d, k, st, 1.0f / sqrtf((float)k)};
+                            hipStream_t stream, bf16_t *colsum, bool accumulate) {
+    SorsArgs g{A, out, n, d, k, st, 1.0f / sqrtf((float)k), colsum, accumulate ? 1 : 0};
     // A kernel's transform length is at least 256; for fewer tokens the rows drawn below n_pad
     // are rows of the larger Walsh-Hadamard matrix restricted to its leading n_pad x n_pad block,
     // which is the n_pad-point matrix itself.

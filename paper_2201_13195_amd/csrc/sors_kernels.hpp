@@ -11,6 +11,8 @@ struct SorsArgs {
     int64_t n, d, k;
     SketchState st;
     float alpha;
+    bf16_t *colsum;     // kernels with SUMS: the column sums of A (the bias gradient), d values,
+    int accumulate;     // added to what is there
 };
 
 namespace {
@@ -33,7 +35,11 @@ __device__ __forceinline__ int sors_phys(int t) { return t + (t >> 4); }
 // selected rows are written directly and k is not limited.  Per chunk: the top LC - 8 index bits
 // in registers while loading (2^(LC-8) rows per thread), then two LDS passes of four bits each,
 // 16-byte LDS accesses throughout.  LDS layout: two halves (columns 0-3, 4-7) of float4 slots,
-// token t at slot t + t / 16.
+// token t at slot t + t / 16.  A backward pass with a bias gradient takes the column sums of dY here, where every
+// element passes through registers anyway: eight additions per row, ten lane exchanges at the end.  It saves the later launch
+// its read of dY (16384 x 1024 -> 1024, k = 1638: backward without the bias gradient 76 us, with it 103 before and 78 now;
+// 4096 x 768 -> 3072, k = 410: 60 -> 52).  A form of its own: with a branch on the argument the strips without sums went
+// from 78 us to 105 at 8192 x 4096.
 template <int LC>
 struct StripShape {
     static constexpr int CH = 1 << LC, W0 = LC - 8, R0 = 1 << W0, SLOTS = CH + CH / 16;
@@ -55,22 +61,23 @@ __device__ __forceinline__ void sors_butterflies4(float4 (&v)[16]) {
             }
 }
 
-// Index bits SHIFT .. SHIFT+3 of the chunk-local token index, both halves.
+// Index bits SHIFT .. SHIFT+3 of the chunk-local token index, both halves.  (The sixteen slots of an item lie STEP
+// apart, which the slot formula does not show the compiler: it would keep an address for each of them over the whole loop.)
 template <int LC, int SHIFT>
 __device__ __forceinline__ void strip_lds_pass(float4 *planes, int tid) {
     typedef StripShape<LC> S;
-    constexpr int VEC = S::CH / 16;
+    static_assert(SHIFT == 0 || SHIFT == 4, "two passes");
+    constexpr int VEC = S::CH / 16, STEP = SHIFT == 0 ? 1 : 17;
     for (int item = tid; item < 2 * VEC; item += 256) {
         const int h = item / VEC, b = item % VEC;
         const int low = b & ((1 << SHIFT) - 1), high = b >> SHIFT;
-        const int base = (high << (SHIFT + 4)) | low;
-        float4 *plane = planes + h * S::SLOTS;
+        float4 *p = planes + h * S::SLOTS + sors_phys((high << (SHIFT + 4)) | low);
         float4 v[16];
 #pragma unroll
-        for (int i = 0; i < 16; ++i) v[i] = plane[sors_phys(base + (i << SHIFT))];
+        for (int i = 0; i < 16; ++i) v[i] = p[STEP * i];
         sors_butterflies4(v);
 #pragma unroll
-        for (int i = 0; i < 16; ++i) plane[sors_phys(base + (i << SHIFT))] = v[i];
+        for (int i = 0; i < 16; ++i) p[STEP * i] = v[i];
     }
 }
 
@@ -80,7 +87,7 @@ __device__ __forceinline__ void strip_lds_pass(float4 *planes, int tid) {
 // lanes of the two strips stay on different banks): the form that shares a grid with the 512-thread
 // work-groups of a plain product.  `block` of `blocks` numbers the work-group among those of the
 // sketch product; LDS: NPROB * StripShape::REGION float4 slots and 1024 words.
-template <int LC, bool ACC, int NPROB>
+template <int LC, bool ACC, int NPROB, bool SUMS>
 __device__ __forceinline__ void sors_strip_body(const SorsArgs &g, int chunks, float4 *planes_all, uint32_t *sign_words,
                                                 int64_t block, int64_t blocks) {
     typedef StripShape<LC> S;
@@ -121,18 +128,25 @@ __device__ __forceinline__ void sors_strip_body(const SorsArgs &g, int chunks, f
         }
     }
 
+    // Buffer loads: a row beyond the tokens lies outside the descriptor's range (256 rows each) and reads as zero, so
+    // there is no branch between the loads and the compiler can count them: with one it waited for the next chunk's rows in front of
+    // this chunk's transform.
+    const uint32_t off = live ? (uint32_t)((tid * g.d + col0) * 2) : 0x80000000u;
     auto load_chunk = [&](int ch, sors_u32x4_t (&raw)[R0]) {
 #pragma unroll
         for (int i = 0; i < R0; ++i) {
-            const int64_t t = (int64_t)ch * CH + tid + i * 256;
-            if (live && t < g.n)
-                raw[i] = *reinterpret_cast<const sors_u32x4_t *>(g.A + t * g.d + col0);
-            else
-                raw[i] = (sors_u32x4_t){0u, 0u, 0u, 0u};
+            const int64_t t0 = (int64_t)ch * CH + i * 256, rows = min((int64_t)256, g.n - t0);
+            const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
+                const_cast<bf16_t *>(g.A + t0 * g.d), (short)0, __builtin_amdgcn_readfirstlane((int)((rows > 0 ? rows : 0) * g.d * 2)), 0x00020000);
+            raw[i] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, off, 0, 0);
         }
     };
 
-    sors_u32x4_t raw[R0], raw_next[R0];
+    float sums[SUMS ? 8 : 1];
+    if constexpr (SUMS)
+#pragma unroll
+        for (int c = 0; c < 8; ++c) sums[c] = 0.0f;
+    sors_u32x4_t raw[R0];
     load_chunk(0, raw);
     __syncthreads();  // sign words
     for (int ch = 0; ch < chunks; ++ch) {
@@ -143,13 +157,26 @@ __device__ __forceinline__ void sors_strip_body(const SorsArgs &g, int chunks, f
             for (int i = 0; i < R0; ++i) {
                 const int t = ch * CH + tid + i * 256;
                 const uint32_t flip = ((sign_words[t >> 5] >> (t & 31)) & 1u) << 31;
-                const sors_u32x4_t w = raw[i];  // eight bf16: element 2q in the low half of word q
-                v[i][0] = make_float4(__uint_as_float((w.x << 16) ^ flip), __uint_as_float((w.x & 0xFFFF0000u) ^ flip),
-                                      __uint_as_float((w.y << 16) ^ flip), __uint_as_float((w.y & 0xFFFF0000u) ^ flip));
-                v[i][1] = make_float4(__uint_as_float((w.z << 16) ^ flip), __uint_as_float((w.z & 0xFFFF0000u) ^ flip),
-                                      __uint_as_float((w.w << 16) ^ flip), __uint_as_float((w.w & 0xFFFF0000u) ^ flip));
+                asm volatile("" : "+v"(raw[i]));  // (unpacked here: not before, in twice the registers)
+                float x[8];                      // (element 2q in the low half of word q)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    x[2 * q] = __uint_as_float(raw[i][q] << 16);
+                    x[2 * q + 1] = __uint_as_float(raw[i][q] & 0xFFFF0000u);
+                }
+                if constexpr (SUMS) {
+#pragma unroll
+                    for (int c = 0; c < 8; ++c) {
+                        sums[c] += x[c];
+                        asm volatile("" : "+v"(sums[c]));  // (now: not after all rows, with a second copy of each)
+                    }
+                }
+#pragma unroll
+                for (int c = 0; c < 8; ++c) x[c] = __uint_as_float(__float_as_uint(x[c]) ^ flip);
+                v[i][0] = make_float4(x[0], x[1], x[2], x[3]);
+                v[i][1] = make_float4(x[4], x[5], x[6], x[7]);
             }
-            if (ch + 1 < chunks) load_chunk(ch + 1, raw_next);  // arrives while this chunk is transformed
+            if constexpr (ACC) load_chunk(ch + 1, raw);  // arrives while this chunk is transformed (past the end: zeros)
 #pragma unroll
             for (int h = 1; h < R0; h <<= 1)
 #pragma unroll
@@ -164,9 +191,9 @@ __device__ __forceinline__ void sors_strip_body(const SorsArgs &g, int chunks, f
                     }
 #pragma unroll
             for (int i = 0; i < R0; ++i) {
-                const int at = sors_phys(tid + i * 256);
-                planes[at] = v[i][0];
-                planes[S::SLOTS + at] = v[i][1];
+                float4 *p = planes + sors_phys(tid) + 272 * i;  // token tid + 256 i
+                p[0] = v[i][0];
+                p[S::SLOTS] = v[i][1];
             }
         }
         __syncthreads();
@@ -187,9 +214,24 @@ __device__ __forceinline__ void sors_strip_body(const SorsArgs &g, int chunks, f
                     acc[m][u][1].x += sgn * b.x, acc[m][u][1].y += sgn * b.y, acc[m][u][1].z += sgn * b.z, acc[m][u][1].w += sgn * b.w;
                 }
             __syncthreads();  // the next chunk overwrites the planes
-#pragma unroll
-            for (int i = 0; i < R0; ++i) raw[i] = raw_next[i];
         }
+    }
+
+    float *wave_sums = reinterpret_cast<float *>(sign_words);  // (the signs are behind a barrier) 8 per wave and strip
+    if constexpr (SUMS) {
+        // Over the lanes of a strip in fixed order: three exchanges leave each lane one of the eight columns, the others add.
+        const int lane = (int)threadIdx.x % 64 / NPROB;
+#pragma unroll
+        for (int h = 4; h > 0; h >>= 1)
+#pragma unroll
+            for (int c = 0; c < h; ++c) {
+                const bool up = (lane & h) != 0;
+                const float keep = up ? sums[c + h] : sums[c], give = up ? sums[c] : sums[c + h];
+                sums[c] = keep + __shfl_xor(give, h * NPROB);
+            }
+#pragma unroll
+        for (int h = 8; h < 64 / NPROB; h <<= 1) sums[0] += __shfl_xor(sums[0], h * NPROB);
+        if (lane < 8) wave_sums[((int)threadIdx.x / 64 * NPROB + prob) * 8 + lane] = sums[0];
     }
 
     auto store_row = [&](int64_t j, const float4 &a, const float4 &b) {
@@ -218,6 +260,16 @@ __device__ __forceinline__ void sors_strip_body(const SorsArgs &g, int chunks, f
                 const int at = sors_phys((int)(w.w[u] & g.st.row_mask));
                 store_row(j, planes[at], planes[S::SLOTS + at]);
             }
+        }
+    }
+    if constexpr (SUMS) {
+        __syncthreads();
+        if (tid < 8 && live) {
+            float x = 0.0f;
+#pragma unroll
+            for (int w = 0; w < 4 * NPROB; ++w) x += wave_sums[(w * NPROB + prob) * 8 + tid];
+            if (g.accumulate) x += load_f32<bf16_t>(g.colsum + col0 + tid);
+            store_f32<bf16_t>(g.colsum + col0 + tid, x);
         }
     }
 }

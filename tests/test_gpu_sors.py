@@ -147,3 +147,21 @@ def test_paired_launch_gives_the_bits_of_the_separate_launches(name):
     X2, W2, dY2 = synth.layer_inputs(4096, 776, 3080, "bf16", (7, 8, 9))
     if rmm.rmm_uses_paired_launch(4096, 776, 3080, 300, torch.bfloat16, SORS, binding.OP_FORWARD):
         check_layer(X2, W2, dY2, 300, SORS, 0xFEED, 3, "bf16", label="sors paired, odd strips")
+
+
+@pytest.mark.parametrize("n,d_out,k", [(1, 8, 1), (100, 24, 40), (300, 40, 70), (700, 136, 64), (2000, 24, 2000), (4000, 16, 2050),
+                                       (4097, 776, 300), (5000, 264, 2048), (5000, 24, 2050), (16384, 136, 100)])
+def test_bias_gradient_from_the_strips(n, d_out, k):
+    """Column sums of dY taken by the strip kernels (every chunk length, one and several chunks, two strips to a
+    work-group), by the column-sum kernel where those do not serve, and once more on top of what is there."""
+    d_in = 264
+    X, W, dY = synth.layer_inputs(n, d_in, d_out, "bf16", (n, d_out, k))
+    Xd, Wd, dYd = X.to(DEV), W.to(DEV), dY.to(DEV)
+    _, Xp = rmm.rmm_forward(Xd, Wd, None, k, SORS, 3, 4)
+    for need_dX in (True, False):
+        _, dW, db = rmm.rmm_backward(dYd, Wd, Xp, SORS, 3, 4, need_dX=need_dX, need_dbias=True)
+        want = synth.to_f64(dY).sum(axis=0)
+        assert_close(db, want, "db", "bf16", label="sors db %s" % ((n, d_out, k),))
+        first = synth.to_f64(db).copy()
+        rmm.rmm_backward(dYd, Wd, Xp, SORS, 3, 4, need_dX=need_dX, dW=dW, dbias=db, need_dbias=True, accumulate=True)
+        assert_close(db, want + first, "db", "bf16", label="sors db twice %s" % ((n, d_out, k),))
