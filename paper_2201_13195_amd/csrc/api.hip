@@ -37,18 +37,31 @@ bool use_mfma(const rmm_layer_desc_t *d) {
 }
 
 // Workspace layout.
-//   sketch / forward: fp32 partial sums of the token slices of S^T A (MFMA path only).
+//   sketch / forward: fp32 partial sums of the token slices of S^T A.
 //   backward: G = S^T dY (k x d_out, in the layer's dtype), then the partial sums.
+// fp32 has no token slices.  Nor has, off the MFMA path, rmm_sketch and the forward pass over an X whose width is no multiple of 8:
+// they have never asked for scratch, and callers may rely on it.
 size_t g_bytes(const rmm_layer_desc_t *d) { return round_up((size_t)d->k * d->d_out * elem_bytes(d->dtype), 256); }
 // (the SORS kind has no token slices: its sketch products need no scratch)
 bool sliced_sketch(const rmm_layer_desc_t *d) { return use_mfma(d) && d->kind != RMM_SKETCH_SORS; }
 size_t ws_sketch(const rmm_layer_desc_t *d) {
     return sliced_sketch(d) ? round_up(sketch_workspace_bf16(d->n, d->d_in, d->k), 256) : 0;
 }
+PlainSlices plain_forward_slices(const rmm_layer_desc_t *d) {
+    return d->dtype == RMM_DTYPE_BF16 && !use_mfma(d) && d->d_in % 8 == 0 ? plain_slices(d->n, d->d_in, d->k, d->d_out, d->kind) : PlainSlices{1, 0, 0};
+}
+PlainSlices plain_backward_slices(const rmm_layer_desc_t *d) {
+    return d->dtype == RMM_DTYPE_BF16 && !use_mfma(d) ? plain_slices(d->n, d->d_out, d->k, d->d_in, d->kind) : PlainSlices{1, 0, 0};
+}
+size_t slices_bytes(const PlainSlices &cut) {
+    return cut.slices > 1 ? round_up((size_t)cut.slices * (size_t)cut.stride * sizeof(float), 256) : 0;
+}
 size_t ws_forward(const rmm_layer_desc_t *d) {
+    if (!use_mfma(d)) return slices_bytes(plain_forward_slices(d));
     return sliced_sketch(d) ? round_up(sketch_workspace_bf16(d->n, d->d_in, d->k, d->d_out), 256) : 0;
 }
 size_t ws_backward(const rmm_layer_desc_t *d) {
+    if (!use_mfma(d)) return g_bytes(d) + slices_bytes(plain_backward_slices(d));
     return g_bytes(d) + (sliced_sketch(d) ? round_up(sketch_workspace_bf16(d->n, d->d_out, d->k, d->d_in), 256) : 0);
 }
 
@@ -122,7 +135,8 @@ private:
 template <typename T>
 int sketch_impl(int64_t n, int64_t d, int64_t k, int kind, SketchState st, const void *A, void *out, bool mfma,
                 void *ws, hipStream_t stream, const StageEvents &ev = StageEvents(), int product_stage = RMM_STAGE_NONE,
-                int64_t d_other = 0, bool with_dbias = false, bf16_t *colsum = nullptr, bool accumulate = false) {
+                int64_t d_other = 0, bool with_dbias = false, bf16_t *colsum = nullptr, bool accumulate = false,
+                const PlainSlices &cut = PlainSlices{1, 0, 0}) {
     const bool timed = product_stage != RMM_STAGE_NONE && ev.stage == product_stage;
     if (kind == RMM_SKETCH_SORS && mfma && sors_fast_ok(n, d)) {  // fast transform; otherwise S is applied densely below
         StageScope scope(ev, product_stage, stream);
@@ -131,8 +145,8 @@ int sketch_impl(int64_t n, int64_t d, int64_t k, int kind, SketchState st, const
     if (mfma && kind != RMM_SKETCH_SORS)
         return from_hip(launch_sketch_bf16((const bf16_t *)A, (bf16_t *)out, n, d, k, kind, st, ws, stream,
                                            timed ? ev.begin : nullptr, timed ? ev.end : nullptr, d_other, with_dbias));
-    StageScope scope(ev, product_stage, stream);  // the plain path is one kernel
-    return from_hip(launch_forward_plain<T>((const T *)A, nullptr, nullptr, nullptr, (T *)out, n, d, d, k, kind, st, stream));
+    StageScope scope(ev, product_stage, stream);
+    return from_hip(launch_forward_plain<T>((const T *)A, nullptr, nullptr, nullptr, (T *)out, n, d, d, k, kind, st, stream, cut, ws));
 }
 
 // Whether a pass on the bf16 kernels launches its plain product together with its sketch product.
@@ -149,7 +163,7 @@ int forward_impl(const rmm_layer_desc_t *d, SketchState st, const void *X, const
     if (!mfma && X_proj != nullptr && !separate_stage(ev.stage)) {  // both products in one launch
         StageScope scope(ev, RMM_STAGE_FWD_PAIR, stream);
         return from_hip(launch_forward_plain<T>((const T *)X, (const T *)W, (const T *)bias, (T *)Y, (T *)X_proj, d->n,
-                                                d->d_in, d->d_out, d->k, d->kind, st, stream));
+                                                d->d_in, d->d_out, d->k, d->kind, st, stream, plain_forward_slices(d), ws));
     }
     if (X_proj != nullptr && sliced_sketch(d) && !separate_stage(ev.stage) &&
         pass_pair_available(d->k)) {
@@ -172,13 +186,13 @@ int forward_impl(const rmm_layer_desc_t *d, SketchState st, const void *X, const
                                          d->n, d->d_in, d->d_out,
                                          X_proj != nullptr && pass_is_paired(d, RMM_OP_FORWARD) ? d->k : 0, d->kind, stream)
                  : launch_forward_plain<T>((const T *)X, (const T *)W, (const T *)bias, (T *)Y, nullptr, d->n, d->d_in,
-                                           d->d_out, d->k, d->kind, st, stream);
+                                           d->d_out, d->k, d->kind, st, stream, PlainSlices{1, 0, 0}, nullptr);
         if (e != hipSuccess) return RMM_ERR_LAUNCH;
     }
     if (X_proj == nullptr) return RMM_OK;  // no backward pass will follow: nothing to keep
     StageScope scope(ev, RMM_STAGE_FWD_XPROJ, stream);
     return sketch_impl<T>(d->n, d->d_in, d->k, d->kind, st, X, X_proj, mfma, ws, stream, ev,
-                          RMM_STAGE_FWD_XPROJ_PRODUCT, d->d_out);
+                          RMM_STAGE_FWD_XPROJ_PRODUCT, d->d_out, false, nullptr, false, plain_forward_slices(d));
 }
 
 template <typename T>
@@ -205,7 +219,7 @@ int backward_impl(const rmm_layer_desc_t *d, SketchState st, const void *dY, con
     if (paired_plain) {  // dX, G and db in one launch
         StageScope scope(ev, RMM_STAGE_BWD_PAIR, stream);
         e = launch_backward_plain<T>((const T *)dY, (const T *)W, (T *)dX, G, ev.stage == RMM_STAGE_BWD_DBIAS ? nullptr : (T *)dbias,
-                                     d->n, d->d_in, d->d_out, d->k, d->kind, st, accumulate, stream);
+                                     d->n, d->d_in, d->d_out, d->k, d->kind, st, accumulate, stream, plain_backward_slices(d), (char *)ws + g_bytes(d));
         if (e != hipSuccess) return RMM_ERR_LAUNCH;
     }
     const bool paired = paired_plain || paired_sors || (sliced_sketch(d) && dX != nullptr && !separate_stage(ev.stage) &&
@@ -225,13 +239,13 @@ int backward_impl(const rmm_layer_desc_t *d, SketchState st, const void *dY, con
         e = mfma ? launch_linear_nn_bf16((const bf16_t *)dY, (const bf16_t *)W, (bf16_t *)dX, d->n, d->d_in, d->d_out,
                                          pass_is_paired(d, RMM_OP_BACKWARD) ? d->k : 0, d->kind, stream)
                  : launch_backward_plain<T>((const T *)dY, (const T *)W, (T *)dX, nullptr, nullptr, d->n, d->d_in,
-                                            d->d_out, d->k, d->kind, st, false, stream);
+                                            d->d_out, d->k, d->kind, st, false, stream, PlainSlices{1, 0, 0}, nullptr);
         if (e != hipSuccess) return RMM_ERR_LAUNCH;
     }
     if (!paired) {
         StageScope scope(ev, RMM_STAGE_BWD_G, stream);
         int rc = sketch_impl<T>(d->n, d->d_out, d->k, d->kind, st, dY, G, mfma, (char *)ws + g_bytes(d), stream, ev,
-                                RMM_STAGE_BWD_G_PRODUCT, d->d_in, dbias != nullptr, sors_db ? (bf16_t *)dbias : nullptr, accumulate);
+                                RMM_STAGE_BWD_G_PRODUCT, d->d_in, dbias != nullptr, sors_db ? (bf16_t *)dbias : nullptr, accumulate, plain_backward_slices(d));
         if (rc != RMM_OK) return rc;
     }
     if (mfma && dbias != nullptr && !db_done && !own_db_stage) {

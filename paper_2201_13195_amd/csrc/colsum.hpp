@@ -33,7 +33,7 @@ inline int64_t colsum_blocks(int64_t d, int64_t elem_bytes) {
 inline bool colsum_wide_ok(const void *A, int64_t d, int64_t elem_bytes) {  // 16-byte loads apply
     return (d * elem_bytes) % 16 == 0 && (reinterpret_cast<uintptr_t>(A) & 15u) == 0;
 }
-inline int64_t colsum_narrow_blocks(int64_t d) { return (d + 15) / 16; }
+inline int64_t colsum_narrow_blocks(int64_t d) { return (d + 7) / 8; }
 constexpr int kColsumLdsFloats = 256 * 9;  // 256 row groups x (8 columns + 1), the larger of the two forms
 
 // `lds` holds kColsumLdsFloats floats; block `blk` of `blocks`.
@@ -88,32 +88,37 @@ __device__ __forceinline__ void colsum_body(const ColsumArgs &g, float *lds, int
     }
 }
 
-// The same for widths that rule out 16-byte loads: 16 columns per work-group, 16 row
-// lanes per column with eight loads in flight each (latency bounds a thread's chain of loads: 64
-// columns and 4 row lanes without the unrolling took 75 us at 3000 x 1001).
+// The same for widths that rule out 16-byte loads: 8 columns per work-group, 32 row lanes per column with eight loads in
+// flight each.  Latency bounds a thread's chain of loads (backward with a bias, 3000 x 768 -> 1001, +-1 entries: 39 us; 16
+// columns and 16 lanes 63, 64 columns and 4 lanes 75).  Sixteen loads in flight cost the kernel these blocks share its third work-group per
+// compute unit.
 template <typename T>
-__device__ __forceinline__ void colsum_narrow_body(const ColsumArgs &g, float *lds, int64_t blk) {
+__device__ __forceinline__ void colsum_narrow_body(const ColsumArgs &g, float *lds, int64_t blk, int64_t blocks) {
     constexpr int U = 8;
     const T *A = reinterpret_cast<const T *>(g.A);
     T *out = reinterpret_cast<T *>(g.out);
-    const int cl = threadIdx.x & 15, rl = threadIdx.x >> 4;
-    const int64_t c = blk * 16 + cl;
+    {
+        const int64_t per = blocks / 8, rem = blocks % 8, x = blk % 8, r = blk / 8;
+        blk = x * per + (x < rem ? x : rem) + r;
+    }
+    const int cl = threadIdx.x & 7, rl = threadIdx.x >> 3;
+    const int64_t c = blk * 8 + cl;
     float s = 0.0f;
-    if (rl < 16 && c < g.d) {
-        for (int64_t r = rl; r < g.n; r += 16 * U) {
+    if (rl < 32 && c < g.d) {
+        for (int64_t r = rl; r < g.n; r += 32 * U) {
             float v[U];
 #pragma unroll
-            for (int u = 0; u < U; ++u) v[u] = r + 16 * u < g.n ? load_f32<T>(A + (r + 16 * u) * g.d + c) : 0.0f;
+            for (int u = 0; u < U; ++u) v[u] = load_f32<T>(A + min(r + 32 * u, g.n - 1) * g.d + c);
 #pragma unroll
-            for (int u = 0; u < U; ++u) s += v[u];
+            for (int u = 0; u < U; ++u) s += r + 32 * u < g.n ? v[u] : 0.0f;
         }
     }
-    if (rl < 16) lds[rl * 17 + cl] = s;
+    if (rl < 32) lds[rl * 9 + cl] = s;
     __syncthreads();
     if (rl == 0 && c < g.d) {
         float t = 0.0f;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) t += lds[r * 17 + cl];
+        for (int r = 0; r < 32; ++r) t += lds[r * 9 + cl];
         if (g.accumulate) t += load_f32<T>(out + c);
         store_f32<T>(out + c, t);
     }
@@ -122,7 +127,7 @@ __device__ __forceinline__ void colsum_narrow_body(const ColsumArgs &g, float *l
 template <typename T>
 __device__ __forceinline__ void colsum_any_body(const ColsumArgs &g, float *lds, int64_t blk, int64_t blocks) {
     if (g.lpr == 0)
-        colsum_narrow_body<T>(g, lds, blk);
+        colsum_narrow_body<T>(g, lds, blk, blocks);
     else
         colsum_body<T>(g, lds, blk, blocks);
 }

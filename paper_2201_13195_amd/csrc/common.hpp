@@ -39,14 +39,23 @@ __device__ __forceinline__ void store_f32<bf16_t>(bf16_t *p, float v) { *p = f32
 
 // fp32-matrix kernels (plain.hip): the fp32 data path, and the bf16 shapes the bf16 MFMA path does
 // not take.  One launch per call:
+//   Token slices of a bf16 pass's sketch product: `slices` runs of `chunk` tokens, their fp32 sums `stride` elements apart in
+//   scratch.  One slice: no scratch.
+struct PlainSlices {
+    int slices;
+    int64_t chunk, stride;
+};
+PlainSlices plain_slices(int64_t n, int64_t d, int64_t k, int64_t d_other, int kind);
 //   Y = X W^T (+ bias) and X_proj = S^T X; either output may be null
 template <typename T>
 hipError_t launch_forward_plain(const T *X, const T *W, const T *bias, T *Y, T *X_proj, int64_t n, int64_t d_in,
-                                int64_t d_out, int64_t k, int kind, SketchState st, hipStream_t stream);
+                                int64_t d_out, int64_t k, int kind, SketchState st, hipStream_t stream,
+                                const PlainSlices &cut, void *ws);
 //   dX = dY W, G = S^T dY and dbias = dY^T 1 (+ the old dbias); any output may be null
 template <typename T>
 hipError_t launch_backward_plain(const T *dY, const T *W, T *dX, T *G, T *dbias, int64_t n, int64_t d_in, int64_t d_out,
-                                 int64_t k, int kind, SketchState st, bool accumulate_dbias, hipStream_t stream);
+                                 int64_t k, int kind, SketchState st, bool accumulate_dbias, hipStream_t stream,
+                                 const PlainSlices &cut, void *ws);
 //   C[m x n] = A^T B (+ the old C if `accumulate`), A[kk x m], B[kk x n]
 template <typename Tin, typename Tout>
 hipError_t launch_tn_plain(const Tin *A, const Tin *B, Tout *C, int64_t m, int64_t n, int64_t kk, hipStream_t stream,

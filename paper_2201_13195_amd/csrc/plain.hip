@@ -59,8 +59,8 @@ hipError_t launch_pass(PlainLaunch &p, bool has_plain, bool has_sketch, bool b_r
     p.sketch_small = false;
     if (has_sketch) {
         // 32 x 32 tiles generate every entry four times as often as 32 x 128 tiles: only where those are few
-        p.sketch_small = p.cfg == PLAIN_TINY || (p.cfg == PLAIN_MID && tiles_of(p.gs, 32, 128) < 64);
-        p.sketch_blocks = (int)tiles_of(p.gs, 32, p.sketch_small ? 32 : 128);
+        p.sketch_small = mode == 0 || (p.gs.slices <= 1 && (p.cfg == PLAIN_TINY || (p.cfg == PLAIN_MID && tiles_of(p.gs, 32, 128) < 64)));
+        p.sketch_blocks = (int)tiles_of(p.gs, 32, p.sketch_small ? 32 : 128) * (p.gs.slices > 1 ? p.gs.slices : 1);
     }
     if constexpr (sizeof(T) == 2)
         return mode == 0 ? launch_plain_pass_far_bf16(p, b_rows_k, stream) : launch_plain_pass_bf16(p, b_rows_k, stream);
@@ -71,11 +71,40 @@ hipError_t launch_pass(PlainLaunch &p, bool has_plain, bool has_sketch, bool b_r
 }
 
 template <typename T>
-PlainArgs sketch_args(const T *A, T *out, int64_t n, int64_t d, int64_t k, int kind, SketchState st) {
+PlainArgs sketch_args(const T *A, T *out, int64_t n, int64_t d, int64_t k, int kind, SketchState st, const PlainSlices &cut, void *ws) {
     PlainArgs g{};
-    g.B = A, g.ldb = d, g.C = out, g.ldc = d, g.M = k, g.N = d, g.K = n, g.alpha = 1.0f / sqrtf((float)k);
+    g.B = A, g.ldb = d, g.C = cut.slices > 1 ? ws : (void *)out, g.ldc = d, g.M = k, g.N = d, g.K = n, g.alpha = 1.0f / sqrtf((float)k);
     g.kind = kind, g.st = st;
+    g.slices = cut.slices, g.k_chunk = cut.slices > 1 ? cut.chunk : n, g.split_stride = cut.stride;
     return g;
+}
+
+// out = alpha * the sum of the slices' sums, in their order.
+__global__ void __launch_bounds__(256) reduce_slices_kernel(const float *__restrict__ part, bf16_t *__restrict__ out, int64_t elems,
+                                                            int slices, int64_t stride, float alpha) {
+    const int64_t e = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 2;  // (stride is even)
+    if (e >= elems) return;
+    float2 s = *reinterpret_cast<const float2 *>(part + e);
+#pragma unroll 8
+    for (int z = 1; z < slices; ++z) {
+        const float2 p = *reinterpret_cast<const float2 *>(part + z * stride + e);
+        s.x += p.x, s.y += p.y;
+    }
+    if (e + 1 < elems)
+        *reinterpret_cast<uint32_t *>(out + e) = (uint32_t)f32_to_bf16(alpha * s.x) | ((uint32_t)f32_to_bf16(alpha * s.y) << 16);
+    else
+        out[e] = f32_to_bf16(alpha * s.x);
+}
+
+// The slices of a pass's sketch product are its last launch.
+template <typename T>
+hipError_t finish_slices(const PlainArgs &gs, T *out, hipStream_t stream) {
+    if constexpr (sizeof(T) == 2) {
+        const int64_t elems = gs.M * gs.N;
+        reduce_slices_kernel<<<(unsigned)((elems + 511) / 512), 256, 0, stream>>>((const float *)gs.C, out, elems, gs.slices,
+                                                                                  gs.split_stride, gs.alpha);
+    }
+    return hipGetLastError();
 }
 
 template <typename T, typename Tout, int MODE>
@@ -115,29 +144,66 @@ __global__ void debug_sketch_tile_kernel(int kind, SketchState st, int64_t i0, i
 
 }  // namespace
 
+// Token slices of the sketch product of a bf16 pass (sketch of an n x d operand, beside a product n x d_other).  An entry is generated again for
+// every column tile, and generating is most of what a Gaussian sketch tile does, so few wide tiles are wanted; slices make them
+// many.  Modelled in us per pass, from what the tiles take alone: a 32 x 32 sketch tile 9 ns per token (+-1 entries 4.8), a
+// 32 x 128 one 15 (9) and two on a compute unit 12 (6.5) each, a 64 x 64 tile of the other product 10 ns per contraction element and a 32 x 32 one 7; a launch ends no
+// sooner than its longest tile, nor than all its tiles on 256 compute units; slices add a launch of 4.5 us that reads
+// their sums.  3000 x 768 -> 1001, Gaussian, k = 300: forward 48 us in one slice, 36 in
+// two, 41 in four; backward 57, 47 in two and in four.  4096 x 1024 -> 111, k = 205: backward 62, 21 in eleven.  Where the two
+// come out alike (within 1 us) there are none.
+PlainSlices plain_slices(int64_t n, int64_t d, int64_t k, int64_t d_other, int kind) {
+    if (load_mode<bf16_t>(d, d_other) == 0) return PlainSlices{1, n, 0};
+    PlainArgs plain{}, sketch{};
+    plain.M = n, plain.N = d_other, plain.K = d, sketch.M = k, sketch.N = d, sketch.K = n;
+    const int cfg = plain_cfg<bf16_t>(plain, true);
+    const double per_cu = 1.0 / 256, chain = (cfg == PLAIN_TINY ? 7e-3 : 10e-3) * (double)d,
+                 plain_work = chain * (double)cfg_tiles(plain, cfg) * (cfg == PLAIN_BIG ? 4 : 1) * per_cu;
+    const double narrow = (kind == 0 ? 9e-3 : 4.8e-3) * (double)n, wide = (kind == 0 ? 15e-3 : 9e-3) * (double)n,
+                 wide_work = (kind == 0 ? 12e-3 : 6.5e-3) * (double)n * (double)tiles_of(sketch, 32, 128);
+    const int64_t tiles = tiles_of(sketch, 32, 128);
+    const bool small = cfg == PLAIN_TINY || (cfg == PLAIN_MID && tiles < 64);  // (launch_pass)
+    auto longest = [&](double sketch_chain, double sketch_work) {
+        const double most = sketch_chain > chain ? sketch_chain : chain, all = plain_work + sketch_work * per_cu;
+        return most > all ? most : all;
+    };
+    double best = (small ? longest(narrow, narrow * (double)tiles_of(sketch, 32, 32)) : longest(wide, wide_work)) - 1.0;
+    PlainSlices cut{1, n, 0};
+    for (int64_t s = 2; s <= 16; ++s) {
+        const int64_t chunk = ((n + s - 1) / s + 127) / 128 * 128, slices = (n + chunk - 1) / chunk;
+        if (slices != s || chunk < 256) continue;
+        const double t = longest(wide * (double)chunk / (double)n, wide_work) + 4.5 + 1e-6 * (double)(s * k * d);
+        if (t < best) best = t, cut = PlainSlices{(int)s, chunk, (k * d + 3) / 4 * 4};
+    }
+    return cut;
+}
+
 template <typename T>
 hipError_t launch_forward_plain(const T *X, const T *W, const T *bias, T *Y, T *X_proj, int64_t n, int64_t d_in,
-                                int64_t d_out, int64_t k, int kind, SketchState st, hipStream_t stream) {
+                                int64_t d_out, int64_t k, int kind, SketchState st, hipStream_t stream, const PlainSlices &cut, void *ws) {
     PlainLaunch p{};
     if (Y != nullptr) {
         p.ga.A = X, p.ga.lda = d_in, p.ga.B = W, p.ga.ldb = d_in, p.ga.C = Y, p.ga.ldc = d_out, p.ga.bias = bias;
         p.ga.M = n, p.ga.N = d_out, p.ga.K = d_in, p.ga.alpha = 1.0f;
     }
-    if (X_proj != nullptr) p.gs = sketch_args<T>(X, X_proj, n, d_in, k, kind, st);
-    return launch_pass<T>(p, Y != nullptr, X_proj != nullptr, false, load_mode<T>(d_in, d_in), stream);
+    if (X_proj != nullptr) p.gs = sketch_args<T>(X, X_proj, n, d_in, k, kind, st, cut, ws);
+    const hipError_t e = launch_pass<T>(p, Y != nullptr, X_proj != nullptr, false, load_mode<T>(d_in, d_in), stream);
+    return e != hipSuccess || cut.slices <= 1 || X_proj == nullptr ? e : finish_slices<T>(p.gs, X_proj, stream);
 }
 
 template <typename T>
 hipError_t launch_backward_plain(const T *dY, const T *W, T *dX, T *G, T *dbias, int64_t n, int64_t d_in, int64_t d_out,
-                                 int64_t k, int kind, SketchState st, bool accumulate_dbias, hipStream_t stream) {
+                                 int64_t k, int kind, SketchState st, bool accumulate_dbias, hipStream_t stream, const PlainSlices &cut,
+                                 void *ws) {
     PlainLaunch p{};
     if (dX != nullptr) {
         p.ga.A = dY, p.ga.lda = d_out, p.ga.B = W, p.ga.ldb = d_in, p.ga.C = dX, p.ga.ldc = d_in;
         p.ga.M = n, p.ga.N = d_in, p.ga.K = d_out, p.ga.alpha = 1.0f;
     }
-    if (G != nullptr) p.gs = sketch_args<T>(dY, G, n, d_out, k, kind, st);
+    if (G != nullptr) p.gs = sketch_args<T>(dY, G, n, d_out, k, kind, st, cut, ws);
     if (dbias != nullptr) p.gc = colsum_args<T>(dY, dbias, n, d_out, accumulate_dbias, &p.colsum_blocks);
-    return launch_pass<T>(p, dX != nullptr, G != nullptr, true, load_mode<T>(d_in, d_out), stream);
+    const hipError_t e = launch_pass<T>(p, dX != nullptr, G != nullptr, true, load_mode<T>(d_in, d_out), stream);
+    return e != hipSuccess || cut.slices <= 1 || G == nullptr ? e : finish_slices<T>(p.gs, G, stream);
 }
 
 template <typename Tin, typename Tout>
@@ -176,9 +242,9 @@ hipError_t launch_debug_sketch_tile(int kind, SketchState st, int64_t i0, int64_
 
 #define RMM_INSTANTIATE(T)                                                                                           \
     template hipError_t launch_forward_plain<T>(const T *, const T *, const T *, T *, T *, int64_t, int64_t,         \
-                                                int64_t, int64_t, int, SketchState, hipStream_t);                    \
+                                                int64_t, int64_t, int, SketchState, hipStream_t, const PlainSlices &, void *);                    \
     template hipError_t launch_backward_plain<T>(const T *, const T *, T *, T *, T *, int64_t, int64_t, int64_t,     \
-                                                 int64_t, int, SketchState, bool, hipStream_t);                      \
+                                                 int64_t, int, SketchState, bool, hipStream_t, const PlainSlices &, void *);                      \
     template hipError_t launch_tn_plain<T, T>(const T *, const T *, T *, int64_t, int64_t, int64_t, hipStream_t,     \
                                               bool);                                                                 \
     template hipError_t launch_colsum<T>(const T *, T *, int64_t, int64_t, hipStream_t, bool);

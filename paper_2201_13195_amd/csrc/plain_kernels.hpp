@@ -51,6 +51,10 @@ struct PlainArgs {
     int accumulate;
     int kind;  // sketch operand only
     SketchState st;
+    // bf16 sketch products only: a tile's tokens in `slices` runs of k_chunk (a multiple of 128), a work-group each; with more
+    // than one they write fp32 sums, unscaled, split_stride elements apart, which reduce_slices_kernel adds.
+    int slices;
+    int64_t k_chunk, split_stride;
 };
 
 namespace {
@@ -264,16 +268,16 @@ __device__ __forceinline__ bf16x8_t sign_eight(int kind, const SketchState &st, 
     return out.v;
 }
 
-// One output by fp32 multiply-adds, unscaled; ends early where nothing can change the result any more.  A
+// One output (of the contraction's elements k_begin .. k_end) by fp32 multiply-adds, unscaled; ends early where nothing can change the result any more.  A
 // generated operand is made eight entries at a time (one generator call, eight loads of B in flight).
 template <typename T, int AMODE, int BMODE>
-__device__ __forceinline__ float plain_dot(const PlainArgs &g, int64_t r, int64_t c) {
+__device__ __forceinline__ float plain_dot(const PlainArgs &g, int64_t r, int64_t c, int64_t k_begin, int64_t k_end) {
     constexpr bool GEN = AMODE == PA_GAUSS || AMODE == PA_SIGN;
     constexpr int STEP = GEN ? 8 : 1;
     const T *A = reinterpret_cast<const T *>(g.A), *B = reinterpret_cast<const T *>(g.B);
     float sum = 0.0f;
 #pragma unroll 1
-    for (int64_t k0 = 0; k0 < g.K && sum == sum; k0 += STEP) {
+    for (int64_t k0 = k_begin; k0 < k_end && sum == sum; k0 += STEP) {
         float a[STEP];
         if constexpr (AMODE == PA_GAUSS) {
             gauss_eight_precise(g.st, (uint32_t)k0, (uint32_t)r, a);
@@ -287,7 +291,7 @@ __device__ __forceinline__ float plain_dot(const PlainArgs &g, int64_t r, int64_
         float b[STEP];
 #pragma unroll
         for (int u = 0; u < STEP; ++u)  // (entries beyond the contraction meet zeros)
-            b[u] = !GEN || k0 + u < g.K ? load_f32<T>(BMODE == PB_K ? B + c * g.ldb + k0 + u : B + (k0 + u) * g.ldb + c) : 0.0f;
+            b[u] = !GEN || k0 + u < k_end ? load_f32<T>(BMODE == PB_K ? B + c * g.ldb + k0 + u : B + (k0 + u) * g.ldb + c) : 0.0f;
 #pragma unroll
         for (int u = 0; u < STEP; ++u) sum = fmaf(a[u], b[u], sum);
     }
@@ -304,15 +308,26 @@ __device__ __forceinline__ void plain_tile(const PlainArgs &g, bf16_t *lds, int6
     const int kg = wave / (S::WM * S::WN), wm = wave % (S::WM * S::WN) / S::WN, wn = wave % S::WN;
     // Work-groups are dealt round-robin to the 8 XCDs: give each a contiguous run of positions, walked
     // in bands of 8 tile rows, so that work-groups that run together on one XCD share operands in its L2.
-    const int64_t tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN;
-    int64_t tile;
+    // (32 bits: a grid has fewer than 2^31 work-groups, and a division of 64 bits is a microsecond in front of the first load)
+    const uint32_t tiles_m = (uint32_t)((g.M + BM - 1) / BM), tiles_n = (uint32_t)((g.N + BN - 1) / BN);
+    uint32_t tile;
     {
-        const int64_t per = blocks / 8, rem = blocks % 8, x = block % 8, r = block / 8;
+        const uint32_t per = (uint32_t)blocks / 8, rem = (uint32_t)blocks % 8, x = (uint32_t)block % 8, r = (uint32_t)block / 8;
         tile = x * per + (x < rem ? x : rem) + r;
     }
-    const int64_t band = tile / (8 * tiles_n), in_band = tile % (8 * tiles_n);
-    const int64_t band_rows = min((int64_t)8, tiles_m - band * 8);
-    const int64_t m0 = (band * 8 + in_band % band_rows) * BM, n0 = (in_band / band_rows) * BN;
+    constexpr bool GEN = AMODE == PA_GAUSS || AMODE == PA_SIGN, SLICED = GEN && sizeof(T) == 2;
+    int64_t slice = 0, k_begin = 0, k_end = g.K;
+    if constexpr (SLICED) {
+        if (g.slices > 1) {  // (neighbours in a run of positions share their slice's rows of B)
+            const uint32_t s = __builtin_amdgcn_readfirstlane(tile / (tiles_m * tiles_n));
+            tile -= s * (tiles_m * tiles_n);
+            slice = s, k_begin = s * g.k_chunk, k_end = min(k_end, k_begin + g.k_chunk);
+        }
+    }
+    const int64_t len = k_end - k_begin;
+    const uint32_t band = tile / (8 * tiles_n), in_band = tile - band * (8 * tiles_n);
+    const uint32_t band_rows = min(8u, tiles_m - band * 8), in_col = in_band / band_rows;
+    const int64_t m0 = (int64_t)(band * 8 + in_band - in_col * band_rows) * BM, n0 = (int64_t)in_col * BN;
 
     // With planes, the products of the two first planes are summed apart from the others, which are 2^-8 of them, and where a
     // wave has the whole contraction of a row-indexed operand (dX, dW) those of every other 16 elements in a sum of their
@@ -332,7 +347,6 @@ __device__ __forceinline__ void plain_tile(const PlainArgs &g, bf16_t *lds, int6
                 if constexpr (PLANES) low[a][b][v] = 0.0f;
             }
 
-    constexpr bool GEN = AMODE == PA_GAUSS || AMODE == PA_SIGN;
     typedef PlainLoader<T, BN, BK, BMODE == PB_K, MODE, L::SB, L::B_PLANE> LoadB;
     typedef std::conditional_t<GEN, LoadB, PlainLoader<T, GEN ? BN : BM, BK, AMODE == PA_K, MODE, L::SA, L::A_PLANE>> LoadA;
     [[maybe_unused]] LoadA la;  // (not used by a generated operand)
@@ -340,12 +354,12 @@ __device__ __forceinline__ void plain_tile(const PlainArgs &g, bf16_t *lds, int6
     typename LoadA::Regs va[2];
     typename LoadB::Regs vb[2];
     if constexpr (!GEN) la.init(reinterpret_cast<const T *>(g.A), g.lda, m0, g.M, tid);
-    lb.init(reinterpret_cast<const T *>(g.B), g.ldb, n0, g.N, tid);
+    lb.init(reinterpret_cast<const T *>(g.B) + (SLICED ? k_begin * g.ldb : 0), g.ldb, n0, g.N, tid);
 
     int64_t asked = 0;  // contraction elements requested so far
     auto issue = [&](int set) {
-        if constexpr (!GEN) la.load(va[set], g.K - asked);
-        lb.load(vb[set], g.K - asked);
+        if constexpr (!GEN) la.load(va[set], len - asked);
+        lb.load(vb[set], len - asked);
         asked += BK;
     };
     // Writes tile t (in register set `set`) into LDS stage `set`.  A generated tile is made here: one
@@ -359,7 +373,7 @@ __device__ __forceinline__ void plain_tile(const PlainArgs &g, bf16_t *lds, int6
             static_assert(CALLS % 64 == 0 && TURNS * CALLS == kPlainThreads, "whole waves take turns");
             if (TURNS == 1 || tid / CALLS == (int)(t % TURNS)) {
                 const int c = tid % CALLS, j = c / (BK / 8), kc = c % (BK / 8);
-                const uint32_t tok = (uint32_t)(t * BK + kc * 8), col = (uint32_t)(m0 + j);
+                const uint32_t tok = (uint32_t)(k_begin + t * BK + kc * 8), col = (uint32_t)(m0 + j);
                 bf16_t *to = As + j * L::SA + kchunk_pos<BK>(j, kc) * 8;
                 if constexpr (AMODE == PA_GAUSS) {
                     float e[8];
@@ -373,9 +387,9 @@ __device__ __forceinline__ void plain_tile(const PlainArgs &g, bf16_t *lds, int6
                 }
             }
         } else {
-            la.store(va[set], As, g.K - t * BK);
+            la.store(va[set], As, len - t * BK);
         }
-        lb.store(vb[set], Bs, g.K - t * BK);
+        lb.store(vb[set], Bs, len - t * BK);
     };
     constexpr int STEPS = BK / 16 / S::WK;  // 16-deep contraction steps per tile and wave
     struct Frags {
@@ -420,7 +434,7 @@ __device__ __forceinline__ void plain_tile(const PlainArgs &g, bf16_t *lds, int6
 
     // Two LDS stages, two register sets: while tile t is multiplied, t+1 goes from registers to LDS and
     // t+3 is requested (past the end: zeros).
-    const int64_t num = (g.K + BK - 1) / BK;
+    const int64_t num = (len + BK - 1) / BK;
     // Short chains of fp32 tiles: those past the end are not split (256 x 128 -> 128: 18.6 -> 16 us a step).  Elsewhere the
     // branch costs more (Y 4096 x 768 -> 3072: 162 -> 175 us).
     constexpr bool SKIP = PB == 3 && S::WK == 8;
@@ -464,7 +478,14 @@ __device__ __forceinline__ void plain_tile(const PlainArgs &g, bf16_t *lds, int6
     const T *bias = reinterpret_cast<const T *>(g.bias);
     const int half = lane >> 5;
     const float alpha = g.alpha * (PA == 3 && !GEN ? kSplitDown : 1.0f) * (PB == 3 ? kSplitDown : 1.0f);  // (exact)
-    auto write = [&](int64_t r, int64_t c, float x, float bv) {
+    auto write = [&](int64_t r, int64_t c, float x, float scale, float bv) {
+        if constexpr (SLICED) {
+            if (g.slices > 1) {
+                reinterpret_cast<float *>(g.C)[slice * g.split_stride + r * g.ldc + c] = x;
+                return;
+            }
+        }
+        x *= scale;
         if (g.bias != nullptr) x += bv;
         if (g.accumulate) x += load_f32<Tout>(C + r * g.ldc + c);
         store_f32<Tout>(C + r * g.ldc + c, x);
@@ -475,7 +496,7 @@ __device__ __forceinline__ void plain_tile(const PlainArgs &g, bf16_t *lds, int6
         if (PLANES && !__builtin_isfinite(x))  // made again below
             open |= 1u << e;
         else
-            write(r, c, alpha * x, bv);
+            write(r, c, x, alpha, bv);
     };
     auto bias_at = [&](int64_t c) { return bias != nullptr && c < g.N ? load_f32<T>(bias + c) : 0.0f; };
     auto row_of = [&](int v) { return 8 * (v / 4) + 4 * half + v % 4; };
@@ -517,7 +538,7 @@ __device__ __forceinline__ void plain_tile(const PlainArgs &g, bf16_t *lds, int6
                       w = S::WK > 1 ? 0 : e / 16 / TM;
             open &= open - 1;
             const int64_t r = m0 + wm * (BM / S::WM) + u * 32 + row_of(v), c = n0 + wn * (BN / S::WN) + w * 32 + (lane & 31);
-            write(r, c, g.alpha * plain_dot<T, AMODE, BMODE>(g, r, c), bias_at(c));
+            write(r, c, plain_dot<T, AMODE, BMODE>(g, r, c, k_begin, k_end), g.alpha, bias_at(c));
         }
     }
 }

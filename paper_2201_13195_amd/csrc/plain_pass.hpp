@@ -12,7 +12,7 @@ struct PlainLaunch {
     ColsumArgs gc;
     int plain_blocks, sketch_blocks, colsum_blocks;
     int cfg;            // tile shape of the plain product
-    bool sketch_small;  // the 32 x 32 tile for the sketch product (always with PLAIN_TINY, never with PLAIN_BIG)
+    bool sketch_small;  // the 32 x 32 tile for the sketch product (never with PLAIN_BIG)
 };
 
 // One for each element type and way of loading it (plain_kernels.hpp: MODE 4, 3, 0).
@@ -31,9 +31,14 @@ hipError_t launch_plain_pass_kind(const PlainLaunch &p, hipStream_t stream) {
     if constexpr (MODE == 0) {
         RMM_PLAIN_PASS(PlainTiny, PlainTiny);
     } else {
-        if (p.cfg == PLAIN_TINY)
-            RMM_PLAIN_PASS(PlainTiny, PlainTiny);
-        else if (p.cfg == PLAIN_BIG)
+        if (p.cfg == PLAIN_TINY) {
+            bool small = p.sketch_small || p.sketch_blocks == 0;
+            if constexpr (sizeof(T) == 4) small = true;  // (no slices)
+            if (small)
+                RMM_PLAIN_PASS(PlainTiny, PlainTiny);
+            else
+                RMM_PLAIN_PASS(PlainTiny, PlainSketch);
+        } else if (p.cfg == PLAIN_BIG)
             RMM_PLAIN_PASS(PlainBig, PlainSketch);
         else if (p.sketch_small)
             RMM_PLAIN_PASS(PlainMid, PlainTiny);

@@ -52,6 +52,32 @@ def test_bf16_widths_that_are_no_multiple_of_8(shape, kind):
     check_layer(X, W, dY, k, kind, 0x5EED0032, 6, "bf16", bias=bias, label="bf16 %s kind=%d" % (shape, kind))
 
 
+@pytest.mark.parametrize("kind", [rmm.GAUSSIAN, rmm.RADEMACHER, rmm.SORS])
+@pytest.mark.parametrize("shape", [(4001, 512, 77, 33), (4001, 77, 264, 65), (4096, 264, 35, 31)])
+def test_bf16_sketch_products_in_token_slices(shape, kind):
+    """Slices of unequal length, an odd number of sketch values, tiles with one row or column; the scratch is asked for."""
+    n, d_in, d_out, k = shape
+    fwd, bwd = (rmm.rmm_workspace_bytes(n, d_in, d_out, k, torch.bfloat16, kind, op) for op in (0, 1))
+    assert (fwd > 0) == (d_in % 8 == 0) and bwd > (k * d_out * 2 + 255) // 256 * 256
+    X, W, dY = synth.layer_inputs(n, d_in, d_out, "bf16", (n, d_in + 1, d_out + 2), w_std=1.0 / math.sqrt(d_in))
+    bias = synth.to_torch(synth.normal((d_out,), 16), "bf16")
+    check_layer(X, W, dY, k, kind, 0x5EED0034, 6, "bf16", bias=bias, label="sliced %s kind=%d" % (shape, kind))
+
+
+def test_an_infinity_in_one_token_slice():
+    """It meets every sketch column with the sign of its entry; the other columns do not see it."""
+    n, d_in, d_out, k = 4001, 512, 77, 33
+    X, W, _ = synth.layer_inputs(n, d_in, d_out, "bf16", (1, 2, 3), w_std=0.02)
+    X, W = X.to(DEV), W.to(DEV)
+    _, want = rmm.rmm_forward(X, W, None, k, rmm.GAUSSIAN, 9, 4)
+    X[3333, 100] = float("inf")
+    _, got = rmm.rmm_forward(X, W, None, k, rmm.GAUSSIAN, 9, 4)
+    P = rmm.rmm_debug_sketch_tile(rmm.GAUSSIAN, 9, 4, 3333, 0, 1, k)[0]
+    assert torch.equal(got[:, 100].float(), torch.copysign(torch.full_like(P, float("inf")), P))
+    got[:, 100] = want[:, 100]
+    assert torch.equal(got, want)
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_rows_beyond_the_descriptor_range(dtype):
     """Rows of 2^22 elements and more are loaded from 64-bit addresses."""
