@@ -41,17 +41,19 @@ bool use_mfma(const rmm_layer_desc_t *d) {
 //   backward: G = S^T dY (k x d_out, in the layer's dtype), then the partial sums.
 // fp32 has no token slices.  Nor has, off the MFMA path, rmm_sketch and the forward pass over an X whose width is no multiple of 8:
 // they have never asked for scratch, and callers may rely on it.
-size_t g_bytes(const rmm_layer_desc_t *d) { return round_up((size_t)d->k * d->d_out * elem_bytes(d->dtype), 256); }
+// (bf16: rows of G start on 16 bytes)
+int64_t g_row(const rmm_layer_desc_t *d) { return d->dtype == RMM_DTYPE_BF16 ? (d->d_out + 7) / 8 * 8 : d->d_out; }
+size_t g_bytes(const rmm_layer_desc_t *d) { return round_up((size_t)d->k * g_row(d) * elem_bytes(d->dtype), 256); }
 // (the SORS kind has no token slices: its sketch products need no scratch)
 bool sliced_sketch(const rmm_layer_desc_t *d) { return use_mfma(d) && d->kind != RMM_SKETCH_SORS; }
 size_t ws_sketch(const rmm_layer_desc_t *d) {
     return sliced_sketch(d) ? round_up(sketch_workspace_bf16(d->n, d->d_in, d->k), 256) : 0;
 }
 PlainSlices plain_forward_slices(const rmm_layer_desc_t *d) {
-    return d->dtype == RMM_DTYPE_BF16 && !use_mfma(d) && d->d_in % 8 == 0 ? plain_slices(d->n, d->d_in, d->k, d->d_out, d->kind) : PlainSlices{1, 0, 0};
+    return d->dtype == RMM_DTYPE_BF16 && !use_mfma(d) && d->d_in % 8 == 0 ? plain_slices(d->n, d->d_in, d->k, d->d_out, d->kind) : PlainSlices{1, 0, 0, 0};
 }
 PlainSlices plain_backward_slices(const rmm_layer_desc_t *d) {
-    return d->dtype == RMM_DTYPE_BF16 && !use_mfma(d) ? plain_slices(d->n, d->d_out, d->k, d->d_in, d->kind) : PlainSlices{1, 0, 0};
+    return d->dtype == RMM_DTYPE_BF16 && !use_mfma(d) ? plain_slices(d->n, d->d_out, d->k, d->d_in, d->kind) : PlainSlices{1, 0, 0, 0};
 }
 size_t slices_bytes(const PlainSlices &cut) {
     return cut.slices > 1 ? round_up((size_t)cut.slices * (size_t)cut.stride * sizeof(float), 256) : 0;
@@ -136,7 +138,7 @@ template <typename T>
 int sketch_impl(int64_t n, int64_t d, int64_t k, int kind, SketchState st, const void *A, void *out, bool mfma,
                 void *ws, hipStream_t stream, const StageEvents &ev = StageEvents(), int product_stage = RMM_STAGE_NONE,
                 int64_t d_other = 0, bool with_dbias = false, bf16_t *colsum = nullptr, bool accumulate = false,
-                const PlainSlices &cut = PlainSlices{1, 0, 0}) {
+                const PlainSlices &cut = PlainSlices{1, 0, 0, 0}) {
     const bool timed = product_stage != RMM_STAGE_NONE && ev.stage == product_stage;
     if (kind == RMM_SKETCH_SORS && mfma && sors_fast_ok(n, d)) {  // fast transform; otherwise S is applied densely below
         StageScope scope(ev, product_stage, stream);
@@ -186,7 +188,7 @@ int forward_impl(const rmm_layer_desc_t *d, SketchState st, const void *X, const
                                          d->n, d->d_in, d->d_out,
                                          X_proj != nullptr && pass_is_paired(d, RMM_OP_FORWARD) ? d->k : 0, d->kind, stream)
                  : launch_forward_plain<T>((const T *)X, (const T *)W, (const T *)bias, (T *)Y, nullptr, d->n, d->d_in,
-                                           d->d_out, d->k, d->kind, st, stream, PlainSlices{1, 0, 0}, nullptr);
+                                           d->d_out, d->k, d->kind, st, stream, PlainSlices{1, 0, 0, 0}, nullptr);
         if (e != hipSuccess) return RMM_ERR_LAUNCH;
     }
     if (X_proj == nullptr) return RMM_OK;  // no backward pass will follow: nothing to keep
@@ -239,7 +241,7 @@ int backward_impl(const rmm_layer_desc_t *d, SketchState st, const void *dY, con
         e = mfma ? launch_linear_nn_bf16((const bf16_t *)dY, (const bf16_t *)W, (bf16_t *)dX, d->n, d->d_in, d->d_out,
                                          pass_is_paired(d, RMM_OP_BACKWARD) ? d->k : 0, d->kind, stream)
                  : launch_backward_plain<T>((const T *)dY, (const T *)W, (T *)dX, nullptr, nullptr, d->n, d->d_in,
-                                            d->d_out, d->k, d->kind, st, false, stream, PlainSlices{1, 0, 0}, nullptr);
+                                            d->d_out, d->k, d->kind, st, false, stream, PlainSlices{1, 0, 0, 0}, nullptr);
         if (e != hipSuccess) return RMM_ERR_LAUNCH;
     }
     if (!paired) {
@@ -258,7 +260,7 @@ int backward_impl(const rmm_layer_desc_t *d, SketchState st, const void *dY, con
         StageScope scope(ev, RMM_STAGE_BWD_DW, stream);
         e = mfma ? launch_dw_bf16((const bf16_t *)G, (const bf16_t *)X_proj, (bf16_t *)dW, d->k, d->d_in, d->d_out,
                                   stream, accumulate)
-                 : launch_tn_plain<T, T>(G, (const T *)X_proj, (T *)dW, d->d_out, d->d_in, d->k, stream, accumulate);
+                 : launch_tn_plain<T, T>(G, g_row(d), (const T *)X_proj, (T *)dW, d->d_out, d->d_in, d->k, stream, accumulate);
         if (e != hipSuccess) return RMM_ERR_LAUNCH;
     }
     if (dbias != nullptr && !db_done) {
@@ -436,14 +438,14 @@ int rmm_variance_stats(const rmm_layer_desc_t *desc, const void *X, const void *
             e = launch_row_norms<bf16_t>((const bf16_t *)X, (const bf16_t *)dY, desc->n, desc->d_in, desc->d_out, rows, s);
             if (e != hipSuccess) return RMM_ERR_LAUNCH;
             float *P = (float *)((char *)ws + var_partial_bytes(desc));  // P(i, j) = sum_t X[t][i] dY[t][j]
-            e = launch_tn_plain<bf16_t, float>((const bf16_t *)X, (const bf16_t *)dY, P, desc->d_in, desc->d_out, desc->n, s);
+            e = launch_tn_plain<bf16_t, float>((const bf16_t *)X, desc->d_in, (const bf16_t *)dY, P, desc->d_in, desc->d_out, desc->n, s);
             if (e == hipSuccess) e = launch_sumsq(P, desc->d_in * desc->d_out, xty, s);
         }
     } else {
         e = launch_row_norms<float>((const float *)X, (const float *)dY, desc->n, desc->d_in, desc->d_out, rows, s);
         if (e != hipSuccess) return RMM_ERR_LAUNCH;
         float *P = (float *)((char *)ws + var_partial_bytes(desc));
-        e = launch_tn_plain<float, float>((const float *)X, (const float *)dY, P, desc->d_in, desc->d_out, desc->n, s);
+        e = launch_tn_plain<float, float>((const float *)X, desc->d_in, (const float *)dY, P, desc->d_in, desc->d_out, desc->n, s);
         if (e == hipSuccess) e = launch_sumsq(P, desc->d_in * desc->d_out, xty, s);
     }
     if (e != hipSuccess) return RMM_ERR_LAUNCH;

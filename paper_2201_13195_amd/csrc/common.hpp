@@ -40,10 +40,10 @@ __device__ __forceinline__ void store_f32<bf16_t>(bf16_t *p, float v) { *p = f32
 // fp32-matrix kernels (plain.hip): the fp32 data path, and the bf16 shapes the bf16 MFMA path does
 // not take.  One launch per call:
 //   Token slices of a bf16 pass's sketch product: `slices` runs of `chunk` tokens, their fp32 sums `stride` elements apart in
-//   scratch.  One slice: no scratch.
+//   scratch.  One slice: no scratch.  `ld`: row length of the result and of the sums (0: as wide as the operand).
 struct PlainSlices {
     int slices;
-    int64_t chunk, stride;
+    int64_t chunk, stride, ld;
 };
 PlainSlices plain_slices(int64_t n, int64_t d, int64_t k, int64_t d_other, int kind);
 //   Y = X W^T (+ bias) and X_proj = S^T X; either output may be null
@@ -58,7 +58,7 @@ hipError_t launch_backward_plain(const T *dY, const T *W, T *dX, T *G, T *dbias,
                                  const PlainSlices &cut, void *ws);
 //   C[m x n] = A^T B (+ the old C if `accumulate`), A[kk x m], B[kk x n]
 template <typename Tin, typename Tout>
-hipError_t launch_tn_plain(const Tin *A, const Tin *B, Tout *C, int64_t m, int64_t n, int64_t kk, hipStream_t stream,
+hipError_t launch_tn_plain(const Tin *A, int64_t lda, const Tin *B, Tout *C, int64_t m, int64_t n, int64_t kk, hipStream_t stream,
                            bool accumulate = false);
 //   out[d] = column sums of A[n x d] (+ the old out if `accumulate`).
 template <typename T>

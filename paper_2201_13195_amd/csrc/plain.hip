@@ -29,14 +29,17 @@ int64_t cfg_tiles(const PlainArgs &g, int cfg) {
     return tiles_of(g, e, e);
 }
 
-// How a launch loads its operands (rows of `a` and `b` elements): 4 = 16-byte loads (rows that start on 16
-// bytes), 3 = rows that start anywhere, 0 = rows too long for 32-bit offsets inside a tile of 128 of them.
+// How a launch loads its operands (rows of `a` and `b` elements): 4 = 16-byte loads (fp32, rows that start on 16
+// bytes), 3 = rows that start anywhere, 0 = rows too long for 32-bit offsets inside a tile of 128 of them.  bf16 operands
+// differ (rows_on_16): a row that starts anywhere costs a fifth dword, a funnel shift and its masks per eight
+// elements (Y 3000 x 768 -> 1001 23 us with it, 17 without).
 template <typename T>
 int load_mode(int64_t a, int64_t b) {
     const int64_t lim = (int64_t)1 << 22;
     if (a >= lim || b >= lim) return 0;
     return sizeof(T) == 4 && a % 4 == 0 && b % 4 == 0 ? 4 : 3;
 }
+bool rows_on_16(int64_t row) { return row % 8 == 0; }  // bf16
 
 template <typename T>
 __global__ void __launch_bounds__(256) colsum_kernel(ColsumArgs g) {
@@ -62,66 +65,71 @@ hipError_t launch_pass(PlainLaunch &p, bool has_plain, bool has_sketch, bool b_r
         p.sketch_small = mode == 0 || (p.gs.slices <= 1 && (p.cfg == PLAIN_TINY || (p.cfg == PLAIN_MID && tiles_of(p.gs, 32, 128) < 64)));
         p.sketch_blocks = (int)tiles_of(p.gs, 32, p.sketch_small ? 32 : 128) * (p.gs.slices > 1 ? p.gs.slices : 1);
     }
-    if constexpr (sizeof(T) == 2)
+    if constexpr (sizeof(T) == 2) {
+        const bool a16 = rows_on_16(has_plain ? p.ga.lda : p.gs.ldb), b16 = rows_on_16(has_plain ? p.ga.ldb : p.gs.ldb);
+        if (mode != 0 && !b_rows_k && a16 && b16) return launch_forward_pass_bf16x8(p, stream);
+        if (mode != 0 && b_rows_k && (!has_plain ? a16 : a16 && !b16)) return launch_backward_pass_bf16x8_(p, stream);
+        if (mode != 0 && b_rows_k && !a16 && b16) return launch_backward_pass_bf16_x8(p, stream);
         return mode == 0 ? launch_plain_pass_far_bf16(p, b_rows_k, stream) : launch_plain_pass_bf16(p, b_rows_k, stream);
-    else
+    } else {
         return mode == 0   ? launch_plain_pass_far_f32(p, b_rows_k, stream)
                : mode == 4 ? launch_plain_pass_f32x4(p, b_rows_k, stream)
                            : launch_plain_pass_f32(p, b_rows_k, stream);
+    }
 }
 
 template <typename T>
 PlainArgs sketch_args(const T *A, T *out, int64_t n, int64_t d, int64_t k, int kind, SketchState st, const PlainSlices &cut, void *ws) {
     PlainArgs g{};
-    g.B = A, g.ldb = d, g.C = cut.slices > 1 ? ws : (void *)out, g.ldc = d, g.M = k, g.N = d, g.K = n, g.alpha = 1.0f / sqrtf((float)k);
+    g.B = A, g.ldb = d, g.C = cut.slices > 1 ? ws : (void *)out, g.ldc = cut.ld != 0 ? cut.ld : d, g.M = k, g.N = d, g.K = n, g.alpha = 1.0f / sqrtf((float)k);
     g.kind = kind, g.st = st;
     g.slices = cut.slices, g.k_chunk = cut.slices > 1 ? cut.chunk : n, g.split_stride = cut.stride;
     return g;
 }
 
-// out = alpha * the sum of the slices' sums, in their order.
+// out = alpha * the sum of the slices' sums, in their order.  (Rows of a multiple of 8 values: what lies behind a row's
+// end is summed too, and used by nobody.)
 __global__ void __launch_bounds__(256) reduce_slices_kernel(const float *__restrict__ part, bf16_t *__restrict__ out, int64_t elems,
-                                                            int slices, int64_t stride, float alpha) {
-    const int64_t e = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 2;  // (stride is even)
+                                                            int slices, float alpha) {
+    const int64_t e = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4;
     if (e >= elems) return;
-    float2 s = *reinterpret_cast<const float2 *>(part + e);
+    float4 s = *reinterpret_cast<const float4 *>(part + e);
 #pragma unroll 8
     for (int z = 1; z < slices; ++z) {
-        const float2 p = *reinterpret_cast<const float2 *>(part + z * stride + e);
-        s.x += p.x, s.y += p.y;
+        const float4 p = *reinterpret_cast<const float4 *>(part + z * elems + e);
+        s.x += p.x, s.y += p.y, s.z += p.z, s.w += p.w;
     }
-    if (e + 1 < elems)
-        *reinterpret_cast<uint32_t *>(out + e) = (uint32_t)f32_to_bf16(alpha * s.x) | ((uint32_t)f32_to_bf16(alpha * s.y) << 16);
-    else
-        out[e] = f32_to_bf16(alpha * s.x);
+    uint2 o;
+    o.x = (uint32_t)f32_to_bf16(alpha * s.x) | ((uint32_t)f32_to_bf16(alpha * s.y) << 16);
+    o.y = (uint32_t)f32_to_bf16(alpha * s.z) | ((uint32_t)f32_to_bf16(alpha * s.w) << 16);
+    *reinterpret_cast<uint2 *>(out + e) = o;
 }
 
 // The slices of a pass's sketch product are its last launch.
 template <typename T>
 hipError_t finish_slices(const PlainArgs &gs, T *out, hipStream_t stream) {
     if constexpr (sizeof(T) == 2) {
-        const int64_t elems = gs.M * gs.N;
-        reduce_slices_kernel<<<(unsigned)((elems + 511) / 512), 256, 0, stream>>>((const float *)gs.C, out, elems, gs.slices,
-                                                                                  gs.split_stride, gs.alpha);
+        reduce_slices_kernel<<<(unsigned)((gs.split_stride + 1023) / 1024), 256, 0, stream>>>((const float *)gs.C, out, gs.split_stride,
+                                                                                              gs.slices, gs.alpha);
     }
     return hipGetLastError();
 }
 
-template <typename T, typename Tout, int MODE>
+template <typename T, typename Tout, int MODE_A, int MODE_B>
 hipError_t launch_tn(const PlainArgs &g, hipStream_t stream) {
-    const int cfg = MODE == 0 ? PLAIN_TINY : plain_cfg<T>(g, true);
+    const int cfg = MODE_A == 0 ? PLAIN_TINY : plain_cfg<T>(g, true);
     const unsigned grid = (unsigned)cfg_tiles(g, cfg);
-    if constexpr (MODE != 0) {
+    if constexpr (MODE_A != 0) {
         if (cfg == PLAIN_BIG) {
-            plain_tn_kernel<T, Tout, PlainBig, MODE><<<grid, kPlainThreads, 0, stream>>>(g);
+            plain_tn_kernel<T, Tout, PlainBig, MODE_A, MODE_B><<<grid, kPlainThreads, 0, stream>>>(g);
             return hipGetLastError();
         }
         if (cfg == PLAIN_MID) {
-            plain_tn_kernel<T, Tout, PlainMid, MODE><<<grid, kPlainThreads, 0, stream>>>(g);
+            plain_tn_kernel<T, Tout, PlainMid, MODE_A, MODE_B><<<grid, kPlainThreads, 0, stream>>>(g);
             return hipGetLastError();
         }
     }
-    plain_tn_kernel<T, Tout, PlainTiny, MODE><<<grid, kPlainThreads, 0, stream>>>(g);
+    plain_tn_kernel<T, Tout, PlainTiny, MODE_A, MODE_B><<<grid, kPlainThreads, 0, stream>>>(g);
     return hipGetLastError();
 }
 
@@ -144,20 +152,21 @@ __global__ void debug_sketch_tile_kernel(int kind, SketchState st, int64_t i0, i
 
 }  // namespace
 
-// Token slices of the sketch product of a bf16 pass (sketch of an n x d operand, beside a product n x d_other).  An entry is generated again for
-// every column tile, and generating is most of what a Gaussian sketch tile does, so few wide tiles are wanted; slices make them
-// many.  Modelled in us per pass, from what the tiles take alone: a 32 x 32 sketch tile 9 ns per token (+-1 entries 4.8), a
-// 32 x 128 one 15 (9) and two on a compute unit 12 (6.5) each, a 64 x 64 tile of the other product 10 ns per contraction element and a 32 x 32 one 7; a launch ends no
-// sooner than its longest tile, nor than all its tiles on 256 compute units; slices add a launch of 4.5 us that reads
-// their sums.  3000 x 768 -> 1001, Gaussian, k = 300: forward 48 us in one slice, 36 in
-// two, 41 in four; backward 57, 47 in two and in four.  4096 x 1024 -> 111, k = 205: backward 62, 21 in eleven.  Where the two
-// come out alike (within 1 us) there are none.
+// Token slices of the sketch product of a bf16 pass (sketch of an n x d operand, beside a product n x d_other).  An entry is
+// generated again for every column tile, and generating is most of what a Gaussian sketch tile does, so few wide tiles are
+// wanted; slices make them many.  Modelled in us per pass, from what the tiles take alone: a 32 x 32 sketch tile 9 ns per token
+// (+-1 entries 4.8), a 32 x 128 one 15 (9) and two on a compute unit 12 (6.5) each, a 64 x 64 tile of the other product 8 ns per
+// contraction element and a 32 x 32 one 6; a launch ends no sooner than its longest tile, nor than all its tiles on 256 compute
+// units; slices add a launch of 4.5 us that reads their sums.  3000 x 768 -> 1001, Gaussian, k = 300: forward 43 us in one
+// slice, 30 in two; backward 53, 43 in two.  4096 x 1024 -> 111, k = 205: backward 62, 20 in eleven.  Where the two come out
+// alike (within 1 us) there are none.
 PlainSlices plain_slices(int64_t n, int64_t d, int64_t k, int64_t d_other, int kind) {
-    if (load_mode<bf16_t>(d, d_other) == 0) return PlainSlices{1, n, 0};
+    PlainSlices cut{1, n, 0, (d + 7) / 8 * 8};
+    if (load_mode<bf16_t>(d, d_other) == 0) return cut;
     PlainArgs plain{}, sketch{};
     plain.M = n, plain.N = d_other, plain.K = d, sketch.M = k, sketch.N = d, sketch.K = n;
     const int cfg = plain_cfg<bf16_t>(plain, true);
-    const double per_cu = 1.0 / 256, chain = (cfg == PLAIN_TINY ? 7e-3 : 10e-3) * (double)d,
+    const double per_cu = 1.0 / 256, chain = (cfg == PLAIN_TINY ? 6e-3 : 8e-3) * (double)d,
                  plain_work = chain * (double)cfg_tiles(plain, cfg) * (cfg == PLAIN_BIG ? 4 : 1) * per_cu;
     const double narrow = (kind == 0 ? 9e-3 : 4.8e-3) * (double)n, wide = (kind == 0 ? 15e-3 : 9e-3) * (double)n,
                  wide_work = (kind == 0 ? 12e-3 : 6.5e-3) * (double)n * (double)tiles_of(sketch, 32, 128);
@@ -168,12 +177,11 @@ PlainSlices plain_slices(int64_t n, int64_t d, int64_t k, int64_t d_other, int k
         return most > all ? most : all;
     };
     double best = (small ? longest(narrow, narrow * (double)tiles_of(sketch, 32, 32)) : longest(wide, wide_work)) - 1.0;
-    PlainSlices cut{1, n, 0};
     for (int64_t s = 2; s <= 16; ++s) {
         const int64_t chunk = ((n + s - 1) / s + 127) / 128 * 128, slices = (n + chunk - 1) / chunk;
         if (slices != s || chunk < 256) continue;
         const double t = longest(wide * (double)chunk / (double)n, wide_work) + 4.5 + 1e-6 * (double)(s * k * d);
-        if (t < best) best = t, cut = PlainSlices{(int)s, chunk, (k * d + 3) / 4 * 4};
+        if (t < best) best = t, cut = PlainSlices{(int)s, chunk, k * cut.ld, cut.ld};
     }
     return cut;
 }
@@ -207,16 +215,19 @@ hipError_t launch_backward_plain(const T *dY, const T *W, T *dX, T *G, T *dbias,
 }
 
 template <typename Tin, typename Tout>
-hipError_t launch_tn_plain(const Tin *A, const Tin *B, Tout *C, int64_t m, int64_t n, int64_t kk, hipStream_t stream,
+hipError_t launch_tn_plain(const Tin *A, int64_t lda, const Tin *B, Tout *C, int64_t m, int64_t n, int64_t kk, hipStream_t stream,
                            bool accumulate) {
     PlainArgs g{};
-    g.A = A, g.lda = m, g.B = B, g.ldb = n, g.C = C, g.ldc = n, g.M = m, g.N = n, g.K = kk, g.alpha = 1.0f;
+    g.A = A, g.lda = lda, g.B = B, g.ldb = n, g.C = C, g.ldc = n, g.M = m, g.N = n, g.K = kk, g.alpha = 1.0f;
     g.accumulate = accumulate ? 1 : 0;
     const int mode = load_mode<Tin>(m, n);
-    if (mode == 0) return launch_tn<Tin, Tout, 0>(g, stream);
-    if constexpr (sizeof(Tin) == 4)
-        if (mode == 4) return launch_tn<Tin, Tout, 4>(g, stream);
-    return launch_tn<Tin, Tout, 3>(g, stream);
+    if (mode == 0) return launch_tn<Tin, Tout, 0, 0>(g, stream);
+    if constexpr (sizeof(Tin) == 4) {
+        if (mode == 4) return launch_tn<Tin, Tout, 4, 4>(g, stream);
+    } else if constexpr (sizeof(Tout) == 2) {  // (G has rows on 16 bytes)
+        if (rows_on_16(lda)) return rows_on_16(n) ? launch_tn<Tin, Tout, 4, 4>(g, stream) : launch_tn<Tin, Tout, 4, 3>(g, stream);
+    }
+    return launch_tn<Tin, Tout, 3, 3>(g, stream);
 }
 
 template <typename T>
@@ -245,13 +256,13 @@ hipError_t launch_debug_sketch_tile(int kind, SketchState st, int64_t i0, int64_
                                                 int64_t, int64_t, int, SketchState, hipStream_t, const PlainSlices &, void *);                    \
     template hipError_t launch_backward_plain<T>(const T *, const T *, T *, T *, T *, int64_t, int64_t, int64_t,     \
                                                  int64_t, int, SketchState, bool, hipStream_t, const PlainSlices &, void *);                      \
-    template hipError_t launch_tn_plain<T, T>(const T *, const T *, T *, int64_t, int64_t, int64_t, hipStream_t,     \
-                                              bool);                                                                 \
+    template hipError_t launch_tn_plain<T, T>(const T *, int64_t, const T *, T *, int64_t, int64_t, int64_t,         \
+                                              hipStream_t, bool);                                                    \
     template hipError_t launch_colsum<T>(const T *, T *, int64_t, int64_t, hipStream_t, bool);
 RMM_INSTANTIATE(float)
 RMM_INSTANTIATE(bf16_t)
 #undef RMM_INSTANTIATE
-template hipError_t launch_tn_plain<bf16_t, float>(const bf16_t *, const bf16_t *, float *, int64_t, int64_t, int64_t,
+template hipError_t launch_tn_plain<bf16_t, float>(const bf16_t *, int64_t, const bf16_t *, float *, int64_t, int64_t, int64_t,
                                                    hipStream_t, bool);
 
 }  // namespace rmm

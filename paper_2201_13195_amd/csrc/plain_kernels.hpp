@@ -73,9 +73,9 @@ typedef PlainShape<64, 64, 64, 2, 2, 2> PlainMid;      // four times as many til
 typedef PlainShape<32, 32, 128, 1, 1, 8> PlainTiny;    // few tiles: short chains, each wave an eighth of the contraction
 typedef PlainShape<32, 128, 64, 1, 4, 2> PlainSketch;  // sketch products: an entry is generated once per 128 columns
 
-// How operands are loaded: 4 = 16-byte buffer loads (fp32, every row on 16 bytes); 3 = the same for rows
-// that start anywhere (fp32 or bf16); both with 32-bit offsets inside a tile (rows below 2^22 elements).
-// 0 = element loads from 64-bit addresses, for longer rows.
+// How an operand is loaded: 4 = 16-byte buffer loads (every row on 16 bytes; bf16: a whole number of them); 3 = the same for
+// rows that start anywhere; both with 32-bit offsets inside a tile (rows below 2^22 elements).
+// 0 = element loads from 64-bit addresses, for longer rows.  Of bf16 operands in one product one may be 4 and the other 3.
 template <typename T>
 constexpr int plain_planes() { return sizeof(T) == 4 ? 3 : 1; }
 
@@ -131,9 +131,8 @@ constexpr float kSplitUp = 0x1p24f, kSplitDown = 0x1p-24f;
 template <typename T, int ROWS, int BK, bool KROWS, int MODE, int STRIDE, int PLANE>
 struct PlainLoader {
     static constexpr int CHUNKS = ROWS * BK / 8 / kPlainThreads, ES = (int)sizeof(T);
-    static constexpr int WORDS = MODE == 0 ? 8 : ES == 4 ? 8 : 5;  // registers of a chunk in flight
+    static constexpr int WORDS = MODE == 0 ? 8 : ES == 4 ? 8 : MODE == 4 ? 4 : 5;  // registers of a chunk in flight
     static_assert(ROWS * BK % (8 * kPlainThreads) == 0, "whole chunks per thread");
-    static_assert(MODE != 4 || ES == 4, "bf16 rows on 16 bytes are the other kernels' business");
     struct Regs {
         uint32_t v[CHUNKS][WORDS];
     };
@@ -148,7 +147,7 @@ struct PlainLoader {
     __device__ __forceinline__ void init(const T *operand, int64_t ld_, int64_t row0, int64_t rows, int tid) {
         ld = ld_, rows_left = rows - row0;
         base = operand + (MODE == 0 ? 0 : row0 * (KROWS ? ld : 1));
-        if constexpr (ES == 2 && MODE != 0) {  // descriptors start on a dword
+        if constexpr (ES == 2 && MODE == 3) {  // descriptors start on a dword
             skew = (uint32_t)(reinterpret_cast<uintptr_t>(base) & 2u);
             base -= skew / 2;
         }
@@ -194,7 +193,7 @@ struct PlainLoader {
 #pragma unroll
                     for (int u = 0; u < 4; ++u) g.v[q][4 * h + u] = w[u];
                 }
-                if constexpr (ES == 2)
+                if constexpr (ES == 2 && MODE == 3)
                     g.v[q][4] = __builtin_amdgcn_raw_buffer_load_b32(rsrc, !KROWS || kk[q] < l ? (off[q] & ~3u) + 16 : 0x80000000u, 0, 0);
             }
             base += KROWS ? BK : BK * ld;
@@ -205,7 +204,9 @@ struct PlainLoader {
         for (int q = 0; q < CHUNKS; ++q) {
             // (a select at the load would make every request wait for its data)
             const int valid = (int)max((int64_t)0, min((int64_t)8, KROWS ? left - kk[q] : (kk[q] < left ? (int64_t)8 : (int64_t)0)));
-            if constexpr (ES == 2) {
+            if constexpr (ES == 2 && MODE == 4) {  // (chunks lie wholly inside the operand or read as zeros)
+                *reinterpret_cast<u32x4_t *>(tile + at[q]) = (u32x4_t){g.v[q][0], g.v[q][1], g.v[q][2], g.v[q][3]};
+            } else if constexpr (ES == 2) {
                 uint32_t w[4];
                 if constexpr (MODE == 0) {
 #pragma unroll
@@ -299,7 +300,7 @@ __device__ __forceinline__ float plain_dot(const PlainArgs &g, int64_t r, int64_
 }
 
 // Output tile number `block` of `blocks`.
-template <typename T, typename Tout, typename S, int AMODE, int BMODE, int MODE>
+template <typename T, typename Tout, typename S, int AMODE, int BMODE, int MODE_A, int MODE_B>
 __device__ __forceinline__ void plain_tile(const PlainArgs &g, bf16_t *lds, int64_t block, int64_t blocks) {
     typedef PlainTile<T, S, AMODE, BMODE> L;
     constexpr int BM = S::BM, BN = S::BN, BK = S::BK, PA = L::PA, PB = L::PB;
@@ -347,8 +348,8 @@ __device__ __forceinline__ void plain_tile(const PlainArgs &g, bf16_t *lds, int6
                 if constexpr (PLANES) low[a][b][v] = 0.0f;
             }
 
-    typedef PlainLoader<T, BN, BK, BMODE == PB_K, MODE, L::SB, L::B_PLANE> LoadB;
-    typedef std::conditional_t<GEN, LoadB, PlainLoader<T, GEN ? BN : BM, BK, AMODE == PA_K, MODE, L::SA, L::A_PLANE>> LoadA;
+    typedef PlainLoader<T, BN, BK, BMODE == PB_K, MODE_B, L::SB, L::B_PLANE> LoadB;
+    typedef std::conditional_t<GEN, LoadB, PlainLoader<T, GEN ? BN : BM, BK, AMODE == PA_K, MODE_A, L::SA, L::A_PLANE>> LoadA;
     [[maybe_unused]] LoadA la;  // (not used by a generated operand)
     LoadB lb;
     typename LoadA::Regs va[2];
@@ -546,7 +547,8 @@ __device__ __forceinline__ void plain_tile(const PlainArgs &g, bf16_t *lds, int6
 // One launch for what a pass computes from one activation: `sketch_blocks` tiles of the sketch
 // product (first: they are the long ones), `colsum_blocks` column blocks of the bias gradient and
 // the tiles of the plain product.  Any of the three may be absent.
-template <typename T, typename S, typename SS, int SKETCH, int BMODE, int MODE>
+// (The operand of the sketch product is the plain product's A.)
+template <typename T, typename S, typename SS, int SKETCH, int BMODE, int MODE_A, int MODE_B>
 __global__ void __launch_bounds__(kPlainThreads) plain_pass_kernel(PlainArgs ga, PlainArgs gs, ColsumArgs gc, int plain_blocks,
                                                                    int sketch_blocks, int colsum_blocks) {
     constexpr int BA = PlainTile<T, S, PA_K, BMODE>::LDS_BYTES, BS = PlainTile<T, SS, SKETCH, PB_N>::LDS_BYTES;
@@ -554,18 +556,18 @@ __global__ void __launch_bounds__(kPlainThreads) plain_pass_kernel(PlainArgs ga,
     __shared__ __attribute__((aligned(16))) unsigned char lds[BYTES];
     const int b = (int)blockIdx.x;
     if (b < sketch_blocks)
-        plain_tile<T, T, SS, SKETCH, PB_N, MODE>(gs, reinterpret_cast<bf16_t *>(lds), b, sketch_blocks);
+        plain_tile<T, T, SS, SKETCH, PB_N, MODE_A, MODE_A>(gs, reinterpret_cast<bf16_t *>(lds), b, sketch_blocks);
     else if (b < sketch_blocks + colsum_blocks)
         colsum_any_body<T>(gc, reinterpret_cast<float *>(lds), b - sketch_blocks, colsum_blocks);
     else
-        plain_tile<T, T, S, PA_K, BMODE, MODE>(ga, reinterpret_cast<bf16_t *>(lds), b - sketch_blocks - colsum_blocks, plain_blocks);
+        plain_tile<T, T, S, PA_K, BMODE, MODE_A, MODE_B>(ga, reinterpret_cast<bf16_t *>(lds), b - sketch_blocks - colsum_blocks, plain_blocks);
 }
 
 // A^T B products (dW = G^T X_proj; X^T dY of the variance monitors).
-template <typename T, typename Tout, typename S, int MODE>
+template <typename T, typename Tout, typename S, int MODE_A, int MODE_B>
 __global__ void __launch_bounds__(kPlainThreads) plain_tn_kernel(PlainArgs g) {
     __shared__ __attribute__((aligned(16))) unsigned char lds[PlainTile<T, S, PA_M, PB_N>::LDS_BYTES];
-    plain_tile<T, Tout, S, PA_M, PB_N, MODE>(g, reinterpret_cast<bf16_t *>(lds), blockIdx.x, gridDim.x);
+    plain_tile<T, Tout, S, PA_M, PB_N, MODE_A, MODE_B>(g, reinterpret_cast<bf16_t *>(lds), blockIdx.x, gridDim.x);
 }
 
 }  // namespace

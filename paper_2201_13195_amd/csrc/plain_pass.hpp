@@ -15,18 +15,21 @@ struct PlainLaunch {
     bool sketch_small;  // the 32 x 32 tile for the sketch product (never with PLAIN_BIG)
 };
 
-// One for each element type and way of loading it (plain_kernels.hpp: MODE 4, 3, 0).
+// One for each element type and way of loading it (plain_kernels.hpp: MODE 4, 3, 0); bf16: of A, then of W.
 hipError_t launch_plain_pass_f32x4(const PlainLaunch &p, bool b_rows_k, hipStream_t stream);
 hipError_t launch_plain_pass_f32(const PlainLaunch &p, bool b_rows_k, hipStream_t stream);
-hipError_t launch_plain_pass_bf16(const PlainLaunch &p, bool b_rows_k, hipStream_t stream);
+hipError_t launch_plain_pass_bf16(const PlainLaunch &p, bool b_rows_k, hipStream_t stream);  // 3, 3
+hipError_t launch_forward_pass_bf16x8(const PlainLaunch &p, hipStream_t stream);             // 4, 4
+hipError_t launch_backward_pass_bf16_x8(const PlainLaunch &p, hipStream_t stream);           // 3, 4
+hipError_t launch_backward_pass_bf16x8_(const PlainLaunch &p, hipStream_t stream);           // 4, 3
 hipError_t launch_plain_pass_far_f32(const PlainLaunch &p, bool b_rows_k, hipStream_t stream);   // PLAIN_TINY only
 hipError_t launch_plain_pass_far_bf16(const PlainLaunch &p, bool b_rows_k, hipStream_t stream);  // PLAIN_TINY only
 
-template <typename T, int MODE, int BMODE, int SKETCH>
+template <typename T, int MODE, int MODE_B, int BMODE, int SKETCH>
 hipError_t launch_plain_pass_kind(const PlainLaunch &p, hipStream_t stream) {
     const unsigned grid = (unsigned)(p.plain_blocks + p.sketch_blocks + p.colsum_blocks);
 #define RMM_PLAIN_PASS(S, SS)                                                                                        \
-    plain_pass_kernel<T, S, SS, SKETCH, BMODE, MODE>                                                                 \
+    plain_pass_kernel<T, S, SS, SKETCH, BMODE, MODE, MODE_B>                                                                \
         <<<grid, kPlainThreads, 0, stream>>>(p.ga, p.gs, p.gc, p.plain_blocks, p.sketch_blocks, p.colsum_blocks)
     if constexpr (MODE == 0) {
         RMM_PLAIN_PASS(PlainTiny, PlainTiny);
@@ -49,13 +52,15 @@ hipError_t launch_plain_pass_kind(const PlainLaunch &p, hipStream_t stream) {
     return hipGetLastError();
 }
 
+template <typename T, int MODE, int MODE_B, int BMODE>
+hipError_t launch_plain_pass_rows(const PlainLaunch &p, hipStream_t stream) {
+    return p.gs.kind == 0 ? launch_plain_pass_kind<T, MODE, MODE_B, BMODE, PA_GAUSS>(p, stream)
+                          : launch_plain_pass_kind<T, MODE, MODE_B, BMODE, PA_SIGN>(p, stream);
+}
+
 template <typename T, int MODE>
 hipError_t launch_plain_pass_impl(const PlainLaunch &p, bool b_rows_k, hipStream_t stream) {
-    if (p.gs.kind == 0)
-        return b_rows_k ? launch_plain_pass_kind<T, MODE, PB_N, PA_GAUSS>(p, stream)
-                        : launch_plain_pass_kind<T, MODE, PB_K, PA_GAUSS>(p, stream);
-    return b_rows_k ? launch_plain_pass_kind<T, MODE, PB_N, PA_SIGN>(p, stream)
-                    : launch_plain_pass_kind<T, MODE, PB_K, PA_SIGN>(p, stream);
+    return b_rows_k ? launch_plain_pass_rows<T, MODE, MODE, PB_N>(p, stream) : launch_plain_pass_rows<T, MODE, MODE, PB_K>(p, stream);
 }
 
 }  // namespace rmm
