@@ -97,7 +97,7 @@ typedef Shape<64, 256, 64, 2, 4, 1> ShapeSkNarrow64;
 
 // A Box-Muller pair of bf16 entries from one word of a Philox call: the radius, then the pair.
 __device__ __forceinline__ float gauss_radius(uint32_t w) {
-    const float u1 = (float)(2u * (w >> 16) + 1u) * (1.0f / 131072.0f);
+    const float u1 = fmaf((float)(w >> 16), 1.0f / 65536.0f, 1.0f / 131072.0f);  // (exact)
     return __builtin_amdgcn_sqrtf(-1.3862943611198906f * __builtin_amdgcn_logf(u1));  // -2 ln2 log2 u1
 }
 __device__ __forceinline__ bf16x2_t gauss_pair(uint32_t w, float rad) {
