@@ -5,7 +5,8 @@
 // A work-group owns LPR x 16 bytes of every row (LPR = 4: 32 bf16 or 16 fp32 columns): thread t
 // (of the first 256) takes 16 bytes of rows t / LPR, t / LPR + 256 / LPR, ..., eight loads in
 // flight, and keeps fp32 sums of its 8 (4) columns; the row groups of a column are then added
-// through LDS in fixed order.  Column blocks that share a 128-byte line of A are numbered onto one
+// through LDS in fixed order, by all 256 threads (backward with a bias gradient, 4096 x 768 -> 768, k = 410: 29.4 us; with one
+// thread a column 32.1; 3001 x 520 -> 1304, k = 600: 35.2 and 37.3; fp32 2000 x 500 -> 1000, k = 200: 53.3 and 57.0).  Column blocks that share a 128-byte line of A are numbered onto one
 // XCD (work-groups are dealt round-robin to the 8 XCDs, each with its own L2), so HBM sees every
 // line once.  Narrow matrices take one 16-byte piece per work-group, so that enough work-groups
 // exist to pull the matrix in.  The result does not depend on the size of the work-group that runs
@@ -34,7 +35,7 @@ inline bool colsum_wide_ok(const void *A, int64_t d, int64_t elem_bytes) {  // 1
     return (d * elem_bytes) % 16 == 0 && (reinterpret_cast<uintptr_t>(A) & 15u) == 0;
 }
 inline int64_t colsum_narrow_blocks(int64_t d) { return (d + 7) / 8; }
-constexpr int kColsumLdsFloats = 256 * 9;  // 256 row groups x (8 columns + 1), the larger of the two forms
+constexpr int kColsumLdsFloats = 256 * 9 + 4 * 32;  // 256 row groups x (8 columns + 1), the larger of the two forms, and the waves' sums
 
 // `lds` holds kColsumLdsFloats floats; block `blk` of `blocks`.
 template <typename T>
@@ -79,10 +80,20 @@ __device__ __forceinline__ void colsum_body(const ColsumArgs &g, float *lds, int
         for (int e = 0; e < VEC; ++e) lds[rg * PITCH + cq * VEC + e] = acc[e];
     }
     __syncthreads();
+    // 256 threads add VEC row groups of a column each, the lanes of a wave those of a column, eight or more threads the four waves'.
+    float *waves = lds + 256 * (VEC + 1);
+    if (tid < 256) {
+        const int cc = tid % BC, part = tid / BC;
+        float s = 0.0f;
+#pragma unroll
+        for (int r = 0; r < VEC; ++r) s += lds[(part * VEC + r) * PITCH + cc];
+        for (int h = BC; h < 64; h <<= 1) s += __shfl_xor(s, h);
+        if ((tid & 63) < BC) waves[tid / 64 * BC + cc] = s;
+    }
+    __syncthreads();
     const int64_t col = blk * BC + tid;
     if (tid < BC && col < g.d) {
-        float s = 0.0f;
-        for (int r = 0; r < RPP; ++r) s += lds[r * PITCH + tid];
+        float s = waves[tid] + waves[BC + tid] + waves[2 * BC + tid] + waves[3 * BC + tid];
         if (g.accumulate) s += load_f32<T>(out + col);
         store_f32<T>(out + col, s);
     }
