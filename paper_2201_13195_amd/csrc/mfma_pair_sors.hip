@@ -27,7 +27,7 @@ __global__ void __launch_bounds__(SA::THREADS) gemm_sors_pair_kernel(GemmArgs ga
     if (plain >= 0 && plain < blocks_a)
         gemm_tile<SA, A_KCONTIG, BMODE_A, OUT_BF16>(ga, reinterpret_cast<bf16_t *>(lds), plain, blocks_a);
     else
-        sors_strip_body<kPairChunkLog, true, 2, SUMS>(gs, chunks, reinterpret_cast<float4 *>(lds),
+        sors_strip_body<kPairChunkLog, true, 2, 8, SUMS>(gs, chunks, reinterpret_cast<float4 *>(lds),
                                                 reinterpret_cast<uint32_t *>(lds + PLANE_BYTES),
                                                 sors_first ? (int64_t)blockIdx.x : (int64_t)blockIdx.x - blocks_a, strips);
 }

@@ -5,14 +5,15 @@
 //
 //   A_proj[j][c] = (1 / sqrt(k)) * sum_i (-1)^popcount(i AND r_j) * sigma_i * A[i][c]
 //
-// A work-group owns C neighbouring columns of A and all tokens.  It reads its C x n strip once
+// The layer's shapes run on the strip kernel of sors_kernels.hpp.  This file adds the one for many tokens and many sketch columns
+// (more than 4096 and 2048): a work-group owns C neighbouring columns of A and all tokens.  It reads its C x n strip once
 // (one load of C bf16 per token row), keeps it as fp32 in LDS (one plane of n_pad tokens per
 // column), runs the log2(n_pad) butterfly stages four at a time (a thread takes 16 tokens that
 // differ in the four index bits of the pass into registers, does the four stages there and puts
 // them back), and finally writes the k selected rows, scaled and rounded to bf16.  The first pass
 // is fused with the load and the sign flip.  Bound: one read of A from HBM.
 //
-// LDS layout: plane c starts at c * PLANE; token t sits at t + t / 16 (one float of padding per 16
+// Its LDS layout: plane c starts at c * PLANE; token t sits at t + t / 16 (one float of padding per 16
 // tokens), which keeps the 16-token-stride accesses of the last pass and the 64-consecutive-token
 // accesses of the other passes off each other's banks.
 #include "sors_kernels.hpp"
@@ -20,6 +21,8 @@
 namespace rmm {
 
 namespace {
+
+__device__ __forceinline__ int sors_phys(int t) { return t + (t >> 4); }
 
 template <int L>
 struct SorsShape {
@@ -168,20 +171,34 @@ __global__ void __launch_bounds__(256) sors_kernel(SorsArgs g) {
     }
 }
 
-template <int LC, bool ACC, bool SUMS>
-__global__ void __launch_bounds__(256) sors_strip_kernel(SorsArgs g, int chunks) {
-    __shared__ float4 planes[StripShape<LC>::REGION];
+// Eight waves a strip (four where a chunk has tokens for no more): two strips are resident on a compute unit, by LDS.
+template <int LC>
+constexpr int strip_waves() { return LC == 9 ? 4 : 8; }
+template <int LC, bool ACC, int NPROB, bool SUMS>
+__global__ void __launch_bounds__(64 * NPROB * strip_waves<LC>(), LC < 12 ? strip_waves<LC>() / 2 : 2) sors_strip_kernel(SorsArgs g, int chunks) {
+    __shared__ float4 planes[NPROB * StripShape<LC>::REGION];
     __shared__ uint32_t sign_words[1024];  // up to 32768 tokens
-    sors_strip_body<LC, ACC, 1, SUMS>(g, chunks, planes, sign_words, blockIdx.x, gridDim.x);
+    sors_strip_body<LC, ACC, NPROB, NPROB * strip_waves<LC>(), SUMS>(g, chunks, planes, sign_words, blockIdx.x, gridDim.x);
 }
 
+template <int LC, bool ACC, int NPROB>
+hipError_t launch_strips(const SorsArgs &g, int chunks, hipStream_t stream) {
+    const unsigned grid = (unsigned)((g.d / 8 + NPROB - 1) / NPROB), threads = 64 * NPROB * strip_waves<LC>();
+    if (g.colsum != nullptr)
+        sors_strip_kernel<LC, ACC, NPROB, true><<<grid, threads, 0, stream>>>(g, chunks);
+    else
+        sors_strip_kernel<LC, ACC, NPROB, false><<<grid, threads, 0, stream>>>(g, chunks);
+    return hipGetLastError();
+}
+
+// Two strips to a work-group where some compute unit has two anyway: a row is then 32 bytes of a line instead of 16, and half as many
+// lines go from L2 to the compute units, which at 16384 x 4096 is what the strips wait for (58 -> 51 us; 8192 x 4096 32.5 -> 28,
+// 4096 x 3072 17.0 -> 15.4; at 16384 x 1024, where every strip has a compute unit of its own, 26 -> 36).
 template <int LC, bool ACC>
 hipError_t launch_strip(const SorsArgs &g, int chunks, hipStream_t stream) {
-    if (g.colsum != nullptr)
-        sors_strip_kernel<LC, ACC, true><<<(unsigned)(g.d / 8), 256, 0, stream>>>(g, chunks);
-    else
-        sors_strip_kernel<LC, ACC, false><<<(unsigned)(g.d / 8), 256, 0, stream>>>(g, chunks);
-    return hipGetLastError();
+    if constexpr (LC == 11)
+        if (g.d / 8 > 256) return launch_strips<LC, ACC, 2>(g, chunks, stream);
+    return launch_strips<LC, ACC, 1>(g, chunks, stream);
 }
 
 template <int L>
@@ -198,7 +215,7 @@ int log2_ceil(int64_t n) {
 
 }  // namespace
 
-// (d: 256 rows stay inside one buffer descriptor's 2^31 bytes)
+// (d: the 64 rows of a load stay inside one buffer descriptor, below the offset that stands for none)
 bool sors_fast_ok(int64_t n, int64_t d) { return d % 8 == 0 && d < (1 << 22) && n >= 1 && n <= 32768; }
 
 bool sors_takes_colsum(int64_t n, int64_t k) { return k <= kSorsAccMaxK || n <= 4096; }
@@ -206,13 +223,12 @@ bool sors_takes_colsum(int64_t n, int64_t k) { return k <= kSorsAccMaxK || n <= 
 hipError_t launch_sors_bf16(const bf16_t *A, bf16_t *out, int64_t n, int64_t d, int64_t k, SketchState st,
                             hipStream_t stream, bf16_t *colsum, bool accumulate) {
     SorsArgs g{A, out, n, d, k, st, 1.0f / sqrtf((float)k), colsum, accumulate ? 1 : 0};
-    // A kernel's transform length is at least 256; for fewer tokens the rows drawn below n_pad
+    // A kernel's transform length is at least 512; for fewer tokens the rows drawn below n_pad
     // are rows of the larger Walsh-Hadamard matrix restricted to its leading n_pad x n_pad block,
     // which is the n_pad-point matrix itself.
-    const int l = log2_ceil(n) < 8 ? 8 : log2_ceil(n);
+    const int l = log2_ceil(n) < 9 ? 9 : log2_ceil(n);
     if (l >= 12 && k <= kSorsAccMaxK) return launch_strip<11, true>(g, 1 << (l - 11), stream);  // chunks of 2048 tokens
     switch (l) {
-        case 8: return launch_strip<8, false>(g, 1, stream);
         case 9: return launch_strip<9, false>(g, 1, stream);
         case 10: return launch_strip<10, false>(g, 1, stream);
         case 11: return launch_strip<11, false>(g, 1, stream);

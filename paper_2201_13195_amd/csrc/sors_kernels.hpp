@@ -2,6 +2,7 @@
 // header because it also runs inside the paired launches of a layer pass.
 #pragma once
 #include "common.hpp"
+#include "mfma_frag.hpp"
 
 namespace rmm {
 
@@ -19,67 +20,42 @@ namespace {
 
 typedef unsigned int sors_u32x4_t __attribute__((ext_vector_type(4)));
 typedef unsigned int sors_u32x2_t __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ int sors_phys(int t) { return t + (t >> 4); }
+__host__ __device__ constexpr int strip_phys(int t) { return t + (t >> 4) + 2 * (t >> 7); }
 
 // ---------------------------------------------------------------------------------------------
 // The kernel that serves the layer's shapes: strips of 8 columns (one 16-byte load per token row,
-// the widest strip whose fp32 copy fits in LDS next to a second work-group's), tokens taken in
+// the widest strip whose fp32 copy fits in LDS next to a second one), tokens taken in
 // chunks of CH = 2^LC.  The transform factors over the chunks,
 //
 //   out[j] = sum_chunks (-1)^popcount(hi(r_j) AND chunk) * T_chunk[lo(r_j)],
 //   T_chunk = the CH-point transform of the chunk's signed tokens,
 //
 // so a work-group runs one CH-point transform per chunk in the same LDS buffer and adds the
-// selected entries into per-thread accumulators (k <= 2048: 8 rows x 8 columns per thread), with
+// selected entries into per-thread accumulators (k <= 2048), with
 // the next chunk's rows already on their way from memory.  With a single chunk (CH >= n_pad) the
-// selected rows are written directly and k is not limited.  Per chunk: the top LC - 8 index bits
-// in registers while loading (2^(LC-8) rows per thread), then two LDS passes of four bits each,
-// 16-byte LDS accesses throughout.  LDS layout: two halves (columns 0-3, 4-7) of float4 slots,
-// token t at slot t + t / 16.  A backward pass with a bias gradient takes the column sums of dY here, where every
-// element passes through registers anyway: eight additions per row, ten lane exchanges at the end.  It saves the later launch
-// its read of dY (16384 x 1024 -> 1024, k = 1638: backward without the bias gradient 76 us, with it 103 before and 78 now;
-// 4096 x 768 -> 3072, k = 410: 60 -> 52).  A form of its own: with a branch on the argument the strips without sums went
-// from 78 us to 105 at 8192 x 4096.
+// selected rows are written directly and k is not limited.
+//
+// A chunk's index bits, lowest first, each wave on tokens of its own as long as it can: five on the matrix pipes (the 32 x 32
+// Walsh-Hadamard matrix times 32 tokens of 32 columns; the products are exact and the sums fp32), where the rows go as they are,
+// bf16 with their signs, through LDS into transposed fragments; one between the halves of two registers' lanes; tiles against tiles;
+// one between lanes 8 apart; then all through LDS as fp32, and the waves' bits in one pass, 16 bytes of a token at a time.  With
+// every bit after the top three in two LDS passes of vector additions the vector units were busy for 54 % of the time and
+// LDS for 41: 970 vector instructions a wave and chunk, 600 now, and twice the waves resident (16384 x 4096, k = 1638: 61 -> 51 us,
+// 16384 x 1024 39 -> 26, 4096 x 4096, k = 4000 44 -> 31, 4096 x 768, k = 410 11.9 -> 9.1).
+// LDS layout: two halves (columns 0-3, 4-7) of float4 slots, token t at slot strip_phys(t): the pads keep the sixteen-byte
+// accesses, and the four-byte ones of lanes that differ in column, token bits 0 and 2, strip and upper half, on banks of their own.
+//
+// A backward pass with a bias gradient takes the column sums of dY here, where every
+// element passes through registers anyway: two instructions per element, ten lane exchanges at the end.  It saves the later launch
+// its read of dY (16384 x 1024 -> 1024, k = 1638: backward without the bias gradient 66 us, with it 69; in a launch of its own
+// 19 us more).  A form of its own: with a branch on the argument the strips without sums went from 78 us to 105 at 8192 x 4096.
 template <int LC>
 struct StripShape {
-    static constexpr int CH = 1 << LC, W0 = LC - 8, R0 = 1 << W0, SLOTS = CH + CH / 16;
-    static constexpr int REGION = 2 * SLOTS + 4;  // float4 slots of one strip
-    static_assert(LC >= 8 && LC <= 12, "chunks of 256 .. 4096 tokens");
+    static constexpr int CH = 1 << LC, SLOTS = strip_phys(CH);
+    static constexpr int PLANE = SLOTS + 4, REGION = 2 * PLANE + 2;  // float4 slots of half a strip and of a strip
+    static_assert(LC >= 9 && LC <= 12, "chunks of 512 .. 4096 tokens");
 };
-constexpr int kSorsAccCalls = 2;                      // row-selection calls per thread with accumulators
-constexpr int64_t kSorsAccMaxK = 256 * 4 * kSorsAccCalls;  // 2048
-
-__device__ __forceinline__ void sors_butterflies4(float4 (&v)[16]) {
-#pragma unroll
-    for (int h = 1; h < 16; h <<= 1)
-#pragma unroll
-        for (int i = 0; i < 16; ++i)
-            if ((i & h) == 0) {
-                const float4 a = v[i], b = v[i + h];
-                v[i] = make_float4(a.x + b.x, a.y + b.y, a.z + b.z, a.w + b.w);
-                v[i + h] = make_float4(a.x - b.x, a.y - b.y, a.z - b.z, a.w - b.w);
-            }
-}
-
-// Index bits SHIFT .. SHIFT+3 of the chunk-local token index, both halves.  (The sixteen slots of an item lie STEP
-// apart, which the slot formula does not show the compiler: it would keep an address for each of them over the whole loop.)
-template <int LC, int SHIFT>
-__device__ __forceinline__ void strip_lds_pass(float4 *planes, int tid) {
-    typedef StripShape<LC> S;
-    static_assert(SHIFT == 0 || SHIFT == 4, "two passes");
-    constexpr int VEC = S::CH / 16, STEP = SHIFT == 0 ? 1 : 17;
-    for (int item = tid; item < 2 * VEC; item += 256) {
-        const int h = item / VEC, b = item % VEC;
-        const int low = b & ((1 << SHIFT) - 1), high = b >> SHIFT;
-        float4 *p = planes + h * S::SLOTS + sors_phys((high << (SHIFT + 4)) | low);
-        float4 v[16];
-#pragma unroll
-        for (int i = 0; i < 16; ++i) v[i] = p[STEP * i];
-        sors_butterflies4(v);
-#pragma unroll
-        for (int i = 0; i < 16; ++i) p[STEP * i] = v[i];
-    }
-}
+constexpr int64_t kSorsAccMaxK = 2048;  // sketch columns with accumulators
 
 //
 // NPROB = 2 puts two neighbouring strips into one work-group of 512 threads (thread 2r + p is
@@ -87,13 +63,16 @@ __device__ __forceinline__ void strip_lds_pass(float4 *planes, int tid) {
 // lanes of the two strips stay on different banks): the form that shares a grid with the 512-thread
 // work-groups of a plain product.  `block` of `blocks` numbers the work-group among those of the
 // sketch product; LDS: NPROB * StripShape::REGION float4 slots and 1024 words.
-template <int LC, bool ACC, int NPROB, bool SUMS>
+template <int LC, bool ACC, int NPROB, int WAVES, bool SUMS>
 __device__ __forceinline__ void sors_strip_body(const SorsArgs &g, int chunks, float4 *planes_all, uint32_t *sign_words,
                                                 int64_t block, int64_t blocks) {
     typedef StripShape<LC> S;
-    constexpr int CH = S::CH, R0 = S::R0;
+    // Threads of a strip; tokens of a wave, rows of one load of it, loads; tokens of a wave and strip in either plane, tiles of 64 of them
+    constexpr int CH = S::CH, NT = 64 * WAVES / NPROB, TW = CH / WAVES, LPW = 64 / NPROB, R0 = TW / LPW, TOP = NPROB == 2 ? TW : TW / 2,
+                  TILES = TOP / 64, ACC_CALLS = (int)kSorsAccMaxK / 4 / NT;
+    static_assert(TILES >= 1 && (NPROB == 1 || WAVES >= 8), "a tile per wave");
     const int prob = NPROB == 2 ? (int)(threadIdx.x & 1) : 0;
-    const int tid = NPROB == 2 ? (int)(threadIdx.x >> 1) : (int)threadIdx.x;  // thread number inside the strip, 0 .. 255
+    const int tid = NPROB == 2 ? (int)(threadIdx.x >> 1) : (int)threadIdx.x;  // thread number inside the strip
     float4 *planes = planes_all + prob * S::REGION;
 
     // Strips that share 128-byte lines of A should meet in one L2: work-groups are dealt round-robin
@@ -106,19 +85,19 @@ __device__ __forceinline__ void sors_strip_body(const SorsArgs &g, int chunks, f
     const int64_t col0 = (group * NPROB + prob) * 8;
     const bool live = col0 < g.d;  // the last work-group's second strip may not exist
 
-    for (int c = threadIdx.x; c < chunks * (CH / 128); c += 256 * NPROB) {
+    for (int c = threadIdx.x; c < chunks * (CH / 128); c += 64 * WAVES) {
         const Words4 w = philox4x32_10((uint32_t)c, kSorsSignColumn, g.st.off0, g.st.off1, g.st.key0, g.st.key1);
 #pragma unroll
         for (int q = 0; q < 4; ++q) sign_words[4 * c + q] = w.w[q];
     }
 
     // Rows of this thread's sketch columns and their accumulators (ACC only).
-    uint32_t rows[ACC ? kSorsAccCalls : 1][4];
-    float4 acc[ACC ? kSorsAccCalls : 1][4][2];
+    uint32_t rows[ACC ? ACC_CALLS : 1][4];
+    float4 acc[ACC ? ACC_CALLS : 1][4][2];
     if constexpr (ACC) {
 #pragma unroll
-        for (int m = 0; m < kSorsAccCalls; ++m) {
-            const Words4 w = philox4x32_10((uint32_t)(tid + 256 * m), kSorsRowColumn, g.st.off0, g.st.off1, g.st.key0,
+        for (int m = 0; m < ACC_CALLS; ++m) {
+            const Words4 w = philox4x32_10((uint32_t)(tid + NT * m), kSorsRowColumn, g.st.off0, g.st.off1, g.st.key0,
                                            g.st.key1);
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
@@ -128,19 +107,35 @@ __device__ __forceinline__ void sors_strip_body(const SorsArgs &g, int chunks, f
         }
     }
 
-    // Buffer loads: a row beyond the tokens lies outside the descriptor's range (256 rows each) and reads as zero, so
-    // there is no branch between the loads and the compiler can count them: with one it waited for the next chunk's rows in front of
-    // this chunk's transform.
-    const uint32_t off = live ? (uint32_t)((tid * g.d + col0) * 2) : 0x80000000u;
+    // Wave `wave` of the work-group loads, and transforms as far as it can alone, tokens wave * TW .. + TW - 1 of a chunk: row
+    // 8 columns of it per lane, for two strips those of either in turn.  Buffer loads: a row beyond the tokens lies outside the
+    // descriptor's range (one for each load) and reads as zero, so there is no branch between the loads and the compiler can count
+    // them: with one it waited for the next chunk's rows in front of this chunk's transform.
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), row = tid % LPW;
+    const uint32_t off = live ? (uint32_t)((row * g.d + col0) * 2) : 0x80000000u;
     auto load_chunk = [&](int ch, sors_u32x4_t (&raw)[R0]) {
 #pragma unroll
         for (int i = 0; i < R0; ++i) {
-            const int64_t t0 = (int64_t)ch * CH + i * 256, rows = min((int64_t)256, g.n - t0);
+            const int64_t t0 = (int64_t)ch * CH + wave * TW + i * LPW, rows = min((int64_t)LPW, g.n - t0);
             const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
                 const_cast<bf16_t *>(g.A + t0 * g.d), (short)0, __builtin_amdgcn_readfirstlane((int)((rows > 0 ? rows : 0) * g.d * 2)), 0x00020000);
             raw[i] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, off, 0, 0);
         }
     };
+    // The 32 x 32 Walsh-Hadamard matrix as an MFMA operand.
+    bf16x8_t hadamard[2];
+#pragma unroll
+    for (int kh = 0; kh < 2; ++kh) {
+        union {
+            bf16x8_t v;
+            uint16_t h[8];
+        } o;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) o.h[j] = (uint16_t)(0x3F80u | (uint32_t)(__popc((lane & 31) & (16 * kh + 8 * (lane >> 5) + j)) & 1) << 15);
+        hadamard[kh] = o.v;
+    }
+    float4 *mine = planes_all + strip_phys(wave * TW);  // slots of the wave's tokens (of the first strip), lower half; upper half: + PLANE
+    const float odd8 = (lane & 8) != 0 ? -1.0f : 1.0f;
 
     float sums[SUMS ? 8 : 1];
     if constexpr (SUMS)
@@ -150,66 +145,133 @@ __device__ __forceinline__ void sors_strip_body(const SorsArgs &g, int chunks, f
     load_chunk(0, raw);
     __syncthreads();  // sign words
     for (int ch = 0; ch < chunks; ++ch) {
-        // first pass: the chunk's top LC - 8 index bits, in registers, signs applied on the way
-        {
-            float4 v[R0][2];
+        // The chunk's rows with their signs, as they are, into the wave's part of LDS: 16 bytes per row, in the plane that lane bit 3
+        // of a transposed read picks (the upper half of its tokens; the strip, if there are two).
 #pragma unroll
-            for (int i = 0; i < R0; ++i) {
-                const int t = ch * CH + tid + i * 256;
-                const uint32_t flip = ((sign_words[t >> 5] >> (t & 31)) & 1u) << 31;
-                asm volatile("" : "+v"(raw[i]));  // (unpacked here: not before, in twice the registers)
-                float x[8];                      // (element 2q in the low half of word q)
+        for (int i = 0; i < R0; ++i) {
+            const int t = ch * CH + wave * TW + i * LPW + row;
+            const int flip = (int)(sign_words[t >> 5] << (31 - (t & 31))) >> 31;
+            asm volatile("" : "+v"(raw[i]));  // (unpacked here: not before, in twice the registers)
+            if constexpr (SUMS) {
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    x[2 * q] = __uint_as_float(raw[i][q] << 16);
-                    x[2 * q + 1] = __uint_as_float(raw[i][q] & 0xFFFF0000u);
-                }
-                if constexpr (SUMS) {
-#pragma unroll
-                    for (int c = 0; c < 8; ++c) {
-                        sums[c] += x[c];
-                        asm volatile("" : "+v"(sums[c]));  // (now: not after all rows, with a second copy of each)
-                    }
+                for (int q = 0; q < 4; ++q) {  // (element 2q in the low half of word q)
+                    sums[2 * q] += __uint_as_float(raw[i][q] << 16);
+                    sums[2 * q + 1] += __uint_as_float(raw[i][q] & 0xFFFF0000u);
                 }
 #pragma unroll
-                for (int c = 0; c < 8; ++c) x[c] = __uint_as_float(__float_as_uint(x[c]) ^ flip);
-                v[i][0] = make_float4(x[0], x[1], x[2], x[3]);
-                v[i][1] = make_float4(x[4], x[5], x[6], x[7]);
+                for (int c = 0; c < 8; ++c) asm volatile("" : "+v"(sums[c]));  // (now: not after all rows, with a second copy of each)
             }
-            if constexpr (ACC) load_chunk(ch + 1, raw);  // arrives while this chunk is transformed (past the end: zeros)
+            sors_u32x4_t w;
 #pragma unroll
-            for (int h = 1; h < R0; h <<= 1)
+            for (int q = 0; q < 4; ++q) w[q] = raw[i][q] ^ ((uint32_t)flip & 0x80008000u);
+            *reinterpret_cast<sors_u32x4_t *>(mine + (NPROB == 2 ? prob : i * LPW / TOP) * S::PLANE + i * LPW % TOP + row) = w;
+        }
+        if constexpr (ACC) load_chunk(ch + 1, raw);  // arrives while this chunk is transformed (past the end: zeros)
+        asm volatile("" ::: "memory");  // (the wave's own LDS accesses keep their order)
+        // Index bits 0 .. 4: the matrix times 32 tokens of 32 (group of 32 tokens, column) pairs a tile.
+        f32x16_t acc16[TILES];
 #pragma unroll
-                for (int i = 0; i < R0; ++i)
-                    if ((i & h) == 0) {
+        for (int q = 0; q < TILES; ++q) {
 #pragma unroll
-                        for (int e = 0; e < 2; ++e) {
-                            const float4 a = v[i][e], b = v[i + h][e];
-                            v[i][e] = make_float4(a.x + b.x, a.y + b.y, a.z + b.z, a.w + b.w);
-                            v[i + h][e] = make_float4(a.x - b.x, a.y - b.y, a.z - b.z, a.w - b.w);
-                        }
+            for (int v = 0; v < 16; ++v) acc16[q][v] = 0.0f;
+#pragma unroll
+            for (int kh = 0; kh < 2; ++kh) {
+                const int i = lane & 15, blk = lane >> 4;
+                const char *p = reinterpret_cast<const char *>(mine + ((i >> 1) & 1) * S::PLANE + 32 * (2 * q + (blk & 1)) + 16 * kh + 8 * (blk >> 1) + (i >> 2)) + (i & 1) * 8;
+                typedef __attribute__((address_space(3))) s16x4_t *lds_ptr_t;
+                const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr_t)(p));
+                const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr_t)(p + 64));
+                union {
+                    s16x8_t s;
+                    bf16x8_t v;
+                } b;
+                b.s = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+                acc16[q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(hadamard[kh], b.v, acc16[q], 0, 0, 0);
+            }
+        }
+        // The other bits, in ascending order, which does not depend on WAVES or NPROB.
+        // Bit 5, in lane bit 4: registers v and v + 1 (bit 0) exchange halves of their lanes, sum and difference follow.
+        // Afterwards lane bit 4 is bit 0, and the lowest bit of v is bit 5.
+#pragma unroll
+        for (int q = 0; q < TILES; ++q)
+#pragma unroll
+            for (int v = 0; v < 16; v += 2) {
+                const auto x = __builtin_amdgcn_permlane16_swap(__float_as_uint(acc16[q][v]), __float_as_uint(acc16[q][v + 1]), false, false);
+                const float a = __uint_as_float(x[0]), b = __uint_as_float(x[1]);
+                acc16[q][v] = a + b;
+                acc16[q][v + 1] = a - b;
+            }
+        // Tiles: register with register.
+#pragma unroll
+        for (int h = 1; h < TILES; h <<= 1)
+#pragma unroll
+            for (int q = 0; q < TILES; ++q)
+                if ((q & h) == 0) {
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) {
+                        const float a = acc16[q][v], b = acc16[q + h][v];
+                        acc16[q][v] = a + b;
+                        acc16[q + h][v] = a - b;
                     }
+                }
+        // The upper half of the wave's tokens, with one strip, in lane bit 3: in lanes that have it the result comes out negated
+        // (store_row puts that right).
+        if constexpr (NPROB == 1)
 #pragma unroll
-            for (int i = 0; i < R0; ++i) {
-                float4 *p = planes + sors_phys(tid) + 272 * i;  // token tid + 256 i
-                p[0] = v[i][0];
-                p[S::SLOTS] = v[i][1];
+            for (int q = 0; q < TILES; ++q)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    const float other = __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(acc16[q][v]), 0x128, 0xF, 0xF, true));  // row_ror:8
+                    acc16[q][v] = fmaf(other, odd8, acc16[q][v]);
+                }
+        {
+            asm volatile("" ::: "memory");
+            const int low = ((lane >> 4) & 1) + 4 * (lane >> 5), top = (lane >> 3) & 1;
+            float *p = reinterpret_cast<float *>(mine + low + top * (NPROB == 2 ? S::REGION : strip_phys(TOP)) + ((lane >> 2) & 1) * S::PLANE) + (lane & 3);
+#pragma unroll
+            for (int q = 0; q < TILES; ++q)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    const int high = 2 * ((v >> 1) & 1) + 8 * (v >> 2) + 32 * (v & 1) + 64 * q;
+                    p[4 * strip_phys(high)] = acc16[q][v];
+                }
+        }
+        __syncthreads();
+        // The waves' bits, 16 bytes of a token at a time (8 where that leaves threads without one).
+        {
+            constexpr int E = 2 * TW < NT ? 2 : 4;
+            typedef float vec_t __attribute__((ext_vector_type(E)));
+            float *strip = reinterpret_cast<float *>(planes_all + (int)threadIdx.x / NT * S::REGION);
+#pragma unroll
+            for (int item = (int)threadIdx.x % NT; item < 8 / E * TW; item += NT) {
+                const int h = item / (4 / E * TW), t = item / (4 / E) % TW;
+                vec_t *p = reinterpret_cast<vec_t *>(strip + 4 * (h * S::PLANE + strip_phys(t)) + item % (4 / E) * E);
+                vec_t v[WAVES];
+#pragma unroll
+                for (int w = 0; w < WAVES; ++w) v[w] = p[4 / E * strip_phys(w * TW)];
+#pragma unroll
+                for (int b = 1; b < WAVES; b <<= 1)
+#pragma unroll
+                    for (int w = 0; w < WAVES; ++w)
+                        if ((w & b) == 0) {
+                            const vec_t x = v[w], y = v[w + b];
+                            v[w] = x + y;
+                            v[w + b] = x - y;
+                        }
+#pragma unroll
+                for (int w = 0; w < WAVES; ++w) p[4 / E * strip_phys(w * TW)] = v[w];
             }
         }
         __syncthreads();
-        strip_lds_pass<LC, 4>(planes, tid);
-        __syncthreads();
-        strip_lds_pass<LC, 0>(planes, tid);
-        __syncthreads();
         if constexpr (ACC) {
 #pragma unroll
-            for (int m = 0; m < kSorsAccCalls; ++m)
+            for (int m = 0; m < ACC_CALLS; ++m)
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
                     const uint32_t r = rows[m][u];
-                    const int at = sors_phys((int)(r & (CH - 1)));
+                    const int at = strip_phys((int)(r & (CH - 1)));
                     const float sgn = (__popc((r >> LC) & (uint32_t)ch) & 1) ? -1.0f : 1.0f;
-                    const float4 a = planes[at], b = planes[S::SLOTS + at];
+                    const float4 a = planes[at], b = planes[S::PLANE + at];
                     acc[m][u][0].x += sgn * a.x, acc[m][u][0].y += sgn * a.y, acc[m][u][0].z += sgn * a.z, acc[m][u][0].w += sgn * a.w;
                     acc[m][u][1].x += sgn * b.x, acc[m][u][1].y += sgn * b.y, acc[m][u][1].z += sgn * b.z, acc[m][u][1].w += sgn * b.w;
                 }
@@ -217,48 +279,53 @@ __device__ __forceinline__ void sors_strip_body(const SorsArgs &g, int chunks, f
         }
     }
 
+    if constexpr (ACC)  // (the last request, past the end, ends here: left open, the compiler waits for it in the loop of the tile that shares the kernel)
+#pragma unroll
+        for (int i = 0; i < R0; ++i) asm volatile("" ::"v"(raw[i]));
     float *wave_sums = reinterpret_cast<float *>(sign_words);  // (the signs are behind a barrier) 8 per wave and strip
     if constexpr (SUMS) {
         // Over the lanes of a strip in fixed order: three exchanges leave each lane one of the eight columns, the others add.
-        const int lane = (int)threadIdx.x % 64 / NPROB;
+        const int row8 = lane / NPROB;
 #pragma unroll
         for (int h = 4; h > 0; h >>= 1)
 #pragma unroll
             for (int c = 0; c < h; ++c) {
-                const bool up = (lane & h) != 0;
+                const bool up = (row8 & h) != 0;
                 const float keep = up ? sums[c + h] : sums[c], give = up ? sums[c] : sums[c + h];
                 sums[c] = keep + __shfl_xor(give, h * NPROB);
             }
 #pragma unroll
         for (int h = 8; h < 64 / NPROB; h <<= 1) sums[0] += __shfl_xor(sums[0], h * NPROB);
-        if (lane < 8) wave_sums[((int)threadIdx.x / 64 * NPROB + prob) * 8 + lane] = sums[0];
+        if (row8 < 8) wave_sums[(wave * NPROB + prob) * 8 + row8] = sums[0];
     }
 
-    auto store_row = [&](int64_t j, const float4 &a, const float4 &b) {
+    auto store_row = [&](int64_t j, uint32_t r, const float4 &a, const float4 &b) {
+        const float alpha = NPROB == 1 && (r & (uint32_t)TOP) != 0 ? -g.alpha : g.alpha;
         sors_u32x4_t o;
-        o.x = (uint32_t)f32_to_bf16(g.alpha * a.x) | ((uint32_t)f32_to_bf16(g.alpha * a.y) << 16);
-        o.y = (uint32_t)f32_to_bf16(g.alpha * a.z) | ((uint32_t)f32_to_bf16(g.alpha * a.w) << 16);
-        o.z = (uint32_t)f32_to_bf16(g.alpha * b.x) | ((uint32_t)f32_to_bf16(g.alpha * b.y) << 16);
-        o.w = (uint32_t)f32_to_bf16(g.alpha * b.z) | ((uint32_t)f32_to_bf16(g.alpha * b.w) << 16);
+        o.x = (uint32_t)f32_to_bf16(alpha * a.x) | ((uint32_t)f32_to_bf16(alpha * a.y) << 16);
+        o.y = (uint32_t)f32_to_bf16(alpha * a.z) | ((uint32_t)f32_to_bf16(alpha * a.w) << 16);
+        o.z = (uint32_t)f32_to_bf16(alpha * b.x) | ((uint32_t)f32_to_bf16(alpha * b.y) << 16);
+        o.w = (uint32_t)f32_to_bf16(alpha * b.z) | ((uint32_t)f32_to_bf16(alpha * b.w) << 16);
         if (live) *reinterpret_cast<sors_u32x4_t *>(g.out + j * g.d + col0) = o;
     };
     if constexpr (ACC) {
 #pragma unroll
-        for (int m = 0; m < kSorsAccCalls; ++m)
+        for (int m = 0; m < ACC_CALLS; ++m)
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
-                const int64_t j = 4 * (int64_t)(tid + 256 * m) + u;
-                if (j < g.k) store_row(j, acc[m][u][0], acc[m][u][1]);
+                const int64_t j = 4 * (int64_t)(tid + NT * m) + u;
+                if (j < g.k) store_row(j, rows[m][u], acc[m][u][0], acc[m][u][1]);
             }
     } else {
-        for (int64_t q = tid; q < (g.k + 3) / 4; q += 256) {
+        for (int64_t q = tid; q < (g.k + 3) / 4; q += NT) {
             const Words4 w = philox4x32_10((uint32_t)q, kSorsRowColumn, g.st.off0, g.st.off1, g.st.key0, g.st.key1);
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
                 const int64_t j = 4 * q + u;
                 if (j >= g.k) break;
-                const int at = sors_phys((int)(w.w[u] & g.st.row_mask));
-                store_row(j, planes[at], planes[S::SLOTS + at]);
+                const uint32_t r = w.w[u] & g.st.row_mask;
+                const int at = strip_phys((int)r);
+                store_row(j, r, planes[at], planes[S::PLANE + at]);
             }
         }
     }
@@ -267,7 +334,7 @@ __device__ __forceinline__ void sors_strip_body(const SorsArgs &g, int chunks, f
         if (tid < 8 && live) {
             float x = 0.0f;
 #pragma unroll
-            for (int w = 0; w < 4 * NPROB; ++w) x += wave_sums[(w * NPROB + prob) * 8 + tid];
+            for (int w = 0; w < WAVES; ++w) x += wave_sums[(w * NPROB + prob) * 8 + tid];
             if (g.accumulate) x += load_f32<bf16_t>(g.colsum + col0 + tid);
             store_f32<bf16_t>(g.colsum + col0 + tid, x);
         }

@@ -54,6 +54,19 @@ def test_sketch_primitive_fast_transform(n, d, k):
     assert rmm.rmm_workspace_bytes(n, d, d, k, torch.bfloat16, SORS, binding.OP_SKETCH) == 0
 
 
+@pytest.mark.parametrize("n,d,k", [(1025, 2056, 90), (2048, 2064, 300), (2049, 2072, 65), (4097, 2056, 2048)])
+def test_two_strips_to_a_work_group(n, d, k):
+    """More than 256 strips, also an odd number of them; one and several chunks, and the column sums beside them."""
+    A = synth.to_torch(synth.normal((n, d), 0x5EED0024 + n), "bf16")
+    got = rmm.rmm_sketch(A.to(DEV), k, SORS, 0x5EED0025, 5)
+    want = o_rmm.sketch_apply(synth.to_f64(A), k, o_sketch.SORS, 0x5EED0025, 5)
+    assert_close(got, want, "X_proj", "bf16", "sors sketch n=%d d=%d k=%d" % (n, d, k))
+    W = torch.zeros((d, 8), dtype=torch.bfloat16, device=DEV)
+    Xp = torch.zeros((k, 8), dtype=torch.bfloat16, device=DEV)
+    _, _, db = rmm.rmm_backward(A.to(DEV), W, Xp, SORS, 0x5EED0025, 5, need_dX=False, need_dbias=True)
+    assert_close(db, synth.to_f64(A).sum(axis=0), "db", "bf16", "sors db n=%d d=%d k=%d" % (n, d, k))
+
+
 @pytest.mark.parametrize("dtype,n,d,k", [("f32", 256, 128, 32), ("f32", 333, 50, 77), ("bf16", 333, 52, 20),
                                          ("bf16", 40000, 8, 8)])
 def test_sketch_primitive_entry_by_entry_path(dtype, n, d, k):
