@@ -50,10 +50,10 @@ size_t ws_sketch(const rmm_layer_desc_t *d) {
     return sliced_sketch(d) ? round_up(sketch_workspace_bf16(d->n, d->d_in, d->k), 256) : 0;
 }
 PlainSlices plain_forward_slices(const rmm_layer_desc_t *d) {
-    return d->dtype == RMM_DTYPE_BF16 && !use_mfma(d) && d->d_in % 8 == 0 ? plain_slices(d->n, d->d_in, d->k, d->d_out, d->kind) : PlainSlices{1, 0, 0, 0};
+    return d->dtype == RMM_DTYPE_BF16 && !use_mfma(d) && d->d_in % 8 == 0 ? plain_slices(d->n, d->d_in, d->k, d->d_out, d->kind, false) : PlainSlices{1, 0, 0, 0};
 }
 PlainSlices plain_backward_slices(const rmm_layer_desc_t *d) {
-    return d->dtype == RMM_DTYPE_BF16 && !use_mfma(d) ? plain_slices(d->n, d->d_out, d->k, d->d_in, d->kind) : PlainSlices{1, 0, 0, 0};
+    return d->dtype == RMM_DTYPE_BF16 && !use_mfma(d) ? plain_slices(d->n, d->d_out, d->k, d->d_in, d->kind, true) : PlainSlices{1, 0, 0, 0};
 }
 size_t slices_bytes(const PlainSlices &cut) {
     return cut.slices > 1 ? round_up((size_t)cut.slices * (size_t)cut.stride * sizeof(float), 256) : 0;

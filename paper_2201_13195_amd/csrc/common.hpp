@@ -45,7 +45,7 @@ struct PlainSlices {
     int slices;
     int64_t chunk, stride, ld;
 };
-PlainSlices plain_slices(int64_t n, int64_t d, int64_t k, int64_t d_other, int kind);
+PlainSlices plain_slices(int64_t n, int64_t d, int64_t k, int64_t d_other, int kind, bool backward);
 //   Y = X W^T (+ bias) and X_proj = S^T X; either output may be null
 template <typename T>
 hipError_t launch_forward_plain(const T *X, const T *W, const T *bias, T *Y, T *X_proj, int64_t n, int64_t d_in,

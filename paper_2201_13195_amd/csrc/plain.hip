@@ -16,12 +16,14 @@ int64_t tiles_of(const PlainArgs &g, int64_t bm, int64_t bn) { return ((g.M + bm
 // 64 x 64 tile per compute unit the 32 x 32 tile, whose eight waves split the contraction.  fp32 operands are what
 // splitting costs most: there a 128 x 128 tile takes 2.6 times as long as a 64 x 64 tile, not four times (dX 4096 x 3072 ->
 // 768 with G beside it, k = 410: 328 -> 280 us; dW 768 -> 3072 38 -> 30).  `two_sums`: the 128 x 128 tile keeps two sums
-// (plain_tile); with one, which is rounded twice as often, it stays where it was.
+// (plain_tile; dX and dW); with one, which is rounded twice as often, it stays where it was.  bf16 operands are not split:
+// 64 x 64 tiles from 140 on (Y 700 x 300 -> 901, 165 tiles: 10.8 us on 32 x 32, 7.7 on 64 x 64; 500 x 1024 -> 1001, 128 tiles: 8.8 and
+// 9.7), and of Y a 128 x 128 tile costs 2.8 of them (4096 x 1024 -> 1001: 23.9 and 18.4 us; dW 2048 x 1499, k = 1500: 58.9 and 60.0).
 template <typename T>
 int plain_cfg(const PlainArgs &g, bool two_sums) {
     const int64_t big = tiles_of(g, 128, 128), mid = tiles_of(g, 64, 64);
-    if (mid < 256) return PLAIN_TINY;
-    const double times = sizeof(T) == 4 && two_sums ? 2.6 : 4.0;
+    if (mid < (sizeof(T) == 4 ? 256 : 140)) return PLAIN_TINY;
+    const double times = sizeof(T) == 4 ? (two_sums ? 2.6 : 4.0) : two_sums ? 4.0 : 2.8;
     return times * (double)((big + 255) / 256) <= (double)((mid + 255) / 256) ? PLAIN_BIG : PLAIN_MID;
 }
 int64_t cfg_tiles(const PlainArgs &g, int cfg) {
@@ -156,18 +158,18 @@ __global__ void debug_sketch_tile_kernel(int kind, SketchState st, int64_t i0, i
 // generated again for every column tile, and generating is most of what a Gaussian sketch tile does, so few wide tiles are
 // wanted; slices make them many.  Modelled in us per pass, from what the tiles take alone: a 32 x 32 sketch tile 9 ns per token
 // (+-1 entries 4.8), a 32 x 128 one 15 (9) and two on a compute unit 12 (6.5) each, a 64 x 64 tile of the other product 8 ns per
-// contraction element and a 32 x 32 one 6; a launch ends no sooner than its longest tile, nor than all its tiles on 256 compute
+// contraction element, a 128 x 128 one 22 and a 32 x 32 one 6; a launch ends no sooner than its longest tile, nor than all its tiles on 256 compute
 // units; slices add a launch of 4.5 us that reads their sums.  3000 x 768 -> 1001, Gaussian, k = 300: forward 43 us in one
 // slice, 30 in two; backward 53, 43 in two.  4096 x 1024 -> 111, k = 205: backward 62, 20 in eleven.  Where the two come out
 // alike (within 1 us) there are none.
-PlainSlices plain_slices(int64_t n, int64_t d, int64_t k, int64_t d_other, int kind) {
+PlainSlices plain_slices(int64_t n, int64_t d, int64_t k, int64_t d_other, int kind, bool backward) {
     PlainSlices cut{1, n, 0, (d + 7) / 8 * 8};
     if (load_mode<bf16_t>(d, d_other) == 0) return cut;
     PlainArgs plain{}, sketch{};
     plain.M = n, plain.N = d_other, plain.K = d, sketch.M = k, sketch.N = d, sketch.K = n;
-    const int cfg = plain_cfg<bf16_t>(plain, true);
-    const double per_cu = 1.0 / 256, chain = (cfg == PLAIN_TINY ? 6e-3 : 8e-3) * (double)d,
-                 plain_work = chain * (double)cfg_tiles(plain, cfg) * (cfg == PLAIN_BIG ? 4 : 1) * per_cu;
+    const int cfg = plain_cfg<bf16_t>(plain, backward);
+    const double per_cu = 1.0 / 256, chain = (cfg == PLAIN_TINY ? 6e-3 : cfg == PLAIN_MID ? 8e-3 : 22e-3) * (double)d,
+                 plain_work = chain * (double)cfg_tiles(plain, cfg) * per_cu;
     const double narrow = (kind == 0 ? 9e-3 : 4.8e-3) * (double)n, wide = (kind == 0 ? 15e-3 : 9e-3) * (double)n,
                  wide_work = (kind == 0 ? 12e-3 : 6.5e-3) * (double)n * (double)tiles_of(sketch, 32, 128);
     const int64_t tiles = tiles_of(sketch, 32, 128);
