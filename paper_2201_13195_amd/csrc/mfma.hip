@@ -45,7 +45,8 @@ int gemm_cfg(int64_t m, int64_t n, int64_t kk) {
     int best = GEMM_FEW;
     double best_us = -1.0;
     const int64_t few = tiles_of(m, n, FewTile::E, FewTile::E);
-    if (few <= 512) best_us = 2.5 + ceil((double)few / 256.0) * (1.0 + 0.85 * (double)kk / (double)kFewSingle);
+    if (few <= 512)  // (two on a compute unit: where a wave's share is one step the second costs 0.6 of the first)
+        best_us = 2.5 + (few <= 256 ? 1.0 : kk <= kFewSingle ? 1.6 : 2.0) * (1.0 + 0.85 * (double)kk / (double)kFewSingle);
     for (const auto &e : menu) {
         const double us = tile_us(e.t, m, n, kk);
         if (best_us < 0.0 || us < best_us) best = e.cfg, best_us = us;
