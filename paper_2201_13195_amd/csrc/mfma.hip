@@ -16,23 +16,24 @@ int64_t tiles_in(int64_t m, int64_t n) { return tiles_of(m, n, S::BM, S::BN); }
 // Time of a product on a menu of tiles, to choose between them (us, fitted to products from 256 x 384 to 16384 x 4096
 // outputs and contractions from 51 to 4096): a launch, then rounds of 256 work-groups, each `fix` for the first loads and
 // the writing of the tile and `step` for every 64 contraction elements.  Of the small tiles two share a compute unit: a
-// full round of 512 takes 1.9 times the time of one of up to 256, one of 257 to 511 from 1.4 times on.
+// full round of 512 takes 1.9 times the time of one of up to 256, one of 257 to 511 from 1.4 times on (`filled`, where other
+// work-groups of the launch take the second places: 1.9 times too).
 struct TileTime {
     int64_t bm, bn;
     double fix, step;
     bool shared;
 };
-double tile_us(const TileTime &t, int64_t m, int64_t n, int64_t kk) {
+double tile_us(const TileTime &t, int64_t m, int64_t n, int64_t kk, bool filled) {
     const int64_t tiles = tiles_of(m, n, t.bm, t.bn), rest = tiles % 512;
     const double rounds = !t.shared ? (double)((tiles + 255) / 256)
-                                    : 1.9 * (double)(tiles / 512) + (rest == 0 ? 0.0 : rest <= 256 ? 1.0 : 1.4 + 0.5 * (double)(rest - 256) / 256.0);
+                                    : 1.9 * (double)(tiles / 512) + (rest == 0 ? 0.0 : rest <= 256 ? 1.0 : filled ? 1.9 : 1.4 + 0.5 * (double)(rest - 256) / 256.0);
     return 2.5 + rounds * (t.fix + (double)((kk + 63) / 64) * t.step);
 }
 
 // Tile of a plain product with an m x n output and contraction kk.  32 x 32 tiles whose contraction is shared by eight
 // waves (few_tile) only while there are at most 512 of them.  256 x 256 tiles from 160 of them on whatever the model
 // says: they need half the bytes per flop of 128 x 128 tiles, which a full chip cannot bring into its LDS at MFMA rate.
-int gemm_cfg(int64_t m, int64_t n, int64_t kk) {
+int gemm_cfg(int64_t m, int64_t n, int64_t kk, bool filled = false) {
     if (tiles_in<ShapeLarge>(m, n) >= 160) return GEMM_LARGE;
     static const struct {
         int cfg;
@@ -48,7 +49,7 @@ int gemm_cfg(int64_t m, int64_t n, int64_t kk) {
     if (few <= 512)  // (two on a compute unit: where a wave's share is one step the second costs 0.6 of the first)
         best_us = 2.5 + (few <= 256 ? 1.0 : kk <= kFewSingle ? 1.6 : 2.0) * (1.0 + 0.85 * (double)kk / (double)kFewSingle);
     for (const auto &e : menu) {
-        const double us = tile_us(e.t, m, n, kk);
+        const double us = tile_us(e.t, m, n, kk, filled);
         if (best_us < 0.0 || us < best_us) best = e.cfg, best_us = us;
     }
     return best;
@@ -496,9 +497,10 @@ hipError_t launch_dw_colsum_bf16(const bf16_t *G, const bf16_t *X_proj, bf16_t *
 }
 
 // |X^T dY|_F^2 per tile for the variance monitors: the dW-type product (both operands stored
-// [token][feature]) with the squared-norm epilogue; the tiles of the other products, but for 32 x 32.
+// [token][feature]) with the squared-norm epilogue; the tiles of the other products, but for 32 x 32, beside the work-groups of
+// the row norms (6670 tokens, 608 x 1704: 270 tiles of 64 x 64 63 us, 140 of 64 x 128 49).
 static int xty_cfg(int64_t m, int64_t n, int64_t kk) {
-    const int cfg = gemm_cfg(m, n, kk);
+    const int cfg = gemm_cfg(m, n, kk, true);
     return cfg == GEMM_FEW ? GEMM_SMALL : cfg;
 }
 
