@@ -126,8 +126,8 @@ struct SketchPlan {
 // one slice the kernel writes fp32 partial results to workspace and reduce_partials_kernel sums them in slice
 // order.  104 tiles would get two slices each, and 48 compute units nothing to do.  So a tile may also get a last,
 // shorter slice; the work-groups left over take those of per_tail tiles each, as long in all as a long slice
-// (16384 x 4096, k = 1638: 111 steps on 243 compute units instead of 128 on 208, with the sum of the slices 264 ->
-// 246 us, Rademacher 220 -> 205; k = 819 140 -> 138 and 120 -> 115).
+// (16384 x 4096, k = 1638: 111 steps on 243 compute units instead of 128 on 208, with the sum of the slices 253 ->
+// 235 us, Rademacher 208 -> 194; k = 819 129 -> 130 and 110 -> 107).
 // `overhead` is what a tile costs besides its steps, in steps; a tile gets at most `most` slices.
 void slice_sketch(SketchPlan &p, int64_t n, int target_wgs, double overhead, int64_t most) {
     const int64_t units = (n + 63) / 64;
@@ -166,10 +166,10 @@ const SketchMenu &sketch_menu(int cfg) {
 // 512, 384 or 256 columns, operand columns staged once per 128 or 64 rows, and filling the chip when tokens are few.
 // It ranks the tiles and does not predict: what every tile costs alike (launch, first step, 8 us and more at small
 // sizes) is left out.  All six tiles timed at sixteen shapes from 2000 x 400, k = 100 to 16384 x 4096, k = 1638
-// (profiles/sketch_products.txt): the one taken is 1.7 % slower than the fastest on average with the Gaussian kind,
-// 17 % at most (32000 x 512, k = 640: 49 us, 128 x 256 42), 0.6 and 3.9 % with Rademacher.  ((16384 x 4096, k = 410)
-// 64 x 512: 83 us, 128 x 512: 126; (10000 x 3000, k = 1000) 128 x 384: 85, 64 x 256: 114; 4096 x 3072, k = 3686
-// unsliced on 128 x 384: 107, 128 x 512: 119.)
+// (profiles/sketch_products.txt): the one taken is 2.0 % slower than the fastest on average with the Gaussian kind,
+// 18 % at most (32000 x 512, k = 640: 49 us, 128 x 256 42), 0.3 and 1.9 % with Rademacher.  ((16384 x 4096, k = 410)
+// 64 x 512: 79 us, 128 x 512: 107; (10000 x 3000, k = 1000) 128 x 384: 81, 64 x 256: 108; 4096 x 3072, k = 3686
+// unsliced on 128 x 384: 102, 128 x 512: 107.)
 // `limited`: the caller may be rmm_sketch_static.
 SketchPlan plan_sketch(int64_t n, int64_t d, int64_t k, int kind, bool limited) {
     // rmm_sketch_static serves the shapes whose partial results fit RMM_STATIC_SCRATCH_BYTES with the plainest
@@ -324,8 +324,12 @@ double pair_us(const PairPlain &plain, int64_t kk, const SketchPlan &p, int kind
     const SketchTimes &b = two ? sk_compact : sk[p.cfg];
     const double ta = a.fix + a.step * (double)((kk + 63) / 64), tb = b.fix + b.step[kind != 0] * (double)(p.k_chunk / 64);
     const int64_t slots = two ? 512 : 256;
-    const double t = sketch_goes_first(plain.tiles, p.slices) ? makespan(p.shares(), tb, plain.tiles, ta, slots)
-                                                              : makespan(plain.tiles, ta, p.shares(), tb, slots);
+    double t = sketch_goes_first(plain.tiles, p.slices) ? makespan(p.shares(), tb, plain.tiles, ta, slots)
+                                                        : makespan(plain.tiles, ta, p.shares(), tb, slots);
+    // Beside 256 x 256 tiles, several rounds of them, power limits the chip's clock and a sketch work-group as long as the launch takes a
+    // tenth more (16384 x 1024 -> 4096, k = 1638, Rademacher: 78 work-groups of 169 us by the times above 202 us with the sum of the
+    // slices, 91 of 115 185).
+    if (plain.cfg == GEMM_LARGE && plain.tiles > 256 && t < 1.1 * tb) t = 1.1 * tb;
     return t + (p.splits > 1 ? 2.6 + 0.213 * (double)p.splits * partial_mb : 0.0);
 }
 

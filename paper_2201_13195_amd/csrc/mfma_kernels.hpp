@@ -559,7 +559,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &g, bf16_t *lds, int64_
 // ---------------------------------------------------------------------------------------------
 // Products with few output tiles (short requests, narrow layers, dW of a base layer): what bounds them
 // is the chain of loads, LDS and barriers along the contraction, not bandwidth or MFMA rate.  So a
-// work-group takes an E x E tile (32 or 64), its eight waves an eighth of the contraction each, and a
+// work-group takes an E x E tile, its eight waves an eighth of the contraction each, and a
 // wave walks its share without a barrier, 64 contraction elements per step through a piece of LDS of its
 // own (128-byte lines from memory, the MFMA's layout out of LDS), with the next two steps in flight.  The
 // eight partial tiles meet once, in LDS, in wave order.
