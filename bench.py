@@ -37,8 +37,8 @@ KERNEL_STAGE_ID = {"fwd_Y": 0, "fwd_Xproj": 6, "bwd_dX": 2, "bwd_G": 7, "bwd_dW"
 # separate-launch path (same kernels, one after the other).
 PAIR_STAGE_ID = {"fwd_pair": 8, "bwd_pair": 9}
 PAIR_PARTS = {"fwd_pair": ("fwd_Y", "fwd_Xproj"), "bwd_pair": ("bwd_dX", "bwd_G")}
-KERNEL_NAME = {"fwd_Y": "gemm_dma_kernel or gemm_mfma_kernel, by size (X, W^T operands)", "fwd_Xproj": "sketch product kernel on X",
-               "bwd_dX": "gemm_dma_kernel or gemm_mfma_kernel, by size (dY, W operands)", "bwd_G": "sketch product kernel on dY",
+KERNEL_NAME = {"fwd_Y": "gemm_mfma_kernel or few_tile_kernel, by size (X, W^T operands)", "fwd_Xproj": "sketch product kernel on X",
+               "bwd_dX": "gemm_mfma_kernel or few_tile_kernel, by size (dY, W operands)", "bwd_G": "sketch product kernel on dY",
                "bwd_dW": "gemm_mfma_kernel or few_tile_kernel, by size (G^T, X_proj operands)",
                "fwd_pair": "gemm_pair_kernel (Y = X W^T with the sketch product of X, one launch)",
                "bwd_pair": "gemm_pair_kernel (dX = dY W with the sketch product of dY, one launch)"}
