@@ -336,6 +336,15 @@ struct OperandLoads {
     __device__ __forceinline__ void load(int j) const { load_to_lds(rsrc, to + j * 1024, !KROWS || kk[j] < left ? off[j] : OOB, soff); }
 };
 
+// First row and column of output tile number `tile`: bands of 8 tile rows, column by column.
+template <int BM, int BN>
+__device__ __forceinline__ void tile_origin(uint32_t tile, uint32_t tiles_m, uint32_t tiles_n, int64_t &m0, int64_t &n0) {
+    constexpr uint32_t GROUP_M = 8;
+    const uint32_t band = tile / (GROUP_M * tiles_n), in_band = tile - band * (GROUP_M * tiles_n);
+    const uint32_t band_rows = min(GROUP_M, tiles_m - band * GROUP_M), col = in_band / band_rows;
+    m0 = (int64_t)(band * GROUP_M + in_band - col * band_rows) * BM, n0 = (int64_t)col * BN;
+}
+
 // One work-group's share of a product: output tile number `block` of `blocks`.  `lds` holds S::LDS_BYTES bytes.
 template <typename S, int AMODE, int BMODE, int OUT>
 __device__ __forceinline__ void gemm_tile(const GemmArgs &g, bf16_t *lds, int64_t block, int64_t blocks) {
@@ -347,23 +356,23 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &g, bf16_t *lds, int64_
     // renumber them such that one XCD owns a contiguous run of positions; then walk the tile grid
     // in bands of GROUP_M tile rows, column by column, so that the work-groups resident on one XCD
     // at the same time form a compact block that shares A row blocks and B column blocks in L2.
-    const int64_t tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN;
-    int64_t tile;
+    // (In 32 bits: a grid has fewer than 2^31 work-groups, and five divisions of 64 bits stood in front of the first load: a step of
+    // 1277 x 344 -> 344, k = 64, 31.3 -> 30.6 us, of 16384 x 1024 -> 4096 559 -> 557.)
+    const uint32_t tiles_m = (uint32_t)((g.M + BM - 1) / BM), tiles_n = (uint32_t)((g.N + BN - 1) / BN);
+    uint32_t tile;
     {
-        const int64_t per = blocks / 8, rem = blocks % 8, x = block % 8, r = block / 8;
+        const uint32_t per = (uint32_t)blocks / 8, rem = (uint32_t)blocks % 8, x = (uint32_t)block % 8, r = (uint32_t)block / 8;
         tile = x * per + (x < rem ? x : rem) + r;   // XCD x owns `per` (+1 for the first `rem`) consecutive positions
     }
-    constexpr int64_t GROUP_M = 8;
-    const int64_t band = tile / (GROUP_M * tiles_n), in_band = tile % (GROUP_M * tiles_n);
-    const int64_t band_rows = min(GROUP_M, tiles_m - band * GROUP_M);
-    const int64_t m0 = (band * GROUP_M + in_band % band_rows) * BM, n0 = (in_band / band_rows) * BN;
+    int64_t m0, n0;
+    tile_origin<BM, BN>(tile, tiles_m, tiles_n, m0, n0);
     const int kk = (int)g.K, steps = (kk + BK - 1) / BK;
     // Work-groups walk the contraction from different starting steps (and wrap around): with a
     // power-of-two row pitch all rows of a tile fall on the same one or two L2 channels, and the
     // rotation spreads concurrently running work-groups over the channels.  The eight tiles of one
     // band column (same B column block, neighbouring A row blocks) share a starting step so that
     // their common operand is fetched once into L2.
-    const int stagger = (int)((tile / 8) % steps);
+    const int stagger = (int)(tile / 8 % (uint32_t)steps);
 
     constexpr int JA = S::A_LOADS, JB = S::B_LOADS, LOADS = JA + JB;
     OperandLoads<BM, JA, AMODE == A_KCONTIG> la;
@@ -580,13 +589,14 @@ __device__ __forceinline__ void few_tile(const GemmArgs &g, unsigned char *lds, 
     constexpr int E = F::E, BK = F::BK, L = F::LOADS;
     constexpr bool A_K = AMODE == A_KCONTIG, B_K = BMODE == B_KCONTIG;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int64_t tiles_m = (g.M + E - 1) / E;
-    int64_t tile = block;
+    const uint32_t tiles_m = (uint32_t)((g.M + E - 1) / E);
+    uint32_t tile = (uint32_t)block;
     {
-        const int64_t per = blocks / 8, rem = blocks % 8, x = tile % 8, r = tile / 8;
+        const uint32_t per = (uint32_t)blocks / 8, rem = (uint32_t)blocks % 8, x = tile % 8, r = tile / 8;
         tile = x * per + (x < rem ? x : rem) + r;  // an XCD takes neighbouring tiles: same columns, other rows
     }
-    const int64_t m0 = tile % tiles_m * E, n0 = tile / tiles_m * E;
+    const uint32_t tile_n = tile / tiles_m;
+    const int64_t m0 = (int64_t)(tile - tile_n * tiles_m) * E, n0 = (int64_t)tile_n * E;
     const int64_t steps = (g.K + 15) / 16, share = (steps + 7) / 8;
     const int64_t k_begin = wave * share * 16;
     const int k_len = (int)max((int64_t)0, min(g.K, k_begin + share * 16) - k_begin);  // this wave's contraction elements
@@ -766,13 +776,10 @@ __device__ __forceinline__ void sketch_tile(const GemmArgs &g, bf16_t *lds, int6
     typedef SketchTile<S> T;
     constexpr int BM = T::BM, BN = T::BN, BK = T::BK, TM = T::TM, TN = T::TN;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave / T::WN, wn = wave % T::WN;
-    const int64_t tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN;
-    constexpr int64_t GROUP_M = 8;  // (tile order: see gemm_tile)
-    const int64_t band = tile / (GROUP_M * tiles_n), in_band = tile % (GROUP_M * tiles_n);
-    const int64_t band_rows = min(GROUP_M, tiles_m - band * GROUP_M);
-    const int64_t m0 = (band * GROUP_M + in_band % band_rows) * BM, n0 = (in_band / band_rows) * BN;
+    int64_t m0, n0;
+    tile_origin<BM, BN>((uint32_t)tile, (uint32_t)((g.M + BM - 1) / BM), (uint32_t)((g.N + BN - 1) / BN), m0, n0);
     const int steps = (kk + BK - 1) / BK;
-    const int stagger = (int)((tile / 8) % steps);
+    const int stagger = (int)((uint32_t)tile / 8 % (uint32_t)steps);
     auto first = [&](int t) { return (t + stagger >= steps ? t + stagger - steps : t + stagger) * BK; };  // first token of step t
 
     constexpr uint32_t OOB = 0x80000000u;
