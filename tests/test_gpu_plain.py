@@ -122,3 +122,15 @@ def test_fp32_products_are_no_further_off_than_a_chain_of_multiply_adds(n, d_in,
     rms = [float(np.sqrt(np.mean(((a - want) / size) ** 2)) * 2.0 ** 24) for a in (synth.to_f64(Y)[rows], chain)]
     print("%s spread %d: %.3f, chain %.3f (rms, 2^-24 of the sum of magnitudes)" % ((n, d_in, d_out), spread, *rms), flush=True)
     assert rms[0] <= rms[1]
+
+
+@pytest.mark.parametrize("n,d_out,dtype", [(300, 3080, "bf16"), (257, 24, "bf16"), (700, 1544, "f32"), (1000, 20, "f32"), (513, 1001, "bf16"),
+                                           (33, 7, "f32"), (1, 8, "bf16")])
+def test_column_sums_of_whole_numbers_are_exact(n, d_out, dtype):
+    """Both widths of a work-group's pieces and the element-wise form, in the launch of dW or of the pass (sums below 2^8)."""
+    t = torch.bfloat16 if dtype == "bf16" else torch.float32
+    dY = torch.randint(-1, 2, (n, d_out), generator=torch.Generator().manual_seed(n)).to(t)
+    W, Xp = torch.zeros((d_out, 16), dtype=t, device=DEV), torch.zeros((5, 16), dtype=t, device=DEV)
+    for need_dX in (True, False):
+        _, _, db = rmm.rmm_backward(dY.to(DEV), W, Xp, rmm.RADEMACHER, 3, 4, need_dX=need_dX, need_dbias=True)
+        assert torch.equal(db.float().cpu(), dY.float().sum(dim=0))
