@@ -27,7 +27,8 @@
  *     RMM_ERR_SCRATCH_LIMIT mean that no kernel ran.  RMM_ERR_LAUNCH (the HIP
  *     runtime refused a launch) can come after earlier kernels of the same call
  *     were enqueued; the outputs are then undefined.
- *   - The library holds no mutable global state and calls are re-entrant; the one exception is
+ *   - The library holds no mutable global state (each thread remembers a few launch plans, which
+ *     follow from sizes alone) and calls are re-entrant; the one exception is
  *     rmm_sketch_static, whose scratch array is shared by all calls on a GPU (see there).
  *   - dtype RMM_DTYPE_BF16: inputs, Y, dX, X_proj, dW are bfloat16 (round to
  *     nearest even from fp32 accumulators); bias / dbias are bfloat16 too and,
