@@ -24,17 +24,9 @@ struct ColsumArgs {
     int lpr;        // 16-byte pieces of a row per work-group: 4 or 1 (colsum_lpr); 0: element by element
 };
 
-// 16-byte pieces per row and work-group: four where that still gives 96 work-groups, else one
-// (measured at 16384 x 1024 bf16: 15 us with one, 21 with two, 41 with four).
-inline int colsum_lpr(int64_t d, int64_t elem_bytes) { return d * elem_bytes / 16 >= 384 ? 4 : 1; }
-inline int64_t colsum_blocks(int64_t d, int64_t elem_bytes) {
-    const int64_t vecs = d * elem_bytes / 16, lpr = colsum_lpr(d, elem_bytes);
-    return (vecs + lpr - 1) / lpr;
-}
 inline bool colsum_wide_ok(const void *A, int64_t d, int64_t elem_bytes) {  // 16-byte loads apply
     return (d * elem_bytes) % 16 == 0 && (reinterpret_cast<uintptr_t>(A) & 15u) == 0;
 }
-inline int64_t colsum_narrow_blocks(int64_t d) { return (d + 7) / 8; }
 constexpr int kColsumLdsFloats = 256 * 9 + 4 * 32;  // 256 row groups x (8 columns + 1), the larger of the two forms, and the waves' sums
 
 // `lds` holds kColsumLdsFloats floats; block `blk` of `blocks`.

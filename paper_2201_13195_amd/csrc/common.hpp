@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "launch_plans.hpp"
 #include "philox.hpp"
 
 namespace rmm {
@@ -39,13 +40,7 @@ __device__ __forceinline__ void store_f32<bf16_t>(bf16_t *p, float v) { *p = f32
 
 // fp32-matrix kernels (plain.hip): the fp32 data path, and the bf16 shapes the bf16 MFMA path does
 // not take.  One launch per call:
-//   Token slices of a bf16 pass's sketch product: `slices` runs of `chunk` tokens, their fp32 sums `stride` elements apart in
-//   scratch.  One slice: no scratch.  `ld`: row length of the result and of the sums (0: as wide as the operand).
-struct PlainSlices {
-    int slices;
-    int64_t chunk, stride, ld;
-};
-PlainSlices plain_slices(int64_t n, int64_t d, int64_t k, int64_t d_other, int kind, bool backward);
+//   (`cut`: the token slices of the sketch product, their sums in `ws`)
 //   Y = X W^T (+ bias) and X_proj = S^T X; either output may be null
 template <typename T>
 hipError_t launch_forward_plain(const T *X, const T *W, const T *bias, T *Y, T *X_proj, int64_t n, int64_t d_in,
@@ -68,7 +63,6 @@ hipError_t launch_colsum(const T *A, T *out, int64_t n, int64_t d, hipStream_t s
 // must hold sketch_workspace_bf16() bytes (fp32 partial sums of the token slices).
 // launch_sketch_bf16 records the optional event pair around its product kernel
 // alone (the sum over token slices, when there is one, comes after `ev_end`).
-bool mfma_shape_ok(int64_t n, int64_t d_in, int64_t d_out, int64_t k);
 // (`pair_k`, if not 0: with the tiles of the pass's paired launch with a sketch of pair_k columns, for passes that launch
 // their products one by one)
 hipError_t launch_linear_nt_bf16(const bf16_t *X, const bf16_t *W, const bf16_t *bias, bf16_t *Y, int64_t n,
@@ -86,7 +80,6 @@ hipError_t launch_dw_colsum_bf16(const bf16_t *G, const bf16_t *X_proj, bf16_t *
 // token slicing is then the one the paired launch of that pass uses, so that the separate and the
 // paired launches give the same bits.  0 = the product on its own (rmm_sketch).  `with_dbias`: a backward
 // pass that also makes the bias gradient (it may slice the tokens otherwise).
-size_t sketch_workspace_bf16(int64_t n, int64_t d, int64_t k, int64_t d_other = 0);
 hipError_t launch_sketch_bf16(const bf16_t *A, bf16_t *out, int64_t n, int64_t d, int64_t k, int kind, SketchState st,
                               void *ws, hipStream_t stream, hipEvent_t ev_begin = nullptr,
                               hipEvent_t ev_end = nullptr, int64_t d_other = 0, bool with_dbias = false);
@@ -96,7 +89,6 @@ hipError_t launch_sketch_bf16(const bf16_t *A, bf16_t *out, int64_t n, int64_t d
 // k x d_out), followed by the sum over the sketch's token slices.  Results are bit-identical to
 // the separate launches above (same kernels, same slices).  Only where pass_pair_available() says so;
 // the optional event pair brackets the paired kernel alone.
-bool pass_pair_available(int64_t k);
 hipError_t launch_forward_pair_bf16(const bf16_t *X, const bf16_t *W, const bf16_t *bias, bf16_t *Y, bf16_t *X_proj,
                                     int64_t n, int64_t d_in, int64_t d_out, int64_t k, int kind, SketchState st, void *ws,
                                     hipStream_t stream, hipEvent_t ev_begin = nullptr, hipEvent_t ev_end = nullptr);
@@ -107,7 +99,6 @@ hipError_t launch_backward_pair_bf16(const bf16_t *dY, const bf16_t *W, bf16_t *
                                      int64_t d_out, int64_t k, int kind, SketchState st, void *ws, hipStream_t stream,
                                      hipEvent_t ev_begin, hipEvent_t ev_end, bool with_dbias, bf16_t *dbias,
                                      bool accumulate_dbias);
-bool backward_pair_takes_colsum(int64_t n, int64_t d_in, int64_t d_out, int64_t k, int kind);
 
 // SORS sketch kind, bf16 (sors.hip): signs, Walsh-Hadamard transform along the tokens and row
 // selection in one kernel, no workspace.  Usable when sors_fast_ok(): d a multiple of 8 and at most
@@ -141,7 +132,6 @@ int sumsq_blocks(int64_t elems);
 hipError_t launch_sumsq(const float *A, int64_t elems, double *part, hipStream_t stream);
 //   part[t] = sum of squares of tile t of X^T dY (d_in x d_out), bf16 MFMA path; xty_sumsq_tiles() tiles;
 //   rows = the row norms (part of launch_row_norms), in the same launch.
-int xty_sumsq_tiles(int64_t n, int64_t d_in, int64_t d_out);
 hipError_t launch_xty_norms_bf16(const bf16_t *X, const bf16_t *dY, double *part, double *rows, int64_t n, int64_t d_in,
                                  int64_t d_out, hipStream_t stream);
 hipError_t launch_variance_finalize(const double *rows, int nb, const double *xty, int nt, int64_t n, int64_t k,

@@ -1,0 +1,456 @@
+// Which tiles, slices and workspace a product takes: plain C++ on sizes alone, so that a test compiles it on the host and asks
+// it.  mfma.hip and plain.hip launch what is planned here.
+#pragma once
+#include <math.h>
+#include <stddef.h>
+#include <stdint.h>
+
+#include <initializer_list>
+
+#include "../../include/rmm.h"
+
+namespace rmm {
+
+inline int64_t tiles_of(int64_t m, int64_t n, int64_t bm, int64_t bn) { return ((m + bm - 1) / bm) * ((n + bn - 1) / bn); }
+
+// Tile a plain product runs with (typedefs of mfma_kernels.hpp) and a sketch product's kernel.
+enum { GEMM_LARGE = 0, GEMM_WIDE = 1, GEMM_SPLIT = 2, GEMM_MID = 3, GEMM_FLAT = 4, GEMM_SMALL = 5, GEMM_FEW = 6, GEMM_COMPACT = 7 };
+enum { SK_NARROW = 0, SK_WIDE = 1, SK_WIDE64 = 2, SK_MID64 = 3, SK_MID = 4, SK_NARROW64 = 5 };
+struct TileEdges {
+    int64_t bm, bn;
+};
+constexpr TileEdges kGemmTiles[] = {{256, 256}, {128, 256}, {128, 128}, {128, 128}, {64, 128}, {64, 64}, {32, 32}, {128, 128}};
+constexpr int64_t kFewSingle = 512;  // the longest contraction that is one step of every wave of few_tile
+inline int64_t gemm_tiles(int cfg, int64_t m, int64_t n) { return tiles_of(m, n, kGemmTiles[cfg].bm, kGemmTiles[cfg].bn); }
+
+// Work-groups of the column sums (colsum.hpp).
+// 16-byte pieces per row and work-group: four where that still gives 96 work-groups, else one
+// (measured at 16384 x 1024 bf16: 15 us with one, 21 with two, 41 with four).
+inline int colsum_lpr(int64_t d, int64_t elem_bytes) { return d * elem_bytes / 16 >= 384 ? 4 : 1; }
+inline int64_t colsum_blocks(int64_t d, int64_t elem_bytes) {
+    const int64_t vecs = d * elem_bytes / 16, lpr = colsum_lpr(d, elem_bytes);
+    return (vecs + lpr - 1) / lpr;
+}
+inline int64_t colsum_narrow_blocks(int64_t d) { return (d + 7) / 8; }
+
+// The plain product of a paired launch: its tile (GEMM_LARGE, GEMM_SPLIT, GEMM_MID or, with SK_NARROW64, GEMM_COMPACT) and
+// number of tiles.
+struct PairPlain {
+    int cfg, tiles;
+};
+// The sketch work-groups are put in front of the plain tiles when the sketch product is unsliced (few, long
+// work-groups) or the plain product fills the chip at least once (256 tiles or more: measured 4 % faster at the
+// RoBERTa-large shapes, 2-3 % slower where the plain product has 192 tiles and the sketch work-groups fill in behind).
+inline bool sketch_goes_first(int64_t plain_tiles, int slices) { return slices == 1 || plain_tiles >= 256; }
+
+inline bool mfma_shape_ok(int64_t n, int64_t d_in, int64_t d_out, int64_t k) {
+    // 16-byte chunks need widths that are multiples of 8; a buffer descriptor spans up to 256 rows
+    // of an operand with 32-bit byte offsets, so a row has to stay below 2^22 elements.  The token
+    // count and the sketch size are not limited here (operands of 2 GiB and more are fine).
+    (void)n, (void)k;
+    const int64_t lim = (int64_t)1 << 22;
+    return d_in % 8 == 0 && d_out % 8 == 0 && d_in < lim && d_out < lim;
+}
+
+// Time of a product on a menu of tiles, to choose between them (us, fitted to products from 256 x 384 to 16384 x 4096
+// outputs and contractions from 51 to 4096): a launch, then rounds of 256 work-groups, each `fix` for the first loads and
+// the writing of the tile and `step` for every 64 contraction elements.  Of the small tiles two share a compute unit: a
+// full round of 512 takes 1.9 times the time of one of up to 256, one of 257 to 511 from 1.4 times on (`filled`, where other
+// work-groups of the launch take the second places: 1.9 times too).
+struct TileTime {
+    double fix, step;
+    bool shared;
+};
+inline double tile_us(const TileTime &t, int64_t tiles, int64_t kk, bool filled) {
+    const int64_t rest = tiles % 512;
+    const double rounds = !t.shared ? (double)((tiles + 255) / 256)
+                                    : 1.9 * (double)(tiles / 512) + (rest == 0 ? 0.0 : rest <= 256 ? 1.0 : filled ? 1.9 : 1.4 + 0.5 * (double)(rest - 256) / 256.0);
+    return 2.5 + rounds * (t.fix + (double)((kk + 63) / 64) * t.step);
+}
+
+// Tile of a plain product with an m x n output and contraction kk.  32 x 32 tiles whose contraction is shared by eight
+// waves (few_tile) only while there are at most 512 of them.  256 x 256 tiles from 160 of them on whatever the model
+// says: they need half the bytes per flop of 128 x 128 tiles, which a full chip cannot bring into its LDS at MFMA rate.
+inline int gemm_cfg(int64_t m, int64_t n, int64_t kk, bool filled = false) {
+    if (gemm_tiles(GEMM_LARGE, m, n) >= 160) return GEMM_LARGE;
+    static const struct {
+        int cfg;
+        TileTime t;
+    } menu[] = {{GEMM_WIDE, {3.0, 0.90, false}},
+                {GEMM_SPLIT, {2.4, 0.47, false}},
+                {GEMM_MID, {2.0, 0.50, false}},
+                {GEMM_FLAT, {1.0, 0.42, true}},
+                {GEMM_SMALL, {1.0, 0.27, true}}};
+    int best = GEMM_FEW;
+    double best_us = -1.0;
+    const int64_t few = gemm_tiles(GEMM_FEW, m, n);
+    if (few <= 512)  // (two on a compute unit: where a wave's share is one step the second costs 0.6 of the first)
+        best_us = 2.5 + (few <= 256 ? 1.0 : kk <= kFewSingle ? 1.6 : 2.0) * (1.0 + 0.85 * (double)kk / (double)kFewSingle);
+    for (const auto &e : menu) {
+        const double us = tile_us(e.t, gemm_tiles(e.cfg, m, n), kk, filled);
+        if (best_us < 0.0 || us < best_us) best = e.cfg, best_us = us;
+    }
+    return best;
+}
+
+// |X^T dY|_F^2 per tile for the variance monitors: the dW-type product (both operands stored
+// [token][feature]) with the squared-norm epilogue; the tiles of the other products, but for 32 x 32, beside the work-groups of
+// the row norms (6670 tokens, 608 x 1704: 270 tiles of 64 x 64 63 us, 140 of 64 x 128 49).
+inline int xty_cfg(int64_t m, int64_t n, int64_t kk) {
+    const int cfg = gemm_cfg(m, n, kk, true);
+    return cfg == GEMM_FEW ? GEMM_SMALL : cfg;
+}
+
+inline int xty_sumsq_tiles(int64_t n, int64_t d_in, int64_t d_out) { return (int)gemm_tiles(xty_cfg(d_in, d_out, n), d_in, d_out); }
+
+// Which kernel serves a sketch product with k > 64 and how its token dimension is cut.  The work-group
+// generates the sketch tile into LDS and all eight waves read it.
+struct SketchPlan {
+    int cfg;
+    int slices, per_tail;  // slices of k_chunk tokens of every tile; tiles per work-group that takes short last slices (0: there are none)
+    int splits;            // slices of a tile, the short one included
+    int64_t k_chunk, tiles;
+    int shares() const { return slices * (int)tiles + (per_tail > 0 ? (int)((tiles + per_tail - 1) / per_tail) : 0); }
+};
+
+// Tokens are cut into slices of `k_chunk` tokens (a multiple of 64) so that about `target_wgs` work-groups exist
+// (256 = one per compute unit; measured: more or fewer are slower when the product runs alone); with more than
+// one slice the kernel writes fp32 partial results to workspace and reduce_partials_kernel sums them in slice
+// order.  104 tiles would get two slices each, and 48 compute units nothing to do.  So a tile may also get a last,
+// shorter slice; the work-groups left over take those of per_tail tiles each, as long in all as a long slice
+// (16384 x 4096, k = 1638: 111 steps on 243 compute units instead of 128 on 208, with the sum of the slices 253 ->
+// 235 us, Rademacher 208 -> 194; k = 819 129 -> 130 and 110 -> 107).
+// `overhead` is what a tile costs besides its steps, in steps; a tile gets at most `most` slices.
+inline void slice_sketch(SketchPlan &p, int64_t n, int target_wgs, double overhead, int64_t most) {
+    const int64_t units = (n + 63) / 64;
+    int64_t s = target_wgs / p.tiles;
+    if (s > (units + 1) / 2) s = (units + 1) / 2;  // (a slice of one step: 1000 x 2000, k = 100 12.9 -> 14.7 us)
+    if (s > most) s = most;
+    if (s < 1) s = 1;
+    int64_t len = (units + s - 1) / s;
+    p.slices = p.splits = (int)((units + len - 1) / len), p.per_tail = 0;
+    const int64_t spare = target_wgs - s * p.tiles;
+    if (spare > 0 && s < most) {
+        const int64_t m = (p.tiles + spare - 1) / spare;
+        const int64_t tail_len = (int64_t)ceil(((double)units + overhead) * (double)m / (double)(s * m + 1));
+        if (s * tail_len < units && (double)tail_len < 0.92 * (double)len)
+            len = tail_len, p.slices = (int)s, p.splits = (int)s + 1, p.per_tail = (int)m;
+    }
+    p.k_chunk = len * 64;
+}
+
+// The tiles of a sketch product, and the time of a 64-token step on a full chip (alone).
+struct SketchMenu {
+    int64_t bm, bn;
+    double step_us[2];  // Gaussian, Rademacher
+};
+constexpr int kSketchTiles = 6;
+constexpr SketchMenu kSketchMenu[kSketchTiles] = {{128, 256, {1.18, 0.91}}, {128, 512, {1.92, 1.63}}, {64, 512, {1.20, 1.04}},  // (in the order of SK_NARROW ..)
+                                                  {64, 384, {0.93, 0.86}},  {128, 384, {1.54, 1.30}}, {64, 256, {0.85, 0.61}}};
+
+// The tile is the one of the menu whose time comes out lowest: rounds of 256 work-groups, each as long as
+// its slice's 64-token steps, plus the partial results.  The times of a step on a full chip come from a fit over
+// measured shapes, adjusted by hand where another choice was faster; partial results cost 0.2 us per MB written and
+// read (they mostly stay in the last-level cache).  What that weighs: padding of k and d, entries generated once per
+// 512, 384 or 256 columns, operand columns staged once per 128 or 64 rows, and filling the chip when tokens are few.
+// It ranks the tiles and does not predict: what every tile costs alike (launch, first step, 8 us and more at small
+// sizes) is left out.  All six tiles timed at sixteen shapes from 2000 x 400, k = 100 to 16384 x 4096, k = 1638
+// (profiles/sketch_products.txt): the one taken is 2.0 % slower than the fastest on average with the Gaussian kind,
+// 18 % at most (32000 x 512, k = 640: 49 us, 128 x 256 42), 0.3 and 1.9 % with Rademacher.  ((16384 x 4096, k = 410)
+// 64 x 512: 79 us, 128 x 512: 107; (10000 x 3000, k = 1000) 128 x 384: 81, 64 x 256: 108; 4096 x 3072, k = 3686
+// unsliced on 128 x 384: 102, 128 x 512: 107.)
+// `limited`: the caller may be rmm_sketch_static.
+inline SketchPlan plan_sketch(int64_t n, int64_t d, int64_t k, int kind, bool limited) {
+    // rmm_sketch_static serves the shapes whose partial results fit RMM_STATIC_SCRATCH_BYTES with the plainest
+    // tiling (rows by k, columns by d); those keep fitting, whichever tile they run with.
+    int64_t most = 64;
+    const double partial_bytes = (double)k * (double)d * 4.0;
+    if (limited) {
+        const int64_t tiles = d >= 1024 ? tiles_of(k, d, k <= 512 ? 64 : 128, 512) : d % 384 == 0 ? tiles_of(k, d, k <= 512 ? 64 : 128, 384) : tiles_of(k, d, 128, 256);
+        const int64_t blocks = (n + 127) / 128, s = tiles >= 256 ? 1 : blocks < 256 / tiles ? blocks : 256 / tiles;
+        const int64_t chunk = (blocks + s - 1) / s, slices = (blocks + chunk - 1) / chunk, fit = (int64_t)((double)RMM_STATIC_SCRATCH_BYTES / partial_bytes);
+        if (slices == 1 || slices <= fit) most = fit < 1 ? 1 : fit < 64 ? fit : 64;
+    }
+    SketchPlan best{};
+    double best_us = -1.0;
+    static const int order[kSketchTiles] = {SK_WIDE64, SK_WIDE, SK_MID64, SK_MID, SK_NARROW64, SK_NARROW};
+    for (int cfg : order) {
+        const SketchMenu &e = kSketchMenu[cfg];
+        SketchPlan p;
+        p.cfg = cfg, p.tiles = tiles_of(k, d, e.bm, e.bn);
+        const double step_us = e.step_us[kind != 0];
+        slice_sketch(p, n, 256, 4.0 / step_us, most);
+        const double us = (double)((p.shares() + 255) / 256) * (double)(p.k_chunk / 64) * step_us + 2.0 * p.per_tail +
+                          (p.splits > 1 ? (double)p.splits * (double)k * (double)d * 0.82e-6 : 0.0);
+        if (best_us < 0.0 || us < 0.98 * best_us) best = p, best_us = us;  // (ties: the wider tile)
+    }
+    return best;
+}
+
+// The streaming kernel of small sketch sizes: token slices so that about one work-group per
+// compute unit exists; 2 register sets of loads in flight.  Work-groups take 256 columns, or 128
+// where that would leave slices of at most 2048 tokens (k <= 32) / 512 tokens (k <= 64): half as many,
+// twice as long slices then halve the partial sums and the final cross-wave sum of a work-group
+// (measured: 26.6 against 27.6 us at 16384 x 4096, k = 32; 11.7 against 15.3 us at 16384 x 1024),
+// while on long slices the wider work-group is ahead (82.8 against 84.6 us at 65536 x 4096).
+constexpr int64_t kSmallK = 64;
+inline int smallk_slices_for(int64_t n, int64_t d, int64_t bn, int64_t *k_chunk) {
+    const int64_t col_tiles = (d + bn - 1) / bn, blocks = (n + 127) / 128;
+    int64_t s = 256 / col_tiles;
+    if (s > blocks) s = blocks;
+    if (s < 1) s = 1;
+    *k_chunk = (blocks + s - 1) / s * 128;
+    return (int)((n + *k_chunk - 1) / *k_chunk);
+}
+inline int64_t smallk_bn(int64_t n, int64_t d, int64_t k) {
+    int64_t k_chunk;
+    (void)smallk_slices_for(n, d, 256, &k_chunk);
+    return k_chunk <= (k <= 32 ? 2048 : 512) ? 128 : 256;
+}
+inline int smallk_slices(int64_t n, int64_t d, int64_t k, int64_t *k_chunk) {
+    return smallk_slices_for(n, d, smallk_bn(n, d, k), k_chunk);
+}
+
+// ---- Paired launches: which tiles and slices a pass takes.
+
+// Time until `second` jobs of t2 us each are done that follow `first` jobs of t1 us on `slots` equal slots.
+inline double makespan(int64_t first, double t1, int64_t second, double t2, int64_t slots) {
+    const int64_t late = first % slots, early = slots - late;  // slots that become free a round later / at once
+    const double base = (double)(first / slots) * t1;
+    double t = 0.0;
+    for (int64_t i = 0, j = 0, done = 0; done < second;) {  // rounds of the early slots and of the late ones, by the time they end
+        const double e = (double)(i + 1) * t2, l = late > 0 ? t1 + (double)(j + 1) * t2 : 1e30;
+        if (e <= l)
+            t = e, ++i, done += early;
+        else
+            t = l, ++j, done += late;
+    }
+    return base + (late > 0 && t < t1 ? t1 : t);
+}
+
+// us of a paired launch and the sum of its slices: work-groups of either kind take a time of their own (first loads and
+// writing, and every step of 64 contraction elements) and are dealt to 256 slots in grid order, or to 512 where two share
+// a compute unit.  The times are fitted to 4300 launches of 60 passes (256 to 16384 tokens, widths 256 to 4096,
+// k = 73 to 6911; all sketch tiles, 64 to 512 work-groups): 7 % rms off.  Over those passes the plan it leads to is 3.3 % slower than the
+// best one on average and 30 % at most; plans made for the sketch product alone were 12 and 50 %.
+inline double pair_us(const PairPlain &plain, int64_t kk, const SketchPlan &p, int kind, double partial_mb) {
+    struct Times {
+        double fix, step;
+    };
+    static const Times large{6.3, 1.405}, split{4.0, 0.478}, mid{3.4, 0.487}, compact{5.4, 0.733};
+    struct SketchTimes {
+        double fix, step[2];  // Gaussian, Rademacher
+    };
+    static const SketchTimes sk_compact{5.5, {1.009, 0.935}};
+    static const SketchTimes sk[] = {{5.3, {1.288, 0.957}}, {7.2, {1.651, 1.476}}, {5.1, {1.078, 1.080}},   // (in the order of SK_NARROW ..)
+                                     {5.0, {0.929, 0.910}}, {6.3, {1.490, 1.192}}, {4.05, {0.780, 0.722}}};
+    const bool two = plain.cfg == GEMM_COMPACT;
+    const Times &a = plain.cfg == GEMM_LARGE ? large : plain.cfg == GEMM_SPLIT ? split : two ? compact : mid;
+    const SketchTimes &b = two ? sk_compact : sk[p.cfg];
+    const double ta = a.fix + a.step * (double)((kk + 63) / 64), tb = b.fix + b.step[kind != 0] * (double)(p.k_chunk / 64);
+    const int64_t slots = two ? 512 : 256;
+    double t = sketch_goes_first(plain.tiles, p.slices) ? makespan(p.shares(), tb, plain.tiles, ta, slots)
+                                                        : makespan(plain.tiles, ta, p.shares(), tb, slots);
+    // Beside 256 x 256 tiles, several rounds of them, power limits the chip's clock and a sketch work-group as long as the launch takes a
+    // tenth more (16384 x 1024 -> 4096, k = 1638, Rademacher: 78 work-groups of 169 us by the times above 202 us with the sum of the
+    // slices, 91 of 115 185).
+    if (plain.cfg == GEMM_LARGE && plain.tiles > 256 && t < 1.1 * tb) t = 1.1 * tb;
+    return t + (p.splits > 1 ? 2.6 + 0.213 * (double)p.splits * partial_mb : 0.0);
+}
+
+struct PassPlan {
+    PairPlain plain;
+    SketchPlan sketch;
+};
+
+// The plain product of a pass (contraction kk, n x m outputs) beside a sketch product on one work-group per compute unit:
+// 256 x 256 tiles where it fills the chip with them, else 128 x 128; with two wave groups where the contraction is long (4096 x
+// 3072 -> 768 alone: 25.0 us, without 25.5; 768 -> 768: 10.3, without 9.7).
+inline PairPlain pair_plain(int64_t n, int64_t m, int64_t kk) {
+    const int cfg = gemm_tiles(GEMM_LARGE, n, m) >= 160 ? GEMM_LARGE : kk >= 1536 ? GEMM_SPLIT : GEMM_MID;
+    return PairPlain{cfg, (int)gemm_tiles(cfg, n, m)};
+}
+
+// Plan of a pass: sketch of the n x d_sk operand, plain product n x d_other over d_sk.  Every sketch tile with slices for 64
+// to 320 work-groups, and 64 x 256 tiles with ShapeCompact where all work-groups are resident at once.  (4096 x 768 ->
+// 768, k = 410, with the sum of its slices: 26.9 -> 21.3 us; 4096 x 3072 -> 768, k = 2048, Rademacher 82 -> 69; 3001 x 1304 ->
+// 520, k = 600: 32 -> 24.)  At most a quarter more slices than alone: no pass needs much more workspace than its sketch
+// product.  Less than 0.8 us, which is what the model is off by at the smallest sizes, is not worth another order of additions
+// than that of the product alone.
+inline PassPlan make_pass_plan(int64_t n, int64_t d_sk, int64_t d_other, int64_t k, int kind) {
+    const SketchPlan alone = plan_sketch(n, d_sk, k, kind, true);
+    const double partial_mb = (double)k * (double)d_sk * 4e-6;
+    const PairPlain usual = pair_plain(n, d_other, d_sk);
+    const PairPlain compact{GEMM_COMPACT, (int)gemm_tiles(GEMM_COMPACT, n, d_other)};
+    PassPlan best{usual, alone};
+    double best_us = pair_us(usual, d_sk, alone, kind, partial_mb) - 0.8;
+    for (int cfg = 0; cfg < kSketchTiles; ++cfg) {
+        int slices = -1, per_tail = -1;
+        for (int target : {64, 96, 128, 192, 256, 320}) {
+            SketchPlan p;
+            p.cfg = cfg, p.tiles = tiles_of(k, d_sk, kSketchMenu[cfg].bm, kSketchMenu[cfg].bn);
+            slice_sketch(p, n, target, 4.0 / kSketchMenu[cfg].step_us[kind != 0], 64);
+            if (p.slices == slices && p.per_tail == per_tail) continue;
+            slices = p.slices, per_tail = p.per_tail;
+            if (p.splits > 1 && (alone.splits == 1 || 4 * (p.splits - 1) > 5 * alone.splits)) continue;
+            double us = pair_us(usual, d_sk, p, kind, partial_mb);
+            if (us < best_us) best = PassPlan{usual, p}, best_us = us;
+            if (cfg != SK_NARROW64 || usual.cfg == GEMM_LARGE || compact.tiles + p.shares() > 512) continue;
+            us = pair_us(compact, d_sk, p, kind, partial_mb);
+            if (us < best_us) best = PassPlan{compact, p}, best_us = us;
+        }
+    }
+    return best;
+}
+
+// The same, remembered: a pass asks for its plan three times (workspace of either kind, launch), and it depends on the
+// sizes alone.
+inline PassPlan plan_pass(int64_t n, int64_t d_sk, int64_t d_other, int64_t k, int kind) {
+    struct Entry {
+        int64_t n, d_sk, d_other, k;
+        int kind;
+        PassPlan plan;
+    };
+    constexpr size_t ENTRIES = 64;
+    static thread_local Entry memo[ENTRIES];  // (n = 0: empty)
+    kind = kind != 0;
+    const uint64_t h = ((uint64_t)n * 0x9E3779B97F4A7C15u ^ (uint64_t)d_sk * 0xC2B2AE3D27D4EB4Fu ^ (uint64_t)d_other * 0x165667B19E3779F9u ^
+                        (uint64_t)k * 0x27D4EB2F165667C5u) + (uint64_t)kind;
+    Entry &e = memo[(h ^ h >> 32) % ENTRIES];
+    if (e.n != n || e.d_sk != d_sk || e.d_other != d_other || e.k != k || e.kind != kind)
+        e = Entry{n, d_sk, d_other, k, kind, make_pass_plan(n, d_sk, d_other, k, kind)};
+    return e.plan;
+}
+
+// Whether the launch of dW has room for the column sums of the bias gradient beside it.
+inline bool dw_takes_colsum(int64_t d_in, int64_t d_out, int64_t k) {
+    const int cfg = gemm_cfg(d_out, d_in, k);
+    const int64_t tiles = gemm_tiles(cfg, d_out, d_in);
+    if (cfg == GEMM_FEW || cfg == GEMM_SMALL || cfg == GEMM_FLAT) return tiles + colsum_blocks(d_out, 2) <= 512;  // (two on a compute unit)
+    return (256 - tiles % 256) % 256 >= 64;
+}
+
+// Places for a work-group that the last round of a pass's paired launch leaves empty.
+inline int64_t pair_idle(const PassPlan &p) {
+    const int64_t slots = p.plain.cfg == GEMM_COMPACT ? 512 : 256;
+    return (slots - (p.plain.tiles + p.sketch.shares()) % slots) % slots;
+}
+
+// Plan of a backward pass.  With a bias gradient that the launch of dW has no room for, short last slices
+// that take the compute units its column sums need are given up (16384 x 1024 -> 4096, k = 1638: 208 sketch
+// work-groups instead of 243).
+inline PassPlan plan_backward(int64_t n, int64_t d_in, int64_t d_out, int64_t k, int kind, bool with_dbias) {
+    const PassPlan p = plan_pass(n, d_out, d_in, k, kind);
+    if (!with_dbias || p.sketch.per_tail == 0 || p.sketch.slices < 2 || dw_takes_colsum(d_in, d_out, k) || pair_idle(p) >= 16) return p;
+    PassPlan even = p;
+    const int64_t units = (n + 63) / 64, len = (units + p.sketch.slices - 1) / p.sketch.slices;
+    even.sketch.per_tail = 0, even.sketch.k_chunk = len * 64, even.sketch.slices = even.sketch.splits = (int)((units + len - 1) / len);
+    return even.sketch.splits >= 2 && pair_idle(even) >= 16 ? even : p;
+}
+
+inline bool pass_pair_available(int64_t k) { return k > kSmallK; }
+
+// Where the bias gradient goes in a backward pass that has the paired launch: into the launch of
+// dW when that leaves at least 64 compute units idle (dW is short and mostly latency; where it runs on
+// few_tile, whose work-groups want a compute unit each, when the column blocks fit beside them);
+// otherwise into the paired launch when its last round leaves at least 16 idle (the sketch work-groups
+// of that round run for long, and dY is being read there anyway; plan_backward sees to it where it
+// can); otherwise into the launch of dW.
+inline bool backward_pair_takes_colsum(int64_t n, int64_t d_in, int64_t d_out, int64_t k, int kind) {
+    if (!pass_pair_available(k)) return false;
+    return !dw_takes_colsum(d_in, d_out, k) &&
+           (gemm_cfg(d_out, d_in, k) == GEMM_FEW ||
+            pair_idle(plan_backward(n, d_in, d_out, k, kind, true)) >= 16);
+}
+
+// The two dense kinds may take different tiles and slices; a workspace serves either (and both plans of
+// plan_backward: the one with a bias gradient has fewer slices).
+inline size_t sketch_workspace_bf16(int64_t n, int64_t d, int64_t k, int64_t d_other = 0) {
+    int64_t k_chunk;
+    size_t most = 0;
+    if (k <= kSmallK) {
+        const int s = smallk_slices(n, d, k, &k_chunk);
+        return s > 1 ? (size_t)s * (size_t)k * (size_t)d * sizeof(float) : 0;
+    }
+    for (int kind = 0; kind < 2; ++kind) {
+        const SketchPlan p = d_other > 0 ? plan_pass(n, d, d_other, k, kind).sketch : plan_sketch(n, d, k, kind, true);
+        const size_t bytes = p.splits > 1 ? (size_t)p.splits * (size_t)k * (size_t)d * sizeof(float) : 0;
+        if (bytes > most) most = bytes;
+    }
+    return most;
+}
+
+// ---- fp32 products, and bf16 products of widths the kernels above refuse (plain_kernels.hpp).
+enum { PLAIN_BIG = 0, PLAIN_MID = 1, PLAIN_TINY = 2 };
+
+// Tile shape of a plain product.  What counts is how evenly the tiles share the 256 compute units (one
+// work-group each): the 128 x 128 tile where its last round costs no more than that of the 64 x 64 tile
+// (it moves and splits half as many operand bytes per flop), the 64 x 64 tile otherwise, and below one
+// 64 x 64 tile per compute unit the 32 x 32 tile, whose eight waves split the contraction.  fp32 operands are what
+// splitting costs most: there a 128 x 128 tile takes 2.6 times as long as a 64 x 64 tile, not four times (dX 4096 x 3072 ->
+// 768 with G beside it, k = 410: 328 -> 280 us; dW 768 -> 3072 38 -> 30).  `two_sums`: the 128 x 128 tile keeps two sums
+// (plain_tile; dX and dW); with one, which is rounded twice as often, it stays where it was.  bf16 operands are not split:
+// 64 x 64 tiles from 140 on (Y 700 x 300 -> 901, 165 tiles: 10.8 us on 32 x 32, 7.7 on 64 x 64; 500 x 1024 -> 1001, 128 tiles: 8.8 and
+// 9.7), and of Y a 128 x 128 tile costs 2.8 of them (4096 x 1024 -> 1001: 23.9 and 18.4 us; dW 2048 x 1499, k = 1500: 58.9 and 60.0).
+inline int plain_cfg(int elem_bytes, int64_t m, int64_t n, bool two_sums) {
+    const int64_t big = tiles_of(m, n, 128, 128), mid = tiles_of(m, n, 64, 64);
+    if (mid < (elem_bytes == 4 ? 256 : 140)) return PLAIN_TINY;
+    const double times = elem_bytes == 4 ? (two_sums ? 2.6 : 4.0) : two_sums ? 4.0 : 2.8;
+    return times * (double)((big + 255) / 256) <= (double)((mid + 255) / 256) ? PLAIN_BIG : PLAIN_MID;
+}
+inline int64_t plain_tiles(int cfg, int64_t m, int64_t n) {
+    const int64_t e = cfg == PLAIN_BIG ? 128 : cfg == PLAIN_MID ? 64 : 32;
+    return tiles_of(m, n, e, e);
+}
+
+// How a launch loads its operands (rows of `a` and `b` elements): 4 = 16-byte loads (fp32, rows that start on 16
+// bytes), 3 = rows that start anywhere, 0 = rows too long for 32-bit offsets inside a tile of 128 of them.  bf16 operands
+// differ (rows_on_16): a row that starts anywhere costs a fifth dword, a funnel shift and its masks per eight
+// elements (Y 3000 x 768 -> 1001 23 us with it, 17 without).
+inline int load_mode(int elem_bytes, int64_t a, int64_t b) {
+    const int64_t lim = (int64_t)1 << 22;
+    if (a >= lim || b >= lim) return 0;
+    return elem_bytes == 4 && a % 4 == 0 && b % 4 == 0 ? 4 : 3;
+}
+inline bool rows_on_16(int64_t row) { return row % 8 == 0; }  // bf16
+
+// Token slices of a bf16 pass's sketch product: `slices` runs of `chunk` tokens, their fp32 sums `stride` elements apart in
+// scratch.  One slice: no scratch.  `ld`: row length of the result and of the sums (0: as wide as the operand).
+struct PlainSlices {
+    int slices;
+    int64_t chunk, stride, ld;
+};
+
+// Token slices of the sketch product of a bf16 pass (sketch of an n x d operand, beside a product n x d_other).  An entry is
+// generated again for every column tile, and generating is most of what a Gaussian sketch tile does, so few wide tiles are
+// wanted; slices make them many.  Modelled in us per pass, from what the tiles take alone: a 32 x 32 sketch tile 9 ns per token
+// (+-1 entries 4.8), a 32 x 128 one 15 (9) and two on a compute unit 12 (6.5) each, a 64 x 64 tile of the other product 8 ns per
+// contraction element, a 128 x 128 one 22 and a 32 x 32 one 6; a launch ends no sooner than its longest tile, nor than all its tiles on 256 compute
+// units; slices add a launch of 4.5 us that reads their sums.  3000 x 768 -> 1001, Gaussian, k = 300: forward 43 us in one
+// slice, 30 in two; backward 53, 43 in two.  4096 x 1024 -> 111, k = 205: backward 62, 20 in eleven.  Where the two come out
+// alike (within 1 us) there are none.
+inline PlainSlices plain_slices(int64_t n, int64_t d, int64_t k, int64_t d_other, int kind, bool backward) {
+    PlainSlices cut{1, n, 0, (d + 7) / 8 * 8};
+    if (load_mode(2, d, d_other) == 0) return cut;
+    const int cfg = plain_cfg(2, n, d_other, backward);
+    const int64_t tiles = tiles_of(k, d, 32, 128);
+    const double per_cu = 1.0 / 256, chain = (cfg == PLAIN_TINY ? 6e-3 : cfg == PLAIN_MID ? 8e-3 : 22e-3) * (double)d,
+                 plain_work = chain * (double)plain_tiles(cfg, n, d_other) * per_cu;
+    const double narrow = (kind == 0 ? 9e-3 : 4.8e-3) * (double)n, wide = (kind == 0 ? 15e-3 : 9e-3) * (double)n,
+                 wide_work = (kind == 0 ? 12e-3 : 6.5e-3) * (double)n * (double)tiles;
+    const bool small = cfg == PLAIN_TINY || (cfg == PLAIN_MID && tiles < 64);  // (launch_pass)
+    auto longest = [&](double sketch_chain, double sketch_work) {
+        const double most = sketch_chain > chain ? sketch_chain : chain, all = plain_work + sketch_work * per_cu;
+        return most > all ? most : all;
+    };
+    double best = (small ? longest(narrow, narrow * (double)tiles_of(k, d, 32, 32)) : longest(wide, wide_work)) - 1.0;
+    for (int64_t s = 2; s <= 16; ++s) {
+        const int64_t chunk = ((n + s - 1) / s + 127) / 128 * 128, slices = (n + chunk - 1) / chunk;
+        if (slices != s || chunk < 256) continue;
+        const double t = longest(wide * (double)chunk / (double)n, wide_work) + 4.5 + 1e-6 * (double)(s * k * d);
+        if (t < best) best = t, cut = PlainSlices{(int)s, chunk, k * cut.ld, cut.ld};
+    }
+    return cut;
+}
+
+}  // namespace rmm

@@ -581,7 +581,6 @@ struct FewTile {
     static constexpr int LDS_BYTES = 8 * 2 * PATCH * 2;
     static_assert(LDS_BYTES >= 8 * E * E * 4, "room for the partial tiles");
 };
-constexpr int64_t kFewSingle = 8 * FewTile::BK;  // the longest contraction that is one step of every wave
 
 template <int AMODE, int BMODE, bool SINGLE>
 __device__ __forceinline__ void few_tile(const GemmArgs &g, unsigned char *lds, int64_t block, int64_t blocks) {

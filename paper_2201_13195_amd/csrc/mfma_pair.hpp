@@ -6,23 +6,10 @@
 
 namespace rmm {
 
-// Tile a plain product runs with (typedefs of mfma_kernels.hpp) and a sketch product's kernel.
-enum { GEMM_LARGE = 0, GEMM_WIDE = 1, GEMM_SPLIT = 2, GEMM_MID = 3, GEMM_FLAT = 4, GEMM_SMALL = 5, GEMM_FEW = 6, GEMM_COMPACT = 7 };
-enum { SK_NARROW = 0, SK_WIDE = 1, SK_WIDE64 = 2, SK_MID64 = 3, SK_MID = 4, SK_NARROW64 = 5 };
-
-// The plain product of a paired launch: its tile (GEMM_LARGE, GEMM_SPLIT, GEMM_MID or, with SK_NARROW64, GEMM_COMPACT) and
-// number of tiles.
-struct PairPlain {
-    int cfg, tiles;
-};
-
 // One launch for a plain product (`ga`; nt: Y = X W^T, nn: dX = dY W) and a sketch product (`gb`, `tiles_b`
 // tiles in `shares` work-groups, see sketch_share) with the kernel sk_cfg.
 // `gc`, if not null, adds the column blocks of a column-sum problem (colsum.hpp) behind the sketch work-groups.
-// The sketch work-groups are put in front of the plain tiles when the sketch product is unsliced (few, long
-// work-groups) or the plain product fills the chip at least once (256 tiles or more: measured 4 % faster at the
-// RoBERTa-large shapes, 2-3 % slower where the plain product has 192 tiles and the sketch work-groups fill in behind).
-inline bool sketch_goes_first(int64_t plain_tiles, int slices) { return slices == 1 || plain_tiles >= 256; }
+// sketch_goes_first() says which of the two comes first in the grid.
 hipError_t launch_pair_nt(const PairPlain &plain, int sk_cfg, int kind, const GemmArgs &ga, const GemmArgs &gb, int tiles_b,
                           int shares, hipStream_t stream, const ColsumArgs *gc = nullptr);
 hipError_t launch_pair_nn(const PairPlain &plain, int sk_cfg, int kind, const GemmArgs &ga, const GemmArgs &gb, int tiles_b,

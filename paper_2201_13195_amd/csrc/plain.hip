@@ -1,5 +1,5 @@
-// Host side of the fp32 kernels (plain_kernels.hpp): tile shapes, launches, and the small
-// kernels that go with them (column sums on their own, the generator test hooks).
+// Host side of the fp32 kernels (plain_kernels.hpp): launches (launch_plans.hpp: tile shapes, slices), and the small kernels
+// that go with them (column sums on their own, the generator test hooks).
 #include <type_traits>
 
 #include "plain_pass.hpp"
@@ -7,41 +7,6 @@
 namespace rmm {
 
 namespace {
-
-int64_t tiles_of(const PlainArgs &g, int64_t bm, int64_t bn) { return ((g.M + bm - 1) / bm) * ((g.N + bn - 1) / bn); }
-
-// Tile shape of a plain product.  What counts is how evenly the tiles share the 256 compute units (one
-// work-group each): the 128 x 128 tile where its last round costs no more than that of the 64 x 64 tile
-// (it moves and splits half as many operand bytes per flop), the 64 x 64 tile otherwise, and below one
-// 64 x 64 tile per compute unit the 32 x 32 tile, whose eight waves split the contraction.  fp32 operands are what
-// splitting costs most: there a 128 x 128 tile takes 2.6 times as long as a 64 x 64 tile, not four times (dX 4096 x 3072 ->
-// 768 with G beside it, k = 410: 328 -> 280 us; dW 768 -> 3072 38 -> 30).  `two_sums`: the 128 x 128 tile keeps two sums
-// (plain_tile; dX and dW); with one, which is rounded twice as often, it stays where it was.  bf16 operands are not split:
-// 64 x 64 tiles from 140 on (Y 700 x 300 -> 901, 165 tiles: 10.8 us on 32 x 32, 7.7 on 64 x 64; 500 x 1024 -> 1001, 128 tiles: 8.8 and
-// 9.7), and of Y a 128 x 128 tile costs 2.8 of them (4096 x 1024 -> 1001: 23.9 and 18.4 us; dW 2048 x 1499, k = 1500: 58.9 and 60.0).
-template <typename T>
-int plain_cfg(const PlainArgs &g, bool two_sums) {
-    const int64_t big = tiles_of(g, 128, 128), mid = tiles_of(g, 64, 64);
-    if (mid < (sizeof(T) == 4 ? 256 : 140)) return PLAIN_TINY;
-    const double times = sizeof(T) == 4 ? (two_sums ? 2.6 : 4.0) : two_sums ? 4.0 : 2.8;
-    return times * (double)((big + 255) / 256) <= (double)((mid + 255) / 256) ? PLAIN_BIG : PLAIN_MID;
-}
-int64_t cfg_tiles(const PlainArgs &g, int cfg) {
-    const int64_t e = cfg == PLAIN_BIG ? 128 : cfg == PLAIN_MID ? 64 : 32;
-    return tiles_of(g, e, e);
-}
-
-// How a launch loads its operands (rows of `a` and `b` elements): 4 = 16-byte loads (fp32, rows that start on 16
-// bytes), 3 = rows that start anywhere, 0 = rows too long for 32-bit offsets inside a tile of 128 of them.  bf16 operands
-// differ (rows_on_16): a row that starts anywhere costs a fifth dword, a funnel shift and its masks per eight
-// elements (Y 3000 x 768 -> 1001 23 us with it, 17 without).
-template <typename T>
-int load_mode(int64_t a, int64_t b) {
-    const int64_t lim = (int64_t)1 << 22;
-    if (a >= lim || b >= lim) return 0;
-    return sizeof(T) == 4 && a % 4 == 0 && b % 4 == 0 ? 4 : 3;
-}
-bool rows_on_16(int64_t row) { return row % 8 == 0; }  // bf16
 
 template <typename T>
 __global__ void __launch_bounds__(256) colsum_kernel(ColsumArgs g) {
@@ -58,14 +23,14 @@ ColsumArgs colsum_args(const T *A, T *out, int64_t n, int64_t d, bool accumulate
 
 template <typename T>
 hipError_t launch_pass(PlainLaunch &p, bool has_plain, bool has_sketch, bool b_rows_k, int mode, hipStream_t stream) {
-    p.cfg = mode == 0 ? PLAIN_TINY : has_plain ? plain_cfg<T>(p.ga, b_rows_k) : PLAIN_MID;
-    p.plain_blocks = has_plain ? (int)cfg_tiles(p.ga, p.cfg) : 0;
+    p.cfg = mode == 0 ? PLAIN_TINY : has_plain ? plain_cfg(sizeof(T), p.ga.M, p.ga.N, b_rows_k) : PLAIN_MID;
+    p.plain_blocks = has_plain ? (int)plain_tiles(p.cfg, p.ga.M, p.ga.N) : 0;
     p.sketch_blocks = 0;
     p.sketch_small = false;
     if (has_sketch) {
         // 32 x 32 tiles generate every entry four times as often as 32 x 128 tiles: only where those are few
-        p.sketch_small = mode == 0 || (p.gs.slices <= 1 && (p.cfg == PLAIN_TINY || (p.cfg == PLAIN_MID && tiles_of(p.gs, 32, 128) < 64)));
-        p.sketch_blocks = (int)tiles_of(p.gs, 32, p.sketch_small ? 32 : 128) * (p.gs.slices > 1 ? p.gs.slices : 1);
+        p.sketch_small = mode == 0 || (p.gs.slices <= 1 && (p.cfg == PLAIN_TINY || (p.cfg == PLAIN_MID && tiles_of(p.gs.M, p.gs.N, 32, 128) < 64)));
+        p.sketch_blocks = (int)tiles_of(p.gs.M, p.gs.N, 32, p.sketch_small ? 32 : 128) * (p.gs.slices > 1 ? p.gs.slices : 1);
     }
     if constexpr (sizeof(T) == 2) {
         const bool a16 = rows_on_16(has_plain ? p.ga.lda : p.gs.ldb), b16 = rows_on_16(has_plain ? p.ga.ldb : p.gs.ldb);
@@ -119,8 +84,8 @@ hipError_t finish_slices(const PlainArgs &gs, T *out, hipStream_t stream) {
 
 template <typename T, typename Tout, int MODE_A, int MODE_B>
 hipError_t launch_tn(const PlainArgs &g, hipStream_t stream) {
-    const int cfg = MODE_A == 0 ? PLAIN_TINY : plain_cfg<T>(g, true);
-    const unsigned grid = (unsigned)cfg_tiles(g, cfg);
+    const int cfg = MODE_A == 0 ? PLAIN_TINY : plain_cfg(sizeof(T), g.M, g.N, true);
+    const unsigned grid = (unsigned)plain_tiles(cfg, g.M, g.N);
     if constexpr (MODE_A != 0) {
         if (cfg == PLAIN_BIG) {
             plain_tn_kernel<T, Tout, PlainBig, MODE_A, MODE_B><<<grid, kPlainThreads, 0, stream>>>(g);
@@ -154,40 +119,6 @@ __global__ void debug_sketch_tile_kernel(int kind, SketchState st, int64_t i0, i
 
 }  // namespace
 
-// Token slices of the sketch product of a bf16 pass (sketch of an n x d operand, beside a product n x d_other).  An entry is
-// generated again for every column tile, and generating is most of what a Gaussian sketch tile does, so few wide tiles are
-// wanted; slices make them many.  Modelled in us per pass, from what the tiles take alone: a 32 x 32 sketch tile 9 ns per token
-// (+-1 entries 4.8), a 32 x 128 one 15 (9) and two on a compute unit 12 (6.5) each, a 64 x 64 tile of the other product 8 ns per
-// contraction element, a 128 x 128 one 22 and a 32 x 32 one 6; a launch ends no sooner than its longest tile, nor than all its tiles on 256 compute
-// units; slices add a launch of 4.5 us that reads their sums.  3000 x 768 -> 1001, Gaussian, k = 300: forward 43 us in one
-// slice, 30 in two; backward 53, 43 in two.  4096 x 1024 -> 111, k = 205: backward 62, 20 in eleven.  Where the two come out
-// alike (within 1 us) there are none.
-PlainSlices plain_slices(int64_t n, int64_t d, int64_t k, int64_t d_other, int kind, bool backward) {
-    PlainSlices cut{1, n, 0, (d + 7) / 8 * 8};
-    if (load_mode<bf16_t>(d, d_other) == 0) return cut;
-    PlainArgs plain{}, sketch{};
-    plain.M = n, plain.N = d_other, plain.K = d, sketch.M = k, sketch.N = d, sketch.K = n;
-    const int cfg = plain_cfg<bf16_t>(plain, backward);
-    const double per_cu = 1.0 / 256, chain = (cfg == PLAIN_TINY ? 6e-3 : cfg == PLAIN_MID ? 8e-3 : 22e-3) * (double)d,
-                 plain_work = chain * (double)cfg_tiles(plain, cfg) * per_cu;
-    const double narrow = (kind == 0 ? 9e-3 : 4.8e-3) * (double)n, wide = (kind == 0 ? 15e-3 : 9e-3) * (double)n,
-                 wide_work = (kind == 0 ? 12e-3 : 6.5e-3) * (double)n * (double)tiles_of(sketch, 32, 128);
-    const int64_t tiles = tiles_of(sketch, 32, 128);
-    const bool small = cfg == PLAIN_TINY || (cfg == PLAIN_MID && tiles < 64);  // (launch_pass)
-    auto longest = [&](double sketch_chain, double sketch_work) {
-        const double most = sketch_chain > chain ? sketch_chain : chain, all = plain_work + sketch_work * per_cu;
-        return most > all ? most : all;
-    };
-    double best = (small ? longest(narrow, narrow * (double)tiles_of(sketch, 32, 32)) : longest(wide, wide_work)) - 1.0;
-    for (int64_t s = 2; s <= 16; ++s) {
-        const int64_t chunk = ((n + s - 1) / s + 127) / 128 * 128, slices = (n + chunk - 1) / chunk;
-        if (slices != s || chunk < 256) continue;
-        const double t = longest(wide * (double)chunk / (double)n, wide_work) + 4.5 + 1e-6 * (double)(s * k * d);
-        if (t < best) best = t, cut = PlainSlices{(int)s, chunk, k * cut.ld, cut.ld};
-    }
-    return cut;
-}
-
 template <typename T>
 hipError_t launch_forward_plain(const T *X, const T *W, const T *bias, T *Y, T *X_proj, int64_t n, int64_t d_in,
                                 int64_t d_out, int64_t k, int kind, SketchState st, hipStream_t stream, const PlainSlices &cut, void *ws) {
@@ -197,7 +128,7 @@ hipError_t launch_forward_plain(const T *X, const T *W, const T *bias, T *Y, T *
         p.ga.M = n, p.ga.N = d_out, p.ga.K = d_in, p.ga.alpha = 1.0f;
     }
     if (X_proj != nullptr) p.gs = sketch_args<T>(X, X_proj, n, d_in, k, kind, st, cut, ws);
-    const hipError_t e = launch_pass<T>(p, Y != nullptr, X_proj != nullptr, false, load_mode<T>(d_in, d_in), stream);
+    const hipError_t e = launch_pass<T>(p, Y != nullptr, X_proj != nullptr, false, load_mode(sizeof(T), d_in, d_in), stream);
     return e != hipSuccess || cut.slices <= 1 || X_proj == nullptr ? e : finish_slices<T>(p.gs, X_proj, stream);
 }
 
@@ -212,7 +143,7 @@ hipError_t launch_backward_plain(const T *dY, const T *W, T *dX, T *G, T *dbias,
     }
     if (G != nullptr) p.gs = sketch_args<T>(dY, G, n, d_out, k, kind, st, cut, ws);
     if (dbias != nullptr) p.gc = colsum_args<T>(dY, dbias, n, d_out, accumulate_dbias, &p.colsum_blocks);
-    const hipError_t e = launch_pass<T>(p, dX != nullptr, G != nullptr, true, load_mode<T>(d_in, d_out), stream);
+    const hipError_t e = launch_pass<T>(p, dX != nullptr, G != nullptr, true, load_mode(sizeof(T), d_in, d_out), stream);
     return e != hipSuccess || cut.slices <= 1 || G == nullptr ? e : finish_slices<T>(p.gs, G, stream);
 }
 
@@ -222,7 +153,7 @@ hipError_t launch_tn_plain(const Tin *A, int64_t lda, const Tin *B, Tout *C, int
     PlainArgs g{};
     g.A = A, g.lda = lda, g.B = B, g.ldb = n, g.C = C, g.ldc = n, g.M = m, g.N = n, g.K = kk, g.alpha = 1.0f;
     g.accumulate = accumulate ? 1 : 0;
-    const int mode = load_mode<Tin>(m, n);
+    const int mode = load_mode(sizeof(Tin), m, n);
     if (mode == 0) return launch_tn<Tin, Tout, 0, 0>(g, stream);
     if constexpr (sizeof(Tin) == 4) {
         if (mode == 4) return launch_tn<Tin, Tout, 4, 4>(g, stream);

@@ -6,7 +6,6 @@
 namespace rmm {
 
 // Which tile shapes a launch uses.
-enum { PLAIN_BIG = 0, PLAIN_MID = 1, PLAIN_TINY = 2 };
 struct PlainLaunch {
     PlainArgs ga, gs;
     ColsumArgs gc;

@@ -18,7 +18,7 @@ pytestmark = pytest.mark.gpu
                                         ((6365, 632, 576, 318), rmm.GAUSSIAN),
                                         ((4100, 264, 1000, 300), rmm.GAUSSIAN),    # a contraction of five steps
                                         ((1201, 896, 3656, 240), rmm.RADEMACHER),  # 64 sketch work-groups beside 290 tiles
-                                        ((3001, 1304, 520, 600), rmm.GAUSSIAN),    # half as many slices as alone
+                                        ((3001, 1304, 520, 600), rmm.GAUSSIAN),    # fewer slices than alone
                                         ((1500, 1544, 520, 1400), rmm.RADEMACHER)])
 def test_passes_with_plans_of_their_own(shape, kind):
     n, d_in, d_out, k = shape

@@ -1,5 +1,6 @@
 """GPU: plain products on each tile of the menu (64 x 64 to 128 x 256; 256 x 256: test_gpu_large_tiles.py) at contractions
-of one step, fewer steps than LDS stages, an odd number and a ragged last one, with ragged edges, against the fp64 oracle."""
+of one step, fewer steps than LDS stages, an odd number and a ragged last one, with ragged edges, against the fp64 oracle.
+(test_launch_plans.py: these shapes take these tiles.)"""
 import math
 
 import pytest

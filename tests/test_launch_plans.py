@@ -1,0 +1,109 @@
+"""CPU: the rules that choose tiles and token slices (csrc/launch_plans.hpp, compiled for the host).  The shapes of the GPU
+tests are there for the kernel that serves them: here each is asked for it."""
+import ctypes
+import os
+import shutil
+import subprocess
+
+import pytest
+
+import test_gpu_large_tiles
+import test_gpu_pair_plans
+import test_gpu_plain_tiles
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+HEADER = os.path.join(HERE, "..", "paper_2201_13195_amd", "csrc", "launch_plans.hpp")
+TILES = ["256x256", "128x256", "128x128 split", "128x128", "64x128", "64x64", "32x32", "128x128 compact"]   # GEMM_LARGE ..
+SOURCE = """
+#include "%s"
+using namespace rmm;
+extern "C" {
+int plain_tile(int64_t m, int64_t n, int64_t kk) { return gemm_cfg(m, n, kk); }
+int variance_tile(int64_t n, int64_t d_in, int64_t d_out) { return xty_cfg(d_in, d_out, n); }
+static void put(const SketchPlan &p, int64_t *o) { o[0] = p.cfg, o[1] = p.slices, o[2] = p.per_tail, o[3] = p.splits, o[4] = p.tiles, o[5] = p.shares(); }
+void sketch_plan(int64_t n, int64_t d, int64_t k, int kind, int64_t *o) { put(plan_sketch(n, d, k, kind, true), o); }
+int pass_plan(int64_t n, int64_t d_sk, int64_t d_other, int64_t k, int kind, int64_t *o) {
+    const PassPlan p = plan_pass(n, d_sk, d_other, k, kind);
+    put(p.sketch, o);
+    return p.plain.cfg;
+}
+void backward_plan(int64_t n, int64_t d_in, int64_t d_out, int64_t k, int kind, int with_dbias, int64_t *o) {
+    put(plan_backward(n, d_in, d_out, k, kind, with_dbias != 0).sketch, o);
+}
+}
+"""
+
+
+class Sketch:
+    def __init__(self, o):
+        self.cfg, self.slices, self.per_tail, self.splits, self.tiles, self.shares = o
+
+
+class Plans:
+    def __init__(self, lib):
+        self.lib = lib
+
+    def _sketch(self, f, *a):
+        o = (ctypes.c_int64 * 6)()
+        r = f(*[ctypes.c_int64(x) for x in a[:-1]], ctypes.c_int(a[-1]), o)
+        return Sketch(list(o)), r
+
+    def plain(self, m, n, kk):
+        return TILES[self.lib.plain_tile(*map(ctypes.c_int64, (m, n, kk)))]
+
+    def variance(self, n, d_in, d_out):
+        return TILES[self.lib.variance_tile(*map(ctypes.c_int64, (n, d_in, d_out)))]
+
+    def sketch(self, n, d, k, kind):
+        return self._sketch(self.lib.sketch_plan, n, d, k, kind)[0]
+
+    def forward(self, n, d_in, d_out, k, kind):
+        s, cfg = self._sketch(self.lib.pass_plan, n, d_in, d_out, k, kind)
+        return TILES[cfg], s
+
+    def backward(self, n, d_in, d_out, k, kind, with_dbias=False):
+        tile = TILES[self._sketch(self.lib.pass_plan, n, d_out, d_in, k, kind)[1]]
+        o = (ctypes.c_int64 * 6)()
+        self.lib.backward_plan(*[ctypes.c_int64(x) for x in (n, d_in, d_out, k)], ctypes.c_int(kind), ctypes.c_int(with_dbias), o)
+        return tile, Sketch(list(o))
+
+
+@pytest.fixture(scope="module")
+def plans(tmp_path_factory):
+    if shutil.which("g++") is None:
+        pytest.skip("no host compiler")
+    where = tmp_path_factory.mktemp("plans")
+    src, lib = str(where / "plans.cpp"), str(where / "plans.so")
+    with open(src, "w") as f:
+        f.write(SOURCE % HEADER)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Wextra", "-Werror", "-shared", "-fPIC", src, "-o", lib], check=True)
+    return Plans(ctypes.CDLL(lib))
+
+
+def cases(test):
+    """What a test is parametrised with."""
+    return [m for m in test.pytestmark if m.name == "parametrize"][0].args[1]
+
+
+def test_plain_products_take_the_tiles_that_their_tests_name(plans):
+    for (n, width, contractions), tile in zip(test_gpu_plain_tiles.TILES, ("64x64", "64x128", "128x128", "128x128 split", "128x256")):
+        for c in contractions:
+            assert plans.plain(n, width, c) == tile, (n, width, c)
+    taken = [plans.plain(d_out - d_out % 8, d_in, k) for d_out, d_in, k in cases(test_gpu_plain_tiles.test_weight_gradient_on_every_tile)]
+    assert taken == ["64x128", "128x128", "128x128 split", "128x256", "64x64"]
+    for n, d_in, d_out, _ in test_gpu_large_tiles.SHAPES:
+        assert (plans.plain(n, d_out, d_in) if d_out == 4000 else plans.plain(n, d_in, d_out)) == "256x256"
+
+
+
+def test_paired_launches_take_the_plans_that_their_tests_name(plans):
+    F, B = plans.forward, plans.backward
+    (a, b, c, d, e, f, g) = [(s, kind) for s, kind in cases(test_gpu_pair_plans.test_passes_with_plans_of_their_own)]
+    for shape, kind in (a, b, c):
+        assert F(*shape, kind)[0] == B(*shape, kind)[0] == "128x128 compact"
+    assert F(*d[0], d[1])[0] == "128x128 compact" and -(-d[0][1] // 64) == 5
+    assert F(*e[0], e[1])[0] == "128x128 compact" and F(*e[0], e[1])[1].shares == 64
+    n, d_in, d_out, k = f[0]
+    assert F(*f[0], f[1])[1].splits < plans.sketch(n, d_in, k, f[1]).splits and B(*f[0], f[1])[1].splits < plans.sketch(n, d_out, k, f[1]).splits
+    n, d_in, d_out, k = g[0]
+    assert F(*g[0], g[1])[1].splits == 1 < plans.sketch(n, d_in, k, g[1]).splits
