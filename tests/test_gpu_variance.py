@@ -60,6 +60,18 @@ def test_variance_stats_on_correlated_inputs_and_large_tiles():
     assert got[6] > 1.3 / n      # independent X, dY would give about 1/n
 
 
+# (n, d_in, d_out) of each tile that X^T dY runs with, ragged in every dimension (test_launch_plans.py: they are taken)
+TILES = [((201, 200, 136), "64x64"), ((201, 1800, 520), "64x128"), ((197, 2504, 776), "128x128"), ((1101, 2312, 776), "128x128 split"),
+         ((203, 1672, 2312), "128x256"), ((71, 4104, 4104), "256x256")]
+
+
+@pytest.mark.parametrize("shape,tile", TILES)
+def test_variance_stats_on_every_tile(shape, tile):
+    n, d_in, d_out = shape
+    X, _, dY = synth.layer_inputs(n, d_in, d_out, "bf16", (87, 88, 89))
+    check(X, dY, 30, rmm.RADEMACHER, "variance %s" % tile)
+
+
 def test_worked_example_of_the_paper(golden_dir):
     """Section 2.3, B = 2: (B-1) D2_SGD = 4 and B_proj D2_RMM = 2 + eps^2 + eps^-2 (X^T Y = 0)."""
     with open(os.path.join(golden_dir, "worked_example_b2.txt")) as f:

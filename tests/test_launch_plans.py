@@ -10,6 +10,7 @@ import pytest
 import test_gpu_large_tiles
 import test_gpu_pair_plans
 import test_gpu_plain_tiles
+import test_gpu_variance
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 HEADER = os.path.join(HERE, "..", "paper_2201_13195_amd", "csrc", "launch_plans.hpp")
@@ -94,6 +95,12 @@ def test_plain_products_take_the_tiles_that_their_tests_name(plans):
     for n, d_in, d_out, _ in test_gpu_large_tiles.SHAPES:
         assert (plans.plain(n, d_out, d_in) if d_out == 4000 else plans.plain(n, d_in, d_out)) == "256x256"
 
+
+
+def test_variance_monitors_reach_every_tile(plans):
+    for shape, tile in test_gpu_variance.TILES:
+        assert plans.variance(*shape) == tile, shape
+    assert {tile for _, tile in test_gpu_variance.TILES} == set(TILES) - {"32x32", "128x128 compact"}
 
 
 def test_paired_launches_take_the_plans_that_their_tests_name(plans):
