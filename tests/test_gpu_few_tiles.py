@@ -14,7 +14,8 @@ SHAPES = [
     # (n, d_in, d_out, k)
     (1, 8, 8, 1), (31, 40, 24, 7), (33, 504, 72, 66),        # less than a tile, a wave with nothing to do
     (64, 512, 520, 512), (65, 520, 512, 520),                 # contractions of one step of every wave and one chunk more
-    (512, 1024, 1024, 70), (520, 1032, 1016, 129),            # 512 and 561 tiles of 32 x 32
+    (512, 1024, 1024, 70), (520, 1032, 1016, 129),            # 512 and 561 tiles of 32 x 32, on 64 x 64 tiles by the contraction
+    (1277, 344, 344, 50), (1000, 512, 400, 30),               # 440 and 416 of them, two to a compute unit
     (40, 4104, 24, 300), (1000, 1032, 1000, 1030),            # long contractions, ragged everywhere
 ]
 

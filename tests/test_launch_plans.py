@@ -7,9 +7,12 @@ import subprocess
 
 import pytest
 
+import paper_2201_13195_amd as rmm
+import test_gpu_few_tiles
 import test_gpu_large_tiles
 import test_gpu_pair_plans
 import test_gpu_plain_tiles
+import test_gpu_sketch_slices
 import test_gpu_variance
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -96,6 +99,15 @@ def test_plain_products_take_the_tiles_that_their_tests_name(plans):
         assert (plans.plain(n, d_out, d_in) if d_out == 4000 else plans.plain(n, d_in, d_out)) == "256x256"
 
 
+def test_few_tile_is_reached_in_each_of_its_forms(plans):
+    """Y with a contraction of one step of every wave and of more, on up to 256 tiles of 32 x 32 and on up to 512."""
+    seen = set()
+    for n, d_in, d_out, _ in test_gpu_few_tiles.SHAPES:
+        if plans.plain(n, d_out, d_in) == "32x32":
+            seen.add((d_in > 512, -(-n // 32) * -(-d_out // 32) > 256))
+    assert seen == {(False, False), (True, False), (False, True)}          # (longer contractions on more than 256 tiles: 64 x 64)
+    assert all(plans.plain(n, w, c) != "32x32" for n in (600, 1000, 1300) for w in (504, 840) for c in (520, 1024) if -(-n // 32) * -(-w // 32) > 256)
+
 
 def test_variance_monitors_reach_every_tile(plans):
     for shape, tile in test_gpu_variance.TILES:
@@ -114,3 +126,13 @@ def test_paired_launches_take_the_plans_that_their_tests_name(plans):
     assert F(*f[0], f[1])[1].splits < plans.sketch(n, d_in, k, f[1]).splits and B(*f[0], f[1])[1].splits < plans.sketch(n, d_out, k, f[1]).splits
     n, d_in, d_out, k = g[0]
     assert F(*g[0], g[1])[1].splits == 1 < plans.sketch(n, d_in, k, g[1]).splits
+
+
+def test_short_last_slices_are_where_their_tests_expect_them(plans):
+    for (n, d_in, _, k), kind in cases(test_gpu_sketch_slices.test_long_and_short_slices_of_a_product_alone):
+        assert plans.sketch(n, d_in, k, kind).per_tail > 0, (n, d_in, k)
+    for shape, kind in test_gpu_sketch_slices.IN_A_PASS:
+        assert plans.backward(*shape, kind)[1].per_tail > 0, shape
+    for kind in (rmm.GAUSSIAN, rmm.RADEMACHER):
+        assert plans.backward(8192, 1000, 4000, 800, kind)[1].per_tail > 0
+        assert plans.backward(8192, 1000, 4000, 800, kind, True)[1].per_tail == 0
