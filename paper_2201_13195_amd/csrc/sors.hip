@@ -27,7 +27,7 @@ __device__ __forceinline__ int sors_phys(int t) { return t + (t >> 4); }
 template <int L>
 struct SorsShape {
     static constexpr int NP = 1 << L;                      // tokens the transform runs over
-    static constexpr int C = L <= 12 ? 8 : (32768 >> L);   // columns per work-group: NP * C <= 32768 floats
+    static constexpr int C = 32768 >> L;                   // columns per work-group: NP * C = 32768 floats
     static constexpr int PLANE = NP + NP / 16;
     static constexpr int SIGN_WORDS = NP / 32;
     static_assert(L >= 13 && L <= 15, "8192 .. 32768 tokens");
@@ -71,8 +71,6 @@ __device__ __forceinline__ void sors_lds_pass(float *planes, int tid) {
 
 template <int C>
 struct SorsRow;  // C bf16 values of one row as one load / store
-template <>
-struct SorsRow<8> { typedef sors_u32x4_t type; };
 template <>
 struct SorsRow<4> { typedef sors_u32x2_t type; };
 template <>
@@ -136,21 +134,15 @@ __global__ void __launch_bounds__(256) sors_kernel(SorsArgs g) {
     }
     __syncthreads();
 
-    // The other index bits, four at a time from the top; what is left below four goes last.
+    // The other index bits, four at a time from the top; the one to three that are left go last.
     constexpr int REST = L - 4;
-    if constexpr (REST >= 4) {
-        sors_lds_pass<L, REST - 4, 4>(planes, tid);
-        __syncthreads();
-    }
-    if constexpr (REST >= 8) {
-        sors_lds_pass<L, REST - 8, 4>(planes, tid);
-        __syncthreads();
-    }
-    if constexpr (REST % 4 != 0) {
-        sors_lds_pass<L, 0, REST % 4>(planes, tid);
-        __syncthreads();
-    }
-    static_assert(REST < 12, "at most two full passes and one partial pass below the first");
+    static_assert(REST > 8 && REST < 12, "two full passes and one partial pass below the first");
+    sors_lds_pass<L, REST - 4, 4>(planes, tid);
+    __syncthreads();
+    sors_lds_pass<L, REST - 8, 4>(planes, tid);
+    __syncthreads();
+    sors_lds_pass<L, 0, REST - 8>(planes, tid);
+    __syncthreads();
 
     // Row selection: sketch columns 4q .. 4q+3 take their rows from the four words of call q.
     for (int64_t q = tid; q < (g.k + 3) / 4; q += 256) {
