@@ -9,7 +9,8 @@
 
 #include "../../include/rmm.h"
 
-namespace rmm {
+// (hidden: the plans that plan_pass remembers belong to one library)
+namespace rmm __attribute__((visibility("hidden"))) {
 
 inline int64_t tiles_of(int64_t m, int64_t n, int64_t bm, int64_t bn) { return ((m + bm - 1) / bm) * ((n + bn - 1) / bn); }
 
