@@ -275,8 +275,10 @@ inline PairPlain pair_plain(int64_t n, int64_t m, int64_t kk) {
 // Plan of a pass: sketch of the n x d_sk operand, plain product n x d_other over d_sk.  Every sketch tile with slices for 64
 // to 320 work-groups, and 64 x 256 tiles with ShapeCompact where all work-groups are resident at once.  (4096 x 768 ->
 // 768, k = 410, with the sum of its slices: 26.9 -> 21.3 us; 4096 x 3072 -> 768, k = 2048, Rademacher 82 -> 69; 3001 x 1304 ->
-// 520, k = 600: 32 -> 24.)  At most a quarter more slices than alone: no pass needs much more workspace than its sketch
-// product.  Less than 0.8 us, which is what the model is off by at the smallest sizes, is not worth another order of additions
+// 520, k = 600: 32 -> 24.)  At most a quarter more slices than alone, and one more (two may become three; where the product
+// alone has one the pass has one): by so much a pass may ask for more scratch than its sketch product.  (Without the one, 3 % of the
+// passes of those ranges take other plans, 4 % slower on average; the worst of 60: 13986 x 376 -> 1808, k = 6993, Rademacher,
+// forward 102 -> 132 us.)  Less than 0.8 us, which is what the model is off by at the smallest sizes, is not worth another order of additions
 // than that of the product alone.
 inline PassPlan make_pass_plan(int64_t n, int64_t d_sk, int64_t d_other, int64_t k, int kind) {
     const SketchPlan alone = plan_sketch(n, d_sk, k, kind, true);

@@ -110,7 +110,7 @@ def test_product_package_does_not_touch_the_oracle():
 def test_workspace_sizes_follow_the_documented_layout(lib):
     """Host-side planning only: forward = the partial sums of the sketch of X; backward = G (k x d_out
     in the layer's dtype, rounded to 256 bytes) + the partial sums of the sketch of dY; inside a layer
-    pass the sketch may use fewer token slices than on its own, or up to a quarter more; partial-sum slices never
+    pass the sketch may use fewer token slices than on its own, or up to a quarter more and one; partial-sum slices never
     outnumber the 128-token blocks; the fp32 path needs no sketch partials; the variance op always
     needs some."""
     bf16, f32 = torch.bfloat16, torch.float32

@@ -5,6 +5,7 @@ import os
 import shutil
 import subprocess
 
+import numpy as np
 import pytest
 
 import paper_2201_13195_amd as rmm
@@ -136,3 +137,17 @@ def test_short_last_slices_are_where_their_tests_expect_them(plans):
     for kind in (rmm.GAUSSIAN, rmm.RADEMACHER):
         assert plans.backward(8192, 1000, 4000, 800, kind)[1].per_tail > 0
         assert plans.backward(8192, 1000, 4000, 800, kind, True)[1].per_tail == 0
+
+
+def test_passes_take_at_most_a_quarter_more_slices_and_one(plans):
+    """... than their sketch products alone, and one where those have one."""
+    g = np.random.default_rng(20260301)
+    seen = set()
+    for _ in range(3000):
+        n, d_sk, d_other = (int(x) for x in np.exp(g.uniform(np.log((256, 256, 256)), np.log((16384, 4096, 4096)))))
+        d_sk, d_other = d_sk // 8 * 8, d_other // 8 * 8
+        k, kind = max(65, int(g.choice([0.05, 0.1, 0.2, 0.5, 0.9]) * n)), int(g.integers(0, 2))
+        alone, ours = plans.sketch(n, d_sk, k, kind).splits, plans.forward(n, d_sk, d_other, k, kind)[1].splits
+        assert ours == 1 if alone == 1 else 4 * (ours - 1) <= 5 * alone, (n, d_sk, d_other, k, kind)
+        seen.add((alone, ours))
+    assert (2, 3) in seen
