@@ -99,6 +99,7 @@ hipError_t launch_backward_pair_bf16(const bf16_t *dY, const bf16_t *W, bf16_t *
                                      int64_t d_out, int64_t k, int kind, SketchState st, void *ws, hipStream_t stream,
                                      hipEvent_t ev_begin, hipEvent_t ev_end, bool with_dbias, bf16_t *dbias,
                                      bool accumulate_dbias);
+bool backward_pair_takes_colsum(int64_t n, int64_t d_in, int64_t d_out, int64_t k, int kind);
 
 // SORS sketch kind, bf16 (sors.hip): signs, Walsh-Hadamard transform along the tokens and row
 // selection in one kernel, no workspace.  Usable when sors_fast_ok(): d a multiple of 8 and at most

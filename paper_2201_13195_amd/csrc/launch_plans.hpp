@@ -353,19 +353,6 @@ inline PassPlan plan_backward(int64_t n, int64_t d_in, int64_t d_out, int64_t k,
 
 inline bool pass_pair_available(int64_t k) { return k > kSmallK; }
 
-// Where the bias gradient goes in a backward pass that has the paired launch: into the launch of
-// dW when that leaves at least 64 compute units idle (dW is short and mostly latency; where it runs on
-// few_tile, whose work-groups want a compute unit each, when the column blocks fit beside them);
-// otherwise into the paired launch when its last round leaves at least 16 idle (the sketch work-groups
-// of that round run for long, and dY is being read there anyway; plan_backward sees to it where it
-// can); otherwise into the launch of dW.
-inline bool backward_pair_takes_colsum(int64_t n, int64_t d_in, int64_t d_out, int64_t k, int kind) {
-    if (!pass_pair_available(k)) return false;
-    return !dw_takes_colsum(d_in, d_out, k) &&
-           (gemm_cfg(d_out, d_in, k) == GEMM_FEW ||
-            pair_idle(plan_backward(n, d_in, d_out, k, kind, true)) >= 16);
-}
-
 // The two dense kinds may take different tiles and slices; a workspace serves either (and both plans of
 // plan_backward: the one with a bias gradient has fewer slices).
 inline size_t sketch_workspace_bf16(int64_t n, int64_t d, int64_t k, int64_t d_other = 0) {

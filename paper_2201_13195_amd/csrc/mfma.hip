@@ -263,6 +263,19 @@ hipError_t launch_forward_pair_bf16(const bf16_t *X, const bf16_t *W, const bf16
     return launch_reduce(ws, X_proj, k, d_in, p.splits, stream);
 }
 
+// Where the bias gradient goes in a backward pass that has the paired launch: into the launch of
+// dW when that leaves at least 64 compute units idle (dW is short and mostly latency; where it runs on
+// few_tile, whose work-groups want a compute unit each, when the column blocks fit beside them);
+// otherwise into the paired launch when its last round leaves at least 16 idle (the sketch work-groups
+// of that round run for long, and dY is being read there anyway; plan_backward sees to it where it
+// can); otherwise into the launch of dW.
+bool backward_pair_takes_colsum(int64_t n, int64_t d_in, int64_t d_out, int64_t k, int kind) {
+    if (!pass_pair_available(k)) return false;
+    return !dw_takes_colsum(d_in, d_out, k) &&
+           (gemm_cfg(d_out, d_in, k) == GEMM_FEW ||
+            pair_idle(plan_backward(n, d_in, d_out, k, kind, true)) >= 16);
+}
+
 hipError_t launch_backward_pair_bf16(const bf16_t *dY, const bf16_t *W, bf16_t *dX, bf16_t *G, int64_t n, int64_t d_in,
                                      int64_t d_out, int64_t k, int kind, SketchState st, void *ws, hipStream_t stream,
                                      hipEvent_t ev_begin, hipEvent_t ev_end, bool with_dbias, bf16_t *dbias,
