@@ -15,7 +15,8 @@
  *     owns all of them; the library never allocates, frees or keeps a pointer.
  *   - `ws` is caller-provided device scratch of at least
  *     rmm_workspace_bytes(...) bytes (16-byte aligned); its contents are
- *     undefined on entry and on return.
+ *     undefined on entry and on return.  Where this header says so a call also runs in less, slower
+ *     and with its fp32 sums in another order; below that it is RMM_ERR_WORKSPACE.
  *   - `stream` is a hipStream_t passed as void* (NULL = the null stream).  All
  *     work is enqueued on it and the call returns without waiting.
  *   - Output buffers are overwritten; the one entry point that adds to what its
@@ -81,7 +82,7 @@ typedef enum {
     RMM_OK = 0,
     RMM_ERR_INVALID_ARG = -1, /* NULL required pointer, non-positive size, unknown enum, misaligned pointer */
     RMM_ERR_UNSUPPORTED = -2, /* sizes beyond the documented limits */
-    RMM_ERR_WORKSPACE = -3,   /* ws is NULL or ws_bytes is below rmm_workspace_bytes() */
+    RMM_ERR_WORKSPACE = -3,   /* ws is NULL or ws_bytes is below what the call runs in */
     RMM_ERR_LAUNCH = -4,      /* the HIP runtime refused a launch */
     RMM_ERR_SCRATCH_LIMIT = -5 /* rmm_sketch_static only: the shape needs more than RMM_STATIC_SCRATCH_BYTES */
 } rmm_status_t;
@@ -106,9 +107,10 @@ typedef struct {
     int32_t kind;  /* rmm_sketch_kind_t */
 } rmm_layer_desc_t;
 
-/* Scratch bytes the given operation needs for this shape.  For RMM_OP_SKETCH
+/* Scratch bytes the given operation takes for this shape.  For RMM_OP_SKETCH
  * only n, k, dtype, kind and d_in (= the operand's column count d) are read.
- * Returns 0 for an invalid descriptor. */
+ * Returns 0 for an invalid descriptor.  Less is enough for: a bf16 pass with a width that is no multiple
+ * of 8 (forward: none; backward: k * d_out * 2 bytes rounded up to 256). */
 size_t rmm_workspace_bytes(const rmm_layer_desc_t *desc, int op);
 
 /* Static, NUL-terminated description of a status code. */

@@ -39,33 +39,51 @@ bool use_mfma(const rmm_layer_desc_t *d) {
 // Workspace layout.
 //   sketch / forward: fp32 partial sums of the token slices of S^T A.
 //   backward: G = S^T dY (k x d_out, in the layer's dtype), then the partial sums.
-// fp32 has no token slices.  Nor has, off the MFMA path, rmm_sketch and the forward pass over an X whose width is no multiple of 8:
-// they have never asked for scratch, and callers may rely on it.
-// (bf16: rows of G start on 16 bytes)
-int64_t g_row(const rmm_layer_desc_t *d) { return d->dtype == RMM_DTYPE_BF16 ? (d->d_out + 7) / 8 * 8 : d->d_out; }
-size_t g_bytes(const rmm_layer_desc_t *d) { return round_up((size_t)d->k * g_row(d) * elem_bytes(d->dtype), 256); }
+// fp32 has no token slices.  Nor has, off the MFMA path, rmm_sketch and the forward pass over an X whose width is no multiple of 8.
+// Off the MFMA path a pass takes the slices that its workspace has room for, down to one: it has run in no scratch
+// but G's, and callers may have kept that size.
+// (bf16: rows of G start on 16 bytes, where there is room)
+struct GRows {
+    int64_t row;   // elements of a row of G
+    size_t bytes;  // of G
+};
+GRows g_rows(const rmm_layer_desc_t *d, size_t room = SIZE_MAX) {
+    auto rows = [&](int64_t row) { return GRows{row, round_up((size_t)d->k * row * elem_bytes(d->dtype), 256)}; };
+    const GRows even = rows(d->dtype == RMM_DTYPE_BF16 ? (d->d_out + 7) / 8 * 8 : d->d_out);
+    return even.bytes <= room ? even : rows(d->d_out);
+}
 // (the SORS kind has no token slices: its sketch products need no scratch)
 bool sliced_sketch(const rmm_layer_desc_t *d) { return use_mfma(d) && d->kind != RMM_SKETCH_SORS; }
 size_t ws_sketch(const rmm_layer_desc_t *d) {
     return sliced_sketch(d) ? round_up(sketch_workspace_bf16(d->n, d->d_in, d->k), 256) : 0;
 }
-PlainSlices plain_forward_slices(const rmm_layer_desc_t *d) {
-    return d->dtype == RMM_DTYPE_BF16 && !use_mfma(d) && d->d_in % 8 == 0 ? plain_slices(d->n, d->d_in, d->k, d->d_out, d->kind, false) : PlainSlices{1, 0, 0, 0};
+// Slices whose sums of k rows fit `room` bytes.
+int64_t slices_in(size_t room, int64_t k, int64_t row) { return (int64_t)(room / sizeof(float) / (size_t)k / (size_t)row); }
+PlainSlices plain_forward_slices(const rmm_layer_desc_t *d, size_t room) {
+    return d->dtype == RMM_DTYPE_BF16 && !use_mfma(d) && d->d_in % 8 == 0
+               ? plain_slices(d->n, d->d_in, d->k, d->d_out, d->kind, false, slices_in(room, d->k, d->d_in))
+               : PlainSlices{1, 0, 0, 0};
 }
-PlainSlices plain_backward_slices(const rmm_layer_desc_t *d) {
-    return d->dtype == RMM_DTYPE_BF16 && !use_mfma(d) ? plain_slices(d->n, d->d_out, d->k, d->d_in, d->kind, true) : PlainSlices{1, 0, 0, 0};
+PlainSlices plain_backward_slices(const rmm_layer_desc_t *d, size_t room) {
+    const GRows g = g_rows(d, room);
+    return d->dtype == RMM_DTYPE_BF16 && !use_mfma(d) && g.row % 8 == 0
+               ? plain_slices(d->n, d->d_out, d->k, d->d_in, d->kind, true, slices_in(room - g.bytes, d->k, g.row))
+               : PlainSlices{1, 0, 0, 0};
 }
 size_t slices_bytes(const PlainSlices &cut) {
     return cut.slices > 1 ? round_up((size_t)cut.slices * (size_t)cut.stride * sizeof(float), 256) : 0;
 }
 size_t ws_forward(const rmm_layer_desc_t *d) {
-    if (!use_mfma(d)) return slices_bytes(plain_forward_slices(d));
+    if (!use_mfma(d)) return slices_bytes(plain_forward_slices(d, SIZE_MAX));
     return sliced_sketch(d) ? round_up(sketch_workspace_bf16(d->n, d->d_in, d->k, d->d_out), 256) : 0;
 }
 size_t ws_backward(const rmm_layer_desc_t *d) {
-    if (!use_mfma(d)) return g_bytes(d) + slices_bytes(plain_backward_slices(d));
-    return g_bytes(d) + (sliced_sketch(d) ? round_up(sketch_workspace_bf16(d->n, d->d_out, d->k, d->d_in), 256) : 0);
+    if (!use_mfma(d)) return g_rows(d).bytes + slices_bytes(plain_backward_slices(d, SIZE_MAX));
+    return g_rows(d).bytes + (sliced_sketch(d) ? round_up(sketch_workspace_bf16(d->n, d->d_out, d->k, d->d_in), 256) : 0);
 }
+// The least that a pass runs in.
+size_t least_forward(const rmm_layer_desc_t *d) { return use_mfma(d) ? ws_forward(d) : 0; }
+size_t least_backward(const rmm_layer_desc_t *d) { return use_mfma(d) ? ws_backward(d) : g_rows(d, 0).bytes; }
 
 // variance monitors: per-block partials (doubles), then, off the MFMA path, X^T dY in fp32.
 int var_xty_partials(const rmm_layer_desc_t *d) {
@@ -160,12 +178,13 @@ bool pass_is_paired(const rmm_layer_desc_t *d, int op) {
 
 template <typename T>
 int forward_impl(const rmm_layer_desc_t *d, SketchState st, const void *X, const void *W, const void *bias, void *Y,
-                 void *X_proj, void *ws, hipStream_t stream, const StageEvents &ev) {
+                 void *X_proj, void *ws, size_t ws_bytes, hipStream_t stream, const StageEvents &ev) {
     const bool mfma = use_mfma(d);
+    const PlainSlices cut = X_proj != nullptr ? plain_forward_slices(d, ws_bytes) : PlainSlices{1, 0, 0, 0};
     if (!mfma && X_proj != nullptr && !separate_stage(ev.stage)) {  // both products in one launch
         StageScope scope(ev, RMM_STAGE_FWD_PAIR, stream);
         return from_hip(launch_forward_plain<T>((const T *)X, (const T *)W, (const T *)bias, (T *)Y, (T *)X_proj, d->n,
-                                                d->d_in, d->d_out, d->k, d->kind, st, stream, plain_forward_slices(d), ws));
+                                                d->d_in, d->d_out, d->k, d->kind, st, stream, cut, ws));
     }
     if (X_proj != nullptr && sliced_sketch(d) && !separate_stage(ev.stage) &&
         pass_pair_available(d->k)) {
@@ -194,16 +213,19 @@ int forward_impl(const rmm_layer_desc_t *d, SketchState st, const void *X, const
     if (X_proj == nullptr) return RMM_OK;  // no backward pass will follow: nothing to keep
     StageScope scope(ev, RMM_STAGE_FWD_XPROJ, stream);
     return sketch_impl<T>(d->n, d->d_in, d->k, d->kind, st, X, X_proj, mfma, ws, stream, ev,
-                          RMM_STAGE_FWD_XPROJ_PRODUCT, d->d_out, false, nullptr, false, plain_forward_slices(d));
+                          RMM_STAGE_FWD_XPROJ_PRODUCT, d->d_out, false, nullptr, false, cut);
 }
 
 template <typename T>
 int backward_impl(const rmm_layer_desc_t *d, SketchState st, const void *dY, const void *W, const void *X_proj,
-                  void *dX, void *dW, void *dbias, void *ws, hipStream_t stream, const StageEvents &ev,
+                  void *dX, void *dW, void *dbias, void *ws, size_t ws_bytes, hipStream_t stream, const StageEvents &ev,
                   bool accumulate) {
     hipError_t e;
     const bool mfma = use_mfma(d);
     T *G = (T *)ws;  // G = S^T dY, k x d_out
+    const GRows g = g_rows(d, ws_bytes);
+    void *sums = (char *)ws + g.bytes;
+    const PlainSlices cut = plain_backward_slices(d, ws_bytes);
     const bool paired_sors = mfma && d->kind == RMM_SKETCH_SORS && dX != nullptr && !separate_stage(ev.stage) &&
                              sors_pair_available(d->n, d->d_out, d->d_in, d->k);
     const bool own_db_stage = ev.stage == RMM_STAGE_BWD_DW || ev.stage == RMM_STAGE_BWD_DBIAS;
@@ -221,7 +243,7 @@ int backward_impl(const rmm_layer_desc_t *d, SketchState st, const void *dY, con
     if (paired_plain) {  // dX, G and db in one launch
         StageScope scope(ev, RMM_STAGE_BWD_PAIR, stream);
         e = launch_backward_plain<T>((const T *)dY, (const T *)W, (T *)dX, G, ev.stage == RMM_STAGE_BWD_DBIAS ? nullptr : (T *)dbias,
-                                     d->n, d->d_in, d->d_out, d->k, d->kind, st, accumulate, stream, plain_backward_slices(d), (char *)ws + g_bytes(d));
+                                     d->n, d->d_in, d->d_out, d->k, d->kind, st, accumulate, stream, cut, sums);
         if (e != hipSuccess) return RMM_ERR_LAUNCH;
     }
     const bool paired = paired_plain || paired_sors || (sliced_sketch(d) && dX != nullptr && !separate_stage(ev.stage) &&
@@ -231,7 +253,7 @@ int backward_impl(const rmm_layer_desc_t *d, SketchState st, const void *dY, con
         const bool timed = ev.stage == RMM_STAGE_BWD_PAIR;
         db_done = dbias != nullptr && !own_db_stage && backward_pair_takes_colsum(d->n, d->d_in, d->d_out, d->k, d->kind);
         e = launch_backward_pair_bf16((const bf16_t *)dY, (const bf16_t *)W, (bf16_t *)dX, (bf16_t *)G, d->n, d->d_in,
-                                      d->d_out, d->k, d->kind, st, (char *)ws + g_bytes(d), stream,
+                                      d->d_out, d->k, d->kind, st, sums, stream,
                                       timed ? ev.begin : nullptr, timed ? ev.end : nullptr, dbias != nullptr,
                                       db_done ? (bf16_t *)dbias : nullptr, accumulate);
         if (e != hipSuccess) return RMM_ERR_LAUNCH;
@@ -246,8 +268,8 @@ int backward_impl(const rmm_layer_desc_t *d, SketchState st, const void *dY, con
     }
     if (!paired) {
         StageScope scope(ev, RMM_STAGE_BWD_G, stream);
-        int rc = sketch_impl<T>(d->n, d->d_out, d->k, d->kind, st, dY, G, mfma, (char *)ws + g_bytes(d), stream, ev,
-                                RMM_STAGE_BWD_G_PRODUCT, d->d_in, dbias != nullptr, sors_db ? (bf16_t *)dbias : nullptr, accumulate, plain_backward_slices(d));
+        int rc = sketch_impl<T>(d->n, d->d_out, d->k, d->kind, st, dY, G, mfma, sums, stream, ev,
+                                RMM_STAGE_BWD_G_PRODUCT, d->d_in, dbias != nullptr, sors_db ? (bf16_t *)dbias : nullptr, accumulate, cut);
         if (rc != RMM_OK) return rc;
     }
     if (mfma && dbias != nullptr && !db_done && !own_db_stage) {
@@ -260,7 +282,7 @@ int backward_impl(const rmm_layer_desc_t *d, SketchState st, const void *dY, con
         StageScope scope(ev, RMM_STAGE_BWD_DW, stream);
         e = mfma ? launch_dw_bf16((const bf16_t *)G, (const bf16_t *)X_proj, (bf16_t *)dW, d->k, d->d_in, d->d_out,
                                   stream, accumulate)
-                 : launch_tn_plain<T, T>(G, g_row(d), (const T *)X_proj, (T *)dW, d->d_out, d->d_in, d->k, stream, accumulate);
+                 : launch_tn_plain<T, T>(G, g.row, (const T *)X_proj, (T *)dW, d->d_out, d->d_in, d->k, stream, accumulate);
         if (e != hipSuccess) return RMM_ERR_LAUNCH;
     }
     if (dbias != nullptr && !db_done) {
@@ -360,16 +382,16 @@ int rmm_forward_profiled(const rmm_layer_desc_t *desc, rmm_rng_state_t state, co
     if (!aligned16(X) || !aligned16(W) || !aligned16(bias) || !aligned16(Y) || !aligned16(X_proj) || !aligned16(ws))
         return RMM_ERR_INVALID_ARG;
     if (!grid_ok(desc->n) || !grid_ok(desc->k)) return RMM_ERR_UNSUPPORTED;
-    const size_t need = X_proj != nullptr ? ws_forward(desc) : 0;
-    if (need > 0 && (ws == nullptr || ws_bytes < need)) return RMM_ERR_WORKSPACE;
+    if (ws == nullptr) ws_bytes = 0;
+    if (X_proj != nullptr && ws_bytes < least_forward(desc)) return RMM_ERR_WORKSPACE;
     const SketchState st = make_state(state.seed, state.offset, desc->n);
     hipStream_t s = (hipStream_t)stream;
     StageEvents ev;
     ev.stage = stage;
     ev.begin = (hipEvent_t)ev_begin;
     ev.end = (hipEvent_t)ev_end;
-    return desc->dtype == RMM_DTYPE_BF16 ? forward_impl<bf16_t>(desc, st, X, W, bias, Y, X_proj, ws, s, ev)
-                                         : forward_impl<float>(desc, st, X, W, bias, Y, X_proj, ws, s, ev);
+    return desc->dtype == RMM_DTYPE_BF16 ? forward_impl<bf16_t>(desc, st, X, W, bias, Y, X_proj, ws, ws_bytes, s, ev)
+                                         : forward_impl<float>(desc, st, X, W, bias, Y, X_proj, ws, ws_bytes, s, ev);
 }
 
 int rmm_forward(const rmm_layer_desc_t *desc, rmm_rng_state_t state, const void *X, const void *W, const void *bias,
@@ -387,8 +409,7 @@ static int backward_checked(const rmm_layer_desc_t *desc, rmm_rng_state_t state,
         !aligned16(ws))
         return RMM_ERR_INVALID_ARG;
     if (!grid_ok(desc->n) || !grid_ok(desc->k) || !grid_ok(desc->d_out)) return RMM_ERR_UNSUPPORTED;
-    const size_t need = ws_backward(desc);
-    if (need > 0 && (ws == nullptr || ws_bytes < need)) return RMM_ERR_WORKSPACE;
+    if (ws == nullptr || ws_bytes < least_backward(desc)) return RMM_ERR_WORKSPACE;
     const SketchState st = make_state(state.seed, state.offset, desc->n);
     hipStream_t s = (hipStream_t)stream;
     StageEvents ev;
@@ -396,8 +417,8 @@ static int backward_checked(const rmm_layer_desc_t *desc, rmm_rng_state_t state,
     ev.begin = (hipEvent_t)ev_begin;
     ev.end = (hipEvent_t)ev_end;
     return desc->dtype == RMM_DTYPE_BF16
-               ? backward_impl<bf16_t>(desc, st, dY, W, X_proj, dX, dW, dbias, ws, s, ev, accumulate)
-               : backward_impl<float>(desc, st, dY, W, X_proj, dX, dW, dbias, ws, s, ev, accumulate);
+               ? backward_impl<bf16_t>(desc, st, dY, W, X_proj, dX, dW, dbias, ws, ws_bytes, s, ev, accumulate)
+               : backward_impl<float>(desc, st, dY, W, X_proj, dX, dW, dbias, ws, ws_bytes, s, ev, accumulate);
 }
 
 int rmm_backward_profiled(const rmm_layer_desc_t *desc, rmm_rng_state_t state, const void *dY, const void *W,

@@ -418,8 +418,8 @@ struct PlainSlices {
 // contraction element, a 128 x 128 one 22 and a 32 x 32 one 6; a launch ends no sooner than its longest tile, nor than all its tiles on 256 compute
 // units; slices add a launch of 4.5 us that reads their sums.  3000 x 768 -> 1001, Gaussian, k = 300: forward 43 us in one
 // slice, 30 in two; backward 53, 43 in two.  4096 x 1024 -> 111, k = 205: backward 62, 20 in eleven.  Where the two come out
-// alike (within 1 us) there are none.
-inline PlainSlices plain_slices(int64_t n, int64_t d, int64_t k, int64_t d_other, int kind, bool backward) {
+// alike (within 1 us) there are none.  At most `most`: what the caller's scratch holds.
+inline PlainSlices plain_slices(int64_t n, int64_t d, int64_t k, int64_t d_other, int kind, bool backward, int64_t most = 16) {
     PlainSlices cut{1, n, 0, (d + 7) / 8 * 8};
     if (load_mode(2, d, d_other) == 0) return cut;
     const int cfg = plain_cfg(2, n, d_other, backward);
@@ -434,7 +434,7 @@ inline PlainSlices plain_slices(int64_t n, int64_t d, int64_t k, int64_t d_other
         return most > all ? most : all;
     };
     double best = (small ? longest(narrow, narrow * (double)tiles_of(k, d, 32, 32)) : longest(wide, wide_work)) - 1.0;
-    for (int64_t s = 2; s <= 16; ++s) {
+    for (int64_t s = 2; s <= 16 && s <= most; ++s) {
         const int64_t chunk = ((n + s - 1) / s + 127) / 128 * 128, slices = (n + chunk - 1) / chunk;
         if (slices != s || chunk < 256) continue;
         const double t = longest(wide * (double)chunk / (double)n, wide_work) + 4.5 + 1e-6 * (double)(s * k * d);
