@@ -109,8 +109,10 @@ typedef struct {
 
 /* Scratch bytes the given operation takes for this shape.  For RMM_OP_SKETCH
  * only n, k, dtype, kind and d_in (= the operand's column count d) are read.
- * Returns 0 for an invalid descriptor.  Less is enough for: a bf16 pass with a width that is no multiple
- * of 8 (forward: none; backward: k * d_out * 2 bytes rounded up to 256). */
+ * Returns 0 for an invalid descriptor.  A bf16 pass runs in less too: with a width that is no multiple of
+ * 8 in none (forward) or k * d_out * 2 bytes rounded up to 256 (backward); with k > 64 and widths that are multiples
+ * of 8 in the fp32 sums of two token slices where it asks for more of them (forward 8 * k * d_in bytes; backward
+ * 2 * k * d_out and 8 * k * d_out, each rounded up to 256). */
 size_t rmm_workspace_bytes(const rmm_layer_desc_t *desc, int op);
 
 /* Static, NUL-terminated description of a status code. */

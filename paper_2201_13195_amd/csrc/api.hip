@@ -40,8 +40,8 @@ bool use_mfma(const rmm_layer_desc_t *d) {
 //   sketch / forward: fp32 partial sums of the token slices of S^T A.
 //   backward: G = S^T dY (k x d_out, in the layer's dtype), then the partial sums.
 // fp32 has no token slices.  Nor has, off the MFMA path, rmm_sketch and the forward pass over an X whose width is no multiple of 8.
-// Off the MFMA path a pass takes the slices that its workspace has room for, down to one: it has run in no scratch
-// but G's, and callers may have kept that size.
+// A pass takes the slices that its workspace has room for, down to two on the MFMA path and down to one off it: it has run in
+// less scratch than it asks for now, and callers may have kept that size.
 // (bf16: rows of G start on 16 bytes, where there is room)
 struct GRows {
     int64_t row;   // elements of a row of G
@@ -82,8 +82,12 @@ size_t ws_backward(const rmm_layer_desc_t *d) {
     return g_rows(d).bytes + (sliced_sketch(d) ? round_up(sketch_workspace_bf16(d->n, d->d_out, d->k, d->d_in), 256) : 0);
 }
 // The least that a pass runs in.
-size_t least_forward(const rmm_layer_desc_t *d) { return use_mfma(d) ? ws_forward(d) : 0; }
-size_t least_backward(const rmm_layer_desc_t *d) { return use_mfma(d) ? ws_backward(d) : g_rows(d, 0).bytes; }
+size_t least_forward(const rmm_layer_desc_t *d) {
+    return sliced_sketch(d) ? round_up(least_sketch_workspace_bf16(d->n, d->d_in, d->k, d->d_out), 256) : 0;
+}
+size_t least_backward(const rmm_layer_desc_t *d) {
+    return g_rows(d, 0).bytes + (sliced_sketch(d) ? round_up(least_sketch_workspace_bf16(d->n, d->d_out, d->k, d->d_in), 256) : 0);
+}
 
 // variance monitors: per-block partials (doubles), then, off the MFMA path, X^T dY in fp32.
 int var_xty_partials(const rmm_layer_desc_t *d) {
@@ -156,7 +160,7 @@ template <typename T>
 int sketch_impl(int64_t n, int64_t d, int64_t k, int kind, SketchState st, const void *A, void *out, bool mfma,
                 void *ws, hipStream_t stream, const StageEvents &ev = StageEvents(), int product_stage = RMM_STAGE_NONE,
                 int64_t d_other = 0, bool with_dbias = false, bf16_t *colsum = nullptr, bool accumulate = false,
-                const PlainSlices &cut = PlainSlices{1, 0, 0, 0}) {
+                const PlainSlices &cut = PlainSlices{1, 0, 0, 0}, int64_t room = kMostSlices) {
     const bool timed = product_stage != RMM_STAGE_NONE && ev.stage == product_stage;
     if (kind == RMM_SKETCH_SORS && mfma && sors_fast_ok(n, d)) {  // fast transform; otherwise S is applied densely below
         StageScope scope(ev, product_stage, stream);
@@ -164,7 +168,7 @@ int sketch_impl(int64_t n, int64_t d, int64_t k, int kind, SketchState st, const
     }
     if (mfma && kind != RMM_SKETCH_SORS)
         return from_hip(launch_sketch_bf16((const bf16_t *)A, (bf16_t *)out, n, d, k, kind, st, ws, stream,
-                                           timed ? ev.begin : nullptr, timed ? ev.end : nullptr, d_other, with_dbias));
+                                           timed ? ev.begin : nullptr, timed ? ev.end : nullptr, d_other, with_dbias, room));
     StageScope scope(ev, product_stage, stream);
     return from_hip(launch_forward_plain<T>((const T *)A, nullptr, nullptr, nullptr, (T *)out, n, d, d, k, kind, st, stream, cut, ws));
 }
@@ -181,6 +185,7 @@ int forward_impl(const rmm_layer_desc_t *d, SketchState st, const void *X, const
                  void *X_proj, void *ws, size_t ws_bytes, hipStream_t stream, const StageEvents &ev) {
     const bool mfma = use_mfma(d);
     const PlainSlices cut = X_proj != nullptr ? plain_forward_slices(d, ws_bytes) : PlainSlices{1, 0, 0, 0};
+    const int64_t room = X_proj != nullptr ? slices_in(ws_bytes, d->k, d->d_in) : 0;
     if (!mfma && X_proj != nullptr && !separate_stage(ev.stage)) {  // both products in one launch
         StageScope scope(ev, RMM_STAGE_FWD_PAIR, stream);
         return from_hip(launch_forward_plain<T>((const T *)X, (const T *)W, (const T *)bias, (T *)Y, (T *)X_proj, d->n,
@@ -190,7 +195,7 @@ int forward_impl(const rmm_layer_desc_t *d, SketchState st, const void *X, const
         pass_pair_available(d->k)) {
         const bool timed = ev.stage == RMM_STAGE_FWD_PAIR;
         return from_hip(launch_forward_pair_bf16((const bf16_t *)X, (const bf16_t *)W, (const bf16_t *)bias, (bf16_t *)Y,
-                                                 (bf16_t *)X_proj, d->n, d->d_in, d->d_out, d->k, d->kind, st, ws, stream,
+                                                 (bf16_t *)X_proj, d->n, d->d_in, d->d_out, d->k, d->kind, st, ws, room, stream,
                                                  timed ? ev.begin : nullptr, timed ? ev.end : nullptr));
     }
     if (X_proj != nullptr && mfma && d->kind == RMM_SKETCH_SORS && !separate_stage(ev.stage) &&
@@ -205,7 +210,7 @@ int forward_impl(const rmm_layer_desc_t *d, SketchState st, const void *X, const
         hipError_t e =
             mfma ? launch_linear_nt_bf16((const bf16_t *)X, (const bf16_t *)W, (const bf16_t *)bias, (bf16_t *)Y,
                                          d->n, d->d_in, d->d_out,
-                                         X_proj != nullptr && pass_is_paired(d, RMM_OP_FORWARD) ? d->k : 0, d->kind, stream)
+                                         X_proj != nullptr && pass_is_paired(d, RMM_OP_FORWARD) ? d->k : 0, d->kind, room, stream)
                  : launch_forward_plain<T>((const T *)X, (const T *)W, (const T *)bias, (T *)Y, nullptr, d->n, d->d_in,
                                            d->d_out, d->k, d->kind, st, stream, PlainSlices{1, 0, 0, 0}, nullptr);
         if (e != hipSuccess) return RMM_ERR_LAUNCH;
@@ -213,7 +218,7 @@ int forward_impl(const rmm_layer_desc_t *d, SketchState st, const void *X, const
     if (X_proj == nullptr) return RMM_OK;  // no backward pass will follow: nothing to keep
     StageScope scope(ev, RMM_STAGE_FWD_XPROJ, stream);
     return sketch_impl<T>(d->n, d->d_in, d->k, d->kind, st, X, X_proj, mfma, ws, stream, ev,
-                          RMM_STAGE_FWD_XPROJ_PRODUCT, d->d_out, false, nullptr, false, cut);
+                          RMM_STAGE_FWD_XPROJ_PRODUCT, d->d_out, false, nullptr, false, cut, room);
 }
 
 template <typename T>
@@ -226,6 +231,7 @@ int backward_impl(const rmm_layer_desc_t *d, SketchState st, const void *dY, con
     const GRows g = g_rows(d, ws_bytes);
     void *sums = (char *)ws + g.bytes;
     const PlainSlices cut = plain_backward_slices(d, ws_bytes);
+    const int64_t room = slices_in(ws_bytes - g.bytes, d->k, d->d_out);
     const bool paired_sors = mfma && d->kind == RMM_SKETCH_SORS && dX != nullptr && !separate_stage(ev.stage) &&
                              sors_pair_available(d->n, d->d_out, d->d_in, d->k);
     const bool own_db_stage = ev.stage == RMM_STAGE_BWD_DW || ev.stage == RMM_STAGE_BWD_DBIAS;
@@ -251,9 +257,9 @@ int backward_impl(const rmm_layer_desc_t *d, SketchState st, const void *dY, con
     bool db_done = sors_db || (paired_plain && ev.stage != RMM_STAGE_BWD_DBIAS);
     if (paired && !paired_sors && !paired_plain) {
         const bool timed = ev.stage == RMM_STAGE_BWD_PAIR;
-        db_done = dbias != nullptr && !own_db_stage && backward_pair_takes_colsum(d->n, d->d_in, d->d_out, d->k, d->kind);
+        db_done = dbias != nullptr && !own_db_stage && backward_pair_takes_colsum_in(d->n, d->d_in, d->d_out, d->k, d->kind, room);
         e = launch_backward_pair_bf16((const bf16_t *)dY, (const bf16_t *)W, (bf16_t *)dX, (bf16_t *)G, d->n, d->d_in,
-                                      d->d_out, d->k, d->kind, st, sums, stream,
+                                      d->d_out, d->k, d->kind, st, sums, room, stream,
                                       timed ? ev.begin : nullptr, timed ? ev.end : nullptr, dbias != nullptr,
                                       db_done ? (bf16_t *)dbias : nullptr, accumulate);
         if (e != hipSuccess) return RMM_ERR_LAUNCH;
@@ -261,7 +267,7 @@ int backward_impl(const rmm_layer_desc_t *d, SketchState st, const void *dY, con
     if (!paired && dX != nullptr) {  // dX = dY W: B(kk, c) = W[kk][c]
         StageScope scope(ev, RMM_STAGE_BWD_DX, stream);
         e = mfma ? launch_linear_nn_bf16((const bf16_t *)dY, (const bf16_t *)W, (bf16_t *)dX, d->n, d->d_in, d->d_out,
-                                         pass_is_paired(d, RMM_OP_BACKWARD) ? d->k : 0, d->kind, stream)
+                                         pass_is_paired(d, RMM_OP_BACKWARD) ? d->k : 0, d->kind, room, stream)
                  : launch_backward_plain<T>((const T *)dY, (const T *)W, (T *)dX, nullptr, nullptr, d->n, d->d_in,
                                             d->d_out, d->k, d->kind, st, false, stream, PlainSlices{1, 0, 0, 0}, nullptr);
         if (e != hipSuccess) return RMM_ERR_LAUNCH;
@@ -269,7 +275,7 @@ int backward_impl(const rmm_layer_desc_t *d, SketchState st, const void *dY, con
     if (!paired) {
         StageScope scope(ev, RMM_STAGE_BWD_G, stream);
         int rc = sketch_impl<T>(d->n, d->d_out, d->k, d->kind, st, dY, G, mfma, sums, stream, ev,
-                                RMM_STAGE_BWD_G_PRODUCT, d->d_in, dbias != nullptr, sors_db ? (bf16_t *)dbias : nullptr, accumulate, cut);
+                                RMM_STAGE_BWD_G_PRODUCT, d->d_in, dbias != nullptr, sors_db ? (bf16_t *)dbias : nullptr, accumulate, cut, room);
         if (rc != RMM_OK) return rc;
     }
     if (mfma && dbias != nullptr && !db_done && !own_db_stage) {

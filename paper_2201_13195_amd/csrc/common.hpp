@@ -60,15 +60,15 @@ template <typename T>
 hipError_t launch_colsum(const T *A, T *out, int64_t n, int64_t d, hipStream_t stream, bool accumulate = false);
 
 // bf16 MFMA path (mfma.hip).  Usable when mfma_shape_ok(); `ws` for the sketch
-// must hold sketch_workspace_bf16() bytes (fp32 partial sums of the token slices).
+// must hold sketch_workspace_bf16() bytes (fp32 partial sums of the token slices), in a pass those of `room` slices.
 // launch_sketch_bf16 records the optional event pair around its product kernel
 // alone (the sum over token slices, when there is one, comes after `ev_end`).
 // (`pair_k`, if not 0: with the tiles of the pass's paired launch with a sketch of pair_k columns, for passes that launch
 // their products one by one)
 hipError_t launch_linear_nt_bf16(const bf16_t *X, const bf16_t *W, const bf16_t *bias, bf16_t *Y, int64_t n,
-                                 int64_t d_in, int64_t d_out, int64_t pair_k, int kind, hipStream_t stream);
+                                 int64_t d_in, int64_t d_out, int64_t pair_k, int kind, int64_t room, hipStream_t stream);
 hipError_t launch_linear_nn_bf16(const bf16_t *dY, const bf16_t *W, bf16_t *dX, int64_t n, int64_t d_in,
-                                 int64_t d_out, int64_t pair_k, int kind, hipStream_t stream);
+                                 int64_t d_out, int64_t pair_k, int kind, int64_t room, hipStream_t stream);
 hipError_t launch_dw_bf16(const bf16_t *G, const bf16_t *X_proj, bf16_t *dW, int64_t k, int64_t d_in, int64_t d_out,
                           hipStream_t stream, bool accumulate = false);
 // dW together with db = column sums of dY (n x d_out, 16-byte aligned, d_out a multiple of 8) in
@@ -82,7 +82,7 @@ hipError_t launch_dw_colsum_bf16(const bf16_t *G, const bf16_t *X_proj, bf16_t *
 // pass that also makes the bias gradient (it may slice the tokens otherwise).
 hipError_t launch_sketch_bf16(const bf16_t *A, bf16_t *out, int64_t n, int64_t d, int64_t k, int kind, SketchState st,
                               void *ws, hipStream_t stream, hipEvent_t ev_begin = nullptr,
-                              hipEvent_t ev_end = nullptr, int64_t d_other = 0, bool with_dbias = false);
+                              hipEvent_t ev_end = nullptr, int64_t d_other = 0, bool with_dbias = false, int64_t room = kMostSlices);
 
 // One launch for the two products of a pass that do not depend on each other: Y = X W^T (+ bias)
 // with the sketch product of X (forward), dX = dY W with the sketch product of dY (backward; G is
@@ -90,16 +90,17 @@ hipError_t launch_sketch_bf16(const bf16_t *A, bf16_t *out, int64_t n, int64_t d
 // the separate launches above (same kernels, same slices).  Only where pass_pair_available() says so;
 // the optional event pair brackets the paired kernel alone.
 hipError_t launch_forward_pair_bf16(const bf16_t *X, const bf16_t *W, const bf16_t *bias, bf16_t *Y, bf16_t *X_proj,
-                                    int64_t n, int64_t d_in, int64_t d_out, int64_t k, int kind, SketchState st, void *ws,
+                                    int64_t n, int64_t d_in, int64_t d_out, int64_t k, int kind, SketchState st, void *ws, int64_t room,
                                     hipStream_t stream, hipEvent_t ev_begin = nullptr, hipEvent_t ev_end = nullptr);
 // `with_dbias`: the pass makes the bias gradient, in whichever launch.  With `dbias` this launch takes the
 // column sums of dY, on the compute units its last round leaves idle; backward_pair_takes_colsum() says where that
 // beats the launch of dW.
 hipError_t launch_backward_pair_bf16(const bf16_t *dY, const bf16_t *W, bf16_t *dX, bf16_t *G, int64_t n, int64_t d_in,
-                                     int64_t d_out, int64_t k, int kind, SketchState st, void *ws, hipStream_t stream,
+                                     int64_t d_out, int64_t k, int kind, SketchState st, void *ws, int64_t room, hipStream_t stream,
                                      hipEvent_t ev_begin, hipEvent_t ev_end, bool with_dbias, bf16_t *dbias,
                                      bool accumulate_dbias);
-bool backward_pair_takes_colsum(int64_t n, int64_t d_in, int64_t d_out, int64_t k, int kind);
+bool backward_pair_takes_colsum_in(int64_t n, int64_t d_in, int64_t d_out, int64_t k, int kind, int64_t room);
+bool backward_pair_takes_colsum(int64_t n, int64_t d_in, int64_t d_out, int64_t k, int kind);  // in any scratch asked for
 
 // SORS sketch kind, bf16 (sors.hip): signs, Walsh-Hadamard transform along the tokens and row
 // selection in one kernel, no workspace.  Usable when sors_fast_ok(): d a multiple of 8 and at most

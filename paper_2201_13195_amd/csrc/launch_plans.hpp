@@ -160,18 +160,20 @@ constexpr SketchMenu kSketchMenu[kSketchTiles] = {{128, 256, {1.18, 0.91}}, {128
 // 18 % at most (32000 x 512, k = 640: 49 us, 128 x 256 42), 0.3 and 1.9 % with Rademacher.  ((16384 x 4096, k = 410)
 // 64 x 512: 79 us, 128 x 512: 107; (10000 x 3000, k = 1000) 128 x 384: 81, 64 x 256: 108; 4096 x 3072, k = 3686
 // unsliced on 128 x 384: 102, 128 x 512: 107.)
-// `limited`: the caller may be rmm_sketch_static.
-inline SketchPlan plan_sketch(int64_t n, int64_t d, int64_t k, int kind, bool limited) {
+// `limited`: the caller may be rmm_sketch_static.  `room`: token slices that the caller's scratch holds.
+constexpr int64_t kMostSlices = 64;
+inline SketchPlan plan_sketch(int64_t n, int64_t d, int64_t k, int kind, bool limited, int64_t room = kMostSlices) {
     // rmm_sketch_static serves the shapes whose partial results fit RMM_STATIC_SCRATCH_BYTES with the plainest
     // tiling (rows by k, columns by d); those keep fitting, whichever tile they run with.
-    int64_t most = 64;
+    int64_t most = kMostSlices;
     const double partial_bytes = (double)k * (double)d * 4.0;
     if (limited) {
         const int64_t tiles = d >= 1024 ? tiles_of(k, d, k <= 512 ? 64 : 128, 512) : d % 384 == 0 ? tiles_of(k, d, k <= 512 ? 64 : 128, 384) : tiles_of(k, d, 128, 256);
         const int64_t blocks = (n + 127) / 128, s = tiles >= 256 ? 1 : blocks < 256 / tiles ? blocks : 256 / tiles;
         const int64_t chunk = (blocks + s - 1) / s, slices = (blocks + chunk - 1) / chunk, fit = (int64_t)((double)RMM_STATIC_SCRATCH_BYTES / partial_bytes);
-        if (slices == 1 || slices <= fit) most = fit < 1 ? 1 : fit < 64 ? fit : 64;
+        if (slices == 1 || slices <= fit) most = fit < 1 ? 1 : fit < kMostSlices ? fit : kMostSlices;
     }
+    if (room < most) most = room;
     SketchPlan best{};
     double best_us = -1.0;
     static const int order[kSketchTiles] = {SK_WIDE64, SK_WIDE, SK_MID64, SK_MID, SK_NARROW64, SK_NARROW};
@@ -280,8 +282,8 @@ inline PairPlain pair_plain(int64_t n, int64_t m, int64_t kk) {
 // passes of those ranges take other plans, 4 % slower on average; the worst of 60: 13986 x 376 -> 1808, k = 6993, Rademacher,
 // forward 102 -> 132 us.)  Less than 0.8 us, which is what the model is off by at the smallest sizes, is not worth another order of additions
 // than that of the product alone.
-inline PassPlan make_pass_plan(int64_t n, int64_t d_sk, int64_t d_other, int64_t k, int kind) {
-    const SketchPlan alone = plan_sketch(n, d_sk, k, kind, true);
+inline PassPlan make_pass_plan(int64_t n, int64_t d_sk, int64_t d_other, int64_t k, int kind, int64_t room) {
+    const SketchPlan alone = plan_sketch(n, d_sk, k, kind, true, room);
     const double partial_mb = (double)k * (double)d_sk * 4e-6;
     const PairPlain usual = pair_plain(n, d_other, d_sk);
     const PairPlain compact{GEMM_COMPACT, (int)gemm_tiles(GEMM_COMPACT, n, d_other)};
@@ -292,7 +294,7 @@ inline PassPlan make_pass_plan(int64_t n, int64_t d_sk, int64_t d_other, int64_t
         for (int target : {64, 96, 128, 192, 256, 320}) {
             SketchPlan p;
             p.cfg = cfg, p.tiles = tiles_of(k, d_sk, kSketchMenu[cfg].bm, kSketchMenu[cfg].bn);
-            slice_sketch(p, n, target, 4.0 / kSketchMenu[cfg].step_us[kind != 0], 64);
+            slice_sketch(p, n, target, 4.0 / kSketchMenu[cfg].step_us[kind != 0], room);
             if (p.slices == slices && p.per_tail == per_tail) continue;
             slices = p.slices, per_tail = p.per_tail;
             if (p.splits > 1 && (alone.splits == 1 || 4 * (p.splits - 1) > 5 * alone.splits)) continue;
@@ -307,21 +309,27 @@ inline PassPlan make_pass_plan(int64_t n, int64_t d_sk, int64_t d_other, int64_t
 }
 
 // The same, remembered: a pass asks for its plan three times (workspace of either kind, launch), and it depends on the
-// sizes alone.
-inline PassPlan plan_pass(int64_t n, int64_t d_sk, int64_t d_other, int64_t k, int kind) {
+// sizes alone.  With scratch for fewer slices than it takes, another one for these.
+inline PassPlan plan_pass(int64_t n, int64_t d_sk, int64_t d_other, int64_t k, int kind, int64_t room = kMostSlices) {
     struct Entry {
-        int64_t n, d_sk, d_other, k;
+        int64_t n, d_sk, d_other, k, room;
         int kind;
         PassPlan plan;
     };
     constexpr size_t ENTRIES = 64;
     static thread_local Entry memo[ENTRIES];  // (n = 0: empty)
+    if (room < kMostSlices) {
+        const PassPlan p = plan_pass(n, d_sk, d_other, k, kind);
+        if (p.sketch.splits == 1 || p.sketch.splits <= room) return p;
+    } else {
+        room = kMostSlices;
+    }
     kind = kind != 0;
     const uint64_t h = ((uint64_t)n * 0x9E3779B97F4A7C15u ^ (uint64_t)d_sk * 0xC2B2AE3D27D4EB4Fu ^ (uint64_t)d_other * 0x165667B19E3779F9u ^
-                        (uint64_t)k * 0x27D4EB2F165667C5u) + (uint64_t)kind;
+                        (uint64_t)k * 0x27D4EB2F165667C5u) + (uint64_t)(2 * room + kind);
     Entry &e = memo[(h ^ h >> 32) % ENTRIES];
-    if (e.n != n || e.d_sk != d_sk || e.d_other != d_other || e.k != k || e.kind != kind)
-        e = Entry{n, d_sk, d_other, k, kind, make_pass_plan(n, d_sk, d_other, k, kind)};
+    if (e.n != n || e.d_sk != d_sk || e.d_other != d_other || e.k != k || e.room != room || e.kind != kind)
+        e = Entry{n, d_sk, d_other, k, room, kind, make_pass_plan(n, d_sk, d_other, k, kind, room)};
     return e.plan;
 }
 
@@ -342,8 +350,8 @@ inline int64_t pair_idle(const PassPlan &p) {
 // Plan of a backward pass.  With a bias gradient that the launch of dW has no room for, short last slices
 // that take the compute units its column sums need are given up (16384 x 1024 -> 4096, k = 1638: 208 sketch
 // work-groups instead of 243).
-inline PassPlan plan_backward(int64_t n, int64_t d_in, int64_t d_out, int64_t k, int kind, bool with_dbias) {
-    const PassPlan p = plan_pass(n, d_out, d_in, k, kind);
+inline PassPlan plan_backward(int64_t n, int64_t d_in, int64_t d_out, int64_t k, int kind, bool with_dbias, int64_t room = kMostSlices) {
+    const PassPlan p = plan_pass(n, d_out, d_in, k, kind, room);
     if (!with_dbias || p.sketch.per_tail == 0 || p.sketch.slices < 2 || dw_takes_colsum(d_in, d_out, k) || pair_idle(p) >= 16) return p;
     PassPlan even = p;
     const int64_t units = (n + 63) / 64, len = (units + p.sketch.slices - 1) / p.sketch.slices;
@@ -368,6 +376,11 @@ inline size_t sketch_workspace_bf16(int64_t n, int64_t d, int64_t k, int64_t d_o
         if (bytes > most) most = bytes;
     }
     return most;
+}
+// The least that a pass runs in: two slices where it asks for any.
+inline size_t least_sketch_workspace_bf16(int64_t n, int64_t d, int64_t k, int64_t d_other) {
+    const size_t most = sketch_workspace_bf16(n, d, k, d_other);
+    return k <= kSmallK || most == 0 ? most : (size_t)2 * (size_t)k * (size_t)d * sizeof(float);
 }
 
 // ---- fp32 products, and bf16 products of widths the kernels above refuse (plain_kernels.hpp).

@@ -132,20 +132,20 @@ struct EventPair {
 // `pair_k`, if not 0: with the tiles the product has in its pass's paired launch with a sketch of pair_k columns, so that a
 // pass whose products are launched one by one (to be timed) gives the same bits.  (ShapeCompact adds in ShapeMid's order.)
 template <int BMODE>
-static hipError_t launch_plain_of_pass(const GemmArgs &g, int64_t pair_k, int kind, hipStream_t stream) {
+static hipError_t launch_plain_of_pass(const GemmArgs &g, int64_t pair_k, int kind, int64_t room, hipStream_t stream) {
     if (pair_k == 0) return launch_gemm<A_KCONTIG, BMODE>(gemm_cfg(g.M, g.N, g.K), g, stream);
-    const int cfg = (kind == RMM_SKETCH_SORS ? pair_plain(g.M, g.N, g.K) : plan_pass(g.M, g.K, g.N, pair_k, kind).plain).cfg;
+    const int cfg = (kind == RMM_SKETCH_SORS ? pair_plain(g.M, g.N, g.K) : plan_pass(g.M, g.K, g.N, pair_k, kind, room).plain).cfg;
     return launch_gemm<A_KCONTIG, BMODE>(cfg == GEMM_COMPACT ? GEMM_MID : cfg, g, stream);
 }
 
 hipError_t launch_linear_nt_bf16(const bf16_t *X, const bf16_t *W, const bf16_t *bias, bf16_t *Y, int64_t n,
-                                 int64_t d_in, int64_t d_out, int64_t pair_k, int kind, hipStream_t stream) {
-    return launch_plain_of_pass<B_KCONTIG>(args_nt(X, W, bias, Y, n, d_in, d_out), pair_k, kind, stream);
+                                 int64_t d_in, int64_t d_out, int64_t pair_k, int kind, int64_t room, hipStream_t stream) {
+    return launch_plain_of_pass<B_KCONTIG>(args_nt(X, W, bias, Y, n, d_in, d_out), pair_k, kind, room, stream);
 }
 
 hipError_t launch_linear_nn_bf16(const bf16_t *dY, const bf16_t *W, bf16_t *dX, int64_t n, int64_t d_in,
-                                 int64_t d_out, int64_t pair_k, int kind, hipStream_t stream) {
-    return launch_plain_of_pass<B_NCONTIG>(args_nn(dY, W, dX, n, d_in, d_out), pair_k, kind, stream);
+                                 int64_t d_out, int64_t pair_k, int kind, int64_t room, hipStream_t stream) {
+    return launch_plain_of_pass<B_NCONTIG>(args_nn(dY, W, dX, n, d_in, d_out), pair_k, kind, room, stream);
 }
 
 hipError_t launch_dw_bf16(const bf16_t *G, const bf16_t *X_proj, bf16_t *dW, int64_t k, int64_t d_in, int64_t d_out,
@@ -220,7 +220,7 @@ hipError_t launch_xty_norms_bf16(const bf16_t *X, const bf16_t *dY, double *part
 
 hipError_t launch_sketch_bf16(const bf16_t *A, bf16_t *out, int64_t n, int64_t d, int64_t k, int kind, SketchState st,
                               void *ws, hipStream_t stream, hipEvent_t ev_begin, hipEvent_t ev_end, int64_t d_other,
-                              bool with_dbias) {
+                              bool with_dbias, int64_t room) {
     EventPair pev(ev_begin, ev_end, stream);
     if (k <= kSmallK) {  // bound by one pass over A: streaming kernel
         SmallkArgs a{};
@@ -239,8 +239,8 @@ hipError_t launch_sketch_bf16(const bf16_t *A, bf16_t *out, int64_t n, int64_t d
         if (e != hipSuccess || slices == 1) return e;
         return launch_reduce(ws, out, k, d, slices, stream);
     }
-    const SketchPlan p = with_dbias    ? plan_backward(n, d_other, d, k, kind, true).sketch
-                         : d_other > 0 ? plan_pass(n, d, d_other, k, kind).sketch
+    const SketchPlan p = with_dbias    ? plan_backward(n, d_other, d, k, kind, true, room).sketch
+                         : d_other > 0 ? plan_pass(n, d, d_other, k, kind, room).sketch
                                        : plan_sketch(n, d, k, kind, true);
     const GemmArgs g = args_sketch(A, n, d, k, st, p, out, ws);
     hipError_t e = launch_sketch_plan(p, kind, g, stream);
@@ -250,10 +250,10 @@ hipError_t launch_sketch_bf16(const bf16_t *A, bf16_t *out, int64_t n, int64_t d
 }
 
 hipError_t launch_forward_pair_bf16(const bf16_t *X, const bf16_t *W, const bf16_t *bias, bf16_t *Y, bf16_t *X_proj,
-                                    int64_t n, int64_t d_in, int64_t d_out, int64_t k, int kind, SketchState st, void *ws,
+                                    int64_t n, int64_t d_in, int64_t d_out, int64_t k, int kind, SketchState st, void *ws, int64_t room,
                                     hipStream_t stream, hipEvent_t ev_begin, hipEvent_t ev_end) {
     const GemmArgs ga = args_nt(X, W, bias, Y, n, d_in, d_out);
-    const PassPlan pass = plan_pass(n, d_in, d_out, k, kind);
+    const PassPlan pass = plan_pass(n, d_in, d_out, k, kind, room);
     const SketchPlan &p = pass.sketch;
     const GemmArgs gb = args_sketch(X, n, d_in, k, st, p, X_proj, ws);
     EventPair pev(ev_begin, ev_end, stream);
@@ -269,19 +269,22 @@ hipError_t launch_forward_pair_bf16(const bf16_t *X, const bf16_t *W, const bf16
 // otherwise into the paired launch when its last round leaves at least 16 idle (the sketch work-groups
 // of that round run for long, and dY is being read there anyway; plan_backward sees to it where it
 // can); otherwise into the launch of dW.
-bool backward_pair_takes_colsum(int64_t n, int64_t d_in, int64_t d_out, int64_t k, int kind) {
+bool backward_pair_takes_colsum_in(int64_t n, int64_t d_in, int64_t d_out, int64_t k, int kind, int64_t room) {
     if (!pass_pair_available(k)) return false;
     return !dw_takes_colsum(d_in, d_out, k) &&
            (gemm_cfg(d_out, d_in, k) == GEMM_FEW ||
-            pair_idle(plan_backward(n, d_in, d_out, k, kind, true)) >= 16);
+            pair_idle(plan_backward(n, d_in, d_out, k, kind, true, room)) >= 16);
+}
+bool backward_pair_takes_colsum(int64_t n, int64_t d_in, int64_t d_out, int64_t k, int kind) {
+    return backward_pair_takes_colsum_in(n, d_in, d_out, k, kind, kMostSlices);
 }
 
 hipError_t launch_backward_pair_bf16(const bf16_t *dY, const bf16_t *W, bf16_t *dX, bf16_t *G, int64_t n, int64_t d_in,
-                                     int64_t d_out, int64_t k, int kind, SketchState st, void *ws, hipStream_t stream,
+                                     int64_t d_out, int64_t k, int kind, SketchState st, void *ws, int64_t room, hipStream_t stream,
                                      hipEvent_t ev_begin, hipEvent_t ev_end, bool with_dbias, bf16_t *dbias,
                                      bool accumulate_dbias) {
     const GemmArgs ga = args_nn(dY, W, dX, n, d_in, d_out);
-    const PassPlan pass = plan_backward(n, d_in, d_out, k, kind, with_dbias);
+    const PassPlan pass = plan_backward(n, d_in, d_out, k, kind, with_dbias, room);
     const SketchPlan &p = pass.sketch;
     const GemmArgs gb = args_sketch(dY, n, d_out, k, st, p, G, ws);
     const ColsumArgs gc{dY, dbias, n, d_out, accumulate_dbias ? 1 : 0, colsum_lpr(d_out, 2)};

@@ -75,3 +75,25 @@ def test_odd_widths_in_any_scratch_from_none_up(shape, kind):
     forward = [0] + [s for s in (2 * k * d_in * 4 - 4, 2 * k * d_in * 4, need[0]) if s <= need[0]]
     backward = [up(k * d_out * 2)] + [s for s in (padded, padded + 2 * k * row * 4, need[1]) if s <= need[1]]
     check_pass(shape, kind, forward, backward)
+
+
+@pytest.mark.parametrize("shape,kind", [((4096, 768, 3072, 410), rmm.GAUSSIAN), ((3001, 520, 1304, 600), rmm.RADEMACHER),
+                                        ((2690, 864, 2376, 269), rmm.GAUSSIAN),        # (6 slices of X asked for)
+                                        ((8192, 1000, 4000, 800), rmm.RADEMACHER),     # short last slices; column sums in the pair
+                                        ((4096, 3072, 768, 2048), rmm.GAUSSIAN)])
+def test_token_slices_follow_the_scratch(shape, kind):
+    """From two slices up; and with the same scratch the same bits, whichever launches."""
+    n, d_in, d_out, k = shape
+    need = [rmm.rmm_workspace_bytes(n, d_in, d_out, k, torch.bfloat16, kind, op) for op in (binding.OP_FORWARD, binding.OP_BACKWARD)]
+    g = up(k * d_out * 2)
+    forward = [s for s in (up(2 * k * d_in * 4), 3 * k * d_in * 4, 5 * k * d_in * 4 - 4, need[0]) if s <= need[0]]
+    backward = [g + s for s in (up(2 * k * d_out * 4), 3 * k * d_out * 4, 5 * k * d_out * 4 - 4, need[1] - g) if g + s <= need[1]]
+    if not forward:
+        forward = [0]
+    if not backward:
+        backward = [g]
+    check_pass(shape, kind, forward, backward)
+    if need[0] > 0:
+        with pytest.raises(rmm.RmmError) as e:
+            check_pass(shape, kind, [forward[0] - 1], [])
+        assert e.value.status == -3

@@ -27,6 +27,9 @@ int plain_tile(int64_t m, int64_t n, int64_t kk) { return gemm_cfg(m, n, kk); }
 int variance_tile(int64_t n, int64_t d_in, int64_t d_out) { return xty_cfg(d_in, d_out, n); }
 static void put(const SketchPlan &p, int64_t *o) { o[0] = p.cfg, o[1] = p.slices, o[2] = p.per_tail, o[3] = p.splits, o[4] = p.tiles, o[5] = p.shares(); }
 void sketch_plan(int64_t n, int64_t d, int64_t k, int kind, int64_t *o) { put(plan_sketch(n, d, k, kind, true), o); }
+void pass_plan_in(int64_t n, int64_t d_in, int64_t d_out, int64_t k, int64_t room, int kind, int64_t *o) {
+    put(plan_pass(n, d_in, d_out, k, kind, room).sketch, o), put(plan_backward(n, d_in, d_out, k, kind, true, room).sketch, o + 6);
+}
 int pass_plan(int64_t n, int64_t d_sk, int64_t d_other, int64_t k, int kind, int64_t *o) {
     const PassPlan p = plan_pass(n, d_sk, d_other, k, kind);
     put(p.sketch, o);
@@ -151,3 +154,19 @@ def test_passes_take_at_most_a_quarter_more_slices_and_one(plans):
         assert ours == 1 if alone == 1 else 4 * (ours - 1) <= 5 * alone, (n, d_sk, d_other, k, kind)
         seen.add((alone, ours))
     assert (2, 3) in seen
+
+
+def test_passes_take_no_more_slices_than_their_scratch_holds(plans):
+    """... from two up, and what they take without a limit where that fits."""
+    g = np.random.default_rng(20260302)
+    for _ in range(1000):
+        n, d_in, d_out = (int(x) // 8 * 8 for x in np.exp(g.uniform(np.log((256, 256, 256)), np.log((16384, 4096, 4096)))))
+        k, kind = max(65, int(g.choice([0.05, 0.1, 0.2, 0.5, 0.9]) * n)), int(g.integers(0, 2))
+        free = (plans.forward(n, d_in, d_out, k, kind)[1], plans.backward(n, d_in, d_out, k, kind, True)[1])
+        asked = (free[0].splits, plans.backward(n, d_in, d_out, k, kind)[1].splits)     # (a bias gradient may leave fewer)
+        for room in (2, 3, 4, 7, 16, 64, 1 << 40):
+            o = (ctypes.c_int64 * 12)()
+            plans.lib.pass_plan_in(*[ctypes.c_int64(x) for x in (n, d_in, d_out, k, room)], ctypes.c_int(kind), o)
+            for mine, theirs, splits in zip((Sketch(list(o)[:6]), Sketch(list(o)[6:])), free, asked):
+                assert 1 <= mine.splits <= room and mine.splits == mine.slices + (mine.per_tail > 0), (n, d_in, d_out, k, kind, room)
+                assert splits > room or (mine.cfg, mine.shares, mine.splits) == (theirs.cfg, theirs.shares, theirs.splits)
