@@ -89,15 +89,15 @@ size_t least_backward(const rmm_layer_desc_t *d) {
     return g_rows(d, 0).bytes + (sliced_sketch(d) ? round_up(least_sketch_workspace_bf16(d->n, d->d_out, d->k, d->d_in), 256) : 0);
 }
 
-// variance monitors: per-block partials (doubles), then, off the MFMA path, X^T dY in fp32.
-int var_xty_partials(const rmm_layer_desc_t *d) {
-    return use_mfma(d) ? xty_sumsq_tiles(d->n, d->d_in, d->d_out) : sumsq_blocks(d->d_in * d->d_out);
+// variance monitors: per-block partials (doubles), then, off the MFMA path, X^T dY in fp32.  (`room`: partials of X^T dY that there is scratch for)
+int var_xty_partials(const rmm_layer_desc_t *d, int64_t room = INT64_MAX) {
+    return use_mfma(d) ? xty_sumsq_tiles(d->n, d->d_in, d->d_out, room) : sumsq_blocks(d->d_in * d->d_out);
 }
-size_t var_partial_bytes(const rmm_layer_desc_t *d) {
-    return round_up(((size_t)3 * row_norm_blocks(d->n) + (size_t)var_xty_partials(d)) * sizeof(double), 256);
+size_t var_partial_bytes(const rmm_layer_desc_t *d, int64_t room = INT64_MAX) {
+    return round_up(((size_t)3 * row_norm_blocks(d->n) + (size_t)var_xty_partials(d, room)) * sizeof(double), 256);
 }
-size_t ws_variance(const rmm_layer_desc_t *d) {
-    return var_partial_bytes(d) + (use_mfma(d) ? 0 : round_up((size_t)d->d_in * d->d_out * sizeof(float), 256));
+size_t ws_variance(const rmm_layer_desc_t *d, int64_t room = INT64_MAX) {
+    return var_partial_bytes(d, room) + (use_mfma(d) ? 0 : round_up((size_t)d->d_in * d->d_out * sizeof(float), 256));
 }
 
 int from_hip(hipError_t e) { return e == hipSuccess ? RMM_OK : RMM_ERR_LAUNCH; }
@@ -453,14 +453,17 @@ int rmm_variance_stats(const rmm_layer_desc_t *desc, const void *X, const void *
     if (!aligned16(X) || !aligned16(dY) || !aligned16(ws) || ((uintptr_t)out & 7u) != 0) return RMM_ERR_INVALID_ARG;
     if (!use_mfma(desc) && !grid_ok(desc->d_in)) return RMM_ERR_UNSUPPORTED;  // plain X^T dY: d_in rows of tiles
     if (desc->kind == RMM_SKETCH_SORS) return RMM_ERR_UNSUPPORTED;  // Lemma 2.2 is about i.i.d. entries
-    if (ws == nullptr || ws_bytes < ws_variance(desc)) return RMM_ERR_WORKSPACE;
+    const int nb = row_norm_blocks(desc->n);
+    // (the MFMA path has run with a partial for every 128 x 128 tile: callers may have kept that size)
+    const int64_t room = (int64_t)(ws_bytes / 256 * 256 / sizeof(double)) - 3 * (int64_t)nb;
+    if (ws == nullptr || ws_bytes < ws_variance(desc, room)) return RMM_ERR_WORKSPACE;
     hipStream_t s = (hipStream_t)stream;
-    const int nb = row_norm_blocks(desc->n), nt = var_xty_partials(desc);
+    const int nt = var_xty_partials(desc, room);
     double *rows = (double *)ws, *xty = rows + 3 * (size_t)nb;
     hipError_t e;
     if (desc->dtype == RMM_DTYPE_BF16) {
         if (use_mfma(desc)) {
-            e = launch_xty_norms_bf16((const bf16_t *)X, (const bf16_t *)dY, xty, rows, desc->n, desc->d_in, desc->d_out, s);
+            e = launch_xty_norms_bf16((const bf16_t *)X, (const bf16_t *)dY, xty, rows, desc->n, desc->d_in, desc->d_out, room, s);
         } else {
             e = launch_row_norms<bf16_t>((const bf16_t *)X, (const bf16_t *)dY, desc->n, desc->d_in, desc->d_out, rows, s);
             if (e != hipSuccess) return RMM_ERR_LAUNCH;

@@ -135,7 +135,7 @@ hipError_t launch_sumsq(const float *A, int64_t elems, double *part, hipStream_t
 //   part[t] = sum of squares of tile t of X^T dY (d_in x d_out), bf16 MFMA path; xty_sumsq_tiles() tiles;
 //   rows = the row norms (part of launch_row_norms), in the same launch.
 hipError_t launch_xty_norms_bf16(const bf16_t *X, const bf16_t *dY, double *part, double *rows, int64_t n, int64_t d_in,
-                                 int64_t d_out, hipStream_t stream);
+                                 int64_t d_out, int64_t room, hipStream_t stream);
 hipError_t launch_variance_finalize(const double *rows, int nb, const double *xty, int nt, int64_t n, int64_t k,
                                     int kind, double *out, hipStream_t stream);
 

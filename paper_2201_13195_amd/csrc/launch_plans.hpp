@@ -97,12 +97,14 @@ inline int gemm_cfg(int64_t m, int64_t n, int64_t kk, bool filled = false) {
 // |X^T dY|_F^2 per tile for the variance monitors: the dW-type product (both operands stored
 // [token][feature]) with the squared-norm epilogue; the tiles of the other products, but for 32 x 32, beside the work-groups of
 // the row norms (6670 tokens, 608 x 1704: 270 tiles of 64 x 64 63 us, 140 of 64 x 128 49).
-inline int xty_cfg(int64_t m, int64_t n, int64_t kk) {
-    const int cfg = gemm_cfg(m, n, kk, true);
-    return cfg == GEMM_FEW ? GEMM_SMALL : cfg;
+// In scratch for less than a partial sum of each of these, 128 x 128 tiles.
+inline int xty_cfg(int64_t m, int64_t n, int64_t kk, int64_t room = INT64_MAX) {
+    const int cfg = gemm_cfg(m, n, kk, true), small = cfg == GEMM_FEW ? GEMM_SMALL : cfg;
+    return gemm_tiles(small, m, n) <= room ? small : kk >= 1536 ? GEMM_SPLIT : GEMM_MID;
 }
-
-inline int xty_sumsq_tiles(int64_t n, int64_t d_in, int64_t d_out) { return (int)gemm_tiles(xty_cfg(d_in, d_out, n), d_in, d_out); }
+inline int xty_sumsq_tiles(int64_t n, int64_t d_in, int64_t d_out, int64_t room = INT64_MAX) {
+    return (int)gemm_tiles(xty_cfg(d_in, d_out, n, room), d_in, d_out);
+}
 
 // Which kernel serves a sketch product with k > 64 and how its token dimension is cut.  The work-group
 // generates the sketch tile into LDS and all eight waves read it.

@@ -203,12 +203,12 @@ static hipError_t launch_xty_norms(const GemmArgs &g, const RowNormArgs &r, hipS
 }
 
 hipError_t launch_xty_norms_bf16(const bf16_t *X, const bf16_t *dY, double *part, double *rows, int64_t n, int64_t d_in,
-                                 int64_t d_out, hipStream_t stream) {
+                                 int64_t d_out, int64_t room, hipStream_t stream) {
     GemmArgs g{};
     g.A = X, g.lda = d_in, g.B = dY, g.ldb = d_out, g.C = part, g.ldc = d_out, g.bias = nullptr;
     g.M = d_in, g.N = d_out, g.K = n, g.alpha = 1.0f;
     const RowNormArgs r{X, dY, n, d_in, d_out, 1, rows};
-    switch (xty_cfg(g.M, g.N, g.K)) {
+    switch (xty_cfg(g.M, g.N, g.K, room)) {
         case GEMM_LARGE: return launch_xty_norms<ShapeLarge>(g, r, stream);
         case GEMM_WIDE: return launch_xty_norms<ShapeWide>(g, r, stream);
         case GEMM_SPLIT: return launch_xty_norms<ShapeSplit>(g, r, stream);

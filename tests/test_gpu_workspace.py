@@ -2,6 +2,7 @@
 but for the order of fp32 sums, and nothing written behind the scratch that was given."""
 import math
 
+import numpy as np
 import pytest
 import torch
 
@@ -97,3 +98,26 @@ def test_token_slices_follow_the_scratch(shape, kind):
         with pytest.raises(rmm.RmmError) as e:
             check_pass(shape, kind, [forward[0] - 1], [])
         assert e.value.status == -3
+
+
+@pytest.mark.parametrize("shape", [(201, 200, 136), (1000, 264, 520), (2100, 1800, 520), (197, 2504, 776)])
+def test_variance_monitors_in_less_scratch(shape):
+    """Down to what 128 x 128 tiles of X^T dY take, and not below it; the same values but for the order of the sums."""
+    n, d_in, d_out = shape
+    (X, _, dY), (Xd, _, dYd) = inputs(n, d_in, d_out)
+    need = rmm.rmm_workspace_bytes(n, d_in, d_out, 30, torch.bfloat16, rmm.GAUSSIAN, binding.OP_VARIANCE)
+    want = rmm.rmm_variance_stats(Xd, dYd, 30, rmm.GAUSSIAN).cpu()
+    xty = float(np.sum((synth.to_f64(X).T @ synth.to_f64(dY)) ** 2))
+    sizes = []
+    for size in range(need, 0, -256):
+        s = Scratch(size)
+        try:
+            got = rmm.rmm_variance_stats(Xd, dYd, 30, rmm.GAUSSIAN, ws=s.ws).cpu()
+        except rmm.RmmError as e:
+            assert e.status == -3
+            break
+        assert s.untouched(), (shape, size)
+        assert torch.allclose(got, want, rtol=1e-6, atol=0) and abs(float(got[3]) - xty) <= 2e-5 * xty, (shape, size)
+        sizes.append(size)
+    blocks = min((n + 7) // 8, 1024)                        # work-groups of the row norms: three values each
+    assert sizes[-1] == min(need, up(8 * (3 * blocks + -(-d_in // 128) * -(-d_out // 128))))
