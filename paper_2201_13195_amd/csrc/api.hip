@@ -59,16 +59,19 @@ size_t ws_sketch(const rmm_layer_desc_t *d) {
 }
 // Slices whose sums of k rows fit `room` bytes.
 int64_t slices_in(size_t room, int64_t k, int64_t row) { return (int64_t)(room / sizeof(float) / (size_t)k / (size_t)row); }
+const PlainSlices kOneSlice{1, 0, 0, 0, -1};
 PlainSlices plain_forward_slices(const rmm_layer_desc_t *d, size_t room) {
-    return d->dtype == RMM_DTYPE_BF16 && !use_mfma(d) && d->d_in % 8 == 0
-               ? plain_slices(d->n, d->d_in, d->k, d->d_out, d->kind, false, slices_in(room, d->k, d->d_in))
-               : PlainSlices{1, 0, 0, 0};
+    if (use_mfma(d)) return kOneSlice;
+    if (d->dtype == RMM_DTYPE_BF16 && d->d_in % 8 == 0)
+        return plain_slices(d->n, d->d_in, d->k, d->d_out, d->kind, false, slices_in(room, d->k, d->d_in));
+    return PlainSlices{1, 0, 0, 0, plain_cfg((int)elem_bytes(d->dtype), d->n, d->d_out, false)};
 }
 PlainSlices plain_backward_slices(const rmm_layer_desc_t *d, size_t room) {
+    if (use_mfma(d)) return kOneSlice;
     const GRows g = g_rows(d, room);
-    return d->dtype == RMM_DTYPE_BF16 && !use_mfma(d) && g.row % 8 == 0
-               ? plain_slices(d->n, d->d_out, d->k, d->d_in, d->kind, true, slices_in(room - g.bytes, d->k, g.row))
-               : PlainSlices{1, 0, 0, 0};
+    if (d->dtype == RMM_DTYPE_BF16 && g.row % 8 == 0)
+        return plain_slices(d->n, d->d_out, d->k, d->d_in, d->kind, true, slices_in(room - g.bytes, d->k, g.row));
+    return PlainSlices{1, 0, 0, 0, plain_cfg((int)elem_bytes(d->dtype), d->n, d->d_in, true)};
 }
 size_t slices_bytes(const PlainSlices &cut) {
     return cut.slices > 1 ? round_up((size_t)cut.slices * (size_t)cut.stride * sizeof(float), 256) : 0;
@@ -160,7 +163,7 @@ template <typename T>
 int sketch_impl(int64_t n, int64_t d, int64_t k, int kind, SketchState st, const void *A, void *out, bool mfma,
                 void *ws, hipStream_t stream, const StageEvents &ev = StageEvents(), int product_stage = RMM_STAGE_NONE,
                 int64_t d_other = 0, bool with_dbias = false, bf16_t *colsum = nullptr, bool accumulate = false,
-                const PlainSlices &cut = PlainSlices{1, 0, 0, 0}, int64_t room = kMostSlices) {
+                const PlainSlices &cut = kOneSlice, int64_t room = kMostSlices) {
     const bool timed = product_stage != RMM_STAGE_NONE && ev.stage == product_stage;
     if (kind == RMM_SKETCH_SORS && mfma && sors_fast_ok(n, d)) {  // fast transform; otherwise S is applied densely below
         StageScope scope(ev, product_stage, stream);
@@ -184,7 +187,7 @@ template <typename T>
 int forward_impl(const rmm_layer_desc_t *d, SketchState st, const void *X, const void *W, const void *bias, void *Y,
                  void *X_proj, void *ws, size_t ws_bytes, hipStream_t stream, const StageEvents &ev) {
     const bool mfma = use_mfma(d);
-    const PlainSlices cut = X_proj != nullptr ? plain_forward_slices(d, ws_bytes) : PlainSlices{1, 0, 0, 0};
+    const PlainSlices cut = X_proj != nullptr ? plain_forward_slices(d, ws_bytes) : kOneSlice;
     const int64_t room = X_proj != nullptr ? slices_in(ws_bytes, d->k, d->d_in) : 0;
     if (!mfma && X_proj != nullptr && !separate_stage(ev.stage)) {  // both products in one launch
         StageScope scope(ev, RMM_STAGE_FWD_PAIR, stream);
@@ -212,7 +215,7 @@ int forward_impl(const rmm_layer_desc_t *d, SketchState st, const void *X, const
                                          d->n, d->d_in, d->d_out,
                                          X_proj != nullptr && pass_is_paired(d, RMM_OP_FORWARD) ? d->k : 0, d->kind, room, stream)
                  : launch_forward_plain<T>((const T *)X, (const T *)W, (const T *)bias, (T *)Y, nullptr, d->n, d->d_in,
-                                           d->d_out, d->k, d->kind, st, stream, PlainSlices{1, 0, 0, 0}, nullptr);
+                                           d->d_out, d->k, d->kind, st, stream, cut, nullptr);
         if (e != hipSuccess) return RMM_ERR_LAUNCH;
     }
     if (X_proj == nullptr) return RMM_OK;  // no backward pass will follow: nothing to keep
@@ -230,7 +233,8 @@ int backward_impl(const rmm_layer_desc_t *d, SketchState st, const void *dY, con
     T *G = (T *)ws;  // G = S^T dY, k x d_out
     const GRows g = g_rows(d, ws_bytes);
     void *sums = (char *)ws + g.bytes;
-    const PlainSlices cut = plain_backward_slices(d, ws_bytes);
+    PlainSlices cut = plain_backward_slices(d, ws_bytes);
+    if (dX == nullptr) cut.cfg = -1;
     const int64_t room = slices_in(ws_bytes - g.bytes, d->k, d->d_out);
     const bool paired_sors = mfma && d->kind == RMM_SKETCH_SORS && dX != nullptr && !separate_stage(ev.stage) &&
                              sors_pair_available(d->n, d->d_out, d->d_in, d->k);
@@ -269,7 +273,7 @@ int backward_impl(const rmm_layer_desc_t *d, SketchState st, const void *dY, con
         e = mfma ? launch_linear_nn_bf16((const bf16_t *)dY, (const bf16_t *)W, (bf16_t *)dX, d->n, d->d_in, d->d_out,
                                          pass_is_paired(d, RMM_OP_BACKWARD) ? d->k : 0, d->kind, room, stream)
                  : launch_backward_plain<T>((const T *)dY, (const T *)W, (T *)dX, nullptr, nullptr, d->n, d->d_in,
-                                            d->d_out, d->k, d->kind, st, false, stream, PlainSlices{1, 0, 0, 0}, nullptr);
+                                            d->d_out, d->k, d->kind, st, false, stream, cut, nullptr);
         if (e != hipSuccess) return RMM_ERR_LAUNCH;
     }
     if (!paired) {

@@ -420,10 +420,13 @@ inline int load_mode(int elem_bytes, int64_t a, int64_t b) {
 inline bool rows_on_16(int64_t row) { return row % 8 == 0; }  // bf16
 
 // Token slices of a bf16 pass's sketch product: `slices` runs of `chunk` tokens, their fp32 sums `stride` elements apart in
-// scratch.  One slice: no scratch.  `ld`: row length of the result and of the sums (0: as wide as the operand).
+// scratch.  One slice: no scratch.  `ld`: row length of the result and of the sums (0: as wide as the operand).  `cfg`: tile of
+// the plain product of the pass (-1: none), which the sketch product's own tile depends on; the two take the same ones
+// launched one by one.
 struct PlainSlices {
     int slices;
     int64_t chunk, stride, ld;
+    int cfg;
 };
 
 // Token slices of the sketch product of a bf16 pass (sketch of an n x d operand, beside a product n x d_other).  An entry is
@@ -435,9 +438,9 @@ struct PlainSlices {
 // slice, 30 in two; backward 53, 43 in two.  4096 x 1024 -> 111, k = 205: backward 62, 20 in eleven.  Where the two come out
 // alike (within 1 us) there are none.  At most `most`: what the caller's scratch holds.
 inline PlainSlices plain_slices(int64_t n, int64_t d, int64_t k, int64_t d_other, int kind, bool backward, int64_t most = 16) {
-    PlainSlices cut{1, n, 0, (d + 7) / 8 * 8};
-    if (load_mode(2, d, d_other) == 0) return cut;
     const int cfg = plain_cfg(2, n, d_other, backward);
+    PlainSlices cut{1, n, 0, (d + 7) / 8 * 8, cfg};
+    if (load_mode(2, d, d_other) == 0) return cut;
     const int64_t tiles = tiles_of(k, d, 32, 128);
     const double per_cu = 1.0 / 256, chain = (cfg == PLAIN_TINY ? 6e-3 : cfg == PLAIN_MID ? 8e-3 : 22e-3) * (double)d,
                  plain_work = chain * (double)plain_tiles(cfg, n, d_other) * per_cu;
@@ -453,7 +456,7 @@ inline PlainSlices plain_slices(int64_t n, int64_t d, int64_t k, int64_t d_other
         const int64_t chunk = ((n + s - 1) / s + 127) / 128 * 128, slices = (n + chunk - 1) / chunk;
         if (slices != s || chunk < 256) continue;
         const double t = longest(wide * (double)chunk / (double)n, wide_work) + 4.5 + 1e-6 * (double)(s * k * d);
-        if (t < best) best = t, cut = PlainSlices{(int)s, chunk, k * cut.ld, cut.ld};
+        if (t < best) best = t, cut = PlainSlices{(int)s, chunk, k * cut.ld, cut.ld, cfg};
     }
     return cut;
 }

@@ -22,14 +22,18 @@ ColsumArgs colsum_args(const T *A, T *out, int64_t n, int64_t d, bool accumulate
 }
 
 template <typename T>
-hipError_t launch_pass(PlainLaunch &p, bool has_plain, bool has_sketch, bool b_rows_k, int mode, hipStream_t stream) {
-    p.cfg = mode == 0 ? PLAIN_TINY : has_plain ? plain_cfg(sizeof(T), p.ga.M, p.ga.N, b_rows_k) : PLAIN_MID;
+hipError_t launch_pass(PlainLaunch &p, bool has_plain, bool has_sketch, bool b_rows_k, int mode, int cfg, hipStream_t stream) {
+    if (mode == 0)
+        cfg = PLAIN_TINY;
+    else if (cfg < 0)
+        cfg = has_plain ? plain_cfg(sizeof(T), p.ga.M, p.ga.N, b_rows_k) : PLAIN_MID;
+    p.cfg = has_plain || mode == 0 ? cfg : PLAIN_MID;
     p.plain_blocks = has_plain ? (int)plain_tiles(p.cfg, p.ga.M, p.ga.N) : 0;
     p.sketch_blocks = 0;
     p.sketch_small = false;
     if (has_sketch) {
         // 32 x 32 tiles generate every entry four times as often as 32 x 128 tiles: only where those are few
-        p.sketch_small = mode == 0 || (p.gs.slices <= 1 && (p.cfg == PLAIN_TINY || (p.cfg == PLAIN_MID && tiles_of(p.gs.M, p.gs.N, 32, 128) < 64)));
+        p.sketch_small = mode == 0 || (p.gs.slices <= 1 && (cfg == PLAIN_TINY || (cfg == PLAIN_MID && tiles_of(p.gs.M, p.gs.N, 32, 128) < 64)));
         p.sketch_blocks = (int)tiles_of(p.gs.M, p.gs.N, 32, p.sketch_small ? 32 : 128) * (p.gs.slices > 1 ? p.gs.slices : 1);
     }
     if constexpr (sizeof(T) == 2) {
@@ -128,7 +132,7 @@ hipError_t launch_forward_plain(const T *X, const T *W, const T *bias, T *Y, T *
         p.ga.M = n, p.ga.N = d_out, p.ga.K = d_in, p.ga.alpha = 1.0f;
     }
     if (X_proj != nullptr) p.gs = sketch_args<T>(X, X_proj, n, d_in, k, kind, st, cut, ws);
-    const hipError_t e = launch_pass<T>(p, Y != nullptr, X_proj != nullptr, false, load_mode(sizeof(T), d_in, d_in), stream);
+    const hipError_t e = launch_pass<T>(p, Y != nullptr, X_proj != nullptr, false, load_mode(sizeof(T), d_in, d_in), cut.cfg, stream);
     return e != hipSuccess || cut.slices <= 1 || X_proj == nullptr ? e : finish_slices<T>(p.gs, X_proj, stream);
 }
 
@@ -143,7 +147,7 @@ hipError_t launch_backward_plain(const T *dY, const T *W, T *dX, T *G, T *dbias,
     }
     if (G != nullptr) p.gs = sketch_args<T>(dY, G, n, d_out, k, kind, st, cut, ws);
     if (dbias != nullptr) p.gc = colsum_args<T>(dY, dbias, n, d_out, accumulate_dbias, &p.colsum_blocks);
-    const hipError_t e = launch_pass<T>(p, dX != nullptr, G != nullptr, true, load_mode(sizeof(T), d_in, d_out), stream);
+    const hipError_t e = launch_pass<T>(p, dX != nullptr, G != nullptr, true, load_mode(sizeof(T), d_in, d_out), cut.cfg, stream);
     return e != hipSuccess || cut.slices <= 1 || G == nullptr ? e : finish_slices<T>(p.gs, G, stream);
 }
 

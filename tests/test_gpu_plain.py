@@ -8,7 +8,7 @@ import pytest
 import torch
 
 import paper_2201_13195_amd as rmm
-from paper_2201_13195_amd import synth
+from paper_2201_13195_amd import binding, synth
 from test_gpu_parity import check_layer
 
 pytestmark = pytest.mark.gpu
@@ -134,3 +134,25 @@ def test_column_sums_of_whole_numbers_are_exact(n, d_out, dtype):
     for need_dX in (True, False):
         _, _, db = rmm.rmm_backward(dY.to(DEV), W, Xp, rmm.RADEMACHER, 3, 4, need_dX=need_dX, need_dbias=True)
         assert torch.equal(db.float().cpu(), dY.float().sum(dim=0))
+
+
+# 32 x 32, 64 x 64 and 128 x 128 tiles of the plain product, few and many sketch tiles beside them
+@pytest.mark.parametrize("kind", [rmm.GAUSSIAN, rmm.RADEMACHER, rmm.SORS])
+@pytest.mark.parametrize("dtype,shape", [("f32", (1000, 600, 700, 500)), ("f32", (300, 2000, 100, 250)), ("f32", (2100, 640, 1350, 90)),
+                                         ("bf16", (1800, 640, 1351, 90)), ("bf16", (500, 1001, 300, 300)), ("bf16", (600, 264, 401, 500)),
+                                         ("bf16", (2207, 1440, 1019, 110)), ("bf16", (3000, 768, 1001, 300))])
+def test_products_one_by_one_give_the_bits_of_one_launch(dtype, shape, kind):
+    n, d_in, d_out, k = shape
+    X, W, dY = (t.to(DEV) for t in synth.layer_inputs(n, d_in, d_out, dtype, (51, 52, 53), w_std=1.0 / math.sqrt(d_in)))
+    a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    a.record(); b.record()
+    torch.cuda.synchronize()
+    Y, Xp = rmm.rmm_forward(X, W, None, k, kind, 5, 1)
+    for stage in (binding.STAGE_FWD_Y, binding.STAGE_FWD_XPROJ, binding.STAGE_FWD_PAIR):
+        got = rmm.rmm_forward(X, W, None, k, kind, 5, 1, profile=(stage, a, b))
+        assert torch.equal(Y, got[0]) and torch.equal(Xp, got[1]), stage
+    for need_dX in (True, False):
+        want = rmm.rmm_backward(dY, W, Xp, kind, 5, 1, need_dX=need_dX, need_dbias=True)
+        for stage in (binding.STAGE_BWD_DX, binding.STAGE_BWD_G, binding.STAGE_BWD_DW, binding.STAGE_BWD_DBIAS):
+            got = rmm.rmm_backward(dY, W, Xp, kind, 5, 1, need_dX=need_dX, need_dbias=True, profile=(stage, a, b))
+            assert all(torch.equal(x, y) for x, y in zip(want, got) if x is not None), stage
