@@ -437,8 +437,7 @@ struct PlainSlices {
 // units; slices add a launch of 4.5 us that reads their sums.  3000 x 768 -> 1001, Gaussian, k = 300: forward 43 us in one
 // slice, 30 in two; backward 53, 43 in two.  4096 x 1024 -> 111, k = 205: backward 62, 20 in eleven.  Where the two come out
 // alike (within 1 us) there are none.  At most `most`: what the caller's scratch holds.
-inline PlainSlices plain_slices(int64_t n, int64_t d, int64_t k, int64_t d_other, int kind, bool backward, int64_t most = 16) {
-    const int cfg = plain_cfg(2, n, d_other, backward);
+inline PlainSlices plain_slices_beside(int cfg, int64_t n, int64_t d, int64_t k, int64_t d_other, int kind, int64_t most) {
     PlainSlices cut{1, n, 0, (d + 7) / 8 * 8, cfg};
     if (load_mode(2, d, d_other) == 0) return cut;
     const int64_t tiles = tiles_of(k, d, 32, 128);
@@ -448,8 +447,8 @@ inline PlainSlices plain_slices(int64_t n, int64_t d, int64_t k, int64_t d_other
                  wide_work = (kind == 0 ? 12e-3 : 6.5e-3) * (double)n * (double)tiles;
     const bool small = cfg == PLAIN_TINY || (cfg == PLAIN_MID && tiles < 64);  // (launch_pass)
     auto longest = [&](double sketch_chain, double sketch_work) {
-        const double most = sketch_chain > chain ? sketch_chain : chain, all = plain_work + sketch_work * per_cu;
-        return most > all ? most : all;
+        const double tile = sketch_chain > chain ? sketch_chain : chain, all = plain_work + sketch_work * per_cu;
+        return tile > all ? tile : all;
     };
     double best = (small ? longest(narrow, narrow * (double)tiles_of(k, d, 32, 32)) : longest(wide, wide_work)) - 1.0;
     for (int64_t s = 2; s <= 16 && s <= most; ++s) {
@@ -459,6 +458,19 @@ inline PlainSlices plain_slices(int64_t n, int64_t d, int64_t k, int64_t d_other
         if (t < best) best = t, cut = PlainSlices{(int)s, chunk, k * cut.ld, cut.ld, cfg};
     }
     return cut;
+}
+
+// The tile of the plain product and the slices of a pass.  A launch of 128 x 128 tiles of Y and sketch tiles that goes a little over a
+// round, by up to a quarter of the compute units, has most of them wait for the last few.  With 64 x 64 tiles, three rounds of
+// them at most, the +-1 kind is 9 % faster there (29 of 87 random forward passes that the rule of plain_cfg brings to 128 x 128
+// tiles; 0.82 to 1.085 of the time; the others 2 % slower: 3000 x 768 -> 1001, k = 300, 312 work-groups: 22.4 and 20.7 us), the Gaussian kind,
+// whose sketch tiles are longest by far, is not.
+inline PlainSlices plain_slices(int64_t n, int64_t d, int64_t k, int64_t d_other, int kind, bool backward, int64_t most = 16) {
+    const PlainSlices cut = plain_slices_beside(plain_cfg(2, n, d_other, backward), n, d, k, d_other, kind, most);
+    if (backward || kind != RMM_SKETCH_RADEMACHER || cut.cfg != PLAIN_BIG) return cut;
+    const int64_t plain = plain_tiles(PLAIN_BIG, n, d_other), all = plain + tiles_of(k, d, 32, 128) * cut.slices;
+    const bool short_round = plain <= 256 && all > 256 && all % 256 >= 1 && all % 256 <= 64;
+    return short_round && plain_tiles(PLAIN_MID, n, d_other) <= 768 ? plain_slices_beside(PLAIN_MID, n, d, k, d_other, kind, most) : cut;
 }
 
 }  // namespace rmm

@@ -27,6 +27,11 @@ int plain_tile(int64_t m, int64_t n, int64_t kk) { return gemm_cfg(m, n, kk); }
 int variance_tile(int64_t n, int64_t d_in, int64_t d_out) { return xty_cfg(d_in, d_out, n); }
 static void put(const SketchPlan &p, int64_t *o) { o[0] = p.cfg, o[1] = p.slices, o[2] = p.per_tail, o[3] = p.splits, o[4] = p.tiles, o[5] = p.shares(); }
 void sketch_plan(int64_t n, int64_t d, int64_t k, int kind, int64_t *o) { put(plan_sketch(n, d, k, kind, true), o); }
+int odd_pass(int64_t n, int64_t d, int64_t k, int64_t d_other, int64_t backward, int kind, int64_t *o) {
+    const PlainSlices c = plain_slices(n, d, k, d_other, kind, backward != 0);
+    o[0] = c.slices, o[1] = plain_tiles(c.cfg, n, d_other), o[2] = tiles_of(k, d, 32, 128);
+    return c.cfg;
+}
 void pass_plan_in(int64_t n, int64_t d_in, int64_t d_out, int64_t k, int64_t room, int kind, int64_t *o) {
     put(plan_pass(n, d_in, d_out, k, kind, room).sketch, o), put(plan_backward(n, d_in, d_out, k, kind, true, room).sketch, o + 6);
 }
@@ -170,3 +175,23 @@ def test_passes_take_no_more_slices_than_their_scratch_holds(plans):
             for mine, theirs, splits in zip((Sketch(list(o)[:6]), Sketch(list(o)[6:])), free, asked):
                 assert 1 <= mine.splits <= room and mine.splits == mine.slices + (mine.per_tail > 0), (n, d_in, d_out, k, kind, room)
                 assert splits > room or (mine.cfg, mine.shares, mine.splits) == (theirs.cfg, theirs.shares, theirs.splits)
+
+
+def test_odd_widths_with_a_short_last_round_take_smaller_tiles(plans):
+    """Y beside a +-1 sketch: 64 x 64 tiles where a launch of 128 x 128 tiles is up to 64 work-groups longer than a round."""
+    def tile(n, d, k, d_other, kind, backward=0):
+        s, cfg = plans._sketch(plans.lib.odd_pass, n, d, k, d_other, backward, kind)
+        return ("128", "64", "32")[cfg], s.cfg, s.slices + s.per_tail * s.cfg      # edge, slices, work-groups
+
+    n, d, d_other = 3000, 768, 1001                                                # 192 tiles of 128 x 128, 752 of 64 x 64
+    assert tile(n, d, 300, d_other, rmm.RADEMACHER)[:2] == ("64", 2)
+    assert tile(n, d, 300, d_other, rmm.GAUSSIAN)[0] == tile(n, d, 300, d_other, rmm.SORS)[0] == "128"
+    seen = set()
+    for k in range(1, 1200, 9):
+        big, small = tile(n, d, k, d_other, rmm.GAUSSIAN), tile(n, d, k, d_other, rmm.RADEMACHER)
+        assert big[0] == "128"
+        seen.add(small[0])
+        assert small[0] == "64" or small[2] <= 256 or small[2] % 256 == 0 or small[2] % 256 > 64, (k, small)
+    assert seen == {"64", "128"}
+    assert tile(4096, 512, 300, 1499, rmm.RADEMACHER)[0] == "128"                  # 1536 tiles of 64 x 64: six rounds
+    assert tile(3000, 1001, 300, 768, rmm.RADEMACHER, 1)[0] == "64"                # (dX has 64 x 64 tiles by itself)
