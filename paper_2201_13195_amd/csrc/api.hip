@@ -239,9 +239,10 @@ int backward_impl(const rmm_layer_desc_t *d, SketchState st, const void *dY, con
     const bool paired_sors = mfma && d->kind == RMM_SKETCH_SORS && dX != nullptr && !separate_stage(ev.stage) &&
                              sors_pair_available(d->n, d->d_out, d->d_in, d->k);
     const bool own_db_stage = ev.stage == RMM_STAGE_BWD_DW || ev.stage == RMM_STAGE_BWD_DBIAS;
-    // the strips of the SORS kind read all of dY once and take its column sums on the way
-    const bool sors_db = mfma && d->kind == RMM_SKETCH_SORS && dbias != nullptr && !own_db_stage && sors_fast_ok(d->n, d->d_out) &&
-                         sors_takes_colsum(d->n, d->k);
+    // the strips of the SORS kind read all of dY once and take its column sums on the way; asked for its events, the bias gradient
+    // has a launch of its own, in the same order of additions
+    const bool strips_db = mfma && d->kind == RMM_SKETCH_SORS && dbias != nullptr && sors_fast_ok(d->n, d->d_out) && sors_takes_colsum(d->n, d->k);
+    const bool sors_db = strips_db && ev.stage != RMM_STAGE_BWD_DBIAS;
     if (paired_sors) {
         const bool timed = ev.stage == RMM_STAGE_BWD_PAIR;
         e = launch_backward_pair_sors_bf16((const bf16_t *)dY, (const bf16_t *)W, (bf16_t *)dX, (bf16_t *)G, d->n, d->d_in,
@@ -297,7 +298,8 @@ int backward_impl(const rmm_layer_desc_t *d, SketchState st, const void *dY, con
     }
     if (dbias != nullptr && !db_done) {
         StageScope scope(ev, RMM_STAGE_BWD_DBIAS, stream);
-        e = launch_colsum<T>((const T *)dY, (T *)dbias, d->n, d->d_out, stream, accumulate);
+        e = strips_db ? launch_sors_colsum_bf16((const bf16_t *)dY, (bf16_t *)dbias, d->n, d->d_out, d->k, accumulate, stream)
+                      : launch_colsum<T>((const T *)dY, (T *)dbias, d->n, d->d_out, stream, accumulate);
         if (e != hipSuccess) return RMM_ERR_LAUNCH;
     }
     return RMM_OK;

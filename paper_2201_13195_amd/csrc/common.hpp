@@ -110,6 +110,8 @@ bool sors_fast_ok(int64_t n, int64_t d);
 bool sors_takes_colsum(int64_t n, int64_t k);
 hipError_t launch_sors_bf16(const bf16_t *A, bf16_t *out, int64_t n, int64_t d, int64_t k, SketchState st,
                             hipStream_t stream, bf16_t *colsum = nullptr, bool accumulate = false);
+// The column sums alone, with the same bits (where sors_takes_colsum()).
+hipError_t launch_sors_colsum_bf16(const bf16_t *A, bf16_t *colsum, int64_t n, int64_t d, int64_t k, bool accumulate, hipStream_t stream);
 
 // One launch for the plain product of a pass and the SORS sketch product of the same pass, where
 // the plain product leaves compute units idle (mfma.hip decides, mfma_pair_sors.hip holds the

@@ -193,6 +193,33 @@ hipError_t launch_strip(const SorsArgs &g, int chunks, hipStream_t stream) {
     return launch_strips<LC, ACC, 1>(g, chunks, stream);
 }
 
+// The column sums alone, as the strips take them: for a pass whose bias gradient is to be timed on its own.
+template <int LC>
+__global__ void __launch_bounds__(64 * strip_waves<LC>()) sors_colsum_kernel(SorsArgs g, int chunks) {
+    constexpr int CH = 1 << LC, TW = CH / strip_waves<LC>();
+    typedef StripSums<CH, TW, 1> Sums;
+    __shared__ float part[CH / 128 * 8];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int64_t col0 = (int64_t)blockIdx.x * 8;
+    const uint32_t off = (uint32_t)((lane * g.d + col0) * 2);
+    Sums sums;
+    sums.clear();
+    for (int ch = 0; ch < chunks; ++ch) {
+        sors_u32x4_t raw[Sums::R0];
+        strip_rows<64>(g, (int64_t)ch * CH + wave * TW, off, raw);
+        sums.add(raw);
+    }
+    sums.park(part, wave, lane);
+    __syncthreads();
+    if (threadIdx.x < 8) sums.write(g, part, 0, col0, (int)threadIdx.x);
+}
+
+template <int LC>
+hipError_t launch_colsum_strips(const SorsArgs &g, int chunks, hipStream_t stream) {
+    sors_colsum_kernel<LC><<<(unsigned)(g.d / 8), 64 * strip_waves<LC>(), 0, stream>>>(g, chunks);
+    return hipGetLastError();
+}
+
 template <int L>
 hipError_t launch_sors(const SorsArgs &g, hipStream_t stream) {
     sors_kernel<L><<<(unsigned)(g.d / SorsShape<L>::C), 256, 0, stream>>>(g);
@@ -229,6 +256,19 @@ hipError_t launch_sors_bf16(const bf16_t *A, bf16_t *out, int64_t n, int64_t d, 
         case 13: return launch_sors<13>(g, stream);
         case 14: return launch_sors<14>(g, stream);
         case 15: return launch_sors<15>(g, stream);
+        default: return hipErrorInvalidValue;
+    }
+}
+
+hipError_t launch_sors_colsum_bf16(const bf16_t *A, bf16_t *colsum, int64_t n, int64_t d, int64_t k, bool accumulate, hipStream_t stream) {
+    const SorsArgs g{A, nullptr, n, d, k, SketchState{}, 0.0f, colsum, accumulate ? 1 : 0};
+    const int l = log2_ceil(n) < 9 ? 9 : log2_ceil(n);  // (chunks: see launch_sors_bf16)
+    if (l >= 12 && k <= kSorsAccMaxK) return launch_colsum_strips<11>(g, 1 << (l - 11), stream);
+    switch (l) {
+        case 9: return launch_colsum_strips<9>(g, 1, stream);
+        case 10: return launch_colsum_strips<10>(g, 1, stream);
+        case 11: return launch_colsum_strips<11>(g, 1, stream);
+        case 12: return launch_colsum_strips<12>(g, 1, stream);
         default: return hipErrorInvalidValue;
     }
 }

@@ -45,10 +45,10 @@ __host__ __device__ constexpr int strip_phys(int t) { return t + (t >> 4) + 2 * 
 // LDS layout: two halves (columns 0-3, 4-7) of float4 slots, token t at slot strip_phys(t): the pads keep the sixteen-byte
 // accesses, and the four-byte ones of lanes that differ in column, token bits 0 and 2, strip and upper half, on banks of their own.
 //
-// A backward pass with a bias gradient takes the column sums of dY here, where every
-// element passes through registers anyway: two instructions per element, ten lane exchanges at the end.  It saves the later launch
-// its read of dY (16384 x 1024 -> 1024, k = 1638: backward without the bias gradient 66 us, with it 69; in a launch of its own
-// 19 us more).  A form of its own: with a branch on the argument the strips without sums went from 78 us to 105 at 8192 x 4096.
+// A backward pass with a bias gradient takes the column sums of dY here, where every element passes through registers anyway (StripSums):
+// two instructions per element, ten lane exchanges at the end.  It saves the later launch its read of dY (16384 x 1024 -> 1024, k =
+// 1638: backward without the bias gradient 66 us, with it 69; in a launch of its own 19 us more).  A form of its own: with a branch on
+// the argument the strips without sums went from 78 us to 105 at 8192 x 4096.
 template <int LC>
 struct StripShape {
     static constexpr int CH = 1 << LC, SLOTS = strip_phys(CH);
@@ -56,6 +56,89 @@ struct StripShape {
     static_assert(LC >= 9 && LC <= 12, "chunks of 512 .. 4096 tokens");
 };
 constexpr int64_t kSorsAccMaxK = 2048;  // sketch columns with accumulators
+
+// Rows t, t + LPW, .. of a strip, 16 bytes from `off` on in each lane.  Buffer loads: a row beyond the tokens lies outside the
+// descriptor's range (one for each load) and reads as zero, so there is no branch between the loads and the compiler can count
+// them: with one it waited for the next chunk's rows in front of this chunk's transform.
+template <int LPW, int R0>
+__device__ __forceinline__ void strip_rows(const SorsArgs &g, int64_t t, uint32_t off, sors_u32x4_t (&raw)[R0]) {
+#pragma unroll
+    for (int i = 0; i < R0; ++i) {
+        const int64_t t0 = t + i * LPW, rows = min((int64_t)LPW, g.n - t0);
+        const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<bf16_t *>(g.A + t0 * g.d), (short)0, __builtin_amdgcn_readfirstlane((int)((rows > 0 ? rows : 0) * g.d * 2)), 0x00020000);
+        raw[i] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, off, 0, 0);
+    }
+}
+
+// The column sums of a strip, in an order of additions that depends on CH alone and not on how the waves share the strip, so that
+// paired, separate and column-sum launches give the same bits: of 128 tokens of a chunk, rows r, r + 64, r + 32 and r + 96 in pairs,
+// for r = 0 .. 31; this over the chunks, then over r (bits 2, 1, 0, 3, 4 of it), then over the 128-token blocks of a chunk.
+// A wave has TW tokens and NPROB strips; load i of a chunk holds LPW rows from i * LPW on.
+template <int CH, int TW, int NPROB>
+struct StripSums {
+    static constexpr int LPW = 64 / NPROB, R0 = TW / LPW, BLOCKS = TW / 128, SETS = NPROB == 2 ? BLOCKS : (BLOCKS + 1) / 2;
+    static_assert(BLOCKS == 1 || BLOCKS % 2 == 0, "with one strip, lanes 32 .. 63 have every other block");
+    float s[SETS][8];
+    __device__ __forceinline__ void clear() {
+#pragma unroll
+        for (int x = 0; x < SETS; ++x)
+#pragma unroll
+            for (int c = 0; c < 8; ++c) s[x][c] = 0.0f;
+    }
+    static __device__ __forceinline__ float element(const sors_u32x4_t &raw, int c) {  // (element 2q in the low half of word q)
+        return __uint_as_float(c % 2 == 0 ? raw[c / 2] << 16 : raw[c / 2] & 0xFFFF0000u);
+    }
+    __device__ __forceinline__ void add(const sors_u32x4_t (&raw)[R0]) {
+#pragma unroll
+        for (int x = 0; x < SETS; ++x)
+#pragma unroll
+            for (int c = 0; c < 8; ++c) {
+                const int i = 4 * x;
+                if constexpr (NPROB == 2) {
+                    s[x][c] += (element(raw[i], c) + element(raw[i + 2], c)) + (element(raw[i + 1], c) + element(raw[i + 3], c));
+                } else {  // (the halves of the lanes: rows r and r + 32)
+                    const float even = element(raw[i], c) + element(raw[i + 1], c);
+                    const float odd = BLOCKS == 1 ? even : element(raw[(i + 2) % R0], c) + element(raw[(i + 3) % R0], c);
+                    const auto v = __builtin_amdgcn_permlane32_swap(__float_as_uint(even), __float_as_uint(odd), false, false);
+                    s[x][c] += __uint_as_float(v[0]) + __uint_as_float(v[1]);
+                }
+                asm volatile("" : "+v"(s[x][c]));  // (now, and no copies)
+            }
+    }
+    // The first 2 H columns of a set, over lanes that differ in bit H of the row: a lane keeps H of them.
+    template <int H>
+    static __device__ __forceinline__ void halve(float (&v)[8], int row) {
+        const bool up = (row & H) != 0;
+#pragma unroll
+        for (int c = 0; c < H; ++c) {
+            const float keep = up ? v[c + H] : v[c], give = up ? v[c] : v[c + H];
+            v[c] = keep + __shfl_xor(give, H * NPROB);
+        }
+    }
+    // Three exchanges leave each lane one of the eight columns, the others add; part: CH / 128 * 8 floats per strip.
+    __device__ __forceinline__ void park(float *part, int wave, int lane) {
+        const int prob = lane % NPROB, row = lane / NPROB % 32, half = NPROB == 2 ? 0 : lane / 32;
+#pragma unroll
+        for (int x = 0; x < SETS; ++x) {
+            halve<4>(s[x], row), halve<2>(s[x], row), halve<1>(s[x], row);
+            s[x][0] += __shfl_xor(s[x][0], 8 * NPROB);
+            s[x][0] += __shfl_xor(s[x][0], 16 * NPROB);
+        }
+        if (row < 8 && half < BLOCKS) {
+#pragma unroll
+            for (int x = 0; x < SETS; ++x) part[((wave * BLOCKS + x * (3 - NPROB) + half) * NPROB + prob) * 8 + row] = s[x][0];
+        }
+    }
+    // (behind a barrier; threads 0 .. 7 of each strip)
+    static __device__ __forceinline__ void write(const SorsArgs &g, const float *part, int prob, int64_t col0, int c) {
+        float x = 0.0f;
+#pragma unroll
+        for (int b = 0; b < CH / 128; ++b) x += part[(b * NPROB + prob) * 8 + c];
+        if (g.accumulate) x += load_f32<bf16_t>(g.colsum + col0 + c);
+        store_f32<bf16_t>(g.colsum + col0 + c, x);
+    }
+};
 
 //
 // NPROB = 2 puts two neighbouring strips into one work-group of 512 threads (thread 2r + p is
@@ -108,20 +191,10 @@ __device__ __forceinline__ void sors_strip_body(const SorsArgs &g, int chunks, f
     }
 
     // Wave `wave` of the work-group loads, and transforms as far as it can alone, tokens wave * TW .. + TW - 1 of a chunk: row
-    // 8 columns of it per lane, for two strips those of either in turn.  Buffer loads: a row beyond the tokens lies outside the
-    // descriptor's range (one for each load) and reads as zero, so there is no branch between the loads and the compiler can count
-    // them: with one it waited for the next chunk's rows in front of this chunk's transform.
+    // 8 columns of it per lane, for two strips those of either in turn.
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), row = tid % LPW;
     const uint32_t off = live ? (uint32_t)((row * g.d + col0) * 2) : 0x80000000u;
-    auto load_chunk = [&](int ch, sors_u32x4_t (&raw)[R0]) {
-#pragma unroll
-        for (int i = 0; i < R0; ++i) {
-            const int64_t t0 = (int64_t)ch * CH + wave * TW + i * LPW, rows = min((int64_t)LPW, g.n - t0);
-            const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
-                const_cast<bf16_t *>(g.A + t0 * g.d), (short)0, __builtin_amdgcn_readfirstlane((int)((rows > 0 ? rows : 0) * g.d * 2)), 0x00020000);
-            raw[i] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, off, 0, 0);
-        }
-    };
+    auto load_chunk = [&](int ch, sors_u32x4_t (&raw)[R0]) { strip_rows<LPW>(g, (int64_t)ch * CH + wave * TW, off, raw); };
     // The 32 x 32 Walsh-Hadamard matrix as an MFMA operand.
     bf16x8_t hadamard[2];
 #pragma unroll
@@ -137,10 +210,8 @@ __device__ __forceinline__ void sors_strip_body(const SorsArgs &g, int chunks, f
     float4 *mine = planes_all + strip_phys(wave * TW);  // slots of the wave's tokens (of the first strip), lower half; upper half: + PLANE
     const float odd8 = (lane & 8) != 0 ? -1.0f : 1.0f;
 
-    float sums[SUMS ? 8 : 1];
-    if constexpr (SUMS)
-#pragma unroll
-        for (int c = 0; c < 8; ++c) sums[c] = 0.0f;
+    [[maybe_unused]] StripSums<CH, TW, NPROB> sums;
+    if constexpr (SUMS) sums.clear();
     sors_u32x4_t raw[R0];
     load_chunk(0, raw);
     __syncthreads();  // sign words
@@ -152,20 +223,12 @@ __device__ __forceinline__ void sors_strip_body(const SorsArgs &g, int chunks, f
             const int t = ch * CH + wave * TW + i * LPW + row;
             const int flip = (int)(sign_words[t >> 5] << (31 - (t & 31))) >> 31;
             asm volatile("" : "+v"(raw[i]));  // (unpacked here: not before, in twice the registers)
-            if constexpr (SUMS) {
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {  // (element 2q in the low half of word q)
-                    sums[2 * q] += __uint_as_float(raw[i][q] << 16);
-                    sums[2 * q + 1] += __uint_as_float(raw[i][q] & 0xFFFF0000u);
-                }
-#pragma unroll
-                for (int c = 0; c < 8; ++c) asm volatile("" : "+v"(sums[c]));  // (now: not after all rows, with a second copy of each)
-            }
             sors_u32x4_t w;
 #pragma unroll
             for (int q = 0; q < 4; ++q) w[q] = raw[i][q] ^ ((uint32_t)flip & 0x80008000u);
             *reinterpret_cast<sors_u32x4_t *>(mine + (NPROB == 2 ? prob : i * LPW / TOP) * S::PLANE + i * LPW % TOP + row) = w;
         }
+        if constexpr (SUMS) sums.add(raw);  // (while the rows go to LDS)
         if constexpr (ACC) load_chunk(ch + 1, raw);  // arrives while this chunk is transformed (past the end: zeros)
         asm volatile("" ::: "memory");  // (the wave's own LDS accesses keep their order)
         // Index bits 0 .. 4: the matrix times 32 tokens of 32 (group of 32 tokens, column) pairs a tile.
@@ -282,22 +345,8 @@ __device__ __forceinline__ void sors_strip_body(const SorsArgs &g, int chunks, f
     if constexpr (ACC)  // (the last request, past the end, ends here: left open, the compiler waits for it in the loop of the tile that shares the kernel)
 #pragma unroll
         for (int i = 0; i < R0; ++i) asm volatile("" ::"v"(raw[i]));
-    float *wave_sums = reinterpret_cast<float *>(sign_words);  // (the signs are behind a barrier) 8 per wave and strip
-    if constexpr (SUMS) {
-        // Over the lanes of a strip in fixed order: three exchanges leave each lane one of the eight columns, the others add.
-        const int row8 = lane / NPROB;
-#pragma unroll
-        for (int h = 4; h > 0; h >>= 1)
-#pragma unroll
-            for (int c = 0; c < h; ++c) {
-                const bool up = (row8 & h) != 0;
-                const float keep = up ? sums[c + h] : sums[c], give = up ? sums[c] : sums[c + h];
-                sums[c] = keep + __shfl_xor(give, h * NPROB);
-            }
-#pragma unroll
-        for (int h = 8; h < 64 / NPROB; h <<= 1) sums[0] += __shfl_xor(sums[0], h * NPROB);
-        if (row8 < 8) wave_sums[(wave * NPROB + prob) * 8 + row8] = sums[0];
-    }
+    float *part = reinterpret_cast<float *>(sign_words);  // (the signs are behind a barrier)
+    if constexpr (SUMS) sums.park(part, wave, lane);
 
     auto store_row = [&](int64_t j, uint32_t r, const float4 &a, const float4 &b) {
         const float alpha = NPROB == 1 && (r & (uint32_t)TOP) != 0 ? -g.alpha : g.alpha;
@@ -331,13 +380,7 @@ __device__ __forceinline__ void sors_strip_body(const SorsArgs &g, int chunks, f
     }
     if constexpr (SUMS) {
         __syncthreads();
-        if (tid < 8 && live) {
-            float x = 0.0f;
-#pragma unroll
-            for (int w = 0; w < WAVES; ++w) x += wave_sums[(w * NPROB + prob) * 8 + tid];
-            if (g.accumulate) x += load_f32<bf16_t>(g.colsum + col0 + tid);
-            store_f32<bf16_t>(g.colsum + col0 + tid, x);
-        }
+        if (tid < 8 && live) sums.write(g, part, prob, col0, tid);
     }
 }
 

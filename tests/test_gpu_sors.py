@@ -178,3 +178,29 @@ def test_bias_gradient_from_the_strips(n, d_out, k):
         first = synth.to_f64(db).copy()
         rmm.rmm_backward(dYd, Wd, Xp, SORS, 3, 4, need_dX=need_dX, dW=dW, dbias=db, need_dbias=True, accumulate=True)
         assert_close(db, want + first, "db", "bf16", label="sors db twice %s" % ((n, d_out, k),))
+
+
+@pytest.mark.parametrize("n,d_in,d_out,k", [(4096, 768, 3072, 410),      # paired; by themselves the strips go two to a work-group
+                                            (16384, 4096, 1024, 1638),   # paired, several rounds of tiles; alone one strip each
+                                            (5000, 264, 2056, 90), (5000, 264, 520, 90),
+                                            (4000, 264, 136, 2050), (700, 264, 136, 64), (300, 264, 40, 70)])
+def test_bias_gradient_has_the_same_bits_in_every_form_of_the_pass(n, d_in, d_out, k):
+    """With dX and without, in one launch with it or with an event pair for any stage.  Every column of dY sums to zero, so
+    that db is nothing but the fp32 roundings of the order it was added in."""
+    X, W, dY = synth.layer_inputs(n, d_in, d_out, "bf16", (n, d_out, k))
+    gen = torch.Generator().manual_seed(n)
+    dY *= torch.exp2(-torch.randint(0, 13, (n, 1), generator=gen).float()).to(dY.dtype)     # (exact)
+    dY[n // 2:n // 2 * 2] = -dY[:n // 2][torch.randperm(n // 2, generator=gen)]
+    dY[n // 2 * 2:] = 0
+    Xd, Wd, dYd = X.to(DEV), W.to(DEV), dY.to(DEV)
+    _, Xp = rmm.rmm_forward(Xd, Wd, None, k, SORS, 3, 4)
+    dX, dW, db = rmm.rmm_backward(dYd, Wd, Xp, SORS, 3, 4, need_dbias=True)
+    assert np.abs(synth.to_f64(db)).max() > 0
+    _, dW1, db1 = rmm.rmm_backward(dYd, Wd, Xp, SORS, 3, 4, need_dX=False, need_dbias=True)
+    assert torch.equal(db, db1) and torch.equal(dW, dW1), "without dX"
+    a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    a.record(); b.record()
+    for stage in (binding.STAGE_BWD_DX, binding.STAGE_BWD_G, binding.STAGE_BWD_DW, binding.STAGE_BWD_DBIAS,
+                  binding.STAGE_BWD_G_PRODUCT, binding.STAGE_BWD_PAIR):
+        dX1, dW1, db1 = rmm.rmm_backward(dYd, Wd, Xp, SORS, 3, 4, need_dbias=True, profile=(stage, a, b))
+        assert torch.equal(dX, dX1) and torch.equal(dW, dW1) and torch.equal(db, db1), stage
