@@ -8,6 +8,8 @@ import torch
 
 import paper_2201_13195_amd as rmm
 from paper_2201_13195_amd import binding, synth
+from oracle import rmm as o_rmm
+from parity import assert_close
 from test_gpu_parity import check_layer
 
 pytestmark = pytest.mark.gpu
@@ -34,3 +36,65 @@ def test_passes_with_plans_of_their_own(shape, kind):
     dX0, dW0, _ = rmm.rmm_backward(dYd, Wd, Xp0, kind, 5, 1)
     dX1, dW1, _ = rmm.rmm_backward(dYd, Wd, Xp0, kind, 5, 1, profile=(binding.STAGE_BWD_DX, a, b))
     assert torch.equal(Y0, Y1) and torch.equal(Xp0, Xp1) and torch.equal(dX0, dX1) and torch.equal(dW0, dW1)
+
+
+# Every pairing of a plain tile and a sketch tile that passes with 256 to 16384 tokens and widths of 256 to 4096 take:
+# (tokens, width of the sketched operand, other width, k), kind, tiles.  (test_launch_plans.py: they take these, and there are no others.)
+PAIRS = [((4439, 280, 2776, 222), rmm.GAUSSIAN, "256x256", "128x256"),
+         ((4439, 280, 2776, 222), rmm.RADEMACHER, "256x256", "128x256"),
+         ((7121, 304, 1320, 356), rmm.GAUSSIAN, "256x256", "128x384"),
+         ((7121, 304, 1320, 356), rmm.RADEMACHER, "256x256", "128x384"),
+         ((4563, 272, 2632, 228), rmm.GAUSSIAN, "256x256", "128x512"),
+         ((4563, 272, 2632, 228), rmm.RADEMACHER, "256x256", "128x512"),
+         ((2567, 272, 3736, 128), rmm.GAUSSIAN, "256x256", "64x256"),
+         ((2567, 272, 3736, 128), rmm.RADEMACHER, "256x256", "64x256"),
+         ((3243, 272, 3992, 162), rmm.GAUSSIAN, "256x256", "64x384"),
+         ((3331, 392, 3152, 167), rmm.RADEMACHER, "256x256", "64x384"),
+         ((5356, 264, 1928, 268), rmm.GAUSSIAN, "256x256", "64x512"),
+         ((5356, 264, 1928, 268), rmm.RADEMACHER, "256x256", "64x512"),
+         ((962, 2744, 328, 192), rmm.GAUSSIAN, "128x128 split", "128x256"),
+         ((1285, 1872, 272, 257), rmm.RADEMACHER, "128x128 split", "128x256"),
+         ((4056, 1576, 264, 406), rmm.GAUSSIAN, "128x128 split", "128x384"),
+         ((2604, 1552, 440, 521), rmm.RADEMACHER, "128x128 split", "128x384"),
+         ((3865, 1552, 664, 193), rmm.GAUSSIAN, "128x128 split", "128x512"),
+         ((904, 1624, 3728, 90), rmm.RADEMACHER, "128x128 split", "128x512"),
+         ((330, 1624, 264, 66), rmm.GAUSSIAN, "128x128 split", "64x256"),
+         ((330, 1624, 264, 66), rmm.RADEMACHER, "128x128 split", "64x256"),
+         ((516, 3920, 280, 103), rmm.GAUSSIAN, "128x128 split", "64x384"),
+         ((516, 3920, 280, 103), rmm.RADEMACHER, "128x128 split", "64x384"),
+         ((1687, 2120, 312, 337), rmm.GAUSSIAN, "128x128 split", "64x512"),
+         ((2819, 2632, 296, 141), rmm.RADEMACHER, "128x128 split", "64x512"),
+         ((1456, 520, 2184, 73), rmm.GAUSSIAN, "128x128", "128x256"),
+         ((1299, 400, 2480, 65), rmm.RADEMACHER, "128x128", "128x256"),
+         ((1550, 344, 2200, 78), rmm.GAUSSIAN, "128x128", "128x384"),
+         ((1358, 264, 2696, 68), rmm.RADEMACHER, "128x128", "128x384"),
+         ((1352, 392, 2776, 68), rmm.GAUSSIAN, "128x128", "128x512"),
+         ((1352, 392, 2776, 68), rmm.RADEMACHER, "128x128", "128x512"),
+         ((324, 272, 280, 65), rmm.GAUSSIAN, "128x128", "64x256"),
+         ((324, 272, 280, 65), rmm.RADEMACHER, "128x128", "64x256"),
+         ((520, 776, 280, 468), rmm.GAUSSIAN, "128x128", "64x384"),
+         ((520, 776, 280, 468), rmm.RADEMACHER, "128x128", "64x384"),
+         ((1299, 400, 2480, 65), rmm.GAUSSIAN, "128x128", "64x512"),
+         ((2840, 400, 1064, 142), rmm.RADEMACHER, "128x128", "64x512"),
+         ((1358, 264, 2696, 68), rmm.GAUSSIAN, "128x128 compact", "64x256"),
+         ((1411, 264, 2648, 71), rmm.RADEMACHER, "128x128 compact", "64x256")]
+
+
+@pytest.mark.parametrize("shape,kind,plain,sketch", PAIRS)
+def test_every_pairing_of_tiles(shape, kind, plain, sketch):
+    """Forward over A, backward over the same A as dY with W transposed: Y and dX are the same product, X_proj and G too."""
+    n, d, d_other, k = shape
+    A, W, Xp = (synth.to_torch(synth.normal(s, 0x5EED0080 + sum(s), std), "bf16")
+                for s, std in (((n, d), 1.0), ((d_other, d), 1.0 / math.sqrt(d)), ((k, d_other), 1.0)))
+    oY, oG = o_rmm.forward(synth.to_f64(A), synth.to_f64(W), None, k, kind, 0x5EED0081, 14)
+    Ad, Wd, Wt, Xpd = A.to("cuda"), W.to("cuda"), W.t().contiguous().to("cuda"), Xp.to("cuda")
+    a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    a.record(); b.record()
+    Y, G = rmm.rmm_forward(Ad, Wd, None, k, kind, 0x5EED0081, 14)
+    dX, dW, _ = rmm.rmm_backward(Ad, Wt, Xpd, kind, 0x5EED0081, 14)
+    label = "%s beside %s %s" % (sketch, plain, shape)
+    for got, want, what in ((Y, oY, "Y"), (G, oG, "X_proj"), (dX, oY, "dX"), (dW, oG.T @ synth.to_f64(Xp), "dW")):
+        assert_close(got, want, what, "bf16", label)
+    Y1, G1 = rmm.rmm_forward(Ad, Wd, None, k, kind, 0x5EED0081, 14, profile=(binding.STAGE_FWD_Y, a, b))
+    dX1, dW1, _ = rmm.rmm_backward(Ad, Wt, Xpd, kind, 0x5EED0081, 14, profile=(binding.STAGE_BWD_DX, a, b))
+    assert torch.equal(Y, Y1) and torch.equal(G, G1) and torch.equal(dX, dX1) and torch.equal(dW, dW1)

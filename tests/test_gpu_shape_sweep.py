@@ -1,7 +1,6 @@
-"""GPU: parity on shapes chosen around every switch point of the host-side kernel selection
-(streaming kernel up to k = 64, LDS-generated sketch tile from d = 1024, 256x256 tiles from 160
-such tiles, two wave groups for few tiles with a contraction of 768 or more, token slices that
-do not divide n) and on seeded random shapes."""
+"""GPU: parity on shapes around the fixed switch points of the host-side kernel selection (streaming sketch kernel up to
+k = 64, 256 x 256 tiles from 160 of them, two wave groups from a contraction of 1536, token blocks) and on seeded random
+shapes.  What the fitted time models choose: test_gpu_plain_tiles.py, test_gpu_pair_plans.py and test_launch_plans.py."""
 import math
 
 import numpy as np
@@ -18,11 +17,11 @@ DEV = "cuda"
 
 BOUNDARY = [
     # (n, d_in, d_out, k)
-    (700, 1016, 1024, 64), (700, 1024, 1032, 65), (1300, 1032, 1016, 63),   # sketch kernel switches (k, d)
-    (2500, 264, 4096, 129), (2560, 4096, 256, 70),                            # 160 / 10 x 16 large tiles in Y / dX
-    (2432, 264, 4096, 129),                                                   # 152 large tiles: small-tile path
-    (260, 1536, 136, 1536), (260, 1528, 136, 1528),                           # long contractions, few tiles
-    (1200, 768, 1024, 100), (1200, 760, 1024, 100),                           # 80 tiles of Y, contraction at / below 768
+    (700, 1016, 1024, 64), (700, 1024, 1032, 65), (1300, 1032, 1016, 63),   # k on both sides of 64
+    (2500, 264, 4096, 129), (2560, 4096, 256, 70), (2432, 264, 4096, 129),    # 10 x 16 large tiles in Y / dX / Y
+    (2300, 264, 4096, 129),                                                   # 9 x 16 would be 144: 128 x 128
+    (260, 1536, 136, 1536), (260, 1528, 136, 1528),                           # few tiles, contraction at / below 1536
+    (1200, 768, 1024, 100), (1200, 760, 1024, 100),                           # contraction of whole and of ragged steps
     (127, 520, 264, 127), (129, 520, 264, 130), (1, 1024, 1024, 1),           # token blocks of 128, n = 1
     (3000, 2056, 8, 410), (3000, 8, 2056, 410),                               # one 8-wide side
 ]

@@ -18,6 +18,7 @@ import test_gpu_variance
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 HEADER = os.path.join(HERE, "..", "paper_2201_13195_amd", "csrc", "launch_plans.hpp")
+SKETCH_TILES = ["128x256", "128x512", "64x512", "64x384", "128x384", "64x256"]                            # SK_NARROW ..
 TILES = ["256x256", "128x256", "128x128 split", "128x128", "64x128", "64x64", "32x32", "128x128 compact"]   # GEMM_LARGE ..
 SOURCE = """
 #include "%s"
@@ -135,6 +136,20 @@ def test_paired_launches_take_the_plans_that_their_tests_name(plans):
     assert F(*f[0], f[1])[1].splits < plans.sketch(n, d_in, k, f[1]).splits and B(*f[0], f[1])[1].splits < plans.sketch(n, d_out, k, f[1]).splits
     n, d_in, d_out, k = g[0]
     assert F(*g[0], g[1])[1].splits == 1 < plans.sketch(n, d_in, k, g[1]).splits
+
+
+def test_every_pairing_of_tiles_is_tested(plans):
+    for (n, d, d_other, k), kind, plain, sketch in test_gpu_pair_plans.PAIRS:
+        for tile, s in (plans.forward(n, d, d_other, k, kind), plans.backward(n, d_other, d, k, kind)):
+            assert (tile, SKETCH_TILES[s.cfg]) == (plain, sketch), (n, d, d_other, k, kind)
+    named = {(plain, sketch, kind) for _, kind, plain, sketch in test_gpu_pair_plans.PAIRS}
+    g = np.random.default_rng(20260303)
+    for _ in range(5000):
+        n, d, d_other = (int(x) for x in np.exp(g.uniform(np.log((256, 256, 256)), np.log((16384, 4096, 4096)))))
+        k = max(65, int(g.choice([0.05, 0.1, 0.2, 0.5, 0.9]) * n))
+        for kind in (rmm.GAUSSIAN, rmm.RADEMACHER):
+            tile, s = plans.forward(n, d // 8 * 8, d_other // 8 * 8, k, kind)
+            assert (tile, SKETCH_TILES[s.cfg], kind) in named, (n, d, d_other, k)
 
 
 def test_short_last_slices_are_where_their_tests_expect_them(plans):
