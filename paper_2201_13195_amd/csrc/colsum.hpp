@@ -72,7 +72,7 @@ __device__ __forceinline__ void colsum_body(const ColsumArgs &g, float *lds, int
         for (int e = 0; e < VEC; ++e) lds[rg * PITCH + cq * VEC + e] = acc[e];
     }
     __syncthreads();
-    // 256 threads add VEC row groups of a column each, the lanes of a wave those of a column, eight or more threads the four waves'.
+    // 256 threads add VEC row groups of a column each, the lanes of a wave those of a column, a thread for each column the four waves'.
     float *waves = lds + 256 * (VEC + 1);
     if (tid < 256) {
         const int cc = tid % BC, part = tid / BC;

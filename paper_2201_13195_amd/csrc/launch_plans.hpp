@@ -335,7 +335,8 @@ inline PassPlan plan_pass(int64_t n, int64_t d_sk, int64_t d_other, int64_t k, i
     return e.plan;
 }
 
-// Whether the launch of dW has room for the column sums of the bias gradient beside it.
+// Whether the bias gradient's column sums go with dW: beside it where its launch has room (64 compute units idle in the last round,
+// or a place each where two work-groups share one); 256 x 256 tiles never share, their column sums are a launch of their own.
 inline bool dw_takes_colsum(int64_t d_in, int64_t d_out, int64_t k) {
     const int cfg = gemm_cfg(d_out, d_in, k);
     const int64_t tiles = gemm_tiles(cfg, d_out, d_in);

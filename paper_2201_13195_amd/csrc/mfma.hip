@@ -264,11 +264,10 @@ hipError_t launch_forward_pair_bf16(const bf16_t *X, const bf16_t *W, const bf16
 }
 
 // Where the bias gradient goes in a backward pass that has the paired launch: into the launch of
-// dW when that leaves at least 64 compute units idle (dW is short and mostly latency; where it runs on
-// few_tile, whose work-groups want a compute unit each, when the column blocks fit beside them);
-// otherwise into the paired launch when its last round leaves at least 16 idle (the sketch work-groups
+// dW when that has room for it (dw_takes_colsum: dW is short and mostly latency); otherwise into the paired launch when dW runs on
+// few_tile or the last round of the paired launch leaves at least 16 compute units idle (the sketch work-groups
 // of that round run for long, and dY is being read there anyway; plan_backward sees to it where it
-// can); otherwise into the launch of dW.
+// can); otherwise behind the tiles of dW, or behind its launch where these are 256 x 256.
 bool backward_pair_takes_colsum_in(int64_t n, int64_t d_in, int64_t d_out, int64_t k, int kind, int64_t room) {
     if (!pass_pair_available(k)) return false;
     return !dw_takes_colsum(d_in, d_out, k) &&
