@@ -147,7 +147,10 @@ int rmm_sketch_static(int64_t n, int64_t d, int64_t k, int dtype, int kind, rmm_
  * caller may drop X and keeps X_proj and `state` for the backward call: the saved
  * bytes are k*d_in*sizeof(dtype) + 16 instead of n*d_in*sizeof(dtype) (Section 2.4.1).
  * X_proj may be NULL when no backward pass will follow (inference): the sketch is then
- * skipped, k and state are ignored beyond validation, and no workspace is needed. */
+ * skipped, k and state are ignored beyond validation, and no workspace is needed.
+ * In bf16 with widths that are multiples of 8, Y of calls that share a launch with the sketch product
+ * (rmm_uses_paired_launch) is the same bits for any k, kind and scratch.  Elsewhere its last bits, and those of
+ * dX below, may differ between calls that differ in these or in whether X_proj is asked for. */
 int rmm_forward(const rmm_layer_desc_t *desc, rmm_rng_state_t state, const void *X, const void *W,
                 const void *bias, void *Y, void *X_proj, void *ws, size_t ws_bytes, void *stream);
 

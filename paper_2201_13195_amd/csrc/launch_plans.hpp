@@ -34,7 +34,7 @@ inline int64_t colsum_blocks(int64_t d, int64_t elem_bytes) {
 }
 inline int64_t colsum_narrow_blocks(int64_t d) { return (d + 7) / 8; }
 
-// The plain product of a paired launch: its tile (GEMM_LARGE, GEMM_SPLIT, GEMM_MID or, with SK_NARROW64, GEMM_COMPACT) and
+// The plain product of a paired launch: its tile (GEMM_LARGE, GEMM_MID or, with SK_NARROW64, GEMM_COMPACT; dX: see dx_cfg) and
 // number of tiles.
 struct PairPlain {
     int cfg, tiles;
@@ -242,7 +242,7 @@ inline double pair_us(const PairPlain &plain, int64_t kk, const SketchPlan &p, i
     struct Times {
         double fix, step;
     };
-    static const Times large{6.3, 1.405}, split{4.0, 0.478}, mid{3.4, 0.487}, compact{5.4, 0.733};
+    static const Times large{6.3, 1.405}, mid{3.4, 0.487}, mid_long{4.0, 0.478}, compact{5.4, 0.733};  // (mid_long: contractions from 1536 on)
     struct SketchTimes {
         double fix, step[2];  // Gaussian, Rademacher
     };
@@ -250,7 +250,7 @@ inline double pair_us(const PairPlain &plain, int64_t kk, const SketchPlan &p, i
     static const SketchTimes sk[] = {{5.3, {1.288, 0.957}}, {7.2, {1.651, 1.476}}, {5.1, {1.078, 1.080}},   // (in the order of SK_NARROW ..)
                                      {5.0, {0.929, 0.910}}, {6.3, {1.490, 1.192}}, {4.05, {0.780, 0.722}}};
     const bool two = plain.cfg == GEMM_COMPACT;
-    const Times &a = plain.cfg == GEMM_LARGE ? large : plain.cfg == GEMM_SPLIT ? split : two ? compact : mid;
+    const Times &a = plain.cfg == GEMM_LARGE ? large : two ? compact : kk >= 1536 ? mid_long : mid;
     const SketchTimes &b = two ? sk_compact : sk[p.cfg];
     const double ta = a.fix + a.step * (double)((kk + 63) / 64), tb = b.fix + b.step[kind != 0] * (double)(p.k_chunk / 64);
     const int64_t slots = two ? 512 : 256;
@@ -268,13 +268,17 @@ struct PassPlan {
     SketchPlan sketch;
 };
 
-// The plain product of a pass (contraction kk, n x m outputs) beside a sketch product on one work-group per compute unit:
-// 256 x 256 tiles where it fills the chip with them, else 128 x 128; with two wave groups where the contraction is long (4096 x
-// 3072 -> 768 alone: 25.0 us, without 25.5; 768 -> 768: 10.3, without 9.7).
-inline PairPlain pair_plain(int64_t n, int64_t m, int64_t kk) {
-    const int cfg = gemm_tiles(GEMM_LARGE, n, m) >= 160 ? GEMM_LARGE : kk >= 1536 ? GEMM_SPLIT : GEMM_MID;
+// The plain product of a pass (n x m outputs) beside a sketch product on one work-group per compute unit: 256 x 256 tiles where it
+// fills the chip with them, else 128 x 128.  ShapeCompact adds in the order of ShapeMid, so that the bits of Y follow from its
+// sizes alone, whatever the sketch is.
+inline PairPlain pair_plain(int64_t n, int64_t m) {
+    const int cfg = gemm_tiles(GEMM_LARGE, n, m) >= 160 ? GEMM_LARGE : GEMM_MID;
     return PairPlain{cfg, (int)gemm_tiles(cfg, n, m)};
 }
+// dX with a long contraction runs with two wave groups on these tiles: its row-indexed operand is read from LDS half as often
+// (backward, 2048 x 1024 -> 4096, k = 205: 36.5 us, without 38.7; Y gains nothing: over 49 passes with contractions from 1536 on
+// 0.994 of the time without them).
+inline int dx_cfg(int cfg, int64_t kk) { return cfg == GEMM_MID && kk >= 1536 ? GEMM_SPLIT : cfg; }
 
 // Plan of a pass: sketch of the n x d_sk operand, plain product n x d_other over d_sk.  Every sketch tile with slices for 64
 // to 320 work-groups, and 64 x 256 tiles with ShapeCompact where all work-groups are resident at once.  (4096 x 768 ->
@@ -287,7 +291,7 @@ inline PairPlain pair_plain(int64_t n, int64_t m, int64_t kk) {
 inline PassPlan make_pass_plan(int64_t n, int64_t d_sk, int64_t d_other, int64_t k, int kind, int64_t room) {
     const SketchPlan alone = plan_sketch(n, d_sk, k, kind, true, room);
     const double partial_mb = (double)k * (double)d_sk * 4e-6;
-    const PairPlain usual = pair_plain(n, d_other, d_sk);
+    const PairPlain usual = pair_plain(n, d_other);
     const PairPlain compact{GEMM_COMPACT, (int)gemm_tiles(GEMM_COMPACT, n, d_other)};
     PassPlan best{usual, alone};
     double best_us = pair_us(usual, d_sk, alone, kind, partial_mb) - 0.8;

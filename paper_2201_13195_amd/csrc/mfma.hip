@@ -134,8 +134,8 @@ struct EventPair {
 template <int BMODE>
 static hipError_t launch_plain_of_pass(const GemmArgs &g, int64_t pair_k, int kind, int64_t room, hipStream_t stream) {
     if (pair_k == 0) return launch_gemm<A_KCONTIG, BMODE>(gemm_cfg(g.M, g.N, g.K), g, stream);
-    const int cfg = (kind == RMM_SKETCH_SORS ? pair_plain(g.M, g.N, g.K) : plan_pass(g.M, g.K, g.N, pair_k, kind, room).plain).cfg;
-    return launch_gemm<A_KCONTIG, BMODE>(cfg == GEMM_COMPACT ? GEMM_MID : cfg, g, stream);
+    const int cfg = (kind == RMM_SKETCH_SORS ? pair_plain(g.M, g.N) : plan_pass(g.M, g.K, g.N, pair_k, kind, room).plain).cfg;
+    return launch_gemm<A_KCONTIG, BMODE>(cfg == GEMM_COMPACT ? GEMM_MID : BMODE == B_NCONTIG ? dx_cfg(cfg, g.K) : cfg, g, stream);
 }
 
 hipError_t launch_linear_nt_bf16(const bf16_t *X, const bf16_t *W, const bf16_t *bias, bf16_t *Y, int64_t n,
@@ -316,7 +316,7 @@ static int sors_pair_order(int64_t blocks_a, int64_t strip_groups) {
 
 bool sors_pair_available(int64_t n, int64_t d_sk, int64_t d_other, int64_t k) {
     if (!sors_fast_ok(n, d_sk) || sors_chunks(n) == 0 || k > 2048) return false;
-    const PairPlain plain = pair_plain(n, d_other, d_sk);
+    const PairPlain plain = pair_plain(n, d_other);
     // 128 x 128 tiles: one round of them, long enough for the strips to finish beside it
     if (plain.cfg != GEMM_LARGE && (plain.tiles < 65 || plain.tiles > 256 || d_sk < 768)) return false;
     return sors_pair_order(plain.tiles, (d_sk / 8 + 1) / 2) != 0;
@@ -324,7 +324,7 @@ bool sors_pair_available(int64_t n, int64_t d_sk, int64_t d_other, int64_t k) {
 
 static hipError_t launch_pass_sors(const GemmArgs &ga, bool row_indexed_b, const SorsArgs &gs, hipStream_t stream, hipEvent_t ev_begin,
                                    hipEvent_t ev_end) {
-    const PairPlain plain = pair_plain(ga.M, ga.N, ga.K);
+    const PairPlain plain = pair_plain(ga.M, ga.N);
     EventPair pev(ev_begin, ev_end, stream);
     return launch_pair_sors(plain, row_indexed_b, ga, gs, sors_chunks(gs.n), sors_pair_order(plain.tiles, (gs.d / 8 + 1) / 2) == 2, stream);
 }

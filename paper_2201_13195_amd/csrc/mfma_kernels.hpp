@@ -72,7 +72,7 @@ struct TileShape {
     static_assert(SB >= 2 && (SA == SB || SA == SB + 1) && SP * (4 / WK) >= A_LOADS + B_LOADS, "the loads of a step fit into it");
     static_assert(WK <= 2 && LDS_BYTES <= 160 * 1024, "LDS of a compute unit");
 };
-// (which product takes which: gemm_cfg and pair_plain in mfma.hip)
+// (which product takes which: gemm_cfg and pair_plain in launch_plans.hpp)
 typedef TileShape<256, 256, 2, 4, 1, 3, 2, 4> ShapeLarge;
 typedef TileShape<128, 256, 2, 4, 1, 3, 3, 2> ShapeWide;
 typedef TileShape<128, 128, 2, 2, 2, 3, 3, 3> ShapeSplit;

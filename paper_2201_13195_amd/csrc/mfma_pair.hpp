@@ -19,7 +19,6 @@ hipError_t launch_pair_nn(const PairPlain &plain, int sk_cfg, int kind, const Ge
     hipError_t launch_pair_##NAME(int sk_cfg, int kind, const GemmArgs &ga, const GemmArgs &gb, int blocks_a, int tiles_b, \
                                   int shares, hipStream_t stream, const ColsumArgs *gc)
 RMM_PAIR_DECL(nt_large);
-RMM_PAIR_DECL(nt_split);
 RMM_PAIR_DECL(nt_mid);
 RMM_PAIR_DECL(nt_compact);
 RMM_PAIR_DECL(nn_large);

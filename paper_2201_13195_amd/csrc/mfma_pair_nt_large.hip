@@ -11,7 +11,6 @@ hipError_t launch_pair_nt(const PairPlain &plain, int sk_cfg, int kind, const Ge
                           int shares, hipStream_t stream, const ColsumArgs *gc) {
     switch (plain.cfg) {
         case GEMM_LARGE: return launch_pair_nt_large(sk_cfg, kind, ga, gb, plain.tiles, tiles_b, shares, stream, gc);
-        case GEMM_SPLIT: return launch_pair_nt_split(sk_cfg, kind, ga, gb, plain.tiles, tiles_b, shares, stream, gc);
         case GEMM_COMPACT: return launch_pair_nt_compact(sk_cfg, kind, ga, gb, plain.tiles, tiles_b, shares, stream, gc);
         default: return launch_pair_nt_mid(sk_cfg, kind, ga, gb, plain.tiles, tiles_b, shares, stream, gc);
     }

@@ -54,9 +54,9 @@ hipError_t launch_pair_sors(const PairPlain &plain, bool row_indexed_b, const Ge
     case CFG:                                                                                         \
         return row_indexed_b ? launch_impl<SHAPE, B_NCONTIG>(ga, gs, plain.tiles, chunks, first, stream) \
                              : launch_impl<SHAPE, B_KCONTIG>(ga, gs, plain.tiles, chunks, first, stream);
+    if (row_indexed_b && dx_cfg(plain.cfg, ga.K) == GEMM_SPLIT) return launch_impl<ShapeSplit, B_NCONTIG>(ga, gs, plain.tiles, chunks, first, stream);
     switch (plain.cfg) {
         RMM_SORS_CASE(GEMM_LARGE, ShapeLarge)
-        RMM_SORS_CASE(GEMM_SPLIT, ShapeSplit)
         RMM_SORS_CASE(GEMM_MID, ShapeMid)
         default: return hipErrorInvalidValue;
     }

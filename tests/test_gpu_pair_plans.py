@@ -39,7 +39,7 @@ def test_passes_with_plans_of_their_own(shape, kind):
 
 
 # Every pairing of a plain tile and a sketch tile that passes with 256 to 16384 tokens and widths of 256 to 4096 take:
-# (tokens, width of the sketched operand, other width, k), kind, tiles.  (test_launch_plans.py: they take these, and there are no others.)
+# (tokens, width of the sketched operand, other width, k), kind, tiles ("split": dX with two wave groups).  (test_launch_plans.py: they take these, and there are no others.)
 PAIRS = [((4439, 280, 2776, 222), rmm.GAUSSIAN, "256x256", "128x256"),
          ((4439, 280, 2776, 222), rmm.RADEMACHER, "256x256", "128x256"),
          ((7121, 304, 1320, 356), rmm.GAUSSIAN, "256x256", "128x384"),
@@ -98,3 +98,16 @@ def test_every_pairing_of_tiles(shape, kind, plain, sketch):
     Y1, G1 = rmm.rmm_forward(Ad, Wd, None, k, kind, 0x5EED0081, 14, profile=(binding.STAGE_FWD_Y, a, b))
     dX1, dW1, _ = rmm.rmm_backward(Ad, Wt, Xpd, kind, 0x5EED0081, 14, profile=(binding.STAGE_BWD_DX, a, b))
     assert torch.equal(Y, Y1) and torch.equal(G, G1) and torch.equal(dX, dX1) and torch.equal(dW, dW1)
+
+
+@pytest.mark.parametrize("n,d,d_other", [(4096, 3072, 768), (4090, 776, 760), (2056, 1544, 1032), (16384, 1024, 1024)])
+def test_y_has_the_same_bits_beside_any_sketch(n, d, d_other):
+    """k, kind and scratch choose how the launch of Y with a sketch product is made up; the bits of Y follow from its sizes."""
+    A, W = (synth.to_torch(synth.normal(s, 0x5EED0090 + sum(s), std), "bf16").to("cuda") for s, std in (((n, d), 1.0), ((d_other, d), 0.05)))
+    want = None
+    for kind in (rmm.GAUSSIAN, rmm.RADEMACHER, rmm.SORS):
+        for k in (65, n // 20, n // 10, n // 5, n // 2, 9 * n // 10):
+            if rmm.rmm_uses_paired_launch(n, d, d_other, k, torch.bfloat16, kind, binding.OP_FORWARD):
+                Y, _ = rmm.rmm_forward(A, W, None, k, kind, 5, 1)
+                want = Y if want is None else want
+                assert torch.equal(Y, want), (kind, k)
