@@ -71,7 +71,7 @@ PlainSlices plain_backward_slices(const rmm_layer_desc_t *d, size_t room) {
     const GRows g = g_rows(d, room);
     if (d->dtype == RMM_DTYPE_BF16 && g.row % 8 == 0)
         return plain_slices(d->n, d->d_out, d->k, d->d_in, d->kind, true, slices_in(room - g.bytes, d->k, g.row));
-    return PlainSlices{1, 0, 0, 0, plain_cfg((int)elem_bytes(d->dtype), d->n, d->d_in, true)};
+    return PlainSlices{1, 0, 0, 0, d->dtype == RMM_DTYPE_F32 ? plain_backward_cfg_f32(d->n, d->d_in, d->d_out, d->k, d->kind) : plain_cfg(2, d->n, d->d_in, true)};
 }
 size_t slices_bytes(const PlainSlices &cut) {
     return cut.slices > 1 ? round_up((size_t)cut.slices * (size_t)cut.stride * sizeof(float), 256) : 0;

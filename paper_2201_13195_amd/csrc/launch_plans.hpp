@@ -413,6 +413,17 @@ inline int64_t plain_tiles(int cfg, int64_t m, int64_t n) {
     return tiles_of(m, n, e, e);
 }
 
+// Tile of dX beside G in an fp32 pass.  Beside 64 x 64 tiles few sketch tiles are 32 x 32, beside 128 x 128 tiles all are 32 x 128,
+// which take 21 ns a token instead of 9 (+-1 entries 12.5 and 5.4): the larger tile only where that stays below what 64 x 64 tiles
+// of dX take, half a round more than there are and 3.5 us and 18.5 ns a contraction element each (3308 x 609 -> 264, k = 331: backward
+// 80 us with 128 x 128 tiles, 50 without; 3076 x 2776 -> 277, k = 615: 100 and 137).
+inline int plain_backward_cfg_f32(int64_t n, int64_t d_in, int64_t d_out, int64_t k, int kind) {
+    const int cfg = plain_cfg(4, n, d_in, true);
+    if (cfg != PLAIN_BIG || plain_cfg(4, n, d_in, false) == PLAIN_BIG || tiles_of(k, d_out, 32, 128) >= 64) return cfg;
+    const double rounds = (double)plain_tiles(PLAIN_MID, n, d_in) / 256 + 0.5;
+    return (kind == 0 ? 21e-3 : 12.5e-3) * (double)n <= rounds * (3.5 + 18.5e-3 * (double)d_out) ? PLAIN_BIG : PLAIN_MID;
+}
+
 // How a launch loads its operands (rows of `a` and `b` elements): 4 = 16-byte loads (fp32, rows that start on 16
 // bytes), 3 = rows that start anywhere, 0 = rows too long for 32-bit offsets inside a tile of 128 of them.  bf16 operands
 // differ (rows_on_16): a row that starts anywhere costs a fifth dword, a funnel shift and its masks per eight

@@ -41,6 +41,7 @@ int pass_plan(int64_t n, int64_t d_sk, int64_t d_other, int64_t k, int kind, int
     put(p.sketch, o);
     return p.plain.cfg;
 }
+int f32_tile(int64_t n, int64_t d_in, int64_t d_out, int64_t k, int64_t kind) { return plain_backward_cfg_f32(n, d_in, d_out, k, (int)kind); }
 int dx_tile(int cfg, int64_t kk) { return dx_cfg(cfg, kk); }
 void backward_plan(int64_t n, int64_t d_in, int64_t d_out, int64_t k, int kind, int with_dbias, int64_t *o) {
     put(plan_backward(n, d_in, d_out, k, kind, with_dbias != 0).sketch, o);
@@ -211,3 +212,16 @@ def test_odd_widths_with_a_short_last_round_take_smaller_tiles(plans):
     assert seen == {"64", "128"}
     assert tile(4096, 512, 300, 1499, rmm.RADEMACHER)[0] == "128"                  # 1536 tiles of 64 x 64: six rounds
     assert tile(3000, 1001, 300, 768, rmm.RADEMACHER, 1)[0] == "64"                # (dX has 64 x 64 tiles by itself)
+
+
+def test_fp32_backward_passes_keep_small_sketch_tiles_where_these_are_the_longest(plans):
+    """dX on 128 x 128 tiles brings G to 32 x 128 tiles: not where few of them would take longer than all of dX."""
+    def edge(*a):
+        return (128, 64, 32)[plans.lib.f32_tile(*map(ctypes.c_int64, a))]
+
+    for shape in ((3308, 609, 264, 331), (4096, 768, 200, 205), (2440, 1011, 78, 244), (4077, 553, 71, 203), (1840, 1204, 143, 184)):
+        assert edge(*shape, rmm.GAUSSIAN) == 64, shape
+    for shape in ((1542, 1698, 1134, 77), (3590, 3032, 1032, 179), (3076, 2776, 277, 615), (2470, 2613, 266, 494), (4096, 768, 3072, 410)):
+        assert edge(*shape, rmm.GAUSSIAN) == 128, shape
+    assert edge(751, 2922, 120, 37, rmm.RADEMACHER) == 128 and edge(3308, 609, 264, 331, rmm.SORS) == 64
+    assert edge(1024, 700, 3072, 64, rmm.GAUSSIAN) == edge(1024, 700, 3072, 1000, rmm.GAUSSIAN) == 32    # too few tiles of 64 x 64 for either
