@@ -84,12 +84,15 @@ size_t ws_backward(const rmm_layer_desc_t *d) {
     if (!use_mfma(d)) return g_rows(d).bytes + slices_bytes(plain_backward_slices(d, SIZE_MAX));
     return g_rows(d).bytes + (sliced_sketch(d) ? round_up(sketch_workspace_bf16(d->n, d->d_out, d->k, d->d_in), 256) : 0);
 }
-// The least that a pass runs in.
-size_t least_forward(const rmm_layer_desc_t *d) {
-    return sliced_sketch(d) ? round_up(least_sketch_workspace_bf16(d->n, d->d_in, d->k, d->d_out), 256) : 0;
+// Whether a pass runs in `bytes`.  (What two slices take is enough for any with more than kSmallK columns, without asking for its plan.)
+bool sketch_runs_in(const rmm_layer_desc_t *d, int64_t d_sk, int64_t d_other, size_t bytes) {
+    if (!sliced_sketch(d) || (d->k > kSmallK && bytes >= round_up((size_t)2 * (size_t)d->k * (size_t)d_sk * sizeof(float), 256))) return true;
+    return bytes >= round_up(least_sketch_workspace_bf16(d->n, d_sk, d->k, d_other), 256);
 }
-size_t least_backward(const rmm_layer_desc_t *d) {
-    return g_rows(d, 0).bytes + (sliced_sketch(d) ? round_up(least_sketch_workspace_bf16(d->n, d->d_out, d->k, d->d_in), 256) : 0);
+bool forward_runs_in(const rmm_layer_desc_t *d, size_t bytes) { return sketch_runs_in(d, d->d_in, d->d_out, bytes); }
+bool backward_runs_in(const rmm_layer_desc_t *d, size_t bytes) {
+    const size_t g = g_rows(d, 0).bytes;
+    return bytes >= g && sketch_runs_in(d, d->d_out, d->d_in, bytes - g);
 }
 
 // variance monitors: per-block partials (doubles), then, off the MFMA path, X^T dY in fp32.  (`room`: partials of X^T dY that there is scratch for)
@@ -395,7 +398,7 @@ int rmm_forward_profiled(const rmm_layer_desc_t *desc, rmm_rng_state_t state, co
         return RMM_ERR_INVALID_ARG;
     if (!grid_ok(desc->n) || !grid_ok(desc->k)) return RMM_ERR_UNSUPPORTED;
     if (ws == nullptr) ws_bytes = 0;
-    if (X_proj != nullptr && ws_bytes < least_forward(desc)) return RMM_ERR_WORKSPACE;
+    if (X_proj != nullptr && !forward_runs_in(desc, ws_bytes)) return RMM_ERR_WORKSPACE;
     const SketchState st = make_state(state.seed, state.offset, desc->n);
     hipStream_t s = (hipStream_t)stream;
     StageEvents ev;
@@ -421,7 +424,7 @@ static int backward_checked(const rmm_layer_desc_t *desc, rmm_rng_state_t state,
         !aligned16(ws))
         return RMM_ERR_INVALID_ARG;
     if (!grid_ok(desc->n) || !grid_ok(desc->k) || !grid_ok(desc->d_out)) return RMM_ERR_UNSUPPORTED;
-    if (ws == nullptr || ws_bytes < least_backward(desc)) return RMM_ERR_WORKSPACE;
+    if (ws == nullptr || !backward_runs_in(desc, ws_bytes)) return RMM_ERR_WORKSPACE;
     const SketchState st = make_state(state.seed, state.offset, desc->n);
     hipStream_t s = (hipStream_t)stream;
     StageEvents ev;

@@ -288,13 +288,19 @@ inline int dx_cfg(int cfg, int64_t kk) { return cfg == GEMM_MID && kk >= 1536 ? 
 // passes of those ranges take other plans, 4 % slower on average; the worst of 60: 13986 x 376 -> 1808, k = 6993, Rademacher,
 // forward 102 -> 132 us.)  Less than 0.8 us, which is what the model is off by at the smallest sizes, is not worth another order of additions
 // than that of the product alone.
-inline PassPlan make_pass_plan(int64_t n, int64_t d_sk, int64_t d_other, int64_t k, int kind, int64_t room) {
+// The product alone is taken as rmm_sketch_static has it, whose partial sums are few.  A pass may have more of them, by as much over what
+// the product alone takes without that limit, for 8 % of the model's time (`limited`: not so).  (12531 x 760 -> 272, k =
+// 6265, Rademacher, forward: 172 us in one slice, 124 in two and a short one; 26 of 260 passes with k from a fifth of the tokens on, 8 % faster
+// on average, 1.00 to 1.20.  With a margin of 5 % two of 28 lose 5 %.)
+inline PassPlan make_pass_plan(int64_t n, int64_t d_sk, int64_t d_other, int64_t k, int kind, bool limited, int64_t room) {
     const SketchPlan alone = plan_sketch(n, d_sk, k, kind, true, room);
+    const int most = limited ? alone.splits : plan_sketch(n, d_sk, k, kind, false, room).splits;
     const double partial_mb = (double)k * (double)d_sk * 4e-6;
     const PairPlain usual = pair_plain(n, d_other);
     const PairPlain compact{GEMM_COMPACT, (int)gemm_tiles(GEMM_COMPACT, n, d_other)};
     PassPlan best{usual, alone};
     double best_us = pair_us(usual, d_sk, alone, kind, partial_mb) - 0.8;
+    auto many = [](int splits, int of_alone) { return splits > 1 && (of_alone == 1 || 4 * (splits - 1) > 5 * of_alone); };
     for (int cfg = 0; cfg < kSketchTiles; ++cfg) {
         int slices = -1, per_tail = -1;
         for (int target : {64, 96, 128, 192, 256, 320}) {
@@ -303,11 +309,12 @@ inline PassPlan make_pass_plan(int64_t n, int64_t d_sk, int64_t d_other, int64_t
             slice_sketch(p, n, target, 4.0 / kSketchMenu[cfg].step_us[kind != 0], room);
             if (p.slices == slices && p.per_tail == per_tail) continue;
             slices = p.slices, per_tail = p.per_tail;
-            if (p.splits > 1 && (alone.splits == 1 || 4 * (p.splits - 1) > 5 * alone.splits)) continue;
-            double us = pair_us(usual, d_sk, p, kind, partial_mb);
+            if (many(p.splits, alone.splits) && many(p.splits, most)) continue;
+            const double worth = many(p.splits, alone.splits) ? 1.08 : 1.0;
+            double us = worth * pair_us(usual, d_sk, p, kind, partial_mb);
             if (us < best_us) best = PassPlan{usual, p}, best_us = us;
             if (cfg != SK_NARROW64 || usual.cfg == GEMM_LARGE || compact.tiles + p.shares() > 512) continue;
-            us = pair_us(compact, d_sk, p, kind, partial_mb);
+            us = worth * pair_us(compact, d_sk, p, kind, partial_mb);
             if (us < best_us) best = PassPlan{compact, p}, best_us = us;
         }
     }
@@ -316,6 +323,7 @@ inline PassPlan make_pass_plan(int64_t n, int64_t d_sk, int64_t d_other, int64_t
 
 // The same, remembered: a pass asks for its plan three times (workspace of either kind, launch), and it depends on the
 // sizes alone.  With scratch for fewer slices than it takes, another one for these.
+constexpr int64_t kLimited = -1;  // (in place of `room`: without a limit, the `limited` plan)
 inline PassPlan plan_pass(int64_t n, int64_t d_sk, int64_t d_other, int64_t k, int kind, int64_t room = kMostSlices) {
     struct Entry {
         int64_t n, d_sk, d_other, k, room;
@@ -323,20 +331,23 @@ inline PassPlan plan_pass(int64_t n, int64_t d_sk, int64_t d_other, int64_t k, i
         PassPlan plan;
     };
     constexpr size_t ENTRIES = 64;
-    static thread_local Entry memo[ENTRIES];  // (n = 0: empty)
-    if (room < kMostSlices) {
+    static thread_local Entry memo[ENTRIES];  // (n = 0: empty; a plan is in either of two neighbours)
+    if (room >= kMostSlices) {
+        room = kMostSlices;
+    } else if (room != kLimited) {
         const PassPlan p = plan_pass(n, d_sk, d_other, k, kind);
         if (p.sketch.splits == 1 || p.sketch.splits <= room) return p;
-    } else {
-        room = kMostSlices;
     }
     kind = kind != 0;
     const uint64_t h = ((uint64_t)n * 0x9E3779B97F4A7C15u ^ (uint64_t)d_sk * 0xC2B2AE3D27D4EB4Fu ^ (uint64_t)d_other * 0x165667B19E3779F9u ^
                         (uint64_t)k * 0x27D4EB2F165667C5u) + (uint64_t)(2 * room + kind);
-    Entry &e = memo[(h ^ h >> 32) % ENTRIES];
-    if (e.n != n || e.d_sk != d_sk || e.d_other != d_other || e.k != k || e.room != room || e.kind != kind)
-        e = Entry{n, d_sk, d_other, k, room, kind, make_pass_plan(n, d_sk, d_other, k, kind, room)};
-    return e.plan;
+    const size_t at = (h ^ h >> 32) % ENTRIES;
+    auto is = [&](const Entry &e) { return e.n == n && e.d_sk == d_sk && e.d_other == d_other && e.k == k && e.room == room && e.kind == kind; };
+    for (Entry *e : {&memo[at], &memo[at ^ 1]})
+        if (is(*e)) return e->plan;
+    memo[at ^ 1] = memo[at];  // (the older of the two goes)
+    memo[at] = Entry{n, d_sk, d_other, k, room, kind, make_pass_plan(n, d_sk, d_other, k, kind, room == kLimited, room == kLimited ? kMostSlices : room)};
+    return memo[at].plan;
 }
 
 // Whether the bias gradient's column sums go with dW: beside it where its launch has room (64 compute units idle in the last round,
@@ -384,10 +395,12 @@ inline size_t sketch_workspace_bf16(int64_t n, int64_t d, int64_t k, int64_t d_o
     }
     return most;
 }
-// The least that a pass runs in: two slices where it asks for any.
+// The least that a pass runs in: two slices, or one where the partial sums are so many that the limited plan has one.
 inline size_t least_sketch_workspace_bf16(int64_t n, int64_t d, int64_t k, int64_t d_other) {
     const size_t most = sketch_workspace_bf16(n, d, k, d_other);
-    return k <= kSmallK || most == 0 ? most : (size_t)2 * (size_t)k * (size_t)d * sizeof(float);
+    if (k <= kSmallK || most == 0) return most;
+    const bool sliced = plan_pass(n, d, d_other, k, 0, kLimited).sketch.splits > 1 || plan_pass(n, d, d_other, k, 1, kLimited).sketch.splits > 1;
+    return sliced ? (size_t)2 * (size_t)k * (size_t)d * sizeof(float) : 0;
 }
 
 // ---- fp32 products, and bf16 products of widths the kernels above refuse (plain_kernels.hpp).
