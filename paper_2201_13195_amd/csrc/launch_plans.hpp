@@ -246,12 +246,14 @@ inline double pair_us(const PairPlain &plain, int64_t kk, const SketchPlan &p, i
     struct SketchTimes {
         double fix, step[2];  // Gaussian, Rademacher
     };
-    static const SketchTimes sk_compact{5.5, {1.009, 0.935}};
+    static const SketchTimes sk_compact{5.5, {1.009, 0.935}}, sk_compact_two{5.5, {1.28, 1.07}};
     static const SketchTimes sk[] = {{5.3, {1.288, 0.957}}, {7.2, {1.651, 1.476}}, {5.1, {1.078, 1.080}},   // (in the order of SK_NARROW ..)
                                      {5.0, {0.929, 0.910}}, {6.3, {1.490, 1.192}}, {4.05, {0.780, 0.722}}};
     const bool two = plain.cfg == GEMM_COMPACT;
     const Times &a = plain.cfg == GEMM_LARGE ? large : two ? compact : kk >= 1536 ? mid_long : mid;
-    const SketchTimes &b = two ? sk_compact : sk[p.cfg];
+    // sk_compact_two: unsliced sketch work-groups that come first and are more than the compute units share some for all of their
+    // time (87 launches; 4859 x 1928 -> 520, k = 2430, 304 of them: 118 us where 82 were planned, another plan 90).
+    const SketchTimes &b = !two ? sk[p.cfg] : p.slices == 1 && p.shares() > 256 ? sk_compact_two : sk_compact;
     const double ta = a.fix + a.step * (double)((kk + 63) / 64), tb = b.fix + b.step[kind != 0] * (double)(p.k_chunk / 64);
     const int64_t slots = two ? 512 : 256;
     double t = sketch_goes_first(plain.tiles, p.slices) ? makespan(p.shares(), tb, plain.tiles, ta, slots)

@@ -229,3 +229,9 @@ def test_fp32_backward_passes_keep_small_sketch_tiles_where_these_are_the_longes
         assert edge(*shape, rmm.GAUSSIAN) == 128, shape
     assert edge(751, 2922, 120, 37, rmm.RADEMACHER) == 128 and edge(3308, 609, 264, 331, rmm.SORS) == 64
     assert edge(1024, 700, 3072, 64, rmm.GAUSSIAN) == edge(1024, 700, 3072, 1000, rmm.GAUSSIAN) == 32    # too few tiles of 64 x 64 for either
+
+
+def test_unsliced_sketch_products_do_not_share_compute_units_with_themselves_lightly(plans):
+    """304 and 322 work-groups of all tokens beside ShapeCompact, two of them on a compute unit: planned too short, and slower than others."""
+    for shape, kind in (((4859, 1928, 520, 2430), rmm.GAUSSIAN), ((3881, 1264, 688, 3492), rmm.RADEMACHER), ((3273, 1576, 704, 2945), rmm.GAUSSIAN)):
+        assert plans.forward(*shape, kind)[0] == "128x128", shape
