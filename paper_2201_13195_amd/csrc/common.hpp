@@ -127,7 +127,6 @@ hipError_t launch_backward_pair_sors_bf16(const bf16_t *dY, const bf16_t *W, bf1
 
 // Variance monitors (variance.hip, and the squared-norm epilogue of the MFMA kernel).
 //   part[3*b..] = per-block (sum |x_k|^2, sum |y_k|^2, sum |x_k|^2 |y_k|^2); row_norm_blocks(n) blocks.
-int row_norm_blocks(int64_t n);
 template <typename T>
 hipError_t launch_row_norms(const T *X, const T *Y, int64_t n, int64_t d_in, int64_t d_out, double *part,
                             hipStream_t stream);

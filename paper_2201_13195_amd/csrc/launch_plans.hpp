@@ -34,6 +34,12 @@ inline int64_t colsum_blocks(int64_t d, int64_t elem_bytes) {
 }
 inline int64_t colsum_narrow_blocks(int64_t d) { return (d + 7) / 8; }
 
+// Work-groups of the row norms of X and dY (row_norms.hpp): eight waves, one row of either per wave at a time; enough of them for the chip.
+inline int row_norm_blocks(int64_t n) {
+    const int64_t b = (n + 7) / 8;
+    return (int)(b < 1024 ? b : 1024);
+}
+
 // The plain product of a paired launch: its tile (GEMM_LARGE, GEMM_MID or, with SK_NARROW64, GEMM_COMPACT; dX: see dx_cfg) and
 // number of tiles.
 struct PairPlain {
@@ -71,9 +77,13 @@ inline double tile_us(const TileTime &t, int64_t tiles, int64_t kk, bool filled)
 
 // Tile of a plain product with an m x n output and contraction kk.  32 x 32 tiles whose contraction is shared by eight
 // waves (few_tile) only while there are at most 512 of them.  256 x 256 tiles from 160 of them on whatever the model
-// says: they need half the bytes per flop of 128 x 128 tiles, which a full chip cannot bring into its LDS at MFMA rate.
-inline int gemm_cfg(int64_t m, int64_t n, int64_t kk, bool filled = false) {
-    if (gemm_tiles(GEMM_LARGE, m, n) >= 160) return GEMM_LARGE;
+// says: they need half the bytes per flop of 128 x 128 tiles, which a full chip cannot bring into its LDS at MFMA rate.  And from 130 on
+// where 128 x 128 tiles, with the `beside` other work-groups of the launch, go over two rounds (36 products from 516 to 660 of those:
+// 0.73 to 1.02 of the time, 0.84 on average; with 455 to 510 of them 0.88 to 1.31).
+inline int gemm_cfg(int64_t m, int64_t n, int64_t kk, int64_t beside = 0) {
+    const int64_t large = gemm_tiles(GEMM_LARGE, m, n);
+    if (large >= 160 || (large >= 130 && gemm_tiles(GEMM_MID, m, n) + beside > 512)) return GEMM_LARGE;
+    const bool filled = beside > 0;
     static const struct {
         int cfg;
         TileTime t;
@@ -99,7 +109,7 @@ inline int gemm_cfg(int64_t m, int64_t n, int64_t kk, bool filled = false) {
 // the row norms (6670 tokens, 608 x 1704: 270 tiles of 64 x 64 63 us, 140 of 64 x 128 49).
 // In scratch for less than a partial sum of each of these, 128 x 128 tiles.
 inline int xty_cfg(int64_t m, int64_t n, int64_t kk, int64_t room = INT64_MAX) {
-    const int cfg = gemm_cfg(m, n, kk, true), small = cfg == GEMM_FEW ? GEMM_SMALL : cfg;
+    const int cfg = gemm_cfg(m, n, kk, row_norm_blocks(kk)), small = cfg == GEMM_FEW ? GEMM_SMALL : cfg;
     return gemm_tiles(small, m, n) <= room ? small : kk >= 1536 ? GEMM_SPLIT : GEMM_MID;
 }
 inline int xty_sumsq_tiles(int64_t n, int64_t d_in, int64_t d_out, int64_t room = INT64_MAX) {

@@ -67,12 +67,6 @@ __global__ void __launch_bounds__(1024) variance_finalize(const double *__restri
 
 }  // namespace
 
-// Work-groups of eight waves, one row of X and dY per wave at a time; enough of them for the chip.
-int row_norm_blocks(int64_t n) {
-    const int64_t b = (n + 7) / 8;
-    return (int)(b < 1024 ? b : 1024);
-}
-
 int sumsq_blocks(int64_t elems) {
     const int64_t b = (elems + 255) / 256;
     return (int)(b < 1024 ? b : 1024);

@@ -235,3 +235,13 @@ def test_unsliced_sketch_products_do_not_share_compute_units_with_themselves_lig
     """304 and 322 work-groups of all tokens beside ShapeCompact, two of them on a compute unit: planned too short, and slower than others."""
     for shape, kind in (((4859, 1928, 520, 2430), rmm.GAUSSIAN), ((3881, 1264, 688, 3492), rmm.RADEMACHER), ((3273, 1576, 704, 2945), rmm.GAUSSIAN)):
         assert plans.forward(*shape, kind)[0] == "128x128", shape
+
+
+def test_products_a_little_over_two_rounds_take_the_largest_tiles(plans):
+    """More than 512 tiles of 128 x 128, the other work-groups of the launch among them, on half the chip or more of 256 x 256."""
+    for shape in ((2696, 2952, 2384), (3992, 2136, 408), (2576, 3168, 104), (13048, 696, 808)):
+        assert plans.plain(*shape) == "256x256", shape
+    for shape in ((2600, 2984, 552), (3040, 2576, 384), (10216, 680, 272), (4096, 2048, 300)):     # up to 512 of them, or no half of the chip
+        assert plans.plain(*shape) != "256x256", shape
+    assert plans.variance(920, 3272, 2776) == plans.variance(384, 3040, 2576) == "256x256"         # 572, and 504 with 48 of the row norms
+    assert plans.variance(400, 1872, 3880) != "256x256" and plans.variance(4096, 768, 3072) == "128x128 split"
