@@ -113,7 +113,7 @@ typedef struct {
  * 8 in none (forward) or k * d_out * 2 bytes rounded up to 256 (backward); with k > 64 and widths that are multiples
  * of 8 in the fp32 sums of two token slices where it asks for more of them (forward 8 * k * d_in bytes; backward
  * 2 * k * d_out and 8 * k * d_out, each rounded up to 256), and without these sums where rmm_sketch of X (dY) has
- * none.  So do the variance monitors in bf16 with widths that are multiples of 8: in what 128 x 128 tiles of
+ * none, and in a few more cases.  So do the variance monitors in bf16 with widths that are multiples of 8: in what 128 x 128 tiles of
  * X^T dY take, where smaller tiles ask for more. */
 size_t rmm_workspace_bytes(const rmm_layer_desc_t *desc, int op);
 

@@ -248,7 +248,7 @@ inline double makespan(int64_t first, double t1, int64_t second, double t2, int6
 // a compute unit.  The times are fitted to 4300 launches of 60 passes (256 to 16384 tokens, widths 256 to 4096,
 // k = 73 to 6911; all sketch tiles, 64 to 512 work-groups): 7 % rms off.  Over those passes the plan it leads to is 3.3 % slower than the
 // best one on average and 30 % at most; plans made for the sketch product alone were 12 and 50 %.
-inline double pair_us(const PairPlain &plain, int64_t kk, const SketchPlan &p, int kind, double partial_mb) {
+inline double pair_us(const PairPlain &plain, int64_t kk, const SketchPlan &p, int kind, double partial_mb, bool limited = false) {
     struct Times {
         double fix, step;
     };
@@ -262,8 +262,9 @@ inline double pair_us(const PairPlain &plain, int64_t kk, const SketchPlan &p, i
     const bool two = plain.cfg == GEMM_COMPACT;
     const Times &a = plain.cfg == GEMM_LARGE ? large : two ? compact : kk >= 1536 ? mid_long : mid;
     // sk_compact_two: unsliced sketch work-groups that come first and are more than the compute units share some for all of their
-    // time (87 launches; 4859 x 1928 -> 520, k = 2430, 304 of them: 118 us where 82 were planned, another plan 90).
-    const SketchTimes &b = !two ? sk[p.cfg] : p.slices == 1 && p.shares() > 256 ? sk_compact_two : sk_compact;
+    // time (87 launches; 4859 x 1928 -> 520, k = 2430, 304 of them: 118 us where 82 were planned, another plan 90).  `limited` plans, which
+    // say the least scratch of a pass, are made without.
+    const SketchTimes &b = !two ? sk[p.cfg] : !limited && p.slices == 1 && p.shares() > 256 ? sk_compact_two : sk_compact;
     const double ta = a.fix + a.step * (double)((kk + 63) / 64), tb = b.fix + b.step[kind != 0] * (double)(p.k_chunk / 64);
     const int64_t slots = two ? 512 : 256;
     double t = sketch_goes_first(plain.tiles, p.slices) ? makespan(p.shares(), tb, plain.tiles, ta, slots)
@@ -311,7 +312,7 @@ inline PassPlan make_pass_plan(int64_t n, int64_t d_sk, int64_t d_other, int64_t
     const PairPlain usual = pair_plain(n, d_other);
     const PairPlain compact{GEMM_COMPACT, (int)gemm_tiles(GEMM_COMPACT, n, d_other)};
     PassPlan best{usual, alone};
-    double best_us = pair_us(usual, d_sk, alone, kind, partial_mb) - 0.8;
+    double best_us = pair_us(usual, d_sk, alone, kind, partial_mb, limited) - 0.8;
     auto many = [](int splits, int of_alone) { return splits > 1 && (of_alone == 1 || 4 * (splits - 1) > 5 * of_alone); };
     for (int cfg = 0; cfg < kSketchTiles; ++cfg) {
         int slices = -1, per_tail = -1;
@@ -323,10 +324,10 @@ inline PassPlan make_pass_plan(int64_t n, int64_t d_sk, int64_t d_other, int64_t
             slices = p.slices, per_tail = p.per_tail;
             if (many(p.splits, alone.splits) && many(p.splits, most)) continue;
             const double worth = many(p.splits, alone.splits) ? 1.08 : 1.0;
-            double us = worth * pair_us(usual, d_sk, p, kind, partial_mb);
+            double us = worth * pair_us(usual, d_sk, p, kind, partial_mb, limited);
             if (us < best_us) best = PassPlan{usual, p}, best_us = us;
             if (cfg != SK_NARROW64 || usual.cfg == GEMM_LARGE || compact.tiles + p.shares() > 512) continue;
-            us = worth * pair_us(compact, d_sk, p, kind, partial_mb);
+            us = worth * pair_us(compact, d_sk, p, kind, partial_mb, limited);
             if (us < best_us) best = PassPlan{compact, p}, best_us = us;
         }
     }

@@ -100,12 +100,14 @@ def test_token_slices_follow_the_scratch(shape, kind):
         assert e.value.status == -3
 
 
-def test_one_slice_where_the_partial_sums_are_many():
-    """A pass whose sketch product alone has no slices, for the size of its partial sums, asks for some and runs without."""
-    n, d_in, d_out, k = 4637, 1008, 304, 4173
+@pytest.mark.parametrize("shape,alone", [((4637, 1008, 304, 4173), False), ((2511, 3088, 440, 1255), True)])
+def test_one_slice_where_passes_had_one(shape, alone):
+    """A pass whose sketch product alone has no slices, for the size of its partial sums, asks for some and runs without; and one
+    that had none beside a plain product on half of the compute units."""
+    n, d_in, d_out, k = shape
     need = [rmm.rmm_workspace_bytes(n, d_in, d_out, k, torch.bfloat16, rmm.RADEMACHER, op) for op in (binding.OP_FORWARD, binding.OP_BACKWARD)]
-    assert rmm.rmm_workspace_bytes(n, d_in, d_in, k, torch.bfloat16, rmm.RADEMACHER, binding.OP_SKETCH) == 0 < need[0]
-    check_pass((n, d_in, d_out, k), rmm.RADEMACHER, [0, need[0] - 4, need[0]], [up(k * d_out * 2) + up(2 * k * d_out * 4), need[1]])
+    assert need[0] > 0 and (rmm.rmm_workspace_bytes(n, d_in, d_in, k, torch.bfloat16, rmm.RADEMACHER, binding.OP_SKETCH) > 0) == alone
+    check_pass(shape, rmm.RADEMACHER, [0, need[0] - 4, need[0]], [up(k * d_out * 2) + up(2 * k * d_out * 4), need[1]])
 
 
 @pytest.mark.parametrize("shape", [(201, 200, 136), (1000, 264, 520), (2100, 1800, 520), (197, 2504, 776)])
