@@ -504,15 +504,18 @@ inline PlainSlices plain_slices_beside(int cfg, int64_t n, int64_t d, int64_t k,
 
 // The tile of the plain product and the slices of a pass.  A launch of 128 x 128 tiles of Y and sketch tiles that goes a little over a
 // round, by up to a quarter of the compute units, has most of them wait for the last few.  With 64 x 64 tiles, three rounds of
-// them at most, the +-1 kind is 9 % faster there (29 of 87 random forward passes that the rule of plain_cfg brings to 128 x 128
-// tiles; 0.82 to 1.085 of the time; the others 2 % slower: 3000 x 768 -> 1001, k = 300, 312 work-groups: 22.4 and 20.7 us), the Gaussian kind,
-// whose sketch tiles are longest by far, is not.
+// them at most, the +-1 kind is 7 % faster there (81 random forward passes; 0.80 to 1.05 of the time; 3000 x 768 -> 1001, k = 300, 312
+// work-groups: 22.4 and 20.7 us), the Gaussian kind, whose sketch tiles are longest by far, is not; nor are passes whose
+// sketch product would lose more than half of its slices beside them (9 passes 1.01 to 1.49: 3495 x 400 -> 799, k = 174, four slices and
+// one: 17.9 and 26.7 us).
 inline PlainSlices plain_slices(int64_t n, int64_t d, int64_t k, int64_t d_other, int kind, bool backward, int64_t most = 16) {
     const PlainSlices cut = plain_slices_beside(plain_cfg(2, n, d_other, backward), n, d, k, d_other, kind, most);
     if (backward || kind != RMM_SKETCH_RADEMACHER || cut.cfg != PLAIN_BIG) return cut;
     const int64_t plain = plain_tiles(PLAIN_BIG, n, d_other), all = plain + tiles_of(k, d, 32, 128) * cut.slices;
     const bool short_round = plain <= 256 && all > 256 && all % 256 >= 1 && all % 256 <= 64;
-    return short_round && plain_tiles(PLAIN_MID, n, d_other) <= 768 ? plain_slices_beside(PLAIN_MID, n, d, k, d_other, kind, most) : cut;
+    if (!short_round || plain_tiles(PLAIN_MID, n, d_other) > 768) return cut;
+    const PlainSlices mid = plain_slices_beside(PLAIN_MID, n, d, k, d_other, kind, most);
+    return 2 * mid.slices >= cut.slices ? mid : cut;
 }
 
 }  // namespace rmm

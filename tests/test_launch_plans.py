@@ -214,6 +214,8 @@ def test_odd_widths_with_a_short_last_round_take_smaller_tiles(plans):
         seen.add(small[0])
         assert small[0] == "64" or small[2] <= 256 or small[2] % 256 == 0 or small[2] % 256 > 64, (k, small)
     assert seen == {"64", "128"}
+    for n, d, d_other, k in ((3495, 400, 799, 174), (3193, 440, 927, 159), (2714, 352, 947, 271)):  # four slices, one beside 64 x 64 tiles
+        assert tile(n, d, k, d_other, rmm.RADEMACHER)[:2] == ("128", 4)
     assert tile(4096, 512, 300, 1499, rmm.RADEMACHER)[0] == "128"                  # 1536 tiles of 64 x 64: six rounds
     assert tile(3000, 1001, 300, 768, rmm.RADEMACHER, 1)[0] == "64"                # (dX has 64 x 64 tiles by itself)
 
