@@ -107,9 +107,16 @@ inline int gemm_cfg(int64_t m, int64_t n, int64_t kk, int64_t beside = 0) {
 // |X^T dY|_F^2 per tile for the variance monitors: the dW-type product (both operands stored
 // [token][feature]) with the squared-norm epilogue; the tiles of the other products, but for 32 x 32, beside the work-groups of
 // the row norms (6670 tokens, 608 x 1704: 270 tiles of 64 x 64 63 us, 140 of 64 x 128 49).
+// Where 128 x 128 tiles take nearly all compute units and are short, the row norms that find none free are a round of their own; there two
+// work-groups to a compute unit (524 tokens, 2824 x 1312: 253 tiles and 66 work-groups of norms 15.4 us, so 12.8; fourteen such shapes of 261
+// to 1594 tokens 0.79 to 0.98 of the time.  Of 2412 tokens and more 0.96 to 1.46, of fewer tiles 0.87 to 1.46, most of them above 1).
 // In scratch for less than a partial sum of each of these, 128 x 128 tiles.
 inline int xty_cfg(int64_t m, int64_t n, int64_t kk, int64_t room = INT64_MAX) {
     const int cfg = gemm_cfg(m, n, kk, row_norm_blocks(kk)), small = cfg == GEMM_FEW ? GEMM_SMALL : cfg;
+    const int64_t mid = gemm_tiles(GEMM_MID, m, n);
+    if ((small == GEMM_MID || small == GEMM_SPLIT) && mid >= 216 && mid <= 256 && mid + row_norm_blocks(kk) > 256 && kk >= 256 && kk <= 2048 &&
+        mid <= room)
+        return GEMM_COMPACT;
     return gemm_tiles(small, m, n) <= room ? small : kk >= 1536 ? GEMM_SPLIT : GEMM_MID;
 }
 inline int xty_sumsq_tiles(int64_t n, int64_t d_in, int64_t d_out, int64_t room = INT64_MAX) {

@@ -213,6 +213,7 @@ hipError_t launch_xty_norms_bf16(const bf16_t *X, const bf16_t *dY, double *part
         case GEMM_WIDE: return launch_xty_norms<ShapeWide>(g, r, stream);
         case GEMM_SPLIT: return launch_xty_norms<ShapeSplit>(g, r, stream);
         case GEMM_MID: return launch_xty_norms<ShapeMid>(g, r, stream);
+        case GEMM_COMPACT: return launch_xty_norms<ShapeCompact>(g, r, stream);
         case GEMM_FLAT: return launch_xty_norms<ShapeFlat>(g, r, stream);
         default: return launch_xty_norms<ShapeSmall>(g, r, stream);
     }

@@ -77,7 +77,7 @@ typedef TileShape<256, 256, 2, 4, 1, 3, 2, 4> ShapeLarge;
 typedef TileShape<128, 256, 2, 4, 1, 3, 3, 2> ShapeWide;
 typedef TileShape<128, 128, 2, 2, 2, 3, 3, 3> ShapeSplit;
 typedef TileShape<128, 128, 2, 4, 1, 3, 3, 1> ShapeMid;
-typedef TileShape<128, 128, 2, 4, 1, 2, 2, 2> ShapeCompact;  // half of LDS: paired launches only
+typedef TileShape<128, 128, 2, 4, 1, 2, 2, 2> ShapeCompact;  // half of LDS: paired launches and X^T dY
 typedef TileShape<64, 128, 2, 4, 1, 3, 3, 1> ShapeFlat;
 typedef TileShape<64, 64, 2, 2, 1, 4, 4, 1> ShapeSmall;
 
@@ -1011,8 +1011,9 @@ __global__ void __launch_bounds__(S::THREADS) dw_colsum_kernel(GemmArgs g, Colsu
 // |X^T dY|_F^2 per tile and the row norms of X and dY (variance monitors) in one launch: the product has
 // few tiles and a long contraction, so the row norms, bound by memory, run on the compute units it leaves
 // idle (or ahead of its last round) instead of in a pass of their own.
+// (ShapeCompact: two work-groups to a compute unit)
 template <typename S>
-__global__ void __launch_bounds__(S::THREADS) xty_norms_kernel(GemmArgs g, RowNormArgs r, int tiles) {
+__global__ void __launch_bounds__(S::THREADS, S::SA == 2 ? 4 : 1) xty_norms_kernel(GemmArgs g, RowNormArgs r, int tiles) {
     __shared__ __attribute__((aligned(1024))) bf16_t lds[S::LDS_BYTES / 2];
     if ((int)blockIdx.x < tiles)
         gemm_tile<S, A_MCONTIG, B_NCONTIG, OUT_SUMSQ>(g, lds, blockIdx.x, tiles);

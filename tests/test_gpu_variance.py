@@ -62,7 +62,7 @@ def test_variance_stats_on_correlated_inputs_and_large_tiles():
 
 # (n, d_in, d_out) of each tile that X^T dY runs with, ragged in every dimension (test_launch_plans.py: they are taken)
 TILES = [((201, 200, 136), "64x64"), ((201, 1800, 520), "64x128"), ((197, 2504, 776), "128x128"), ((1101, 2312, 776), "128x128 split"),
-         ((203, 1672, 2312), "128x256"), ((71, 4104, 4104), "256x256")]
+         ((261, 2552, 1528), "128x128 compact"), ((203, 1672, 2312), "128x256"), ((71, 4104, 4104), "256x256")]
 
 
 @pytest.mark.parametrize("shape,tile", TILES)
