@@ -231,7 +231,8 @@ int rmm_sketch_profiled(int64_t n, int64_t d, int64_t k, int dtype, int kind, rm
 
 /* Whether an unprofiled rmm_forward (op = RMM_OP_FORWARD) / rmm_backward with dX (RMM_OP_BACKWARD)
  * of this shape issues its two independent products as one paired launch (RMM_STAGE_FWD_PAIR /
- * RMM_STAGE_BWD_PAIR): 1 or 0; 0 for an invalid descriptor. */
+ * RMM_STAGE_BWD_PAIR): 1 or 0; 0 for an invalid descriptor.  For the SORS kind 1 says that its strips go between the rounds of the
+ * plain product's tiles; other passes of it may be one launch too. */
 int rmm_uses_paired_launch(const rmm_layer_desc_t *desc, int op);
 
 /* Ceilings of the chip as a kernel sees them, for reporting measured fractions beside the

@@ -80,9 +80,14 @@ inline double tile_us(const TileTime &t, int64_t tiles, int64_t kk, bool filled)
 // says: they need half the bytes per flop of 128 x 128 tiles, which a full chip cannot bring into its LDS at MFMA rate.  And from 130 on
 // where 128 x 128 tiles, with the `beside` other work-groups of the launch, go over two rounds (36 products from 516 to 660 of those:
 // 0.73 to 1.02 of the time, 0.84 on average; with 455 to 510 of them 0.88 to 1.31).
-inline int gemm_cfg(int64_t m, int64_t n, int64_t kk, int64_t beside = 0) {
+struct GemmChoice {
+    int cfg;
+    double us;
+};
+inline GemmChoice choose_gemm(int64_t m, int64_t n, int64_t kk, int64_t beside = 0) {
     const int64_t large = gemm_tiles(GEMM_LARGE, m, n);
-    if (large >= 160 || (large >= 130 && gemm_tiles(GEMM_MID, m, n) + beside > 512)) return GEMM_LARGE;
+    if (large >= 160 || (large >= 130 && gemm_tiles(GEMM_MID, m, n) + beside > 512))
+        return GemmChoice{GEMM_LARGE, tile_us(TileTime{6.3, 1.405, false}, large, kk, false)};
     const bool filled = beside > 0;
     static const struct {
         int cfg;
@@ -92,17 +97,17 @@ inline int gemm_cfg(int64_t m, int64_t n, int64_t kk, int64_t beside = 0) {
                 {GEMM_MID, {2.0, 0.50, false}},
                 {GEMM_FLAT, {1.0, 0.42, true}},
                 {GEMM_SMALL, {1.0, 0.27, true}}};
-    int best = GEMM_FEW;
-    double best_us = -1.0;
+    GemmChoice best{GEMM_FEW, -1.0};
     const int64_t few = gemm_tiles(GEMM_FEW, m, n);
     if (few <= 512)  // (two on a compute unit: where a wave's share is one step the second costs 0.6 of the first)
-        best_us = 2.5 + (few <= 256 ? 1.0 : kk <= kFewSingle ? 1.6 : 2.0) * (1.0 + 0.85 * (double)kk / (double)kFewSingle);
+        best.us = 2.5 + (few <= 256 ? 1.0 : kk <= kFewSingle ? 1.6 : 2.0) * (1.0 + 0.85 * (double)kk / (double)kFewSingle);
     for (const auto &e : menu) {
         const double us = tile_us(e.t, gemm_tiles(e.cfg, m, n), kk, filled);
-        if (best_us < 0.0 || us < best_us) best = e.cfg, best_us = us;
+        if (best.us < 0.0 || us < best.us) best = GemmChoice{e.cfg, us};
     }
     return best;
 }
+inline int gemm_cfg(int64_t m, int64_t n, int64_t kk, int64_t beside = 0) { return choose_gemm(m, n, kk, beside).cfg; }
 
 // |X^T dY|_F^2 per tile for the variance monitors: the dW-type product (both operands stored
 // [token][feature]) with the squared-norm epilogue; the tiles of the other products, but for 32 x 32, beside the work-groups of
@@ -368,6 +373,67 @@ inline PassPlan plan_pass(int64_t n, int64_t d_sk, int64_t d_other, int64_t k, i
     memo[at ^ 1] = memo[at];  // (the older of the two goes)
     memo[at] = Entry{n, d_sk, d_other, k, room, kind, make_pass_plan(n, d_sk, d_other, k, kind, room == kLimited, room == kLimited ? kMostSlices : room)};
     return memo[at].plan;
+}
+
+// ---- The SORS kind: strips of eight columns of the sketched operand, which may share a launch with the plain product of their pass.
+
+// Tokens as a power of two, 1024 at least (the shortest transform of the strip kernel).  Up to 2048 a strip takes them in one piece, and
+// any k; from there on in chunks of 2048, with accumulators for kSorsAccMaxK sketch columns.
+inline int sors_log(int64_t n) {
+    int l = 10;
+    while (((int64_t)1 << l) < n) ++l;
+    return l;
+}
+constexpr int64_t kSorsAccMaxK = 2048;
+inline int sors_chunks(int64_t n) { return sors_log(n) >= 12 ? 1 << (sors_log(n) - 11) : 1; }
+
+enum { SORS_APART = 0, SORS_BEHIND = 1, SORS_FRONT = 2, SORS_COMPACT = 3 };
+struct SorsPlan {
+    int order;
+    PairPlain plain;
+};
+
+// How a pass of n tokens launches the strips of a d_sk wide operand and its plain product, n x d_other over d_sk:
+//   SORS_COMPACT  behind the tiles of ShapeCompact, one strip to a work-group: either needs half of a compute unit, so that the strips
+//                 (vector units, LDS, memory) run beside tiles (matrix pipes) and fill places that these leave
+//   SORS_BEHIND   two strips to a work-group, on the compute units that the last round of 256 x 256 or 128 x 128 tiles leaves, 32 or more
+//   SORS_FRONT    the same in front of three or more rounds of tiles, on at most a quarter of the chip
+//   SORS_APART    launches of their own
+// The first by times fitted to 180 passes (513 to 16384 tokens, widths 256 to 4096, inputs that change from step to step).  Over these 90
+// steps, dW included, it is 8.9 % faster than the others alone, at worst 1.4 % slower; with hindsight 9.9 %.  (2275 x 312 -> 584, k = 455: a
+// step 36.5 -> 25.5 us, 2907 x 1248 -> 1136 59.1 -> 44.5, 4250 x 1232 -> 864 71 -> 55.  Not where 256 x 256 tiles fill the chip, whose
+// operands cost half the L2 traffic: 15053 x 2264 -> 3112 500 against 626; nor beside few tiles of a long contraction, which other
+// tiles have more work-groups for: 3277 x 3480 -> 272 73 against 97.)
+inline int sors_among_rounds(int64_t n, int64_t d_sk, int64_t d_other, int64_t k) {
+    const PairPlain plain = pair_plain(n, d_other);
+    if (sors_log(n) < 12 || sors_log(n) > 15 || k > kSorsAccMaxK) return SORS_APART;
+    // (128 x 128 tiles: one round of them, long enough for the strips to finish beside it)
+    if (plain.cfg != GEMM_LARGE && (plain.tiles < 65 || plain.tiles > 256 || d_sk < 768)) return SORS_APART;
+    return (256 - plain.tiles % 256) % 256 >= 32 ? SORS_BEHIND : plain.tiles >= 256 && (d_sk / 8 + 1) / 2 <= 64 ? SORS_FRONT : SORS_APART;
+}
+inline SorsPlan plan_sors(int64_t n, int64_t d_sk, int64_t d_other, int64_t k) {
+    const SorsPlan best{sors_among_rounds(n, d_sk, d_other, k), pair_plain(n, d_other)};
+    const PairPlain &plain = best.plain;
+    const int64_t l = sors_log(n), strips = d_sk / 8, pairs = (strips + 1) / 2;
+    if (l > 15 || (l >= 12 && k > kSorsAccMaxK)) return best;
+    const double steps = (double)((d_sk + 63) / 64), chunks = l < 11 ? 0.6 : (double)sors_chunks(n);
+    double best_us;
+    if (best.order != SORS_APART) {
+        const double tile = plain.cfg == GEMM_LARGE ? 6.7 + 1.405 * steps : 3.4 + 0.487 * steps, two = 2.5 + 5.5 * chunks;
+        best_us = 2.0 + (best.order == SORS_BEHIND ? makespan(plain.tiles, tile, pairs, two, 256) : makespan(pairs, two, plain.tiles, tile, 256));
+    } else {
+        best_us = choose_gemm(n, d_other, d_sk).us + 5.4 + 2.2 * chunks * (strips <= 512 ? 1.0 : (double)strips / 512.0);
+    }
+    const PairPlain compact{GEMM_COMPACT, (int)gemm_tiles(GEMM_COMPACT, n, d_other)};
+    const double strip = 3.8 + 2.5 * chunks, alone = 3.2 + 0.618 * steps;
+    double us = 2.5;
+    if (compact.tiles + strips <= 256)
+        us += alone > strip ? alone : strip;
+    else if (compact.tiles <= 256 && compact.tiles + strips <= 512)  // (some tiles start beside a strip)
+        us += alone + 0.41 * strip;
+    else
+        us += makespan(compact.tiles, 3.8 + 0.836 * steps, strips, 3.8 + 3.9 * chunks, 512);
+    return us < (plain.cfg == GEMM_LARGE ? 0.9 : 1.0) * best_us ? SorsPlan{SORS_COMPACT, compact} : best;
 }
 
 // Whether the bias gradient's column sums go with dW: beside it where its launch has room (64 compute units idle in the last round,

@@ -134,7 +134,7 @@ struct EventPair {
 template <int BMODE>
 static hipError_t launch_plain_of_pass(const GemmArgs &g, int64_t pair_k, int kind, int64_t room, hipStream_t stream) {
     if (pair_k == 0) return launch_gemm<A_KCONTIG, BMODE>(gemm_cfg(g.M, g.N, g.K), g, stream);
-    const int cfg = (kind == RMM_SKETCH_SORS ? pair_plain(g.M, g.N) : plan_pass(g.M, g.K, g.N, pair_k, kind, room).plain).cfg;
+    const int cfg = (kind == RMM_SKETCH_SORS ? plan_sors(g.M, g.K, g.N, pair_k).plain : plan_pass(g.M, g.K, g.N, pair_k, kind, room).plain).cfg;
     return launch_gemm<A_KCONTIG, BMODE>(cfg == GEMM_COMPACT ? GEMM_MID : BMODE == B_NCONTIG ? dx_cfg(cfg, g.K) : cfg, g, stream);
 }
 
@@ -299,38 +299,20 @@ hipError_t launch_backward_pair_bf16(const bf16_t *dY, const bf16_t *W, bf16_t *
     return launch_reduce(ws, G, k, d_out, p.splits, stream);
 }
 
-// ---- SORS kind: the plain product of a pass together with the strips of its sketch product.
-// Worth it when the plain product leaves at least 32 compute units idle in its last round (the
-// sketch work-groups need a compute unit to themselves); the strip kernel's chunked form must
-// apply (at least 4096 tokens after padding, at most 2048 sketch columns).
-static int sors_chunks(int64_t n) {
-    int l = 0;
-    while (((int64_t)1 << l) < n) ++l;
-    return l >= 12 ? 1 << (l - 11) : 0;
-}
-
-// 0: separate launches; 1: strips behind the plain tiles (they fill the compute units its last
-// round leaves idle, at least 32 of them); 2: strips in front (the plain product runs three or more
-// rounds and the strips, few and long, occupy at most a quarter of the chip beside its first rounds).
-static int sors_pair_order(int64_t blocks_a, int64_t strip_groups) {
-    if ((256 - blocks_a % 256) % 256 >= 32) return 1;
-    if (blocks_a >= 256 && strip_groups <= 64) return 2;
-    return 0;
-}
-
+// ---- SORS kind: the plain product of a pass together with the strips of its sketch product (plan_sors).
 bool sors_pair_available(int64_t n, int64_t d_sk, int64_t d_other, int64_t k) {
-    if (!sors_fast_ok(n, d_sk) || sors_chunks(n) == 0 || k > 2048) return false;
-    const PairPlain plain = pair_plain(n, d_other);
-    // 128 x 128 tiles: one round of them, long enough for the strips to finish beside it
-    if (plain.cfg != GEMM_LARGE && (plain.tiles < 65 || plain.tiles > 256 || d_sk < 768)) return false;
-    return sors_pair_order(plain.tiles, (d_sk / 8 + 1) / 2) != 0;
+    return sors_fast_ok(n, d_sk) && plan_sors(n, d_sk, d_other, k).order != SORS_APART;
+}
+
+bool sors_pair_reported(int64_t n, int64_t d_sk, int64_t d_other, int64_t k) {
+    return sors_fast_ok(n, d_sk) && sors_among_rounds(n, d_sk, d_other, k) != SORS_APART;
 }
 
 static hipError_t launch_pass_sors(const GemmArgs &ga, bool row_indexed_b, const SorsArgs &gs, hipStream_t stream, hipEvent_t ev_begin,
                                    hipEvent_t ev_end) {
-    const PairPlain plain = pair_plain(ga.M, ga.N);
+    const SorsPlan plan = plan_sors(gs.n, gs.d, ga.N, gs.k);
     EventPair pev(ev_begin, ev_end, stream);
-    return launch_pair_sors(plain, row_indexed_b, ga, gs, sors_chunks(gs.n), sors_pair_order(plain.tiles, (gs.d / 8 + 1) / 2) == 2, stream);
+    return launch_pair_sors(plan, row_indexed_b, ga, gs, stream);
 }
 
 hipError_t launch_forward_pair_sors_bf16(const bf16_t *X, const bf16_t *W, const bf16_t *bias, bf16_t *Y, bf16_t *X_proj,

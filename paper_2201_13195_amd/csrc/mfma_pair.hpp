@@ -27,11 +27,10 @@ RMM_PAIR_DECL(nn_mid);
 RMM_PAIR_DECL(nn_compact);
 
 // The same for the SORS sketch kind (mfma_pair_sors.hip): `gs` describes the sketch product, whose
-// strips go two to a work-group; row_indexed_b says whether the plain product is dX = dY W (true) or Y = X W^T (false);
-// `chunks` chunks of 2048 tokens; sors_first puts the strips' work-groups at the front of the grid instead of the back.
+// strips stand in the grid as plan.order says (not SORS_APART); row_indexed_b says whether the plain product is dX = dY W (true) or
+// Y = X W^T (false).
 struct SorsArgs;
-hipError_t launch_pair_sors(const PairPlain &plain, bool row_indexed_b, const GemmArgs &ga, const SorsArgs &gs, int chunks,
-                            bool sors_first, hipStream_t stream);
+hipError_t launch_pair_sors(const SorsPlan &plan, bool row_indexed_b, const GemmArgs &ga, const SorsArgs &gs, hipStream_t stream);
 
 // Shared bodies of launch_pair_{nt,nn}_*.
 template <typename SA, int BMODE_A, typename SB>

@@ -1,7 +1,5 @@
 // Paired-launch kernels for the SORS sketch kind: the tiles of a plain product (Y = X W^T or
-// dX = dY W) and the strips of the sketch product of the same pass in one grid, for shapes whose
-// plain product leaves compute units idle (see mfma_pair.hpp for the idea; the sketch half is the
-// two-strip form of sors_strip_body).
+// dX = dY W) and the strips of the sketch product of the same pass in one grid (plan_sors says which and where).
 #include "mfma_pair.hpp"
 #include "sors_kernels.hpp"
 
@@ -32,6 +30,36 @@ __global__ void __launch_bounds__(SA::THREADS) gemm_sors_pair_kernel(GemmArgs ga
                                                 sors_first ? (int64_t)blockIdx.x : (int64_t)blockIdx.x - blocks_a, strips);
 }
 
+// Tiles of 128 x 128 in half of a compute unit's LDS and registers, strips in the other half or in what the tiles leave.  What bounds a tile
+// is the way of its operands into LDS, what bounds a strip vector additions and LDS passes between barriers: beside each other either
+// waits less.  The tiles come first: they are the longer ones, and the strips fill the places behind them.
+// The strips as the strip kernel has them alone: LC = 10 and 11 all tokens at once, ACC chunks of 2048 with accumulators.
+template <int BMODE_A, int LC, bool ACC, bool SUMS>
+__global__ void __launch_bounds__(512, 4) gemm_sors_compact_kernel(GemmArgs ga, SorsArgs gs, int tiles, int chunks) {
+    constexpr int BYTES_A = ShapeCompact::LDS_BYTES, PLANE_BYTES = StripShape<LC>::REGION * 16, BYTES_S = PLANE_BYTES + 1024 * 4;
+    static_assert(ShapeCompact::THREADS == 512 && BYTES_A <= 80 * 1024 && BYTES_S <= 80 * 1024, "two work-groups on a compute unit");
+    __shared__ __attribute__((aligned(1024))) unsigned char lds[BYTES_A > BYTES_S ? BYTES_A : BYTES_S];
+    const int block = (int)blockIdx.x;
+    if (block < tiles)
+        gemm_tile<ShapeCompact, A_KCONTIG, BMODE_A, OUT_BF16>(ga, reinterpret_cast<bf16_t *>(lds), block, tiles);
+    else
+        sors_strip_body<LC, ACC, 1, 8, SUMS>(gs, chunks, reinterpret_cast<float4 *>(lds), reinterpret_cast<uint32_t *>(lds + PLANE_BYTES), block - tiles,
+                                             (int)gridDim.x - tiles);
+}
+
+template <int BMODE_A, int LC, bool ACC>
+hipError_t launch_compact(const GemmArgs &ga, const SorsArgs &gs, int tiles, hipStream_t stream) {
+    const unsigned grid = (unsigned)(tiles + gs.d / 8);
+    const int chunks = sors_chunks(gs.n);
+    if constexpr (BMODE_A == B_NCONTIG)
+        if (gs.colsum != nullptr) {
+            gemm_sors_compact_kernel<BMODE_A, LC, ACC, true><<<grid, 512, 0, stream>>>(ga, gs, tiles, chunks);
+            return hipGetLastError();
+        }
+    gemm_sors_compact_kernel<BMODE_A, LC, ACC, false><<<grid, 512, 0, stream>>>(ga, gs, tiles, chunks);
+    return hipGetLastError();
+}
+
 template <typename SA, int BMODE_A>
 hipError_t launch_impl(const GemmArgs &ga, const SorsArgs &gs, int blocks_a, int chunks, int sors_first, hipStream_t stream) {
     const unsigned strips2 = (unsigned)((gs.d / 8 + 1) / 2);
@@ -47,9 +75,19 @@ hipError_t launch_impl(const GemmArgs &ga, const SorsArgs &gs, int blocks_a, int
 
 }  // namespace
 
-hipError_t launch_pair_sors(const PairPlain &plain, bool row_indexed_b, const GemmArgs &ga, const SorsArgs &gs, int chunks,
-                            bool sors_first, hipStream_t stream) {
-    const int first = sors_first ? 1 : 0;
+hipError_t launch_pair_sors(const SorsPlan &plan, bool row_indexed_b, const GemmArgs &ga, const SorsArgs &gs, hipStream_t stream) {
+    const PairPlain &plain = plan.plain;
+    if (plan.order == SORS_COMPACT) {
+        const int l = sors_log(gs.n);
+        if (row_indexed_b)
+            return l == 10   ? launch_compact<B_NCONTIG, 10, false>(ga, gs, plain.tiles, stream)
+                   : l == 11 ? launch_compact<B_NCONTIG, 11, false>(ga, gs, plain.tiles, stream)
+                             : launch_compact<B_NCONTIG, 11, true>(ga, gs, plain.tiles, stream);
+        return l == 10   ? launch_compact<B_KCONTIG, 10, false>(ga, gs, plain.tiles, stream)
+               : l == 11 ? launch_compact<B_KCONTIG, 11, false>(ga, gs, plain.tiles, stream)
+                         : launch_compact<B_KCONTIG, 11, true>(ga, gs, plain.tiles, stream);
+    }
+    const int first = plan.order == SORS_FRONT ? 1 : 0, chunks = sors_chunks(gs.n);
 #define RMM_SORS_CASE(CFG, SHAPE)                                                                     \
     case CFG:                                                                                         \
         return row_indexed_b ? launch_impl<SHAPE, B_NCONTIG>(ga, gs, plain.tiles, chunks, first, stream) \

@@ -53,9 +53,8 @@ template <int LC>
 struct StripShape {
     static constexpr int CH = 1 << LC, SLOTS = strip_phys(CH);
     static constexpr int PLANE = SLOTS + 4, REGION = 2 * PLANE + 2;  // float4 slots of half a strip and of a strip
-    static_assert(LC >= 9 && LC <= 12, "chunks of 512 .. 4096 tokens");
+    static_assert(LC >= 10 && LC <= 12, "chunks of 1024 .. 4096 tokens");
 };
-constexpr int64_t kSorsAccMaxK = 2048;  // sketch columns with accumulators
 
 // Rows t, t + LPW, .. of a strip, 16 bytes from `off` on in each lane.  Buffer loads: a row beyond the tokens lies outside the
 // descriptor's range (one for each load) and reads as zero, so there is no branch between the loads and the compiler can count
@@ -143,8 +142,8 @@ struct StripSums {
 //
 // NPROB = 2 puts two neighbouring strips into one work-group of 512 threads (thread 2r + p is
 // thread r of strip p; separate LDS planes, offset by 64 bytes modulo 128 so that the interleaved
-// lanes of the two strips stay on different banks): the form that shares a grid with the 512-thread
-// work-groups of a plain product.  `block` of `blocks` numbers the work-group among those of the
+// lanes of the two strips stay on different banks): a form that shares a grid with the 512-thread
+// work-groups of a plain product (one strip of 512 threads is the other, which shares compute units with them).  `block` of `blocks` numbers the work-group among those of the
 // sketch product; LDS: NPROB * StripShape::REGION float4 slots and 1024 words.
 template <int LC, bool ACC, int NPROB, int WAVES, bool SUMS>
 __device__ __forceinline__ void sors_strip_body(const SorsArgs &g, int chunks, float4 *planes_all, uint32_t *sign_words,

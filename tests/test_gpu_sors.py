@@ -204,3 +204,31 @@ def test_bias_gradient_has_the_same_bits_in_every_form_of_the_pass(n, d_in, d_ou
                   binding.STAGE_BWD_G_PRODUCT, binding.STAGE_BWD_PAIR):
         dX1, dW1, db1 = rmm.rmm_backward(dYd, Wd, Xp, SORS, 3, 4, need_dbias=True, profile=(stage, a, b))
         assert torch.equal(dX, dX1) and torch.equal(dW, dW1) and torch.equal(db, db1), stage
+
+
+# Strips that share compute units with 128 x 128 tiles, forward and backward: fewer tokens than a tile, transforms of 1024 and 2048, one
+# chunk with more sketch columns than accumulators, several chunks, ragged edges, and where 256 x 256 tiles would be 160 or more.
+COMPACT = [(8, 264, 264, 3), (300, 264, 264, 40), (500, 272, 304, 70), (1025, 264, 392, 100), (2000, 264, 392, 2100),
+           (2275, 312, 584, 455), (4250, 1232, 864, 425), (10681, 1216, 840, 1068)]
+
+
+@pytest.mark.parametrize("shape", COMPACT)
+def test_strips_beside_tiles_on_a_compute_unit(shape):
+    """Against the oracle, and bit for bit against launches of their own; Y also against that beside a dense sketch."""
+    n, d_in, d_out, k = shape
+    X, W, dY = synth.layer_inputs(n, d_in, d_out, "bf16", (n, d_in + 1, d_out + 2), w_std=1.0 / math.sqrt(d_in))
+    bias = synth.to_torch(synth.normal((d_out,), 17), "bf16")
+    check_layer(X, W, dY, k, SORS, 0x5EED0091, 15, "bf16", bias=bias, label="compact %s" % (shape,))
+    Xd, Wd, dYd = (t.to(DEV) for t in (X, W, dY))
+    a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    a.record(); b.record()
+    torch.cuda.synchronize()
+    Y0, Xp0 = rmm.rmm_forward(Xd, Wd, None, k, SORS, 9, 1)
+    Y1, Xp1 = rmm.rmm_forward(Xd, Wd, None, k, SORS, 9, 1, profile=(binding.STAGE_FWD_Y, a, b))
+    assert torch.equal(Y0, Y1) and torch.equal(Xp0, Xp1)
+    for need_dbias in (False, True):
+        one = rmm.rmm_backward(dYd, Wd, Xp0, SORS, 9, 1, need_dbias=need_dbias)
+        two = rmm.rmm_backward(dYd, Wd, Xp0, SORS, 9, 1, need_dbias=need_dbias, profile=(binding.STAGE_BWD_DX, a, b))
+        assert all(x is None and y is None or torch.equal(x, y) for x, y in zip(one, two)), need_dbias
+    if k > 64:
+        assert torch.equal(Y0, rmm.rmm_forward(Xd, Wd, None, k, rmm.RADEMACHER, 9, 1)[0])

@@ -14,6 +14,7 @@ import test_gpu_large_tiles
 import test_gpu_pair_plans
 import test_gpu_plain_tiles
 import test_gpu_sketch_slices
+import test_gpu_sors
 import test_gpu_variance
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -43,6 +44,7 @@ int pass_plan(int64_t n, int64_t d_sk, int64_t d_other, int64_t k, int kind, int
     return p.plain.cfg;
 }
 int f32_tile(int64_t n, int64_t d_in, int64_t d_out, int64_t k, int64_t kind) { return plain_backward_cfg_f32(n, d_in, d_out, k, (int)kind); }
+int sors_order(int64_t n, int64_t d_sk, int64_t d_other, int64_t k) { return plan_sors(n, d_sk, d_other, k).order; }
 int dx_tile(int cfg, int64_t kk) { return dx_cfg(cfg, kk); }
 void backward_plan(int64_t n, int64_t d_in, int64_t d_out, int64_t k, int kind, int with_dbias, int64_t *o) {
     put(plan_backward(n, d_in, d_out, k, kind, with_dbias != 0).sketch, o);
@@ -247,3 +249,17 @@ def test_products_a_little_over_two_rounds_take_the_largest_tiles(plans):
         assert plans.plain(*shape) != "256x256", shape
     assert plans.variance(920, 3272, 2776) == plans.variance(384, 3040, 2576) == "256x256"         # 572, and 504 with 48 of the row norms
     assert plans.variance(400, 1872, 3880) != "256x256" and plans.variance(4096, 768, 3072) == "128x128 split"
+
+
+def test_strips_share_compute_units_where_their_tests_expect_it(plans):
+    """... and do not where 256 x 256 tiles fill the chip, or few tiles have a long contraction."""
+    def order(*a):
+        return ("apart", "behind", "front", "compact")[plans.lib.sors_order(*map(ctypes.c_int64, a))]
+
+    for n, d_in, d_out, k in test_gpu_sors.COMPACT:
+        assert order(n, d_out, d_in, k) == "compact" and (n > 10000 or order(n, d_in, d_out, k) == "compact"), (n, d_in, d_out, k)
+    assert order(16384, 1024, 4096, 1638) == "front" and order(15053, 2264, 3112, 753) == order(16384, 4096, 1024, 1638) == "apart"
+    assert order(4096, 768, 3072, 410) == "behind"
+    assert order(3277, 3480, 272, 1639) != "compact"
+    for n, k in ((2049, 2049), (40000, 100)):                   # more sketch columns than accumulators, more tokens than the strips take
+        assert order(n, 264, 392, k) != "compact"
