@@ -140,12 +140,13 @@ struct PlainLoader {
     uint32_t off[CHUNKS];
     const T *p[MODE == 0 ? CHUNKS : 1];
     const T *base;
-    int64_t ld, rows_left;
+    int64_t ld;
+    int rows_left;  // (dimensions are below 2^31)
     uint32_t skew = 0;  // bytes between the base and the first element
     int clamp[MODE == 0 ? CHUNKS : 1];
 
     __device__ __forceinline__ void init(const T *operand, int64_t ld_, int64_t row0, int64_t rows, int tid) {
-        ld = ld_, rows_left = rows - row0;
+        ld = ld_, rows_left = (int)(rows - row0);
         base = operand + (MODE == 0 ? 0 : row0 * (KROWS ? ld : 1));
         if constexpr (ES == 2 && MODE == 3) {  // descriptors start on a dword
             skew = (uint32_t)(reinterpret_cast<uintptr_t>(base) & 2u);
@@ -161,12 +162,13 @@ struct PlainLoader {
                 p[q] = operand + (KROWS ? min(row0 + r, rows - 1) * ld + k : k * ld + min(row0 + r, rows - 1));
                 clamp[q] = KROWS ? 7 : (int)max((int64_t)0, min((int64_t)7, rows - 1 - row0 - r));  // last element of the chunk that exists
             } else {
-                off[q] = row0 + r < rows ? (uint32_t)((KROWS ? r * ld + k : k * ld + r) * ES) + skew : 0x80000000u;
+                const uint32_t w = (uint32_t)ld;
+                off[q] = r < rows_left ? (KROWS ? (uint32_t)r * w + (uint32_t)k : (uint32_t)k * w + (uint32_t)r) * ES + skew : 0x80000000u;
             }
         }
     }
     // Requests the next tile; `left` = contraction elements that remain (may be <= 0).
-    __device__ __forceinline__ void load(Regs &g, int64_t left) {
+    __device__ __forceinline__ void load(Regs &g, int left) {
         if constexpr (MODE == 0) {
 #pragma unroll
             for (int q = 0; q < CHUNKS; ++q) {
@@ -179,11 +181,11 @@ struct PlainLoader {
                 p[q] += KROWS ? BK : BK * ld;
             }
         } else {
-            const int l = (int)(left < 0 ? 0 : left < BK ? left : BK);
-            const int64_t bytes = tile_range_bytes<ES, KROWS>(rows_left, ROWS, ld, l, skew / ES);
+            const int l = max(0, min(left, BK));
+            const uint32_t bytes = tile_range_bytes<ES, KROWS, uint32_t>((uint32_t)rows_left, ROWS, (uint32_t)ld, (uint32_t)l, skew / ES);
             const __amdgpu_buffer_rsrc_t rsrc =
                 __builtin_amdgcn_make_buffer_rsrc(const_cast<T *>(base), (short)0,
-                                                  __builtin_amdgcn_readfirstlane((int)min(bytes, (int64_t)0x7FFFFFFC)), 0x00020000);
+                                                  __builtin_amdgcn_readfirstlane((int)min(bytes, 0x7FFFFFFCu)), 0x00020000);
 #pragma unroll
             for (int q = 0; q < CHUNKS; ++q) {
 #pragma unroll
@@ -199,11 +201,11 @@ struct PlainLoader {
             base += KROWS ? BK : BK * ld;
         }
     }
-    __device__ __forceinline__ void store(const Regs &g, bf16_t *tile, int64_t left) const {
+    __device__ __forceinline__ void store(const Regs &g, bf16_t *tile, int left) const {
 #pragma unroll
         for (int q = 0; q < CHUNKS; ++q) {
             // (a select at the load would make every request wait for its data)
-            const int valid = (int)max((int64_t)0, min((int64_t)8, KROWS ? left - kk[q] : (kk[q] < left ? (int64_t)8 : (int64_t)0)));
+            const int valid = KROWS ? left - kk[q] : kk[q] < left ? 8 : 0;
             if constexpr (ES == 2 && MODE == 4) {  // (chunks lie wholly inside the operand or read as zeros)
                 *reinterpret_cast<u32x4_t *>(tile + at[q]) = (u32x4_t){g.v[q][0], g.v[q][1], g.v[q][2], g.v[q][3]};
             } else if constexpr (ES == 2) {
@@ -357,17 +359,21 @@ __device__ __forceinline__ void plain_tile(const PlainArgs &g, bf16_t *lds, int6
     if constexpr (!GEN) la.init(reinterpret_cast<const T *>(g.A), g.lda, m0, g.M, tid);
     lb.init(reinterpret_cast<const T *>(g.B) + (SLICED ? k_begin * g.ldb : 0), g.ldb, n0, g.N, tid);
 
-    int64_t asked = 0;  // contraction elements requested so far
+    // (32 bits, as the tiles' ranges: uniform comparisons and products of 64 take vector instructions, some 30 in the way of every request
+    // and every split.  Steps of fp32 and odd-width layers are 1 to 8 % shorter: 3000 x 768 -> 1001
+    // bf16, k = 300, 64.3 -> 61.3 us, 569 x 538 -> 985 fp32, k = 57, 51.9 -> 49.1; 20 random fp32 steps 5.3 %.)
+    uint32_t asked = 0;  // contraction elements requested so far
+    auto left_of = [&](uint32_t from) { return (int)((uint32_t)len - from); };  // (dimensions are below 2^31)
     auto issue = [&](int set) {
-        if constexpr (!GEN) la.load(va[set], len - asked);
-        lb.load(vb[set], len - asked);
+        if constexpr (!GEN) la.load(va[set], left_of(asked));
+        lb.load(vb[set], left_of(asked));
         asked += BK;
     };
     // Writes tile t (in register set `set`) into LDS stage `set`.  A generated tile is made here: one
     // chunk of eight tokens of a sketch column per thread, the waves taking turns where the tile has
     // fewer chunks than the work-group threads, so that some generate while the others multiply.
     // Entries beyond the operand meet zeros of B or are not stored.
-    auto put = [&](int set, int64_t t) {
+    auto put = [&](int set, uint32_t t) {
         bf16_t *As = lds + set * L::STAGE, *Bs = As + PA * L::A_PLANE;
         if constexpr (GEN) {
             constexpr int CALLS = BM * BK / 8, TURNS = kPlainThreads / CALLS;
@@ -388,9 +394,9 @@ __device__ __forceinline__ void plain_tile(const PlainArgs &g, bf16_t *lds, int6
                 }
             }
         } else {
-            la.store(va[set], As, len - t * BK);
+            la.store(va[set], As, left_of(t * BK));
         }
-        lb.store(vb[set], Bs, len - t * BK);
+        lb.store(vb[set], Bs, left_of(t * BK));
     };
     constexpr int STEPS = BK / 16 / S::WK;  // 16-deep contraction steps per tile and wave
     struct Frags {
@@ -435,7 +441,7 @@ __device__ __forceinline__ void plain_tile(const PlainArgs &g, bf16_t *lds, int6
 
     // Two LDS stages, two register sets: while tile t is multiplied, t+1 goes from registers to LDS and
     // t+3 is requested (past the end: zeros).
-    const int64_t num = (len + BK - 1) / BK;
+    const uint32_t num = ((uint32_t)len + BK - 1) / BK;
     // Short chains of fp32 tiles: those past the end are not split (256 x 128 -> 128: 18.6 -> 16 us a step).  Elsewhere the
     // branch costs more (Y 4096 x 768 -> 3072: 162 -> 175 us).
     constexpr bool SKIP = PB == 3 && S::WK == 8;
@@ -444,7 +450,7 @@ __device__ __forceinline__ void plain_tile(const PlainArgs &g, bf16_t *lds, int6
     put(0, 0);
     issue(0);
     __syncthreads();
-    for (int64_t t = 0; t < num; t += 2) {
+    for (uint32_t t = 0; t < num; t += 2) {
 #pragma unroll
         for (int s = 0; s < 2; ++s) {
             if (SKIP && s == 1 && t + 1 >= num) break;

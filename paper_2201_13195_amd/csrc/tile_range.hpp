@@ -18,12 +18,14 @@ namespace rmm {
 //   skew       elements between the base, which is on a dword, and the first element (0 or 1, bf16 only)
 // The descriptor's range ends inside the operand's last dword, whose other half, if any, lies on the same
 // page: nothing beyond it is ever touched, wherever the operand ends.
-template <int ES, bool KROWS>
-RMM_RANGE_FN int64_t tile_range_bytes(int64_t rows_left, int64_t tile_rows, int64_t ld, int64_t left, int64_t skew) {
+// `I`: 32 bits hold the range of a tile of 128 rows of fewer than 2^22 elements (2^31 bytes, with no sign); on the device they are a
+// few scalar instructions where 64 are compared in vector ones.
+template <int ES, bool KROWS, typename I>
+RMM_RANGE_FN I tile_range_bytes(I rows_left, I tile_rows, I ld, I left, I skew) {
     if (left <= 0) return 0;
-    const int64_t rows = rows_left < tile_rows ? rows_left : tile_rows;
-    const int64_t elems = KROWS ? (rows - 1) * ld + left : (left - 1) * ld + rows_left;
-    return (((elems + skew) * ES) + 3) & ~(int64_t)3;
+    const I rows = rows_left < tile_rows ? rows_left : tile_rows;
+    const I elems = KROWS ? (rows - 1) * ld + left : (left - 1) * ld + rows_left;
+    return (((elems + skew) * ES) + 3) & ~(I)3;
 }
 
 }  // namespace rmm
