@@ -31,9 +31,13 @@ constexpr int TPAD = 32;  // elements of padding per row of a transposed-read LD
 // Operand fragment of the 32x32x16 MFMA from a K-contiguous LDS tile (rows of BK elements,
 // chunks placed by kchunk_pos): lane l holds row (l % 32), contraction elements 8*(l / 32) .. +7.
 template <int BK>
-__device__ __forceinline__ bf16x8_t frag_kcontig(const bf16_t *tile, int row0, int kk0, int lane) {
+__device__ __forceinline__ int kcontig_offset(int row0, int kk0, int lane) {  // elements
     const int row = row0 + (lane & 31), chunk = (kk0 >> 3) + (lane >> 5);
-    return *reinterpret_cast<const bf16x8_t *>(tile + row * BK + kchunk_pos<BK>(row, chunk) * 8);
+    return row * BK + kchunk_pos<BK>(row, chunk) * 8;
+}
+template <int BK>
+__device__ __forceinline__ bf16x8_t frag_kcontig(const bf16_t *tile, int row0, int kk0, int lane) {
+    return *reinterpret_cast<const bf16x8_t *>(tile + kcontig_offset<BK>(row0, kk0, lane));
 }
 
 // Same fragment from a tile stored [contraction row][column]: two transposing
@@ -41,18 +45,24 @@ __device__ __forceinline__ bf16x8_t frag_kcontig(const bf16_t *tile, int row0, i
 // 4*(i % 4) .. +3 of a 4 x 16 patch; the load returns to lane L the four rows of
 // column L.  Block b of the wave covers columns 16*(b % 2) .. +15 and
 // contraction rows 8*(b / 2) .. +7 (in two patches of four rows).
-__device__ __forceinline__ bf16x8_t frag_transposed(const bf16_t *tile, int stride, int col0, int kk0, int lane) {
+typedef __attribute__((address_space(3))) s16x4_t *lds_patch_t;
+__device__ __forceinline__ int transposed_offset(int stride, int col0, int kk0, int lane) {  // elements
     const int blk = lane >> 4, i = lane & 15;
-    const bf16_t *p = tile + (kk0 + ((blk >> 1) << 3) + (i >> 2)) * stride + col0 + ((blk & 1) << 4) + ((i & 3) << 2);
-    typedef __attribute__((address_space(3))) s16x4_t *lds_ptr_t;
-    const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr_t)(p));
-    const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr_t)(p + 4 * stride));
+    return (kk0 + ((blk >> 1) << 3) + (i >> 2)) * stride + col0 + ((blk & 1) << 4) + ((i & 3) << 2);
+}
+__device__ __forceinline__ bf16x8_t frag_transposed(lds_patch_t rows, lds_patch_t next_four) {
+    const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(rows);
+    const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(next_four);
     union {
         s16x8_t s;
         bf16x8_t v;
     } out;
     out.s = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
     return out.v;
+}
+__device__ __forceinline__ bf16x8_t frag_transposed(const bf16_t *tile, int stride, int col0, int kk0, int lane) {
+    const bf16_t *p = tile + transposed_offset(stride, col0, kk0, lane);
+    return frag_transposed((lds_patch_t)(p), (lds_patch_t)(p + 4 * stride));
 }
 
 }  // namespace

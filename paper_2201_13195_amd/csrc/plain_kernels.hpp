@@ -73,6 +73,20 @@ typedef PlainShape<64, 64, 64, 2, 2, 2> PlainMid;      // four times as many til
 typedef PlainShape<32, 32, 128, 1, 1, 8> PlainTiny;    // few tiles: short chains, each wave an eighth of the contraction
 typedef PlainShape<32, 128, 64, 1, 4, 2> PlainSketch;  // sketch products: an entry is generated once per 128 columns
 
+// LDS by byte address: one register an operand, stage and 16-deep step, everything else in the offsets of the instructions.  (The
+// compiler keeps an address for every fragment otherwise, some thirty, and spills sums for them: `opaque` keeps it from it.)
+template <typename V>
+__device__ __forceinline__ __attribute__((address_space(3))) V *lds_at(uint32_t byte) {
+    return (__attribute__((address_space(3))) V *)(uintptr_t)byte;
+}
+__device__ __forceinline__ uint32_t lds_byte(void *p) {
+    return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)p;
+}
+__device__ __forceinline__ uint32_t opaque(uint32_t x) {
+    asm("" : "+v"(x));
+    return x;
+}
+
 // How an operand is loaded: 4 = 16-byte buffer loads (every row on 16 bytes; bf16: a whole number of them); 3 = the same for
 // rows that start anywhere; both with 32-bit offsets inside a tile (rows below 2^22 elements).
 // 0 = element loads from 64-bit addresses, for longer rows.  Of bf16 operands in one product one may be 4 and the other 3.
@@ -92,30 +106,51 @@ struct PlainTile {
     static constexpr int LDS_BYTES = 2 * STAGE * 2 > RED_BYTES ? 2 * STAGE * 2 : RED_BYTES;
 };
 
-// Eight fp32 values as three bf16 vectors whose sum they are.  (An infinity, or a number that rounds to one
+// Eight fp32 values as three bf16 vectors whose sum they are, a pair at a time.  (An infinity, or a number that rounds to one
 // in bf16: infinity, NaN, NaN.)
-__device__ __forceinline__ void split_eight(const float (&x)[8], bf16x8_t (&out)[3]) {
-    float r[8];
+struct Planes {
+    union {
+        bf16x8_t v;
+        bf16x2_t h[4];
+        uint32_t w[4];
+    } p[3];
+    __device__ __forceinline__ void split(int q, float x, float y) {
 #pragma unroll
-    for (int u = 0; u < 8; ++u) r[u] = x[u];
-#pragma unroll
-    for (int p = 0; p < 3; ++p) {
-        union {
-            bf16x8_t v;
-            bf16x2_t h[4];
-            uint32_t w[4];
-        } o;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            o.h[q] = __builtin_convertvector((f32x2_t){r[2 * q], r[2 * q + 1]}, bf16x2_t);  // nearest even
-            if (p < 2) {
-                r[2 * q] -= __uint_as_float(o.w[q] << 16);
-                r[2 * q + 1] -= __uint_as_float(o.w[q] & 0xFFFF0000u);
+        for (int s = 0; s < 3; ++s) {
+            p[s].h[q] = __builtin_convertvector((f32x2_t){x, y}, bf16x2_t);  // nearest even
+            if (s < 2) {
+                x -= __uint_as_float(p[s].w[q] << 16);
+                y -= __uint_as_float(p[s].w[q] & 0xFFFF0000u);
             }
         }
-        out[p] = o.v;
     }
-}
+};
+// The pairs of planes that a product of operands of PA and PB planes is made of, smallest products first.
+template <int PA, int PB>
+struct PlaneProducts {
+    int a[9] = {}, b[9] = {};
+    static constexpr int COUNT = PA * PB - (PA + PB == 6);
+    constexpr PlaneProducts() {
+        int i = 0;
+        for (int order = PA + PB - 2; order >= 0; --order)
+            for (int s = 0; s < PA; ++s)
+                if (order - s >= 0 && order - s < PB && order <= 3) a[i] = s, b[i] = order - s, ++i;
+    }
+};
+// The fragments of a step in the order in which its products leave them: those that are done with first can be
+// overwritten by the next step's first.
+template <int PA, int PB, int TM, int TN>
+struct FragmentOrder {
+    bool of_a[PA * TM + PB * TN] = {};
+    int plane[PA * TM + PB * TN] = {}, tile[PA * TM + PB * TN] = {};
+    constexpr FragmentOrder() {
+        int i = 0;
+        for (int p = PA > PB ? PA - 1 : PB - 1; p >= 0; --p) {
+            for (int u = 0; p < PB && u < TN; ++u) plane[i] = p, tile[i] = u, ++i;
+            for (int u = 0; p < PA && u < TM; ++u) of_a[i] = true, plane[i] = p, tile[i] = u, ++i;
+        }
+    }
+};
 constexpr float kSplitUp = 0x1p24f, kSplitDown = 0x1p-24f;
 
 // One operand tile (ROWS rows or columns of the product x BK contraction elements) on its way from
@@ -136,7 +171,8 @@ struct PlainLoader {
     struct Regs {
         uint32_t v[CHUNKS][WORDS];
     };
-    int kk[CHUNKS], at[CHUNKS];
+    int kk[CHUNKS];
+    uint32_t to[2][CHUNKS];  // of each LDS stage
     uint32_t off[CHUNKS];
     const T *p[MODE == 0 ? CHUNKS : 1];
     const T *base;
@@ -145,7 +181,7 @@ struct PlainLoader {
     uint32_t skew = 0;  // bytes between the base and the first element
     int clamp[MODE == 0 ? CHUNKS : 1];
 
-    __device__ __forceinline__ void init(const T *operand, int64_t ld_, int64_t row0, int64_t rows, int tid) {
+    __device__ __forceinline__ void init(const T *operand, int64_t ld_, int64_t row0, int64_t rows, int tid, uint32_t lds, uint32_t stage_bytes) {
         ld = ld_, rows_left = (int)(rows - row0);
         base = operand + (MODE == 0 ? 0 : row0 * (KROWS ? ld : 1));
         if constexpr (ES == 2 && MODE == 3) {  // descriptors start on a dword
@@ -157,7 +193,8 @@ struct PlainLoader {
             const int c = tid + kPlainThreads * q;
             const int r = KROWS ? c / (BK / 8) : c % (ROWS / 8) * 8, k = KROWS ? c % (BK / 8) * 8 : c / (ROWS / 8);
             kk[q] = k;
-            at[q] = KROWS ? r * STRIDE + kchunk_pos<BK>(r, k / 8) * 8 : k * STRIDE + r;
+            const uint32_t at = 2 * (KROWS ? r * STRIDE + kchunk_pos<BK>(r, k / 8) * 8 : k * STRIDE + r);
+            to[0][q] = opaque(lds + at), to[1][q] = opaque(lds + stage_bytes + at);
             if constexpr (MODE == 0) {
                 p[q] = operand + (KROWS ? min(row0 + r, rows - 1) * ld + k : k * ld + min(row0 + r, rows - 1));
                 clamp[q] = KROWS ? 7 : (int)max((int64_t)0, min((int64_t)7, rows - 1 - row0 - r));  // last element of the chunk that exists
@@ -201,43 +238,42 @@ struct PlainLoader {
             base += KROWS ? BK : BK * ld;
         }
     }
-    __device__ __forceinline__ void store(const Regs &g, bf16_t *tile, int left) const {
+    // The way of a request's elements into LDS, in UNITS pieces that the caller deals between its MFMAs (fp32: a pair of elements
+    // split, or the chunk's planes written).
+    static constexpr int UNITS = CHUNKS * (ES == 4 ? 5 : 1);
+    Planes planes;
+    __device__ __forceinline__ void store(int unit, const Regs &g, int set, int left) {
+        const int q = unit / (UNITS / CHUNKS), u = unit % (UNITS / CHUNKS);
+        // (a select at the load would make every request wait for its data)
+        const int valid = KROWS ? left - kk[q] : kk[q] < left ? 8 : 0;
+        if constexpr (ES == 4) {
+            if (u == 4) {
 #pragma unroll
-        for (int q = 0; q < CHUNKS; ++q) {
-            // (a select at the load would make every request wait for its data)
-            const int valid = KROWS ? left - kk[q] : kk[q] < left ? 8 : 0;
-            if constexpr (ES == 2 && MODE == 4) {  // (chunks lie wholly inside the operand or read as zeros)
-                *reinterpret_cast<u32x4_t *>(tile + at[q]) = (u32x4_t){g.v[q][0], g.v[q][1], g.v[q][2], g.v[q][3]};
-            } else if constexpr (ES == 2) {
-                uint32_t w[4];
-                if constexpr (MODE == 0) {
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) w[u] = g.v[q][2 * u] | g.v[q][2 * u + 1] << 16;
-                } else {
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) w[u] = __builtin_amdgcn_alignbit(g.v[q][u + 1], g.v[q][u], (off[q] & 2u) * 8);
-                }
-                if constexpr (KROWS || MODE == 0) {
-#pragma unroll
-                    for (int u = 0; u < 4; ++u)
-                        w[u] = 2 * u + 1 < valid ? w[u] : 2 * u < valid ? w[u] & 0xFFFFu : 0u;
-                } else {  // (the descriptor's last dword may hold the first element behind the last row)
-                    w[0] = valid != 0 ? w[0] : 0u;
-                }
-                *reinterpret_cast<u32x4_t *>(tile + at[q]) = (u32x4_t){w[0], w[1], w[2], w[3]};
-            } else {
-                float x[8];
-#pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    x[u] = __uint_as_float(g.v[q][u]);
-                    if constexpr (MODE == 0 || (MODE == 3 && KROWS)) x[u] = u < valid ? x[u] : 0.0f;
-                    x[u] *= kSplitUp;
-                }
-                bf16x8_t o[3];
-                split_eight(x, o);
-#pragma unroll
-                for (int s = 0; s < 3; ++s) *reinterpret_cast<bf16x8_t *>(tile + s * PLANE + at[q]) = o[s];
+                for (int s = 0; s < 3; ++s) *lds_at<bf16x8_t>(to[set][q] + s * PLANE * 2) = planes.p[s].v;
+                return;
             }
+            float x = __uint_as_float(g.v[q][2 * u]), y = __uint_as_float(g.v[q][2 * u + 1]);
+            if constexpr (MODE == 0 || (MODE == 3 && KROWS)) x = 2 * u < valid ? x : 0.0f, y = 2 * u + 1 < valid ? y : 0.0f;
+            planes.split(u, x * kSplitUp, y * kSplitUp);
+        } else if constexpr (MODE == 4) {  // (chunks lie wholly inside the operand or read as zeros)
+            *lds_at<u32x4_t>(to[set][q]) = (u32x4_t){g.v[q][0], g.v[q][1], g.v[q][2], g.v[q][3]};
+        } else {
+            uint32_t w[4];
+            if constexpr (MODE == 0) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) w[e] = g.v[q][2 * e] | g.v[q][2 * e + 1] << 16;
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) w[e] = __builtin_amdgcn_alignbit(g.v[q][e + 1], g.v[q][e], (off[q] & 2u) * 8);
+            }
+            if constexpr (KROWS || MODE == 0) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    w[e] = 2 * e + 1 < valid ? w[e] : 2 * e < valid ? w[e] & 0xFFFFu : 0u;
+            } else {  // (the descriptor's last dword may hold the first element behind the last row)
+                w[0] = valid != 0 ? w[0] : 0u;
+            }
+            *lds_at<u32x4_t>(to[set][q]) = (u32x4_t){w[0], w[1], w[2], w[3]};
         }
     }
 };
@@ -354,10 +390,12 @@ __device__ __forceinline__ void plain_tile(const PlainArgs &g, bf16_t *lds, int6
     typedef std::conditional_t<GEN, LoadB, PlainLoader<T, GEN ? BN : BM, BK, AMODE == PA_K, MODE_A, L::SA, L::A_PLANE>> LoadA;
     [[maybe_unused]] LoadA la;  // (not used by a generated operand)
     LoadB lb;
+    const uint32_t lds0 = lds_byte(lds);
+    constexpr uint32_t STAGE_BYTES = L::STAGE * 2;
     typename LoadA::Regs va[2];
     typename LoadB::Regs vb[2];
-    if constexpr (!GEN) la.init(reinterpret_cast<const T *>(g.A), g.lda, m0, g.M, tid);
-    lb.init(reinterpret_cast<const T *>(g.B) + (SLICED ? k_begin * g.ldb : 0), g.ldb, n0, g.N, tid);
+    if constexpr (!GEN) la.init(reinterpret_cast<const T *>(g.A), g.lda, m0, g.M, tid, lds0, STAGE_BYTES);
+    lb.init(reinterpret_cast<const T *>(g.B) + (SLICED ? k_begin * g.ldb : 0), g.ldb, n0, g.N, tid, lds0 + PA * L::A_PLANE * 2, STAGE_BYTES);
 
     // (32 bits, as the tiles' ranges: uniform comparisons and products of 64 take vector instructions, some 30 in the way of every request
     // and every split.  Steps of fp32 and odd-width layers are 1 to 8 % shorter: 3000 x 768 -> 1001
@@ -369,104 +407,179 @@ __device__ __forceinline__ void plain_tile(const PlainArgs &g, bf16_t *lds, int6
         lb.load(vb[set], left_of(asked));
         asked += BK;
     };
-    // Writes tile t (in register set `set`) into LDS stage `set`.  A generated tile is made here: one
-    // chunk of eight tokens of a sketch column per thread, the waves taking turns where the tile has
-    // fewer chunks than the work-group threads, so that some generate while the others multiply.
-    // Entries beyond the operand meet zeros of B or are not stored.
-    auto put = [&](int set, uint32_t t) {
-        bf16_t *As = lds + set * L::STAGE, *Bs = As + PA * L::A_PLANE;
-        if constexpr (GEN) {
-            constexpr int CALLS = BM * BK / 8, TURNS = kPlainThreads / CALLS;
-            static_assert(CALLS % 64 == 0 && TURNS * CALLS == kPlainThreads, "whole waves take turns");
-            if (TURNS == 1 || tid / CALLS == (int)(t % TURNS)) {
-                const int c = tid % CALLS, j = c / (BK / 8), kc = c % (BK / 8);
-                const uint32_t tok = (uint32_t)(k_begin + t * BK + kc * 8), col = (uint32_t)(m0 + j);
-                bf16_t *to = As + j * L::SA + kchunk_pos<BK>(j, kc) * 8;
-                if constexpr (AMODE == PA_GAUSS) {
-                    float e[8];
-                    gauss_eight_precise(g.st, tok, col, e);
-                    bf16x8_t o[PA];
-                    split_eight(e, o);
+    // Tile t (in register set `set`) goes into LDS stage `set` in units: those of the loaders; the request of tile t + 2 into the same
+    // registers; then those of a generated tile, which is made here, one chunk of eight tokens of a sketch column per thread (half of the
+    // Philox rounds, or a pair of entries), the waves taking turns where the tile has fewer chunks than the work-group
+    // threads.  AHEAD: a chunk is begun one tile before the one that its wave has to finish it for, so that all waves generate all the
+    // time (4096 x 3072, k = 410 fp32 alone 206 -> 197 us).  Entries beyond the operand meet zeros of B or are not stored.
+    constexpr int CALLS = BM * BK / 8, TURNS = GEN ? kPlainThreads / CALLS : 1;
+    static_assert(!GEN || (CALLS % 64 == 0 && TURNS * CALLS == kPlainThreads && TURNS <= 2), "whole waves take turns, by the stage");
+    constexpr bool AHEAD = AMODE == PA_GAUSS && TURNS == 2 && PB == 3;
+    constexpr int GEN_UNITS = AMODE == PA_GAUSS ? (AHEAD ? 3 : 6) : GEN ? 1 : 0, A_UNITS = GEN ? 0 : LoadA::UNITS, B_UNITS = LoadB::UNITS,
+                  UNITS = B_UNITS + A_UNITS + 1 + GEN_UNITS;
+    const int gen_j = tid % CALLS / (BK / 8), gen_k = tid % CALLS % (BK / 8);
+    uint32_t gen_to[2] = {};
+    if constexpr (GEN) {
 #pragma unroll
-                    for (int s = 0; s < PA; ++s) *reinterpret_cast<bf16x8_t *>(to + s * L::A_PLANE) = o[s];
-                } else {
-                    *reinterpret_cast<bf16x8_t *>(to) = sign_eight(g.kind, g.st, tok, col);
-                }
-            }
-        } else {
-            la.store(va[set], As, left_of(t * BK));
+        for (int s = 0; s < 2; ++s) gen_to[s] = opaque(lds0 + s * STAGE_BYTES + 2 * (gen_j * L::SA + kchunk_pos<BK>(gen_j, gen_k) * 8));
+    }
+    const uint32_t column = (uint32_t)m0 + gen_j;
+    auto token = [&](uint32_t t) { return (uint32_t)k_begin + t * BK + gen_k * 8; };
+    auto turn = [&] {  // (opaque: two copies of everything else would move the sums from one to the other)
+        int x = __builtin_amdgcn_readfirstlane(tid / CALLS);
+        asm("" : "+s"(x));
+        return x;
+    };
+    Words4 words{};
+    [[maybe_unused]] Planes made;
+    auto generate = [&](int part, int set, uint32_t t) __attribute__((always_inline)) {  // part 0 .. 5 of a Gaussian chunk
+        uint32_t(&c)[4] = words.w;
+        if (part == 0) c[0] = token(t) >> 3, c[1] = column, c[2] = g.st.off0, c[3] = g.st.off1;
+        if (part < 2) {
+#pragma unroll
+            for (int r = 5 * part; r < 5 * part + 5; ++r)
+                philox_round(c[0], c[1], c[2], c[3], g.st.key0 + (uint32_t)r * kPhiloxBump0, g.st.key1 + (uint32_t)r * kPhiloxBump1);
+            return;
         }
-        lb.store(vb[set], Bs, left_of(t * BK));
+        float x, y;
+        gauss_pair_precise(c[part - 2], x, y);
+        made.split(part - 2, x, y);
+        if (part == 5) {
+#pragma unroll
+            for (int s = 0; s < PA; ++s) *lds_at<bf16x8_t>(gen_to[set] + s * L::A_PLANE * 2) = made.p[s].v;
+        }
+    };
+    auto put = [&](int unit, int set, uint32_t t) __attribute__((always_inline)) {
+        if (unit < B_UNITS) return lb.store(unit, vb[set], set, left_of(t * BK));
+        unit -= B_UNITS;
+        if constexpr (!GEN) {
+            if (unit < A_UNITS) return la.store(unit, va[set], set, left_of(t * BK));
+        }
+        unit -= A_UNITS;
+        if (unit == 0) return issue(set);
+        unit -= 1;
+        if constexpr (AMODE == PA_SIGN) {
+            if (TURNS == 1 || turn() == set) *lds_at<bf16x8_t>(gen_to[set]) = sign_eight(g.kind, g.st, token(t), column);
+        } else if constexpr (GEN) {
+            if (!AHEAD) {
+                if (TURNS == 1 || turn() == set) generate(unit, set, t);
+            } else if (turn() == set) {
+                generate(unit + 3, set, t);
+            } else {
+                generate(unit, set ^ 1, t + 1);
+            }
+        }
     };
     constexpr int STEPS = BK / 16 / S::WK;  // 16-deep contraction steps per tile and wave
     struct Frags {
         bf16x8_t a[PA][TM], b[PB][TN];
     };
-    auto fetch = [&](Frags &f, int set, int step) {
-        const bf16_t *As = lds + set * L::STAGE, *Bs = As + PA * L::A_PLANE;
-        const int k0 = (kg * STEPS + step) * 16;
+    static_assert(STEPS == 1 || STEPS % 2 == 0, "a tile's last step is in f[1]");
+    constexpr bool DEFER = STEPS > 1;  // a tile's last step is multiplied behind the next barrier
+    Frags f[2];
+    constexpr int FRAGS = PA * TM + PB * TN;
+    constexpr FragmentOrder<PA, PB, TM, TN> order{};
+    // (32 rows further down the chunks of a K-contiguous tile lie in the same places)
+    uint32_t a_at[2][L::A_KROWS ? STEPS : 1], b_at[2][L::B_KROWS ? STEPS : 1];
 #pragma unroll
-        for (int s = 0; s < PA; ++s)
+    for (int s = 0; s < 2; ++s)
 #pragma unroll
-            for (int u = 0; u < TM; ++u) {
-                const int r0 = wm * (BM / S::WM) + u * 32;
-                f.a[s][u] = L::A_KROWS ? frag_kcontig<BK>(As + s * L::A_PLANE, r0, k0, lane)
-                                       : frag_transposed(As + s * L::A_PLANE, L::SA, r0, k0, lane);
-            }
-#pragma unroll
-        for (int s = 0; s < PB; ++s)
-#pragma unroll
-            for (int u = 0; u < TN; ++u) {
-                const int c0 = wn * (BN / S::WN) + u * 32;
-                f.b[s][u] = L::B_KROWS ? frag_kcontig<BK>(Bs + s * L::B_PLANE, c0, k0, lane)
-                                       : frag_transposed(Bs + s * L::B_PLANE, L::SB, c0, k0, lane);
-            }
+        for (int step = 0; step < STEPS; ++step) {
+            const int k0 = (kg * STEPS + step) * 16, r0 = wm * (BM / S::WM), c0 = wn * (BN / S::WN);
+            const uint32_t as = lds0 + s * STAGE_BYTES, bs = as + PA * L::A_PLANE * 2;
+            if (L::A_KROWS || step == 0)
+                a_at[s][step] = opaque(as + 2 * (L::A_KROWS ? kcontig_offset<BK>(r0, k0, lane) : transposed_offset(L::SA, r0, k0, lane)));
+            if (L::B_KROWS || step == 0)
+                b_at[s][step] = opaque(bs + 2 * (L::B_KROWS ? kcontig_offset<BK>(c0, k0, lane) : transposed_offset(L::SB, c0, k0, lane)));
+        }
+    auto columns = [](uint32_t at, int stride) { return frag_transposed(lds_at<s16x4_t>(at), lds_at<s16x4_t>(at + 8 * stride)); };
+    auto fetch = [&](int i, Frags &to, int set, int step) __attribute__((always_inline)) {  // fragment i of a step
+        const int p = order.plane[i], u = order.tile[i];
+        if (order.of_a[i])
+            to.a[p][u] = L::A_KROWS ? *lds_at<bf16x8_t>(a_at[set][L::A_KROWS ? step : 0] + 2 * (p * L::A_PLANE + u * 32 * L::SA))
+                                    : columns(a_at[set][0] + 2 * (p * L::A_PLANE + step * 16 * L::SA + u * 32), L::SA);
+        else
+            to.b[p][u] = L::B_KROWS ? *lds_at<bf16x8_t>(b_at[set][L::B_KROWS ? step : 0] + 2 * (p * L::B_PLANE + u * 32 * L::SB))
+                                    : columns(b_at[set][0] + 2 * (p * L::B_PLANE + step * 16 * L::SB + u * 32), L::SB);
     };
-    auto multiply = [&](const Frags &f, int sum) {  // smallest products first
-#pragma unroll
-        for (int order = PA + PB - 2; order >= 0; --order)
-#pragma unroll
-            for (int s = 0; s < PA; ++s) {
-                const int r = order - s;
-                if (r < 0 || r >= PB || s + r > 3) continue;
-#pragma unroll
-                for (int u = 0; u < TM; ++u)
-#pragma unroll
-                    for (int w = 0; w < TN; ++w) {
-                        f32x16_t &to = order > 0 ? low[PLANES ? u : 0][PLANES ? w : 0] : acc[SUMS == 2 ? sum : 0][u][w];
-                        to = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.a[s][u], f.b[r][w], to, 0, 0, 0);
-                    }
-            }
+    constexpr PlaneProducts<PA, PB> products{};
+    constexpr int MFMAS = PlaneProducts<PA, PB>::COUNT * TM * TN;  // of a step
+    auto multiply = [&](int i, const Frags &x, int sum) __attribute__((always_inline)) {  // MFMA i of a step
+        const int s = products.a[i / (TM * TN)], r = products.b[i / (TM * TN)], u = i % (TM * TN) / TN, w = i % TN;
+        f32x16_t &to = s + r > 0 ? low[PLANES ? u : 0][PLANES ? w : 0] : acc[SUMS == 2 ? sum : 0][u][w];
+        to = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x.a[s][u], x.b[r][w], to, 0, 0, 0);
     };
 
-    // Two LDS stages, two register sets: while tile t is multiplied, t+1 goes from registers to LDS and
-    // t+3 is requested (past the end: zeros).
+    // Two LDS stages, two register sets.  Between two barriers tile t is multiplied, t + 1 goes into LDS and t + 3 is requested (past
+    // the end: zeros).  DEFER: a tile's barrier stands in front of the last step of the tile before it.  By then every wave holds
+    // that step's fragments, so the stage can be written again, and the first fragments of the new tile are read under the last
+    // step's MFMAs.  Where a product is several MFMAs everything else is dealt between them (sched_barrier); in one piece it stands
+    // behind the barrier for all waves at once.  Against fetching behind the barrier, same bits: bf16 3000 x 768 -> 1001,
+    // k = 300, 61 -> 56 us a step, 209 x 424 -> 351 15.8 -> 13.4, 830 x 472 -> 1269 +-1 35.3 -> 30.4; fp32 4096 x 768 -> 3072 dX and G 284 -> 262,
+    // 1906 x 69 -> 135, k = 191, 47.6 -> 44.9.  (What is left of the fp32 tiles' time is issue: a wave of the sketch tile
+    // has an instruction in flight 47 % of the time, and there are two to a SIMD.)
     const uint32_t num = ((uint32_t)len + BK - 1) / BK;
     // Short chains of fp32 tiles: those past the end are not split (256 x 128 -> 128: 18.6 -> 16 us a step).  Elsewhere the
     // branch costs more (Y 4096 x 768 -> 3072: 162 -> 175 us).
     constexpr bool SKIP = PB == 3 && S::WK == 8;
+    // A step's fragments are read under the MFMAs READ_FROM to READ_TO of the step before.
+    constexpr int READ_FROM = MFMAS >= 16 ? 4 : 0, READ_TO = MFMAS >= 16 ? MFMAS - 4 : MFMAS > 4 ? MFMAS - 2 : MFMAS;
+    auto reads = [&](int i) { return i <= READ_FROM ? 0 : i >= READ_TO ? FRAGS : FRAGS * (i - READ_FROM) / (READ_TO - READ_FROM); };
+    auto period = [&](auto first_, auto stage_, auto units_, uint32_t t) __attribute__((always_inline)) {
+        constexpr bool FIRST = decltype(first_)::value;
+        constexpr int s = decltype(stage_)::value, MAKE = decltype(units_)::value;
+        constexpr int TOTAL = (FIRST && DEFER ? STEPS - 1 : STEPS) * MFMAS;
+        constexpr int OVER = PLANES ? TOTAL - TOTAL / 8 : TOTAL;  // (the last ones done a while before the barrier)
+        auto dealt = [](int x) { return x >= OVER ? MAKE : MAKE * x / OVER; };
+        int m = 0;
+        __syncthreads();
+        if constexpr (FIRST || !DEFER) {
+#pragma unroll
+            for (int i = 0; i < FRAGS; ++i) fetch(i, f[0], s, 0);
+        }
+#pragma unroll
+        for (int step = FIRST || !DEFER ? 0 : -1; step + DEFER < STEPS; ++step)
+#pragma unroll
+            for (int i = 0; i < MFMAS; ++i, ++m) {
+                multiply(i, f[step & 1], step & 1);
+                if constexpr (DEFER) {
+#pragma unroll
+                    for (int r = reads(i); r < reads(i + 1); ++r) fetch(r, f[(step + 1) & 1], s, step + 1);
+                }
+#pragma unroll
+                for (int u = dealt(m); u < dealt(m + 1); ++u) put(u, s ^ 1, t + 1);
+                if constexpr (PLANES) __builtin_amdgcn_sched_barrier(0);
+            }
+    };
+    typedef std::integral_constant<int, 0> Stage0;
+    typedef std::integral_constant<int, 1> Stage1;
+    typedef std::integral_constant<int, UNITS> Everything;
+    typedef std::integral_constant<int, 0> Nothing;
     issue(0);
     issue(1);
-    put(0, 0);
-    issue(0);
-    __syncthreads();
-    for (uint32_t t = 0; t < num; t += 2) {
+    if constexpr (AHEAD) {
 #pragma unroll
-        for (int s = 0; s < 2; ++s) {
-            if (SKIP && s == 1 && t + 1 >= num) break;
-            Frags f[2];
-            fetch(f[0], s, 0);
+        for (int part = 0; part < 3; ++part)
+            if (turn() == 0) generate(part, 0, 0);
+    }
 #pragma unroll
-            for (int step = 0; step < STEPS; ++step) {
-                if (step + 1 < STEPS) fetch(f[(step + 1) & 1], s, step + 1);
-                multiply(f[step & 1], step & 1);
-                if (step == 0 && (!SKIP || t + s + 1 < num)) {
-                    put(s ^ 1, t + s + 1);
-                    issue(s ^ 1);
-                }
-            }
-            __syncthreads();
-        }
+    for (int u = 0; u < UNITS; ++u) put(u, 0, 0);
+    if (!SKIP || num > 1)
+        period(std::true_type(), Stage0(), Everything(), 0);
+    else
+        period(std::true_type(), Stage0(), Nothing(), 0);
+    uint32_t t = 1;
+    for (; t + 1 < num; t += 2) {
+        period(std::false_type(), Stage1(), Everything(), t);
+        if (!SKIP || t + 2 < num)
+            period(std::false_type(), Stage0(), Everything(), t + 1);
+        else
+            period(std::false_type(), Stage0(), Nothing(), t + 1);
+    }
+    if (t < num) period(std::false_type(), Stage1(), Nothing(), t);
+    if constexpr (DEFER) {
+#pragma unroll
+        for (int i = 0; i < MFMAS; ++i) multiply(i, f[1], 1);
     }
 
     if constexpr (PLANES) {
@@ -513,6 +626,7 @@ __device__ __forceinline__ void plain_tile(const PlainArgs &g, bf16_t *lds, int6
         static_assert(TM == 1 && TN == 1, "one 32x32 tile per wave");
         constexpr int WAVES = S::WM * S::WN;
         float *red = reinterpret_cast<float *>(lds);
+        __syncthreads();  // (the last tiles are read, and what came behind them is written)
 #pragma unroll
         for (int v = 0; v < 16; ++v) red[(wave * 16 + v) * 64 + lane] = acc[0][0][0][v];
         __syncthreads();
@@ -553,9 +667,10 @@ __device__ __forceinline__ void plain_tile(const PlainArgs &g, bf16_t *lds, int6
 // One launch for what a pass computes from one activation: `sketch_blocks` tiles of the sketch
 // product (first: they are the long ones), `colsum_blocks` column blocks of the bias gradient and
 // the tiles of the plain product.  Any of the three may be absent.
-// (The operand of the sketch product is the plain product's A.)
+// (The operand of the sketch product is the plain product's A.  bf16: 128 registers, so that two work-groups share a compute unit;
+// with the 133 that the compiler takes otherwise the backward launch of 3000 x 768 -> 1001, k = 300, is 46 us instead of 32.)
 template <typename T, typename S, typename SS, int SKETCH, int BMODE, int MODE_A, int MODE_B>
-__global__ void __launch_bounds__(kPlainThreads) plain_pass_kernel(PlainArgs ga, PlainArgs gs, ColsumArgs gc, int plain_blocks,
+__global__ void __launch_bounds__(kPlainThreads, sizeof(T) == 2 ? 4 : 2) plain_pass_kernel(PlainArgs ga, PlainArgs gs, ColsumArgs gc, int plain_blocks,
                                                                    int sketch_blocks, int colsum_blocks) {
     constexpr int BA = PlainTile<T, S, PA_K, BMODE>::LDS_BYTES, BS = PlainTile<T, SS, SKETCH, PB_N>::LDS_BYTES;
     constexpr int BYTES = (BA > BS ? BA : BS) > kColsumLdsFloats * 4 ? (BA > BS ? BA : BS) : kColsumLdsFloats * 4;

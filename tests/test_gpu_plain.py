@@ -42,6 +42,21 @@ def test_fp32_large_tiles_of_the_gradients(shape):
     check_layer(X, W, dY, k, rmm.RADEMACHER, 0x5EED0033, 5, "f32", label="f32 large %s" % (shape,))
 
 
+# One to five LDS tiles along a contraction, the last one whole, ragged or a single element: dX and Y on 128 x 128 tiles (of 32
+# elements), on 64 x 64 (64), all products on 32 x 32 (128), X_proj and G on 32 x 128 (64 tokens)
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("shape", [(2041, 1929, 32, 9), (2041, 64, 1929, 9), (2041, 1929, 65, 9), (2041, 128, 1929, 9), (2041, 1929, 129, 9),
+                                   (1100, 1031, 64, 9), (1100, 65, 1031, 9), (1100, 1031, 192, 9), (1100, 256, 1031, 9), (1100, 1031, 257, 9),
+                                   (300, 311, 128, 9), (300, 129, 311, 9), (384, 311, 385, 300), (512, 64, 65, 30), (513, 63, 70, 30),
+                                   (64, 300, 17001, 900), (65, 300, 9001, 900), (129, 300, 9001, 900), (192, 300, 5401, 900),
+                                   (257, 300, 5201, 900)])
+def test_every_number_of_lds_tiles(shape, dtype):
+    n, d_in, d_out, k = shape
+    X, W, dY = synth.layer_inputs(n, d_in, d_out, dtype, (n, d_in + 1, d_out + 2), w_std=1.0 / math.sqrt(d_in))
+    check_layer(X, W, dY, k, rmm.RADEMACHER if n in (192, 512) else rmm.GAUSSIAN, 0x5EED0034, 7, dtype,
+                label="%s %s" % (dtype, shape))
+
+
 @pytest.mark.parametrize("kind", [rmm.GAUSSIAN, rmm.RADEMACHER, rmm.SORS])
 @pytest.mark.parametrize("shape", [(33, 35, 31, 5), (1030, 1028, 1004, 70), (2049, 515, 1030, 290), (3000, 768, 1001, 300),
                                    (4096, 261, 1032, 33)])
