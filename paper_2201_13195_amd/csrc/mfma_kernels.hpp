@@ -259,7 +259,7 @@ __device__ __forceinline__ void write_tile(const GemmArgs &g, const f32x16_t (&a
 
 // One wave's load of 1 KB into LDS from byte `to` on, 16 bytes from `off` + `soff` per lane.  The compiler does
 // not see that it writes LDS (it would wait for it before every LDS read): the explicit waits and barriers order them.
-__device__ __forceinline__ void load_to_lds(__amdgpu_buffer_rsrc_t rsrc, uint32_t to, uint32_t off, uint32_t soff) {
+__device__ __forceinline__ void load_to_lds(u32x4_t rsrc, uint32_t to, uint32_t off, uint32_t soff) {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(to), "v"(off), "s"(rsrc), "s"(soff) : "m0");
 }
 // Waits until at most N of this wave's loads are outstanding.
@@ -267,15 +267,53 @@ template <int N>
 __device__ __forceinline__ void wait_for_loads() {
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
-// A descriptor of `rows` rows of pitch ld from `base` on.  (The byte count is the same in every lane; saying so keeps it in
-// scalar registers.  The asm holds the wait states between a vector instruction that writes a scalar register and a load
-// that reads it: the compiler does not look for them in front of load_to_lds.)
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t rows_descriptor(const bf16_t *base, int64_t ld, int64_t rows) {
-    __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<bf16_t *>(base), (short)0, __builtin_amdgcn_readfirstlane((int)((rows > 0 ? rows : 0) * ld * 2)), 0x00020000);
-    asm volatile("s_nop 4" : "+s"(r));
-    return r;
+// A descriptor of `rows` rows of pitch ld from `base` on.  (The same in every lane; saying so keeps it in scalar registers.)
+__device__ __forceinline__ u32x4_t rows_descriptor(const bf16_t *base, int64_t ld, int64_t rows) {
+    const uint64_t at = reinterpret_cast<uint64_t>(base);
+    return (u32x4_t){(uint32_t)__builtin_amdgcn_readfirstlane((int)at), (uint32_t)__builtin_amdgcn_readfirstlane((int)(at >> 32)),
+                     (uint32_t)__builtin_amdgcn_readfirstlane((int)((rows > 0 ? rows : 0) * ld * 2)), 0x00020000u};
 }
+// The wait states between a vector instruction that writes a scalar register and a load that reads it: the compiler does not
+// look for them in front of load_to_lds.
+__device__ __forceinline__ void settle(u32x4_t &descriptor) { asm volatile("s_nop 4" : "+s"(descriptor)); }
+// The steps of 64 contraction elements in the order in which a work-group takes them: from `start` on and around.  What a request
+// needs is prepared one step ahead, between MFMAs, from what the one before it needed, in scalar registers and mostly 32 bits.  Made
+// anew, with products of 64 bits, selects and a way through the vector unit, it was 45 of the 62 scalar instructions of a step of
+// X^T dY, in one piece between two MFMAs, for both waves of a SIMD at once (it is 22 of 39; 4096 x 768 x 3072: a step of 64 0.48 ->
+// 0.42 us, the monitors 37.3 -> 32.7; dX of 192 128 x 128 tiles, K-contiguous Y: 49 -> 42 and 35 -> 30 a step; whole steps 1.00 to 1.06,
+// 16384 x 1024 -> 4096 567 -> 556).  A scalar instruction costs a wave about as much of its time as a vector one.
+struct Walk {
+    int steps, to_wrap, todo;  // steps until the walk is at the end of the contraction, and steps that are left
+    uint32_t soff;             // of the step that is next, in bytes along a K-contiguous row
+    __device__ __forceinline__ void init(int kk, int start) {
+        steps = todo = (kk + 63) / 64, to_wrap = __builtin_amdgcn_readfirstlane(steps - start), soff = (uint32_t)(steps - to_wrap) * 128u;
+    }
+};
+// 64 rows a step of a row-indexed operand.
+struct StepRows {
+    uint64_t base, next;  // first row of the contraction, of the next step
+    uint32_t step_bytes, last_bytes;
+    __device__ __forceinline__ void init(const bf16_t *first, int64_t ld, int kk, const Walk &w) {  // (rows below 2^22 elements)
+        step_bytes = 128u * (uint32_t)ld, last_bytes = 2u * (uint32_t)ld * (uint32_t)(kk - (w.steps - 1) * 64);
+        base = reinterpret_cast<uint64_t>(first), next = base + (uint64_t)(uint32_t)(w.steps - w.to_wrap) * step_bytes;
+    }
+    // The descriptor of the next step (past the end: of none, a load writes zeros).
+    __device__ __forceinline__ u32x4_t descriptor(bool last, bool live) {
+        const uint64_t at = next, behind = next + step_bytes;
+        const uint32_t bytes = last ? last_bytes : step_bytes;
+        next = last ? base : behind;
+        return (u32x4_t){(uint32_t)at, (uint32_t)(at >> 32), live ? bytes : 0u, 0x00020000u};
+    }
+};
+// Prepares the next step of a walk for what takes it.
+template <typename... Operands>
+__device__ __forceinline__ void prepare_step(Walk &w, Operands &...operands) {
+    const uint32_t along = w.soff + 128u;
+    const bool last = w.to_wrap == 1, live = w.todo > 0;
+    (operands.prepare(w, last, live), ...);
+    w.to_wrap = last ? w.steps : w.to_wrap - 1, w.soff = last ? 0u : along, --w.todo;
+}
+
 // Rows of C columns, contraction row k: chunk c (eight columns) sits at position col_chunk(k, c) and the other way round.
 // The four rows of a transposing read (k, k + 1, k + 2, k + 3) then fall on different 64 bytes of the banks.
 template <int C>
@@ -306,36 +344,51 @@ __device__ __forceinline__ bf16x8_t frag_columns(const bf16_t *tile, int col0, i
 template <int E, int J, bool KROWS>
 struct OperandLoads {
     static constexpr uint32_t OOB = 0x80000000u;
-    uint32_t off[J];
-    int kk[J];
-    const bf16_t *base;
-    int64_t ld;
-    __amdgpu_buffer_rsrc_t rsrc;  // of the step that is being requested
-    uint32_t to, soff;
-    int left;
-    __device__ __forceinline__ void init(const bf16_t *operand, int64_t ld_, int64_t row0, int64_t rows, int wave, int lane) {
-        base = operand, ld = ld_;
+    uint32_t off[J], beyond[KROWS ? J : 1];  // of a step; all ones where the last one of the contraction has nothing
+    StepRows rows;
+    uint32_t range;                            // K-contiguous: bytes of the tile's rows
+    u32x4_t ready, rsrc;                       // descriptors: of the step that is next, of the one that is being requested;
+    uint32_t ready_soff, ready_oob, soff, oob; //   where it is along the rows, and what the chunks beyond a last step get or'ed to their offsets
+    uint32_t to;
+    __device__ __forceinline__ void init(const bf16_t *operand, int64_t ld, int64_t row0, int64_t count, int kk, const Walk &w, int wave, int lane) {
 #pragma unroll
         for (int j = 0; j < J; ++j) {
             if constexpr (KROWS) {
                 const int row = (wave * J + j) * 8 + (lane >> 3), chunk = kchunk_pos<64>(row, lane & 7);
-                kk[j] = chunk * 8;
-                off[j] = row0 + row < rows ? (uint32_t)((row * ld + chunk * 8) * 2) : OOB;
+                off[j] = row0 + row < count ? (uint32_t)((row * ld + chunk * 8) * 2) : OOB;
+                beyond[j] = chunk * 8 < kk - (w.steps - 1) * 64 ? 0u : 0xFFFFFFFFu;
             } else {
                 const int c = (wave * J + j) * 64 + lane, k = c / (E / 8), col = col_chunk<E>(k, c % (E / 8)) * 8;
-                off[j] = row0 + col < rows ? (uint32_t)((k * ld + row0 + col) * 2) : OOB;
+                off[j] = row0 + col < count ? (uint32_t)((k * ld + row0 + col) * 2) : OOB;
             }
         }
-        if constexpr (KROWS) rsrc = rows_descriptor(operand + row0 * ld, ld, min((int64_t)E, rows - row0));
+        if constexpr (KROWS)
+            rsrc = rows_descriptor(operand + row0 * ld, ld, min((int64_t)E, count - row0)), settle(rsrc), range = rsrc[2];
+        else
+            rows.init(operand, ld, kk, w);
     }
-    // The step from contraction element k0 on, of which `left_` exist (<= 0: zeros), goes to LDS byte `to_` (of this wave's share).
-    __device__ __forceinline__ void begin(uint32_t to_, int k0, int left_) {
-        if constexpr (!KROWS) rsrc = rows_descriptor(base + (int64_t)k0 * ld, ld, min(64, left_));
-        to = to_, soff = KROWS ? (uint32_t)k0 * 2 : 0u, left = left_;
+    // The step that is next (prepare_step; past the end: zeros).
+    __device__ __forceinline__ void prepare(const Walk &w, bool last, bool live) {
+        ready_soff = KROWS ? w.soff : 0u;
+        if constexpr (KROWS) {
+            ready_oob = last ? OOB : 0u, ready[2] = live ? range : 0u;
+        } else {
+            ready = rows.descriptor(last, live);
+        }
     }
-    __device__ __forceinline__ void load(int j) const { load_to_lds(rsrc, to + j * 1024, !KROWS || kk[j] < left ? off[j] : OOB, soff); }
+    // The step that was prepared goes to LDS byte `to_` (of this wave's share).
+    __device__ __forceinline__ void begin(uint32_t to_) {
+        to = to_, soff = ready_soff;
+        if constexpr (KROWS) {
+            rsrc[2] = ready[2], oob = ready_oob;
+        } else {
+            rsrc = ready, settle(rsrc);
+        }
+    }
+    __device__ __forceinline__ void load(int j) const {
+        load_to_lds(rsrc, to + j * 1024, KROWS ? off[j] | (oob & beyond[KROWS ? j : 0]) : off[j], soff);
+    }
 };
-
 // First row and column of output tile number `tile`: bands of 8 tile rows, column by column.
 template <int BM, int BN>
 __device__ __forceinline__ void tile_origin(uint32_t tile, uint32_t tiles_m, uint32_t tiles_n, int64_t &m0, int64_t &n0) {
@@ -378,15 +431,14 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &g, bf16_t *lds, int64_
     constexpr int JA = S::A_LOADS, JB = S::B_LOADS, LOADS = JA + JB;
     OperandLoads<BM, JA, AMODE == A_KCONTIG> la;
     OperandLoads<BN, JB, BMODE == B_KCONTIG> lb;
-    la.init(g.A, g.lda, m0, g.M, wave, lane);
-    lb.init(g.B, g.ldb, n0, g.N, wave, lane);
+    Walk walk, walk_a;  // (with as many stages of A as of B one serves both)
+    walk.init(kk, stagger), walk_a.init(kk, stagger);
+    la.init(g.A, g.lda, m0, g.M, kk, walk, wave, lane);
+    lb.init(g.B, g.ldb, n0, g.N, kk, walk, wave, lane);
     typedef __attribute__((address_space(3))) bf16_t *lds_ptr_t;
     const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_ptr_t)lds;
-    auto first = [&](int t) { return t >= steps ? kk : (t + stagger >= steps ? t + stagger - steps : t + stagger) * BK; };
-    auto begin_a = [&](int t, int stage) { la.begin(lds0 + (uint32_t)(stage * S::A_ELEMS * 2 + wave * JA * 1024), first(t), kk - first(t)); };
-    auto begin_b = [&](int t, int stage) {
-        lb.begin(lds0 + (uint32_t)((SA * S::A_ELEMS + stage * S::B_ELEMS) * 2 + wave * JB * 1024), first(t), kk - first(t));
-    };
+    auto begin_a = [&](int stage) { la.begin(lds0 + (uint32_t)(stage * S::A_ELEMS * 2 + wave * JA * 1024)); };
+    auto begin_b = [&](int stage) { lb.begin(lds0 + (uint32_t)((SA * S::A_ELEMS + stage * S::B_ELEMS) * 2 + wave * JB * 1024)); };
     auto load = [&](int i) {  // load i of a step: B's come first (with SA > SB they are waited for first)
         if (i < JB)
             lb.load(i);
@@ -435,6 +487,13 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &g, bf16_t *lds, int64_
             for (int r = i * FRAGS / MFMAS; r < (i + 1) * FRAGS / MFMAS; ++r) read(next, sa, sb, ks, r);
 #pragma unroll
             for (int r = i * SP / MFMAS; r < (i + 1) * SP / MFMAS; ++r) load(l0 + r);
+            const int slot = l0 / SP * MFMAS - MFMAS + i;  // behind the barrier's step: what the next begin needs, away from the barrier
+            if constexpr (SA == SB) {
+                if (l0 > 0 && slot == (KS - 1) * MFMAS / 2) prepare_step(walk, la, lb);
+            } else {
+                if (l0 > 0 && slot == 0) prepare_step(walk_a, la);
+                if (l0 > 0 && slot == (KS - 1) * MFMAS / 2) prepare_step(walk, lb);
+            }
             __builtin_amdgcn_sched_barrier(0);
         }
     };
@@ -448,11 +507,16 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &g, bf16_t *lds, int64_
     Frags f[2];
 #pragma unroll
     for (int s = 0; s < SA - 1; ++s) {
-        begin_a(s, s);
+        if constexpr (SA == SB)
+            prepare_step(walk, la, lb);
+        else
+            prepare_step(walk_a, la);
+        begin_a(s);
 #pragma unroll
         for (int j = 0; j < JA; ++j) la.load(j);
         if (s < SB - 1) {
-            begin_b(s, s);
+            if constexpr (SA != SB) prepare_step(walk, lb);
+            begin_b(s);
 #pragma unroll
             for (int j = 0; j < JB; ++j) lb.load(j);
         }
@@ -461,19 +525,23 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &g, bf16_t *lds, int64_
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < FRAGS; ++i) read(f[0], 0, 0, 0, i);
-    begin_b(SB - 1, SB - 1), begin_a(SA - 1, SA - 1);
+    if constexpr (SA == SB)
+        prepare_step(walk, la, lb);
+    else
+        prepare_step(walk_a, la), prepare_step(walk, lb);
+    begin_b(SB - 1), begin_a(SA - 1);
 #pragma unroll
     for (int i = 0; i < SP; ++i) load(i);
     int sa = 0, sb = 0;
     for (int t = 0; t < steps; ++t) {
-        const int next_a = sa == SA - 1 ? 0 : sa + 1, next_b = sb == SB - 1 ? 0 : sb + 1;
+        const int next_a = sa == SA - 1 ? 0 : sa + 1, next_b = SA == SB ? next_a : sb == SB - 1 ? 0 : sb + 1;
 #pragma unroll
-        for (int ks = 0; ks < KS - 1; ++ks) sixteen(f[ks & 1], f[(ks + 1) & 1], sa, sb, ks + 1, (ks + 1) * SP);
+        for (int ks = 0; ks < KS - 1; ++ks) sixteen(f[ks & 1], f[(ks + 1) & 1], sa, SA == SB ? sa : sb, ks + 1, (ks + 1) * SP);
         wait_for_loads<OUTSTANDING>();
         __syncthreads();
-        begin_b(t + SB, sb), begin_a(t + SA, sa);
+        begin_b(SA == SB ? sa : sb), begin_a(sa);
         sixteen(f[1], f[0], next_a, next_b, 0, 0);  // (past the end: zeros, not used)
-        sa = next_a, sb = next_b;
+        sa = next_a, sb = SA == SB ? sa : next_b;
     }
     wait_for_loads<0>();
     __syncthreads();  // LDS is free
@@ -780,7 +848,16 @@ __device__ __forceinline__ void sketch_tile(const GemmArgs &g, bf16_t *lds, int6
     tile_origin<BM, BN>((uint32_t)tile, (uint32_t)((g.M + BM - 1) / BM), (uint32_t)((g.N + BN - 1) / BN), m0, n0);
     const int steps = (kk + BK - 1) / BK;
     const int stagger = (int)((uint32_t)tile / 8 % (uint32_t)steps);
-    auto first = [&](int t) { return (t + stagger >= steps ? t + stagger - steps : t + stagger) * BK; };  // first token of step t
+    struct Tokens {  // of the slice: rows of A, and the first token of the step
+        StepRows rows;
+        u32x4_t ready;
+        uint32_t step_token;
+        __device__ __forceinline__ void prepare(const Walk &w, bool last, bool live) {
+            ready = rows.descriptor(last, live), step_token = w.soff / 2;
+        }
+    } tokens;
+    Walk walk;
+    walk.init(kk, stagger), tokens.rows.init(g.B + kk_begin * g.ldb, g.ldb, kk, walk);
 
     constexpr uint32_t OOB = 0x80000000u;
     constexpr int CPR = BN / 8;  // chunks per row
@@ -792,12 +869,13 @@ __device__ __forceinline__ void sketch_tile(const GemmArgs &g, bf16_t *lds, int6
     }
     typedef __attribute__((address_space(3))) bf16_t *lds_ptr_t;
     const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_ptr_t)lds;
-    __amdgpu_buffer_rsrc_t rsrc;  // of the step of A that is being requested
+    u32x4_t rsrc;  // of the step of A that is being requested
     uint32_t to;
-    auto begin_loads = [&](int t, int stage) {  // (past the end: zeros)
-        const int k0 = t < steps ? first(t) : kk;
+    uint32_t making = 0;  // first token of the step whose entries are being made (tokens are below 2^31)
+    auto begin_loads = [&](int stage) {  // (past the end: zeros, and the entries of a step that exists, not used)
         to = lds0 + (uint32_t)((stage * T::STAGE_ELEMS + T::A_ELEMS) * 2 + wave * T::LOADS * 1024);
-        rsrc = rows_descriptor(g.B + (kk_begin + k0) * g.ldb, g.ldb, min(BK, kk - k0));
+        making = (uint32_t)kk_begin + tokens.step_token;
+        rsrc = tokens.ready, settle(rsrc);
     };
     auto load = [&](int j) { load_to_lds(rsrc, to + j * 1024, b_off[j], 0); };
 
@@ -809,17 +887,16 @@ __device__ __forceinline__ void sketch_tile(const GemmArgs &g, bf16_t *lds, int6
     GaussChunk gauss;
     uint32_t words[KIND == 0 ? 1 : T::GEN][4] = {};  // Rademacher: of block 8 * held + gen_k
     uint32_t low = 0, high = 0;
-    int64_t held = -1, making = 0;  // first token of the step whose entries are being made
+    uint32_t held = 0xFFFFFFFFu;
     bf16_t *made = lds;
-    auto begin_entries = [&](int t, int stage) {  // (past the end: a step that exists, not used)
-        making = kk_begin + first(min(t, steps - 1));
+    auto begin_entries = [&](int stage) {
         made = lds + stage * T::STAGE_ELEMS;
         if constexpr (KIND != 0) {
             if ((making >> 10) != held) {
                 held = making >> 10;
 #pragma unroll
                 for (int q = 0; q < T::GEN; ++q) {
-                    const Words4 w = philox4x32_10((uint32_t)(held * 8 + gen_k), (uint32_t)(m0 + gen_row + q * ROWS), g.st.off0,
+                    const Words4 w = philox4x32_10(held * 8 + gen_k, (uint32_t)(m0 + gen_row + q * ROWS), g.st.off0,
                                                    g.st.off1, g.st.key0, g.st.key1);
 #pragma unroll
                     for (int x = 0; x < 4; ++x) words[q][x] = w.w[x];
@@ -831,7 +908,7 @@ __device__ __forceinline__ void sketch_tile(const GemmArgs &g, bf16_t *lds, int6
         const int q = u / UNITS, part = u % UNITS, row = gen_row + q * ROWS;
         bf16_t *dst = made + row * BK + kchunk_pos<BK>(row, gen_k) * 8;
         if constexpr (KIND == 0) {
-            gauss.unit(g.st, (uint32_t)(making >> 3) + gen_k, (uint32_t)(m0 + row), part);
+            gauss.unit(g.st, (making >> 3) + gen_k, (uint32_t)(m0 + row), part);
             if (part == UNITS - 1) *reinterpret_cast<bf16x8_t *>(dst) = gauss.out.v;
         } else if (part == 0) {
             // the two words of the step's 64 tokens, from the neighbour that holds their block
@@ -878,6 +955,7 @@ __device__ __forceinline__ void sketch_tile(const GemmArgs &g, bf16_t *lds, int6
             }
 #pragma unroll
             for (int u = slot * ALL / SLOTS; u < (slot + 1) * ALL / SLOTS; ++u) unit(u);
+            if (place == 1 && i == MFMAS / 2) prepare_step(walk, tokens);
             __builtin_amdgcn_sched_barrier(0);
         }
     };
@@ -887,16 +965,16 @@ __device__ __forceinline__ void sketch_tile(const GemmArgs &g, bf16_t *lds, int6
         __syncthreads();
     };
     Frags f[2];
-    begin_loads(0, 0);
+    prepare_step(walk, tokens), begin_loads(0);
 #pragma unroll
     for (int j = 0; j < T::LOADS; ++j) load(j);
-    begin_entries(0, 0);
+    begin_entries(0);
 #pragma unroll
     for (int u = 0; u < ALL; ++u) unit(u);
     meet();
 #pragma unroll
     for (int i = 0; i < FRAGS; ++i) read(f[0], 0, 0, i);
-    begin_loads(1, 1), begin_entries(1, 1);
+    prepare_step(walk, tokens), begin_loads(1), begin_entries(1);
 #pragma unroll
     for (int j = 0; j < HALF; ++j) load(j);
 #pragma unroll
@@ -906,7 +984,7 @@ __device__ __forceinline__ void sketch_tile(const GemmArgs &g, bf16_t *lds, int6
 #pragma unroll
         for (int ks = 0; ks < KS - 1; ++ks) sixteen(f[ks & 1], f[(ks + 1) & 1], stage, ks + 1, ks + 1);
         meet();
-        begin_loads(t + 2, stage), begin_entries(t + 2, stage);
+        begin_loads(stage), begin_entries(stage);
         sixteen(f[1], f[0], stage ^ 1, 0, 0);  // (past the end: what the stage holds, not used)
     }
     wait_for_loads<0>();
