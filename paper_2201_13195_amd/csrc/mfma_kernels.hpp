@@ -262,6 +262,10 @@ __device__ __forceinline__ void write_tile(const GemmArgs &g, const f32x16_t (&a
 __device__ __forceinline__ void load_to_lds(u32x4_t rsrc, uint32_t to, uint32_t off, uint32_t soff) {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(to), "v"(off), "s"(rsrc), "s"(soff) : "m0");
 }
+// The same to a byte that is known but for `to`.
+__device__ __forceinline__ void load_to_lds(u32x4_t rsrc, uint32_t to, uint32_t at, uint32_t off, uint32_t soff) {
+    asm volatile("s_add_u32 m0, %0, %1\n\ts_nop 0\n\tbuffer_load_dwordx4 %2, %3, %4 offen lds" ::"s"(to), "n"(at), "v"(off), "s"(rsrc), "s"(soff) : "m0", "scc");
+}
 // Waits until at most N of this wave's loads are outstanding.
 template <int N>
 __device__ __forceinline__ void wait_for_loads() {
@@ -437,8 +441,9 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &g, bf16_t *lds, int64_
     lb.init(g.B, g.ldb, n0, g.N, kk, walk, wave, lane);
     typedef __attribute__((address_space(3))) bf16_t *lds_ptr_t;
     const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_ptr_t)lds;
-    auto begin_a = [&](int stage) { la.begin(lds0 + (uint32_t)(stage * S::A_ELEMS * 2 + wave * JA * 1024)); };
-    auto begin_b = [&](int stage) { lb.begin(lds0 + (uint32_t)((SA * S::A_ELEMS + stage * S::B_ELEMS) * 2 + wave * JB * 1024)); };
+    const uint32_t share_a = lds0 + (uint32_t)(wave * JA * 1024), share_b = lds0 + (uint32_t)(SA * S::A_ELEMS * 2 + wave * JB * 1024);
+    auto begin_a = [&](int stage) { la.begin(share_a + (uint32_t)(stage * S::A_ELEMS * 2)); };
+    auto begin_b = [&](int stage) { lb.begin(share_b + (uint32_t)(stage * S::B_ELEMS * 2)); };
     auto load = [&](int i) {  // load i of a step: B's come first (with SA > SB they are waited for first)
         if (i < JB)
             lb.load(i);
@@ -532,16 +537,30 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &g, bf16_t *lds, int64_
     begin_b(SB - 1), begin_a(SA - 1);
 #pragma unroll
     for (int i = 0; i < SP; ++i) load(i);
-    int sa = 0, sb = 0;
-    for (int t = 0; t < steps; ++t) {
-        const int next_a = sa == SA - 1 ? 0 : sa + 1, next_b = SA == SB ? next_a : sb == SB - 1 ? 0 : sb + 1;
+    auto one_step = [&](int sa, int sb) __attribute__((always_inline)) {
+        const int next_a = sa == SA - 1 ? 0 : sa + 1, next_b = sb == SB - 1 ? 0 : sb + 1;
 #pragma unroll
-        for (int ks = 0; ks < KS - 1; ++ks) sixteen(f[ks & 1], f[(ks + 1) & 1], sa, SA == SB ? sa : sb, ks + 1, (ks + 1) * SP);
+        for (int ks = 0; ks < KS - 1; ++ks) sixteen(f[ks & 1], f[(ks + 1) & 1], sa, sb, ks + 1, (ks + 1) * SP);
         wait_for_loads<OUTSTANDING>();
         __syncthreads();
-        begin_b(SA == SB ? sa : sb), begin_a(sa);
+        begin_b(sb), begin_a(sa);
         sixteen(f[1], f[0], next_a, next_b, 0, 0);  // (past the end: zeros, not used)
-        sa = next_a, sb = SA == SB ? sa : next_b;
+    };
+    if constexpr (SA == SB) {
+        // The stages one after the other: their places in LDS are offsets of the instructions.
+        int t = 0;
+        for (; t + SA <= steps; t += SA)
+#pragma unroll
+            for (int s = 0; s < SA; ++s) one_step(s, s);
+#pragma unroll
+        for (int s = 0; s < SA - 1; ++s)
+            if (t + s < steps) one_step(s, s);
+    } else {
+        int sa = 0, sb = 0;
+        for (int t = 0; t < steps; ++t) {
+            one_step(sa, sb);
+            sa = sa == SA - 1 ? 0 : sa + 1, sb = sb == SB - 1 ? 0 : sb + 1;
+        }
     }
     wait_for_loads<0>();
     __syncthreads();  // LDS is free
