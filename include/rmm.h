@@ -150,7 +150,7 @@ int rmm_sketch_static(int64_t n, int64_t d, int64_t k, int dtype, int kind, rmm_
  * X_proj may be NULL when no backward pass will follow (inference): the sketch is then
  * skipped, k and state are ignored beyond validation, and no workspace is needed.
  * In bf16 with widths that are multiples of 8, Y of calls that share a launch with the sketch product
- * (rmm_uses_paired_launch) is the same bits for any k, kind and scratch.  Elsewhere its last bits, and those of
+ * (those that record RMM_STAGE_FWD_PAIR) is the same bits for any k, kind and scratch.  Elsewhere its last bits, and those of
  * dX below, may differ between calls that differ in these or in whether X_proj is asked for. */
 int rmm_forward(const rmm_layer_desc_t *desc, rmm_rng_state_t state, const void *X, const void *W,
                 const void *bias, void *Y, void *X_proj, void *ws, size_t ws_bytes, void *stream);
@@ -229,10 +229,13 @@ int rmm_sketch_profiled(int64_t n, int64_t d, int64_t k, int dtype, int kind, rm
                         const void *A, void *A_proj, void *ws, size_t ws_bytes, void *stream,
                         void *ev_begin, void *ev_end);
 
-/* Whether an unprofiled rmm_forward (op = RMM_OP_FORWARD) / rmm_backward with dX (RMM_OP_BACKWARD)
- * of this shape issues its two independent products as one paired launch (RMM_STAGE_FWD_PAIR /
- * RMM_STAGE_BWD_PAIR): 1 or 0; 0 for an invalid descriptor.  For the SORS kind 1 says that its strips go between the rounds of the
- * plain product's tiles; other passes of it may be one launch too. */
+/* Dense kinds: whether an unprofiled rmm_forward (op = RMM_OP_FORWARD) / rmm_backward with dX (RMM_OP_BACKWARD) of
+ * this shape issues its two independent products as one launch: 1 or 0.  SORS kind: whether the strips of the sketch
+ * product can go on compute units of their own, which the rounds of the plain product's tiles leave: 1 or 0.  With 1 a
+ * SORS pass is one launch; with 0 it is two launches, or one in which strips and 128 x 128 tiles share compute units.
+ * 0 for an invalid descriptor.
+ * What a pass of any kind does is told by RMM_STAGE_FWD_PAIR / RMM_STAGE_BWD_PAIR: their events are recorded if its
+ * products are one launch, and not if they are two. */
 int rmm_uses_paired_launch(const rmm_layer_desc_t *desc, int op);
 
 /* Ceilings of the chip as a kernel sees them, for reporting measured fractions beside the

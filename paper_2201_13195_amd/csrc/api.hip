@@ -344,7 +344,7 @@ int rmm_uses_paired_launch(const rmm_layer_desc_t *desc, int op) {
     if (!desc_ok(desc) || (op != RMM_OP_FORWARD && op != RMM_OP_BACKWARD)) return 0;
     if (!use_mfma(desc)) return 1;
     const int64_t d_sk = op == RMM_OP_FORWARD ? desc->d_in : desc->d_out, d_other = op == RMM_OP_FORWARD ? desc->d_out : desc->d_in;
-    return desc->kind == RMM_SKETCH_SORS ? sors_pair_reported(desc->n, d_sk, d_other, desc->k) : pass_is_paired(desc, op);
+    return desc->kind == RMM_SKETCH_SORS ? sors_strips_among_rounds(desc->n, d_sk, d_other, desc->k) : pass_is_paired(desc, op);
 }
 
 int rmm_sketch_profiled(int64_t n, int64_t d, int64_t k, int dtype, int kind, rmm_rng_state_t state, const void *A,

@@ -116,9 +116,9 @@ hipError_t launch_sors_colsum_bf16(const bf16_t *A, bf16_t *colsum, int64_t n, i
 // One launch for the plain product of a pass and the SORS sketch product of the same pass, where
 // the plain product leaves compute units idle (mfma.hip decides, mfma_pair_sors.hip holds the
 // kernels).  Same results as the separate launches, bit for bit.
-// (rmm_uses_paired_launch gives the second answer: what it has said since before strips shared compute units with tiles)
 bool sors_pair_available(int64_t n, int64_t d_sk, int64_t d_other, int64_t k);
-bool sors_pair_reported(int64_t n, int64_t d_sk, int64_t d_other, int64_t k);
+// Whether the strips can have compute units of their own in that launch (what rmm_uses_paired_launch says of this kind).
+bool sors_strips_among_rounds(int64_t n, int64_t d_sk, int64_t d_other, int64_t k);
 hipError_t launch_forward_pair_sors_bf16(const bf16_t *X, const bf16_t *W, const bf16_t *bias, bf16_t *Y, bf16_t *X_proj,
                                          int64_t n, int64_t d_in, int64_t d_out, int64_t k, SketchState st,
                                          hipStream_t stream, hipEvent_t ev_begin = nullptr, hipEvent_t ev_end = nullptr);

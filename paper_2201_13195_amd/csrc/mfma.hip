@@ -304,7 +304,7 @@ bool sors_pair_available(int64_t n, int64_t d_sk, int64_t d_other, int64_t k) {
     return sors_fast_ok(n, d_sk) && plan_sors(n, d_sk, d_other, k).order != SORS_APART;
 }
 
-bool sors_pair_reported(int64_t n, int64_t d_sk, int64_t d_other, int64_t k) {
+bool sors_strips_among_rounds(int64_t n, int64_t d_sk, int64_t d_other, int64_t k) {
     return sors_fast_ok(n, d_sk) && sors_among_rounds(n, d_sk, d_other, k) != SORS_APART;
 }
 

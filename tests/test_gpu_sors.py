@@ -232,3 +232,27 @@ def test_strips_beside_tiles_on_a_compute_unit(shape):
         assert all(x is None and y is None or torch.equal(x, y) for x, y in zip(one, two)), need_dbias
     if k > 64:
         assert torch.equal(Y0, rmm.rmm_forward(Xd, Wd, None, k, rmm.RADEMACHER, 9, 1)[0])
+
+
+@pytest.mark.parametrize("shape,forward,backward", [((4096, 512, 768, 410), True, True), ((2048, 768, 3072, 410), True, False),
+                                                    ((4096, 768, 3072, 410), True, True), ((16384, 1024, 4096, 1638), True, False),
+                                                    ((16384, 4096, 1024, 1638), False, True)])
+def test_events_say_whether_a_pass_is_one_launch(shape, forward, backward):
+    """In every form of the launch; with 1, rmm_uses_paired_launch says so too."""
+    n, d_in, d_out, k = shape
+    X, W, dY = (torch.zeros(s, device=DEV, dtype=torch.bfloat16) for s in ((n, d_in), (d_out, d_in), (n, d_out)))
+    _, Xp = rmm.rmm_forward(X, W, None, k, SORS, 9, 1)
+
+    def recorded(call, stage):
+        a, b, made = (torch.cuda.Event(enable_timing=True) for _ in range(3))
+        for e in (a, b, made):
+            e.record()
+        torch.cuda.synchronize()
+        call((stage, a, b))
+        torch.cuda.synchronize()
+        return made.elapsed_time(a) > 0
+
+    for call, stage, op, expected in ((lambda p: rmm.rmm_forward(X, W, None, k, SORS, 9, 1, profile=p), binding.STAGE_FWD_PAIR, binding.OP_FORWARD, forward),
+                                      (lambda p: rmm.rmm_backward(dY, W, Xp, SORS, 9, 1, profile=p), binding.STAGE_BWD_PAIR, binding.OP_BACKWARD, backward)):
+        assert recorded(call, stage) == expected, stage
+        assert expected or not rmm.rmm_uses_paired_launch(n, d_in, d_out, k, torch.bfloat16, SORS, op)
