@@ -262,6 +262,10 @@ __device__ __forceinline__ void write_tile(const GemmArgs &g, const f32x16_t (&a
 __device__ __forceinline__ void load_to_lds(u32x4_t rsrc, uint32_t to, uint32_t off, uint32_t soff) {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(to), "v"(off), "s"(rsrc), "s"(soff) : "m0");
 }
+// The same from `off`.
+__device__ __forceinline__ void load_to_lds(u32x4_t rsrc, uint32_t to, uint32_t off) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(to), "v"(off), "s"(rsrc) : "m0");
+}
 // The same to a byte that is known but for `to`.
 __device__ __forceinline__ void load_to_lds(u32x4_t rsrc, uint32_t to, uint32_t at, uint32_t off, uint32_t soff) {
     asm volatile("s_add_u32 m0, %0, %1\n\ts_nop 0\n\tbuffer_load_dwordx4 %2, %3, %4 offen lds" ::"s"(to), "n"(at), "v"(off), "s"(rsrc), "s"(soff) : "m0", "scc");
@@ -277,9 +281,11 @@ __device__ __forceinline__ u32x4_t rows_descriptor(const bf16_t *base, int64_t l
     return (u32x4_t){(uint32_t)__builtin_amdgcn_readfirstlane((int)at), (uint32_t)__builtin_amdgcn_readfirstlane((int)(at >> 32)),
                      (uint32_t)__builtin_amdgcn_readfirstlane((int)((rows > 0 ? rows : 0) * ld * 2)), 0x00020000u};
 }
-// The wait states between a vector instruction that writes a scalar register and a load that reads it: the compiler does not
-// look for them in front of load_to_lds.
+// The wait states between a vector instruction that writes a scalar register (a readfirstlane, a spilled one that comes back) and a
+// load that reads it: the compiler does not look for them in front of load_to_lds.  So the scalar registers of a load are written in
+// front of one of these and nowhere behind it.
 __device__ __forceinline__ void settle(u32x4_t &descriptor) { asm volatile("s_nop 4" : "+s"(descriptor)); }
+__device__ __forceinline__ void settle(u32x4_t &descriptor, uint32_t &soff) { asm volatile("s_nop 4" : "+s"(descriptor), "+s"(soff)); }
 // The steps of 64 contraction elements in the order in which a work-group takes them: from `start` on and around.  What a request
 // needs is prepared one step ahead, between MFMAs, from what the one before it needed, in scalar registers and mostly 32 bits.  Made
 // anew, with products of 64 bits, selects and a way through the vector unit, it was 45 of the 62 scalar instructions of a step of
@@ -384,13 +390,16 @@ struct OperandLoads {
     __device__ __forceinline__ void begin(uint32_t to_) {
         to = to_, soff = ready_soff;
         if constexpr (KROWS) {
-            rsrc[2] = ready[2], oob = ready_oob;
+            rsrc[2] = ready[2], oob = ready_oob, settle(rsrc, soff);
         } else {
             rsrc = ready, settle(rsrc);
         }
     }
     __device__ __forceinline__ void load(int j) const {
-        load_to_lds(rsrc, to + j * 1024, KROWS ? off[j] | (oob & beyond[KROWS ? j : 0]) : off[j], soff);
+        if constexpr (KROWS)
+            load_to_lds(rsrc, to + j * 1024, off[j] | (oob & beyond[j]), soff);
+        else
+            load_to_lds(rsrc, to + j * 1024, off[j]);
     }
 };
 // First row and column of output tile number `tile`: bands of 8 tile rows, column by column.
@@ -896,7 +905,7 @@ __device__ __forceinline__ void sketch_tile(const GemmArgs &g, bf16_t *lds, int6
         making = (uint32_t)kk_begin + tokens.step_token;
         rsrc = tokens.ready, settle(rsrc);
     };
-    auto load = [&](int j) { load_to_lds(rsrc, to + j * 1024, b_off[j], 0); };
+    auto load = [&](int j) { load_to_lds(rsrc, to + j * 1024, b_off[j]); };
 
     // Chunk q of this thread: tokens gen_k * 8 .. + 7 of the step, sketch column m0 + gen_row + q * ROWS.  Tokens past the
     // slice are generated too: their rows of A are zeros.

@@ -1,0 +1,70 @@
+"""CPU: the loads into LDS that are written as assembly (load_to_lds), in the code object of the built library.  Between a vector
+instruction that writes a scalar register and a load that reads it the hardware wants five wait states, and nobody counts them in
+front of these loads but settle(): whatever writes their scalar registers stands in front of it."""
+import glob
+import os
+import re
+import shutil
+import subprocess
+
+import pytest
+
+import paper_2201_13195_amd as rmm
+
+OBJDUMP = "/opt/rocm/llvm/bin/llvm-objdump"
+NO_RESULT = ("s_cmp", "s_bitcmp", "s_branch", "s_cbranch", "s_barrier", "s_waitcnt", "s_nop", "s_endpgm", "buffer_", "ds_", "global_", "flat_", "scratch_")
+
+
+def scalars(operand):
+    m = re.fullmatch(r"s(?:\[(\d+):(\d+)\]|(\d+))", operand.strip())
+    return set() if m is None else set(range(int(m[1]), int(m[2]) + 1)) if m[1] else {int(m[3])}
+
+
+def written(instruction):
+    op, _, rest = instruction.partition(" ")
+    if op.startswith(NO_RESULT):
+        return set()
+    operands = rest.split(",")
+    two = op.startswith(("v_mad_u64", "v_mad_i64", "v_div_scale")) or "_co_" in op       # (their carry is a second result)
+    return set().union(*[scalars(o) for o in operands[:2 if two else 1]])
+
+
+def early_writes(text):
+    """(loads into LDS, those whose scalar registers are written in the five wait states before them), in program order."""
+    code = [re.sub(r"\s+", " ", line.split("//")[0]).strip() for line in text.split("\n")]
+    code = [c for c in code if c and not c.endswith(":")]
+    loads = [i for i, c in enumerate(code) if c.startswith("buffer_load") and c.endswith(" lds")]
+    bad = []
+    for i in loads:
+        operands = code[i].split(" ", 1)[1].split(",")
+        need, states, j = scalars(operands[1]) | scalars(operands[2].split(" offen")[0]), 0, i - 1
+        while states < 5 and j >= 0:
+            if written(code[j]) & need:
+                bad.append(code[j:i + 1])
+                break
+            states += int(code[j].split()[1], 0) + 1 if code[j].startswith("s_nop") else 1
+            j -= 1
+    return len(loads), bad
+
+
+def test_the_scan_sees_a_write():
+    settled = "s_mov_b32 s10, s53\n s_nop 4\n s_mov_b32 m0, s2\n s_nop 0\n buffer_load_dwordx4 v1, s[8:11], s4 offen lds\n"
+    assert early_writes(settled) == (1, [])
+    for w in ("s_mov_b32 s10, s53", "v_readlane_b32 s4, v9, 3", "v_mad_u64_u32 v[2:3], s[8:9], v4, v5, 0"):
+        assert len(early_writes(settled.replace("s_nop 4", w))[1]) == 1, w
+
+
+def test_scalar_registers_of_a_load_have_settled(tmp_path):
+    if not os.path.exists(OBJDUMP):
+        pytest.skip("no disassembler")
+    shutil.copy(rmm.lib_path(), str(tmp_path / "librmm.so"))
+    subprocess.run([OBJDUMP, "--offloading", "librmm.so"], cwd=str(tmp_path), check=True, capture_output=True)
+    objects = glob.glob(str(tmp_path / "*gfx950"))
+    assert objects
+    total = 0
+    for path in objects:
+        p = subprocess.run([OBJDUMP, "-d", "--no-show-raw-insn", path], capture_output=True, text=True, check=True)
+        loads, bad = early_writes(p.stdout)
+        assert not bad, (path, len(bad), bad[0])
+        total += loads
+    assert total > 1000
