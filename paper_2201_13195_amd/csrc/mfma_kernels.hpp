@@ -266,10 +266,6 @@ __device__ __forceinline__ void load_to_lds(u32x4_t rsrc, uint32_t to, uint32_t 
 __device__ __forceinline__ void load_to_lds(u32x4_t rsrc, uint32_t to, uint32_t off) {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(to), "v"(off), "s"(rsrc) : "m0");
 }
-// The same to a byte that is known but for `to`.
-__device__ __forceinline__ void load_to_lds(u32x4_t rsrc, uint32_t to, uint32_t at, uint32_t off, uint32_t soff) {
-    asm volatile("s_add_u32 m0, %0, %1\n\ts_nop 0\n\tbuffer_load_dwordx4 %2, %3, %4 offen lds" ::"s"(to), "n"(at), "v"(off), "s"(rsrc), "s"(soff) : "m0", "scc");
-}
 // Waits until at most N of this wave's loads are outstanding.
 template <int N>
 __device__ __forceinline__ void wait_for_loads() {
