@@ -377,10 +377,11 @@ inline PassPlan plan_pass(int64_t n, int64_t d_sk, int64_t d_other, int64_t k, i
 
 // ---- The SORS kind: strips of eight columns of the sketched operand, which may share a launch with the plain product of their pass.
 
-// Tokens as a power of two, 1024 at least (the shortest transform of the strip kernel).  Up to 2048 a strip takes them in one piece, and
+// Tokens as a power of two, 512 at least (the shortest transform of the strip kernel: 512 tokens of 768 columns on 1024 points take 5.8
+// us instead of 5.4, of 4096 columns 6.9 instead of 6.1).  Up to 2048 a strip takes them in one piece, and
 // any k; from there on in chunks of 2048, with accumulators for kSorsAccMaxK sketch columns.
 inline int sors_log(int64_t n) {
-    int l = 10;
+    int l = 9;
     while (((int64_t)1 << l) < n) ++l;
     return l;
 }
@@ -403,7 +404,8 @@ struct SorsPlan {
 // steps, dW included, it is 8.9 % faster than the others alone, at worst 1.4 % slower; with hindsight 9.9 %.  (2275 x 312 -> 584, k = 455: a
 // step 36.5 -> 25.5 us, 2907 x 1248 -> 1136 59.1 -> 44.5, 4250 x 1232 -> 864 71 -> 55.  Not where 256 x 256 tiles fill the chip, whose
 // operands cost half the L2 traffic: 15053 x 2264 -> 3112 500 against 626; nor beside few tiles of a long contraction, which other
-// tiles have more work-groups for: 3277 x 3480 -> 272 73 against 97.)
+// tiles have more work-groups for: 3277 x 3480 -> 272 73 against 97.)  Of 100 passes of 1 to 512 tokens, widths
+// 256 to 4096, it takes 20, which are 0.64 to 0.87 of the time that they were apart.
 inline int sors_among_rounds(int64_t n, int64_t d_sk, int64_t d_other, int64_t k) {
     const PairPlain plain = pair_plain(n, d_other);
     if (sors_log(n) < 12 || sors_log(n) > 15 || k > kSorsAccMaxK) return SORS_APART;

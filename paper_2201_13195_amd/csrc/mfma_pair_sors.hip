@@ -33,7 +33,8 @@ __global__ void __launch_bounds__(SA::THREADS) gemm_sors_pair_kernel(GemmArgs ga
 // Tiles of 128 x 128 in half of a compute unit's LDS and registers, strips in the other half or in what the tiles leave.  What bounds a tile
 // is the way of its operands into LDS, what bounds a strip vector additions and LDS passes between barriers: beside each other either
 // waits less.  The tiles come first: they are the longer ones, and the strips fill the places behind them.
-// The strips as the strip kernel has them alone: LC = 10 and 11 all tokens at once, ACC chunks of 2048 with accumulators.
+// The strips as the strip kernel has them alone: LC = 10 and 11 all tokens at once, ACC chunks of 2048 with accumulators.  Up to 512
+// tokens too take 1024 points, whose work-groups have as many waves as those of the tiles; the upper half is zeros, and the results the same.
 template <int BMODE_A, int LC, bool ACC, bool SUMS>
 __global__ void __launch_bounds__(512, 4) gemm_sors_compact_kernel(GemmArgs ga, SorsArgs gs, int tiles, int chunks) {
     constexpr int BYTES_A = ShapeCompact::LDS_BYTES, PLANE_BYTES = StripShape<LC>::REGION * 16, BYTES_S = PLANE_BYTES + 1024 * 4;
@@ -80,10 +81,10 @@ hipError_t launch_pair_sors(const SorsPlan &plan, bool row_indexed_b, const Gemm
     if (plan.order == SORS_COMPACT) {
         const int l = sors_log(gs.n);
         if (row_indexed_b)
-            return l == 10   ? launch_compact<B_NCONTIG, 10, false>(ga, gs, plain.tiles, stream)
+            return l <= 10   ? launch_compact<B_NCONTIG, 10, false>(ga, gs, plain.tiles, stream)
                    : l == 11 ? launch_compact<B_NCONTIG, 11, false>(ga, gs, plain.tiles, stream)
                              : launch_compact<B_NCONTIG, 11, true>(ga, gs, plain.tiles, stream);
-        return l == 10   ? launch_compact<B_KCONTIG, 10, false>(ga, gs, plain.tiles, stream)
+        return l <= 10   ? launch_compact<B_KCONTIG, 10, false>(ga, gs, plain.tiles, stream)
                : l == 11 ? launch_compact<B_KCONTIG, 11, false>(ga, gs, plain.tiles, stream)
                          : launch_compact<B_KCONTIG, 11, true>(ga, gs, plain.tiles, stream);
     }

@@ -163,18 +163,19 @@ __global__ void __launch_bounds__(256) sors_kernel(SorsArgs g) {
     }
 }
 
-// Eight waves a strip: two strips are resident on a compute unit, by LDS.
-constexpr int kStripWaves = 8;
+// Eight waves a strip (four where a chunk has tokens for no more): two strips are resident on a compute unit, by LDS.
+template <int LC>
+constexpr int strip_waves() { return LC == 9 ? 4 : 8; }
 template <int LC, bool ACC, int NPROB, bool SUMS>
-__global__ void __launch_bounds__(64 * NPROB * kStripWaves, LC < 12 ? kStripWaves / 2 : 2) sors_strip_kernel(SorsArgs g, int chunks) {
+__global__ void __launch_bounds__(64 * NPROB * strip_waves<LC>(), LC < 12 ? strip_waves<LC>() / 2 : 2) sors_strip_kernel(SorsArgs g, int chunks) {
     __shared__ float4 planes[NPROB * StripShape<LC>::REGION];
     __shared__ uint32_t sign_words[1024];  // up to 32768 tokens
-    sors_strip_body<LC, ACC, NPROB, NPROB * kStripWaves, SUMS>(g, chunks, planes, sign_words, blockIdx.x, gridDim.x);
+    sors_strip_body<LC, ACC, NPROB, NPROB * strip_waves<LC>(), SUMS>(g, chunks, planes, sign_words, blockIdx.x, gridDim.x);
 }
 
 template <int LC, bool ACC, int NPROB>
 hipError_t launch_strips(const SorsArgs &g, int chunks, hipStream_t stream) {
-    const unsigned grid = (unsigned)((g.d / 8 + NPROB - 1) / NPROB), threads = 64 * NPROB * kStripWaves;
+    const unsigned grid = (unsigned)((g.d / 8 + NPROB - 1) / NPROB), threads = 64 * NPROB * strip_waves<LC>();
     if (g.colsum != nullptr)
         sors_strip_kernel<LC, ACC, NPROB, true><<<grid, threads, 0, stream>>>(g, chunks);
     else
@@ -194,8 +195,8 @@ hipError_t launch_strip(const SorsArgs &g, int chunks, hipStream_t stream) {
 
 // The column sums alone, as the strips take them: for a pass whose bias gradient is to be timed on its own.
 template <int LC>
-__global__ void __launch_bounds__(64 * kStripWaves) sors_colsum_kernel(SorsArgs g, int chunks) {
-    constexpr int CH = 1 << LC, TW = CH / kStripWaves;
+__global__ void __launch_bounds__(64 * strip_waves<LC>()) sors_colsum_kernel(SorsArgs g, int chunks) {
+    constexpr int CH = 1 << LC, TW = CH / strip_waves<LC>();
     typedef StripSums<CH, TW, 1> Sums;
     __shared__ float part[CH / 128 * 8];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
@@ -215,7 +216,7 @@ __global__ void __launch_bounds__(64 * kStripWaves) sors_colsum_kernel(SorsArgs 
 
 template <int LC>
 hipError_t launch_colsum_strips(const SorsArgs &g, int chunks, hipStream_t stream) {
-    sors_colsum_kernel<LC><<<(unsigned)(g.d / 8), 64 * kStripWaves, 0, stream>>>(g, chunks);
+    sors_colsum_kernel<LC><<<(unsigned)(g.d / 8), 64 * strip_waves<LC>(), 0, stream>>>(g, chunks);
     return hipGetLastError();
 }
 
@@ -235,12 +236,13 @@ bool sors_takes_colsum(int64_t n, int64_t k) { return k <= kSorsAccMaxK || n <= 
 hipError_t launch_sors_bf16(const bf16_t *A, bf16_t *out, int64_t n, int64_t d, int64_t k, SketchState st,
                             hipStream_t stream, bf16_t *colsum, bool accumulate) {
     SorsArgs g{A, out, n, d, k, st, 1.0f / sqrtf((float)k), colsum, accumulate ? 1 : 0};
-    // A kernel's transform length is at least 1024; for fewer tokens the rows drawn below n_pad
+    // A kernel's transform length is at least 512; for fewer tokens the rows drawn below n_pad
     // are rows of the larger Walsh-Hadamard matrix restricted to its leading n_pad x n_pad block,
     // which is the n_pad-point matrix itself.
     const int l = sors_log(n);
     if (l >= 12 && k <= kSorsAccMaxK) return launch_strip<11, true>(g, sors_chunks(n), stream);  // chunks of 2048 tokens
     switch (l) {
+        case 9: return launch_strip<9, false>(g, 1, stream);
         case 10: return launch_strip<10, false>(g, 1, stream);
         case 11: return launch_strip<11, false>(g, 1, stream);
         case 12: return launch_strip<12, false>(g, 1, stream);
@@ -257,6 +259,7 @@ hipError_t launch_sors_colsum_bf16(const bf16_t *A, bf16_t *colsum, int64_t n, i
     const int l = sors_log(n);  // (chunks: see launch_sors_bf16)
     if (l >= 12 && k <= kSorsAccMaxK) return launch_colsum_strips<11>(g, sors_chunks(n), stream);
     switch (l) {
+        case 9: return launch_colsum_strips<9>(g, 1, stream);
         case 10: return launch_colsum_strips<10>(g, 1, stream);
         case 11: return launch_colsum_strips<11>(g, 1, stream);
         case 12: return launch_colsum_strips<12>(g, 1, stream);

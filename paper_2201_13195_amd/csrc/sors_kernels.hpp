@@ -53,7 +53,7 @@ template <int LC>
 struct StripShape {
     static constexpr int CH = 1 << LC, SLOTS = strip_phys(CH);
     static constexpr int PLANE = SLOTS + 4, REGION = 2 * PLANE + 2;  // float4 slots of half a strip and of a strip
-    static_assert(LC >= 10 && LC <= 12, "chunks of 1024 .. 4096 tokens");
+    static_assert(LC >= 9 && LC <= 12, "chunks of 512 .. 4096 tokens");
 };
 
 // Rows t, t + LPW, .. of a strip, 16 bytes from `off` on in each lane.  Buffer loads: a row beyond the tokens lies outside the

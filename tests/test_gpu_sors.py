@@ -256,3 +256,21 @@ def test_events_say_whether_a_pass_is_one_launch(shape, forward, backward):
                                       (lambda p: rmm.rmm_backward(dY, W, Xp, SORS, 9, 1, profile=p), binding.STAGE_BWD_PAIR, binding.OP_BACKWARD, backward)):
         assert recorded(call, stage) == expected, stage
         assert expected or not rmm.rmm_uses_paired_launch(n, d_in, d_out, k, torch.bfloat16, SORS, op)
+
+
+@pytest.mark.parametrize("n", [1, 8, 300, 512])
+def test_short_passes_have_the_same_bits_on_512_points_and_on_1024(n):
+    """Strips beside tiles take 1024 points, those of a launch of their own, and column sums alone, 512."""
+    d_in, d_out, k = 264, 520, max(1, n // 7)
+    X, W, dY = synth.layer_inputs(n, d_in, d_out, "bf16", (n, d_in + 1, d_out + 2), w_std=1.0 / math.sqrt(d_in))
+    check_layer(X, W, dY, k, SORS, 0x5EED0092, 15, "bf16", bias=synth.to_torch(synth.normal((d_out,), 17), "bf16"), label="short %d" % n)
+    Xd, Wd, dYd = (t.to(DEV) for t in (X, W, dY))
+    a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    a.record(); b.record()
+    torch.cuda.synchronize()
+    Xp = rmm.rmm_forward(Xd, Wd, None, k, SORS, 9, 1)[1]
+    assert torch.equal(Xp, rmm.rmm_sketch(Xd, k, SORS, 9, 1))
+    dX, dW, db = rmm.rmm_backward(dYd, Wd, Xp, SORS, 9, 1, need_dbias=True)
+    for stage in (binding.STAGE_BWD_DX, binding.STAGE_BWD_DBIAS):
+        dX1, dW1, db1 = rmm.rmm_backward(dYd, Wd, Xp, SORS, 9, 1, need_dbias=True, profile=(stage, a, b))
+        assert torch.equal(dX, dX1) and torch.equal(dW, dW1) and torch.equal(db, db1), stage

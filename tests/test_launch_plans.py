@@ -45,6 +45,7 @@ int pass_plan(int64_t n, int64_t d_sk, int64_t d_other, int64_t k, int kind, int
 }
 int f32_tile(int64_t n, int64_t d_in, int64_t d_out, int64_t k, int64_t kind) { return plain_backward_cfg_f32(n, d_in, d_out, k, (int)kind); }
 int sors_order(int64_t n, int64_t d_sk, int64_t d_other, int64_t k) { return plan_sors(n, d_sk, d_other, k).order; }
+int64_t sors_points(int64_t n) { return (int64_t)sors_chunks(n) << (sors_chunks(n) > 1 ? 11 : sors_log(n)); }
 int dx_tile(int cfg, int64_t kk) { return dx_cfg(cfg, kk); }
 void backward_plan(int64_t n, int64_t d_in, int64_t d_out, int64_t k, int kind, int with_dbias, int64_t *o) {
     put(plan_backward(n, d_in, d_out, k, kind, with_dbias != 0).sketch, o);
@@ -263,3 +264,10 @@ def test_strips_share_compute_units_where_their_tests_expect_it(plans):
     assert order(3277, 3480, 272, 1639) != "compact"
     for n, k in ((2049, 2049), (40000, 100)):                   # more sketch columns than accumulators, more tokens than the strips take
         assert order(n, 264, 392, k) != "compact"
+
+
+def test_short_transforms_are_no_longer_than_they_have_to_be(plans):
+    f = plans.lib.sors_points
+    f.restype = ctypes.c_int64
+    points = {n: f(ctypes.c_int64(n)) for n in (1, 8, 300, 512, 513, 1024, 1025, 2048, 2049, 4097, 32768)}
+    assert points == {1: 512, 8: 512, 300: 512, 512: 512, 513: 1024, 1024: 1024, 1025: 2048, 2048: 2048, 2049: 4096, 4097: 8192, 32768: 32768}
