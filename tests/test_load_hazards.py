@@ -1,4 +1,4 @@
-"""CPU: the loads into LDS that are written as assembly (load_to_lds), in the code object of the built library.  Between a vector
+"""CPU: the loads into LDS that are written as assembly (load_to_lds), in the code objects of the built library.  Between a vector
 instruction that writes a scalar register and a load that reads it the hardware wants five wait states, and nobody counts them in
 front of these loads but settle(): whatever writes their scalar registers stands in front of it."""
 import glob
@@ -54,17 +54,33 @@ def test_the_scan_sees_a_write():
         assert len(early_writes(settled.replace("s_nop 4", w))[1]) == 1, w
 
 
-def test_scalar_registers_of_a_load_have_settled(tmp_path):
+@pytest.fixture(scope="module")
+def code(tmp_path_factory):
+    """The disassembly of every code object."""
     if not os.path.exists(OBJDUMP):
         pytest.skip("no disassembler")
-    shutil.copy(rmm.lib_path(), str(tmp_path / "librmm.so"))
-    subprocess.run([OBJDUMP, "--offloading", "librmm.so"], cwd=str(tmp_path), check=True, capture_output=True)
-    objects = glob.glob(str(tmp_path / "*gfx950"))
+    where = str(tmp_path_factory.mktemp("objects"))
+    shutil.copy(rmm.lib_path(), os.path.join(where, "librmm.so"))
+    subprocess.run([OBJDUMP, "--offloading", "librmm.so"], cwd=where, check=True, capture_output=True)
+    objects = glob.glob(os.path.join(where, "*gfx950"))
     assert objects
+    return [subprocess.run([OBJDUMP, "-d", "--no-show-raw-insn", path], capture_output=True, text=True, check=True).stdout for path in objects]
+
+
+def test_scalar_registers_of_a_load_have_settled(code):
     total = 0
-    for path in objects:
-        p = subprocess.run([OBJDUMP, "-d", "--no-show-raw-insn", path], capture_output=True, text=True, check=True)
-        loads, bad = early_writes(p.stdout)
-        assert not bad, (path, len(bad), bad[0])
+    for text in code:
+        loads, bad = early_writes(text)
+        assert not bad, (len(bad), bad[0])
         total += loads
     assert total > 1000
+
+
+def test_a_sketch_tile_asks_for_its_operand_before_it_generates(code):
+    """The loads of a tile's first step stand in front of the generator's first multiplication."""
+    kernels = [(name, body) for text in code for name, body in re.findall(r"<(\S*sketch_kernel\S*)>:\n(.*?)(?=\n\n|\Z)", text, re.S)]
+    assert len(kernels) == 12
+    for name, body in kernels:
+        columns = int(re.search(r"ShapeILi\d+ELi(\d+)E", name)[1])
+        before = body[:re.search(r"v_mad_u64_u32 (\S+ ){4}0\b", body).start()]        # (with a third operand they make addresses)
+        assert before.count(" lds") == columns // 64, name          # 1 KB each, of 64 tokens, from eight waves
