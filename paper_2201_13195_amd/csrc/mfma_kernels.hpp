@@ -28,6 +28,7 @@
 #include "colsum.hpp"
 #include "mfma_frag.hpp"
 #include "row_norms.hpp"
+#include "tile_range.hpp"
 
 namespace rmm {
 
@@ -431,11 +432,8 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &g, bf16_t *lds, int64_
     const int kk = (int)g.K, steps = (kk + BK - 1) / BK;
     // Work-groups walk the contraction from different starting steps (and wrap around): with a
     // power-of-two row pitch all rows of a tile fall on the same one or two L2 channels, and the
-    // rotation spreads concurrently running work-groups over the channels.  Neighbouring tiles (same B column block,
-    // neighbouring A row blocks) share a starting step so that their common operand is fetched once into L2.
-    // Y and dX: by the place in the output, so that a product has the same bits on all tiles whose waves do not split the contraction.
-    const uint32_t place = AMODE == A_KCONTIG ? (uint32_t)(m0 >> 10) * (uint32_t)((g.N + 255) >> 8) + (uint32_t)(n0 >> 8) : tile / 8;
-    const int stagger = (int)(place % (uint32_t)steps);
+    // rotation spreads concurrently running work-groups over the channels.
+    const int stagger = (int)((AMODE == A_KCONTIG && BMODE == B_KCONTIG ? start_of_place(m0, n0, g.N) : start_of_tile(tile)) % (uint32_t)steps);
 
     constexpr int JA = S::A_LOADS, JB = S::B_LOADS, LOADS = JA + JB;
     OperandLoads<BM, JA, AMODE == A_KCONTIG> la;

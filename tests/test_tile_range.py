@@ -18,11 +18,14 @@ extern "C" int64_t range_bytes(int es, int krows, int64_t rows_left, int64_t til
     return krows ? rmm::tile_range_bytes<4, true>(rows_left, tile_rows, ld, left, skew)
                  : rmm::tile_range_bytes<4, false>(rows_left, tile_rows, ld, left, skew);
 }
+extern "C" uint32_t start(int y, uint32_t tile, int64_t m0, int64_t n0, int64_t columns) {
+    return y ? rmm::start_of_place(m0, n0, columns) : rmm::start_of_tile(tile);
+}
 """
 
 
 @pytest.fixture(scope="module")
-def range_bytes(tmp_path_factory):
+def built(tmp_path_factory):
     if shutil.which("g++") is None:
         pytest.skip("no host compiler")
     where = tmp_path_factory.mktemp("range")
@@ -30,7 +33,12 @@ def range_bytes(tmp_path_factory):
     with open(src, "w") as f:
         f.write(SOURCE % HEADER)
     subprocess.run(["g++", "-std=c++17", "-shared", "-fPIC", src, "-o", lib], check=True)
-    f = ctypes.CDLL(lib).range_bytes
+    return ctypes.CDLL(lib)
+
+
+@pytest.fixture(scope="module")
+def range_bytes(built):
+    f = built.range_bytes
     f.restype, f.argtypes = ctypes.c_int64, [ctypes.c_int, ctypes.c_int] + [ctypes.c_int64] * 5
     return f
 
@@ -53,3 +61,20 @@ def test_ranges_end_with_the_last_element(range_bytes, es, krows):
                 continue
             last = first + ((min(rows - row0, tile) - 1) * ld + left - 1 if krows else (left - 1) * ld + rows - row0 - 1)
             assert base % 4 == 0 and base + reach == (last * es + es + 3) // 4 * 4 <= end, (outer, ld, row0, done)
+
+
+def test_eight_neighbouring_tiles_start_at_the_same_step(built):
+    """dX and others: on tiles of any size.  Y: on 256 x 256 tiles, and every smaller tile starts as the one that it lies in."""
+    rows, columns, group = 8192, 1304, 8
+    starts = {}
+    for edge in (256, 128, 64):
+        tiles_m, tiles_n = -(-rows // edge), -(-columns // edge)
+        for tile in range(tiles_m * tiles_n):                   # bands of eight tile rows, column by column
+            band, in_band = divmod(tile, group * tiles_n)
+            m0, n0 = (band * group + in_band % group) * edge, in_band // group * edge
+            where = (ctypes.c_uint32(tile), ctypes.c_int64(m0), ctypes.c_int64(n0), ctypes.c_int64(columns))
+            assert built.start(0, *where) == tile // group
+            y = built.start(1, *where)
+            assert y == starts.setdefault((m0 // 256, n0 // 256), y)
+            if edge == 256:
+                assert y == tile // group, tile
