@@ -668,7 +668,9 @@ __device__ __forceinline__ void plain_tile(const PlainArgs &g, bf16_t *lds, int6
 // product (first: they are the long ones), `colsum_blocks` column blocks of the bias gradient and
 // the tiles of the plain product.  Any of the three may be absent.
 // (The operand of the sketch product is the plain product's A.  bf16: 128 registers, so that two work-groups share a compute unit;
-// with the 133 that the compiler takes otherwise the backward launch of 3000 x 768 -> 1001, k = 300, is 46 us instead of 32.)
+// with the 133 that the compiler takes otherwise the backward launch of 3000 x 768 -> 1001, k = 300, is 46 us instead of 32.  The Gaussian
+// forms for rows of 2^22 elements and more, 147 otherwise, have 7 and 10 of them in scratch memory and are faster for the bound too:
+// backward 64 x 2^22 -> 8, k = 4, 2.8 ms instead of 4.0, forward 300 x 2^22 -> 8 60.7 instead of 62.2.)
 template <typename T, typename S, typename SS, int SKETCH, int BMODE, int MODE_A, int MODE_B>
 __global__ void __launch_bounds__(kPlainThreads, sizeof(T) == 2 ? 4 : 2) plain_pass_kernel(PlainArgs ga, PlainArgs gs, ColsumArgs gc, int plain_blocks,
                                                                    int sketch_blocks, int colsum_blocks) {
