@@ -514,6 +514,12 @@ inline int64_t plain_tiles(int cfg, int64_t m, int64_t n) {
     return tiles_of(m, n, e, e);
 }
 
+// Whether an unsliced k x d sketch product beside plain tiles of `cfg` is on 32 x 32 tiles.  They generate every entry four times as often as
+// 32 x 128 tiles: only where those are few.
+inline bool plain_sketch_small(int cfg, int64_t k, int64_t d) {
+    return cfg == PLAIN_TINY || (cfg == PLAIN_MID && tiles_of(k, d, 32, 128) < 64);
+}
+
 // Tile of dX beside G in an fp32 pass.  Beside 64 x 64 tiles few sketch tiles are 32 x 32, beside 128 x 128 tiles all are 32 x 128,
 // which take 21 ns a token instead of 9 (+-1 entries 12.5 and 5.4): the larger tile only where that stays below what 64 x 64 tiles
 // of dX take, half a round more than there are and 3.5 us and 18.5 ns a contraction element each (3308 x 609 -> 264, k = 331: backward
@@ -562,7 +568,7 @@ inline PlainSlices plain_slices_beside(int cfg, int64_t n, int64_t d, int64_t k,
                  plain_work = chain * (double)plain_tiles(cfg, n, d_other) * per_cu;
     const double narrow = (kind == 0 ? 9e-3 : 4.8e-3) * (double)n, wide = (kind == 0 ? 15e-3 : 9e-3) * (double)n,
                  wide_work = (kind == 0 ? 12e-3 : 6.5e-3) * (double)n * (double)tiles;
-    const bool small = cfg == PLAIN_TINY || (cfg == PLAIN_MID && tiles < 64);  // (launch_pass)
+    const bool small = plain_sketch_small(cfg, k, d);
     auto longest = [&](double sketch_chain, double sketch_work) {
         const double tile = sketch_chain > chain ? sketch_chain : chain, all = plain_work + sketch_work * per_cu;
         return tile > all ? tile : all;

@@ -32,8 +32,7 @@ hipError_t launch_pass(PlainLaunch &p, bool has_plain, bool has_sketch, bool b_r
     p.sketch_blocks = 0;
     p.sketch_small = false;
     if (has_sketch) {
-        // 32 x 32 tiles generate every entry four times as often as 32 x 128 tiles: only where those are few
-        p.sketch_small = mode == 0 || (p.gs.slices <= 1 && (cfg == PLAIN_TINY || (cfg == PLAIN_MID && tiles_of(p.gs.M, p.gs.N, 32, 128) < 64)));
+        p.sketch_small = mode == 0 || (p.gs.slices <= 1 && plain_sketch_small(cfg, p.gs.M, p.gs.N));
         p.sketch_blocks = (int)tiles_of(p.gs.M, p.gs.N, 32, p.sketch_small ? 32 : 128) * (p.gs.slices > 1 ? p.gs.slices : 1);
     }
     if constexpr (sizeof(T) == 2) {

@@ -42,8 +42,9 @@ def test_fp32_large_tiles_of_the_gradients(shape):
     check_layer(X, W, dY, k, rmm.RADEMACHER, 0x5EED0033, 5, "f32", label="f32 large %s" % (shape,))
 
 
-# One to five LDS tiles along a contraction, the last one whole, ragged or a single element: dX and Y on 128 x 128 tiles (of 32
-# elements), on 64 x 64 (64), all products on 32 x 32 (128), X_proj and G on 32 x 128 (64 tokens)
+# One to five LDS tiles along a contraction, the last one whole, ragged or a single element: dX on 128 x 128 tiles (of 32
+# elements) and on 64 x 64 (64) with an odd number of them, Y with an even one, products on 32 x 32 (128) and X_proj on 32 x 128 (64 tokens;
+# bf16: most of them in slices).  (LDS_TILES has the others.)
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("shape", [(2041, 1929, 32, 9), (2041, 64, 1929, 9), (2041, 1929, 65, 9), (2041, 128, 1929, 9), (2041, 1929, 129, 9),
                                    (1100, 1031, 64, 9), (1100, 65, 1031, 9), (1100, 1031, 192, 9), (1100, 256, 1031, 9), (1100, 1031, 257, 9),
@@ -55,6 +56,26 @@ def test_every_number_of_lds_tiles(shape, dtype):
     X, W, dY = synth.layer_inputs(n, d_in, d_out, dtype, (n, d_in + 1, d_out + 2), w_std=1.0 / math.sqrt(d_in))
     check_layer(X, W, dY, k, rmm.RADEMACHER if n in (192, 512) else rmm.GAUSSIAN, 0x5EED0034, 7, dtype,
                 label="%s %s" % (dtype, shape))
+
+
+# Two and three LDS tiles along the contraction, whole and ragged, of every product on every tile it can run with, and of the sketch products
+# one and four too, in either type (test_launch_plans.py: these shapes have them)
+LDS_TILES = [(16, 2049, 1473, 40), (31, 1500, 2049, 65), (32, 1473, 2049, 96), (32, 2041, 1929, 64), (33, 192, 17001, 192),
+             (64, 300, 17001, 700), (64, 17001, 300, 700), (65, 95, 17001, 95), (65, 128, 8201, 97), (65, 385, 9001, 500),
+             (65, 17001, 40, 129), (97, 5505, 385, 512), (128, 256, 300, 300), (128, 300, 8201, 700), (128, 5505, 512, 512),
+             (128, 17001, 65, 96), (140, 300, 5505, 700), (140, 5505, 300, 700), (160, 150, 150, 129), (191, 5505, 192, 128),
+             (192, 300, 5505, 700), (192, 5505, 300, 700), (256, 300, 4201, 700), (256, 384, 31, 65), (256, 8201, 33, 95),
+             (300, 257, 384, 384), (384, 31, 256, 32), (512, 31, 33, 256), (1473, 64, 2049, 16), (1473, 96, 2049, 96),
+             (1473, 2049, 64, 31), (1473, 2049, 96, 16), (1929, 65, 1929, 16), (2041, 2041, 33, 31), (2049, 33, 1500, 33),
+             (2049, 500, 128, 40), (5505, 160, 129, 40), (9001, 65, 100, 16), (9001, 384, 65, 16)]
+
+
+@pytest.mark.parametrize("shape", LDS_TILES)
+def test_odd_and_even_numbers_of_lds_tiles(shape):
+    n, d_in, d_out, k = shape
+    for dtype in ("f32", "bf16"):
+        X, W, dY = synth.layer_inputs(n, d_in, d_out, dtype, (n, d_in + 1, d_out + 2), w_std=1.0 / math.sqrt(d_in))
+        check_layer(X, W, dY, k, rmm.GAUSSIAN, 0x5EED0035, 7, dtype, label="%s %s" % (dtype, shape))
 
 
 @pytest.mark.parametrize("kind", [rmm.GAUSSIAN, rmm.RADEMACHER, rmm.SORS])

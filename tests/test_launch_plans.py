@@ -12,6 +12,7 @@ import paper_2201_13195_amd as rmm
 import test_gpu_few_tiles
 import test_gpu_large_tiles
 import test_gpu_pair_plans
+import test_gpu_plain
 import test_gpu_plain_tiles
 import test_gpu_sketch_slices
 import test_gpu_sors
@@ -42,6 +43,16 @@ int pass_plan(int64_t n, int64_t d_sk, int64_t d_other, int64_t k, int kind, int
     const PassPlan p = plan_pass(n, d_sk, d_other, k, kind);
     put(p.sketch, o);
     return p.plain.cfg;
+}
+// the tile of Y and of dX, whether the sketch product beside it is on 32 x 32 tiles, tokens of one of its tiles; the tile of dW
+void odd_products(int64_t es, int64_t n, int64_t d_in, int64_t d_out, int64_t k, int kind, int64_t *o) {
+    for (int b = 0; b < 2; ++b) {
+        const int64_t d = b ? d_out : d_in, other = b ? d_in : d_out;
+        PlainSlices c{1, n, 0, 0, es == 4 && b ? plain_backward_cfg_f32(n, d_in, d_out, k, kind) : plain_cfg((int)es, n, other, b != 0)};
+        if (es == 2 && (d & 7) == 0) c = plain_slices(n, d, k, other, kind, b != 0);
+        *o++ = c.cfg, *o++ = c.slices <= 1 && plain_sketch_small(c.cfg, k, d), *o++ = c.slices > 1 ? c.chunk : n;
+    }
+    *o = plain_cfg((int)es, d_out, d_in, true);
 }
 int f32_tile(int64_t n, int64_t d_in, int64_t d_out, int64_t k, int64_t kind) { return plain_backward_cfg_f32(n, d_in, d_out, k, (int)kind); }
 int sors_order(int64_t n, int64_t d_sk, int64_t d_other, int64_t k) { return plan_sors(n, d_sk, d_other, k).order; }
@@ -271,3 +282,25 @@ def test_short_transforms_are_no_longer_than_they_have_to_be(plans):
     f.restype = ctypes.c_int64
     points = {n: f(ctypes.c_int64(n)) for n in (1, 8, 300, 512, 513, 1024, 1025, 2048, 2049, 4097, 32768)}
     assert points == {1: 512, 8: 512, 300: 512, 512: 512, 513: 1024, 1024: 1024, 1025: 2048, 2048: 2048, 2049: 4096, 4097: 8192, 32768: 32768}
+
+
+def test_odd_width_and_fp32_products_reach_every_number_of_lds_tiles(plans):
+    """Two and three along the contraction, whole and ragged; of the sketch products also one and four whole ones."""
+    elements = {"128x128": 32, "64x64": 64, "32x32": 128, "32x128": 64}
+    seen = set()
+    for shape in test_gpu_plain.LDS_TILES:
+        assert shape[1] % 8 != 0 or shape[2] % 8 != 0                            # (bf16: off the MFMA kernels)
+        for es in (4, 2):
+            o = (ctypes.c_int64 * 7)()
+            plans.lib.odd_products(ctypes.c_int64(es), *map(ctypes.c_int64, shape), ctypes.c_int(rmm.GAUSSIAN), o)
+            for product, tile, length in (("Y", o[0], shape[1]), ("dX", o[3], shape[2]), ("dW", o[6], shape[3])):
+                tile = ("128x128", "64x64", "32x32")[tile]
+                seen.add((es, product, tile, -(-length // elements[tile]), length % elements[tile] == 0))
+            for product, small, length in (("X_proj", o[1], o[2]), ("G", o[4], o[5])):
+                tile = "32x32" if small else "32x128"
+                seen.add((es, product, tile, -(-length // elements[tile]), length % elements[tile] == 0))
+    for es in (4, 2):
+        for count, whole in ((2, True), (2, False), (3, True), (3, False)):
+            assert {(es, p, t, count, whole) for p in ("Y", "dX", "dW") for t in ("128x128", "64x64", "32x32")} <= seen, (es, count, whole)
+        for count, whole in ((1, True), (2, True), (2, False), (3, True), (3, False), (4, True)):
+            assert {(es, p, t, count, whole) for p in ("X_proj", "G") for t in ("32x128", "32x32")} <= seen, (es, count, whole)

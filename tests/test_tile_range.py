@@ -18,6 +18,12 @@ extern "C" int64_t range_bytes(int es, int krows, int64_t rows_left, int64_t til
     return krows ? rmm::tile_range_bytes<4, true>(rows_left, tile_rows, ld, left, skew)
                  : rmm::tile_range_bytes<4, false>(rows_left, tile_rows, ld, left, skew);
 }
+extern "C" uint32_t range_bytes_32(int es, int krows, uint32_t rows_left, uint32_t tile_rows, uint32_t ld, uint32_t left, uint32_t skew) {
+    if (es == 2) return krows ? rmm::tile_range_bytes<2, true>(rows_left, tile_rows, ld, left, skew)
+                              : rmm::tile_range_bytes<2, false>(rows_left, tile_rows, ld, left, skew);
+    return krows ? rmm::tile_range_bytes<4, true>(rows_left, tile_rows, ld, left, skew)
+                 : rmm::tile_range_bytes<4, false>(rows_left, tile_rows, ld, left, skew);
+}
 extern "C" uint32_t start(int y, uint32_t tile, int64_t m0, int64_t n0, int64_t columns) {
     return y ? rmm::start_of_place(m0, n0, columns) : rmm::start_of_tile(tile);
 }
@@ -61,6 +67,23 @@ def test_ranges_end_with_the_last_element(range_bytes, es, krows):
                 continue
             last = first + ((min(rows - row0, tile) - 1) * ld + left - 1 if krows else (left - 1) * ld + rows - row0 - 1)
             assert base % 4 == 0 and base + reach == (last * es + es + 3) // 4 * 4 <= end, (outer, ld, row0, done)
+
+
+@pytest.mark.parametrize("es", [2, 4])
+@pytest.mark.parametrize("krows", [True, False])
+def test_ranges_in_32_bits_are_those_in_64(built, range_bytes, es, krows):
+    """The kernels compute them in 32 bits: tiles of 128 rows (or 128 contraction rows) of up to 2^22 - 1 elements."""
+    f = built.range_bytes_32
+    f.restype, f.argtypes = ctypes.c_uint32, [ctypes.c_int, ctypes.c_int] + [ctypes.c_uint32] * 5
+    most = 0
+    for ld in (1, 7, 1001, (1 << 21) + 1, (1 << 22) - 1):
+        for rows_left in {1, 2, 127, 128, 129, 2 ** 31 - 1} if krows else {1, ld // 2 + 1, ld}:
+            for left in (0, 1, 2, 127, 128):
+                for skew in ((0, 1) if es == 2 else (0,)):
+                    want = range_bytes(es, krows, rows_left, 128, ld, left, skew)
+                    assert f(es, krows, rows_left, 128, ld, left, skew) == want < 1 << 31, (rows_left, ld, left, skew)
+                    most = max(most, want)
+    assert most > 0.99 * (1 << 31) * es / 4
 
 
 def test_eight_neighbouring_tiles_start_at_the_same_step(built):
