@@ -37,7 +37,8 @@ __device__ __forceinline__ int kcontig_offset(int row0, int kk0, int lane) {  //
 }
 template <int BK>
 __device__ __forceinline__ bf16x8_t frag_kcontig(const bf16_t *tile, int row0, int kk0, int lane) {
-    return *reinterpret_cast<const bf16x8_t *>(tile + kcontig_offset<BK>(row0, kk0, lane));
+    const int row = row0 + (lane & 31), chunk = (kk0 >> 3) + (lane >> 5);
+    return *reinterpret_cast<const bf16x8_t *>(tile + row * BK + kchunk_pos<BK>(row, chunk) * 8);
 }
 
 // Same fragment from a tile stored [contraction row][column]: two transposing
@@ -61,7 +62,8 @@ __device__ __forceinline__ bf16x8_t frag_transposed(lds_patch_t rows, lds_patch_
     return out.v;
 }
 __device__ __forceinline__ bf16x8_t frag_transposed(const bf16_t *tile, int stride, int col0, int kk0, int lane) {
-    const bf16_t *p = tile + transposed_offset(stride, col0, kk0, lane);
+    const int blk = lane >> 4, i = lane & 15;
+    const bf16_t *p = tile + (kk0 + ((blk >> 1) << 3) + (i >> 2)) * stride + col0 + ((blk & 1) << 4) + ((i & 3) << 2);
     return frag_transposed((lds_patch_t)(p), (lds_patch_t)(p + 4 * stride));
 }
 
