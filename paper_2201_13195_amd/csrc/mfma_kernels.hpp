@@ -279,10 +279,11 @@ __device__ __forceinline__ u32x4_t rows_descriptor(const bf16_t *base, int64_t l
                      (uint32_t)__builtin_amdgcn_readfirstlane((int)((rows > 0 ? rows : 0) * ld * 2)), 0x00020000u};
 }
 // The wait states between a vector instruction that writes a scalar register (a readfirstlane, a spilled one that comes back) and a
-// load that reads it: the compiler does not look for them in front of load_to_lds.  So the scalar registers of a load are written in
-// front of one of these and nowhere behind it.
+// load that reads it: the compiler does not look for them in front of load_to_lds.  What a step of a K-contiguous operand writes (the range
+// of its descriptor, the offset along its rows) is scalar instructions, which need none, and is not settled: twenty clocks a step and
+// operand, 64 x 64 tiles of Y 5 % (1024 x 1024 -> 512 5.8 and 6.1 us).  That the compiler brings none of it back from a vector register too
+// close to a load is looked for in the built library (tests/test_load_hazards.py).
 __device__ __forceinline__ void settle(u32x4_t &descriptor) { asm volatile("s_nop 4" : "+s"(descriptor)); }
-__device__ __forceinline__ void settle(u32x4_t &descriptor, uint32_t &soff) { asm volatile("s_nop 4" : "+s"(descriptor), "+s"(soff)); }
 // The steps of 64 contraction elements in the order in which a work-group takes them: from `start` on and around.  What a request
 // needs is prepared one step ahead, between MFMAs, from what the one before it needed, in scalar registers and mostly 32 bits.  Made
 // anew, with products of 64 bits, selects and a way through the vector unit, it was 45 of the 62 scalar instructions of a step of
@@ -387,7 +388,7 @@ struct OperandLoads {
     __device__ __forceinline__ void begin(uint32_t to_) {
         to = to_, soff = ready_soff;
         if constexpr (KROWS) {
-            rsrc[2] = ready[2], oob = ready_oob, settle(rsrc, soff);
+            rsrc[2] = ready[2], oob = ready_oob;
         } else {
             rsrc = ready, settle(rsrc);
         }

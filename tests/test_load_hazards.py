@@ -1,6 +1,6 @@
 """CPU: the loads into LDS that are written as assembly (load_to_lds), in the code objects of the built library.  Between a vector
-instruction that writes a scalar register and a load that reads it the hardware wants five wait states, and nobody counts them in
-front of these loads but settle(): whatever writes their scalar registers stands in front of it."""
+instruction that writes a scalar register and a load that reads it the hardware wants five wait states, and the compiler does not
+count them in front of these loads."""
 import glob
 import os
 import re
@@ -12,7 +12,6 @@ import pytest
 import paper_2201_13195_amd as rmm
 
 OBJDUMP = "/opt/rocm/llvm/bin/llvm-objdump"
-NO_RESULT = ("s_cmp", "s_bitcmp", "s_branch", "s_cbranch", "s_barrier", "s_waitcnt", "s_nop", "s_endpgm", "buffer_", "ds_", "global_", "flat_", "scratch_")
 
 
 def scalars(operand):
@@ -21,8 +20,9 @@ def scalars(operand):
 
 
 def written(instruction):
+    """Scalar registers that a vector instruction writes."""
     op, _, rest = instruction.partition(" ")
-    if op.startswith(NO_RESULT):
+    if not op.startswith("v_"):
         return set()
     operands = rest.split(",")
     two = op.startswith(("v_mad_u64", "v_mad_i64", "v_div_scale")) or "_co_" in op       # (their carry is a second result)
@@ -30,7 +30,8 @@ def written(instruction):
 
 
 def early_writes(text):
-    """(loads into LDS, those whose scalar registers are written in the five wait states before them), in program order."""
+    """(loads into LDS, those whose scalar registers a vector instruction writes in the five wait states before them), in
+    program order."""
     code = [re.sub(r"\s+", " ", line.split("//")[0]).strip() for line in text.split("\n")]
     code = [c for c in code if c and not c.endswith(":")]
     loads = [i for i, c in enumerate(code) if c.startswith("buffer_load") and c.endswith(" lds")]
@@ -48,9 +49,11 @@ def early_writes(text):
 
 
 def test_the_scan_sees_a_write():
-    settled = "s_mov_b32 s10, s53\n s_nop 4\n s_mov_b32 m0, s2\n s_nop 0\n buffer_load_dwordx4 v1, s[8:11], s4 offen lds\n"
+    settled = "v_readfirstlane_b32 s10, v1\n s_nop 4\n s_mov_b32 m0, s2\n s_nop 0\n buffer_load_dwordx4 v1, s[8:11], s4 offen lds\n"
     assert early_writes(settled) == (1, [])
-    for w in ("s_mov_b32 s10, s53", "v_readlane_b32 s4, v9, 3", "v_mad_u64_u32 v[2:3], s[8:9], v4, v5, 0"):
+    for w in ("v_add_u32 v2, s10, v3", "s_mov_b32 s10, s53", "v_readlane_b32 s9, v9, 3\n s_nop 2", "v_mov_b32 v10, v4"):
+        assert early_writes(settled.replace("v_readfirstlane_b32 s10, v1\n s_nop 4", w)) == (1, []), w
+    for w in ("v_readlane_b32 s4, v9, 3", "v_mad_u64_u32 v[2:3], s[8:9], v4, v5, 0", "v_readlane_b32 s9, v9, 3\n s_nop 1"):
         assert len(early_writes(settled.replace("s_nop 4", w))[1]) == 1, w
 
 
