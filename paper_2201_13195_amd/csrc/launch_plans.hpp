@@ -400,9 +400,9 @@ struct SorsPlan {
 //   SORS_BEHIND   two strips to a work-group, on the compute units that the last round of 256 x 256 or 128 x 128 tiles leaves, 32 or more
 //   SORS_FRONT    the same in front of three or more rounds of tiles, on at most a quarter of the chip
 //   SORS_APART    launches of their own
-// The first by times fitted to 180 passes (513 to 16384 tokens, widths 256 to 4096, inputs that change from step to step).  Over these 90
-// steps, dW included, it is 8.9 % faster than the others alone, at worst 1.4 % slower; with hindsight 9.9 %.  (2275 x 312 -> 584, k = 455: a
-// step 36.5 -> 25.5 us, 2907 x 1248 -> 1136 59.1 -> 44.5, 4250 x 1232 -> 864 71 -> 55.  Not where 256 x 256 tiles fill the chip, whose
+// The first by times fitted to 180 passes (513 to 16384 tokens, widths 256 to 4096).  Over 1517 others, 256 to 32768 tokens, passes
+// take 0.890 of the time that they take with the others alone, dW included; 20 of them are more than 3 % longer, 1.17 at most; with
+// hindsight 0.878.  (2275 x 312 -> 584, k = 455: a step 36.5 -> 25.5 us, 2907 x 1248 -> 1136 59.1 -> 44.5, 4250 x 1232 -> 864 71 -> 55.  Not where 256 x 256 tiles fill the chip, whose
 // operands cost half the L2 traffic: 15053 x 2264 -> 3112 500 against 626; nor beside few tiles of a long contraction, which other
 // tiles have more work-groups for: 3277 x 3480 -> 272 73 against 97.)  Of 100 passes of 1 to 512 tokens, widths
 // 256 to 4096, it takes 20, which are 0.64 to 0.87 of the time that they were apart.
@@ -419,23 +419,31 @@ inline SorsPlan plan_sors(int64_t n, int64_t d_sk, int64_t d_other, int64_t k) {
     const int64_t l = sors_log(n), strips = d_sk / 8, pairs = (strips + 1) / 2;
     if (l > 15 || (l >= 12 && k > kSorsAccMaxK)) return best;
     const double steps = (double)((d_sk + 63) / 64), chunks = l < 11 ? 0.6 : (double)sors_chunks(n);
+    const GemmChoice apart = choose_gemm(n, d_other, d_sk);
     double best_us;
     if (best.order != SORS_APART) {
         const double tile = plain.cfg == GEMM_LARGE ? 6.7 + 1.405 * steps : 3.4 + 0.487 * steps, two = 2.5 + 5.5 * chunks;
         best_us = 2.0 + (best.order == SORS_BEHIND ? makespan(plain.tiles, tile, pairs, two, 256) : makespan(pairs, two, plain.tiles, tile, 256));
     } else {
-        best_us = choose_gemm(n, d_other, d_sk).us + 5.4 + 2.2 * chunks * (strips <= 512 ? 1.0 : (double)strips / 512.0);
+        best_us = apart.us + 5.4 + 2.2 * chunks * (strips <= 512 ? 1.0 : (double)strips / 512.0);
     }
     const PairPlain compact{GEMM_COMPACT, (int)gemm_tiles(GEMM_COMPACT, n, d_other)};
-    const double strip = 3.8 + 2.5 * chunks, alone = 3.2 + 0.618 * steps;
-    double us = 2.5;
-    if (compact.tiles + strips <= 256)
-        us += alone > strip ? alone : strip;
-    else if (compact.tiles <= 256 && compact.tiles + strips <= 512)  // (some tiles start beside a strip)
-        us += alone + 0.41 * strip;
-    else
-        us += makespan(compact.tiles, 3.8 + 0.836 * steps, strips, 3.8 + 3.9 * chunks, 512);
-    return us < (plain.cfg == GEMM_LARGE ? 0.9 : 1.0) * best_us ? SorsPlan{SORS_COMPACT, compact} : best;
+    const double strip = 3.8 + 2.5 * chunks, alone = 3.2 + 0.618 * steps, limit = (plain.cfg == GEMM_LARGE ? 0.9 : 1.0) * best_us;
+    const SorsPlan shared{SORS_COMPACT, compact};
+    if (compact.tiles + strips <= 256) return 2.5 + (alone > strip ? alone : strip) < limit ? shared : best;
+    if (compact.tiles <= 256 && compact.tiles + strips <= 512) return 2.5 + alone + 0.41 * strip < limit ? shared : best;  // (some tiles start beside a strip)
+    if (2.5 + makespan(compact.tiles, 3.8 + 0.836 * steps, strips, 3.8 + 3.9 * chunks, 512) >= limit) return best;
+    // More work-groups than places: also by times taken since tiles of 256 columns have become faster than these, with two of these on a
+    // compute unit told from one beside a strip (fitted to 311 forward passes that come here).  Of those and 260 backward passes 17 take more than 3 %
+    // longer than with the others above, 1.17 of their time at most; without this second look 52, 1.32 at most (4187 x 3016 -> 2280, k = 419:
+    // 113 and 86 us).  Of 500 passes that none of it was fitted to 4 take that
+    // much longer than before there was a shared launch, 1.14 at most.  All 571 are 0.5 % shorter for it on average.
+    const double two = compact.tiles <= 256 ? 0.0 : compact.tiles >= 512 ? 1.0 : (double)(compact.tiles - 256) / 256.0;
+    const double now = 2.5 + makespan(compact.tiles, 3.5 + (0.832 + 0.279 * two) * steps, strips, 6.0 + 3.37 * chunks, 512);
+    const double other = best.order != SORS_APART ? (plain.cfg == GEMM_LARGE ? 1.017 : 1.033) * best_us
+                                                  : (apart.cfg == GEMM_LARGE ? 0.886 : apart.cfg == GEMM_WIDE ? 0.944 : 1.122) * apart.us + 4.2 +
+                                                        (strips <= 256 ? 2.82 : 3.98 + 1.08 * (double)(strips - 256) / 256.0) * chunks;
+    return now < (apart.cfg == GEMM_LARGE ? 0.97 : 1.03) * other ? shared : best;
 }
 
 // Whether the bias gradient's column sums go with dW: beside it where its launch has room (64 compute units idle in the last round,

@@ -304,3 +304,15 @@ def test_odd_width_and_fp32_products_reach_every_number_of_lds_tiles(plans):
             assert {(es, p, t, count, whole) for p in ("Y", "dX", "dW") for t in ("128x128", "64x64", "32x32")} <= seen, (es, count, whole)
         for count, whole in ((1, True), (2, True), (2, False), (3, True), (3, False), (4, True)):
             assert {(es, p, t, count, whole) for p in ("X_proj", "G") for t in ("32x128", "32x32")} <= seen, (es, count, whole)
+
+
+def test_strips_do_not_share_compute_units_with_rounds_of_tiles_that_wider_ones_serve(plans):
+    """Where tiles of 256 columns serve the plain product and 128 x 128 ones would stand two to a compute unit, these passes were up to
+    a third longer with them; where they have a place beside a strip the pass is shorter."""
+    def order(*a):
+        return ("apart", "behind", "front", "compact")[plans.lib.sors_order(*map(ctypes.c_int64, a))]
+
+    for shape in ((4187, 3016, 2280, 419), (6415, 1944, 3200, 641), (6552, 1944, 1288, 1310), (6717, 2584, 1232, 671), (6983, 2904, 2360, 1396)):
+        assert order(*shape) != "compact", shape
+    for shape in ((2275, 312, 584, 455), (2907, 1248, 1136, 290), (4250, 1232, 864, 425), (3001, 520, 768, 600), (1500, 320, 2048, 150)):
+        assert order(*shape) == "compact", shape
