@@ -408,14 +408,16 @@ __device__ __forceinline__ void plain_tile(const PlainArgs &g, bf16_t *lds, int6
         asked += BK;
     };
     // Tile t (in register set `set`) goes into LDS stage `set` in units: those of the loaders; the request of tile t + 2 into the same
-    // registers; then those of a generated tile, which is made here, one chunk of eight tokens of a sketch column per thread (half of the
-    // Philox rounds, or a pair of entries), the waves taking turns where the tile has fewer chunks than the work-group
-    // threads.  AHEAD: a chunk is begun one tile before the one that its wave has to finish it for, so that all waves generate all the
-    // time (4096 x 3072, k = 410 fp32 alone 206 -> 197 us).  Entries beyond the operand meet zeros of B or are not stored.
+    // registers; and those of a generated tile, which is made here, one chunk of eight tokens of a sketch column per thread, the waves
+    // taking turns where the tile has fewer chunks than the work-group threads.  Entries beyond the operand meet zeros of B or are not
+    // stored.  A chunk is one unit, the first, where a step is few MFMAs: cut up between these, or behind the rest, its instructions wait for
+    // each other (3318 x 1145, k = 663 alone, bf16 50.3 us in pieces, 43.5 in one; +-1 entries 29.3 and 26.9, fp32 51.3 and 46.6).
+    // PIECES: last and in units of half of the Philox rounds, or a pair of entries.  AHEAD: a chunk is begun one tile before the one that its
+    // wave has to finish it for, so that all waves generate all the time (4096 x 3072, k = 410 fp32 alone 206 -> 197 us).
     constexpr int CALLS = BM * BK / 8, TURNS = GEN ? kPlainThreads / CALLS : 1;
     static_assert(!GEN || (CALLS % 64 == 0 && TURNS * CALLS == kPlainThreads && TURNS <= 2), "whole waves take turns, by the stage");
-    constexpr bool AHEAD = AMODE == PA_GAUSS && TURNS == 2 && PB == 3;
-    constexpr int GEN_UNITS = AMODE == PA_GAUSS ? (AHEAD ? 3 : 6) : GEN ? 1 : 0, A_UNITS = GEN ? 0 : LoadA::UNITS, B_UNITS = LoadB::UNITS,
+    constexpr bool PIECES = AMODE == PA_GAUSS && PB == 3, AHEAD = PIECES && TURNS == 2;
+    constexpr int GEN_UNITS = PIECES ? (AHEAD ? 3 : 6) : GEN ? 1 : 0, A_UNITS = GEN ? 0 : LoadA::UNITS, B_UNITS = LoadB::UNITS,
                   UNITS = B_UNITS + A_UNITS + 1 + GEN_UNITS;
     const int gen_j = tid % CALLS / (BK / 8), gen_k = tid % CALLS % (BK / 8);
     uint32_t gen_to[2] = {};
@@ -450,6 +452,19 @@ __device__ __forceinline__ void plain_tile(const PlainArgs &g, bf16_t *lds, int6
         }
     };
     auto put = [&](int unit, int set, uint32_t t) __attribute__((always_inline)) {
+        if constexpr (GEN && !PIECES) {
+            if (unit == 0) {
+                if (TURNS == 2 && turn() != set) return;
+                if constexpr (AMODE == PA_SIGN) {
+                    *lds_at<bf16x8_t>(gen_to[set]) = sign_eight(g.kind, g.st, token(t), column);
+                } else {
+#pragma unroll
+                    for (int part = 0; part < 6; ++part) generate(part, set, t);
+                }
+                return;
+            }
+            unit -= 1;
+        }
         if (unit < B_UNITS) return lb.store(unit, vb[set], set, left_of(t * BK));
         unit -= B_UNITS;
         if constexpr (!GEN) {
@@ -458,11 +473,9 @@ __device__ __forceinline__ void plain_tile(const PlainArgs &g, bf16_t *lds, int6
         unit -= A_UNITS;
         if (unit == 0) return issue(set);
         unit -= 1;
-        if constexpr (AMODE == PA_SIGN) {
-            if (TURNS == 1 || turn() == set) *lds_at<bf16x8_t>(gen_to[set]) = sign_eight(g.kind, g.st, token(t), column);
-        } else if constexpr (GEN) {
+        if constexpr (PIECES) {
             if (!AHEAD) {
-                if (TURNS == 1 || turn() == set) generate(unit, set, t);
+                generate(unit, set, t);
             } else if (turn() == set) {
                 generate(unit + 3, set, t);
             } else {
@@ -513,7 +526,7 @@ __device__ __forceinline__ void plain_tile(const PlainArgs &g, bf16_t *lds, int6
     // Two LDS stages, two register sets.  Between two barriers tile t is multiplied, t + 1 goes into LDS and t + 3 is requested (past
     // the end: zeros).  DEFER: a tile's barrier stands in front of the last step of the tile before it.  By then every wave holds
     // that step's fragments, so the stage can be written again, and the first fragments of the new tile are read under the last
-    // step's MFMAs.  Where a product is several MFMAs everything else is dealt between them (sched_barrier); in one piece it stands
+    // step's MFMAs.  Where a product is eight MFMAs everything else is dealt between them (sched_barrier); in one piece it stands
     // behind the barrier for all waves at once.  Against fetching behind the barrier, same bits: bf16 3000 x 768 -> 1001,
     // k = 300, 61 -> 56 us a step, 209 x 424 -> 351 15.8 -> 13.4, 830 x 472 -> 1269 +-1 35.3 -> 30.4; fp32 4096 x 768 -> 3072 dX and G 284 -> 262,
     // 1906 x 69 -> 135, k = 191, 47.6 -> 44.9.  (What is left of the fp32 tiles' time is issue: a wave of the sketch tile
@@ -548,7 +561,7 @@ __device__ __forceinline__ void plain_tile(const PlainArgs &g, bf16_t *lds, int6
                 }
 #pragma unroll
                 for (int u = dealt(m); u < dealt(m + 1); ++u) put(u, s ^ 1, t + 1);
-                if constexpr (PLANES) __builtin_amdgcn_sched_barrier(0);
+                if constexpr (PA + PB == 6) __builtin_amdgcn_sched_barrier(0);
             }
     };
     typedef std::integral_constant<int, 0> Stage0;
@@ -669,7 +682,7 @@ __device__ __forceinline__ void plain_tile(const PlainArgs &g, bf16_t *lds, int6
 // the tiles of the plain product.  Any of the three may be absent.
 // (The operand of the sketch product is the plain product's A.  bf16: 128 registers, so that two work-groups share a compute unit;
 // with the 133 that the compiler takes otherwise the backward launch of 3000 x 768 -> 1001, k = 300, is 46 us instead of 32.  The Gaussian
-// forms for rows of 2^22 elements and more, 147 otherwise, have 7 and 10 of them in scratch memory and are faster for the bound too:
+// forms for rows of 2^22 elements and more, 147 otherwise, have 9 and 13 of them in scratch memory and are faster for the bound too:
 // backward 64 x 2^22 -> 8, k = 4, 2.8 ms instead of 4.0, forward 300 x 2^22 -> 8 60.7 instead of 62.2.)
 template <typename T, typename S, typename SS, int SKETCH, int BMODE, int MODE_A, int MODE_B>
 __global__ void __launch_bounds__(kPlainThreads, sizeof(T) == 2 ? 4 : 2) plain_pass_kernel(PlainArgs ga, PlainArgs gs, ColsumArgs gc, int plain_blocks,
