@@ -527,7 +527,8 @@ __device__ __forceinline__ void plain_tile(const PlainArgs &g, bf16_t *lds, int6
     // the end: zeros).  DEFER: a tile's barrier stands in front of the last step of the tile before it.  By then every wave holds
     // that step's fragments, so the stage can be written again, and the first fragments of the new tile are read under the last
     // step's MFMAs.  Where a product is eight MFMAs everything else is dealt between them (sched_barrier); in one piece it stands
-    // behind the barrier for all waves at once.  Against fetching behind the barrier, same bits: bf16 3000 x 768 -> 1001,
+    // behind the barrier for all waves at once.  (Not with one step to a tile, where the fragments are read behind the barrier anyway and
+    // the compiler does better: fp32 400 x 3000 -> 500 forward 31.5 and 29.5 us, 834 x 2554 -> 1144 94.7 and 87.1.)  Against fetching behind the barrier, same bits: bf16 3000 x 768 -> 1001,
     // k = 300, 61 -> 56 us a step, 209 x 424 -> 351 15.8 -> 13.4, 830 x 472 -> 1269 +-1 35.3 -> 30.4; fp32 4096 x 768 -> 3072 dX and G 284 -> 262,
     // 1906 x 69 -> 135, k = 191, 47.6 -> 44.9.  (What is left of the fp32 tiles' time is issue: a wave of the sketch tile
     // has an instruction in flight 47 % of the time, and there are two to a SIMD.)
@@ -561,7 +562,7 @@ __device__ __forceinline__ void plain_tile(const PlainArgs &g, bf16_t *lds, int6
                 }
 #pragma unroll
                 for (int u = dealt(m); u < dealt(m + 1); ++u) put(u, s ^ 1, t + 1);
-                if constexpr (PA + PB == 6) __builtin_amdgcn_sched_barrier(0);
+                if constexpr (PA + PB == 6 && DEFER) __builtin_amdgcn_sched_barrier(0);
             }
     };
     typedef std::integral_constant<int, 0> Stage0;
