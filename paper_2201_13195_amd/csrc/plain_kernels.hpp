@@ -407,11 +407,15 @@ __device__ __forceinline__ void plain_tile(const PlainArgs &g, bf16_t *lds, int6
         lb.load(vb[set], left_of(asked));
         asked += BK;
     };
+    constexpr int STEPS = BK / 16 / S::WK;  // 16-deep contraction steps per tile and wave
+    constexpr bool DEFER = STEPS > 1;  // a tile's last step is multiplied behind the next barrier
     // Tile t (in register set `set`) goes into LDS stage `set` in units: those of the loaders; the request of tile t + 2 into the same
     // registers; and those of a generated tile, which is made here, one chunk of eight tokens of a sketch column per thread, the waves
     // taking turns where the tile has fewer chunks than the work-group threads.  Entries beyond the operand meet zeros of B or are not
-    // stored.  A chunk is one unit, the first, where a step is few MFMAs: cut up between these, or behind the rest, its instructions wait for
-    // each other (3318 x 1145, k = 663 alone, bf16 50.3 us in pieces, 43.5 in one; +-1 entries 29.3 and 26.9, fp32 51.3 and 46.6).
+    // stored.  A chunk is one unit where a step is few MFMAs: cut up between these its instructions wait for each other.  It is the first
+    // where tiles have several steps (3318 x 1145, k = 663 alone, bf16 50.3 us in pieces, 43.5 in one; +-1 entries, there behind the rest,
+    // 29.3 and 26.9, fp32 51.3 and 46.6) and the last on tiles of one, which ask for the tile after next first (1000 x 512 -> 513, k = 100
+    // bf16 forward 0.992 of the time).
     // PIECES: last and in units of half of the Philox rounds, or a pair of entries.  AHEAD: a chunk is begun one tile before the one that its
     // wave has to finish it for, so that all waves generate all the time (4096 x 3072, k = 410 fp32 alone 206 -> 197 us).
     constexpr int CALLS = BM * BK / 8, TURNS = GEN ? kPlainThreads / CALLS : 1;
@@ -451,9 +455,10 @@ __device__ __forceinline__ void plain_tile(const PlainArgs &g, bf16_t *lds, int6
             for (int s = 0; s < PA; ++s) *lds_at<bf16x8_t>(gen_to[set] + s * L::A_PLANE * 2) = made.p[s].v;
         }
     };
+    constexpr int CHUNK = DEFER ? 0 : UNITS - 1;
     auto put = [&](int unit, int set, uint32_t t) __attribute__((always_inline)) {
         if constexpr (GEN && !PIECES) {
-            if (unit == 0) {
+            if (unit == CHUNK) {
                 if (TURNS == 2 && turn() != set) return;
                 if constexpr (AMODE == PA_SIGN) {
                     *lds_at<bf16x8_t>(gen_to[set]) = sign_eight(g.kind, g.st, token(t), column);
@@ -463,7 +468,7 @@ __device__ __forceinline__ void plain_tile(const PlainArgs &g, bf16_t *lds, int6
                 }
                 return;
             }
-            unit -= 1;
+            unit -= CHUNK == 0;
         }
         if (unit < B_UNITS) return lb.store(unit, vb[set], set, left_of(t * BK));
         unit -= B_UNITS;
@@ -483,12 +488,10 @@ __device__ __forceinline__ void plain_tile(const PlainArgs &g, bf16_t *lds, int6
             }
         }
     };
-    constexpr int STEPS = BK / 16 / S::WK;  // 16-deep contraction steps per tile and wave
     struct Frags {
         bf16x8_t a[PA][TM], b[PB][TN];
     };
     static_assert(STEPS == 1 || STEPS % 2 == 0, "a tile's last step is in f[1]");
-    constexpr bool DEFER = STEPS > 1;  // a tile's last step is multiplied behind the next barrier
     Frags f[2];
     constexpr int FRAGS = PA * TM + PB * TN;
     constexpr FragmentOrder<PA, PB, TM, TN> order{};
@@ -527,11 +530,14 @@ __device__ __forceinline__ void plain_tile(const PlainArgs &g, bf16_t *lds, int6
     // the end: zeros).  DEFER: a tile's barrier stands in front of the last step of the tile before it.  By then every wave holds
     // that step's fragments, so the stage can be written again, and the first fragments of the new tile are read under the last
     // step's MFMAs.  Where a product is eight MFMAs everything else is dealt between them (sched_barrier); in one piece it stands
-    // behind the barrier for all waves at once.  (Not with one step to a tile, where the fragments are read behind the barrier anyway and
-    // the compiler does better: fp32 400 x 3000 -> 500 forward 31.5 and 29.5 us, 834 x 2554 -> 1144 94.7 and 87.1.)  Against fetching behind the barrier, same bits: bf16 3000 x 768 -> 1001,
-    // k = 300, 61 -> 56 us a step, 209 x 424 -> 351 15.8 -> 13.4, 830 x 472 -> 1269 +-1 35.3 -> 30.4; fp32 4096 x 768 -> 3072 dX and G 284 -> 262,
-    // 1906 x 69 -> 135, k = 191, 47.6 -> 44.9.  (What is left of the fp32 tiles' time is issue: a wave of the sketch tile
-    // has an instruction in flight 47 % of the time, and there are two to a SIMD.)
+    // behind the barrier for all waves at once.  With one step to a tile the fragments are read behind the barrier anyway, and the compiler
+    // does better (fp32 400 x 3000 -> 500 forward 31.5 and 29.5 us, 834 x 2554 -> 1144 94.7 and 87.1) except beside generated entries of
+    // fp32 sketches (2416 x 425 -> 192, k = 242 backward 1.026 and 1.004 of the time of code that fetches behind the barrier).
+    // Against fetching behind the barrier, same bits: bf16 3000 x 768 -> 1001, k = 300, 61 -> 56 us a step, 209 x 424 -> 351 15.8 -> 13.4,
+    // 830 x 472 -> 1269 +-1 35.3 -> 30.4; fp32 4096 x 768 -> 3072 dX and G 284 -> 262, 1906 x 69 -> 135, k = 191, 47.6 -> 44.9.
+    // (What is left of the fp32 tiles' time is issue: a wave of the sketch tile has an instruction in flight 47 % of the time, and there
+    // are two to a SIMD.)
+    constexpr bool HOLD = DEFER ? PA + PB == 6 : GEN && PLANES;
     const uint32_t num = ((uint32_t)len + BK - 1) / BK;
     // Short chains of fp32 tiles: those past the end are not split (256 x 128 -> 128: 18.6 -> 16 us a step).  Elsewhere the
     // branch costs more (Y 4096 x 768 -> 3072: 162 -> 175 us).
@@ -562,7 +568,7 @@ __device__ __forceinline__ void plain_tile(const PlainArgs &g, bf16_t *lds, int6
                 }
 #pragma unroll
                 for (int u = dealt(m); u < dealt(m + 1); ++u) put(u, s ^ 1, t + 1);
-                if constexpr (PA + PB == 6 && DEFER) __builtin_amdgcn_sched_barrier(0);
+                if constexpr (HOLD) __builtin_amdgcn_sched_barrier(0);
             }
     };
     typedef std::integral_constant<int, 0> Stage0;
