@@ -537,7 +537,12 @@ __device__ __forceinline__ void plain_tile(const PlainArgs &g, bf16_t *lds, int6
     // 830 x 472 -> 1269 +-1 35.3 -> 30.4; fp32 4096 x 768 -> 3072 dX and G 284 -> 262, 1906 x 69 -> 135, k = 191, 47.6 -> 44.9.
     // (What is left of the fp32 tiles' time is issue: a wave of the sketch tile has an instruction in flight 47 % of the time, and there
     // are two to a SIMD.)
-    constexpr bool HOLD = DEFER ? PA + PB == 6 : GEN && PLANES;
+    // FUNNEL: what shifts a request into place may not go in front of the barrier before its own: with both sets of the loop shifted at its
+    // top, as the compiler has it, the newer request is waited for as well, right behind its issue (bf16 2132 x 2623 -> 1454 Y 68 us and 54,
+    // 3000 x 1001 -> 768 28.2 and 23.0, 72 x 2461 -> 131, one step to a tile, 12.5 and 11.0).
+    constexpr bool FUNNEL = sizeof(T) == 2 && !GEN && (MODE_A == 3 || MODE_B == 3);
+    constexpr bool HOLD = DEFER ? PA + PB == 6 || FUNNEL : GEN && PLANES;
+    constexpr int MAY_PASS = 0x8C;  // (scalar arithmetic, MFMAs and LDS)
     const uint32_t num = ((uint32_t)len + BK - 1) / BK;
     // Short chains of fp32 tiles: those past the end are not split (256 x 128 -> 128: 18.6 -> 16 us a step).  Elsewhere the
     // branch costs more (Y 4096 x 768 -> 3072: 162 -> 175 us).
@@ -553,6 +558,7 @@ __device__ __forceinline__ void plain_tile(const PlainArgs &g, bf16_t *lds, int6
         auto dealt = [](int x) { return x >= OVER ? MAKE : MAKE * x / OVER; };
         int m = 0;
         __syncthreads();
+        if constexpr (FUNNEL && !DEFER) __builtin_amdgcn_sched_barrier(MAY_PASS);
         if constexpr (FIRST || !DEFER) {
 #pragma unroll
             for (int i = 0; i < FRAGS; ++i) fetch(i, f[0], s, 0);

@@ -1,6 +1,6 @@
-"""CPU: the loads into LDS that are written as assembly (load_to_lds), in the code objects of the built library.  Between a vector
-instruction that writes a scalar register and a load that reads it the hardware wants five wait states, and the compiler does not
-count them in front of these loads."""
+"""CPU: what the compiler made of the loads, in the code objects of the built library.  Those into LDS are written as assembly
+(load_to_lds): between a vector instruction that writes a scalar register and a load that reads it the hardware wants five wait
+states, and the compiler does not count them in front of these loads."""
 import glob
 import os
 import re
@@ -87,3 +87,27 @@ def test_a_sketch_tile_asks_for_its_operand_before_it_generates(code):
         columns = int(re.search(r"ShapeILi\d+ELi(\d+)E", name)[1])
         before = body[:re.search(r"v_mad_u64_u32 (\S+ ){4}0\b", body).start()]        # (with a third operand they make addresses)
         assert before.count(" lds") == columns // 64, name          # 1 KB each, of 64 tokens, from eight waves
+
+
+def loops(body):
+    """The text of the loops of a kernel that are up to 1500 instructions long."""
+    lines = [line for line in body.split("\n") if "//" in line]
+    at = [int(line.split("//")[1].split(":")[0], 16) for line in lines]
+    for i, line in enumerate(lines):
+        back = re.match(r"\s*s_cbranch\S+ (\d+)", line)
+        if back and int(back[1]) >= 1 << 15:
+            start = at[i] + 4 + 4 * (int(back[1]) - (1 << 16))
+            if start in at and i - at.index(start) < 1500:
+                yield "\n".join(lines[at.index(start):i])
+
+
+def test_a_plain_tile_keeps_a_request_in_flight(code):
+    """No step of a loop over tiles waits for every load: the newer of the two requests would be waited for right behind its issue."""
+    total = 0
+    for text in code:
+        for name, body in re.findall(r"<(\S*plain_(?:pass|tn)_kernel\S*)>:\n(.*?)(?=\n\n|\Z)", text, re.S):
+            for loop in loops(body):
+                if "v_mfma" in loop and "buffer_load" in loop:
+                    assert "vmcnt(0)" not in loop, name
+                    total += 1
+    assert total >= 20
