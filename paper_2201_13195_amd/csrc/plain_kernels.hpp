@@ -543,6 +543,9 @@ __device__ __forceinline__ void plain_tile(const PlainArgs &g, bf16_t *lds, int6
     constexpr bool FUNNEL = sizeof(T) == 2 && !GEN && (MODE_A == 3 || MODE_B == 3);
     constexpr bool HOLD = DEFER ? PA + PB == 6 || FUNNEL : GEN && PLANES;
     constexpr int MAY_PASS = 0x8C;  // (scalar arithmetic, MFMAs and LDS)
+    // COLUMNS: the same with one step to a tile, fp32 and both operands row-indexed (dW, monitors), where the first splits went in front of the
+    // barrier and all waves waited there for a load: monitors of 8000 x 128 x 128 70 us and 65, 3338 x 201 x 167 41.2 and 38.1.
+    constexpr bool COLUMNS = PLANES && !DEFER && AMODE == PA_M;
     const uint32_t num = ((uint32_t)len + BK - 1) / BK;
     // Short chains of fp32 tiles: those past the end are not split (256 x 128 -> 128: 18.6 -> 16 us a step).  Elsewhere the
     // branch costs more (Y 4096 x 768 -> 3072: 162 -> 175 us).
@@ -559,6 +562,7 @@ __device__ __forceinline__ void plain_tile(const PlainArgs &g, bf16_t *lds, int6
         int m = 0;
         __syncthreads();
         if constexpr (FUNNEL && !DEFER) __builtin_amdgcn_sched_barrier(MAY_PASS);
+        if constexpr (COLUMNS) __builtin_amdgcn_sched_barrier(0);
         if constexpr (FIRST || !DEFER) {
 #pragma unroll
             for (int i = 0; i < FRAGS; ++i) fetch(i, f[0], s, 0);

@@ -111,3 +111,13 @@ def test_a_plain_tile_keeps_a_request_in_flight(code):
                     assert "vmcnt(0)" not in loop, name
                     total += 1
     assert total >= 20
+
+
+def test_an_fp32_tile_of_columns_waits_for_no_load_between_its_products_and_the_barrier(code):
+    kernels = [(name, body) for text in code
+               for name, body in re.findall(r"<(\S*plain_tn_kernelIffNS\S*PlainShapeILi32E\S*)>:\n(.*?)(?=\n\n|\Z)", text, re.S)]
+    assert len(kernels) >= 2
+    for name, body in kernels:
+        marks = re.findall(r"v_mfma|buffer_load|vmcnt|s_barrier", body)
+        assert not re.search(r"v_mfma(vmcnt)+s_barrier", "".join(marks)), name
+        assert marks.count("s_barrier") >= 4
