@@ -79,7 +79,8 @@ inline double tile_us(const TileTime &t, int64_t tiles, int64_t kk, bool filled)
 // waves (few_tile) only while there are at most 512 of them.  256 x 256 tiles from 160 of them on whatever the model
 // says: they need half the bytes per flop of 128 x 128 tiles, which a full chip cannot bring into its LDS at MFMA rate.  And from 130 on
 // where 128 x 128 tiles, with the `beside` other work-groups of the launch, go over two rounds (36 products from 516 to 660 of those:
-// 0.73 to 1.02 of the time, 0.84 on average; with 455 to 510 of them 0.88 to 1.31).
+// 0.73 to 1.02 of the time, 0.84 on average; with 455 to 510 of them 0.88 to 1.31).  (Times of the menu, and these 36 products, are from before
+// the tiles' loops went through their LDS stages, which made 128 x 128 tiles faster, dX alone by 22 %, than 256 x 256 ones, 6 %.)
 struct GemmChoice {
     int cfg;
     double us;
@@ -259,7 +260,7 @@ inline double makespan(int64_t first, double t1, int64_t second, double t2, int6
 // writing, and every step of 64 contraction elements) and are dealt to 256 slots in grid order, or to 512 where two share
 // a compute unit.  The times are fitted to 4300 launches of 60 passes (256 to 16384 tokens, widths 256 to 4096,
 // k = 73 to 6911; all sketch tiles, 64 to 512 work-groups): 7 % rms off.  Over those passes the plan it leads to is 3.3 % slower than the
-// best one on average and 30 % at most; plans made for the sketch product alone were 12 and 50 %.
+// best one on average and 30 % at most; plans made for the sketch product alone were 12 and 50 %.  (As above: from before the loops.)
 inline double pair_us(const PairPlain &plain, int64_t kk, const SketchPlan &p, int kind, double partial_mb, bool limited = false) {
     struct Times {
         double fix, step;
