@@ -444,7 +444,11 @@ inline SorsPlan plan_sors(int64_t n, int64_t d_sk, int64_t d_other, int64_t k) {
     const double other = best.order != SORS_APART ? (plain.cfg == GEMM_LARGE ? 1.017 : 1.033) * best_us
                                                   : (apart.cfg == GEMM_LARGE ? 0.886 : apart.cfg == GEMM_WIDE ? 0.944 : 1.122) * apart.us + 4.2 +
                                                         (strips <= 256 ? 2.82 : 3.98 + 1.08 * (double)(strips - 256) / 256.0) * chunks;
-    return now < (apart.cfg == GEMM_LARGE ? 0.97 : 1.03) * other ? shared : best;
+    // (More than 16384 tokens, sixteen chunks, are beyond the passes that were fitted to, and tiles of many steps beside them take longer than
+    // these times say: of 28 passes with contractions of 768 and more that came out below 0.97 and were taken, 16 were 1.04 to 1.16 of the time
+    // (28837 x 824 -> 2968, k = 356, backward 253 us and 292); the 7 below 0.8 are 0.89 to 1.02.  41 with shorter contractions are 0.66 to 0.96.)
+    const double margin = chunks > 8.0 && steps >= 12.0 ? 0.8 : apart.cfg == GEMM_LARGE ? 0.97 : 1.03;
+    return now < margin * other ? shared : best;
 }
 
 // Whether the bias gradient's column sums go with dW: beside it where its launch has room (64 compute units idle in the last round,

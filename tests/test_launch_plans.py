@@ -316,3 +316,8 @@ def test_strips_do_not_share_compute_units_with_rounds_of_tiles_that_wider_ones_
         assert order(*shape) != "compact", shape
     for shape in ((2275, 312, 584, 455), (2907, 1248, 1136, 290), (4250, 1232, 864, 425), (3001, 520, 768, 600), (1500, 320, 2048, 150)):
         assert order(*shape) == "compact", shape
+    # more than 16384 tokens, which the times are not fitted to: long contractions (backward passes as d_out, d_in)
+    for shape in ((28837, 2968, 824, 356), (23270, 1928, 848, 715), (25880, 3336, 808, 1614), (30216, 3192, 1040, 374), (17872, 1240, 2528, 1787)):
+        assert order(*shape) != "compact", shape
+    for shape in ((17354, 936, 600, 1408), (25112, 1888, 480, 1711), (31504, 504, 1568, 448), (20373, 512, 352, 884)):
+        assert order(*shape) == "compact", shape
