@@ -292,7 +292,34 @@ inline double pair_us(const PairPlain &plain, int64_t kk, const SketchPlan &p, i
 struct PassPlan {
     PairPlain plain;
     SketchPlan sketch;
+    bool sketch_first;  // the sketch work-groups stand in front of the plain tiles
 };
+
+// us of a pass by times of the tiles as they are: work-groups as in pair_us, and the sum of the slices.  The fuller the chip, the longer all of them
+// take (`full`: power, and lines from L2).  What a round more or less would change is taken at plain tiles of 0.9 and of 1.1 of their time, so that
+// no plan is taken for a round that it may just miss.  Fitted to 135000 launches of 446 passes with kSecondLookProducts and more (all sketch tiles, 64 to 512
+// work-groups of them, either order).
+inline double pass_us(const PassPlan &p, int64_t kk, int kind, double partial_mb) {
+    struct Times {
+        double fix, step, full;
+    };
+    static const Times large{4.56, 0.844, 0.63}, wide{1.67, 0.537, 0.66}, mid{1.20, 0.426, 0.46}, compact{2.30, 0.673, 0.66};
+    struct SketchTimes {
+        double fix, step[2], full;  // Gaussian, Rademacher
+    };
+    static const SketchTimes sk_compact{3.05, {0.818, 0.725}, 0.31};
+    static const SketchTimes sk[] = {{3.18, {0.909, 0.763}, 0.36}, {4.88, {1.096, 1.062}, 0.36}, {2.81, {0.784, 0.997}, 0.43},   // (in the order of SK_NARROW ..)
+                                     {3.51, {0.699, 0.874}, 0.37}, {5.14, {0.990, 0.965}, 0.37}, {2.66, {0.589, 0.573}, 0.31}};
+    const bool two = p.plain.cfg == GEMM_COMPACT;
+    const Times &a = p.plain.cfg == GEMM_LARGE ? large : p.plain.cfg == GEMM_WIDE ? wide : two ? compact : mid;
+    const SketchTimes &b = two ? sk_compact : sk[p.sketch.cfg];
+    const double ta = a.fix + a.step * (double)((kk + 63) / 64), tb = b.fix + b.step[kind != 0] * (double)(p.sketch.k_chunk / 64);
+    const int64_t slots = two ? 512 : 256, tiles = p.plain.tiles, shares = p.sketch.shares();
+    double longest = 0.0;
+    for (double f : {0.89, 1.11}) longest += 0.5 * (p.sketch_first ? makespan(shares, tb, tiles, f * ta, slots) : makespan(tiles, f * ta, shares, tb, slots));
+    const double full = (a.full * (double)tiles * ta + b.full * (double)shares * tb) / (double)slots;
+    return longest + full + (p.sketch.splits > 1 ? 1.2 + 0.304 * (double)p.sketch.splits * partial_mb : 0.0);
+}
 
 // The plain product of a pass (n x m outputs) beside a sketch product on one work-group per compute unit: 256 x 256 tiles where it
 // fills the chip with them, else 128 x 128.  ShapeCompact adds in the order of ShapeMid, so that the bits of Y follow from its
@@ -306,6 +333,9 @@ inline PairPlain pair_plain(int64_t n, int64_t m) {
 // 0.994 of the time without them).
 inline int dx_cfg(int cfg, int64_t kk) { return cfg == GEMM_MID && kk >= 1536 ? GEMM_SPLIT : cfg; }
 
+// More token slices than a pass may have over its sketch product alone.
+inline bool too_many(int splits, int of_alone) { return splits > 1 && (of_alone == 1 || 4 * (splits - 1) > 5 * of_alone); }
+
 // Plan of a pass: sketch of the n x d_sk operand, plain product n x d_other over d_sk.  Every sketch tile with slices for 64
 // to 320 work-groups, and 64 x 256 tiles with ShapeCompact where all work-groups are resident at once.  (4096 x 768 ->
 // 768, k = 410, with the sum of its slices: 26.9 -> 21.3 us; 4096 x 3072 -> 768, k = 2048, Rademacher 82 -> 69; 3001 x 1304 ->
@@ -318,15 +348,14 @@ inline int dx_cfg(int cfg, int64_t kk) { return cfg == GEMM_MID && kk >= 1536 ? 
 // the product alone takes without that limit, for 8 % of the model's time (`limited`: not so).  (12531 x 760 -> 272, k =
 // 6265, Rademacher, forward: 172 us in one slice, 124 in two and a short one; 26 of 260 passes with k from a fifth of the tokens on, 8 % faster
 // on average, 1.00 to 1.20.  With a margin of 5 % two of 28 lose 5 %.)
-inline PassPlan make_pass_plan(int64_t n, int64_t d_sk, int64_t d_other, int64_t k, int kind, bool limited, int64_t room) {
+inline PassPlan first_plan(int64_t n, int64_t d_sk, int64_t d_other, int64_t k, int kind, bool limited, int64_t room) {
     const SketchPlan alone = plan_sketch(n, d_sk, k, kind, true, room);
     const int most = limited ? alone.splits : plan_sketch(n, d_sk, k, kind, false, room).splits;
     const double partial_mb = (double)k * (double)d_sk * 4e-6;
     const PairPlain usual = pair_plain(n, d_other);
     const PairPlain compact{GEMM_COMPACT, (int)gemm_tiles(GEMM_COMPACT, n, d_other)};
-    PassPlan best{usual, alone};
+    PassPlan best{usual, alone, false};
     double best_us = pair_us(usual, d_sk, alone, kind, partial_mb, limited) - 0.8;
-    auto many = [](int splits, int of_alone) { return splits > 1 && (of_alone == 1 || 4 * (splits - 1) > 5 * of_alone); };
     for (int cfg = 0; cfg < kSketchTiles; ++cfg) {
         int slices = -1, per_tail = -1;
         for (int target : {64, 96, 128, 192, 256, 320}) {
@@ -335,16 +364,56 @@ inline PassPlan make_pass_plan(int64_t n, int64_t d_sk, int64_t d_other, int64_t
             slice_sketch(p, n, target, 4.0 / kSketchMenu[cfg].step_us[kind != 0], room);
             if (p.slices == slices && p.per_tail == per_tail) continue;
             slices = p.slices, per_tail = p.per_tail;
-            if (many(p.splits, alone.splits) && many(p.splits, most)) continue;
-            const double worth = many(p.splits, alone.splits) ? 1.08 : 1.0;
+            if (too_many(p.splits, alone.splits) && too_many(p.splits, most)) continue;
+            const double worth = too_many(p.splits, alone.splits) ? 1.08 : 1.0;
             double us = worth * pair_us(usual, d_sk, p, kind, partial_mb, limited);
-            if (us < best_us) best = PassPlan{usual, p}, best_us = us;
+            if (us < best_us) best = PassPlan{usual, p, false}, best_us = us;
             if (cfg != SK_NARROW64 || usual.cfg == GEMM_LARGE || compact.tiles + p.shares() > 512) continue;
             us = worth * pair_us(compact, d_sk, p, kind, partial_mb, limited);
-            if (us < best_us) best = PassPlan{compact, p}, best_us = us;
+            if (us < best_us) best = PassPlan{compact, p, false}, best_us = us;
         }
     }
+    best.sketch_first = sketch_goes_first(best.plain.tiles, best.sketch.slices);
     return best;
+}
+
+// A second look at large passes, by pass_us: 256 x 256 tiles also where they do not fill the chip, 128 x 256 tiles, and either order, with any sketch
+// tile.  At headline size dX on 96 tiles of 128 x 256 beside 112 sketch work-groups of 64 x 384, a compute unit each, takes the place
+// of 192 tiles of 128 x 128 two by two with 168 of 64 x 256: a step that two work-groups of a compute unit share takes them 0.8 us, and some
+// units have one, some two (a step 81.8 -> 73.4 us; 4096 x 3072 -> 768, k = 2048, Rademacher, two micro-batches: 303 -> 266).
+// Only for what the model calls 9 % or more: 530 random passes that it was not fitted to take 0.960 of the time on average, 0.72 to 1.06 but for
+// one of 1.21 (1180 x 2232 -> 2328, k = 1062, Rademacher, forward: 28 -> 34 us), five of them more than 1.03; for 6 % they are 0.955, with 3 % of them.  Of more than 8192 tokens 134 others are 0.99 on average and 7 of
+// them 1.04 to 1.16: long launches, which slow the clock in a way that it does not know.  Below 6e9 products, 6 us of the matrix pipes, a pass is
+// made up as much of launches, first loads and sums, and first_plan is 1 to 3 % behind the best plan.
+constexpr double kSecondLookProducts = 6e9;
+constexpr int64_t kSecondLookTokens = 8192;
+inline PassPlan make_pass_plan(int64_t n, int64_t d_sk, int64_t d_other, int64_t k, int kind, bool limited, int64_t room) {
+    const PassPlan best = first_plan(n, d_sk, d_other, k, kind, limited, room);
+    if (limited || n > kSecondLookTokens || (double)n * (double)d_sk * (double)d_other < kSecondLookProducts) return best;
+    const int alone = plan_sketch(n, d_sk, k, kind, true, room).splits, free = plan_sketch(n, d_sk, k, kind, false, room).splits;
+    const double partial_mb = (double)k * (double)d_sk * 4e-6;
+    PassPlan now = best;
+    double now_us = 0.91 * pass_us(best, d_sk, kind, partial_mb);
+    for (int plain_cfg : {GEMM_LARGE, GEMM_WIDE, GEMM_MID}) {
+        const PairPlain plain{plain_cfg, (int)gemm_tiles(plain_cfg, n, d_other)};
+        for (int cfg = 0; cfg < kSketchTiles; ++cfg) {
+            int shares = -1;
+            for (int target : {64, 96, 128, 160, 192, 224, 256, 320, 384, 448, 512}) {
+                PassPlan p{plain, {}, false};
+                p.sketch.cfg = cfg, p.sketch.tiles = tiles_of(k, d_sk, kSketchMenu[cfg].bm, kSketchMenu[cfg].bn);
+                slice_sketch(p.sketch, n, target, 4.0 / kSketchMenu[cfg].step_us[kind != 0], room);
+                if (p.sketch.shares() == shares) continue;
+                shares = p.sketch.shares();
+                if (too_many(p.sketch.splits, alone) && too_many(p.sketch.splits, free)) continue;
+                for (bool first : {false, true}) {
+                    p.sketch_first = first;
+                    const double us = pass_us(p, d_sk, kind, partial_mb);
+                    if (us < now_us) now = p, now_us = us;
+                }
+            }
+        }
+    }
+    return now;
 }
 
 // The same, remembered: a pass asks for its plan three times (workspace of either kind, launch), and it depends on the

@@ -258,7 +258,7 @@ hipError_t launch_forward_pair_bf16(const bf16_t *X, const bf16_t *W, const bf16
     const SketchPlan &p = pass.sketch;
     const GemmArgs gb = args_sketch(X, n, d_in, k, st, p, X_proj, ws);
     EventPair pev(ev_begin, ev_end, stream);
-    const hipError_t e = launch_pair_nt(pass.plain, p.cfg, kind, ga, gb, (int)p.tiles, p.shares(), stream);
+    const hipError_t e = launch_pair_nt(pass, kind, ga, gb, stream);
     pev.done();
     if (e != hipSuccess || p.splits == 1) return e;
     return launch_reduce(ws, X_proj, k, d_in, p.splits, stream);
@@ -293,7 +293,7 @@ hipError_t launch_backward_pair_bf16(const bf16_t *dY, const bf16_t *W, bf16_t *
     const ColsumArgs gc{dY, dbias, n, d_out, accumulate_dbias ? 1 : 0, colsum_lpr(d_out, 2)};
     const ColsumArgs *gcp = dbias != nullptr ? &gc : nullptr;
     EventPair pev(ev_begin, ev_end, stream);
-    const hipError_t e = launch_pair_nn(pass.plain, p.cfg, kind, ga, gb, (int)p.tiles, p.shares(), stream, gcp);
+    const hipError_t e = launch_pair_nn(pass, kind, ga, gb, stream, gcp);
     pev.done();
     if (e != hipSuccess || p.splits == 1) return e;
     return launch_reduce(ws, G, k, d_out, p.splits, stream);

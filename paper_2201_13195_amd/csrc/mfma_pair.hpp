@@ -6,22 +6,23 @@
 
 namespace rmm {
 
-// One launch for a plain product (`ga`; nt: Y = X W^T, nn: dX = dY W) and a sketch product (`gb`, `tiles_b`
-// tiles in `shares` work-groups, see sketch_share) with the kernel sk_cfg.
+// One launch for a plain product (`ga`; nt: Y = X W^T, nn: dX = dY W) and a sketch product (`gb`).
 // `gc`, if not null, adds the column blocks of a column-sum problem (colsum.hpp) behind the sketch work-groups.
-// sketch_goes_first() says which of the two comes first in the grid.
-hipError_t launch_pair_nt(const PairPlain &plain, int sk_cfg, int kind, const GemmArgs &ga, const GemmArgs &gb, int tiles_b,
-                          int shares, hipStream_t stream, const ColsumArgs *gc = nullptr);
-hipError_t launch_pair_nn(const PairPlain &plain, int sk_cfg, int kind, const GemmArgs &ga, const GemmArgs &gb, int tiles_b,
-                          int shares, hipStream_t stream, const ColsumArgs *gc = nullptr);
+// `pass` says which tiles, and which of the two comes first in the grid.
+hipError_t launch_pair_nt(const PassPlan &pass, int kind, const GemmArgs &ga, const GemmArgs &gb, hipStream_t stream,
+                          const ColsumArgs *gc = nullptr);
+hipError_t launch_pair_nn(const PassPlan &pass, int kind, const GemmArgs &ga, const GemmArgs &gb, hipStream_t stream,
+                          const ColsumArgs *gc = nullptr);
 // (one translation unit for each plain tile)
 #define RMM_PAIR_DECL(NAME)                                                                                               \
-    hipError_t launch_pair_##NAME(int sk_cfg, int kind, const GemmArgs &ga, const GemmArgs &gb, int blocks_a, int tiles_b, \
-                                  int shares, hipStream_t stream, const ColsumArgs *gc)
+    hipError_t launch_pair_##NAME(const PassPlan &pass, int kind, const GemmArgs &ga, const GemmArgs &gb, hipStream_t stream, \
+                                  const ColsumArgs *gc)
 RMM_PAIR_DECL(nt_large);
+RMM_PAIR_DECL(nt_wide);
 RMM_PAIR_DECL(nt_mid);
 RMM_PAIR_DECL(nt_compact);
 RMM_PAIR_DECL(nn_large);
+RMM_PAIR_DECL(nn_wide);
 RMM_PAIR_DECL(nn_split);
 RMM_PAIR_DECL(nn_mid);
 RMM_PAIR_DECL(nn_compact);
@@ -34,9 +35,8 @@ hipError_t launch_pair_sors(const SorsPlan &plan, bool row_indexed_b, const Gemm
 
 // Shared bodies of launch_pair_{nt,nn}_*.
 template <typename SA, int BMODE_A, typename SB>
-hipError_t launch_pair_tiles(int kind, const GemmArgs &ga, const GemmArgs &gb, int blocks_a, int tiles_b, int shares,
-                             hipStream_t stream, const ColsumArgs *gc) {
-    const int sketch_first = sketch_goes_first(blocks_a, gb.slices) ? 1 : 0;
+hipError_t launch_pair_tiles(const PassPlan &pass, int kind, const GemmArgs &ga, const GemmArgs &gb, hipStream_t stream, const ColsumArgs *gc) {
+    const int blocks_a = pass.plain.tiles, tiles_b = (int)pass.sketch.tiles, shares = pass.sketch.shares(), sketch_first = pass.sketch_first ? 1 : 0;
     const ColsumArgs c = gc != nullptr ? *gc : ColsumArgs{};
     const int col_blocks = gc != nullptr ? (int)colsum_blocks(c.d, 2) : 0;
     const unsigned grid = (unsigned)(blocks_a + shares + col_blocks);
@@ -48,15 +48,14 @@ hipError_t launch_pair_tiles(int kind, const GemmArgs &ga, const GemmArgs &gb, i
 }
 
 template <typename SA, int BMODE_A>
-hipError_t launch_pair_impl(int sk_cfg, int kind, const GemmArgs &ga, const GemmArgs &gb, int blocks_a, int tiles_b,
-                            int shares, hipStream_t stream, const ColsumArgs *gc) {
-    switch (sk_cfg) {
-        case SK_WIDE: return launch_pair_tiles<SA, BMODE_A, ShapeSkWide>(kind, ga, gb, blocks_a, tiles_b, shares, stream, gc);
-        case SK_WIDE64: return launch_pair_tiles<SA, BMODE_A, ShapeSkWide64>(kind, ga, gb, blocks_a, tiles_b, shares, stream, gc);
-        case SK_MID64: return launch_pair_tiles<SA, BMODE_A, ShapeSkMid64>(kind, ga, gb, blocks_a, tiles_b, shares, stream, gc);
-        case SK_MID: return launch_pair_tiles<SA, BMODE_A, ShapeSkMid>(kind, ga, gb, blocks_a, tiles_b, shares, stream, gc);
-        case SK_NARROW64: return launch_pair_tiles<SA, BMODE_A, ShapeSkNarrow64>(kind, ga, gb, blocks_a, tiles_b, shares, stream, gc);
-        case SK_NARROW: return launch_pair_tiles<SA, BMODE_A, ShapeSkNarrow>(kind, ga, gb, blocks_a, tiles_b, shares, stream, gc);
+hipError_t launch_pair_impl(const PassPlan &pass, int kind, const GemmArgs &ga, const GemmArgs &gb, hipStream_t stream, const ColsumArgs *gc) {
+    switch (pass.sketch.cfg) {
+        case SK_WIDE: return launch_pair_tiles<SA, BMODE_A, ShapeSkWide>(pass, kind, ga, gb, stream, gc);
+        case SK_WIDE64: return launch_pair_tiles<SA, BMODE_A, ShapeSkWide64>(pass, kind, ga, gb, stream, gc);
+        case SK_MID64: return launch_pair_tiles<SA, BMODE_A, ShapeSkMid64>(pass, kind, ga, gb, stream, gc);
+        case SK_MID: return launch_pair_tiles<SA, BMODE_A, ShapeSkMid>(pass, kind, ga, gb, stream, gc);
+        case SK_NARROW64: return launch_pair_tiles<SA, BMODE_A, ShapeSkNarrow64>(pass, kind, ga, gb, stream, gc);
+        case SK_NARROW: return launch_pair_tiles<SA, BMODE_A, ShapeSkNarrow>(pass, kind, ga, gb, stream, gc);
         default: return hipErrorInvalidValue;
     }
 }

@@ -4,7 +4,7 @@
 namespace rmm {
 
 RMM_PAIR_DECL(nn_split) {
-    return launch_pair_impl<ShapeSplit, B_NCONTIG>(sk_cfg, kind, ga, gb, blocks_a, tiles_b, shares, stream, gc);
+    return launch_pair_impl<ShapeSplit, B_NCONTIG>(pass, kind, ga, gb, stream, gc);
 }
 
 }  // namespace rmm

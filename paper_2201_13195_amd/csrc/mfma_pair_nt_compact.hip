@@ -4,7 +4,7 @@
 namespace rmm {
 
 RMM_PAIR_DECL(nt_compact) {
-    return sk_cfg == SK_NARROW64 ? launch_pair_tiles<ShapeCompact, B_KCONTIG, ShapeSkNarrow64>(kind, ga, gb, blocks_a, tiles_b, shares, stream, gc)
+    return pass.sketch.cfg == SK_NARROW64 ? launch_pair_tiles<ShapeCompact, B_KCONTIG, ShapeSkNarrow64>(pass, kind, ga, gb, stream, gc)
                                  : hipErrorInvalidValue;
 }
 

@@ -4,7 +4,7 @@
 namespace rmm {
 
 RMM_PAIR_DECL(nt_mid) {
-    return launch_pair_impl<ShapeMid, B_KCONTIG>(sk_cfg, kind, ga, gb, blocks_a, tiles_b, shares, stream, gc);
+    return launch_pair_impl<ShapeMid, B_KCONTIG>(pass, kind, ga, gb, stream, gc);
 }
 
 }  // namespace rmm

@@ -77,7 +77,19 @@ PAIRS = [((4439, 280, 2776, 222), rmm.GAUSSIAN, "256x256", "128x256"),
          ((1299, 400, 2480, 65), rmm.GAUSSIAN, "128x128", "64x512"),
          ((2840, 400, 1064, 142), rmm.RADEMACHER, "128x128", "64x512"),
          ((1358, 264, 2696, 68), rmm.GAUSSIAN, "128x128 compact", "64x256"),
-         ((1411, 264, 2648, 71), rmm.RADEMACHER, "128x128 compact", "64x256")]
+         ((1411, 264, 2648, 71), rmm.RADEMACHER, "128x128 compact", "64x256"),
+         ((7362, 408, 2112, 368), rmm.GAUSSIAN, "128x256", "128x256"),
+         ((2428, 840, 2984, 121), rmm.RADEMACHER, "128x256", "128x256"),
+         ((921, 2416, 3232, 828), rmm.GAUSSIAN, "128x256", "128x384"),
+         ((7823, 344, 2280, 391), rmm.RADEMACHER, "128x256", "128x384"),
+         ((2078, 992, 3024, 207), rmm.GAUSSIAN, "128x256", "128x512"),
+         ((2078, 992, 3024, 207), rmm.RADEMACHER, "128x256", "128x512"),
+         ((1042, 1488, 3928, 65), rmm.GAUSSIAN, "128x256", "64x256"),
+         ((1042, 1488, 3928, 65), rmm.RADEMACHER, "128x256", "64x256"),
+         ((3360, 1288, 1472, 168), rmm.GAUSSIAN, "128x256", "64x384"),
+         ((5481, 360, 3496, 274), rmm.RADEMACHER, "128x256", "64x384"),
+         ((2428, 840, 2984, 121), rmm.GAUSSIAN, "128x256", "64x512"),
+         ((2070, 1320, 2808, 414), rmm.RADEMACHER, "128x256", "64x512")]
 
 
 @pytest.mark.parametrize("shape,kind,plain,sketch", PAIRS)
