@@ -244,7 +244,7 @@ int backward_impl(const rmm_layer_desc_t *d, SketchState st, const void *dY, con
     const bool own_db_stage = ev.stage == RMM_STAGE_BWD_DW || ev.stage == RMM_STAGE_BWD_DBIAS;
     // the strips of the SORS kind read all of dY once and take its column sums on the way; asked for its events, the bias gradient
     // has a launch of its own, in the same order of additions
-    const bool strips_db = mfma && d->kind == RMM_SKETCH_SORS && dbias != nullptr && sors_fast_ok(d->n, d->d_out) && sors_takes_colsum(d->n, d->k);
+    const bool strips_db = mfma && d->kind == RMM_SKETCH_SORS && dbias != nullptr && sors_fast_ok(d->n, d->d_out);
     const bool sors_db = strips_db && ev.stage != RMM_STAGE_BWD_DBIAS;
     if (paired_sors) {
         const bool timed = ev.stage == RMM_STAGE_BWD_PAIR;

@@ -104,13 +104,12 @@ bool backward_pair_takes_colsum(int64_t n, int64_t d_in, int64_t d_out, int64_t 
 
 // SORS sketch kind, bf16 (sors.hip): signs, Walsh-Hadamard transform along the tokens and row
 // selection in one kernel, no workspace.  Usable when sors_fast_ok(): d a multiple of 8 and at most
-// 32768 tokens (the strip of one work-group has to fit in LDS); `st` made with the token count.
-// `colsum`, if not null, gets the column sums of A from the same pass over it; only where sors_takes_colsum() says so.
+// 32768 tokens (rows in 16 bits, signs in LDS); `st` made with the token count.
+// `colsum`, if not null, gets the column sums of A from the same pass over it.
 bool sors_fast_ok(int64_t n, int64_t d);
-bool sors_takes_colsum(int64_t n, int64_t k);
 hipError_t launch_sors_bf16(const bf16_t *A, bf16_t *out, int64_t n, int64_t d, int64_t k, SketchState st,
                             hipStream_t stream, bf16_t *colsum = nullptr, bool accumulate = false);
-// The column sums alone, with the same bits (where sors_takes_colsum()).
+// The column sums alone, with the same bits.
 hipError_t launch_sors_colsum_bf16(const bf16_t *A, bf16_t *colsum, int64_t n, int64_t d, int64_t k, bool accumulate, hipStream_t stream);
 
 // One launch for the plain product of a pass and the SORS sketch product of the same pass, where

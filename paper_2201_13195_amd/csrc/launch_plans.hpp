@@ -449,13 +449,30 @@ inline PassPlan plan_pass(int64_t n, int64_t d_sk, int64_t d_other, int64_t k, i
 
 // Tokens as a power of two, 512 at least (the shortest transform of the strip kernel: 512 tokens of 768 columns on 1024 points take 5.8
 // us instead of 5.4, of 4096 columns 6.9 instead of 6.1).  Up to 2048 a strip takes them in one piece, and
-// any k; from there on in chunks of 2048, with accumulators for kSorsAccMaxK sketch columns.
+// any k; from there on in chunks of 2048, with accumulators for kSorsAccMaxK sketch columns, or kSorsManyK by twice the waves.
 inline int sors_log(int64_t n) {
     int l = 9;
     while (((int64_t)1 << l) < n) ++l;
     return l;
 }
 constexpr int64_t kSorsAccMaxK = 2048;
+// Work-groups of a strip beyond that, and the sketch columns of each, a multiple of four: one with kSorsManyK of them takes 1.45 times as long
+// as one with next to none (16384 x 2048: 47.0 us and 33.6), and 256 of them run at a time.
+constexpr int64_t kSorsManyK = 8192;
+struct SorsParts {
+    int64_t parts, part_k;
+};
+inline SorsParts sors_parts(int64_t d, int64_t k) {
+    const int64_t need = (k + kSorsManyK - 1) / kSorsManyK;
+    SorsParts best{};
+    double best_time = -1.0;
+    for (int64_t parts = need; parts < need + 8; ++parts) {
+        const int64_t part_k = ((k + parts - 1) / parts + 3) / 4 * 4;
+        const double time = (double)((d / 8 * parts + 255) / 256) * (1.0 + 0.45 * (double)part_k / (double)kSorsManyK);
+        if (best_time < 0.0 || time < 0.99 * best_time) best = SorsParts{parts, part_k}, best_time = time;
+    }
+    return best;
+}
 inline int sors_chunks(int64_t n) { return sors_log(n) >= 12 ? 1 << (sors_log(n) - 11) : 1; }
 
 enum { SORS_APART = 0, SORS_BEHIND = 1, SORS_FRONT = 2, SORS_COMPACT = 3 };

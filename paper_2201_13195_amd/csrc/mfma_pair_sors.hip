@@ -27,7 +27,7 @@ __global__ void __launch_bounds__(SA::THREADS) gemm_sors_pair_kernel(GemmArgs ga
     else
         sors_strip_body<kPairChunkLog, true, 2, 8, SUMS>(gs, chunks, reinterpret_cast<float4 *>(lds),
                                                 reinterpret_cast<uint32_t *>(lds + PLANE_BYTES),
-                                                sors_first ? (int64_t)blockIdx.x : (int64_t)blockIdx.x - blocks_a, strips);
+                                                sors_first ? (int64_t)blockIdx.x : (int64_t)blockIdx.x - blocks_a, strips, 1, gs.k);
 }
 
 // Tiles of 128 x 128 in half of a compute unit's LDS and registers, strips in the other half or in what the tiles leave.  What bounds a tile
@@ -45,7 +45,7 @@ __global__ void __launch_bounds__(512, 4) gemm_sors_compact_kernel(GemmArgs ga, 
         gemm_tile<ShapeCompact, A_KCONTIG, BMODE_A, OUT_BF16>(ga, reinterpret_cast<bf16_t *>(lds), block, tiles);
     else
         sors_strip_body<LC, ACC, 1, 8, SUMS>(gs, chunks, reinterpret_cast<float4 *>(lds), reinterpret_cast<uint32_t *>(lds + PLANE_BYTES), block - tiles,
-                                             (int)gridDim.x - tiles);
+                                             (int)gridDim.x - tiles, 1, gs.k);
 }
 
 template <int BMODE_A, int LC, bool ACC>

@@ -31,7 +31,7 @@ __host__ __device__ constexpr int strip_phys(int t) { return t + (t >> 4) + 2 * 
 //   T_chunk = the CH-point transform of the chunk's signed tokens,
 //
 // so a work-group runs one CH-point transform per chunk in the same LDS buffer and adds the
-// selected entries into per-thread accumulators (k <= 2048), with
+// selected entries into per-thread accumulators (k <= 2048, or 8192 with sixteen waves), with
 // the next chunk's rows already on their way from memory.  With a single chunk (CH >= n_pad) the
 // selected rows are written directly and k is not limited.
 //
@@ -53,7 +53,7 @@ template <int LC>
 struct StripShape {
     static constexpr int CH = 1 << LC, SLOTS = strip_phys(CH);
     static constexpr int PLANE = SLOTS + 4, REGION = 2 * PLANE + 2;  // float4 slots of half a strip and of a strip
-    static_assert(LC >= 9 && LC <= 12, "chunks of 512 .. 4096 tokens");
+    static_assert(LC >= 9 && LC <= 11, "chunks of 512 .. 2048 tokens");
 };
 
 // Rows t, t + LPW, .. of a strip, 16 bytes from `off` on in each lane.  Buffer loads: a row beyond the tokens lies outside the
@@ -144,14 +144,15 @@ struct StripSums {
 // thread r of strip p; separate LDS planes, offset by 64 bytes modulo 128 so that the interleaved
 // lanes of the two strips stay on different banks): a form that shares a grid with the 512-thread
 // work-groups of a plain product (one strip of 512 threads is the other, which shares compute units with them).  `block` of `blocks` numbers the work-group among those of the
-// sketch product; LDS: NPROB * StripShape::REGION float4 slots and 1024 words.
-template <int LC, bool ACC, int NPROB, int WAVES, bool SUMS>
+// sketch product; LDS: NPROB * StripShape::REGION float4 slots and 1024 words.  With accumulators a strip's sketch columns
+// may be made by `parts` work-groups, part_k (a multiple of 4) by each, up to 4 * ACC_CALLS by a thread.
+template <int LC, bool ACC, int NPROB, int WAVES, bool SUMS, int ACC_CALLS = (int)kSorsAccMaxK / 4 / (64 * WAVES / NPROB)>
 __device__ __forceinline__ void sors_strip_body(const SorsArgs &g, int chunks, float4 *planes_all, uint32_t *sign_words,
-                                                int64_t block, int64_t blocks) {
+                                                int64_t block, int64_t blocks, int parts, int64_t part_k) {
     typedef StripShape<LC> S;
     // Threads of a strip; tokens of a wave, rows of one load of it, loads; tokens of a wave and strip in either plane, tiles of 64 of them
     constexpr int CH = S::CH, NT = 64 * WAVES / NPROB, TW = CH / WAVES, LPW = 64 / NPROB, R0 = TW / LPW, TOP = NPROB == 2 ? TW : TW / 2,
-                  TILES = TOP / 64, ACC_CALLS = (int)kSorsAccMaxK / 4 / NT;
+                  TILES = TOP / 64;
     static_assert(TILES >= 1 && (NPROB == 1 || WAVES >= 8), "a tile per wave");
     const int prob = NPROB == 2 ? (int)(threadIdx.x & 1) : 0;
     const int tid = NPROB == 2 ? (int)(threadIdx.x >> 1) : (int)threadIdx.x;  // thread number inside the strip
@@ -164,6 +165,11 @@ __device__ __forceinline__ void sors_strip_body(const SorsArgs &g, int chunks, f
         const int64_t per = blocks / 8, rem = blocks % 8, x = group % 8, r = group / 8;
         group = x * per + (x < rem ? x : rem) + r;
     }
+    [[maybe_unused]] int64_t j0 = 0, j1 = g.k;  // this work-group's sketch columns (those of a strip are neighbours on an XCD, too)
+    if constexpr (ACC) {
+        const int64_t strip = (uint32_t)group / (uint32_t)parts;
+        j0 = (group - strip * parts) * part_k, j1 = min(g.k, j0 + part_k), group = strip;
+    }
     const int64_t col0 = (group * NPROB + prob) * 8;
     const bool live = col0 < g.d;  // the last work-group's second strip may not exist
 
@@ -174,18 +180,18 @@ __device__ __forceinline__ void sors_strip_body(const SorsArgs &g, int chunks, f
     }
 
     // Rows of this thread's sketch columns and their accumulators (ACC only).
-    uint32_t rows[ACC ? ACC_CALLS : 1][4];
+    uint32_t rows[ACC ? ACC_CALLS : 1][2];  // (below 2^15: two to a register)
+    auto row_of = [&](int m, int u) { return u % 2 == 0 ? rows[m][u / 2] & 0xFFFFu : rows[m][u / 2] >> 16; };
     float4 acc[ACC ? ACC_CALLS : 1][4][2];
     if constexpr (ACC) {
 #pragma unroll
         for (int m = 0; m < ACC_CALLS; ++m) {
-            const Words4 w = philox4x32_10((uint32_t)(tid + NT * m), kSorsRowColumn, g.st.off0, g.st.off1, g.st.key0,
+            const Words4 w = philox4x32_10((uint32_t)(j0 / 4 + tid + NT * m), kSorsRowColumn, g.st.off0, g.st.off1, g.st.key0,
                                            g.st.key1);
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                rows[m][u] = w.w[u] & g.st.row_mask;
-                acc[m][u][0] = acc[m][u][1] = make_float4(0.f, 0.f, 0.f, 0.f);
-            }
+            for (int u = 0; u < 4; ++u) acc[m][u][0] = acc[m][u][1] = make_float4(0.f, 0.f, 0.f, 0.f);
+            rows[m][0] = (w.w[0] & g.st.row_mask) | (w.w[1] & g.st.row_mask) << 16;
+            rows[m][1] = (w.w[2] & g.st.row_mask) | (w.w[3] & g.st.row_mask) << 16;
         }
     }
 
@@ -299,9 +305,9 @@ __device__ __forceinline__ void sors_strip_body(const SorsArgs &g, int chunks, f
                 }
         }
         __syncthreads();
-        // The waves' bits, 16 bytes of a token at a time (8 where that leaves threads without one).
+        // The waves' bits, 16 bytes of a token at a time (8 or 4 where that leaves threads without one).
         {
-            constexpr int E = 2 * TW < NT ? 2 : 4;
+            constexpr int E = 8 * TW / NT < 4 ? 8 * TW / NT : 4;
             typedef float vec_t __attribute__((ext_vector_type(E)));
             float *strip = reinterpret_cast<float *>(planes_all + (int)threadIdx.x / NT * S::REGION);
 #pragma unroll
@@ -327,16 +333,20 @@ __device__ __forceinline__ void sors_strip_body(const SorsArgs &g, int chunks, f
         __syncthreads();
         if constexpr (ACC) {
 #pragma unroll
-            for (int m = 0; m < ACC_CALLS; ++m)
+            for (int m = 0; m < ACC_CALLS; ++m) {
+                if (j0 + 4 * (wave * (64 / NPROB) + NT * m) >= j1) continue;  // (a wave without sketch columns)
+                if constexpr (SUMS)  // (their places are found anew for every chunk: kept, in front of the loop, they spill registers)
+                    asm volatile("" : "+v"(rows[m][0]), "+v"(rows[m][1]));
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
-                    const uint32_t r = rows[m][u];
+                    const uint32_t r = row_of(m, u);
                     const int at = strip_phys((int)(r & (CH - 1)));
                     const float sgn = (__popc((r >> LC) & (uint32_t)ch) & 1) ? -1.0f : 1.0f;
                     const float4 a = planes[at], b = planes[S::PLANE + at];
                     acc[m][u][0].x += sgn * a.x, acc[m][u][0].y += sgn * a.y, acc[m][u][0].z += sgn * a.z, acc[m][u][0].w += sgn * a.w;
                     acc[m][u][1].x += sgn * b.x, acc[m][u][1].y += sgn * b.y, acc[m][u][1].z += sgn * b.z, acc[m][u][1].w += sgn * b.w;
                 }
+            }
             __syncthreads();  // the next chunk overwrites the planes
         }
     }
@@ -361,8 +371,8 @@ __device__ __forceinline__ void sors_strip_body(const SorsArgs &g, int chunks, f
         for (int m = 0; m < ACC_CALLS; ++m)
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
-                const int64_t j = 4 * (int64_t)(tid + NT * m) + u;
-                if (j < g.k) store_row(j, rows[m][u], acc[m][u][0], acc[m][u][1]);
+                const int64_t j = j0 + 4 * (int64_t)(tid + NT * m) + u;
+                if (j < j1) store_row(j, row_of(m, u), acc[m][u][0], acc[m][u][1]);
             }
     } else {
         for (int64_t q = tid; q < (g.k + 3) / 4; q += NT) {
@@ -379,7 +389,7 @@ __device__ __forceinline__ void sors_strip_body(const SorsArgs &g, int chunks, f
     }
     if constexpr (SUMS) {
         __syncthreads();
-        if (tid < 8 && live) sums.write(g, part, prob, col0, tid);
+        if (tid < 8 && live && j0 == 0) sums.write(g, part, prob, col0, tid);
     }
 }
 

@@ -67,6 +67,22 @@ def test_two_strips_to_a_work_group(n, d, k):
     assert_close(db, synth.to_f64(A).sum(axis=0), "db", "bf16", "sors db n=%d d=%d k=%d" % (n, d, k))
 
 
+@pytest.mark.parametrize("n,d,k", [(2049, 8, 2049), (4096, 24, 8192), (4097, 520, 8193), (5000, 2056, 4100), (6001, 16, 9001), (16384, 24, 4099)])
+def test_more_sketch_columns_than_a_strip_has_accumulators(n, d, k):
+    """Strips shared by one to eight work-groups, the last of them with fewer sketch columns; waves with some, all and none of theirs."""
+    A = synth.to_torch(synth.normal((n, d), 0x5EED0026 + n), "bf16")
+    got = rmm.rmm_sketch(A.to(DEV), k, SORS, 0x5EED0027, 5)
+    want = o_rmm.sketch_apply(synth.to_f64(A), k, o_sketch.SORS, 0x5EED0027, 5)
+    assert_close(got, want, "X_proj", "bf16", "sors sketch n=%d d=%d k=%d" % (n, d, k))
+    W = torch.zeros((d, 8), dtype=torch.bfloat16, device=DEV)
+    Xp = torch.zeros((k, 8), dtype=torch.bfloat16, device=DEV)
+    db = None
+    for times in (1, 2):
+        _, _, db = rmm.rmm_backward(A.to(DEV), W, Xp, SORS, 0x5EED0027, 5, need_dX=False, need_dbias=True, dbias=db, accumulate=times == 2,
+                                    dW=torch.zeros((d, 8), dtype=torch.bfloat16, device=DEV))
+        assert_close(db, times * synth.to_f64(A).sum(axis=0), "db", "bf16", "sors db n=%d d=%d k=%d, %d times" % (n, d, k, times))
+
+
 @pytest.mark.parametrize("dtype,n,d,k", [("f32", 256, 128, 32), ("f32", 333, 50, 77), ("bf16", 333, 52, 20),
                                          ("bf16", 40000, 8, 8)])
 def test_sketch_primitive_entry_by_entry_path(dtype, n, d, k):
