@@ -108,7 +108,38 @@ inline GemmChoice choose_gemm(int64_t m, int64_t n, int64_t kk, int64_t beside =
     }
     return best;
 }
-inline int gemm_cfg(int64_t m, int64_t n, int64_t kk, int64_t beside = 0) { return choose_gemm(m, n, kk, beside).cfg; }
+// The tile of a product: with no other work-groups in its launch, a second look by times of the tiles as they are, for what they call 4 % and
+// half a microsecond.  A step takes longer the more of the compute units run one (`full`); of the small tiles two share one, a full round of which takes `two` times, one of
+// 257 and more from `over` times on.  Fitted to 2800 products (1 to 16384 rows, 256 to 4096 columns, contractions from 16 to 4096; Y, dX and
+// dW alike): 1480 of more than 6.5 us: the tile that choose_gemm takes is 4.4 % slower than the fastest on average and 68 % at most, this one 0.4 %,
+// and 1.06 of the time before at most.  What it mends most is few_tile, whose chain of loads is longer than that of 64 x 64 tiles where a wave has
+// several steps (dW 1088 x 272, k = 1407: 12.7 -> 8.0 us; Y 124 x 2496 -> 2496 11.9 -> 9.4), and 64 x 64 tiles in 257 to 400 work-groups (dW 280
+// x 3496, k = 1805: 17.6 -> 13.5 on 64 x 128).
+inline double gemm_us(int cfg, int64_t m, int64_t n, int64_t kk) {
+    static const struct {
+        double launch, fix, step, full, over, two;  // (`over` 0: a compute unit each)
+    } times[] = {{0.95, 5.42, 0.804, 1.01, 0.0, 0.0}, {1.41, 3.55, 0.441, 0.93, 0.0, 0.0}, {2.23, 2.61, 0.247, 1.18, 0.0, 0.0}, {2.59, 1.85, 0.259, 1.07, 0.0, 0.0},
+                 {3.41, 0.76, 0.163, 1.37, 1.48, 1.77}, {3.29, 0.72, 0.123, 1.04, 1.51, 1.70}, {3.53, 0.00, 0.682, 0.74, 1.54, 1.87}};  // (in the order of GEMM_LARGE ..)
+    const auto &t = times[cfg];
+    const int64_t tiles = gemm_tiles(cfg, m, n), rest = tiles % 512;
+    const double rounds = t.over == 0.0 ? (double)((tiles + 255) / 256)
+                                        : t.two * (double)(tiles / 512) + (rest == 0 ? 0.0 : rest <= 256 ? 1.0 : t.over + (t.two - t.over) * (double)(rest - 256) / 256.0);
+    const int64_t steps = cfg == GEMM_FEW ? ((kk + 15) / 16 + 31) / 32 : (kk + 63) / 64;  // (of a wave / of the work-group)
+    return t.launch + rounds * (t.fix + t.step * (double)steps * (1.0 + t.full * (tiles < 256 ? (double)tiles / 256.0 : 1.0)));
+}
+inline int gemm_cfg(int64_t m, int64_t n, int64_t kk, int64_t beside = 0) {
+    const int first = choose_gemm(m, n, kk, beside).cfg;
+    if (beside > 0) return first;
+    int best = first;
+    double best_us = 0.96 * gemm_us(first, m, n, kk) - 0.5;
+    if (best_us < 4.2) return first;  // (no tile is below)
+    for (int cfg = gemm_tiles(GEMM_LARGE, m, n) >= 130 ? GEMM_LARGE : GEMM_WIDE; cfg <= GEMM_FEW; ++cfg) {
+        if (cfg == GEMM_FEW && gemm_tiles(GEMM_FEW, m, n) > 512) continue;
+        const double us = gemm_us(cfg, m, n, kk);
+        if (us < best_us) best = cfg, best_us = us;
+    }
+    return best;
+}
 
 // |X^T dY|_F^2 per tile for the variance monitors: the dW-type product (both operands stored
 // [token][feature]) with the squared-norm epilogue; the tiles of the other products, but for 32 x 32, beside the work-groups of

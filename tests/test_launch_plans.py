@@ -321,3 +321,11 @@ def test_strips_do_not_share_compute_units_with_rounds_of_tiles_that_wider_ones_
         assert order(*shape) != "compact", shape
     for shape in ((17354, 936, 600, 1408), (25112, 1888, 480, 1711), (31504, 504, 1568, 448), (20373, 512, 352, 884)):
         assert order(*shape) == "compact", shape
+
+
+def test_products_are_looked_at_again_where_that_is_clear(plans):
+    """few_tile with several steps to a wave, 64 x 64 tiles a little over a round: the next tile; products of a few microseconds as they were."""
+    for shape, tile in (((1088, 272, 1407), "64x64"), ((124, 2496, 2496), "64x64"), ((280, 3496, 1805), "64x128"), ((608, 1712, 993), "64x128")):
+        assert plans.plain(*shape) == tile, shape
+    for shape in ((24, 3072, 768), (304, 784, 304), (408, 480, 17), (416, 512, 53)):
+        assert plans.plain(*shape) == "32x32", shape
