@@ -639,6 +639,15 @@ inline int plain_cfg(int elem_bytes, int64_t m, int64_t n, bool two_sums) {
     const double times = elem_bytes == 4 ? (two_sums ? 2.6 : 4.0) : two_sums ? 4.0 : 2.8;
     return times * (double)((big + 255) / 256) <= (double)((mid + 255) / 256) ? PLAIN_BIG : PLAIN_MID;
 }
+// Tile of Y where X and W have rows on 16 bytes and Y has not: GEMM_COMPACT or GEMM_FLAT, which load straight into LDS and add in one order, in place
+// of the 128 x 128 tile (`cfg`) and of 64 x 64 ones beyond a round of them; -1: that of `cfg`.  (Y with its sketch, 3000 x 768 -> 1001, k = 300:
+// 25.3 -> 22.2 us; 1340 x 1080 -> 1217, k = 134, Rademacher, 16.1 -> 12.0; Y alone 12.8 -> 10.0.  Within a round their chain is longer: 1863 x 1976 ->
+// 435 Y alone, 210 tiles of 64 x 64 or 120 of 64 x 128, 12.8 and 15.8.  With most of a round of them the sketch tiles find no places beside them: 1308 x
+// 984 -> 1289, k = 262, 231 tiles, 20.3 and 21.3.)
+inline int any_width_tile(int cfg, int64_t m, int64_t n, int64_t kk) {
+    if (cfg == PLAIN_TINY || (cfg == PLAIN_MID && (tiles_of(m, n, 64, 64) <= 256 || gemm_tiles(GEMM_FLAT, m, n) > 224))) return -1;
+    return gemm_us(GEMM_MID, m, n, kk) <= gemm_us(GEMM_FLAT, m, n, kk) ? GEMM_COMPACT : GEMM_FLAT;
+}
 inline int64_t plain_tiles(int cfg, int64_t m, int64_t n) {
     const int64_t e = cfg == PLAIN_BIG ? 128 : cfg == PLAIN_MID ? 64 : 32;
     return tiles_of(m, n, e, e);

@@ -56,8 +56,8 @@ namespace {
 enum { A_KCONTIG = 0, A_MCONTIG = 1 };
 enum { B_KCONTIG = 0, B_NCONTIG = 1 };
 // Output: rounded to bf16 / fp32 partial result of a token slice (streaming sketch kernel) / no matrix at all, only
-// the sum of squares of the tile (one double per work-group, C = double[work-groups]).
-enum { OUT_BF16 = 0, OUT_F32_PARTIAL = 1, OUT_SUMSQ = 2 };
+// the sum of squares of the tile (one double per work-group, C = double[work-groups]) / rounded to bf16, rows of any length.
+enum { OUT_BF16 = 0, OUT_F32_PARTIAL = 1, OUT_SUMSQ = 2, OUT_BF16_ANY = 3 };
 
 // Tiles of a plain product (gemm_tile): BM x BN outputs, WM x WN waves over the tile, WK groups of waves that take
 // every other 16-deep contraction step, SA / SB LDS stages of the two operands, SP loads per wave and 16-deep step.
@@ -143,8 +143,10 @@ __device__ __forceinline__ bf16x8_t radem_operand(const Words4 &r, uint32_t t0) 
 // Storing that directly would touch 32 rows with 16 bytes each per instruction; instead every
 // wave passes a strip of 32 rows x 128 bytes through a private piece of LDS (`stage`, kStripBytes) and
 // writes it out with 16 bytes per lane, 8 lanes per row (full 128-byte lines).
+// ANY: N is no multiple of 8, so that rows (and those 16 bytes) start anywhere; what of a chunk lies behind a row's end is not stored.
 constexpr int kStripBytes = 32 * (128 + 16);
-template <bool BF16, bool BIAS, bool ACCUMULATE, int TM, int TN, int WAVES_K>
+typedef u32x4_t u32x4_anywhere_t __attribute__((aligned(2)));
+template <bool BF16, bool BIAS, bool ACCUMULATE, int TM, int TN, int WAVES_K, bool ANY = false>
 __device__ __forceinline__ void write_tile(const GemmArgs &g, const f32x16_t (&acc)[TM][TN], char *stage, int64_t m0, int64_t n0,
                                            int wm, int wn, int kg, int lane, int slice = 0) {
     constexpr int WTM = 32 * TM, WTN = 32 * TN;
@@ -167,7 +169,14 @@ __device__ __forceinline__ void write_tile(const GemmArgs &g, const f32x16_t (&a
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 const int64_t col = n0 + wn * WTN + b * 32 + 8 * q + 4 * h;
-                bias_v[b][q] = g.bias != nullptr && col < g.N ? *reinterpret_cast<const uint2 *>(g.bias + col) : make_uint2(0u, 0u);
+                if constexpr (ANY) {
+                    uint32_t e[4];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) e[u] = g.bias != nullptr && col + u < g.N ? g.bias[col + u] : 0u;
+                    bias_v[b][q] = make_uint2(e[0] | e[1] << 16, e[2] | e[3] << 16);
+                } else {
+                    bias_v[b][q] = g.bias != nullptr && col < g.N ? *reinterpret_cast<const uint2 *>(g.bias + col) : make_uint2(0u, 0u);
+                }
             }
     }
 #pragma unroll
@@ -225,7 +234,17 @@ __device__ __forceinline__ void write_tile(const GemmArgs &g, const f32x16_t (&a
                 const uint4 d = *reinterpret_cast<const uint4 *>(stage + rr * PITCH + ch * 16);
                 const int64_t row = row0 + rr, col = col0 + ch * (16 / EB);
                 if (row >= g.M || col >= g.N || ch * (16 / EB) >= (TN - b0) * 32) continue;
-                if constexpr (BF16)
+                if constexpr (ANY) {
+                    bf16_t *to = reinterpret_cast<bf16_t *>(g.C) + row * g.ldc + col;
+                    if (col + 8 <= g.N) {
+                        __builtin_nontemporal_store((u32x4_t){d.x, d.y, d.z, d.w}, reinterpret_cast<u32x4_anywhere_t *>(to));
+                    } else {
+                        const uint32_t w[4] = {d.x, d.y, d.z, d.w};
+#pragma unroll
+                        for (int u = 0; u < 8; ++u)
+                            if (col + u < g.N) to[u] = (bf16_t)(w[u / 2] >> (u % 2 * 16));
+                    }
+                } else if constexpr (BF16)
                     // non-temporal: all work-groups of a round write their tiles at the same time, and
                     // nothing reads them before the kernel ends
                     __builtin_nontemporal_store((u32x4_t){d.x, d.y, d.z, d.w},
@@ -653,7 +672,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &g, bf16_t *lds, int64_
     } else {
         static_assert(S::WAVES * kStripBytes <= S::LDS_BYTES, "staging area fits in LDS");
         char *strip = reinterpret_cast<char *>(lds) + wave * kStripBytes;
-        write_tile<true, AMODE == A_KCONTIG && BMODE == B_KCONTIG, AMODE == A_MCONTIG, TM, TN, S::WK>(g, acc, strip, m0, n0, wm, wn, kg, lane);
+        write_tile<true, AMODE == A_KCONTIG && BMODE == B_KCONTIG, AMODE == A_MCONTIG, TM, TN, S::WK, OUT == OUT_BF16_ANY>(g, acc, strip, m0, n0, wm, wn, kg, lane);
     }
 }
 

@@ -40,9 +40,12 @@ hipError_t launch_plain_pass_kind(const PlainLaunch &p, hipStream_t stream) {
                 RMM_PLAIN_PASS(PlainTiny, PlainTiny);
             else
                 RMM_PLAIN_PASS(PlainTiny, PlainSketch);
-        } else if (p.cfg == PLAIN_BIG)
-            RMM_PLAIN_PASS(PlainBig, PlainSketch);
-        else if (p.sketch_small)
+        } else if (p.cfg == PLAIN_BIG) {
+            if constexpr (sizeof(T) == 2 && MODE == 4 && MODE_B == 4 && BMODE == PB_K)
+                return hipErrorInvalidValue;  // (any_width_tile has others for it)
+            else
+                RMM_PLAIN_PASS(PlainBig, PlainSketch);
+        } else if (p.sketch_small)
             RMM_PLAIN_PASS(PlainMid, PlainTiny);
         else
             RMM_PLAIN_PASS(PlainMid, PlainSketch);

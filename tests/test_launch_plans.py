@@ -9,6 +9,7 @@ import numpy as np
 import pytest
 
 import paper_2201_13195_amd as rmm
+import test_gpu_any_width
 import test_gpu_few_tiles
 import test_gpu_large_tiles
 import test_gpu_pair_plans
@@ -54,6 +55,7 @@ void odd_products(int64_t es, int64_t n, int64_t d_in, int64_t d_out, int64_t k,
     }
     *o = plain_cfg((int)es, d_out, d_in, true);
 }
+int any_width(int64_t n, int64_t d, int64_t k, int64_t d_other, int kind) { return any_width_tile(plain_slices(n, d, k, d_other, kind, false).cfg, n, d_other, d); }
 int f32_tile(int64_t n, int64_t d_in, int64_t d_out, int64_t k, int64_t kind) { return plain_backward_cfg_f32(n, d_in, d_out, k, (int)kind); }
 int sors_order(int64_t n, int64_t d_sk, int64_t d_other, int64_t k) { return plan_sors(n, d_sk, d_other, k).order; }
 int64_t sors_points(int64_t n) { return (int64_t)sors_chunks(n) << (sors_chunks(n) > 1 ? 11 : sors_log(n)); }
@@ -329,3 +331,15 @@ def test_products_are_looked_at_again_where_that_is_clear(plans):
         assert plans.plain(*shape) == tile, shape
     for shape in ((24, 3072, 768), (304, 784, 304), (408, 480, 17), (416, 512, 53)):
         assert plans.plain(*shape) == "32x32", shape
+
+
+def test_y_of_any_width_takes_the_tiles_that_its_test_names(plans):
+    def tile(n, d_in, d_out, k, kind):
+        i = plans.lib.any_width(*map(ctypes.c_int64, (n, d_in, k, d_out)), ctypes.c_int(kind))
+        return TILES[i] if i >= 0 else None
+
+    for shape, kind, name in test_gpu_any_width.SHAPES:
+        assert tile(*shape, kind) == name, shape
+    assert {d_out % 8 for (_, _, d_out, _), _, _ in test_gpu_any_width.SHAPES} == set(range(1, 8))
+    for shape in ((1863, 1976, 435, 186), (300, 2000, 101, 30), (700, 300, 901, 70)):     # a round of 64 x 64 tiles, and 32 x 32
+        assert tile(*shape, rmm.GAUSSIAN) is None, shape
