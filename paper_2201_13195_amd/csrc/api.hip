@@ -183,7 +183,7 @@ int sketch_impl(int64_t n, int64_t d, int64_t k, int kind, SketchState st, const
 bool pass_is_paired(const rmm_layer_desc_t *d, int op) {
     if (d->kind == RMM_SKETCH_SORS)
         return op == RMM_OP_FORWARD ? sors_pair_available(d->n, d->d_in, d->d_out, d->k) : sors_pair_available(d->n, d->d_out, d->d_in, d->k);
-    return pass_pair_available(d->k);
+    return op == RMM_OP_FORWARD ? pass_pair_available(d->n, d->d_in, d->d_out, d->k) : pass_pair_available(d->n, d->d_out, d->d_in, d->k);
 }
 
 template <typename T>
@@ -198,7 +198,7 @@ int forward_impl(const rmm_layer_desc_t *d, SketchState st, const void *X, const
                                                 d->d_in, d->d_out, d->k, d->kind, st, stream, cut, ws));
     }
     if (X_proj != nullptr && sliced_sketch(d) && !separate_stage(ev.stage) &&
-        pass_pair_available(d->k)) {
+        pass_is_paired(d, RMM_OP_FORWARD)) {
         const bool timed = ev.stage == RMM_STAGE_FWD_PAIR;
         return from_hip(launch_forward_pair_bf16((const bf16_t *)X, (const bf16_t *)W, (const bf16_t *)bias, (bf16_t *)Y,
                                                  (bf16_t *)X_proj, d->n, d->d_in, d->d_out, d->k, d->kind, st, ws, room, stream,
@@ -261,7 +261,7 @@ int backward_impl(const rmm_layer_desc_t *d, SketchState st, const void *dY, con
         if (e != hipSuccess) return RMM_ERR_LAUNCH;
     }
     const bool paired = paired_plain || paired_sors || (sliced_sketch(d) && dX != nullptr && !separate_stage(ev.stage) &&
-                                        pass_pair_available(d->k));
+                                        pass_is_paired(d, RMM_OP_BACKWARD));
     bool db_done = sors_db || (paired_plain && ev.stage != RMM_STAGE_BWD_DBIAS);
     if (paired && !paired_sors && !paired_plain) {
         const bool timed = ev.stage == RMM_STAGE_BWD_PAIR;
@@ -282,8 +282,9 @@ int backward_impl(const rmm_layer_desc_t *d, SketchState st, const void *dY, con
     }
     if (!paired) {
         StageScope scope(ev, RMM_STAGE_BWD_G, stream);
+        // (few sketch columns without dX: nothing to share a launch with, so the streaming kernel)
         int rc = sketch_impl<T>(d->n, d->d_out, d->k, d->kind, st, dY, G, mfma, sums, stream, ev,
-                                RMM_STAGE_BWD_G_PRODUCT, d->d_in, dbias != nullptr, sors_db ? (bf16_t *)dbias : nullptr, accumulate, cut, room);
+                                RMM_STAGE_BWD_G_PRODUCT, dX != nullptr || d->k > kSmallK ? d->d_in : 0, dbias != nullptr, sors_db ? (bf16_t *)dbias : nullptr, accumulate, cut, room);
         if (rc != RMM_OK) return rc;
     }
     if (mfma && dbias != nullptr && !db_done && !own_db_stage) {

@@ -320,6 +320,14 @@ inline double pair_us(const PairPlain &plain, int64_t kk, const SketchPlan &p, i
     return t + (p.splits > 1 ? 2.6 + 0.213 * (double)p.splits * partial_mb : 0.0);
 }
 
+// Of at most kSmallK columns a pass takes no more slices than this: a quarter more than the streaming kernel of the product alone, and one.
+inline int64_t most_slices_of_pass(int64_t n, int64_t d_sk, int64_t k, int64_t room) {
+    if (k > kSmallK) return room;
+    int64_t k_chunk;
+    const int64_t alone = smallk_slices(n, d_sk, k, &k_chunk), most = alone + alone / 4 + 1;
+    return room < most ? room : most;
+}
+
 struct PassPlan {
     PairPlain plain;
     SketchPlan sketch;
@@ -419,6 +427,7 @@ inline PassPlan first_plan(int64_t n, int64_t d_sk, int64_t d_other, int64_t k, 
 constexpr double kSecondLookProducts = 6e9;
 constexpr int64_t kSecondLookTokens = 8192;
 inline PassPlan make_pass_plan(int64_t n, int64_t d_sk, int64_t d_other, int64_t k, int kind, bool limited, int64_t room) {
+    room = most_slices_of_pass(n, d_sk, k, room);
     const PassPlan best = first_plan(n, d_sk, d_other, k, kind, limited, room);
     if (limited || n > kSecondLookTokens || (double)n * (double)d_sk * (double)d_other < kSecondLookProducts) return best;
     const int alone = plan_sketch(n, d_sk, k, kind, true, room).splits, free = plan_sketch(n, d_sk, k, kind, false, room).splits;
@@ -595,7 +604,36 @@ inline PassPlan plan_backward(int64_t n, int64_t d_in, int64_t d_out, int64_t k,
     return even.sketch.splits >= 2 && pair_idle(even) >= 16 ? even : p;
 }
 
-inline bool pass_pair_available(int64_t k) { return k > kSmallK; }
+// Passes of at most kSmallK sketch columns: the paired launch, or the product and the streaming kernel one after the other.  The latter
+// computes no more rows than k asks for, where a sketch tile has 64 at least; but it reads A a second time by itself, in at most 256
+// work-groups that each go through their tokens alone (2.3 us per 64 of them), and ends with the sum of its slices (0.4 us each), and
+// beside the product's tiles the padding costs less than that.  Taken where the fitted time of the pair is 5 % less than that of the two.
+// Fitted to 650 pairs of passes of 40 to 32768 tokens, widths 256 to 4096, k = 1 to 64; over 820 others, widths 16 to 12000: 0.86 of the
+// time on average (forward 4224 x 848 -> 560, k = 64: 27.2 -> 16.0 us; 738 x 384 -> 2656: 13.3 -> 8.7), 1.11 at most and above 1.025 in 10.  Always in pairs: up to 1.8
+// where few rows meet long contractions, for which gemm_cfg has tiles that a pair has not.  Asked three times a pass, so remembered.
+inline bool small_pass_is_paired(int64_t n, int64_t d_sk, int64_t d_other, int64_t k) {
+    if (k > kSmallK) return false;
+    struct Entry {
+        int64_t n, d_sk, d_other, k;
+        bool paired;
+    };
+    constexpr size_t ENTRIES = 64;
+    static thread_local Entry memo[ENTRIES];  // (n = 0: empty)
+    const uint64_t h = (uint64_t)n * 0x9E3779B97F4A7C15u ^ (uint64_t)d_sk * 0xC2B2AE3D27D4EB4Fu ^ (uint64_t)d_other * 0x165667B19E3779F9u ^
+                       (uint64_t)k * 0x27D4EB2F165667C5u;
+    Entry &e = memo[(h ^ h >> 32) % ENTRIES];
+    if (e.n != n || e.d_sk != d_sk || e.d_other != d_other || e.k != k) {
+        int64_t k_chunk;
+        const int slices = smallk_slices(n, d_sk, k, &k_chunk);
+        const double apart = 1.1 * gemm_us(gemm_cfg(n, d_other, d_sk), n, d_other, d_sk) + 2.3 * (double)(k_chunk / 64) + 0.4 * (double)slices;
+        const PassPlan pass = first_plan(n, d_sk, d_other, k, 0, false, most_slices_of_pass(n, d_sk, k, kMostSlices));  // (one answer for either kind)
+        e = Entry{n, d_sk, d_other, k, pair_us(pass.plain, d_sk, pass.sketch, 0, (double)k * (double)d_sk * 4e-6) * 1.05 + 0.5 < apart};
+    }
+    return e.paired;
+}
+inline bool pass_pair_available(int64_t n, int64_t d_sk, int64_t d_other, int64_t k) {
+    return k > kSmallK || small_pass_is_paired(n, d_sk, d_other, k);
+}
 
 // The two dense kinds may take different tiles and slices; a workspace serves either (and both plans of
 // plan_backward: the one with a bias gradient has fewer slices).
@@ -604,7 +642,8 @@ inline size_t sketch_workspace_bf16(int64_t n, int64_t d, int64_t k, int64_t d_o
     size_t most = 0;
     if (k <= kSmallK) {
         const int s = smallk_slices(n, d, k, &k_chunk);
-        return s > 1 ? (size_t)s * (size_t)k * (size_t)d * sizeof(float) : 0;
+        most = s > 1 ? (size_t)s * (size_t)k * (size_t)d * sizeof(float) : 0;
+        if (d_other == 0 || !small_pass_is_paired(n, d, d_other, k)) return most;  // (no smaller than the streaming kernel's: without dX it runs all the same)
     }
     for (int kind = 0; kind < 2; ++kind) {
         const SketchPlan p = d_other > 0 ? plan_pass(n, d, d_other, k, kind).sketch : plan_sketch(n, d, k, kind, true);
@@ -613,10 +652,12 @@ inline size_t sketch_workspace_bf16(int64_t n, int64_t d, int64_t k, int64_t d_o
     }
     return most;
 }
-// The least that a pass runs in: two slices, or one where the partial sums are so many that the limited plan has one.
+// The least that a pass runs in: two slices, or one where the partial sums are so many that the limited plan has one; of at most
+// kSmallK columns what the streaming kernel takes (paired, such a pass makes do with fewer slices in that).
 inline size_t least_sketch_workspace_bf16(int64_t n, int64_t d, int64_t k, int64_t d_other) {
+    if (k <= kSmallK) return sketch_workspace_bf16(n, d, k);
     const size_t most = sketch_workspace_bf16(n, d, k, d_other);
-    if (k <= kSmallK || most == 0) return most;
+    if (most == 0) return most;
     const bool sliced = plan_pass(n, d, d_other, k, 0, kLimited).sketch.splits > 1 || plan_pass(n, d, d_other, k, 1, kLimited).sketch.splits > 1;
     return sliced ? (size_t)2 * (size_t)k * (size_t)d * sizeof(float) : 0;
 }

@@ -223,7 +223,7 @@ hipError_t launch_sketch_bf16(const bf16_t *A, bf16_t *out, int64_t n, int64_t d
                               void *ws, hipStream_t stream, hipEvent_t ev_begin, hipEvent_t ev_end, int64_t d_other,
                               bool with_dbias, int64_t room) {
     EventPair pev(ev_begin, ev_end, stream);
-    if (k <= kSmallK) {  // bound by one pass over A: streaming kernel
+    if (k <= kSmallK && (d_other == 0 || !small_pass_is_paired(n, d, d_other, k))) {  // bound by one pass over A: streaming kernel
         SmallkArgs a{};
         a.A = A, a.n = n, a.d = d, a.k = k, a.st = st;
         const int slices = smallk_slices(n, d, k, &a.k_chunk);
@@ -272,7 +272,7 @@ hipError_t launch_forward_pair_bf16(const bf16_t *X, const bf16_t *W, const bf16
 // paired launch, unless it is made of such tiles too, on whose way into the chip column blocks can stand, and has no place for every
 // block (57 passes: 2 % faster on average; without the last condition 3395 x 3056 -> 3960, k = 339: 212 -> 247 us).
 bool backward_pair_takes_colsum_in(int64_t n, int64_t d_in, int64_t d_out, int64_t k, int kind, int64_t room) {
-    if (!pass_pair_available(k)) return false;
+    if (!pass_pair_available(n, d_out, d_in, k)) return false;
     const int cfg = gemm_cfg(d_out, d_in, k);
     const PassPlan pass = plan_backward(n, d_in, d_out, k, kind, true, room);
     if (cfg == GEMM_LARGE) return pair_idle(pass) >= (pass.plain.cfg == GEMM_LARGE ? colsum_blocks(d_out, 2) : 16);

@@ -123,3 +123,36 @@ def test_y_has_the_same_bits_beside_any_sketch(n, d, d_other):
                 Y, _ = rmm.rmm_forward(A, W, None, k, kind, 5, 1)
                 want = Y if want is None else want
                 assert torch.equal(Y, want), (kind, k)
+
+
+@pytest.mark.parametrize("shape,kind", [((8192, 776, 760, 64), rmm.GAUSSIAN),      # sketch tiles of exactly 64 rows
+                                        ((4099, 1032, 264, 33), rmm.RADEMACHER),   # ragged tokens and widths, half a sketch tile
+                                        ((640, 512, 2056, 25), rmm.GAUSSIAN),
+                                        ((1030, 264, 1000, 1), rmm.RADEMACHER),    # one sketch column
+                                        ((60, 48, 520, 3), rmm.GAUSSIAN)])         # fewer tokens than a tile has rows
+def test_few_sketch_columns_in_the_paired_launch(shape, kind):
+    """k <= 64: against the oracle, bit for bit against the separate launches, and without dX."""
+    n, d, d_other, k = shape
+    assert rmm.rmm_uses_paired_launch(n, d, d_other, k, torch.bfloat16, kind, binding.OP_FORWARD)
+    assert rmm.rmm_uses_paired_launch(n, d_other, d, k, torch.bfloat16, kind, binding.OP_BACKWARD)
+    A, W, Xp = (synth.to_torch(synth.normal(s, 0x5EED00A0 + sum(s), std), "bf16")
+                for s, std in (((n, d), 1.0), ((d_other, d), 1.0 / math.sqrt(d)), ((k, d_other), 1.0)))
+    oY, oG = o_rmm.forward(synth.to_f64(A), synth.to_f64(W), None, k, kind, 0x5EED00A1, 14)
+    want = dict(Y=oY, X_proj=oG, dX=oY, dW=oG.T @ synth.to_f64(Xp), db=synth.to_f64(A).sum(0))
+    Ad, Wd, Wt, Xpd = A.to("cuda"), W.to("cuda"), W.t().contiguous().to("cuda"), Xp.to("cuda")
+    a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    a.record(); b.record()
+    torch.cuda.synchronize()
+
+    def run(profiles=(None, None)):
+        Y, G = rmm.rmm_forward(Ad, Wd, None, k, kind, 0x5EED00A1, 14, profile=profiles[0])
+        dX, dW, db = rmm.rmm_backward(Ad, Wt, Xpd, kind, 0x5EED00A1, 14, need_dbias=True, profile=profiles[1])
+        return dict(Y=Y, X_proj=G, dX=dX, dW=dW, db=db)
+
+    paired = run()
+    for name, got in paired.items():
+        assert_close(got, want[name], name, "bf16", "few columns %s" % (shape,))
+    for name, got in run(((binding.STAGE_FWD_Y, a, b), (binding.STAGE_BWD_DX, a, b))).items():
+        assert torch.equal(got, paired[name]), name
+    dX, dW, _ = rmm.rmm_backward(Ad, Wt, Xpd, kind, 0x5EED00A1, 14, need_dX=False)
+    assert_close(dW, want["dW"], "dW", "bf16", "few columns %s, no dX" % (shape,))

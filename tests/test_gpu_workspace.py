@@ -110,6 +110,16 @@ def test_one_slice_where_passes_had_one(shape, alone):
     check_pass(shape, rmm.RADEMACHER, [0, need[0] - 4, need[0]], [up(k * d_out * 2) + up(2 * k * d_out * 4), need[1]])
 
 
+@pytest.mark.parametrize("shape", [(4099, 1032, 264, 33), (8192, 776, 760, 64), (640, 2056, 512, 25), (100, 264, 520, 5)])
+def test_few_sketch_columns_in_any_scratch(shape):
+    """k <= 64: from what the streaming kernel of the sketch product takes (none, of few tokens) up to what the query says."""
+    n, d_in, d_out, k = shape
+    for kind in (rmm.GAUSSIAN, rmm.RADEMACHER):
+        need = [rmm.rmm_workspace_bytes(n, d_in, d_out, k, torch.bfloat16, kind, op) for op in (binding.OP_FORWARD, binding.OP_BACKWARD)]
+        alone = [rmm.rmm_workspace_bytes(n, d, d, k, torch.bfloat16, kind, binding.OP_SKETCH) for d in (d_in, d_out)]
+        check_pass(shape, kind, [alone[0], need[0]], [up(k * d_out * 2) + alone[1], need[1]])
+
+
 @pytest.mark.parametrize("shape", [(201, 200, 136), (1000, 264, 520), (2100, 1800, 520), (197, 2504, 776)])
 def test_variance_monitors_in_less_scratch(shape):
     """Down to what 128 x 128 tiles of X^T dY take, and not below it; the same values but for the order of the sums."""

@@ -40,6 +40,10 @@ int odd_pass(int64_t n, int64_t d, int64_t k, int64_t d_other, int64_t backward,
 void pass_plan_in(int64_t n, int64_t d_in, int64_t d_out, int64_t k, int64_t room, int kind, int64_t *o) {
     put(plan_pass(n, d_in, d_out, k, kind, room).sketch, o), put(plan_backward(n, d_in, d_out, k, kind, true, room).sketch, o + 6);
 }
+int few_columns(int64_t n, int64_t d_sk, int64_t d_other, int64_t k, int64_t *bytes) {
+    bytes[0] = least_sketch_workspace_bf16(n, d_sk, k, d_other), bytes[1] = sketch_workspace_bf16(n, d_sk, k, d_other), bytes[2] = sketch_workspace_bf16(n, d_sk, k);
+    return small_pass_is_paired(n, d_sk, d_other, k);
+}
 int pass_plan(int64_t n, int64_t d_sk, int64_t d_other, int64_t k, int kind, int64_t *o) {
     const PassPlan p = plan_pass(n, d_sk, d_other, k, kind);
     put(p.sketch, o);
@@ -212,6 +216,32 @@ def test_passes_take_no_more_slices_than_their_scratch_holds(plans):
             for mine, theirs, splits in zip((Sketch(list(o)[:6]), Sketch(list(o)[6:])), free, asked):
                 assert 1 <= mine.splits <= room and mine.splits == mine.slices + (mine.per_tail > 0), (n, d_in, d_out, k, kind, room)
                 assert splits > room or (mine.cfg, mine.shares, mine.splits) == (theirs.cfg, theirs.shares, theirs.splits)
+
+
+def test_few_sketch_columns_run_in_the_scratch_of_the_streaming_kernel(plans):
+    """k <= 64: paired or not, the least scratch is the streaming kernel's, and a paired pass cuts its tokens into what it gets."""
+    def asked(n, d_sk, d_other, k):
+        o = (ctypes.c_int64 * 3)()
+        return bool(plans.lib.few_columns(*[ctypes.c_int64(x) for x in (n, d_sk, d_other, k)], o)), list(o)
+
+    # many tiles for the product and long slices for the streaming kernel; one row of tiles and a long contraction; more columns
+    assert asked(15360, 2048, 512, 64)[0] and asked(512, 1024, 4096, 25)[0] and asked(8192, 768, 768, 64)[0]
+    assert not asked(64, 4096, 512, 3)[0] and not asked(128, 3072, 768, 12)[0] and not asked(15360, 2048, 512, 65)[0]
+    g, paired = np.random.default_rng(20260401), 0
+    for _ in range(4000):
+        n, a, b = (int(x) for x in np.exp(g.uniform(np.log((1, 1, 1)), np.log((100000, 1500, 1500)))))
+        d_sk, d_other, k = 8 * a, 8 * b, int(g.integers(1, 65))
+        is_paired, (least, most, streaming) = asked(n, d_sk, d_other, k)
+        assert least == streaming <= most and (is_paired or most == streaming)
+        paired += is_paired
+        for size in (least, most) if is_paired else ():
+            o = (ctypes.c_int64 * 12)()
+            for kind in (0, 1):                             # (backward plans: d_in = the other width; either with a bias gradient or forward)
+                plans.lib.pass_plan_in(*[ctypes.c_int64(x) for x in (n, d_other, d_sk, k, size // (4 * k * d_sk))], ctypes.c_int(kind), o)
+                assert o[9] == 1 or o[9] * k * d_sk * 4 <= size, (n, d_sk, d_other, k, kind, size)
+                plans.lib.pass_plan_in(*[ctypes.c_int64(x) for x in (n, d_sk, d_other, k, size // (4 * k * d_sk))], ctypes.c_int(kind), o)
+                assert o[3] == 1 or o[3] * k * d_sk * 4 <= size, (n, d_sk, d_other, k, kind, size)
+    assert 1000 < paired < 3500
 
 
 def test_odd_widths_with_a_short_last_round_take_smaller_tiles(plans):
