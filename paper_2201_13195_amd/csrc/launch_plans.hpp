@@ -606,11 +606,13 @@ inline PassPlan plan_backward(int64_t n, int64_t d_in, int64_t d_out, int64_t k,
 
 // Passes of at most kSmallK sketch columns: the paired launch, or the product and the streaming kernel one after the other.  The latter
 // computes no more rows than k asks for, where a sketch tile has 64 at least; but it reads A a second time by itself, in at most 256
-// work-groups that each go through their tokens alone (2.3 us per 64 of them), and ends with the sum of its slices (0.4 us each), and
-// beside the product's tiles the padding costs less than that.  Taken where the fitted time of the pair is 5 % less than that of the two.
-// Fitted to 650 pairs of passes of 40 to 32768 tokens, widths 256 to 4096, k = 1 to 64; over 820 others, widths 16 to 12000: 0.86 of the
-// time on average (forward 4224 x 848 -> 560, k = 64: 27.2 -> 16.0 us; 738 x 384 -> 2656: 13.3 -> 8.7), 1.11 at most and above 1.025 in 10.  Always in pairs: up to 1.8
-// where few rows meet long contractions, for which gemm_cfg has tiles that a pair has not.  Asked three times a pass, so remembered.
+// work-groups that each go through their tokens alone (2.3 us per 64 of them, or 5 us and 5 TB/s where that is less), and ends with the sum of
+// its slices (0.4 us each), and beside the product's tiles the padding costs less than that.  Taken where the fitted time of the pair is 5 % less
+// than that of the two.  Over 1510 passes that were timed both ways (40 to 250000 tokens, widths 64 to 4096, k = 1 to 64) it takes 0.86 of the
+// time on average, as the better of the two each time does (forward 4224 x 848 -> 560, k = 64: 27.2 -> 16.0 us; 738 x 384 -> 2656: 13.3 ->
+// 8.7), and in 9 of them more than 1.025, 1.07 at most; 1440 others 0.85, 20 of them more than 1.025, 1.19 at most (dY of 51799 x 1984 with dX 144
+// wide, k = 11: 83 -> 99).  Without the 5 TB/s 1.34 at most (3982 x 3760 -> 200, k = 13: 29.9 -> 40.1); always in
+// pairs: up to 1.8 where few rows meet long contractions, for which gemm_cfg has tiles that a pair has not.  Asked three times a pass, so remembered.
 inline bool small_pass_is_paired(int64_t n, int64_t d_sk, int64_t d_other, int64_t k) {
     if (k > kSmallK) return false;
     struct Entry {
@@ -625,7 +627,8 @@ inline bool small_pass_is_paired(int64_t n, int64_t d_sk, int64_t d_other, int64
     if (e.n != n || e.d_sk != d_sk || e.d_other != d_other || e.k != k) {
         int64_t k_chunk;
         const int slices = smallk_slices(n, d_sk, k, &k_chunk);
-        const double apart = 1.1 * gemm_us(gemm_cfg(n, d_other, d_sk), n, d_other, d_sk) + 2.3 * (double)(k_chunk / 64) + 0.4 * (double)slices;
+        const double steps_us = 2.3 * (double)(k_chunk / 64), read_us = 5.0 + (double)n * (double)d_sk * 2e-6 / 5.0;
+        const double apart = 1.1 * gemm_us(gemm_cfg(n, d_other, d_sk), n, d_other, d_sk) + (steps_us < read_us ? steps_us : read_us) + 0.4 * (double)slices;
         const PassPlan pass = first_plan(n, d_sk, d_other, k, 0, false, most_slices_of_pass(n, d_sk, k, kMostSlices));  // (one answer for either kind)
         e = Entry{n, d_sk, d_other, k, pair_us(pass.plain, d_sk, pass.sketch, 0, (double)k * (double)d_sk * 4e-6) * 1.05 + 0.5 < apart};
     }

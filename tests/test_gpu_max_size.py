@@ -50,3 +50,18 @@ def test_operand_beyond_two_gib(k):
     print({k_: "%.2e" % v for k_, v in errs.items()}, flush=True)
     for name, e in errs.items():
         assert e <= 1e-2, (name, e)
+
+
+def test_sketch_product_alone_beyond_two_gib():
+    """k = 8 on its own is on the streaming kernel, whether a pass of these sizes is or not (whose X_proj is compared above)."""
+    n, d_in, k, kind, seed, offset, block = (1 << 20) + 128, 1024, 8, rmm.RADEMACHER, 77, 3, 1 << 16
+    X = torch.empty((n, d_in), dtype=torch.bfloat16, device=DEV)
+    for r0 in range(0, n, block):
+        rows = min(block, n - r0)
+        X[r0:r0 + rows] = torch.from_numpy(synth.pattern_rows(r0, rows, d_in, 131, 17)).to(torch.bfloat16).to(DEV)
+    got = synth.to_f64(rmm.rmm_sketch(X, k, kind, seed, offset))
+    S, want = o_sketch.sketch_S(n, k, kind, seed, offset), np.zeros((k, d_in))
+    for r0 in range(0, n, block):
+        rows = min(block, n - r0)
+        want += S[r0:r0 + rows].T @ synth.pattern_rows(r0, rows, d_in, 131, 17)
+    assert np.linalg.norm(got - want) <= 1e-2 * np.linalg.norm(want)
