@@ -189,7 +189,8 @@ inline void slice_sketch(SketchPlan &p, int64_t n, int target_wgs, double overhe
     const int64_t spare = target_wgs - s * p.tiles;
     if (spare > 0 && s < most) {
         const int64_t m = (p.tiles + spare - 1) / spare;
-        const int64_t tail_len = (int64_t)ceil(((double)units + overhead) * (double)m / (double)(s * m + 1));
+        const double tail = ((double)units + overhead) * (double)m / (double)(s * m + 1);
+        const int64_t tail_len = (int64_t)tail + ((double)(int64_t)tail < tail ? 1 : 0);
         if (s * tail_len < units && (double)tail_len < 0.92 * (double)len)
             len = tail_len, p.slices = (int)s, p.splits = (int)s + 1, p.per_tail = (int)m;
     }
@@ -218,18 +219,17 @@ constexpr SketchMenu kSketchMenu[kSketchTiles] = {{128, 256, {1.18, 0.91}}, {128
 // unsliced on 128 x 384: 102, 128 x 512: 107.)
 // `limited`: the caller may be rmm_sketch_static.  `room`: token slices that the caller's scratch holds.
 constexpr int64_t kMostSlices = 64;
-inline SketchPlan plan_sketch(int64_t n, int64_t d, int64_t k, int kind, bool limited, int64_t room = kMostSlices) {
+inline int64_t most_static_slices(int64_t n, int64_t d, int64_t k) {
     // rmm_sketch_static serves the shapes whose partial results fit RMM_STATIC_SCRATCH_BYTES with the plainest
     // tiling (rows by k, columns by d); those keep fitting, whichever tile they run with.
-    int64_t most = kMostSlices;
-    const double partial_bytes = (double)k * (double)d * 4.0;
-    if (limited) {
-        const int64_t tiles = d >= 1024 ? tiles_of(k, d, k <= 512 ? 64 : 128, 512) : d % 384 == 0 ? tiles_of(k, d, k <= 512 ? 64 : 128, 384) : tiles_of(k, d, 128, 256);
-        const int64_t blocks = (n + 127) / 128, s = tiles >= 256 ? 1 : blocks < 256 / tiles ? blocks : 256 / tiles;
-        const int64_t chunk = (blocks + s - 1) / s, slices = (blocks + chunk - 1) / chunk, fit = (int64_t)((double)RMM_STATIC_SCRATCH_BYTES / partial_bytes);
-        if (slices == 1 || slices <= fit) most = fit < 1 ? 1 : fit < kMostSlices ? fit : kMostSlices;
-    }
-    if (room < most) most = room;
+    const int64_t fit = (int64_t)((double)RMM_STATIC_SCRATCH_BYTES / ((double)k * (double)d * 4.0));
+    if (fit >= kMostSlices) return kMostSlices;
+    const int64_t tiles = d >= 1024 ? tiles_of(k, d, k <= 512 ? 64 : 128, 512) : d % 384 == 0 ? tiles_of(k, d, k <= 512 ? 64 : 128, 384) : tiles_of(k, d, 128, 256);
+    const int64_t blocks = (n + 127) / 128, s = tiles >= 256 ? 1 : blocks < 256 / tiles ? blocks : 256 / tiles;
+    const int64_t chunk = (blocks + s - 1) / s, slices = (blocks + chunk - 1) / chunk;
+    return slices == 1 || slices <= fit ? (fit < 1 ? 1 : fit) : kMostSlices;
+}
+inline SketchPlan plan_sketch_in(int64_t n, int64_t d, int64_t k, int kind, int64_t most) {
     SketchPlan best{};
     double best_us = -1.0;
     static const int order[kSketchTiles] = {SK_WIDE64, SK_WIDE, SK_MID64, SK_MID, SK_NARROW64, SK_NARROW};
@@ -238,12 +238,17 @@ inline SketchPlan plan_sketch(int64_t n, int64_t d, int64_t k, int kind, bool li
         SketchPlan p;
         p.cfg = cfg, p.tiles = tiles_of(k, d, e.bm, e.bn);
         const double step_us = e.step_us[kind != 0];
+        if (best_us >= 0.0 && (double)p.tiles * (double)((n + 63) / 64) * step_us >= 256.0 * best_us) continue;  // (its steps alone, on a full chip)
         slice_sketch(p, n, 256, 4.0 / step_us, most);
         const double us = (double)((p.shares() + 255) / 256) * (double)(p.k_chunk / 64) * step_us + 2.0 * p.per_tail +
                           (p.splits > 1 ? (double)p.splits * (double)k * (double)d * 0.82e-6 : 0.0);
         if (best_us < 0.0 || us < 0.98 * best_us) best = p, best_us = us;  // (ties: the wider tile)
     }
     return best;
+}
+inline SketchPlan plan_sketch(int64_t n, int64_t d, int64_t k, int kind, bool limited, int64_t room = kMostSlices) {
+    const int64_t most = limited ? most_static_slices(n, d, k) : kMostSlices;
+    return plan_sketch_in(n, d, k, kind, room < most ? room : most);
 }
 
 // The streaming kernel of small sketch sizes: token slices so that about one work-group per
@@ -272,10 +277,10 @@ inline int smallk_slices(int64_t n, int64_t d, int64_t k, int64_t *k_chunk) {
 
 // ---- Paired launches: which tiles and slices a pass takes.
 
-// Time until `second` jobs of t2 us each are done that follow `first` jobs of t1 us on `slots` equal slots.
+// Time until `second` jobs of t2 us each are done that follow `first` jobs of t1 us on `slots` equal slots (256 or 512).
 inline double makespan(int64_t first, double t1, int64_t second, double t2, int64_t slots) {
-    const int64_t late = first % slots, early = slots - late;  // slots that become free a round later / at once
-    const double base = (double)(first / slots) * t1;
+    const int64_t late = first & (slots - 1), early = slots - late;  // slots that become free a round later / at once
+    const double base = (double)(slots == 512 ? first >> 9 : first >> 8) * t1;
     double t = 0.0;
     for (int64_t i = 0, j = 0, done = 0; done < second;) {  // rounds of the early slots and of the late ones, by the time they end
         const double e = (double)(i + 1) * t2, l = late > 0 ? t1 + (double)(j + 1) * t2 : 1e30;
@@ -287,12 +292,27 @@ inline double makespan(int64_t first, double t1, int64_t second, double t2, int6
     return base + (late > 0 && t < t1 ? t1 : t);
 }
 
+// us of a work-group of either product of a paired launch, what share of that (`full`) all of them take longer on a full chip, and how many run at a
+// time.  Plans are compared by the hundred for every size that is new, so those are not walked through whose work, shared evenly by all slots, or one of whose
+// work-groups takes as long as the best plan so far (workspace queries of both directions of 768 <-> 3072 at 3600 to 8000 tokens, four plans: 30 us when all
+// were walked through, 9 now, 4 of them without the second look; k = 32 16 and 7).
+struct PairTimes {
+    double plain, sketch, full_plain, full_sketch;
+    int64_t slots;
+    double full(int64_t tiles, int64_t shares) const { return (full_plain * (double)tiles * plain + full_sketch * (double)shares * sketch) / (double)slots; }
+    double work(int64_t tiles, int64_t shares) const { return ((double)tiles * plain + (double)shares * sketch) / (double)slots; }
+    double least(int64_t tiles, int64_t shares) const {
+        const double even = work(tiles, shares), one = plain > sketch ? plain : sketch;
+        return even > one ? even : one;
+    }
+};
+
 // us of a paired launch and the sum of its slices: work-groups of either kind take a time of their own (first loads and
 // writing, and every step of 64 contraction elements) and are dealt to 256 slots in grid order, or to 512 where two share
 // a compute unit.  The times are fitted to 4300 launches of 60 passes (256 to 16384 tokens, widths 256 to 4096,
 // k = 73 to 6911; all sketch tiles, 64 to 512 work-groups): 7 % rms off.  Over those passes the plan it leads to is 3.3 % slower than the
 // best one on average and 30 % at most; plans made for the sketch product alone were 12 and 50 %.  (As above: from before the loops.)
-inline double pair_us(const PairPlain &plain, int64_t kk, const SketchPlan &p, int kind, double partial_mb, bool limited = false) {
+inline PairTimes pair_times(const PairPlain &plain, int64_t kk, const SketchPlan &p, int kind, bool limited) {
     struct Times {
         double fix, step;
     };
@@ -310,14 +330,20 @@ inline double pair_us(const PairPlain &plain, int64_t kk, const SketchPlan &p, i
     // say the least scratch of a pass, are made without.
     const SketchTimes &b = !two ? sk[p.cfg] : !limited && p.slices == 1 && p.shares() > 256 ? sk_compact_two : sk_compact;
     const double ta = a.fix + a.step * (double)((kk + 63) / 64), tb = b.fix + b.step[kind != 0] * (double)(p.k_chunk / 64);
-    const int64_t slots = two ? 512 : 256;
-    double t = sketch_goes_first(plain.tiles, p.slices) ? makespan(p.shares(), tb, plain.tiles, ta, slots)
-                                                        : makespan(plain.tiles, ta, p.shares(), tb, slots);
+    return PairTimes{ta, tb, 0.0, 0.0, two ? 512 : 256};
+}
+// (`enough`: a plan that cannot be below need not be told exactly)
+inline double pair_us(const PairPlain &plain, int64_t kk, const SketchPlan &p, int kind, double partial_mb, bool limited = false, double enough = 1e30) {
+    const PairTimes us = pair_times(plain, kk, p, kind, limited);
+    const double ta = us.plain, tb = us.sketch, sum = p.splits > 1 ? 2.6 + 0.213 * (double)p.splits * partial_mb : 0.0;
+    if (const double least = us.least(plain.tiles, p.shares()) + sum; least >= enough) return least;
+    double t = sketch_goes_first(plain.tiles, p.slices) ? makespan(p.shares(), tb, plain.tiles, ta, us.slots)
+                                                        : makespan(plain.tiles, ta, p.shares(), tb, us.slots);
     // Beside 256 x 256 tiles, several rounds of them, power limits the chip's clock and a sketch work-group as long as the launch takes a
     // tenth more (16384 x 1024 -> 4096, k = 1638, Rademacher: 78 work-groups of 169 us by the times above 202 us with the sum of the
     // slices, 91 of 115 185).
     if (plain.cfg == GEMM_LARGE && plain.tiles > 256 && t < 1.1 * tb) t = 1.1 * tb;
-    return t + (p.splits > 1 ? 2.6 + 0.213 * (double)p.splits * partial_mb : 0.0);
+    return t + sum;
 }
 
 // Of at most kSmallK columns a pass takes no more slices than this: a quarter more than the streaming kernel of the product alone, and one.
@@ -338,7 +364,7 @@ struct PassPlan {
 // take (`full`: power, and lines from L2).  What a round more or less would change is taken at plain tiles of 0.9 and of 1.1 of their time, so that
 // no plan is taken for a round that it may just miss.  Fitted to 135000 launches of 446 passes with kSecondLookProducts and more (all sketch tiles, 64 to 512
 // work-groups of them, either order).
-inline double pass_us(const PassPlan &p, int64_t kk, int kind, double partial_mb) {
+inline PairTimes pass_times(const PassPlan &p, int64_t kk, int kind) {
     struct Times {
         double fix, step, full;
     };
@@ -353,11 +379,16 @@ inline double pass_us(const PassPlan &p, int64_t kk, int kind, double partial_mb
     const Times &a = p.plain.cfg == GEMM_LARGE ? large : p.plain.cfg == GEMM_WIDE ? wide : two ? compact : mid;
     const SketchTimes &b = two ? sk_compact : sk[p.sketch.cfg];
     const double ta = a.fix + a.step * (double)((kk + 63) / 64), tb = b.fix + b.step[kind != 0] * (double)(p.sketch.k_chunk / 64);
-    const int64_t slots = two ? 512 : 256, tiles = p.plain.tiles, shares = p.sketch.shares();
+    return PairTimes{ta, tb, a.full, b.full, two ? 512 : 256};
+}
+inline double pass_sum_us(const SketchPlan &p, double partial_mb) { return p.splits > 1 ? 1.2 + 0.304 * (double)p.splits * partial_mb : 0.0; }
+inline double pass_us(const PassPlan &p, int64_t kk, int kind, double partial_mb) {
+    const PairTimes us = pass_times(p, kk, kind);
+    const int64_t tiles = p.plain.tiles, shares = p.sketch.shares();
     double longest = 0.0;
-    for (double f : {0.89, 1.11}) longest += 0.5 * (p.sketch_first ? makespan(shares, tb, tiles, f * ta, slots) : makespan(tiles, f * ta, shares, tb, slots));
-    const double full = (a.full * (double)tiles * ta + b.full * (double)shares * tb) / (double)slots;
-    return longest + full + (p.sketch.splits > 1 ? 1.2 + 0.304 * (double)p.sketch.splits * partial_mb : 0.0);
+    for (double f : {0.89, 1.11})
+        longest += 0.5 * (p.sketch_first ? makespan(shares, us.sketch, tiles, f * us.plain, us.slots) : makespan(tiles, f * us.plain, shares, us.sketch, us.slots));
+    return longest + us.full(tiles, shares) + pass_sum_us(p.sketch, partial_mb);
 }
 
 // The plain product of a pass (n x m outputs) beside a sketch product on one work-group per compute unit: 256 x 256 tiles where it
@@ -375,6 +406,17 @@ inline int dx_cfg(int cfg, int64_t kk) { return cfg == GEMM_MID && kk >= 1536 ? 
 // More token slices than a pass may have over its sketch product alone.
 inline bool too_many(int splits, int of_alone) { return splits > 1 && (of_alone == 1 || 4 * (splits - 1) > 5 * of_alone); }
 
+// The sketch product of a pass by itself.
+struct SketchAlone {
+    SketchPlan plan;  // as rmm_sketch_static has it
+    int free_splits;  // slices without that limit
+};
+inline SketchAlone sketch_alone(int64_t n, int64_t d, int64_t k, int kind, bool limited, int64_t room) {
+    const int64_t most = most_static_slices(n, d, k);
+    const SketchPlan p = plan_sketch_in(n, d, k, kind, room < most ? room : most);
+    return SketchAlone{p, limited || room <= most ? p.splits : plan_sketch_in(n, d, k, kind, room < kMostSlices ? room : kMostSlices).splits};
+}
+
 // Plan of a pass: sketch of the n x d_sk operand, plain product n x d_other over d_sk.  Every sketch tile with slices for 64
 // to 320 work-groups, and 64 x 256 tiles with ShapeCompact where all work-groups are resident at once.  (4096 x 768 ->
 // 768, k = 410, with the sum of its slices: 26.9 -> 21.3 us; 4096 x 3072 -> 768, k = 2048, Rademacher 82 -> 69; 3001 x 1304 ->
@@ -387,28 +429,55 @@ inline bool too_many(int splits, int of_alone) { return splits > 1 && (of_alone 
 // the product alone takes without that limit, for 8 % of the model's time (`limited`: not so).  (12531 x 760 -> 272, k =
 // 6265, Rademacher, forward: 172 us in one slice, 124 in two and a short one; 26 of 260 passes with k from a fifth of the tokens on, 8 % faster
 // on average, 1.00 to 1.20.  With a margin of 5 % two of 28 lose 5 %.)
-inline PassPlan first_plan(int64_t n, int64_t d_sk, int64_t d_other, int64_t k, int kind, bool limited, int64_t room) {
-    const SketchPlan alone = plan_sketch(n, d_sk, k, kind, true, room);
-    const int most = limited ? alone.splits : plan_sketch(n, d_sk, k, kind, false, room).splits;
+constexpr int kCutTargets[] = {64, 96, 128, 160, 192, 224, 256, 320, 384, 448, 512};
+constexpr int kCuts = sizeof(kCutTargets) / sizeof(int);
+// The ways to cut a sketch product, each made when it is first asked for.
+class SketchCuts {
+public:
+    SketchCuts(int64_t n, int64_t d_sk, int64_t k, int kind, int64_t room) : n_(n), room_(room), kind_(kind != 0) {
+        for (int cfg = 0; cfg < kSketchTiles; ++cfg) {
+            for (SketchPlan &p : plans_[cfg]) p.slices = 0;
+            tiles_[cfg] = tiles_of(k, d_sk, kSketchMenu[cfg].bm, kSketchMenu[cfg].bn);
+        }
+    }
+    const SketchPlan &get(int cfg, int target) {
+        SketchPlan &p = plans_[cfg][target];
+        if (p.slices == 0) {
+            p.cfg = cfg, p.tiles = tiles_[cfg];
+            slice_sketch(p, n_, kCutTargets[target], 4.0 / kSketchMenu[cfg].step_us[kind_], room_);
+        }
+        return p;
+    }
+    // on tiles of `cfg` in one slice: no slices of it are less work
+    SketchPlan whole(int cfg) const { return SketchPlan{cfg, 1, 0, 1, (n_ + 63) / 64 * 64, tiles_[cfg]}; }
+
+private:
+    int64_t n_, room_, tiles_[kSketchTiles];
+    int kind_;
+    SketchPlan plans_[kSketchTiles][kCuts];  // (slices = 0: not cut yet)
+};
+inline PassPlan first_plan(SketchCuts &cuts, int64_t n, int64_t d_sk, int64_t d_other, int64_t k, int kind, bool limited, const SketchAlone &alone) {
     const double partial_mb = (double)k * (double)d_sk * 4e-6;
     const PairPlain usual = pair_plain(n, d_other);
     const PairPlain compact{GEMM_COMPACT, (int)gemm_tiles(GEMM_COMPACT, n, d_other)};
-    PassPlan best{usual, alone, false};
-    double best_us = pair_us(usual, d_sk, alone, kind, partial_mb, limited) - 0.8;
+    PassPlan best{usual, alone.plan, false};
+    double best_us = pair_us(usual, d_sk, alone.plan, kind, partial_mb, limited) - 0.8;
     for (int cfg = 0; cfg < kSketchTiles; ++cfg) {
+        const SketchPlan whole = cuts.whole(cfg);
+        const bool may_share = cfg == SK_NARROW64 && usual.cfg != GEMM_LARGE && compact.tiles + whole.tiles <= 512;
+        if (!may_share && pair_times(usual, d_sk, whole, kind, limited).work(usual.tiles, whole.tiles) >= best_us) continue;
         int slices = -1, per_tail = -1;
-        for (int target : {64, 96, 128, 192, 256, 320}) {
-            SketchPlan p;
-            p.cfg = cfg, p.tiles = tiles_of(k, d_sk, kSketchMenu[cfg].bm, kSketchMenu[cfg].bn);
-            slice_sketch(p, n, target, 4.0 / kSketchMenu[cfg].step_us[kind != 0], room);
+        for (int target : {0, 1, 2, 4, 6, 7}) {
+            const SketchPlan &p = cuts.get(cfg, target);
             if (p.slices == slices && p.per_tail == per_tail) continue;
             slices = p.slices, per_tail = p.per_tail;
-            if (too_many(p.splits, alone.splits) && too_many(p.splits, most)) continue;
-            const double worth = too_many(p.splits, alone.splits) ? 1.08 : 1.0;
-            double us = worth * pair_us(usual, d_sk, p, kind, partial_mb, limited);
+            const bool many = too_many(p.splits, alone.plan.splits);
+            if (many && too_many(p.splits, alone.free_splits)) continue;
+            const double worth = many ? 1.08 : 1.0;
+            double us = worth * pair_us(usual, d_sk, p, kind, partial_mb, limited, 1.0001 * best_us / worth);
             if (us < best_us) best = PassPlan{usual, p, false}, best_us = us;
-            if (cfg != SK_NARROW64 || usual.cfg == GEMM_LARGE || compact.tiles + p.shares() > 512) continue;
-            us = worth * pair_us(compact, d_sk, p, kind, partial_mb, limited);
+            if (!may_share || compact.tiles + p.shares() > 512) continue;
+            us = worth * pair_us(compact, d_sk, p, kind, partial_mb, limited, 1.0001 * best_us / worth);
             if (us < best_us) best = PassPlan{compact, p, false}, best_us = us;
         }
     }
@@ -426,34 +495,59 @@ inline PassPlan first_plan(int64_t n, int64_t d_sk, int64_t d_other, int64_t k, 
 // made up as much of launches, first loads and sums, and first_plan is 1 to 3 % behind the best plan.
 constexpr double kSecondLookProducts = 6e9;
 constexpr int64_t kSecondLookTokens = 8192;
-inline PassPlan make_pass_plan(int64_t n, int64_t d_sk, int64_t d_other, int64_t k, int kind, bool limited, int64_t room) {
-    room = most_slices_of_pass(n, d_sk, k, room);
-    const PassPlan best = first_plan(n, d_sk, d_other, k, kind, limited, room);
-    if (limited || n > kSecondLookTokens || (double)n * (double)d_sk * (double)d_other < kSecondLookProducts) return best;
-    const int alone = plan_sketch(n, d_sk, k, kind, true, room).splits, free = plan_sketch(n, d_sk, k, kind, false, room).splits;
+inline PassPlan second_plan(const PassPlan &best, SketchCuts &cuts, int64_t n, int64_t d_sk, int64_t d_other, int64_t k, int kind, const SketchAlone &alone) {
     const double partial_mb = (double)k * (double)d_sk * 4e-6;
     PassPlan now = best;
     double now_us = 0.91 * pass_us(best, d_sk, kind, partial_mb);
+    struct Cut {
+        SketchPlan plan;
+        double longest, work, more;  // of one of its work-groups; shared evenly by all compute units; what a full chip and the sum of the slices add
+    } some[kSketchTiles][kCuts];
+    int count[kSketchTiles];  // (-1: not looked at yet)
+    for (int &c : count) c = -1;
     for (int plain_cfg : {GEMM_LARGE, GEMM_WIDE, GEMM_MID}) {
         const PairPlain plain{plain_cfg, (int)gemm_tiles(plain_cfg, n, d_other)};
         for (int cfg = 0; cfg < kSketchTiles; ++cfg) {
-            int shares = -1;
-            for (int target : {64, 96, 128, 160, 192, 224, 256, 320, 384, 448, 512}) {
-                PassPlan p{plain, {}, false};
-                p.sketch.cfg = cfg, p.sketch.tiles = tiles_of(k, d_sk, kSketchMenu[cfg].bm, kSketchMenu[cfg].bn);
-                slice_sketch(p.sketch, n, target, 4.0 / kSketchMenu[cfg].step_us[kind != 0], room);
-                if (p.sketch.shares() == shares) continue;
-                shares = p.sketch.shares();
-                if (too_many(p.sketch.splits, alone) && too_many(p.sketch.splits, free)) continue;
+            PassPlan p{plain, cuts.whole(cfg), false};
+            const PairTimes us = pass_times(p, d_sk, kind);
+            const double plain_work = us.work(plain.tiles, 0), plain_more = us.full(plain.tiles, 0);
+            if (plain_work + plain_more + us.work(0, p.sketch.tiles) + us.full(0, p.sketch.tiles) >= 1.0001 * now_us) continue;  // (in one slice; more are no less)
+            if (count[cfg] < 0) {
+                count[cfg] = 0;
+                int shares = -1;
+                for (int target = 0; target < kCuts; ++target) {
+                    p.sketch = cuts.get(cfg, target);
+                    if (p.sketch.shares() == shares) continue;
+                    shares = p.sketch.shares();
+                    if (too_many(p.sketch.splits, alone.plan.splits) && too_many(p.sketch.splits, alone.free_splits)) continue;
+                    const PairTimes t = pass_times(p, d_sk, kind);
+                    some[cfg][count[cfg]++] = Cut{p.sketch, t.sketch, t.work(0, shares), t.full(0, shares) + pass_sum_us(p.sketch, partial_mb)};
+                }
+            }
+            for (int i = 0; i < count[cfg]; ++i) {
+                const Cut &c = some[cfg][i];
+                double least = plain_work + c.work;
+                if (least < us.plain) least = us.plain;
+                if (least < c.longest) least = c.longest;
+                if (least + plain_more + c.more >= 1.0001 * now_us) continue;
+                p.sketch = c.plan;
                 for (bool first : {false, true}) {
                     p.sketch_first = first;
-                    const double us = pass_us(p, d_sk, kind, partial_mb);
-                    if (us < now_us) now = p, now_us = us;
+                    const double all = pass_us(p, d_sk, kind, partial_mb);
+                    if (all < now_us) now = p, now_us = all;
                 }
             }
         }
     }
     return now;
+}
+inline PassPlan make_pass_plan(int64_t n, int64_t d_sk, int64_t d_other, int64_t k, int kind, bool limited, int64_t room) {
+    room = most_slices_of_pass(n, d_sk, k, room);
+    const SketchAlone alone = sketch_alone(n, d_sk, k, kind, limited, room);
+    SketchCuts cuts(n, d_sk, k, kind, room);
+    const PassPlan best = first_plan(cuts, n, d_sk, d_other, k, kind, limited, alone);
+    if (limited || n > kSecondLookTokens || (double)n * (double)d_sk * (double)d_other < kSecondLookProducts) return best;
+    return second_plan(best, cuts, n, d_sk, d_other, k, kind, alone);
 }
 
 // The same, remembered: a pass asks for its plan three times (workspace of either kind, launch), and it depends on the
@@ -630,7 +724,9 @@ inline bool small_pass_is_paired(int64_t n, int64_t d_sk, int64_t d_other, int64
         const int slices = smallk_slices(n, d_sk, k, &k_chunk);
         const double steps_us = 2.3 * (double)(k_chunk / 64), read_us = 5.0 + (double)n * (double)d_sk * 2e-6 / 5.0;
         const double apart = 1.1 * gemm_us(gemm_cfg(n, d_other, d_sk), n, d_other, d_sk) + (steps_us < read_us ? steps_us : read_us) + 0.4 * (double)slices;
-        const PassPlan pass = first_plan(n, d_sk, d_other, k, 0, false, most_slices_of_pass(n, d_sk, k, kMostSlices));  // (one answer for either kind)
+        const int64_t room = most_slices_of_pass(n, d_sk, k, kMostSlices);
+        SketchCuts cuts(n, d_sk, k, 0, room);
+        const PassPlan pass = first_plan(cuts, n, d_sk, d_other, k, 0, false, sketch_alone(n, d_sk, k, 0, false, room));  // (one answer for either kind)
         e = Entry{n, d_sk, d_other, k, pair_us(pass.plain, d_sk, pass.sketch, 0, (double)k * (double)d_sk * 4e-6) * 1.05 + 0.5 < apart};
     }
     return e.paired;

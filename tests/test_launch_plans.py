@@ -105,16 +105,87 @@ class Plans:
         return tile, Sketch(list(o))
 
 
-@pytest.fixture(scope="module")
-def plans(tmp_path_factory):
+def compiled(where, source):
     if shutil.which("g++") is None:
         pytest.skip("no host compiler")
-    where = tmp_path_factory.mktemp("plans")
     src, lib = str(where / "plans.cpp"), str(where / "plans.so")
     with open(src, "w") as f:
-        f.write(SOURCE % HEADER)
+        f.write(source)
     subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Wextra", "-Werror", "-shared", "-fPIC", src, "-o", lib], check=True)
-    return Plans(ctypes.CDLL(lib))
+    return ctypes.CDLL(lib)
+
+
+@pytest.fixture(scope="module")
+def plans(tmp_path_factory):
+    return Plans(compiled(tmp_path_factory.mktemp("plans"), SOURCE % HEADER))
+
+
+# A search that walks through every plan, to compare the header's with, and counters of what the header's costs.
+SEARCH = """
+using namespace rmm;
+static PassPlan every_plan(int64_t n, int64_t d_sk, int64_t d_other, int64_t k, int kind, int64_t room) {
+    room = most_slices_of_pass(n, d_sk, k, room);
+    const SketchPlan alone = plan_sketch(n, d_sk, k, kind, true, room), free = plan_sketch(n, d_sk, k, kind, false, room);
+    const double mb = (double)k * (double)d_sk * 4e-6;
+    const PairPlain usual = pair_plain(n, d_other), compact{GEMM_COMPACT, (int)gemm_tiles(GEMM_COMPACT, n, d_other)};
+    PassPlan best{usual, alone, false};
+    double best_us = pair_us(usual, d_sk, alone, kind, mb) - 0.8;
+    auto cut = [&](int cfg, int target) {
+        SketchPlan p;
+        p.cfg = cfg, p.tiles = tiles_of(k, d_sk, kSketchMenu[cfg].bm, kSketchMenu[cfg].bn);
+        slice_sketch(p, n, target, 4.0 / kSketchMenu[cfg].step_us[kind], room);
+        return p;
+    };
+    for (int cfg = 0; cfg < kSketchTiles; ++cfg)
+        for (int target : {64, 96, 128, 192, 256, 320}) {
+            const SketchPlan p = cut(cfg, target);
+            const bool many = too_many(p.splits, alone.splits);
+            if (many && too_many(p.splits, free.splits)) continue;
+            for (const PairPlain &plain : {usual, compact}) {
+                if (plain.cfg == GEMM_COMPACT && (cfg != SK_NARROW64 || usual.cfg == GEMM_LARGE || compact.tiles + p.shares() > 512)) continue;
+                const double us = (many ? 1.08 : 1.0) * pair_us(plain, d_sk, p, kind, mb);
+                if (us < best_us) best = PassPlan{plain, p, false}, best_us = us;
+            }
+        }
+    best.sketch_first = sketch_goes_first(best.plain.tiles, best.sketch.slices);
+    if (n > kSecondLookTokens || (double)n * (double)d_sk * (double)d_other < kSecondLookProducts) return best;
+    best_us = 0.91 * pass_us(best, d_sk, kind, mb);
+    for (int tile : {GEMM_LARGE, GEMM_WIDE, GEMM_MID})
+        for (int cfg = 0; cfg < kSketchTiles; ++cfg)
+            for (int target : {64, 96, 128, 160, 192, 224, 256, 320, 384, 448, 512})
+                for (bool first : {false, true}) {
+                    const PassPlan p{PairPlain{tile, (int)gemm_tiles(tile, n, d_other)}, cut(cfg, target), first};
+                    if (too_many(p.sketch.splits, alone.splits) && too_many(p.sketch.splits, free.splits)) continue;
+                    const double us = pass_us(p, d_sk, kind, mb);
+                    if (us < best_us) best = p, best_us = us;
+                }
+    return best;
+}
+extern "C" {
+int same_plan(int64_t n, int64_t d_sk, int64_t d_other, int64_t k, int kind, int64_t room) {
+    const PassPlan a = make_pass_plan(n, d_sk, d_other, k, kind, false, room), b = every_plan(n, d_sk, d_other, k, kind, room);
+    const SketchPlan &s = a.sketch, &t = b.sketch;
+    return a.plain.cfg == b.plain.cfg && a.sketch_first == b.sketch_first && s.cfg == t.cfg && s.slices == t.slices && s.per_tail == t.per_tail &&
+           s.splits == t.splits && s.k_chunk == t.k_chunk;
+}
+void queries(int64_t n, int64_t a, int64_t b, int64_t k, int64_t *walked_and_cut) {   // the workspace queries of both directions
+    walks = cuts = 0;
+    (void)(sketch_workspace_bf16(n, a, k, b) + sketch_workspace_bf16(n, b, k, a));
+    walked_and_cut[0] = walks, walked_and_cut[1] = cuts;
+}
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def search(tmp_path_factory):
+    with open(HEADER) as f:
+        source = f.read().replace('"../../include/rmm.h"', '"%s"' % os.path.join(HERE, "..", "include", "rmm.h")).replace("#pragma once", "")
+    for function, counter in (("inline double makespan(", "walks"), ("inline void slice_sketch(", "cuts")):
+        at = source.index("{\n", source.index(function)) + 1
+        source = source[:at] + " ++%s;" % counter + source[at:]
+    head, body = source.split("namespace rmm", 1)
+    return compiled(tmp_path_factory.mktemp("search"), head + "static int64_t walks, cuts;\nnamespace rmm" + body + SEARCH)
 
 
 def cases(test):
@@ -373,3 +444,28 @@ def test_y_of_any_width_takes_the_tiles_that_its_test_names(plans):
     assert {d_out % 8 for (_, _, d_out, _), _, _ in test_gpu_any_width.SHAPES} == set(range(1, 8))
     for shape in ((1863, 1976, 435, 186), (300, 2000, 101, 30), (700, 300, 901, 70)):     # a round of 64 x 64 tiles, and 32 x 32
         assert tile(*shape, rmm.GAUSSIAN) is None, shape
+
+
+def test_plans_are_the_best_ones_of_all(search):
+    """The search leaves out what cannot be better: the same plans as one that walks through all of them."""
+    g = np.random.default_rng(20260501)
+    for i in range(4000):
+        low, high = ((1, 1, 1), (16384, 500, 500)) if i % 2 else ((1000, 90, 90), (8192, 1024, 1024))
+        n, a, b = (int(x) for x in np.exp(g.uniform(np.log(low), np.log(high))))
+        k = int(g.integers(1, 65)) if i % 5 == 0 else max(1, int(g.choice([0.05, 0.1, 0.2, 0.5, 0.9]) * n))
+        kind, room = int(g.integers(0, 2)), int(g.choice([0, 1, 2, 3, 7, 64, 64, 64]))
+        assert search.same_plan(*map(ctypes.c_int64, (n, 8 * a, 8 * b, k)), ctypes.c_int(kind), ctypes.c_int64(room)), (n, 8 * a, 8 * b, k, kind, room)
+
+
+def test_a_new_token_count_is_planned_with_few_walks(search):
+    """Batches without padding have another token count each: what its four plans cost (both directions and kinds) stands in front of the launches.
+    Walked through one by one they were 2000 walks and 1000 cuts for widths of 768 and 3072 at rho 0.1 (30 us)."""
+    for a, b, rho in ((768, 3072, 0.1), (1024, 4096, 0.1), (3072, 3072, 0.5), (768, 768, 0.1)):
+        counts = []
+        for n in range(3001, 8000, 13):
+            o = (ctypes.c_int64 * 2)()
+            search.queries(*map(ctypes.c_int64, (n, a, b, int(rho * n))), o)
+            counts.append(list(o))
+        walked, cut = np.mean(counts, axis=0)
+        print(a, b, rho, walked, cut)
+        assert walked <= 260 and cut <= 350, (a, b, rho, walked, cut)
