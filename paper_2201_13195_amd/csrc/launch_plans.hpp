@@ -485,6 +485,58 @@ inline PassPlan first_plan(SketchCuts &cuts, int64_t n, int64_t d_sk, int64_t d_
     return best;
 }
 
+// What a pass asks for three times (workspace of either kind, launch) and depends on its sizes alone, remembered by each thread.  In sets
+// of four places, the latest first, so that the four plans of a layer, both kinds and directions, never put each other out.  (In single places the
+// directions of one in 64 layers of few sketch columns did, in pairs three of the four plans of one in 260: its queries took 7 us and more, 50 ns each now.)
+struct Sizes {
+    int64_t n, d_sk, d_other, k, what;
+    bool operator==(const Sizes &o) const { return n == o.n && d_sk == o.d_sk && d_other == o.d_other && k == o.k && what == o.what; }
+};
+template <typename Value, typename Make>
+Value remembered(const Sizes &s, Make make) {
+    struct Entry {
+        Sizes sizes;
+        Value value;
+    };
+    constexpr size_t SETS = 32, PLACES = 4;
+    static thread_local Entry memo[SETS][PLACES];  // (n = 0: empty)
+    const uint64_t h = ((uint64_t)s.n * 0x9E3779B97F4A7C15u ^ (uint64_t)s.d_sk * 0xC2B2AE3D27D4EB4Fu ^ (uint64_t)s.d_other * 0x165667B19E3779F9u ^
+                        (uint64_t)s.k * 0x27D4EB2F165667C5u) + (uint64_t)s.what * 0xD6E8FEB86659FD93u;
+    Entry *set = memo[(h ^ h >> 32) % SETS];
+    for (size_t i = 0; i < PLACES; ++i)
+        if (set[i].sizes == s) return set[i].value;
+    const Entry made{s, make()};
+    for (size_t i = PLACES - 1; i > 0; --i) set[i] = set[i - 1];  // (the oldest goes)
+    return (set[0] = made).value;
+}
+
+// Passes of at most kSmallK sketch columns: the paired launch, or the product and the streaming kernel one after the other.  The latter
+// computes no more rows than k asks for, where a sketch tile has 64 at least; but it reads A a second time by itself, in at most 256
+// work-groups that each go through their tokens alone (2.3 us per 64 of them, or 5 us and 5 TB/s where that is less), and ends with the sum of
+// its slices (0.4 us each), and beside the product's tiles the padding costs less than that.  Taken where the fitted time of the pair is 5 % less
+// than that of the two.  Over 1510 passes that were timed both ways (40 to 250000 tokens, widths 64 to 4096, k = 1 to 64) it takes 0.86 of the
+// time on average, as the better of the two each time does (forward 4224 x 848 -> 560, k = 64: 27.2 -> 16.0 us; 738 x 384 -> 2656: 13.3 ->
+// 8.7), and in 9 of them more than 1.025, 1.07 at most; 1440 others 0.85, 20 of them more than 1.025, 1.19 at most (dY of 51799 x 1984 with dX 144
+// wide, k = 11: 83 -> 99).  Without the 5 TB/s 1.34 at most (3982 x 3760 -> 200, k = 13: 29.9 -> 40.1); always in
+// pairs: up to 1.8 where few rows meet long contractions, for which gemm_cfg has tiles that a pair has not.
+struct SmallPass {
+    bool paired;
+    PassPlan first;  // of the Gaussian kind, which answers for either
+};
+inline SmallPass small_pass(int64_t n, int64_t d_sk, int64_t d_other, int64_t k) {
+    return remembered<SmallPass>(Sizes{n, d_sk, d_other, k, 0}, [&] {
+        int64_t k_chunk;
+        const int slices = smallk_slices(n, d_sk, k, &k_chunk);
+        const double steps_us = 2.3 * (double)(k_chunk / 64), read_us = 5.0 + (double)n * (double)d_sk * 2e-6 / 5.0;
+        const double apart = 1.1 * gemm_us(gemm_cfg(n, d_other, d_sk), n, d_other, d_sk) + (steps_us < read_us ? steps_us : read_us) + 0.4 * (double)slices;
+        const int64_t room = most_slices_of_pass(n, d_sk, k, kMostSlices);
+        SketchCuts cuts(n, d_sk, k, 0, room);
+        const PassPlan pass = first_plan(cuts, n, d_sk, d_other, k, 0, false, sketch_alone(n, d_sk, k, 0, false, room));
+        return SmallPass{pair_us(pass.plain, d_sk, pass.sketch, 0, (double)k * (double)d_sk * 4e-6) * 1.05 + 0.5 < apart, pass};
+    });
+}
+inline bool small_pass_is_paired(int64_t n, int64_t d_sk, int64_t d_other, int64_t k) { return k <= kSmallK && small_pass(n, d_sk, d_other, k).paired; }
+
 // A second look at large passes, by pass_us: 256 x 256 tiles also where they do not fill the chip, 128 x 256 tiles, and either order, with any sketch
 // tile.  At headline size dX on 96 tiles of 128 x 256 beside 112 sketch work-groups of 64 x 384, a compute unit each, takes the place
 // of 192 tiles of 128 x 128 two by two with 168 of 64 x 256: a step that two work-groups of a compute unit share takes them 0.8 us, and some
@@ -542,26 +594,19 @@ inline PassPlan second_plan(const PassPlan &best, SketchCuts &cuts, int64_t n, i
     return now;
 }
 inline PassPlan make_pass_plan(int64_t n, int64_t d_sk, int64_t d_other, int64_t k, int kind, bool limited, int64_t room) {
+    const bool known = k <= kSmallK && kind == 0 && !limited && room >= kMostSlices;  // (whether such a pass is paired has been asked before)
     room = most_slices_of_pass(n, d_sk, k, room);
+    const bool again = !limited && n <= kSecondLookTokens && (double)n * (double)d_sk * (double)d_other >= kSecondLookProducts;
+    if (known && !again) return small_pass(n, d_sk, d_other, k).first;
     const SketchAlone alone = sketch_alone(n, d_sk, k, kind, limited, room);
     SketchCuts cuts(n, d_sk, k, kind, room);
-    const PassPlan best = first_plan(cuts, n, d_sk, d_other, k, kind, limited, alone);
-    if (limited || n > kSecondLookTokens || (double)n * (double)d_sk * (double)d_other < kSecondLookProducts) return best;
-    return second_plan(best, cuts, n, d_sk, d_other, k, kind, alone);
+    const PassPlan best = known ? small_pass(n, d_sk, d_other, k).first : first_plan(cuts, n, d_sk, d_other, k, kind, limited, alone);
+    return again ? second_plan(best, cuts, n, d_sk, d_other, k, kind, alone) : best;
 }
 
-// The same, remembered: a pass asks for its plan three times (workspace of either kind, launch), and it depends on the
-// sizes alone.  In pairs of places, the later one first, so that the kinds of a pass cannot put each other out (they did for half of all sizes:
-// the workspace query of 4096 x 3072 -> 768, k = 410, 13 us a call, 20 ns now).  With scratch for fewer slices than it takes, another one for these.
+// Plan of a pass, remembered.  With scratch for fewer slices than it takes, another one for these.
 constexpr int64_t kLimited = -1;  // (in place of `room`: without a limit, the `limited` plan)
 inline PassPlan plan_pass(int64_t n, int64_t d_sk, int64_t d_other, int64_t k, int kind, int64_t room = kMostSlices) {
-    struct Entry {
-        int64_t n, d_sk, d_other, k, room;
-        int kind;
-        PassPlan plan;
-    };
-    constexpr size_t ENTRIES = 64;
-    static thread_local Entry memo[ENTRIES];  // (n = 0: empty)
     if (room >= kMostSlices) {
         room = kMostSlices;
     } else if (room != kLimited) {
@@ -569,15 +614,8 @@ inline PassPlan plan_pass(int64_t n, int64_t d_sk, int64_t d_other, int64_t k, i
         if (p.sketch.splits == 1 || p.sketch.splits <= room) return p;
     }
     kind = kind != 0;
-    const uint64_t h = ((uint64_t)n * 0x9E3779B97F4A7C15u ^ (uint64_t)d_sk * 0xC2B2AE3D27D4EB4Fu ^ (uint64_t)d_other * 0x165667B19E3779F9u ^
-                        (uint64_t)k * 0x27D4EB2F165667C5u) + (uint64_t)(2 * room + kind) * 0xD6E8FEB86659FD93u;
-    const size_t at = (h ^ h >> 32) % (ENTRIES / 2) * 2;
-    auto is = [&](const Entry &e) { return e.n == n && e.d_sk == d_sk && e.d_other == d_other && e.k == k && e.room == room && e.kind == kind; };
-    for (Entry *e : {&memo[at], &memo[at + 1]})
-        if (is(*e)) return e->plan;
-    memo[at + 1] = memo[at];  // (the older of the two goes)
-    memo[at] = Entry{n, d_sk, d_other, k, room, kind, make_pass_plan(n, d_sk, d_other, k, kind, room == kLimited, room == kLimited ? kMostSlices : room)};
-    return memo[at].plan;
+    return remembered<PassPlan>(Sizes{n, d_sk, d_other, k, 2 * room + kind},
+                                [&] { return make_pass_plan(n, d_sk, d_other, k, kind, room == kLimited, room == kLimited ? kMostSlices : room); });
 }
 
 // ---- The SORS kind: strips of eight columns of the sketched operand, which may share a launch with the plain product of their pass.
@@ -699,38 +737,6 @@ inline PassPlan plan_backward(int64_t n, int64_t d_in, int64_t d_out, int64_t k,
     return even.sketch.splits >= 2 && pair_idle(even) >= 16 ? even : p;
 }
 
-// Passes of at most kSmallK sketch columns: the paired launch, or the product and the streaming kernel one after the other.  The latter
-// computes no more rows than k asks for, where a sketch tile has 64 at least; but it reads A a second time by itself, in at most 256
-// work-groups that each go through their tokens alone (2.3 us per 64 of them, or 5 us and 5 TB/s where that is less), and ends with the sum of
-// its slices (0.4 us each), and beside the product's tiles the padding costs less than that.  Taken where the fitted time of the pair is 5 % less
-// than that of the two.  Over 1510 passes that were timed both ways (40 to 250000 tokens, widths 64 to 4096, k = 1 to 64) it takes 0.86 of the
-// time on average, as the better of the two each time does (forward 4224 x 848 -> 560, k = 64: 27.2 -> 16.0 us; 738 x 384 -> 2656: 13.3 ->
-// 8.7), and in 9 of them more than 1.025, 1.07 at most; 1440 others 0.85, 20 of them more than 1.025, 1.19 at most (dY of 51799 x 1984 with dX 144
-// wide, k = 11: 83 -> 99).  Without the 5 TB/s 1.34 at most (3982 x 3760 -> 200, k = 13: 29.9 -> 40.1); always in
-// pairs: up to 1.8 where few rows meet long contractions, for which gemm_cfg has tiles that a pair has not.  Asked three times a pass, so remembered.
-inline bool small_pass_is_paired(int64_t n, int64_t d_sk, int64_t d_other, int64_t k) {
-    if (k > kSmallK) return false;
-    struct Entry {
-        int64_t n, d_sk, d_other, k;
-        bool paired;
-    };
-    constexpr size_t ENTRIES = 64;
-    static thread_local Entry memo[ENTRIES];  // (n = 0: empty)
-    const uint64_t h = (uint64_t)n * 0x9E3779B97F4A7C15u ^ (uint64_t)d_sk * 0xC2B2AE3D27D4EB4Fu ^ (uint64_t)d_other * 0x165667B19E3779F9u ^
-                       (uint64_t)k * 0x27D4EB2F165667C5u;
-    Entry &e = memo[(h ^ h >> 32) % ENTRIES];
-    if (e.n != n || e.d_sk != d_sk || e.d_other != d_other || e.k != k) {
-        int64_t k_chunk;
-        const int slices = smallk_slices(n, d_sk, k, &k_chunk);
-        const double steps_us = 2.3 * (double)(k_chunk / 64), read_us = 5.0 + (double)n * (double)d_sk * 2e-6 / 5.0;
-        const double apart = 1.1 * gemm_us(gemm_cfg(n, d_other, d_sk), n, d_other, d_sk) + (steps_us < read_us ? steps_us : read_us) + 0.4 * (double)slices;
-        const int64_t room = most_slices_of_pass(n, d_sk, k, kMostSlices);
-        SketchCuts cuts(n, d_sk, k, 0, room);
-        const PassPlan pass = first_plan(cuts, n, d_sk, d_other, k, 0, false, sketch_alone(n, d_sk, k, 0, false, room));  // (one answer for either kind)
-        e = Entry{n, d_sk, d_other, k, pair_us(pass.plain, d_sk, pass.sketch, 0, (double)k * (double)d_sk * 4e-6) * 1.05 + 0.5 < apart};
-    }
-    return e.paired;
-}
 inline bool pass_pair_available(int64_t n, int64_t d_sk, int64_t d_other, int64_t k) {
     return k > kSmallK || small_pass_is_paired(n, d_sk, d_other, k);
 }

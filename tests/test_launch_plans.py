@@ -469,3 +469,15 @@ def test_a_new_token_count_is_planned_with_few_walks(search):
         walked, cut = np.mean(counts, axis=0)
         print(a, b, rho, walked, cut)
         assert walked <= 260 and cut <= 350, (a, b, rho, walked, cut)
+
+
+def test_what_is_planned_once_stays_known(search):
+    """Both directions and kinds of a pass have a place each: asked in turn, none is planned again."""
+    g = np.random.default_rng(20260502)
+    o = (ctypes.c_int64 * 2)()
+    for _ in range(2000):
+        n, a, b = (int(x) for x in np.exp(g.uniform(np.log((256, 16, 16)), np.log((16384, 512, 512)))))
+        k = int(g.integers(1, 65)) if g.random() < 0.7 else max(65, n // 10)
+        for asked in range(3):
+            search.queries(*map(ctypes.c_int64, (n, 8 * a, 8 * b, k)), o)
+            assert (o[0] > 0) == (asked == 0), (n, 8 * a, 8 * b, k, asked)
