@@ -112,6 +112,36 @@ def test_every_pairing_of_tiles(shape, kind, plain, sketch):
     assert torch.equal(Y, Y1) and torch.equal(G, G1) and torch.equal(dX, dX1) and torch.equal(dW, dW1)
 
 
+# dX on 128 x 256 tiles with the column sums of dY in its launch, behind the plain tiles or behind sketch work-groups in front of them, with and without short last
+# slices: (tokens, d_in, d_out, k), kind.  (test_launch_plans.py: they take these.)
+WIDE_WITH_BIAS = [((1340, 2864, 2192, 1206), rmm.RADEMACHER), ((1238, 4016, 3768, 247), rmm.GAUSSIAN), ((2486, 1672, 1824, 248), rmm.RADEMACHER),
+                  ((1904, 2168, 1704, 952), rmm.GAUSSIAN), ((2582, 4072, 792, 1291), rmm.GAUSSIAN), ((2575, 3600, 784, 2317), rmm.RADEMACHER),
+                  ((2693, 1776, 1832, 134), rmm.GAUSSIAN), ((3364, 1120, 2016, 168), rmm.RADEMACHER)]
+
+
+@pytest.mark.parametrize("shape,kind", WIDE_WITH_BIAS)
+def test_bias_gradient_beside_wide_tiles(shape, kind):
+    n, d_in, d_out, k = shape
+    dY, W, Xp = (synth.to_torch(synth.normal(s, 0x5EED00B0 + sum(s), std), "bf16")
+                 for s, std in (((n, d_out), 1.0), ((d_out, d_in), 1.0 / math.sqrt(d_out)), ((k, d_in), 1.0)))
+    odX, odW, odb = o_rmm.backward(synth.to_f64(dY), synth.to_f64(W), synth.to_f64(Xp), kind, 0x5EED00B1, 16)
+    dYd, Wd, Xpd = dY.to("cuda"), W.to("cuda"), Xp.to("cuda")
+    a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    a.record(); b.record()
+    torch.cuda.synchronize()
+    got = rmm.rmm_backward(dYd, Wd, Xpd, kind, 0x5EED00B1, 16, need_dbias=True)
+    for x, want, name in zip(got, (odX, odW, odb), ("dX", "dW", "db")):
+        assert_close(x, want, name, "bf16", "wide with bias %s" % (shape,))
+    for stage in (binding.STAGE_BWD_DX, binding.STAGE_BWD_DBIAS):      # both products apart, the column sums apart
+        apart = rmm.rmm_backward(dYd, Wd, Xpd, kind, 0x5EED00B1, 16, need_dbias=True, profile=(stage, a, b))
+        assert all(torch.equal(x, y) for x, y in zip(got, apart)), stage
+    dW, db = got[1].clone(), got[2].clone()
+    again = rmm.rmm_backward(dYd, Wd, Xpd, kind, 0x5EED00B1, 16, dW=dW, dbias=db, need_dbias=True, accumulate=True)
+    assert torch.equal(again[0], got[0])
+    assert_close(db, odb + synth.to_f64(got[2]), "db", "bf16", "wide with bias, accumulated %s" % (shape,))
+    assert_close(dW, odW + synth.to_f64(got[1]), "dW", "bf16", "wide with bias, accumulated %s" % (shape,))
+
+
 @pytest.mark.parametrize("n,d,d_other", [(4096, 3072, 768), (4090, 776, 760), (2056, 1544, 1032), (16384, 1024, 1024)])
 def test_y_has_the_same_bits_beside_any_sketch(n, d, d_other):
     """k, kind and scratch choose how the launch of Y with a sketch product is made up; the bits of Y follow from its sizes."""

@@ -44,6 +44,7 @@ int few_columns(int64_t n, int64_t d_sk, int64_t d_other, int64_t k, int64_t *by
     bytes[0] = least_sketch_workspace_bf16(n, d_sk, k, d_other), bytes[1] = sketch_workspace_bf16(n, d_sk, k, d_other), bytes[2] = sketch_workspace_bf16(n, d_sk, k);
     return small_pass_is_paired(n, d_sk, d_other, k);
 }
+int sketch_first(int64_t n, int64_t d_sk, int64_t d_other, int64_t k, int kind) { return plan_pass(n, d_sk, d_other, k, kind).sketch_first; }
 int pass_plan(int64_t n, int64_t d_sk, int64_t d_other, int64_t k, int kind, int64_t *o) {
     const PassPlan p = plan_pass(n, d_sk, d_other, k, kind);
     put(p.sketch, o);
@@ -244,6 +245,17 @@ def test_every_pairing_of_tiles_is_tested(plans):
         for kind in (rmm.GAUSSIAN, rmm.RADEMACHER):
             tile, s = plans.backward(n, d_other // 8 * 8, d // 8 * 8, k, kind)
             assert (tile, SKETCH_TILES[s.cfg], kind) in named, (n, d, d_other, k)
+
+
+def test_wide_tiles_with_the_bias_gradient_are_where_their_test_expects_them(plans):
+    takes_colsum = rmm.load_library()._ZN3rmm26backward_pair_takes_colsumElllli      # rmm::backward_pair_takes_colsum
+    takes_colsum.restype, seen = ctypes.c_bool, set()
+    for shape, kind in test_gpu_pair_plans.WIDE_WITH_BIAS:
+        tile, sketch = plans.backward(*shape, kind, True)
+        assert tile == "128x256" and takes_colsum(*map(ctypes.c_int64, shape), ctypes.c_int(kind)), shape
+        n, d_in, d_out, k = shape
+        seen.add((bool(plans.lib.sketch_first(*map(ctypes.c_int64, (n, d_out, d_in, k)), ctypes.c_int(kind))), sketch.per_tail > 0))
+    assert {(False, False), (False, True), (True, False)} <= seen
 
 
 def test_short_last_slices_are_where_their_tests_expect_them(plans):
