@@ -151,7 +151,9 @@ int rmm_sketch_static(int64_t n, int64_t d, int64_t k, int dtype, int kind, rmm_
  * skipped, k and state are ignored beyond validation, and no workspace is needed.
  * In bf16 with widths that are multiples of 8, Y of calls that share a launch with the sketch product
  * (those that record RMM_STAGE_FWD_PAIR) is the same bits for any k, kind and scratch.  Elsewhere its last bits, and those of
- * dX below, may differ between calls that differ in these or in whether X_proj is asked for. */
+ * dX below, may differ between calls that differ in these or in whether X_proj is asked for.  The scratch given says into how many
+ * slices of tokens the sketch product may be cut, so that the last bits of X_proj, and of dW below, may differ between calls given more and less
+ * of it; with one size of scratch they are the same in every call. */
 int rmm_forward(const rmm_layer_desc_t *desc, rmm_rng_state_t state, const void *X, const void *W,
                 const void *bias, void *Y, void *X_proj, void *ws, size_t ws_bytes, void *stream);
 
@@ -159,7 +161,8 @@ int rmm_forward(const rmm_layer_desc_t *desc, rmm_rng_state_t state, const void 
  * dX[n x d_in] = dY[n x d_out] W (Eq. 2), dW[d_out x d_in] = (S^T dY)^T X_proj,
  * and, if dbias != NULL, dbias[d_out] = dY^T 1 (Eq. 3).  dX may be NULL to skip
  * the input gradient (first layer of a network).  With dbias the tokens may be cut into other
- * slices, so dW can differ in its last bits from a call without. */
+ * slices, so dW can differ in its last bits from a call without; in bf16 with k <= 64 also a call with dX from one without, whose sketch product
+ * has a kernel of its own. */
 int rmm_backward(const rmm_layer_desc_t *desc, rmm_rng_state_t state, const void *dY, const void *W,
                  const void *X_proj, void *dX, void *dW, void *dbias, void *ws, size_t ws_bytes,
                  void *stream);

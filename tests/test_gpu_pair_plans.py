@@ -146,13 +146,32 @@ def test_bias_gradient_beside_wide_tiles(shape, kind):
 def test_y_has_the_same_bits_beside_any_sketch(n, d, d_other):
     """k, kind and scratch choose how the launch of Y with a sketch product is made up; the bits of Y follow from its sizes."""
     A, W = (synth.to_torch(synth.normal(s, 0x5EED0090 + sum(s), std), "bf16").to("cuda") for s, std in (((n, d), 1.0), ((d_other, d), 0.05)))
-    want = None
+    want, few = None, False
     for kind in (rmm.GAUSSIAN, rmm.RADEMACHER, rmm.SORS):
-        for k in (65, n // 20, n // 10, n // 5, n // 2, 9 * n // 10):
+        for k in (1, 7, 25, 33, 64, 65, n // 20, n // 10, n // 5, n // 2, 9 * n // 10):
             if rmm.rmm_uses_paired_launch(n, d, d_other, k, torch.bfloat16, kind, binding.OP_FORWARD):
                 Y, _ = rmm.rmm_forward(A, W, None, k, kind, 5, 1)
                 want = Y if want is None else want
                 assert torch.equal(Y, want), (kind, k)
+                few |= k <= 64
+    assert few
+
+
+@pytest.mark.parametrize("shape,kind", [((640, 2056, 512, 25), rmm.GAUSSIAN), ((4099, 264, 1032, 33), rmm.RADEMACHER), ((738, 2656, 384, 64), rmm.GAUSSIAN)])
+def test_few_sketch_columns_without_dx_are_made_by_the_streaming_kernel(shape, kind):
+    """(tokens, d_in, d_out, k): dW without dX is the product of what rmm_sketch makes of dY, bit for bit and in any scratch; with dX, whose launch it shares, as
+    close.  (X_proj = 1 where its row and column meet, d_in >= k: dW's columns are G's rows.)"""
+    n, d_in, d_out, k = shape
+    assert rmm.rmm_uses_paired_launch(n, d_in, d_out, k, torch.bfloat16, kind, binding.OP_BACKWARD) and d_in >= k
+    dY = synth.to_torch(synth.normal((n, d_out), 0x5EED00C0), "bf16").to("cuda")
+    W = synth.to_torch(synth.normal((d_out, d_in), 0x5EED00C1, 0.05), "bf16").to("cuda")
+    Xp = torch.zeros((k, d_in), dtype=torch.bfloat16, device="cuda")
+    Xp[range(k), range(k)] = 1
+    G = rmm.rmm_sketch(dY, k, kind, 5, 1)
+    _, alone, _ = rmm.rmm_backward(dY, W, Xp, kind, 5, 1, need_dX=False)
+    assert torch.equal(alone[:, :k], G.t())
+    _, beside, _ = rmm.rmm_backward(dY, W, Xp, kind, 5, 1)
+    assert_close(beside[:, :k], synth.to_f64(G.t()), "dW", "bf16", "few columns beside dX %s" % (shape,))
 
 
 @pytest.mark.parametrize("shape,kind", [((8192, 776, 760, 64), rmm.GAUSSIAN),      # sketch tiles of exactly 64 rows
