@@ -793,6 +793,7 @@ inline int plain_cfg(int elem_bytes, int64_t m, int64_t n, bool two_sums) {
 // 984 -> 1289, k = 262, 231 tiles, 20.3 and 21.3.)
 inline int any_width_tile(int cfg, int64_t m, int64_t n, int64_t kk) {
     if (cfg == PLAIN_TINY || (cfg == PLAIN_MID && (tiles_of(m, n, 64, 64) <= 256 || gemm_tiles(GEMM_FLAT, m, n) > 224))) return -1;
+    if (cfg == PLAIN_MID) return GEMM_FLAT;  // (up to 224 of its tiles, half as many of 128 x 128 are never shorter)
     return gemm_us(GEMM_MID, m, n, kk) <= gemm_us(GEMM_FLAT, m, n, kk) ? GEMM_COMPACT : GEMM_FLAT;
 }
 inline int64_t plain_tiles(int cfg, int64_t m, int64_t n) {

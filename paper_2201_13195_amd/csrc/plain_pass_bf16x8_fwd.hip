@@ -40,8 +40,8 @@ hipError_t launch_forward_pass_bf16x8(const PlainLaunch &p, hipStream_t stream) 
     GemmArgs g{};
     g.A = (const bf16_t *)p.ga.A, g.lda = p.ga.lda, g.B = (const bf16_t *)p.ga.B, g.ldb = p.ga.ldb, g.C = p.ga.C, g.ldc = p.ga.ldc;
     g.bias = (const bf16_t *)p.ga.bias, g.M = p.ga.M, g.N = p.ga.N, g.K = p.ga.K, g.alpha = p.ga.alpha;
-    if (tile == GEMM_COMPACT)
-        return p.sketch_small ? launch_any_width<ShapeCompact, PlainTiny>(p, g, stream) : launch_any_width<ShapeCompact, PlainSketch>(p, g, stream);
+    if (tile == GEMM_COMPACT)  // (in place of 128 x 128 tiles, beside which no sketch tiles are 32 x 32)
+        return p.sketch_small ? hipErrorInvalidValue : launch_any_width<ShapeCompact, PlainSketch>(p, g, stream);
     return p.sketch_small ? launch_any_width<ShapeFlat, PlainTiny>(p, g, stream) : launch_any_width<ShapeFlat, PlainSketch>(p, g, stream);
 }
 

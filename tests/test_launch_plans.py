@@ -61,6 +61,10 @@ void odd_products(int64_t es, int64_t n, int64_t d_in, int64_t d_out, int64_t k,
     *o = plain_cfg((int)es, d_out, d_in, true);
 }
 int any_width(int64_t n, int64_t d, int64_t k, int64_t d_other, int kind) { return any_width_tile(plain_slices(n, d, k, d_other, kind, false).cfg, n, d_other, d); }
+int any_width_small(int64_t n, int64_t d, int64_t k, int64_t d_other, int kind) {
+    const PlainSlices c = plain_slices(n, d, k, d_other, kind, false);
+    return c.slices <= 1 && plain_sketch_small(c.cfg, k, d);
+}
 int f32_tile(int64_t n, int64_t d_in, int64_t d_out, int64_t k, int64_t kind) { return plain_backward_cfg_f32(n, d_in, d_out, k, (int)kind); }
 int sors_order(int64_t n, int64_t d_sk, int64_t d_other, int64_t k) { return plan_sors(n, d_sk, d_other, k).order; }
 int64_t sors_points(int64_t n) { return (int64_t)sors_chunks(n) << (sors_chunks(n) > 1 ? 11 : sors_log(n)); }
@@ -454,6 +458,13 @@ def test_y_of_any_width_takes_the_tiles_that_its_test_names(plans):
     for shape, kind, name in test_gpu_any_width.SHAPES:
         assert tile(*shape, kind) == name, shape
     assert {d_out % 8 for (_, _, d_out, _), _, _ in test_gpu_any_width.SHAPES} == set(range(1, 8))
+    small = {}
+    g = np.random.default_rng(20260503)
+    for _ in range(20000):
+        n, d_in, d_out = (int(x) for x in np.exp(g.uniform(np.log((64, 1, 60)), np.log((20000, 500, 5000)))))
+        shape, kind = (n, 8 * d_in, d_out | 1, max(1, int(g.choice([0.01, 0.05, 0.1, 0.2, 0.5, 0.9]) * n))), int(g.integers(0, 3))
+        small.setdefault(tile(*shape, kind), set()).add(plans.lib.any_width_small(*map(ctypes.c_int64, (n, 8 * d_in, shape[3], d_out | 1)), ctypes.c_int(kind)))
+    assert small["128x128 compact"] == {0} and small["64x128"] == {0, 1}, small           # (there is no kernel of the former beside 32 x 32 sketch tiles)
     for shape in ((1863, 1976, 435, 186), (300, 2000, 101, 30), (700, 300, 901, 70)):     # a round of 64 x 64 tiles, and 32 x 32
         assert tile(*shape, rmm.GAUSSIAN) is None, shape
 
