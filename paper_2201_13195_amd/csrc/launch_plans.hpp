@@ -295,7 +295,7 @@ inline double makespan(int64_t first, double t1, int64_t second, double t2, int6
 // us of a work-group of either product of a paired launch, what share of that (`full`) all of them take longer on a full chip, and how many run at a
 // time.  Plans are compared by the hundred for every size that is new, so those are not walked through whose work, shared evenly by all slots, or one of whose
 // work-groups takes as long as the best plan so far (workspace queries of both directions of 768 <-> 3072 at 3600 to 8000 tokens, four plans: 30 us when all
-// were walked through, 9 now, 4 of them without the second look; k = 32 16 and 7).
+// were walked through, 10 now, 4 of them without the second look; k = 32 16 and 8).
 struct PairTimes {
     double plain, sketch, full_plain, full_sketch;
     int64_t slots;
@@ -361,8 +361,8 @@ struct PassPlan {
 };
 
 // us of a pass by times of the tiles as they are: work-groups as in pair_us, and the sum of the slices.  The fuller the chip, the longer all of them
-// take (`full`: power, and lines from L2).  What a round more or less would change is taken at plain tiles of 0.9 and of 1.1 of their time, so that
-// no plan is taken for a round that it may just miss.  Fitted to 135000 launches of 446 passes with kSecondLookProducts and more (all sketch tiles, 64 to 512
+// take (`full`: power, and lines from L2).  What a round more or less would change is taken at plain tiles of 0.9 and of 1.1 of their time
+// (`plain_times`), so that no plan is taken for a round that it may just miss.  Fitted to 135000 launches of 446 passes with kSecondLookProducts and more (all sketch tiles, 64 to 512
 // work-groups of them, either order).
 inline PairTimes pass_times(const PassPlan &p, int64_t kk, int kind) {
     struct Times {
@@ -382,13 +382,13 @@ inline PairTimes pass_times(const PassPlan &p, int64_t kk, int kind) {
     return PairTimes{ta, tb, a.full, b.full, two ? 512 : 256};
 }
 inline double pass_sum_us(const SketchPlan &p, double partial_mb) { return p.splits > 1 ? 1.2 + 0.304 * (double)p.splits * partial_mb : 0.0; }
-inline double pass_us(const PassPlan &p, int64_t kk, int kind, double partial_mb) {
+inline double pass_us(const PassPlan &p, int64_t kk, int kind, double partial_mb, std::initializer_list<double> plain_times = {0.89, 1.11}) {
     const PairTimes us = pass_times(p, kk, kind);
     const int64_t tiles = p.plain.tiles, shares = p.sketch.shares();
     double longest = 0.0;
-    for (double f : {0.89, 1.11})
-        longest += 0.5 * (p.sketch_first ? makespan(shares, us.sketch, tiles, f * us.plain, us.slots) : makespan(tiles, f * us.plain, shares, us.sketch, us.slots));
-    return longest + us.full(tiles, shares) + pass_sum_us(p.sketch, partial_mb);
+    for (double f : plain_times)
+        longest += p.sketch_first ? makespan(shares, us.sketch, tiles, f * us.plain, us.slots) : makespan(tiles, f * us.plain, shares, us.sketch, us.slots);
+    return longest / (double)plain_times.size() + us.full(tiles, shares) + pass_sum_us(p.sketch, partial_mb);
 }
 
 // The plain product of a pass (n x m outputs) beside a sketch product on one work-group per compute unit: 256 x 256 tiles where it
@@ -541,8 +541,12 @@ inline bool small_pass_is_paired(int64_t n, int64_t d_sk, int64_t d_other, int64
 // tile.  At headline size dX on 96 tiles of 128 x 256 beside 112 sketch work-groups of 64 x 384, a compute unit each, takes the place
 // of 192 tiles of 128 x 128 two by two with 168 of 64 x 256: a step that two work-groups of a compute unit share takes them 0.8 us, and some
 // units have one, some two (a step 81.8 -> 73.4 us; 4096 x 3072 -> 768, k = 2048, Rademacher, two micro-batches: 303 -> 266).
-// Only for what the model calls 9 % or more: 530 random passes that it was not fitted to take 0.960 of the time on average, 0.72 to 1.06 but for
-// one of 1.21 (1180 x 2232 -> 2328, k = 1062, Rademacher, forward: 28 -> 34 us), five of them more than 1.03; for 6 % they are 0.955, with 3 % of them.  Of more than 8192 tokens 134 others are 0.99 on average and 7 of
+// Only for what the model calls 9 % or more, and 7 % with plain tiles of 1.2 of their time: on a full chip these slow down more than sketch
+// work-groups do, and plans whose rounds of them just end with the sketch are not as short as the model has them.  Nor 256 x 256 tiles behind an
+// unsliced sketch product that go over a round, which a chain of two or three such tiles ends (100 of them 0.80 to 1.26 of the time, a fifth above
+// 1.025; 3078 x 928 -> 2960, k = 2631, forward: 51 -> 64 us).  It gives other plans to 45 % of the passes of these sizes: 421 of them were 0.895 of the time on
+// average without these two rules, 18 above 1.025 and five above 1.1 (1180 x 2232 -> 2328, k = 1062, Rademacher, forward: 31 -> 35 us); 600 fresh ones are 0.894 with
+// them, 18 above 1.025 and two above 1.1, 1.114 at most.  Of more than 8192 tokens 134 others are 0.99 on average and 7 of
 // them 1.04 to 1.16: long launches, which slow the clock in a way that it does not know.  Below 6e9 products, 6 us of the matrix pipes, a pass is
 // made up as much of launches, first loads and sums, and first_plan is 1 to 3 % behind the best plan.
 constexpr double kSecondLookProducts = 6e9;
@@ -551,6 +555,7 @@ inline PassPlan second_plan(const PassPlan &best, SketchCuts &cuts, int64_t n, i
     const double partial_mb = (double)k * (double)d_sk * 4e-6;
     PassPlan now = best;
     double now_us = 0.91 * pass_us(best, d_sk, kind, partial_mb);
+    const double slow_us = 0.93 * pass_us(best, d_sk, kind, partial_mb, {1.2});
     struct Cut {
         SketchPlan plan;
         double longest, work, more;  // of one of its work-groups; shared evenly by all compute units; what a full chip and the sum of the slices add
@@ -584,9 +589,10 @@ inline PassPlan second_plan(const PassPlan &best, SketchCuts &cuts, int64_t n, i
                 if (least + plain_more + c.more >= 1.0001 * now_us) continue;
                 p.sketch = c.plan;
                 for (bool first : {false, true}) {
+                    if (first && plain_cfg == GEMM_LARGE && c.plan.splits == 1 && plain.tiles + c.plan.shares() > 256) continue;  // (a chain of large tiles)
                     p.sketch_first = first;
                     const double all = pass_us(p, d_sk, kind, partial_mb);
-                    if (all < now_us) now = p, now_us = all;
+                    if (all < now_us && pass_us(p, d_sk, kind, partial_mb, {1.2}) < slow_us) now = p, now_us = all;
                 }
             }
         }

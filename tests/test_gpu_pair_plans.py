@@ -115,7 +115,7 @@ def test_every_pairing_of_tiles(shape, kind, plain, sketch):
 # dX on 128 x 256 tiles with the column sums of dY in its launch, behind the plain tiles or behind sketch work-groups in front of them, with and without short last
 # slices: (tokens, d_in, d_out, k), kind.  (test_launch_plans.py: they take these.)
 WIDE_WITH_BIAS = [((1340, 2864, 2192, 1206), rmm.RADEMACHER), ((1238, 4016, 3768, 247), rmm.GAUSSIAN), ((2486, 1672, 1824, 248), rmm.RADEMACHER),
-                  ((1904, 2168, 1704, 952), rmm.GAUSSIAN), ((2582, 4072, 792, 1291), rmm.GAUSSIAN), ((2575, 3600, 784, 2317), rmm.RADEMACHER),
+                  ((1904, 2168, 1704, 952), rmm.GAUSSIAN), ((2582, 4072, 792, 1291), rmm.GAUSSIAN), ((2050, 3088, 1216, 1845), rmm.RADEMACHER),
                   ((2693, 1776, 1832, 134), rmm.GAUSSIAN), ((3364, 1120, 2016, 168), rmm.RADEMACHER)]
 
 
