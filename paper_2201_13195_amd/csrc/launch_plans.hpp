@@ -516,9 +516,12 @@ Value remembered(const Sizes &s, Make make) {
 // its slices (0.4 us each), and beside the product's tiles the padding costs less than that.  Taken where the fitted time of the pair is 5 % less
 // than that of the two.  Over 1510 passes that were timed both ways (40 to 250000 tokens, widths 64 to 4096, k = 1 to 64) it takes 0.86 of the
 // time on average, as the better of the two each time does (forward 4224 x 848 -> 560, k = 64: 27.2 -> 16.0 us; 738 x 384 -> 2656: 13.3 ->
-// 8.7), and in 9 of them more than 1.025, 1.07 at most; 1440 others 0.85, 20 of them more than 1.025, 1.19 at most (dY of 51799 x 1984 with dX 144
-// wide, k = 11: 83 -> 99).  Without the 5 TB/s 1.34 at most (3982 x 3760 -> 200, k = 13: 29.9 -> 40.1); always in
-// pairs: up to 1.8 where few rows meet long contractions, for which gemm_cfg has tiles that a pair has not.
+// 8.7), and in 9 of them more than 1.025, 1.07 at most.  Without the 5 TB/s 1.34 at most (3982 x 3760 -> 200, k = 13: 29.9 -> 40.1); always in
+// pairs: up to 1.8 where few rows meet long contractions, for which gemm_cfg has tiles that a pair has not.  Work-groups that are not all resident at once
+// do not read the same of A at the same time: a pair of more than a round is no shorter than A twice at 3.6 TB/s (750 others, most of them long operands beside
+// few columns of Y or dX: 0.829 of the time and 25 above 1.025 without that, 1.18 at most (dY of 51799 x 1984 with dX 144 wide, k = 11: 84 -> 98 us); 0.833
+// and 7 with it, 1.10 at most; 500 fresh ones of all sizes 0.806, 9 above 1.025, three of them above 1.1: 1286 x 1328 -> 640, k = 1, forward 14.0 -> 17.4, 25203 x
+// 2656 -> 808, k = 3, 152 -> 173, dX of 182443 x 1224 with dX 384 wide, k = 1, 303 -> 335).  Asked of the plan that the second look below starts from: it takes another one only where that is much shorter.
 struct SmallPass {
     bool paired;
     PassPlan first;  // of the Gaussian kind, which answers for either
@@ -532,7 +535,10 @@ inline SmallPass small_pass(int64_t n, int64_t d_sk, int64_t d_other, int64_t k)
         const int64_t room = most_slices_of_pass(n, d_sk, k, kMostSlices);
         SketchCuts cuts(n, d_sk, k, 0, room);
         const PassPlan pass = first_plan(cuts, n, d_sk, d_other, k, 0, false, sketch_alone(n, d_sk, k, 0, false, room));
-        return SmallPass{pair_us(pass.plain, d_sk, pass.sketch, 0, (double)k * (double)d_sk * 4e-6) * 1.05 + 0.5 < apart, pass};
+        double pair = pair_us(pass.plain, d_sk, pass.sketch, 0, (double)k * (double)d_sk * 4e-6);
+        const double twice = 2.0 * (double)n * (double)d_sk * 2e-6 / 3.6;
+        if (pass.plain.tiles + pass.sketch.shares() > (pass.plain.cfg == GEMM_COMPACT ? 512 : 256) && pair < twice) pair = twice;
+        return SmallPass{pair * 1.05 + 0.5 < apart, pass};
     });
 }
 inline bool small_pass_is_paired(int64_t n, int64_t d_sk, int64_t d_other, int64_t k) { return k <= kSmallK && small_pass(n, d_sk, d_other, k).paired; }

@@ -315,6 +315,10 @@ def test_few_sketch_columns_run_in_the_scratch_of_the_streaming_kernel(plans):
 
     # a sketch of few work-groups beside a short product; one row of tiles and a long contraction; more columns
     assert asked(4224, 848, 560, 64)[0] and asked(512, 1024, 4096, 25)[0] and asked(8192, 768, 768, 64)[0]
+    # long operands beside few columns, read twice at different times; all work-groups resident at once
+    for shape in ((51799, 1984, 144, 11), (29881, 3760, 136, 1), (29751, 3040, 184, 17), (60705, 1648, 96, 18)):
+        assert not asked(*shape)[0], shape
+    assert asked(40041, 3216, 128, 51)[0] and asked(33978, 3216, 72, 7)[0]
     assert not asked(64, 4096, 512, 3)[0] and not asked(128, 3072, 768, 12)[0] and not asked(15360, 2048, 512, 65)[0]
     g, paired = np.random.default_rng(20260401), 0
     for _ in range(4000):
