@@ -798,11 +798,10 @@ inline int plain_cfg(int elem_bytes, int64_t m, int64_t n, bool two_sums) {
     const double times = elem_bytes == 4 ? (two_sums ? 2.6 : 4.0) : two_sums ? 4.0 : 2.8;
     return times * (double)((big + 255) / 256) <= (double)((mid + 255) / 256) ? PLAIN_BIG : PLAIN_MID;
 }
-// Tile of Y where X and W have rows on 16 bytes and Y has not: GEMM_COMPACT or GEMM_FLAT, which load straight into LDS and add in one order, in place
-// of the 128 x 128 tile (`cfg`) and of 64 x 64 ones beyond a round of them; -1: that of `cfg`.  (Y with its sketch, 3000 x 768 -> 1001, k = 300:
-// 25.3 -> 22.2 us; 1340 x 1080 -> 1217, k = 134, Rademacher, 16.1 -> 12.0; Y alone 12.8 -> 10.0.  Within a round their chain is longer: 1863 x 1976 ->
-// 435 Y alone, 210 tiles of 64 x 64 or 120 of 64 x 128, 12.8 and 15.8.  With most of a round of them the sketch tiles find no places beside them: 1308 x
-// 984 -> 1289, k = 262, 231 tiles, 20.3 and 21.3.)
+// Tile of Y alone where X and W have rows on 16 bytes and Y has not: GEMM_COMPACT or GEMM_FLAT, which load straight into LDS and add in one order, in place
+// of the 128 x 128 tile (`cfg`) and of 64 x 64 ones beyond a round of them; -1: that of `cfg`.  (3000 x 768 -> 1001 12.8 -> 10.0 us; 149 products of up to 4096
+// tokens 0.878 of the time, three above 1.025, 1.06 at most.  Within a round their chain is longer: 1863 x 1976 -> 435, 210 tiles of 64 x 64 or 120 of 64 x 128, 12.8
+// and 15.8.)
 inline int any_width_tile(int cfg, int64_t m, int64_t n, int64_t kk) {
     if (cfg == PLAIN_TINY || (cfg == PLAIN_MID && (tiles_of(m, n, 64, 64) <= 256 || gemm_tiles(GEMM_FLAT, m, n) > 224))) return -1;
     if (cfg == PLAIN_MID) return GEMM_FLAT;  // (up to 224 of its tiles, half as many of 128 x 128 are never shorter)
@@ -843,12 +842,13 @@ inline bool rows_on_16(int64_t row) { return row % 8 == 0; }  // bf16
 
 // Token slices of a bf16 pass's sketch product: `slices` runs of `chunk` tokens, their fp32 sums `stride` elements apart in
 // scratch.  One slice: no scratch.  `ld`: row length of the result and of the sums (0: as wide as the operand).  `cfg`: tile of
-// the plain product of the pass (-1: none), which the sketch product's own tile depends on; the two take the same ones
+// the plain product of the pass (-1: none), which the sketch product's own tile depends on; the two take the same ones, `tile` included,
 // launched one by one.
 struct PlainSlices {
     int slices;
     int64_t chunk, stride, ld;
     int cfg;
+    int tile = -1;  // (Y with rows that start anywhere: the tile of mfma_kernels.hpp in place of that of `cfg`, -1: none)
 };
 
 // Token slices of the sketch product of a bf16 pass (sketch of an n x d operand, beside a product n x d_other).  An entry is
@@ -888,7 +888,7 @@ inline PlainSlices plain_slices_beside(int cfg, int64_t n, int64_t d, int64_t k,
 // work-groups: 22.4 and 20.7 us), the Gaussian kind, whose sketch tiles are longest by far, is not; nor are passes whose
 // sketch product would lose more than half of its slices beside them (9 passes 1.01 to 1.49: 3495 x 400 -> 799, k = 174, four slices and
 // one: 17.9 and 26.7 us).
-inline PlainSlices plain_slices(int64_t n, int64_t d, int64_t k, int64_t d_other, int kind, bool backward, int64_t most = 16) {
+inline PlainSlices plain_slices_on(int64_t n, int64_t d, int64_t k, int64_t d_other, int kind, bool backward, int64_t most = 16) {
     const PlainSlices cut = plain_slices_beside(plain_cfg(2, n, d_other, backward), n, d, k, d_other, kind, most);
     if (backward || kind != RMM_SKETCH_RADEMACHER || cut.cfg != PLAIN_BIG) return cut;
     const int64_t plain = plain_tiles(PLAIN_BIG, n, d_other), all = plain + tiles_of(k, d, 32, 128) * cut.slices;
@@ -896,6 +896,30 @@ inline PlainSlices plain_slices(int64_t n, int64_t d, int64_t k, int64_t d_other
     if (!short_round || plain_tiles(PLAIN_MID, n, d_other) > 768) return cut;
     const PlainSlices mid = plain_slices_beside(PLAIN_MID, n, d, k, d_other, kind, most);
     return 2 * mid.slices >= cut.slices ? mid : cut;
+}
+
+// The tile of Y beside a sketch product, rows of X and W on 16 bytes (as any_width_tile, which has Y alone).  In place of 128 x 128 tiles GEMM_COMPACT: 150 passes 0.945 of
+// the time, 9 above 1.025 (with GEMM_FLAT where that alone is shorter 0.965 and 23).  In place of 64 x 64 ones GEMM_FLAT where with the sketch tiles each
+// work-group has a compute unit to itself (72 passes: 0.87, none above 1.025), or where 64 x 64 tiles and sketch tiles go over two on each and no sketch tile takes
+// 1.5 times as long as Y (`tile_ns` a token, as below; 70 passes 0.865, three above 1.025).  Elsewhere both have their places at once and last as long
+// as the sketch tiles: 157 passes 0.997, 54 of them above 1.025, 1.15 at most (3688 x 2576 -> 277, k = 184, Rademacher, 28.4 -> 32.8 us).  500 fresh
+// passes that one of these tiles is meant for: 0.938, 19 above 1.025, six of them above 1.1, 1.14 at most (1119 x 3168 -> 1857, k = 111, Rademacher, 35.1 ->
+// 40.0: 128 x 128 tiles and sketch tiles one to nearly every compute unit, where GEMM_COMPACT has none beside it to fill its waits).
+// Y with its sketch, 3000 x 768 -> 1001, k = 300: 25.3 -> 22.2 us; 1340 x 1080 -> 1217, k = 134, Rademacher, 16.1 -> 12.0.
+inline int any_width_tile_beside(const PlainSlices &cut, int64_t n, int64_t d, int64_t k, int64_t d_other, int kind) {
+    const int tile = any_width_tile(cut.cfg, n, d_other, d);
+    if (tile < 0 || cut.cfg == PLAIN_BIG) return tile < 0 ? -1 : GEMM_COMPACT;
+    const bool small = cut.slices <= 1 && plain_sketch_small(cut.cfg, k, d);
+    const int64_t sketch = tiles_of(k, d, 32, small ? 32 : 128) * cut.slices;
+    if (gemm_tiles(GEMM_FLAT, n, d_other) + sketch <= 256) return GEMM_FLAT;
+    const double tile_ns = small ? (kind == 0 ? 9e-3 : 4.8e-3) : kind == 0 ? 15e-3 : 9e-3;
+    const bool longest = tile_ns * (double)cut.chunk >= 1.5 * gemm_us(GEMM_FLAT, n, d_other, d);
+    return plain_tiles(PLAIN_MID, n, d_other) + sketch > 512 && !longest ? GEMM_FLAT : -1;
+}
+inline PlainSlices plain_slices(int64_t n, int64_t d, int64_t k, int64_t d_other, int kind, bool backward, int64_t most = 16) {
+    PlainSlices cut = plain_slices_on(n, d, k, d_other, kind, backward, most);
+    if (!backward) cut.tile = any_width_tile_beside(cut, n, d, k, d_other, kind);
+    return cut;
 }
 
 }  // namespace rmm

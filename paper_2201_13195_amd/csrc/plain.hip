@@ -131,6 +131,7 @@ hipError_t launch_forward_plain(const T *X, const T *W, const T *bias, T *Y, T *
         p.ga.M = n, p.ga.N = d_out, p.ga.K = d_in, p.ga.alpha = 1.0f;
     }
     if (X_proj != nullptr) p.gs = sketch_args<T>(X, X_proj, n, d_in, k, kind, st, cut, ws);
+    p.tile = cut.cfg >= 0 ? cut.tile : any_width_tile(plain_cfg(sizeof(T), n, d_out, false), n, d_out, d_in);  // (without a sketch product in the pass: Y alone)
     const hipError_t e = launch_pass<T>(p, Y != nullptr, X_proj != nullptr, false, load_mode(sizeof(T), d_in, d_in), cut.cfg, stream);
     return e != hipSuccess || cut.slices <= 1 || X_proj == nullptr ? e : finish_slices<T>(p.gs, X_proj, stream);
 }

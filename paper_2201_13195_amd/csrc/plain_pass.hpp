@@ -11,6 +11,7 @@ struct PlainLaunch {
     ColsumArgs gc;
     int plain_blocks, sketch_blocks, colsum_blocks;
     int cfg;            // tile shape of the plain product
+    int tile;           // the one of mfma_kernels.hpp in its place (launch_forward_pass_bf16x8), -1: none
     bool sketch_small;  // the 32 x 32 tile for the sketch product (never with PLAIN_BIG)
 };
 

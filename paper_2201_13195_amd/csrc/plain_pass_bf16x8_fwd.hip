@@ -35,7 +35,7 @@ hipError_t launch_any_width(const PlainLaunch &p, const GemmArgs &g, hipStream_t
 }  // namespace
 
 hipError_t launch_forward_pass_bf16x8(const PlainLaunch &p, hipStream_t stream) {
-    const int tile = p.plain_blocks > 0 ? any_width_tile(p.cfg, p.ga.M, p.ga.N, p.ga.K) : -1;
+    const int tile = p.plain_blocks > 0 ? p.tile : -1;
     if (tile < 0) return launch_plain_pass_rows<bf16_t, 4, 4, PB_K>(p, stream);
     GemmArgs g{};
     g.A = (const bf16_t *)p.ga.A, g.lda = p.ga.lda, g.B = (const bf16_t *)p.ga.B, g.ldb = p.ga.ldb, g.C = p.ga.C, g.ldc = p.ga.ldc;

@@ -60,7 +60,8 @@ void odd_products(int64_t es, int64_t n, int64_t d_in, int64_t d_out, int64_t k,
     }
     *o = plain_cfg((int)es, d_out, d_in, true);
 }
-int any_width(int64_t n, int64_t d, int64_t k, int64_t d_other, int kind) { return any_width_tile(plain_slices(n, d, k, d_other, kind, false).cfg, n, d_other, d); }
+int any_width(int64_t n, int64_t d, int64_t k, int64_t d_other, int kind) { return plain_slices(n, d, k, d_other, kind, false).tile; }
+int any_width_alone(int64_t n, int64_t d, int64_t d_other) { return any_width_tile(plain_cfg(2, n, d_other, false), n, d_other, d); }
 int any_width_small(int64_t n, int64_t d, int64_t k, int64_t d_other, int kind) {
     const PlainSlices c = plain_slices(n, d, k, d_other, kind, false);
     return c.slices <= 1 && plain_sketch_small(c.cfg, k, d);
@@ -464,6 +465,12 @@ def test_y_of_any_width_takes_the_tiles_that_its_test_names(plans):
     for shape, kind, name in test_gpu_any_width.SHAPES:
         assert tile(*shape, kind) == name, shape
     assert {d_out % 8 for (_, _, d_out, _), _, _ in test_gpu_any_width.SHAPES} == set(range(1, 8))
+    # alone the next larger tile, beside the sketch product 64 x 64 ones: as long as the sketch tiles, and all resident at once
+    for shape, kind in (((3688, 2576, 277, 184), rmm.RADEMACHER), ((455, 520, 2525, 227), rmm.GAUSSIAN), ((2814, 328, 385, 281), rmm.RADEMACHER), ((351, 2440, 2695, 35), rmm.SORS)):
+        n, d_in, d_out, k = shape
+        assert tile(*shape, kind) is None and plans.lib.any_width_alone(*map(ctypes.c_int64, (n, d_in, d_out))) == TILES.index("64x128"), shape
+    for shape, kind in (((1795, 736, 3249, 179), rmm.RADEMACHER), ((1835, 512, 2903, 917), rmm.RADEMACHER)):      # 64 x 128 alone, and slower beside sketch tiles
+        assert tile(*shape, kind) == "128x128 compact", shape
     small = {}
     g = np.random.default_rng(20260503)
     for _ in range(20000):
