@@ -40,7 +40,8 @@ bool use_mfma(const rmm_layer_desc_t *d) {
 //   sketch / forward: fp32 partial sums of the token slices of S^T A.
 //   backward: G = S^T dY (k x d_out, in the layer's dtype), then the partial sums.
 // fp32 has no token slices.  Nor has, off the MFMA path, rmm_sketch and the forward pass over an X whose width is no multiple of 8.
-// A pass takes the slices that its workspace has room for, down to two on the MFMA path and down to one off it: it has run in
+// A pass takes the slices that its workspace has room for, down to two on the MFMA path (of at most kSmallK columns: down to what
+// the streaming kernel takes) and down to one off it: it has run in
 // less scratch than it asks for now, and callers may have kept that size.
 // (bf16: rows of G start on 16 bytes, where there is room)
 struct GRows {

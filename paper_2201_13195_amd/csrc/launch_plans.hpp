@@ -40,8 +40,8 @@ inline int row_norm_blocks(int64_t n) {
     return (int)(b < 1024 ? b : 1024);
 }
 
-// The plain product of a paired launch: its tile (GEMM_LARGE, GEMM_MID or, with SK_NARROW64, GEMM_COMPACT; dX: see dx_cfg) and
-// number of tiles.
+// The plain product of a paired launch: its tile (GEMM_LARGE, GEMM_WIDE, GEMM_MID or, with SK_NARROW64, GEMM_COMPACT; dX: see dx_cfg)
+// and number of tiles.
 struct PairPlain {
     int cfg, tiles;
 };
@@ -76,8 +76,8 @@ inline double tile_us(const TileTime &t, int64_t tiles, int64_t kk, bool filled)
 }
 
 // Tile of a plain product with an m x n output and contraction kk.  32 x 32 tiles whose contraction is shared by eight
-// waves (few_tile) only while there are at most 512 of them.  256 x 256 tiles from 160 of them on whatever the model
-// says: they need half the bytes per flop of 128 x 128 tiles, which a full chip cannot bring into its LDS at MFMA rate.  And from 130 on
+// waves (few_tile) only while there are at most 512 of them.  256 x 256 tiles from 160 of them on whatever the model here
+// says (a product alone in its launch is looked at again: gemm_cfg): they need half the bytes per flop of 128 x 128 tiles, which a full chip cannot bring into its LDS at MFMA rate.  And from 130 on
 // where 128 x 128 tiles, with the `beside` other work-groups of the launch, go over two rounds (36 products from 516 to 660 of those:
 // 0.73 to 1.02 of the time, 0.84 on average; with 455 to 510 of them 0.88 to 1.31).  (Times of the menu, and these 36 products, are from before
 // the tiles' loops went through their LDS stages, which made 128 x 128 tiles faster, dX alone by 22 %, than 256 x 256 ones, 6 %.)
@@ -132,7 +132,7 @@ inline int gemm_cfg(int64_t m, int64_t n, int64_t kk, int64_t beside = 0) {
     if (beside > 0) return first;
     int best = first;
     double best_us = 0.96 * gemm_us(first, m, n, kk) - 0.5;
-    if (best_us < 4.2) return first;  // (no tile is below)
+    if (best_us < 4.2) return first;  // (no tile takes less than 4.13: nothing to gain)
     for (int cfg = gemm_tiles(GEMM_LARGE, m, n) >= 130 ? GEMM_LARGE : GEMM_WIDE; cfg <= GEMM_FEW; ++cfg) {
         if (cfg == GEMM_FEW && gemm_tiles(GEMM_FEW, m, n) > 512) continue;
         const double us = gemm_us(cfg, m, n, kk);
@@ -160,7 +160,7 @@ inline int xty_sumsq_tiles(int64_t n, int64_t d_in, int64_t d_out, int64_t room 
     return (int)gemm_tiles(xty_cfg(d_in, d_out, n, room), d_in, d_out);
 }
 
-// Which kernel serves a sketch product with k > 64 and how its token dimension is cut.  The work-group
+// Which kernel serves a sketch product (with k > kSmallK, or fewer columns in a paired launch) and how its token dimension is cut.  The work-group
 // generates the sketch tile into LDS and all eight waves read it.
 struct SketchPlan {
     int cfg;

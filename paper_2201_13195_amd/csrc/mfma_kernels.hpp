@@ -13,7 +13,7 @@
 //   gemm_tile       Y, dX, dW and X^T dY on tiles from 64 x 64 to 256 x 256: memory straight into LDS, two to four
 //                   stages of 64 contraction elements
 //   few_tile        products with very few output tiles: the waves of a work-group share the contraction, no barriers
-//   sketch_tile     sketch products with k > 64, in the same kind of pipeline.  The sketch operand is never in
+//   sketch_tile     sketch products with k > 64, and smaller ones in a paired launch, in the same kind of pipeline.  The sketch operand is never in
 //                   memory: the work-group generates its tile of P^T into LDS (one 16-byte chunk = 8 consecutive
 //                   tokens of one sketch column = one Philox-4x32-10 call for the Gaussian kind, one byte of a
 //                   call's 128 sign bits for the Rademacher kind).  The 1/sqrt(k) of S = P/sqrt(k) is applied to

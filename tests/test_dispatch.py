@@ -18,6 +18,6 @@ def test_column_sums_go_where_there_is_room(pair_takes_colsum, kind):
     # dW fills the chip (256 tiles): beside the sketch work-groups, which leave room for them
     for n, d_in, d_out, k in ((16384, 1024, 4096, 1638), (32768, 1024, 4096, 1638), (16384, 4096, 1024, 1638)):
         assert pair_takes_colsum(n, d_in, d_out, k, kind), (n, d_in, d_out, k)
-    # dW leaves most of it idle; no paired launch (k at most 64)
+    # dW leaves most of it idle; the paired launch has no place left (k = 64)
     for n, d_in, d_out, k in ((4096, 768, 3072, 410), (4096, 768, 768, 410), (16384, 1024, 4096, 64)):
         assert not pair_takes_colsum(n, d_in, d_out, k, kind), (n, d_in, d_out, k)

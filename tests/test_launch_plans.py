@@ -28,6 +28,7 @@ SOURCE = """
 using namespace rmm;
 extern "C" {
 int plain_tile(int64_t m, int64_t n, int64_t kk) { return gemm_cfg(m, n, kk); }
+int gemm_ns(int cfg, int64_t m, int64_t n, int64_t kk) { return (int)(1e3 * gemm_us(cfg, m, n, kk)); }
 int variance_tile(int64_t n, int64_t d_in, int64_t d_out) { return xty_cfg(d_in, d_out, n); }
 static void put(const SketchPlan &p, int64_t *o) { o[0] = p.cfg, o[1] = p.slices, o[2] = p.per_tail, o[3] = p.splits, o[4] = p.tiles, o[5] = p.shares(); }
 void sketch_plan(int64_t n, int64_t d, int64_t k, int kind, int64_t *o) { put(plan_sketch(n, d, k, kind, true), o); }
@@ -447,6 +448,12 @@ def test_strips_do_not_share_compute_units_with_rounds_of_tiles_that_wider_ones_
         assert order(*shape) != "compact", shape
     for shape in ((17354, 936, 600, 1408), (25112, 1888, 480, 1711), (31504, 504, 1568, 448), (20373, 512, 352, 884)):
         assert order(*shape) == "compact", shape
+
+
+def test_no_product_is_below_where_the_second_look_begins(plans):
+    """4.13 us are the least of any tile: below 4.2 there is nothing that it could take."""
+    least = min(plans.lib.gemm_ns(ctypes.c_int(cfg), *map(ctypes.c_int64, (m, n, kk))) for cfg in range(7) for m, n in ((1, 1), (64, 64), (500, 500)) for kk in (1, 17, 64, 65))
+    assert 4130 <= least <= 4140, least
 
 
 def test_products_are_looked_at_again_where_that_is_clear(plans):
