@@ -546,7 +546,8 @@ inline bool small_pass_is_paired(int64_t n, int64_t d_sk, int64_t d_other, int64
 // A second look at large passes, by pass_us: 256 x 256 tiles also where they do not fill the chip, 128 x 256 tiles, and either order, with any sketch
 // tile.  At headline size dX on 96 tiles of 128 x 256 beside 112 sketch work-groups of 64 x 384, a compute unit each, takes the place
 // of 192 tiles of 128 x 128 two by two with 168 of 64 x 256: a step that two work-groups of a compute unit share takes them 0.8 us, and some
-// units have one, some two (a step 81.8 -> 73.4 us; 4096 x 3072 -> 768, k = 2048, Rademacher, two micro-batches: 303 -> 266).
+// units have one, some two (a step 84.3 -> 75.8 us; 4096 x 3072 -> 768, k = 2048, Rademacher, two micro-batches: 310 -> 280; by box 1.09 to 1.11 and 1.085
+// to 1.11 times as fast).
 // Only for what the model calls 9 % or more, and 7 % with plain tiles of 1.2 of their time: on a full chip these slow down more than sketch
 // work-groups do, and plans whose rounds of them just end with the sketch are not as short as the model has them.  Nor 256 x 256 tiles behind an
 // unsliced sketch product that go over a round, which a chain of two or three such tiles ends (100 of them 0.80 to 1.26 of the time, a fifth above
