@@ -39,3 +39,23 @@ def test_y_of_any_width(shape, kind, tile):
         assert torch.equal(alone[0], Y) and torch.equal(alone[1], Xp)
         only, _ = rmm.rmm_forward(Xd, Wd, bd if with_bias else None, k, kind, 0, 0, need_xproj=False)
         assert_close(only, oY, "Y", "bf16", "%s %s alone" % (tile, shape))
+
+
+# beside a sketch product on 64 x 64 tiles, or on another tile than alone (test_launch_plans.py)
+BESIDE = [((455, 520, 2525, 227), rmm.GAUSSIAN), ((351, 2440, 2695, 35), rmm.SORS), ((1835, 512, 2903, 917), rmm.RADEMACHER)]
+
+
+@pytest.mark.parametrize("shape,kind", BESIDE)
+def test_y_keeps_its_tile_when_the_products_of_a_pass_are_launched_one_by_one(shape, kind):
+    n, d_in, d_out, k = shape
+    X, W = (synth.to_torch(synth.normal(s, 0x5EED00A8 + sum(s), std), "bf16") for s, std in (((n, d_in), 1.0), ((d_out, d_in), 1.0 / math.sqrt(d_in))))
+    oY, oXp = o_rmm.forward(synth.to_f64(X), synth.to_f64(W), None, k, kind, 0x5EED00A9, 15)
+    Xd, Wd = X.to("cuda"), W.to("cuda")
+    a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    a.record(); b.record()
+    Y, Xp = rmm.rmm_forward(Xd, Wd, None, k, kind, 0x5EED00A9, 15)
+    only, _ = rmm.rmm_forward(Xd, Wd, None, k, kind, 0, 0, need_xproj=False)
+    for got, want, name in ((Y, oY, "Y"), (only, oY, "Y"), (Xp, oXp, "X_proj")):
+        assert_close(got, want, name, "bf16", "beside %s" % (shape,))
+    alone = rmm.rmm_forward(Xd, Wd, None, k, kind, 0x5EED00A9, 15, profile=(binding.STAGE_FWD_Y, a, b))
+    assert torch.equal(alone[0], Y) and torch.equal(alone[1], Xp)

@@ -472,6 +472,8 @@ def test_y_of_any_width_takes_the_tiles_that_its_test_names(plans):
     for shape, kind, name in test_gpu_any_width.SHAPES:
         assert tile(*shape, kind) == name, shape
     assert {d_out % 8 for (_, _, d_out, _), _, _ in test_gpu_any_width.SHAPES} == set(range(1, 8))
+    for (n, d_in, d_out, k), kind in test_gpu_any_width.BESIDE:
+        assert tile(n, d_in, d_out, k, kind) != TILES[plans.lib.any_width_alone(*map(ctypes.c_int64, (n, d_in, d_out)))], (n, d_in, d_out)
     # alone the next larger tile, beside the sketch product 64 x 64 ones: as long as the sketch tiles, and all resident at once
     for shape, kind in (((3688, 2576, 277, 184), rmm.RADEMACHER), ((455, 520, 2525, 227), rmm.GAUSSIAN), ((2814, 328, 385, 281), rmm.RADEMACHER), ((351, 2440, 2695, 35), rmm.SORS)):
         n, d_in, d_out, k = shape
