@@ -42,7 +42,7 @@ def test_y_of_any_width(shape, kind, tile):
 
 
 # beside a sketch product on 64 x 64 tiles, or on another tile than alone (test_launch_plans.py)
-BESIDE = [((455, 520, 2525, 227), rmm.GAUSSIAN), ((351, 2440, 2695, 35), rmm.SORS), ((1835, 512, 2903, 917), rmm.RADEMACHER)]
+BESIDE = [((1200, 264, 1043, 300), rmm.GAUSSIAN), ((455, 520, 2525, 227), rmm.GAUSSIAN), ((351, 2440, 2695, 35), rmm.SORS), ((1835, 512, 2903, 917), rmm.RADEMACHER)]
 
 
 @pytest.mark.parametrize("shape,kind", BESIDE)
